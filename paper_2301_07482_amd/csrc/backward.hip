@@ -151,110 +151,230 @@ __global__ __launch_bounds__(BW_THREADS) void relu_backward_kernel(const char* _
 // GCN: the transpose of the propagation (h_r + sum of the neighbours) / (deg + 1): dx has d_in columns, and
 //   out[j, :] = [j computed] dx[j, :] / (deg(j) + 1)  +  sum over the computed rows r that sampled j of dx[r, :] / (deg(r) + 1)
 // (a row found in a transposed list sampled at least one neighbour, so it is computed exactly when deg(r) > 0).
-// one source position j by a group of `lanes` lanes (this lane: `lane`); s0 .. e0 is its range of the transposed block
+// What bounds it: every output row sits behind a chain of dependent index reads (transposed range -> row -> its degree ->
+// the row's gradient), and most rows have one to three incoming edges. The lanes of a group therefore read the rows and
+// degrees of up to `lanes` edges side by side, once per row, and hand them round by shuffles; the pieces a lane holds and
+// two edges each are then in flight together, from addresses that always exist (a slot with nothing to read takes row 0
+// of dx and is dropped by a select: rows that were not computed hold anything). Measured per layer call (with the matrix
+// product in front), against one walk of the whole chain per piece and one wavefront per hub: 6.1 k rows -> 66 k positions of
+// 256 columns, at most 13 edges each: 47 us (58); the same with hubs of 76: 47 (96); 26 k positions of 88 columns, hubs of
+// 84: 23 (51); 14 k positions of 128 columns, hubs of 639: 41 (648); 7 k positions of 1024 columns: 38 (45).
+struct BwAgg {
+    const char* dx;
+    int64_t dx_stride;
+    int n, nb_byte, pieces;      // rows of dx; first byte of the neighbours' share of a row
+    const uint8_t* live;
+    const uint8_t* hit;
+    const int32_t* row_start;
+    const int32_t* row_end;
+    const int32_t* t_start;
+    const int32_t* t_end;
+    const int32_t* t_row;
+    int64_t nnz;
+    int n_src;
+    char* out;
+    int64_t out_stride;
+    float* norms;
+};
+
+// edge t of the transposed block: its row (0 where there is nothing to add) and what the row's gradient is multiplied with
 template <bool GCN>
-__device__ __forceinline__ void aggregate_backward_row(
-    const int64_t j, const int32_t s0, const int32_t e0, const int lane, const int lanes, const char* __restrict__ dx, int n, int d_in,
-    const uint8_t* __restrict__ live, const uint8_t* __restrict__ hit, const int32_t* __restrict__ row_start,
-    const int32_t* __restrict__ row_end, const int32_t* __restrict__ t_row, char* __restrict__ out, int64_t out_stride,
-    float* __restrict__ norms) {
-    const int pieces = d_in >> 2;
-    const int64_t dx_stride = (int64_t)(GCN ? 1 : 2) * d_in * 4;
-    const int nb_col = GCN ? 0 : d_in;      // first column of the neighbours' share in a row of dx
-    const bool own = j < n && (live ? live[j] != 0 : true) && (hit ? hit[j] == 0 : true);
-    double own_w = 1.0;
+__device__ __forceinline__ void bw_edge(const BwAgg& A, int t, bool there, int32_t& r, double& w) {
+    r = there ? A.t_row[t] : -1;
+    const bool ok = r >= 0 && r < A.n;
+    r = ok ? r : 0;
+    const int32_t deg = ok ? A.row_end[r] - A.row_start[r] : 0;
+    w = deg > 0 ? 1.0 / (double)(GCN ? deg + 1 : deg) : 0.0;
+}
+
+// whether position j was computed, and the weight of its own gradient
+template <bool GCN>
+__device__ __forceinline__ bool bw_own(const BwAgg& A, int64_t j, double& w) {
+    const bool own = j < A.n && (A.live ? A.live[j] != 0 : true) && (A.hit ? A.hit[j] == 0 : true);
+    w = own ? 1.0 : 0.0;
     if (GCN && own) {
-        const int32_t deg = row_end[j] - row_start[j];
-        own_w = 1.0 / (double)((deg > 0 ? deg : 0) + 1);
+        const int32_t deg = A.row_end[j] - A.row_start[j];
+        w = 1.0 / (double)((deg > 0 ? deg : 0) + 1);
     }
-    double ss = 0.0;  // this lane's share of the row's sum of squares (of the fp32 values written)
-    for (int piece = lane; piece < pieces; piece += lanes) {
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        if (own) {
-            const f32x4 v = *(const f32x4*)(dx + j * dx_stride + (int64_t)piece * 16);
-            acc[0] = (double)v.x * own_w; acc[1] = (double)v.y * own_w; acc[2] = (double)v.z * own_w; acc[3] = (double)v.w * own_w;
-        }
-        for (int t = s0; t < e0; t += 4) {
-            f32x4 v[4];
-            double w[4];
+    return own;
+}
+
+__device__ __forceinline__ void bw_add(double* acc, const f32x4 v, const double w) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                w[u] = 0.0;
-                v[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-                if (t + u < e0) {
-                    const int32_t r = t_row[t + u];
-                    if (r >= 0 && r < n) {
-                        const int32_t deg = row_end[r] - row_start[r];
-                        if (deg > 0) {
-                            w[u] = 1.0 / (double)(GCN ? deg + 1 : deg);
-                            v[u] = *(const f32x4*)(dx + (int64_t)r * dx_stride + (int64_t)(nb_col + 4 * piece) * 4);
-                        }
-                    }
+    for (int e = 0; e < 4; ++e) acc[e] += w > 0.0 ? (double)v[e] * w : 0.0;
+}
+
+constexpr int BW_MANY = 16;   // incoming edges from which on a position is taken by a whole workgroup
+
+// position j by a group of `lanes` lanes (this lane: `lane`); s0 .. e0 is its range of the transposed block
+// PU: 16-byte pieces of the row a lane holds at a time
+template <bool GCN, int PU>
+__device__ __forceinline__ void aggregate_backward_row(const BwAgg& A, const int64_t j, const int32_t s0, const int32_t e0,
+                                                       const int lane, const int lanes) {
+    double own_w;
+    const bool own = bw_own<GCN>(A, j, own_w);
+    double ss = 0.0;  // this lane's share of the row's sum of squares (of the fp32 values written)
+    for (int p0 = 0; p0 < A.pieces; p0 += lanes * PU) {
+        double acc[PU][4];
+        int64_t off[PU];
+#pragma unroll
+        for (int q = 0; q < PU; ++q) {
+            const int piece = p0 + q * lanes + lane;
+            off[q] = piece < A.pieces ? (int64_t)piece * 16 : 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[q][e] = 0.0;
+        }
+        if (own) {
+            f32x4 v[PU];
+#pragma unroll
+            for (int q = 0; q < PU; ++q) v[q] = *(const f32x4*)(A.dx + j * A.dx_stride + off[q]);
+#pragma unroll
+            for (int q = 0; q < PU; ++q) bw_add(acc[q], v[q], own_w);
+        }
+        for (int c = s0; c < e0; c += lanes) {
+            const int m = e0 - c < lanes ? e0 - c : lanes;
+            int32_t r;
+            double w;
+            bw_edge<GCN>(A, c + lane, lane < m, r, w);
+            for (int u = 0; u < m; u += 2) {     // uniform over the group
+                const int u1 = u + 1 < m ? u + 1 : u;
+                const int32_t r0 = __shfl(r, u, lanes), r1 = __shfl(r, u1, lanes);
+                const double w0 = __shfl(w, u, lanes);
+                double w1 = __shfl(w, u1, lanes);
+                if (u1 == u) w1 = 0.0;
+                const char* b0 = A.dx + (int64_t)r0 * A.dx_stride + A.nb_byte;
+                const char* b1 = A.dx + (int64_t)r1 * A.dx_stride + A.nb_byte;
+                f32x4 v0[PU], v1[PU];
+#pragma unroll
+                for (int q = 0; q < PU; ++q) {
+                    v0[q] = *(const f32x4*)(b0 + off[q]);
+                    v1[q] = *(const f32x4*)(b1 + off[q]);
+                }
+#pragma unroll
+                for (int q = 0; q < PU; ++q) {
+                    bw_add(acc[q], v0[q], w0);
+                    bw_add(acc[q], v1[q], w1);
                 }
             }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                acc[0] += (double)v[u].x * w[u];
-                acc[1] += (double)v[u].y * w[u];
-                acc[2] += (double)v[u].z * w[u];
-                acc[3] += (double)v[u].w * w[u];
-            }
         }
-        const f32x4 o = {(float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]};
-        *(f32x4*)(out + j * out_stride + (int64_t)piece * 16) = o;
-        ss += (double)o.x * o.x + (double)o.y * o.y + (double)o.z * o.z + (double)o.w * o.w;
+#pragma unroll
+        for (int q = 0; q < PU; ++q) {
+            if (p0 + q * lanes + lane >= A.pieces) continue;
+            const f32x4 o = {(float)acc[q][0], (float)acc[q][1], (float)acc[q][2], (float)acc[q][3]};
+            *(f32x4*)(A.out + j * A.out_stride + off[q]) = o;
+            ss += (double)o.x * o.x + (double)o.y * o.y + (double)o.z * o.z + (double)o.w * o.w;
+        }
     }
-    if (norms) {  // the lanes of a group are neighbours in one wavefront and leave the loop together
+    if (A.norms) {  // the lanes of a group are neighbours in one wavefront and leave the loop together
         for (int off = lanes >> 1; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
-        if (lane == 0) norms[j] = (float)sqrt(ss);
+        if (lane == 0) A.norms[j] = (float)sqrt(ss);
     }
 }
 
-// Groups of 2^lanes_log2 lanes take the source positions in turn. Where a group is smaller than a wavefront (several rows,
-// several chains of index reads, per wavefront: what a layer with many rows wants), a position with more than `many`
-// incoming edges is left out of that sweep and taken by a whole wavefront in a second one (by other workgroups of the same
-// launch): a small group walks the edge list
-// once per piece it holds, which for the hubs of a power-law graph was the whole launch (measured: 166 us against 84 us
-// with one row per wavefront on the workload with average degree 50). Every position is written by exactly one group.
+// A position with many incoming edges by a whole workgroup: its wavefronts take blocks of 64 edges in turn and, where a row
+// has fewer than 64 pieces, the sub-groups of a wavefront take the block's edges in turn; the partial sums meet by
+// shuffles and in LDS, in a fixed order.
 template <bool GCN>
-__global__ __launch_bounds__(BW_THREADS) void aggregate_backward_kernel(
-    const char* __restrict__ dx, int n, int d_in, const uint8_t* __restrict__ live, const uint8_t* __restrict__ hit,
-    const int32_t* __restrict__ row_start, const int32_t* __restrict__ row_end, const int32_t* __restrict__ t_start,
-    const int32_t* __restrict__ t_end, const int32_t* __restrict__ t_row, int64_t nnz, int n_src, char* __restrict__ out,
-    int64_t out_stride, int lanes_log2, float* __restrict__ norms, int many, int sweep2_blocks) {
-    const int lanes = 1 << lanes_log2;
-    const int lane = threadIdx.x & (lanes - 1);
-    const int gpb = BW_THREADS >> lanes_log2;
-    const bool two_sweeps = lanes < 64;
-    if ((int)blockIdx.x < sweep2_blocks) {
-        // second sweep, by workgroups of its own at the front of the grid (the long rows start first): a wavefront looks
-        // at 64 positions at once (one coalesced read of their ranges) and takes those with many incoming edges one after the
-        // other, all 64 lanes on each
-        const int wl = threadIdx.x & 63;
-        const int64_t n_waves = (int64_t)sweep2_blocks * (BW_THREADS >> 6);
-        for (int64_t j0 = ((int64_t)blockIdx.x * (BW_THREADS >> 6) + (threadIdx.x >> 6)) * 64; j0 < n_src; j0 += n_waves * 64) {
+__device__ __forceinline__ void aggregate_backward_hub(const BwAgg& A, const int64_t j, const int32_t s0, const int32_t e0,
+                                                       double (*part)[64 * 4]) {
+    constexpr int WAVES = BW_THREADS / 64;
+    const int wl = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int hl = 1;
+    while (hl < A.pieces && hl < 64) hl <<= 1;
+    const int lane = wl & (hl - 1), sub = wl / hl, subs = 64 / hl;
+    double own_w;
+    const bool own = bw_own<GCN>(A, j, own_w);
+    double ss = 0.0;
+    for (int p0 = 0; p0 < A.pieces; p0 += hl) {      // the trip count is uniform over the workgroup
+        const int piece = p0 + lane;
+        const int64_t off = piece < A.pieces ? (int64_t)piece * 16 : 0;
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int c = s0 + wave * 64; c < e0; c += WAVES * 64) {
+            const int m = e0 - c < 64 ? e0 - c : 64;
+            int32_t r;
+            double w;
+            bw_edge<GCN>(A, c + wl, wl < m, r, w);
+            constexpr int EB = 8;      // edges in flight per sub-group
+            for (int u0 = 0; u0 < m; u0 += EB * subs) {      // uniform over the wavefront; a slot past m has weight 0
+                f32x4 v[EB];
+                double we[EB];
+#pragma unroll
+                for (int q = 0; q < EB; ++q) {
+                    const int u = u0 + q * subs + sub;
+                    const int32_t re = __shfl(r, u < m ? u : 0, 64);
+                    we[q] = __shfl(w, u < m ? u : 0, 64);
+                    if (u >= m) we[q] = 0.0;
+                    v[q] = *(const f32x4*)(A.dx + (int64_t)re * A.dx_stride + A.nb_byte + off);
+                }
+#pragma unroll
+                for (int q = 0; q < EB; ++q) bw_add(acc, v[q], we[q]);
+            }
+        }
+        for (int o = hl; o < 64; o <<= 1)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
+        if (sub == 0)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[wave][lane * 4 + e] = acc[e];
+        __syncthreads();
+        if (wave == 0 && sub == 0 && piece < A.pieces) {
+            double sum[4] = {0.0, 0.0, 0.0, 0.0};
+            if (own) bw_add(sum, *(const f32x4*)(A.dx + j * A.dx_stride + off), own_w);
+#pragma unroll
+            for (int v = 0; v < WAVES; ++v)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[e] += part[v][lane * 4 + e];
+            const f32x4 o = {(float)sum[0], (float)sum[1], (float)sum[2], (float)sum[3]};
+            *(f32x4*)(A.out + j * A.out_stride + off) = o;
+            ss += (double)o.x * o.x + (double)o.y * o.y + (double)o.z * o.z + (double)o.w * o.w;
+        }
+        __syncthreads();      // the partial sums are read
+    }
+    if (A.norms && wave == 0) {
+        ss = wave_sum(ss);
+        if (wl == 0) A.norms[j] = (float)sqrt(ss);
+    }
+}
+
+// Groups of 2^lanes_log2 lanes take the source positions in turn, except those with more than BW_MANY incoming edges: the
+// first hub_blocks workgroups look at 64 positions each, spread over the whole layer (the hubs of a power-law graph are
+// drawn early and lie together at its front), and take such a position with all their wavefronts. Every position is
+// written by exactly one group.
+template <bool GCN, int PU>
+__global__ __launch_bounds__(BW_THREADS) void aggregate_backward_kernel(BwAgg A, int lanes_log2, int hub_blocks) {
+    __shared__ double part[BW_THREADS / 64][64 * 4];
+    __shared__ unsigned long long s_big;
+    __shared__ int32_t s_range[2][64];
+    auto range_of = [&](int64_t j, int32_t& s, int32_t& e) {
+        s = A.t_start[j];
+        e = A.t_end[j];
+        if (s < 0 || e < s || (int64_t)e > A.nnz) s = e = 0;
+    };
+    if ((int)blockIdx.x < hub_blocks) {
+        if (threadIdx.x < 64) {
+            const int64_t j = (int64_t)threadIdx.x * hub_blocks + blockIdx.x;
             int32_t s = 0, e = 0;
-            if (j0 + wl < n_src) {
-                s = t_start[j0 + wl];
-                e = t_end[j0 + wl];
-                if (s < 0 || e < s || (int64_t)e > nnz) s = e = 0;
-            }
-            unsigned long long big = __ballot(e - s > many);
-            while (big) {      // uniform over the wavefront
-                const int b = __ffsll((long long)big) - 1;
-                big &= big - 1;
-                const int32_t s0 = __shfl(s, b, 64), e0 = __shfl(e, b, 64);
-                aggregate_backward_row<GCN>(j0 + b, s0, e0, wl, 64, dx, n, d_in, live, hit, row_start, row_end, t_row, out, out_stride, norms);
-            }
+            if (j < A.n_src) range_of(j, s, e);
+            s_range[0][threadIdx.x] = s;
+            s_range[1][threadIdx.x] = e;
+            const unsigned long long big = __ballot(e - s > BW_MANY);
+            if (threadIdx.x == 0) s_big = big;
+        }
+        __syncthreads();
+        for (unsigned long long big = s_big; big; big &= big - 1) {      // uniform over the workgroup
+            const int b = __ffsll((long long)big) - 1;
+            aggregate_backward_hub<GCN>(A, (int64_t)b * hub_blocks + blockIdx.x, s_range[0][b], s_range[1][b], part);
         }
         return;
     }
-    const int64_t block = (int64_t)blockIdx.x - sweep2_blocks, n_blocks = (int64_t)gridDim.x - sweep2_blocks;
-    for (int64_t j = block * gpb + (threadIdx.x >> lanes_log2); j < n_src; j += n_blocks * gpb) {
-        int32_t s0 = t_start[j], e0 = t_end[j];
-        if (s0 < 0 || e0 < s0 || (int64_t)e0 > nnz) s0 = e0 = 0;
-        if (two_sweeps && e0 - s0 > many) continue;
-        aggregate_backward_row<GCN>(j, s0, e0, lane, lanes, dx, n, d_in, live, hit, row_start, row_end, t_row, out, out_stride, norms);
+    const int lanes = 1 << lanes_log2;
+    const int gpb = BW_THREADS >> lanes_log2;
+    const int64_t block = (int64_t)blockIdx.x - hub_blocks, n_blocks = (int64_t)gridDim.x - hub_blocks;
+    for (int64_t j = block * gpb + (threadIdx.x >> lanes_log2); j < A.n_src; j += n_blocks * gpb) {
+        int32_t s0, e0;
+        range_of(j, s0, e0);
+        if (e0 - s0 > BW_MANY) continue;
+        aggregate_backward_row<GCN, PU>(A, j, s0, e0, threadIdx.x & (lanes - 1), lanes);
     }
 }
 
@@ -399,26 +519,34 @@ static fg_status_t layer_backward_launch(const char* who, int kind, const float*
     }
     if (n_src == 0) return FG_OK;
     const int pieces = d_in / 4;
-    // lanes per source row: a wavefront's rows each wait on their own chain of index reads, so a layer with many rows gets
-    // four rows per wavefront (16 lanes, each walking several 16-byte pieces); measured on 54 k rows of 1 KB: 34 -> 25 us,
-    // on 6 k rows: slower than one row per wavefront
-    const int lg_cap = n_src >= 16384 ? 4 : 6;
+    // Lanes per source row: up to 16 for rows of at most 64 pieces (four rows, four index chains, per wavefront; a lane holds
+    // up to four pieces), a whole wavefront for wider ones. Measured per call of the whole layer's backward pass: 256 columns,
+    // 6.1 k rows: 20.3 us against 22.7 with one row per wavefront (66 k rows: 47); 1024 columns, 7 k rows: 38.5.
+    const int lg_cap = pieces <= 64 ? 4 : 6;
     int lg = 0;
     while ((1 << lg) < pieces && lg < lg_cap) ++lg;
     const int gpb = BW_THREADS >> lg;
     int64_t blocks = fg_ceil_div(n_src, gpb);
     if (blocks > 256 * 16) blocks = 256 * 16;
-    // with groups smaller than a wavefront: workgroups of their own for the positions with many incoming edges (one pass of
-    // 64 positions per wavefront)
-    const int sweep2 = lg < 6 ? (int)fg_ceil_div(n_src, 64 * (BW_THREADS / 64)) : 0;
-    if (gcn)
-        hipLaunchKernelGGL(aggregate_backward_kernel<true>, dim3((unsigned)(blocks + sweep2)), dim3(BW_THREADS), 0, st, (const char*)dx, n, d_in,
-                           live_dev, hit_dev, row_start_dev, row_end_dev, t_start_dev, t_end_dev, t_row_dev, nnz, n_src, (char*)dh_src_dev,
-                           dh_src_stride, lg, norms_src_dev, 16, sweep2);
+    const int hub_blocks = nnz > BW_MANY ? (int)fg_ceil_div(n_src, 64) : 0;
+    const BwAgg A = {(const char*)dx, (int64_t)cols * 4, n, gcn ? 0 : d_in * 4, pieces, live_dev, hit_dev, row_start_dev, row_end_dev,
+                     t_start_dev, t_end_dev, t_row_dev, nnz, n_src, (char*)dh_src_dev, dh_src_stride, norms_src_dev};
+    const dim3 agrid((unsigned)(blocks + hub_blocks));
+    const int pu = (int)fg_ceil_div(pieces, 1 << lg);
+#define FG_AGG_BW(P)                                                                                                           \
+    do {                                                                                                                       \
+        if (gcn)                                                                                                               \
+            hipLaunchKernelGGL((aggregate_backward_kernel<true, P>), agrid, dim3(BW_THREADS), 0, st, A, lg, hub_blocks);        \
+        else                                                                                                                   \
+            hipLaunchKernelGGL((aggregate_backward_kernel<false, P>), agrid, dim3(BW_THREADS), 0, st, A, lg, hub_blocks);       \
+    } while (0)
+    if (pu <= 1)
+        FG_AGG_BW(1);
+    else if (pu <= 2)
+        FG_AGG_BW(2);
     else
-        hipLaunchKernelGGL(aggregate_backward_kernel<false>, dim3((unsigned)(blocks + sweep2)), dim3(BW_THREADS), 0, st, (const char*)dx, n, d_in,
-                           live_dev, hit_dev, row_start_dev, row_end_dev, t_start_dev, t_end_dev, t_row_dev, nnz, n_src, (char*)dh_src_dev,
-                           dh_src_stride, lg, norms_src_dev, 16, sweep2);
+        FG_AGG_BW(4);
+#undef FG_AGG_BW
     FG_LAUNCH_CHECK("aggregate_backward_kernel");
     return FG_OK;
 }

@@ -941,6 +941,59 @@ def test_layer_backward_matches_oracle(env, d_in, d_out, n, n_src, max_deg, relu
     assert (np.abs(want).sum(axis=1) == 0).sum() == (np.abs(got).sum(axis=1) == 0).sum()
 
 
+@pytest.mark.parametrize("kind,d_in,d_out", [("sage", 4, 8), ("sage", 88, 16), ("gcn", 68, 16), ("sage", 256, 64), ("sage", 260, 8), ("gcn", 1024, 8)])
+def test_layer_backward_with_hubs_matches_oracle(env, kind, d_in, d_out):
+    """Positions on both sides of the number of incoming edges from which a whole workgroup takes one, and of its blocks of
+    edges: no edge, 16, 17, 64, 65, 256, 257 and every row, next to each other and far apart; widths of one piece up to rows of
+    several passes."""
+    torch, B = env
+    from fg_inputs.sampler import transpose_block
+    r = np.random.default_rng(d_in)
+    n, n_src = 700, 1500
+    want_deg = {0: 0, 1: n, 2: 257, 3: 17, 4: 16, 700: 256, 701: 65, 702: 64, n_src - 1: 300}
+    cols = [[] for _ in range(n)]
+    for pos, k in want_deg.items():
+        for row in r.choice(n, size=k, replace=False):
+            cols[row].append(pos)
+    rest = np.setdiff1d(np.arange(n_src), list(want_deg))
+    for row in range(n):
+        cols[row].extend(r.choice(rest, size=3, replace=False).tolist())
+    deg = np.asarray([len(c) for c in cols])
+    start = np.concatenate([[0], np.cumsum(deg)[:-1]]).astype(np.int32)
+    end, col = (start + deg).astype(np.int32), np.concatenate(cols).astype(np.int32)
+    ts, te, tr = transpose_block(start, end, col, n_src)
+    assert te[1] - ts[1] == n and te[3] - ts[3] == 17
+    hit = r.random(n) < 0.1
+    rows = np.flatnonzero(~hit).astype(np.int32)
+    end_pruned = np.where(hit, start, end).astype(np.int32)
+    dh = r.standard_normal((n, d_out)).astype(np.float32)
+    h = np.maximum(r.standard_normal((n, d_out)), 0).astype(np.float32)
+    k_w = d_in if kind == "gcn" else 2 * d_in
+    W = (r.standard_normal((k_w, d_out)) / np.sqrt(k_w)).astype(np.float32)
+    dummy = np.zeros((len(rows), d_in))
+    if kind == "gcn":
+        want = O.layer_backward_gcn(start, end_pruned, col, rows, dh, h, dummy, W, n_src, relu=True)[0]
+    else:
+        want = O.layer_backward(start, end_pruned, col, rows, dh, h, dummy, dummy, W, n_src, relu=True)[0]
+    cnt = dev(torch, np.asarray([len(rows)], dtype=np.int64))
+    out = torch.full((n_src, d_in), 7.0, dtype=torch.float32, device="cuda")
+    wsb = B.fg_layer_backward_workspace_bytes(n, n, d_in, d_out, kind=kind)
+    ws = torch.full((wsb,), 0xFF, dtype=torch.uint8, device="cuda")      # NaN wherever nothing was computed
+    norms = torch.full((n_src,), -1.0, dtype=torch.float32, device="cuda")
+    rows_dev = torch.zeros(n, dtype=torch.int32, device="cuda")
+    rows_dev[:len(rows)] = dev(torch, rows)
+    B.fg_layer_backward(dev(torch, dh), d_out * 4, dev(torch, h), d_out * 4, n, rows_dev, cnt, n, None, dev(torch, hit.astype(np.uint8)),
+                        dev(torch, start), dev(torch, end_pruned), dev(torch, ts), dev(torch, te), dev(torch, tr), len(tr), n_src, d_in,
+                        d_out, dev(torch, W), out, d_in * 4, norms, ws, wsb, kind=kind)
+    got = out.cpu().numpy()
+    np.testing.assert_allclose(norms.cpu().numpy(), O.row_norms(got).astype(np.float32), rtol=5e-7, atol=1e-37)
+    # The narrow products sum 8 to 64 terms of about 1 per element, and a hub up to 700 of them with random signs, each rounded
+    # to fp32 once: its error is far below 2^-24 times the sum of magnitudes
+    scale = np.abs(dh).max() * np.abs(W).sum(axis=1).max()
+    tol = np.maximum(REL_TOL_F32 * np.maximum(np.abs(want), np.abs(want).max(axis=1, keepdims=True) / 16), 4 * 2.0 ** -24 * scale)
+    assert (np.abs(got - want) <= tol).all(), np.abs(got - want).max()
+
+
 @pytest.mark.parametrize("variant", [0, 32])
 @pytest.mark.parametrize("d_in,d_out,n,n_rows,relu,seed", [(128, 256, 5000, 4100, True, 0), (256, 256, 700, 700, True, 1),
                                                          (64, 64, 300, 250, False, 2), (24, 72, 130, 77, True, 3),
