@@ -633,11 +633,14 @@ class HotPath:
             # run there, each as soon as its dH exists, beside the rest of the backward chain and the cache update.
             wg_beside = self.weight_grads and self.overlap_update and timer is None
 
+            # (both streams are named in every call: making the second one torch's current stream and asking for the current
+            # one costs about 20 us of host time per layer, more than the launches it is for)
+            side_st = self.side.cuda_stream if wg_beside else None
+
             def weight_grads_beside(l):
-                self.ev_bw[l].record(torch.cuda.current_stream())
-                with torch.cuda.stream(self.side):
-                    self.side.wait_event(self.ev_bw[l])
-                    weight_grads(l, self.side.cuda_stream)
+                self.ev_bw[l].record(main)
+                self.side.wait_event(self.ev_bw[l])
+                weight_grads(l, side_st)
 
             tick("loss_grad")
             B.fg_softmax_xent_grad(self.H[L], self.dims[L] * 4, bt.labels, bt.n[L], self.dims[L], self.dH[L], self.dims[L] * 4, st)
@@ -682,7 +685,7 @@ class HotPath:
                                   self.p_grad, self.H[l], out_b, self.stats.data_ptr() + l * 32, self.ws, self.ws_bytes, st)
         if self.backward and self.weight_grads and self.overlap_update and timer is None:
             self.ev_bw[0].record(self.side)       # the next iteration overwrites what the weight gradients read
-            torch.cuda.current_stream().wait_event(self.ev_bw[0])
+            main.wait_event(self.ev_bw[0])
         tick(None)
 
     def holds_second_stream(self):
