@@ -11,8 +11,8 @@
 // touches the previous owner's map entry, a check-out only writes the node's own map entry, and the slots
 // handed out in one update are distinct. The result is therefore the same as the sequential procedure.
 //
-// Update = 5 launches for any number of layers (a workgroup finds its layer from its index), no host
-// synchronisation and no waiting between workgroups:
+// Update = 5 launches for any number of layers (a workgroup finds its layer from its index), or 2 where all of them are
+// small (update_one_kernel does the first four), no host synchronisation and no waiting between workgroups:
 //   1. digit 0       histogram of the top 11 bits of the order-preserving integer image of the live nodes' norms
 //   2. digit 1       every workgroup derives m, k = floor(p_grad*m) and the first digit of the norm of rank k from
 //                    the finished histogram, then histograms the next 11 bits of its keys that carry that digit
@@ -118,6 +118,18 @@ struct UpdBatch {
     int32_t scan_first[FG_MAX_UPD_LAYERS + 1];  // the same for launches 3 and 4
     UpdLayer l[FG_MAX_UPD_LAYERS];
 };
+
+// leaves the number of admitted rows, the advanced ring header and how far the ring has ever been written
+__device__ __forceinline__ void finish_header(const UpdLayer& L, int64_t head, int64_t in) {
+    const CacheRW& c = L.c;
+    L.hdr->n_admit = in;
+    *c.head_next = (head + in) % c.capacity;
+    const int64_t reach = head + in;  // the ring fills slots upwards until it first wraps
+    if (reach >= c.capacity)
+        *c.used = c.capacity;
+    else if (reach > *c.used)
+        *c.used = reach;
+}
 
 __device__ __forceinline__ int layer_of_block(const int32_t* first, int n_layers, int b, int& local) {
     int l = 0;
@@ -334,6 +346,243 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void classify_update_kernel(UpdBatch
     }
 }
 
+// ---- launches 1 to 4 as one: a whole layer by one workgroup -------------------------------------------------------------------
+//
+// What bounds the four launches on a small layer is not their work but their chain: each is a few dependent reads, barriers
+// and scans long (6 + 9 + 13 + 6 us at 1.2 k positions, hardly more at 54 k). A workgroup of 1024 threads holds the keys of up
+// to 8192 positions in registers (four per thread and step), so it reads them once, finds tau by the same three digits in
+// LDS, classifies, ranks the admissible nodes and hands out their slots, with no other workgroup to wait for. The
+// histograms are kept four times (by lane mod 4): norms share their leading digits, and equal bins of a wavefront are
+// added one after the other. Measured, whole update with its row copy of 256 bytes, p_grad 0.4: 1.2 k positions 17 us against 31, 4096: 19
+// (31), 8192: 25 (33; with p_grad 0.9 30 against 34); 12 288: 34 (33) and 16 384: 40 (34), where one compute unit's
+// random accesses to the index are the bound: the four launches from 8193 positions on.
+constexpr int ONE_COPIES = 4;
+constexpr int ONE_MAX_STEPS = 2;      // 8192 positions
+
+__device__ __attribute__((aligned(16))) uint32_t upd_spare[4];      // what is read where a layer has no quad
+
+// Finds the bin holding rank *s_rank among hist[bin * ONE_COPIES + copy], stores it in *s_bin and rebases *s_rank to that bin.
+__device__ __forceinline__ void select_bin_copies(const uint32_t* hist, long long* red, uint32_t* s_bin, long long* s_rank) {
+    static_assert(SEL_BPT == 2 && ONE_COPIES == 4, "two bins of four counters per thread");
+    const int t = threadIdx.x;
+    const uint4 a = ((const uint4*)hist)[2 * t], b = ((const uint4*)hist)[2 * t + 1];
+    const long long c0 = (long long)a.x + a.y + a.z + a.w, c1 = (long long)b.x + b.y + b.z + b.w;
+    long long incl = c0 + c1;
+    for (int off = 1; off < FG_WAVE; off <<= 1) {
+        const long long v = __shfl_up(incl, off, FG_WAVE);
+        if (fg_lane() >= off) incl += v;
+    }
+    if (fg_lane() == FG_WAVE - 1) red[fg_wave()] = incl;
+    __syncthreads();
+    long long lo = incl - c0 - c1;
+    for (int w = 0; w < fg_wave(); ++w) lo += red[w];
+    const long long rank = *s_rank;
+    __syncthreads();      // everybody has read the rank and the wavefronts' totals
+    if (rank >= lo && rank < lo + c0 + c1) {      // true for exactly one thread
+        const bool second = rank >= lo + c0;
+        *s_bin = 2 * t + (second ? 1 : 0);
+        *s_rank = rank - (second ? lo + c0 : lo);
+    }
+    __syncthreads();
+}
+
+template <int STEPS>
+__global__ __launch_bounds__(SEL_THREADS) void update_one_kernel(UpdBatch B) {
+    __shared__ __attribute__((aligned(16))) uint32_t hist[SEL_BINS * ONE_COPIES];
+    __shared__ int wave_count[STEPS][SEL_THREADS / FG_WAVE];
+    __shared__ long long red[16];
+    __shared__ uint32_t s_bin;
+    __shared__ long long s_rank;
+    __shared__ int s_evicted, s_over;
+    const UpdLayer& L = B.l[blockIdx.x];
+    const CacheRW& c = L.c;
+    const int t = threadIdx.x, lane = fg_lane(), wave = fg_wave();
+    const int n = upd_count(L);
+    const int64_t head = *c.head;
+    // Position of element e of step k: 4 * (k * 1024 + t) + e. Every read is unconditional (the first quad, or 16 bytes of the
+    // library's own, where a quad is not wholly there) so that a batch of steps is in flight together; the one quad that the end of the layer
+    // cuts is read one by one by the thread that owns it, and joins below.
+    const int n_quads = n >> 2;
+    const bool cut_mine = (n & 3) != 0 && n_quads % SEL_THREADS == t;
+    const int cut_step = n_quads / SEL_THREADS;
+    uint32_t cut_key[4] = {0, 0, 0, 0}, cut_live = 0, cut_hit = 0;
+    int32_t cut_id[4] = {-1, -1, -1, -1};
+    if (cut_mine)
+        for (int e = 0; e < 3; ++e) {
+            const int j = 4 * n_quads + e;
+            if (j >= n) break;
+            cut_key[e] = order_key(L.gnorm[j]);
+            cut_id[e] = L.ids[j];
+            if (L.live ? L.live[j] != 0 : true) cut_live |= 1u << e;
+            if (L.hit[j] != 0) cut_hit |= 1u << e;
+        }
+    const char* gnorm_base = n_quads > 0 ? (const char*)L.gnorm : (const char*)upd_spare;
+    const char* hit_base = n_quads > 0 ? (const char*)L.hit : (const char*)upd_spare;
+    const char* live_base = n_quads > 0 && L.live ? (const char*)L.live : hit_base;
+    const char* ids_base = n_quads > 0 ? (const char*)L.ids : (const char*)upd_spare;
+    const uint32_t all_live = L.live ? 0u : 0x01010101u;
+    uint32_t key[4 * STEPS];
+    uint32_t is_live = 0, is_hit = 0;      // four bits per step
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) {
+        const int q = k * SEL_THREADS + t;
+        const bool whole = q < n_quads;
+        typedef float f4 __attribute__((ext_vector_type(4)));
+        const uint32_t at = whole ? (uint32_t)q : 0u;
+        const f4 g = *(const f4*)(gnorm_base + 16u * at);
+        const uint32_t l4 = *(const uint32_t*)(live_base + 4u * at) | all_live;
+        const uint32_t h4 = *(const uint32_t*)(hit_base + 4u * at);
+        const bool cut = cut_mine && cut_step == k;
+        uint32_t lb = 0, hb = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            key[4 * k + e] = cut ? cut_key[e] : order_key(g[e]);
+            lb |= ((l4 >> (8 * e)) & 0xFFu) ? 1u << e : 0u;
+            hb |= ((h4 >> (8 * e)) & 0xFFu) ? 1u << e : 0u;
+        }
+        lb = cut ? cut_live : (whole ? lb : 0u);
+        hb = cut ? cut_hit : (whole ? hb : 0u);
+        is_live |= lb << (4 * k);
+        is_hit |= hb << (4 * k);
+    }
+    auto live_bit = [&](int k, int e) { return ((is_live >> (4 * k + e)) & 1u) != 0; };
+    auto hit_bit = [&](int k, int e) { return ((is_hit >> (4 * k + e)) & 1u) != 0; };
+    auto clear_hist = [&]() {
+        for (int b = t; b < SEL_BINS * ONE_COPIES / 4; b += SEL_THREADS) ((uint4*)hist)[b] = uint4{0, 0, 0, 0};
+    };
+    if (t == 0) s_evicted = s_over = 0;
+    clear_hist();
+    const long long m = fg_block_sum((long long)__popc(is_live), red);      // (its barriers also end the clearing)
+    const long long k_rank = (long long)floor((double)L.p_grad * (double)m);
+    const int mode = k_rank <= 0 ? 0 : (k_rank >= m ? 2 : 1);
+    uint32_t tau_key = 0;
+    if (mode == 1) {      // uniform over the workgroup: tau is the key of rank k, found digit by digit (11 + 11 + 10 bits)
+        if (t == 0) s_rank = k_rank;
+#pragma unroll 1
+        for (int pass = 0; pass < 3; ++pass) {
+            const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
+            const uint32_t bins = pass == 2 ? 1023u : 2047u;
+            const uint32_t above = pass == 0 ? 0u : (pass == 1 ? 0xFFE00000u : 0xFFFFFC00u);      // the digits found so far
+            if (pass > 0) {
+                clear_hist();
+                __syncthreads();
+            }
+#pragma unroll
+            for (int k = 0; k < STEPS; ++k) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t x = key[4 * k + e];
+                    if (live_bit(k, e) && (x & above) == tau_key)
+                        atomicAdd(&hist[((x >> shift) & bins) * ONE_COPIES + (lane & (ONE_COPIES - 1))], 1u);
+                }
+            }
+            __syncthreads();
+            select_bin_copies(hist, red, &s_bin, &s_rank);
+            tau_key |= s_bin << shift;
+        }
+    }
+    // check-outs and admissible nodes
+    int32_t id[4 * STEPS];
+    uint32_t admit_bits = 0;      // four bits per step
+    int evicted = 0;
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) {
+        const int j = 4 * (k * SEL_THREADS + t);
+        const bool whole = k * SEL_THREADS + t < n_quads, cut = cut_mine && cut_step == k;
+        int32_t* v = id + 4 * k;
+        const int4 v4 = *(const int4*)(ids_base + (whole ? 4u * (uint32_t)j : 0u));
+        v[0] = cut ? cut_id[0] : v4.x;
+        v[1] = cut ? cut_id[1] : v4.y;
+        v[2] = cut ? cut_id[2] : v4.z;
+        v[3] = cut ? cut_id[3] : v4.w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool low = mode == 2 || (mode == 1 && key[4 * k + e] < tau_key);
+            if (!live_bit(k, e) || v[e] < 0 || v[e] >= c.num_nodes || hit_bit(k, e) == low) continue;
+            if (low) {
+                admit_bits |= 1u << (4 * k + e);
+            } else {
+                c.map[v[e]] = -1;
+                ++evicted;
+            }
+        }
+    }
+    for (int off = FG_WAVE / 2; off > 0; off >>= 1) evicted += __shfl_down(evicted, off, FG_WAVE);
+    if (lane == 0 && evicted) atomicAdd(&s_evicted, evicted);
+    // ranks in position order: steps first, then threads, then a thread's elements
+    int before[STEPS];
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) {
+        const int own = __popc((admit_bits >> (4 * k)) & 15u);
+        int incl = own;
+        for (int off = 1; off < FG_WAVE; off <<= 1) {
+            const int v = __shfl_up(incl, off, FG_WAVE);
+            if (lane >= off) incl += v;
+        }
+        if (lane == FG_WAVE - 1) wave_count[k][wave] = incl;
+        before[k] = incl - own;
+    }
+    __syncthreads();
+    int total = 0;
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) {
+        before[k] += total;
+        for (int w = 0; w < SEL_THREADS / FG_WAVE; ++w) {
+            const int x = wave_count[k][w];
+            if (w < wave) before[k] += x;
+            total += x;
+        }
+    }
+    int over = 0;
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) {
+        const int j = 4 * (k * SEL_THREADS + t);
+        int32_t slot[4], old[4], old_map[4], old_stamp[4];
+        int rank[4];
+        bool in[4];
+        // the four chains slot -> owner -> its map entry side by side (reads of slot 0 / node 0 where there is nothing to do)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            rank[e] = before[k] + __popc((admit_bits >> (4 * k)) & ((1u << e) - 1u));
+            in[e] = ((admit_bits >> (4 * k + e)) & 1u) != 0 && rank[e] < L.room;
+            slot[e] = in[e] ? (int32_t)((head + rank[e]) % c.capacity) : 0;
+            old[e] = c.slot_node[slot[e]];
+            old_stamp[e] = c.slot_stamp[slot[e]];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) old_map[e] = c.map[old[e] >= 0 && old[e] < c.num_nodes ? old[e] : 0];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (!in[e]) continue;
+            if (old[e] >= 0 && old[e] < c.num_nodes && old_map[e] == slot[e]) {
+                const int64_t age = c.iter + 1 - (int64_t)old_stamp[e];
+                over += age >= 1 && age <= (int64_t)c.t_stale ? 1 : 0;
+            }
+            c.slot_node[slot[e]] = id[4 * k + e];
+            c.slot_stamp[slot[e]] = (int32_t)c.iter;
+            c.map[id[4 * k + e]] = slot[e];
+            L.apos[rank[e]] = j + e;
+            L.aslot[rank[e]] = slot[e];
+        }
+    }
+    for (int off = FG_WAVE / 2; off > 0; off >>= 1) over += __shfl_down(over, off, FG_WAVE);
+    if (lane == 0 && over) atomicAdd(&s_over, over);
+    __syncthreads();
+    if (t == 0) {
+        const int64_t in = total < L.room ? total : L.room;
+        L.hdr->mode = mode;
+        L.hdr->tau_key = tau_key;
+        L.hdr->m_live = m;
+        finish_header(L, head, in);
+        if (L.stats) {
+            L.stats[0] = in;
+            L.stats[1] = s_evicted;
+            L.stats[2] = s_over;
+            L.stats[3] = total - in;
+        }
+    }
+}
+
 // Access-aware policy, between classify and assign_slots: with T admissible nodes and room for R < T of them, the R
 // largest estimates get in, equal estimates in position order. Every workgroup finds the threshold estimate a* (rank
 // T - R in ascending order) and how many nodes at a* still fit, then re-flags its nodes: above a* -> 2, at a* -> 1,
@@ -443,13 +692,7 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void assign_slots_kernel(UpdBatch B)
             const long long ties = before + total;
             const long long in = sure_all + (ties < room ? ties : room);
             const long long all = n_cand >= 0 ? n_cand : ties;
-            L.hdr->n_admit = in;
-            *c.head_next = (head + in) % c.capacity;
-            const int64_t reach = head + in;  // the ring fills slots upwards until it first wraps
-            if (reach >= c.capacity)
-                *c.used = c.capacity;
-            else if (reach > *c.used)
-                *c.used = reach;
+            finish_header(L, head, in);
             if (L.stats) {
                 L.stats[0] = in;
                 L.stats[3] = all - in;
@@ -767,7 +1010,25 @@ fg_status_t launch_update(UpdBatch& B, hipStream_t st, bool select = true, bool 
         B.scan_first[i + 1] = B.scan_first[i] + (int)fg_ceil_div(n, FG_SCAN_BLOCK);
     }
     const unsigned n_sel = (unsigned)B.sel_first[B.n_layers], n_scan = (unsigned)B.scan_first[B.n_layers];
-    if (select) {
+    // One workgroup per layer where the layers fit its registers, their arrays can be read four at a time and no layer ranks by
+    // saved accesses (that needs the counts of all its admissible nodes first).
+    int64_t n_most = 0;
+    bool one = true;
+    for (int i = 0; i < B.n_layers; ++i) {
+        const UpdLayer& u = B.l[i];
+        if (u.n > n_most) n_most = u.n;
+        one = one && !u.saving && !(((uintptr_t)u.gnorm | (uintptr_t)u.ids) & 15) && !(((uintptr_t)u.live | (uintptr_t)u.hit) & 3);
+    }
+    const int steps = (int)fg_ceil_div(n_most, 4 * SEL_THREADS);
+    one = one && steps <= ONE_MAX_STEPS;
+    if (select && one) {
+        const dim3 grid((unsigned)B.n_layers), block(SEL_THREADS);
+        if (steps <= 1)
+            hipLaunchKernelGGL(update_one_kernel<1>, grid, block, 0, st, B);
+        else
+            hipLaunchKernelGGL(update_one_kernel<ONE_MAX_STEPS>, grid, block, 0, st, B);
+        FG_LAUNCH_CHECK("update_one_kernel");
+    } else if (select) {
         hipLaunchKernelGGL(update_digit0_kernel, dim3(n_sel), dim3(SEL_THREADS), 0, st, B);
         FG_LAUNCH_CHECK("update_digit0_kernel");
         hipLaunchKernelGGL(update_digit1_kernel, dim3(n_sel), dim3(SEL_THREADS), 0, st, B);

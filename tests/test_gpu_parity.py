@@ -552,6 +552,33 @@ def test_cache_update_sequences_match_oracle(env, cap, t_stale, p, nmax):
         B.fg_cache_destroy(cache)
 
 
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 63, 4095, 4096, 4097, 8187, 8191, 8192, 8193])
+@pytest.mark.parametrize("p", [0.0, 0.37, 1.0])
+def test_cache_update_sizes_around_a_workgroups_share(env, n, p):
+    """Layers on both sides of what one workgroup takes in one and in two steps of four positions a thread, cut quads included;
+    a ring that some of them wrap, two updates in a row (the second overwrites the first's entries and checks hits out)."""
+    torch, B = env
+    r = np.random.default_rng(n)
+    N, cap, d = 20000, 4500, 8
+    oc = O.HistoricalCache(N, cap, d, 5)
+    cache = B.fg_cache_create(N, [cap], [d], B.FG_F32, 5, None)
+    try:
+        for i in range(2):
+            ids = r.permutation(min(N, 2 * n + 8))[:n].astype(np.int32)
+            live = r.random(n) < (0.9 if i else 1.1)
+            gn = np.round(np.exp(r.standard_normal(n)), 2).astype(np.float32)      # ties occur
+            rows = r.standard_normal((n, d)).astype(np.float32)
+            look = O.lookup_prune(oc, i, ids, live, None, None, None, 0)
+            _, _, stats = _device_update(torch, B, cache, i, ids, live, gn, p, rows, misalign=False)
+            st = O.cache_update(oc, i, ids, live, look["hit"], gn, p, rows)
+            assert stats == [st["admitted"], st["evicted_by_gradient"], st["overwritten"], st["dropped_overflow"]]
+            exp = _export(torch, B, cache, cap, i + 1)
+            assert exp["head"] == oc.head
+            assert dict(zip(exp["nodes"].tolist(), zip(exp["slots"].tolist(), exp["stamps"].tolist()))) == oc.valid_entries(i + 1)
+    finally:
+        B.fg_cache_destroy(cache)
+
+
 def _export(torch, B, cache, cap, it, layer=1):
     t = [torch.zeros(cap, dtype=torch.int32, device="cuda") for _ in range(3)]
     cnt = torch.zeros(2, dtype=torch.int64, device="cuda")
