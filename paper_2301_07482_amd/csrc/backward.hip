@@ -398,7 +398,7 @@ BwWs bw_layout(int64_t n, int64_t max_rows, int64_t cols, int64_t d_out, int64_t
 fg_status_t fg_launch_linear_bf16(const void* h_src, int32_t n_src, int64_t src_stride, fg_dtype_t in_dtype, const void* agg,
                                   int64_t agg_stride, const int32_t* rows_dev, const int64_t* n_rows_dev, int64_t max_rows,
                                   int32_t d_in, int32_t d_out, const void* W, const float* bias, int32_t relu, void* h_out,
-                                  int32_t n_out, int64_t out_stride, fg_dtype_t out_dtype, hipStream_t st, bool w_nk, const int64_t* k_limit_dev = nullptr,
+                                  int32_t n_out, int64_t out_stride, fg_dtype_t out_dtype, hipStream_t st, bool w_nk,
                                   const int32_t* src_ids_dev = nullptr);
 
 extern "C" fg_status_t fg_softmax_xent_grad(const float* h_dev, int64_t h_stride, const int32_t* labels_dev, int32_t n, int32_t d,
@@ -591,170 +591,45 @@ extern "C" fg_status_t fg_layer_backward_bf16(const float* dh_dev, int64_t dh_st
 // dW = X^T . dz and db = column sums of dz over the computed rows, X[k, :] = [h_src[rows[k], :] ‖ agg[k, :]],
 // dz[k, :] = dh[rows[k], :] * (h[rows[k], :] > 0). A contraction over the rows (K = tens of thousands) with a small
 // result (2*d_in x d_out), so K is split over the workgroups: workgroup `chunk` multiplies its rows on the matrix
-// cores and leaves a partial result, a second launch adds the partials up in fp64. Two kernels for the partial
-// products: weight_grad_partial_x3_kernel (further down, the default: bf16 matrix instructions on three-way splits of
-// both operands) and this one on the fp32 matrix instructions (operands beyond 4 GB, or asked for through the tuning key).
-// Here both operands are read straight from global memory in the layout v_mfma_f32_32x32x2_f32 wants (for the two rows k, k+1 a
-// lane supplies one element of row k + lane/32 per block), with no transposition and no LDS.
-// A workgroup of 8 wavefronts (4 along M x 2 along N) owns a 256 x 256 tile of the result, a wavefront 64 x 128 of it as
-// 2 x 4 blocks of 32 x 32. The blocks interleave: a lane's elements for the two row blocks are adjacent columns of X and
-// those for the four column blocks adjacent columns of dz, so a pair of rows costs a lane one 8-byte and two 16-byte loads
-// (dh and h) for 8 matrix instructions.
+// cores and leaves a partial result, a second launch adds the partials up in fp64.
 namespace {
 
 constexpr int WG_THREADS = 512;
-constexpr int WG_TILE = 256;
-constexpr int WG_PAIRS = 3;  // pairs of rows whose loads are issued together
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-__global__ __launch_bounds__(WG_THREADS) void weight_grad_partial_kernel(
-    const char* __restrict__ h_src, int n_src, int64_t src_stride, const char* __restrict__ agg, int64_t agg_stride,
-    const char* __restrict__ dh, int64_t dh_stride, const char* __restrict__ h, int64_t h_stride, int n,
-    const int32_t* __restrict__ rows, const int64_t* __restrict__ n_rows_dev, int64_t max_rows, int d_in, int d_out,
-    float* __restrict__ part_w, float* __restrict__ part_b) {
-    int64_t n_rows = n_rows_dev ? *n_rows_dev : max_rows;
-    if (n_rows > max_rows) n_rows = max_rows;
-    const int M = 2 * d_in, N = d_out;
-    const int chunk = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int l32 = lane & 31, kh = lane >> 5;
-    const int wm = wave & 3, wn = wave >> 2;
-    const int m_base = blockIdx.y * WG_TILE + wm * 64;
-    const int n_base = blockIdx.z * WG_TILE + wn * 128;
-    // the rows there are, split evenly over the chunks of the launch (whole batches per chunk)
-    const int64_t per = (n_rows + gridDim.x - 1) / gridDim.x;
-    const int64_t per_b = (per + 2 * WG_PAIRS - 1) / (2 * WG_PAIRS) * (2 * WG_PAIRS);
-    const int64_t k_begin = (int64_t)chunk * per_b < n_rows ? (int64_t)chunk * per_b : n_rows;
-    int64_t k_end = k_begin + per_b;
-    if (k_end > n_rows) k_end = n_rows;
-
-    // This lane's columns. A wavefront's 64 rows of the result are split over its two row blocks by parity and its 128
-    // columns over its four column blocks modulo 4, so that a lane's operands for all blocks are adjacent in memory:
-    // X[k][m_pair], X[k][m_pair + 1] (one 8-byte load) and dz[k][n_quad .. n_quad + 3] (16-byte loads).
-    // Row l of result block i is then row m_base + 2*l + i, column l of result block j is column n_base + 4*l + j.
-    const int m_pair = m_base + 2 * l32;
-    const bool a_ok = m_pair < M;              // M is even: both columns exist or neither
-    const bool a_self = m_pair < d_in;         // d_in is even: a pair never straddles the two panels
-    const int a_col = a_ok ? (a_self ? m_pair : m_pair - d_in) : 0;
-    const int n_quad = n_base + 4 * l32;
-    const bool b_ok = n_quad < N;              // N is a multiple of 4
-    const int b_col = b_ok ? n_quad : 0;
-    f32x16 acc[2][4];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    float colsum[4] = {0.f, 0.f, 0.f, 0.f};
-
-    // the position of list entry k, or of entry k_begin where k is past the chunk (that entry exists whenever this is called)
-    auto row_of = [&](int64_t kk) -> int32_t {
-        const int64_t ks = kk < k_end ? kk : k_begin;
-        return rows ? rows[ks] : (int32_t)ks;
-    };
-    // One batch = WG_PAIRS pairs of rows: 11 loads per pair and lane, then 8 matrix instructions per pair. Two batches are
-    // kept in registers: while one is multiplied the loads of the next are in flight. The row positions are fetched one
-    // batch further ahead so that the row loads do not wait for them.
-    struct Batch {
-        f32x2 a[WG_PAIRS];
-        f32x4 g[WG_PAIRS], o[WG_PAIRS];
-        bool ok[WG_PAIRS];
-    };
-    int32_t r_next[WG_PAIRS];
-#pragma unroll
-    for (int p = 0; p < WG_PAIRS; ++p) r_next[p] = k_begin < k_end ? row_of(k_begin + 2 * p + kh) : 0;
-    auto load_batch = [&](int64_t k0, Batch& B) {  // all loads from a safe row where this lane has none; masks come later
-#pragma unroll
-        for (int p = 0; p < WG_PAIRS; ++p) {
-            const int64_t kk = k0 + 2 * p + kh;
-            const bool in = kk < k_end;
-            const int64_t ks = in ? kk : k_begin;
-            const int32_t r = r_next[p];
-            r_next[p] = row_of(kk + 2 * WG_PAIRS);
-            B.ok[p] = in && r >= 0 && r < n && r < n_src;
-            const int64_t rs = B.ok[p] ? r : 0;
-            const float* xs = (const float*)(h_src + rs * src_stride);
-            const float* xa = (const float*)(agg + ks * agg_stride);
-            B.a[p] = *(const f32x2*)((a_self ? xs : xa) + a_col);
-            const float* gr = (const float*)(dh + rs * dh_stride);
-            const float* hr = h ? (const float*)(h + rs * h_stride) : gr;
-            B.g[p] = *(const f32x4*)(gr + b_col);
-            B.o[p] = *(const f32x4*)(hr + b_col);
-        }
-    };
-    auto multiply_batch = [&](Batch& B) {
-#pragma unroll
-        for (int p = 0; p < WG_PAIRS; ++p) {
-#pragma unroll
-            for (int i = 0; i < 2; ++i) B.a[p][i] = (B.ok[p] && a_ok) ? B.a[p][i] : 0.f;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const bool pass = B.ok[p] && b_ok && (h ? B.o[p][j] > 0.f : true);
-                B.g[p][j] = pass ? B.g[p][j] : 0.f;
-                colsum[j] += B.g[p][j];
-            }
-        }
-#pragma unroll
-        for (int p = 0; p < WG_PAIRS; ++p)
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(B.a[p][i], B.g[p][j], acc[i][j], 0, 0, 0);
-    };
-    constexpr int64_t STEP = 2 * WG_PAIRS;
-    Batch X, Y;
-    if (k_begin < k_end) load_batch(k_begin, X);
-    for (int64_t k0 = k_begin; k0 < k_end; k0 += 2 * STEP) {
-        const bool second = k0 + STEP < k_end;            // uniform over the workgroup
-        if (second) load_batch(k0 + STEP, Y);
-        __builtin_amdgcn_sched_barrier(0);                // the next batch's loads are issued before this batch's arithmetic
-        multiply_batch(X);
-        if (k0 + 2 * STEP < k_end) load_batch(k0 + 2 * STEP, X);
-        __builtin_amdgcn_sched_barrier(0);
-        if (second) multiply_batch(Y);
-    }
-    // partial result of this chunk (zeros if the chunk lies beyond the rows there are)
-    float* pw = part_w + (int64_t)chunk * M * N;
-    // a lane's elements of the four column blocks are four adjacent columns of one row: one 16-byte store
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int m = m_base + 2 * (8 * (e >> 2) + 4 * kh + (e & 3)) + i;  // accumulator element e is block row 8*(e/4) + 4*kh + e%4
-            const f32x4 v = {acc[i][0][e], acc[i][1][e], acc[i][2][e], acc[i][3][e]};
-            if (m < M && b_ok) *(f32x4*)(pw + (int64_t)m * N + n_quad) = v;
-        }
-    if (blockIdx.y == 0 && wm == 0) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float s = colsum[j] + __shfl_xor(colsum[j], 32, 64);
-            const int c = n_quad + j;
-            if (kh == 0 && c < N) part_b[(int64_t)chunk * N + c] = s;
-        }
-    }
-}
-
-// The same partial products on the bf16 matrix cores. Every fp32 value is the exact sum of three bf16 values
-// (x1 = bf16(x), x2 = bf16(x - x1), x3 = bf16(x - x1 - x2), nearest even), and the six products a_i * b_j with i + j <= 4
-// (1-based; each exact in fp32) are kept: the dropped three are below 2^-24 of the product. v_mfma_f32_32x32x16_bf16 wants
-// its contraction index contiguous in a lane, which for X^T . dz is the row index, so both operands go through LDS
-// transposed: a step is 16 rows; thread (column c, group g) of the workgroup loads the 8 values X[k0 + 8g .. + 7][c] (each
-// load coalesced over the columns), splits them and writes the three 16-byte fragments where the lane that needs them
-// for (column c, k half g) reads them back with one LDS load: [term][g][column], conflict-free both ways. The same thread
-// does the same for dz (mask applied to the loaded values, column sums for db kept in a register). Splitting is shared by
-// the whole workgroup: 16 values per thread and step next to 48 matrix instructions per wavefront. Two LDS buffers, one
-// barrier per step; the values of step s + 1 and the row positions of step s + 2 are in flight while step s is multiplied.
-// A wavefront owns 64 x 128 of the 256 x 256 tile as before; fp32 sums within a slice, fp64 across the slices.
+// The partial products on the bf16 matrix cores, for the fp32 model (TERMS = 3) and the mixed-precision one (TERMS = 1).
+//
+// fp32: every value is the exact sum of three bf16 values (x1 = bf16(x), x2 = bf16(x - x1), x3 = bf16(x - x1 - x2), nearest
+// even), and the six products a_i * b_j with i + j <= 4 (1-based; each exact in fp32) are kept: the dropped three are below
+// 2^-24 of the product. The leading products have an accumulator of their own: what limits an fp32 running sum is the
+// rounding of the sum at every step, and that one is rounded once per 16 rows; the roundings of the other are 2^-8 of it.
+// Mixed precision: both operands are bf16 values (the rows of X as the forward product rounded them, dz rounded after the
+// mask; the bias gradient sums the unrounded dz), one product each.
+//
+// v_mfma_f32_32x32x16_bf16 wants its contraction index contiguous in a lane, which for X^T . dz is the row index, so both
+// operands go through LDS transposed: a step is 32 rows; a thread loads 8 rows of its column (or of a pair of 16-bit
+// columns; each load coalesced over the columns), masks and splits them and writes 16-byte fragments where the lane that
+// needs them for (column, 8 rows) reads them back with one LDS load: [term][group of 8 rows][column]. Rows are the same for
+// a whole wavefront, so their positions and addresses are scalars. Two LDS buffers, one barrier per step; the values of
+// step s + 2 are in flight while step s is multiplied.
+//
+// Split: every chunk of rows leaves a partial result of 2*d_in x d_out that the reduction reads again, and every tile of
+// the result reads the operands again, so the tile is as large as LDS and registers allow.
+//
+// What bounds it: reading the operands (52 k rows x 256 x 256: 160 MB and 33 MB of partial results). Measured with its
+// reduction, before (one 256 x 256 tile; mixed precision: a transposing pass, then a product that did not split the rows) and
+// now: fp32 52 k rows x 256 x 256 75 -> 68 us, 6 k x 512 x 256 38 -> 29, 1 k x 512 x 256 26 -> 17, 19 k x 104 x 88 31 -> 22;
+// mixed 5.9 k x 1536 x 1024 104 -> 69, 30 k x 512 x 256 323 -> 49, 6 k x 256 x 128 74 -> 19.
 typedef unsigned int wu32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 wbf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 wbf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
 
-constexpr int WX_STEP = 16;                          // rows per step: the K of one matrix instruction
-constexpr int WX_FRAGS = 3 * 2 * WG_TILE;            // 16-byte fragments of one operand per step
-constexpr size_t WX_LDS_BYTES = (size_t)2 * 2 * WX_FRAGS * 16;  // two operands, two buffers: 96 KB
+constexpr int WX_STEP = 32;             // rows per step: two matrix instructions deep
+constexpr int WX_GROUPS = WX_STEP / 8;  // groups of 8 rows: one 16-byte fragment per column and term
+constexpr size_t wx_lds_bytes(int tm, int tn, int terms) { return (size_t)2 * terms * WX_GROUPS * (tm + tn) * 16; }
 
 // v[0..7] -> three fragments of eight bf16 (element j in half j % 2 of word j / 2)
 __device__ __forceinline__ void wx_split8(const float* v, wu32x4& t1, wu32x4& t2, wu32x4& t3) {
@@ -774,153 +649,262 @@ __device__ __forceinline__ void wx_split8(const float* v, wu32x4& t1, wu32x4& t2
     }
 }
 
-__global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_partial_x3_kernel(
-    const char* __restrict__ h_src, int n_src, int64_t src_stride, const char* __restrict__ agg, int64_t agg_stride,
-    const char* __restrict__ dh, int64_t dh_stride, const char* __restrict__ h, int64_t h_stride, int n,
-    const int32_t* __restrict__ rows, const int64_t* __restrict__ n_rows_dev, int64_t max_rows, int d_in, int d_out,
-    float* __restrict__ part_w, float* __restrict__ part_b) {
-    extern __shared__ __attribute__((aligned(16))) wu32x4 wx_lds[];   // [buffer][operand][term][group][column]
-    int64_t n_rows = n_rows_dev ? *n_rows_dev : max_rows;
-    if (n_rows > max_rows) n_rows = max_rows;
-    const int M = 2 * d_in, N = d_out;
-    const int chunk = blockIdx.x;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+struct WgIn {
+    const char *h_src, *agg, *dh, *h;      // own rows and dh, h by position, agg in list order; h NULL: no mask
+    int64_t src_stride, agg_stride, dh_stride, h_stride, max_rows;
+    const int32_t* rows;
+    const int64_t* n_rows_dev;
+    int n_src, n, d_in, d_pad, d_out, n_chunks, tiles_m, tiles_n;
+};
+
+// row * stride on the scalar unit (both are the same in all lanes; left to itself the compiler multiplies on the vector unit)
+__device__ __forceinline__ int64_t wx_row_offset(int32_t row, int64_t stride) {
+    const uint32_t r = (uint32_t)row, lo = (uint32_t)stride, hi = (uint32_t)((uint64_t)stride >> 32);
+    return (int64_t)(((uint64_t)(__umulhi(r, lo) + r * hi) << 32) | (uint64_t)(r * lo));
+}
+
+// TM x TN: the tile of the result, 8 wavefronts as 4 x 2. SRC: element type of h_src (TERMS = 3: fp32).
+template <int TM, int TN, int TERMS, int SRC>
+__global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_tile_kernel(WgIn A, float* __restrict__ part_w, float* __restrict__ part_b) {
+    constexpr int W = (TERMS == 1 && TM == 256) ? 2 : 1;          // adjacent columns per thread
+    constexpr int XT = TM / W, ZT = TN / W;                       // threads side by side on a row
+    constexpr int XU = XT * WX_GROUPS / WG_THREADS, ZU = ZT * WX_GROUPS / WG_THREADS;      // groups of 8 rows per thread
+    constexpr int XR = (TERMS == 1 && W == 2 && SRC == FG_F32) ? 2 : 1;                    // words per loaded piece of h_src
+    constexpr int XFRAGS = TERMS * WX_GROUPS * TM, BUF = TERMS * WX_GROUPS * (TM + TN);
+    constexpr int MB = TM / 128, NB = TN / 64;                    // 32 x 32 blocks per wavefront
+    constexpr int ESZ = SRC == FG_F32 ? 4 : 2, ASZ = TERMS == 3 ? 4 : 2;                   // bytes per element: h_src; agg and h
+    extern __shared__ __attribute__((aligned(16))) wu32x4 wx_lds[];   // [buffer][X, then dz][term][group][column]
+    // A chunk's tiles read the same rows: the workgroups of one XCD (ids congruent mod 8) take consecutive (chunk, tile) pairs
+    const int tiles = A.tiles_m * A.tiles_n;
+    const int unit = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+    if (unit >= A.n_chunks * tiles) return;       // uniform over the workgroup, before any barrier
+    const int chunk = unit / tiles, tile = unit % tiles;
+    const int m_tile = (tile / A.tiles_n) * TM, n_tile = (tile % A.tiles_n) * TN;
+    int64_t n_rows = A.n_rows_dev ? *A.n_rows_dev : A.max_rows;
+    if (n_rows > A.max_rows) n_rows = A.max_rows;
+    const int M = 2 * A.d_in, N = A.d_out, d_in = A.d_in;      // M: rows of the result (m counts them with each half padded to d_pad)
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int l32 = lane & 31, half = lane >> 5;
-    const int wm = wave & 3, wn = wave >> 2;
-    const int m_tile = blockIdx.y * WG_TILE, n_tile = blockIdx.z * WG_TILE;
-    // the rows there are, split evenly over the chunks of the launch (whole steps per chunk)
-    const int64_t per = (n_rows + gridDim.x - 1) / gridDim.x;
+    const int wm = (wave & 3) * (TM / 4), wn = (wave >> 2) * (TN / 2);
+    // the rows there are, split evenly over the chunks (whole steps per chunk)
+    const int64_t per = (n_rows + A.n_chunks - 1) / A.n_chunks;
     const int64_t per_b = (per + WX_STEP - 1) / WX_STEP * WX_STEP;
     const int64_t k_begin = (int64_t)chunk * per_b < n_rows ? (int64_t)chunk * per_b : n_rows;
     int64_t k_end = k_begin + per_b;
     if (k_end > n_rows) k_end = n_rows;
     const int n_steps = (int)((k_end - k_begin + WX_STEP - 1) / WX_STEP);
 
-    // staging role of this thread: column pc of both tiles, rows 8 * pg .. 8 * pg + 7 of a step
-    const int pc = t & (WG_TILE - 1), pg = t >> 8;
-    const int xc = m_tile + pc;
-    const bool x_ok = xc < M, x_self = xc < d_in;
-    const int x_col = x_ok ? (x_self ? xc : xc - d_in) : 0;
-    const int zc = n_tile + pc;
-    const bool z_ok = zc < N;
-    const int z_col = z_ok ? zc : 0;
+    // Staging role of this thread: W adjacent columns of X and of dz, rows 8 * group .. + 7 of a step for its groups xg + .., zg + ..:
+    // the same for all lanes of a wavefront. Each half of X is walked as if it were d_pad columns wide, so that a wavefront's
+    // columns lie in one half. (A column that does not exist reads another one: its products go to outputs that are not stored.)
+    const int xp = (t % XT) * W, zp = (t % ZT) * W;
+    const int xg = __builtin_amdgcn_readfirstlane(t / XT), zg = __builtin_amdgcn_readfirstlane(t / ZT);
+    const bool x_agg = __builtin_amdgcn_readfirstlane(m_tile + xp) >= A.d_pad;
+    const int xc = m_tile + xp - (x_agg ? A.d_pad : 0), zc = n_tile + zp;
+    const char* x_base = x_agg ? A.agg : A.h_src;
+    const int64_t x_stride = x_agg ? A.agg_stride : A.src_stride;
+    const int x_off = (xc < d_in ? xc : 0) * (x_agg ? ASZ : ESZ), z_off = (zc < N ? zc : 0) * 4, h_off = (zc < N ? zc : 0) * (A.h ? ASZ : 4);
+    const char* hm = A.h ? A.h : A.dh;                       // without a mask: the words of dh again, replaced by 1
+    const int64_t hm_stride = A.h ? A.h_stride : A.dh_stride;
+    const unsigned int h_and = A.h ? 0xFFFFFFFFu : 0u, h_or = A.h ? 0u : 0x3F800000u;
+    const int kb = (int)k_begin, ke = (int)k_end;            // list entries are positions: below 2^31
 
-    // The loaded values of one step wait in registers: they are requested a whole step (its matrix instructions, its
-    // barrier) before they are split and written to LDS, the row positions one step earlier still.
     struct Vals {
-        float xv[8], gv[8], ov[8];
-        unsigned ok;     // bit e: row e exists
+        unsigned int x[XU][8][XR];
+        float g[ZU][8][W];
+        unsigned int o[ZU][8];
+        unsigned int x_in, z_in;      // bit e: row e of the step exists for this thread's columns of X, for dz (scalars)
     };
-    int32_t pos_next[8];
-    float colsum = 0.f;
-    // positions of the rows of step s (list entries k_begin + 16 s + 8 pg + e); an entry past the chunk reads entry k_begin
-    auto load_positions = [&](int s) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int64_t kk = k_begin + (int64_t)s * WX_STEP + 8 * pg + e;
-            const int64_t ks = kk < k_end ? kk : k_begin;
-            pos_next[e] = rows ? rows[ks] : (int32_t)ks;
-        }
+    // position of row `l32` of step s; one load for the whole step, one register
+    const int32_t* list = A.rows ? A.rows : (const int32_t*)A.dh;
+    auto load_positions = [&](int s) -> int32_t {
+        const int kk = kb + s * WX_STEP + l32;
+        const int ks = kk < ke ? kk : ke - 1;
+        const int32_t raw = list[A.rows ? ks : 0];
+        return A.rows ? raw : ks;
     };
-    // values of step s from the positions loaded for it; rows that do not exist read row 0 / entry k_begin and count as zero
-    auto load_values = [&](int s, Vals& V) {
-        V.ok = 0;
+    // Values of step s from the positions loaded for it. The rows of a group are the same for the whole wavefront: their
+    // positions are read out of the lanes that hold them and the address arithmetic is scalar. Rows that do not exist read
+    // row 0 / the last entry and are masked when they are staged (with masks, not branches: a branch per row would make the
+    // wavefront wait for each load by itself).
+    auto load_values = [&](int s, int32_t raw, Vals& V) {
+        const int kk = kb + s * WX_STEP + l32;
+        // a position without own features: the fp32 product leaves the row out, the mixed one takes zeros for them
+        const bool z_ok = kk < ke && raw >= 0 && raw < A.n && (TERMS == 1 || raw < A.n_src);
+        const bool x_ok = z_ok && (x_agg || raw < A.n_src);
+        const int32_t pos = z_ok ? raw : 0, x_row = x_agg ? (kk < ke ? kk : ke - 1) : (x_ok ? raw : 0);
+        V.x_in = (unsigned int)__ballot(x_ok);
+        V.z_in = (unsigned int)__ballot(z_ok);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int64_t kk = k_begin + (int64_t)s * WX_STEP + 8 * pg + e;
-            const bool in = kk < k_end;
-            const int64_t ks = in ? kk : k_begin;
-            const int32_t r = pos_next[e];
-            const bool ok = in && r >= 0 && r < n && r < n_src;
-            V.ok |= ok ? (1u << e) : 0u;
-            // byte offsets in 32 bits (the host checks that every operand is below 4 GB): one register per address
-            const uint32_t rs = ok ? (uint32_t)r : 0u;
-            const uint32_t x_off = x_self ? rs * (uint32_t)src_stride + 4u * (uint32_t)x_col
-                                          : (uint32_t)ks * (uint32_t)agg_stride + 4u * (uint32_t)x_col;
-            V.xv[e] = *(const float*)((x_self ? h_src : agg) + x_off);
-            V.gv[e] = *(const float*)(dh + (rs * (uint32_t)dh_stride + 4u * (uint32_t)z_col));
-            V.ov[e] = h ? *(const float*)(h + (rs * (uint32_t)h_stride + 4u * (uint32_t)z_col)) : 1.f;
+        for (int i = 0; i < XU; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const char* p = x_base + wx_row_offset(__builtin_amdgcn_readlane(x_row, 8 * (xg + i * (WG_THREADS / XT)) + e), x_stride);
+                if constexpr (TERMS == 3 || W == 2) {
+                    V.x[i][e][0] = *(const unsigned int*)(p + x_off);
+                    if constexpr (XR == 2) V.x[i][e][1] = *(const unsigned int*)(p + (x_off + (x_agg ? 0 : 4)));
+                } else if constexpr (SRC == FG_F32) {
+                    V.x[i][e][0] = *(const unsigned int*)(p + (x_off & ~3));      // a mean (bf16): the word it lies in
+                } else {
+                    V.x[i][e][0] = *(const unsigned short*)(p + x_off);
+                }
+            }
+#pragma unroll
+        for (int i = 0; i < ZU; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int32_t r = __builtin_amdgcn_readlane(pos, 8 * (zg + i * (WG_THREADS / ZT)) + e);
+                const char* gp = A.dh + wx_row_offset(r, A.dh_stride);
+#pragma unroll
+                for (int w = 0; w < W; ++w) V.g[i][e][w] = *(const float*)(gp + (z_off + 4 * w));
+                const char* hp = hm + wx_row_offset(r, hm_stride);
+                if constexpr (TERMS == 3 || W == 2)
+                    V.o[i][e] = *(const unsigned int*)(hp + h_off);
+                else
+                    V.o[i][e] = *(const unsigned short*)(hp + h_off);
+            }
+    };
+    // rows that do not exist become zeros (only a chunk's last step, or a list with bad entries, has any)
+    auto mask_rows = [&](Vals& V) {
+        if ((V.x_in & V.z_in) == 0xFFFFFFFFu) return;      // uniform
+#pragma unroll
+        for (int i = 0; i < XU; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const unsigned int m = 0u - ((V.x_in >> (8 * (xg + i * (WG_THREADS / XT)) + e)) & 1u);
+#pragma unroll
+                for (int q = 0; q < XR; ++q) V.x[i][e][q] &= m;
+            }
+#pragma unroll
+        for (int i = 0; i < ZU; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const unsigned int m = 0u - ((V.z_in >> (8 * (zg + i * (WG_THREADS / ZT)) + e)) & 1u);
+#pragma unroll
+                for (int w = 0; w < W; ++w) V.g[i][e][w] = __uint_as_float(__float_as_uint(V.g[i][e][w]) & m);
+            }
+    };
+    double colsum[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) colsum[w] = 0.0;
+    auto put = [&](wu32x4* to, int tile_w, int group, int col, const float* v) {
+        if constexpr (TERMS == 3) {
+            wu32x4 a1, a2, a3;
+            wx_split8(v, a1, a2, a3);
+            to[(0 * WX_GROUPS + group) * tile_w + col] = a1;
+            to[(1 * WX_GROUPS + group) * tile_w + col] = a2;
+            to[(2 * WX_GROUPS + group) * tile_w + col] = a3;
+        } else {
+            const f32x8 f = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]};
+            to[group * tile_w + col] = __builtin_bit_cast(wu32x4, __builtin_convertvector(f, wbf16x8));
         }
     };
     // mask, split and write the loaded step to buffer b
-    auto stage = [&](int b, const Vals& V) {
-        float xs8[8], zs8[8];
+    auto stage = [&](int b, Vals& V) {
+        mask_rows(V);
+        wu32x4* X = wx_lds + b * BUF;
+        wu32x4* Z = X + XFRAGS;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const bool ok = (V.ok >> e) & 1u;
-            xs8[e] = (ok && x_ok) ? V.xv[e] : 0.f;
-            zs8[e] = (ok && z_ok && V.ov[e] > 0.f) ? V.gv[e] : 0.f;
-            colsum += zs8[e];
-        }
-        wu32x4 a1, a2, a3, b1, b2, b3;
-        wx_split8(xs8, a1, a2, a3);
-        wx_split8(zs8, b1, b2, b3);
-        wu32x4* X = wx_lds + (size_t)b * 2 * WX_FRAGS;
-        wu32x4* Z = X + WX_FRAGS;
-        X[(0 * 2 + pg) * WG_TILE + pc] = a1;
-        X[(1 * 2 + pg) * WG_TILE + pc] = a2;
-        X[(2 * 2 + pg) * WG_TILE + pc] = a3;
-        Z[(0 * 2 + pg) * WG_TILE + pc] = b1;
-        Z[(1 * 2 + pg) * WG_TILE + pc] = b2;
-        Z[(2 * 2 + pg) * WG_TILE + pc] = b3;
+        for (int i = 0; i < XU; ++i)
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                float v[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const unsigned int raw = V.x[i][e][0];
+                    float f;
+                    if constexpr (TERMS == 3) {
+                        f = __uint_as_float(raw);
+                    } else {
+                        const unsigned short own16 = (unsigned short)(W == 2 ? raw >> (16 * w) : raw);
+                        const unsigned short agg16 = (unsigned short)((W == 2 ? w : (SRC == FG_F32 ? (x_off & 2) : 0)) ? raw >> 16 : raw);
+                        const float self = SRC == FG_F32   ? __uint_as_float(XR == 2 && w ? V.x[i][e][XR - 1] : raw)
+                                           : SRC == FG_F16 ? __half2float(__ushort_as_half(own16))
+                                                           : bw_bf16_value(own16);
+                        f = x_agg ? bw_bf16_value(agg16) : self;
+                    }
+                    v[e] = f;
+                }
+                put(X, TM, xg + i * (WG_THREADS / XT), xp + w, v);
+            }
+#pragma unroll
+        for (int i = 0; i < ZU; ++i)
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                float v[8], s8 = 0.f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const unsigned int raw = V.o[i][e];
+                    const float o = TERMS == 3 ? __uint_as_float(raw) : bw_bf16_value((unsigned short)(w ? raw >> 16 : raw));
+                    const float act = __uint_as_float((__float_as_uint(o) & h_and) | h_or);
+                    v[e] = act > 0.f ? V.g[i][e][w] : 0.f;
+                    s8 += v[e];
+                }
+                colsum[w] += (double)s8;
+                put(Z, TN, zg + i * (WG_THREADS / ZT), zp + w, v);
+            }
     };
 
-    f32x16 acc[2][4];
+    // `lead` takes the products of the leading terms, `rest` the others (TERMS = 3 only)
+    f32x16 lead[MB][NB], rest[TERMS == 3 ? MB : 1][TERMS == 3 ? NB : 1];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-    // one step out of buffer b: 48 matrix instructions per wavefront
+            for (int e = 0; e < 16; ++e) {
+                lead[i][j][e] = 0.f;
+                if constexpr (TERMS == 3) rest[i][j][e] = 0.f;
+            }
     auto multiply = [&](int b) {
-        const wu32x4* X = wx_lds + (size_t)b * 2 * WX_FRAGS;
-        const wu32x4* Z = X + WX_FRAGS;
-        wu32x4 ax[2][3];
+        const wu32x4* X = wx_lds + b * BUF;
+        const wu32x4* Z = X + XFRAGS;
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int ph = 0; ph < WX_STEP / 16; ++ph) {
+            const int g = 2 * ph + half;
+            wu32x4 ax[MB][TERMS];
 #pragma unroll
-            for (int term = 0; term < 3; ++term) ax[mb][term] = X[(term * 2 + half) * WG_TILE + wm * 64 + mb * 32 + l32];
-        // (X term, dz term) pairs, smallest products first
-        constexpr int TA[6] = {2, 0, 1, 1, 0, 0};
-        constexpr int TZ[6] = {0, 2, 1, 0, 1, 0};
+            for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb) {
-            wu32x4 bz[3];
+                for (int term = 0; term < TERMS; ++term) ax[mb][term] = X[(term * WX_GROUPS + g) * TM + wm + mb * 32 + l32];
 #pragma unroll
-            for (int term = 0; term < 3; ++term) bz[term] = Z[(term * 2 + half) * WG_TILE + wn * 128 + nb * 32 + l32];
+            for (int nb = 0; nb < NB; ++nb) {
+                wu32x4 bz[TERMS];
 #pragma unroll
-            for (int e = 0; e < 6; ++e)
+                for (int term = 0; term < TERMS; ++term) bz[term] = Z[(term * WX_GROUPS + g) * TN + wn + nb * 32 + l32];
+                if constexpr (TERMS == 3) {      // (X term, dz term) pairs, smallest products first
+                    constexpr int TA[5] = {2, 0, 1, 1, 0};
+                    constexpr int TZ[5] = {0, 2, 1, 0, 1};
 #pragma unroll
-                for (int mb = 0; mb < 2; ++mb)
-                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(wbf16x8, ax[mb][TA[e]]),
-                                                                          __builtin_bit_cast(wbf16x8, bz[TZ[e]]), acc[mb][nb], 0, 0, 0);
+                    for (int e = 0; e < 5; ++e)
+#pragma unroll
+                        for (int mb = 0; mb < MB; ++mb)
+                            rest[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(wbf16x8, ax[mb][TA[e]]),
+                                                                                   __builtin_bit_cast(wbf16x8, bz[TZ[e]]), rest[mb][nb], 0, 0, 0);
+                }
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+                    lead[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(wbf16x8, ax[mb][0]),
+                                                                           __builtin_bit_cast(wbf16x8, bz[0]), lead[mb][nb], 0, 0, 0);
+            }
         }
     };
 
     if (n_steps > 0) {      // uniform over the workgroup
         Vals V;
-        load_positions(0);
-        load_values(0, V);
-        if (n_steps > 1) load_positions(1);
+        int32_t p0 = load_positions(0), p1 = load_positions(1), p2 = load_positions(2);
+        load_values(0, p0, V);
         stage(0, V);
-        if (n_steps > 1) {
-            load_values(1, V);
-            if (n_steps > 2) load_positions(2);
-        }
+        load_values(1, p1, V);
         __syncthreads();
         for (int s = 0; s < n_steps; ++s) {
             const int b = s & 1;
             // step s + 1 goes to the other buffer (last read a step ago, before the previous barrier), then the registers take
-            // step s + 2, and step s is multiplied with those loads in flight
-            if (s + 1 < n_steps) stage(b ^ 1, V);
-            if (s + 2 < n_steps) {
-                load_values(s + 2, V);
-                if (s + 3 < n_steps) load_positions(s + 3);
-            }
-            __builtin_amdgcn_sched_barrier(0);
+            // step s + 2, and step s is multiplied with those loads in flight (past the chunk: rows that count as zero)
             multiply(b);
+            stage(b ^ 1, V);
+            load_values(s + 2, p2, V);
+            p2 = load_positions(s + 3);
             __syncthreads();
         }
     }
@@ -928,21 +912,29 @@ __global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_partial_x3_kernel(
     // its row 8 * (e / 4) + 4 * half + e % 4, column l32
     float* pw = part_w + (int64_t)chunk * M * N;
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const int m = m_tile + wm * 64 + mb * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+            const int mp = m_tile + wm + mb * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+            const int m = mp < A.d_pad ? (mp < d_in ? mp : M) : d_in + mp - A.d_pad;
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb) {
-                const int c = n_tile + wn * 128 + nb * 32 + l32;
-                if (m < M && c < N) pw[(int64_t)m * N + c] = acc[mb][nb][e];
+            for (int nb = 0; nb < NB; ++nb) {
+                const int c = n_tile + wn + nb * 32 + l32;
+                float v = lead[mb][nb][e];
+                if constexpr (TERMS == 3) v += rest[mb][nb][e];
+                if (m < M && c < N) pw[(int64_t)m * N + c] = v;
             }
         }
-    if (blockIdx.y == 0) {      // column sums of dz: the two row groups of a column meet in LDS
-        float* red = (float*)wx_lds;
-        red[t] = colsum;
+    if (m_tile == 0) {      // column sums of dz: the threads of a column meet in LDS
+        double* red = (double*)wx_lds;
+#pragma unroll
+        for (int w = 0; w < W; ++w) red[t * W + w] = colsum[w];
         __syncthreads();
-        if (t < WG_TILE && z_ok) part_b[(int64_t)chunk * N + zc] = red[t] + red[t + WG_TILE];
+        if (t < TN && n_tile + t < N) {
+            double sum = 0.0;
+            for (int j = 0; j < WG_THREADS / ZT; ++j) sum += red[(t / W + j * ZT) * W + t % W];
+            part_b[(int64_t)chunk * N + n_tile + t] = (float)sum;
+        }
     }
 }
 
@@ -991,112 +983,62 @@ __global__ __launch_bounds__(BW_THREADS) void weight_grad_reduce_kernel(const fl
     }
 }
 
-// Mixed precision: the weight gradients as a product on the bf16 matrix cores. Both operands of dW = X^T . dz are bf16 values
-// (the rows of X as the forward product rounded them, dz rounded after the mask), so the contraction over the computed rows
-// is a plain bf16 matrix product; the matrix instruction wants the contraction index contiguous, which for X^T . dz is the
-// row index. This kernel writes both operands transposed, XT [2*d_in x Kp] and DZT [d_out x Kp] in bf16 (Kp = the bound on
-// the rows rounded up to 64; zeros from the row count to the end of its block of 64), 64 x 64 tiles through LDS, reads and
-// writes coalesced. The dz tiles also leave the column sums of the unrounded dz of their 64 rows (the bias gradient's
-// partial sums; zeros for blocks beyond the rows there are).
-constexpr int ST_TILE = 64;
-__global__ __launch_bounds__(BW_THREADS) void weight_grad_stage_bf16_kernel(
-    const char* __restrict__ h_src, int n_src, int64_t src_stride, int src_code, const char* __restrict__ agg, int64_t agg_stride,
-    const char* __restrict__ dh, int64_t dh_stride, const char* __restrict__ h, int64_t h_stride, int n,
-    const int32_t* __restrict__ rows, const int64_t* __restrict__ n_rows_dev, int64_t max_rows, int d_in, int d_out, int tiles_x,
-    unsigned short* __restrict__ xt, unsigned short* __restrict__ dzt, int64_t kp, float* __restrict__ part_b) {
-    __shared__ unsigned short tile[ST_TILE][ST_TILE + 2];
-    __shared__ float sums[BW_THREADS / ST_TILE][ST_TILE];
-    int64_t n_rows = n_rows_dev ? *n_rows_dev : max_rows;
-    if (n_rows > max_rows) n_rows = max_rows;
-    const int64_t k0 = (int64_t)blockIdx.x * ST_TILE;
-    const bool is_x = (int)blockIdx.y < tiles_x;
-    const int c0 = (is_x ? (int)blockIdx.y : (int)blockIdx.y - tiles_x) * ST_TILE;   // first column of X (of 2*d_in) or of dz
-    const int n_cols = is_x ? 2 * d_in : d_out;
-    const int tx = threadIdx.x & (ST_TILE - 1), ty = threadIdx.x / ST_TILE;          // 64 x 4
-    const int c = c0 + tx;
-    if (k0 >= n_rows) {      // nothing to stage: only the bias gradient's partial sums need their zeros
-        if (!is_x && ty == 0 && c < d_out) part_b[(int64_t)blockIdx.x * d_out + c] = 0.f;
-        return;
-    }
-    float colsum = 0.f;
-    for (int rr = ty; rr < ST_TILE; rr += BW_THREADS / ST_TILE) {
-        const int64_t k = k0 + rr;
-        float v = 0.f;
-        if (k < n_rows && c < n_cols) {
-            const int32_t r = rows ? rows[k] : (int32_t)k;
-            if (r >= 0 && r < n) {
-                if (is_x) {
-                    if (c < d_in) {
-                        if (r < n_src) {
-                            const char* row = h_src + (int64_t)r * src_stride;
-                            v = src_code == FG_F32 ? ((const float*)row)[c]
-                                : src_code == FG_F16 ? __half2float(__ushort_as_half(((const unsigned short*)row)[c]))
-                                                     : bw_bf16_value(((const unsigned short*)row)[c]);
-                        }
-                    } else {
-                        v = bw_bf16_value(((const unsigned short*)(agg + k * agg_stride))[c - d_in]);
-                    }
-                } else {
-                    v = ((const float*)(dh + (int64_t)r * dh_stride))[c];
-                    if (h && !(bw_bf16_value(((const unsigned short*)(h + (int64_t)r * h_stride))[c]) > 0.f)) v = 0.f;
-                    colsum += v;
-                }
-            }
-        }
-        tile[rr][tx] = bw_bf16_bits(v);
-    }
-    if (!is_x) sums[ty][tx] = colsum;
-    __syncthreads();
-    if (!is_x && ty == 0 && c < d_out) {
-        float t = 0.f;
-#pragma unroll
-        for (int q = 0; q < BW_THREADS / ST_TILE; ++q) t += sums[q][tx];
-        part_b[(int64_t)blockIdx.x * d_out + c] = t;
-    }
-    unsigned short* out = is_x ? xt : dzt;
-    for (int cc = ty; cc < ST_TILE; cc += BW_THREADS / ST_TILE)
-        if (c0 + cc < n_cols) out[(int64_t)(c0 + cc) * kp + k0 + tx] = tile[tx][cc];
-}
-
-struct WgStage {
-    int64_t kp;
-    size_t dzt, part_b, total;
-};
-WgStage wg_stage_plan(int64_t max_rows, int64_t d_in, int64_t d_out) {
-    WgStage p;
-    p.kp = fg_ceil_div(max_rows > 0 ? max_rows : 1, ST_TILE) * ST_TILE;
-    p.dzt = fg_align_up((size_t)(2 * d_in) * p.kp * 2, 256);
-    p.part_b = p.dzt + fg_align_up((size_t)d_out * p.kp * 2, 256);
-    p.total = p.part_b + fg_align_up((size_t)(p.kp / ST_TILE) * d_out * 4, 256);
-    return p;
-}
-
+// How a contraction is split: tiles of the result, times chunks of rows.
 struct WgPlan {
-    int n_chunks, rows_per_chunk, tiles_m, tiles_n;
+    int tm, tn, d_pad, n_chunks, tiles_m, tiles_n;
     size_t part_b, total;
 };
-WgPlan wg_plan(int64_t max_rows, int64_t d_in, int64_t d_out) {
+WgPlan wg_plan(int64_t max_rows, int64_t d_in, int64_t d_out, bool mixed) {
     WgPlan p;
-    p.tiles_m = (int)fg_ceil_div(2 * d_in, WG_TILE);
-    p.tiles_n = (int)fg_ceil_div(d_out, WG_TILE);
-    int64_t chunks = 256 / (p.tiles_m * p.tiles_n);  // one workgroup per compute unit
+    // Large tiles halve the reads of the operands; small ones fill the chip with fewer chunks, whose partial results have to be
+    // written and read. fp32, 256 result rows and columns: 68 us against 74 at 52 k rows, 34 = 34 at 20 k, 28 against 26 at 12 k.
+    // Mixed precision, rows x 128-wide tiles: 42 us against 58 at 240 k, 30 = 30 at 84 k, 30 against 24 at 33 k.
+    const int64_t tiles128 = fg_ceil_div(2 * fg_ceil_div(d_in, 64) * 64, 128) * fg_ceil_div(d_out, 128);
+    const bool large = mixed ? d_in > 64 && d_out > 128 && tiles128 * max_rows >= 98304 : d_in > 64 && max_rows >= 32768;
+    p.tm = large ? 256 : 128;
+    p.tn = large && mixed ? 256 : 128;
+    const int wide = mixed && p.tm == 256 ? 128 : 64;      // columns of a wavefront
+    p.d_pad = (int)fg_ceil_div(d_in, wide) * wide;
+    p.tiles_m = (int)fg_ceil_div(2 * p.d_pad, p.tm);
+    p.tiles_n = (int)fg_ceil_div(d_out, p.tn);
+    // One workgroup fills a compute unit. 32 of them are left to the launches this one runs beside: with all 256 taken the cache
+    // update waited for the whole product (its second launch 63 us instead of 9; large SAGE iteration 453 -> 441 us).
+    int64_t chunks = 224 / (p.tiles_m * p.tiles_n);
     if (chunks < 1) chunks = 1;
-    const int64_t by_rows = fg_ceil_div(max_rows > 0 ? max_rows : 1, 32);  // at least 32 rows per chunk (1024 rows: 40 -> 30 us against 64)
+    // at least two steps per chunk, one where there are few tiles and rows (64 / 32 rows: 1024 rows x 512 x 256 17 / 22 us,
+    // 777 rows x 176 x 88 13 / 11 us); more rows never make fewer chunks: a workspace for them serves fewer rows too
+    const int64_t some = max_rows > 0 ? max_rows : 1;
+    int64_t by_rows = fg_ceil_div(some, 2 * WX_STEP);
+    if (p.tiles_m * p.tiles_n <= 2) {
+        const int64_t by_step = fg_ceil_div(some, WX_STEP) < 64 ? fg_ceil_div(some, WX_STEP) : 64;
+        if (by_rows < by_step) by_rows = by_step;
+    }
     if (chunks > by_rows) chunks = by_rows;
-    int64_t per = fg_ceil_div(max_rows > 0 ? max_rows : 1, chunks);
-    per = fg_ceil_div(per, 2 * WG_PAIRS) * 2 * WG_PAIRS;
-    p.rows_per_chunk = (int)per;
-    p.n_chunks = (int)fg_ceil_div(max_rows > 0 ? max_rows : 1, per);
+    p.n_chunks = (int)chunks;
     p.part_b = fg_align_up((size_t)p.n_chunks * 2 * d_in * d_out * 4, 256);
     p.total = p.part_b + fg_align_up((size_t)p.n_chunks * d_out * 4, 256);
     return p;
+}
+
+// partial products of every chunk, then their sum
+template <typename Kernel>
+fg_status_t wg_launch(Kernel kernel, int terms, const WgPlan& P, const WgIn& A, float* part_w, float* part_b, float* dw, float* db, hipStream_t st) {
+    const unsigned grid = (unsigned)(fg_ceil_div((int64_t)P.n_chunks * P.tiles_m * P.tiles_n, 8) * 8);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(WG_THREADS), wx_lds_bytes(P.tm, P.tn, terms), st, A, part_w, part_b);
+    FG_LAUNCH_CHECK("weight_grad_tile_kernel");
+    const int64_t mn = (int64_t)2 * A.d_in * A.d_out;
+    const int w_blocks = (int)fg_ceil_div(mn, 128), b_blocks = (int)fg_ceil_div(A.d_out, 128);
+    hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3((unsigned)(w_blocks + b_blocks)), dim3(BW_THREADS), 0, st, part_w, part_b, P.n_chunks,
+                       mn, A.d_out, w_blocks, dw, db);
+    FG_LAUNCH_CHECK("weight_grad_reduce_kernel");
+    return FG_OK;
 }
 
 }  // namespace
 
 extern "C" size_t fg_layer_backward_weights_workspace_bytes(int64_t max_rows, int32_t d_in, int32_t d_out) {
     if (max_rows < 0 || d_in <= 0 || d_out <= 0) return 0;
-    return wg_plan(max_rows, d_in, d_out).total;
+    return wg_plan(max_rows, d_in, d_out, false).total;
 }
 
 extern "C" fg_status_t fg_layer_backward_weights(const float* h_src_dev, int32_t n_src, int64_t src_stride, const float* agg_dev,
@@ -1117,7 +1059,7 @@ extern "C" fg_status_t fg_layer_backward_weights(const float* h_src_dev, int32_t
     if (((uintptr_t)h_src_dev | (uintptr_t)agg_dev | (uintptr_t)dh_dev | (uintptr_t)h_dev | (uintptr_t)src_stride | (uintptr_t)agg_stride |
          (uintptr_t)dh_stride | (uintptr_t)h_stride) & 15)
         FG_FAIL(FG_ERR_INVALID_ARG, "%s: h_src, agg, dh, h and their strides must be 16-byte aligned", who);
-    const WgPlan P = wg_plan(max_rows, d_in, d_out);
+    const WgPlan P = wg_plan(max_rows, d_in, d_out, false);
     if (!ws_dev || ws_bytes < P.total) FG_FAIL(FG_ERR_SHAPE, "%s: workspace of %zu bytes given, %zu needed", who, ws_bytes, P.total);
     if ((uintptr_t)ws_dev & 15) FG_FAIL(FG_ERR_INVALID_ARG, "%s: the workspace must be 16-byte aligned", who);
     fg_clear_error();
@@ -1126,32 +1068,15 @@ extern "C" fg_status_t fg_layer_backward_weights(const float* h_src_dev, int32_t
     float* part_b = (float*)((char*)ws_dev + P.part_b);
     // without rows (or without anything they could index) every chunk is empty and the partials are zeros
     const int64_t rows_bound = (n > 0 && n_src > 0) ? max_rows : 0;
-    // the products on the bf16 matrix cores (three-way split of both operands) unless the fp32 instructions are asked for
-    const int64_t forced = fg_tuning(FG_TUNE_LINEAR_TILE);
-    // (its byte offsets are 32-bit: every operand has to end below 4 GB)
-    const int64_t lim = (int64_t)1 << 32;
-    const bool near = (int64_t)n_src * src_stride < lim && max_rows * agg_stride < lim && (int64_t)n * dh_stride < lim &&
-                      (!h_dev || (int64_t)n * h_stride < lim);
-    if (forced == 32 || forced == 64 || forced == 128 || !near)
-        hipLaunchKernelGGL(weight_grad_partial_kernel, dim3((unsigned)P.n_chunks, (unsigned)P.tiles_m, (unsigned)P.tiles_n), dim3(WG_THREADS), 0, st,
-                           (const char*)h_src_dev, n_src, src_stride, (const char*)agg_dev, agg_stride, (const char*)dh_dev, dh_stride,
-                           (const char*)h_dev, h_stride, n, rows_dev, n_rows_dev, rows_bound, d_in, d_out, part_w, part_b);
-    else
-        hipLaunchKernelGGL(weight_grad_partial_x3_kernel, dim3((unsigned)P.n_chunks, (unsigned)P.tiles_m, (unsigned)P.tiles_n), dim3(WG_THREADS),
-                           WX_LDS_BYTES, st, (const char*)h_src_dev, n_src, src_stride, (const char*)agg_dev, agg_stride, (const char*)dh_dev,
-                           dh_stride, (const char*)h_dev, h_stride, n, rows_dev, n_rows_dev, rows_bound, d_in, d_out, part_w, part_b);
-    FG_LAUNCH_CHECK("weight_grad_partial_kernel");
-    const int64_t mn = (int64_t)2 * d_in * d_out;
-    const int w_blocks = (int)fg_ceil_div(mn, 128), b_blocks = (int)fg_ceil_div(d_out, 128);
-    hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3((unsigned)(w_blocks + b_blocks)), dim3(BW_THREADS), 0, st, part_w, part_b, P.n_chunks,
-                       mn, d_out, w_blocks, dw_dev, db_dev);
-    FG_LAUNCH_CHECK("weight_grad_reduce_kernel");
-    return FG_OK;
+    const WgIn A = {(const char*)h_src_dev, (const char*)agg_dev, (const char*)dh_dev, (const char*)h_dev, src_stride, agg_stride, dh_stride,
+                    h_stride, rows_bound, rows_dev, n_rows_dev, n_src, n, d_in, P.d_pad, d_out, P.n_chunks, P.tiles_m, P.tiles_n};
+    if (P.tm == 256) return wg_launch(weight_grad_tile_kernel<256, 128, 3, FG_F32>, 3, P, A, part_w, part_b, dw_dev, db_dev, st);
+    return wg_launch(weight_grad_tile_kernel<128, 128, 3, FG_F32>, 3, P, A, part_w, part_b, dw_dev, db_dev, st);
 }
 
 extern "C" size_t fg_layer_backward_weights_bf16_workspace_bytes(int64_t max_rows, int32_t d_in, int32_t d_out) {
     if (max_rows < 0 || d_in <= 0 || d_out <= 0) return 0;
-    return wg_stage_plan(max_rows, d_in, d_out).total;
+    return wg_plan(max_rows, d_in, d_out, true).total;
 }
 
 extern "C" fg_status_t fg_layer_backward_weights_bf16(const void* h_src_dev, int32_t n_src, int64_t src_stride, fg_dtype_t src_dtype,
@@ -1173,43 +1098,21 @@ extern "C" fg_status_t fg_layer_backward_weights_bf16(const void* h_src_dev, int
     if (((uintptr_t)h_src_dev | (uintptr_t)agg_dev | (uintptr_t)dh_dev | (uintptr_t)h_dev | (uintptr_t)src_stride | (uintptr_t)agg_stride |
          (uintptr_t)dh_stride | (uintptr_t)h_stride) & 3)
         FG_FAIL(FG_ERR_INVALID_ARG, "%s: h_src, agg, dh, h and their strides must be 4-byte aligned", who);
-    const WgStage P = wg_stage_plan(max_rows, d_in, d_out);
+    const WgPlan P = wg_plan(max_rows, d_in, d_out, true);
     if (!ws_dev || ws_bytes < P.total) FG_FAIL(FG_ERR_SHAPE, "%s: workspace of %zu bytes given, %zu needed", who, ws_bytes, P.total);
     if ((uintptr_t)ws_dev & 15) FG_FAIL(FG_ERR_INVALID_ARG, "%s: the workspace must be 16-byte aligned", who);
     fg_clear_error();
     hipStream_t st = (hipStream_t)stream;
-    unsigned short* xt = (unsigned short*)ws_dev;
-    unsigned short* dzt = (unsigned short*)((char*)ws_dev + P.dzt);
+    float* part_w = (float*)ws_dev;
     float* part_b = (float*)((char*)ws_dev + P.part_b);
-    // without rows (or without anything they could index) nothing is staged and the product below is over nothing
+    // without rows (or without anything they could index) every chunk is empty and the partials are zeros
     const int64_t rows_bound = (n > 0 && n_src > 0) ? max_rows : 0;
-    const int tiles_k = (int)(P.kp / ST_TILE), tiles_x = (int)fg_ceil_div(2 * d_in, ST_TILE), tiles_z = (int)fg_ceil_div(d_out, ST_TILE);
-    hipLaunchKernelGGL(weight_grad_stage_bf16_kernel, dim3((unsigned)tiles_k, (unsigned)(tiles_x + tiles_z)), dim3(BW_THREADS), 0, st,
-                       (const char*)h_src_dev, n_src, src_stride, (int)src_dtype, (const char*)agg_dev, agg_stride, (const char*)dh_dev,
-                       dh_stride, (const char*)h_dev, h_stride, n, rows_dev, n_rows_dev, rows_bound, d_in, d_out, tiles_x, xt, dzt, P.kp,
-                       part_b);
-    FG_LAUNCH_CHECK("weight_grad_stage_bf16_kernel");
-    // dW [2*d_in x d_out] = XT . DZT^T: the forward kernel with XT's rows as its rows (both halves of its K from the one
-    // matrix), DZT as the transposed weights, K = the rows there are (a count in device memory, or the bound)
-    const int64_t half_k = P.kp / 2;
-    const int64_t* k_limit = nullptr;
-    // the count the K loop stops at must be min(*n_rows_dev, rows_bound): the staging kernel zero-fills up to the end of
-    // that block of 64; with a host-side bound only, the whole of Kp is valid (zeros beyond the rows)
-    if (n_rows_dev && rows_bound == max_rows) k_limit = n_rows_dev;
-    if (rows_bound == 0) {      // nothing staged: dW = 0 without touching the (unwritten) operands
-        fg_status_t rc = fg_launch_fill_i32((int32_t*)dw_dev, (int64_t)2 * d_in * d_out, 0, st);
-        if (rc != FG_OK) return rc;
-    } else {
-        fg_status_t rc = fg_launch_linear_bf16(xt, 2 * d_in, P.kp * 2, FG_BF16, xt + half_k, P.kp * 2, nullptr, nullptr, 2 * d_in,
-                                               (int32_t)half_k, d_out, dzt, nullptr, 0, dw_dev, 2 * d_in, (int64_t)d_out * 4, FG_F32, st,
-                                               true, k_limit);
-        if (rc != FG_OK) return rc;
-    }
-    if (db_dev) {
-        const int b_blocks = (int)fg_ceil_div(d_out, 128);
-        hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3((unsigned)b_blocks), dim3(BW_THREADS), 0, st, part_b, part_b, tiles_k, (int64_t)0,
-                           d_out, 0, dw_dev, db_dev);
-        FG_LAUNCH_CHECK("weight_grad_reduce_kernel");
-    }
-    return FG_OK;
+    const WgIn A = {(const char*)h_src_dev, (const char*)agg_dev, (const char*)dh_dev, (const char*)h_dev, src_stride, agg_stride, dh_stride,
+                    h_stride, rows_bound, rows_dev, n_rows_dev, n_src, n, d_in, P.d_pad, d_out, P.n_chunks, P.tiles_m, P.tiles_n};
+#define FG_WG(SRC)                                                                                                                        \
+    (P.tm == 256 ? wg_launch(weight_grad_tile_kernel<256, 256, 1, SRC>, 1, P, A, part_w, part_b, dw_dev, db_dev, st)                      \
+                 : wg_launch(weight_grad_tile_kernel<128, 128, 1, SRC>, 1, P, A, part_w, part_b, dw_dev, db_dev, st))
+    if (src_dtype == FG_F32) return FG_WG(FG_F32);
+    return src_dtype == FG_F16 ? FG_WG(FG_F16) : FG_WG(FG_BF16);
+#undef FG_WG
 }

@@ -770,8 +770,7 @@ fg_status_t fg_launch_linear_bf16(const void* h_src, int32_t n_src, int64_t src_
                                   const void* agg, int64_t agg_stride, const int32_t* rows_dev,
                                   const int64_t* n_rows_dev, int64_t max_rows, int32_t d_in, int32_t d_out, const void* W,
                                   const float* bias, int32_t relu, void* h_out, int32_t n_out, int64_t out_stride,
-                                  fg_dtype_t out_dtype, hipStream_t st, bool w_nk, const int64_t* k_limit_dev = nullptr,
-                                  const int32_t* src_ids_dev = nullptr);
+                                  fg_dtype_t out_dtype, hipStream_t st, bool w_nk, const int32_t* src_ids_dev = nullptr);
 
 // fg_linear (src_ids_dev == NULL: the own features of position r are row r of h_src) and fg_linear_ids (row src_ids_dev[r])
 static fg_status_t linear_launch(const char* who, const void* h_src, int32_t n_src, int64_t src_stride, fg_dtype_t in_dtype,
@@ -876,7 +875,7 @@ static fg_status_t linear_launch(const char* who, const void* h_src, int32_t n_s
     }
     if (w_dtype == FG_BF16)
         return fg_launch_linear_bf16(h_src, n_src, src_stride, in_dtype, agg, agg_stride, rows_dev, n_rows_dev, max_rows,
-                                     d_in, d_out, W, bias, relu, h_out, n_out, out_stride, out_dtype, st, false, nullptr, src_ids_dev);
+                                     d_in, d_out, W, bias, relu, h_out, n_out, out_stride, out_dtype, st, false, src_ids_dev);
     FG_FAIL(FG_ERR_DTYPE, "%s: weights must be F32 or BF16", who);
 }
 

@@ -1182,6 +1182,62 @@ def test_layer_backward_weights_bf16_match_oracle(env, src, d_in, d_out, n, n_ro
     assert e <= REL_TOL_F32 and e_b <= REL_TOL_F32, f"rel err dW {e:.3e}, db {e_b:.3e}"
 
 
+@pytest.mark.parametrize("kind,src,d_in,d_out,n,n_rows,rows,relu", [
+    ("f32", "f32", 68, 132, 32768, 32767, "list", True),          # 256 x 128 tiles, halves padded to 128 columns
+    ("f32", "f32", 128, 64, 33000, 100, "list", False),            # most chunks without a row
+    ("f32", "f32", 64, 128, 33000, 33000, "all", True),            # many rows, one tile of 128
+    ("f32", "f32", 60, 36, 2049, 2000, "bad", True), ("f32", "f32", 132, 260, 300, 33, "bad", False),
+    ("bf16", "f16", 136, 264, 12000, 11111, "list", True),         # 256 x 256 tiles, ragged in both directions
+    ("bf16", "bf16", 136, 264, 12000, 12000, "all", False), ("bf16", "f32", 136, 264, 12000, 65, "bad", True),
+    ("bf16", "f16", 520, 136, 5500, 5400, "bad", True), ("bf16", "f32", 72, 40, 1000, 999, "bad", True),
+    ("f32", "f32", 64, 64, 500, 480, "short", True), ("bf16", "bf16", 64, 64, 500, 480, "short", True)])
+def test_weight_gradients_tiles_and_chunks(env, kind, src, d_in, d_out, n, n_rows, rows, relu):
+    """Both tile sizes of the weight gradients, at sizes that no tile, chunk or step divides; lists that name every position
+    ("all": no list at all), some, positions that do not exist ("bad": they contribute nothing) and positions without own
+    features ("short": left out of the fp32 product, zeros in the mixed one), in a workspace that holds NaN patterns. Reference: torch in fp64 on the operands as the product takes them."""
+    torch, B = env
+    g = torch.Generator(device="cuda").manual_seed(n + d_in)
+    bf = kind == "bf16"
+    tdt = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}
+    code = {"f16": B.FG_F16, "bf16": B.FG_BF16, "f32": B.FG_F32}
+    act_t = torch.bfloat16 if bf else torch.float32
+    n_src = n - 40 if rows == "short" else n + 7
+    rnd = lambda *shape: torch.randn(*shape, device="cuda", generator=g)
+    h_src, agg, dh, h = rnd(n_src, d_in).to(tdt[src]), rnd(n, d_in).to(act_t), rnd(n, d_out), rnd(n, d_out).to(act_t)
+    pos = torch.arange(n, device="cuda") if rows == "all" else torch.sort(torch.randperm(n, device="cuda", generator=g)[:n_rows])[0]
+    lst = torch.zeros(n, dtype=torch.int32, device="cuda")
+    lst[:n_rows] = pos.int()
+    good = torch.ones(n_rows, dtype=torch.bool, device="cuda")
+    if rows == "bad":
+        good[::5] = False
+        lst[:n_rows][~good] = torch.tensor([-1, n, n_src + 3], dtype=torch.int32, device="cuda").repeat(n_rows)[:int((~good).sum())]
+    if rows == "short" and not bf:
+        good = pos < n_src
+    own = torch.where((pos < n_src)[:, None], h_src[pos.clamp(max=n_src - 1)], torch.zeros_like(h_src[:1]))
+    x = torch.cat([own.to(torch.bfloat16) if bf else own, agg[:n_rows]], 1)
+    dz = torch.where(h[pos] > 0, dh[pos], torch.zeros_like(dh[pos])) if relu else dh[pos]
+    x, dz = x[good], dz[good]
+    want = x.double().t() @ (dz.to(torch.bfloat16) if bf else dz).double()
+    want_b = dz.double().sum(0)
+    cnt = dev(torch, np.asarray([n_rows], dtype=np.int64))
+    size = B.fg_layer_backward_weights_bf16_workspace_bytes if bf else B.fg_layer_backward_weights_workspace_bytes
+    wsb = size(n, d_in, d_out)
+    assert all(size(m, d_in, d_out) <= wsb for m in (0, 1, 32, 64, n // 2, n - 1))      # a workspace serves fewer rows too
+    ws = torch.full((wsb,), 255, dtype=torch.uint8, device="cuda")
+    dw, db = torch.full((2 * d_in, d_out), 3.0, device="cuda"), torch.full((d_out,), 3.0, device="cuda")
+    lst_arg, act_arg, asz = None if rows == "all" else lst, h if relu else None, 2 if bf else 4
+    if bf:
+        B.fg_layer_backward_weights_bf16(h_src, n_src, d_in * h_src.element_size(), code[src], agg, d_in * 2, dh, d_out * 4, act_arg,
+                                         d_out * asz, n, lst_arg, cnt, n, d_in, d_out, dw, db, ws, wsb)
+    else:
+        B.fg_layer_backward_weights(h_src, n_src, d_in * 4, agg, d_in * 4, dh, d_out * 4, act_arg, d_out * asz, n, lst_arg, cnt, n,
+                                    d_in, d_out, dw, db, ws, wsb)
+    e, e_b = float((dw.double() - want).norm() / want.norm()), float((db.double() - want_b).norm() / want_b.norm())
+    # random products: a sum of k of them in fp32 steps of 16 is off by about sqrt(k / 16) half-ulps of its own size at most,
+    # 32 of them for the longest chunk here (a chunk has at most 512 rows); the bias sums are fp64 over fp32 sums of eight
+    assert e <= 32 * 2.0 ** -24 and e_b <= 8 * 2.0 ** -24, f"rel err dW {e:.3e}, db {e_b:.3e}"
+
+
 def test_iterations_gcn_layers_with_backward_pass(env):
     """GCN layers with the gradient norms from the backward pass (input and weight gradients of every layer)."""
     torch, B = env
