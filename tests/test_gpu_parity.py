@@ -759,6 +759,51 @@ def test_sample_block_matches_oracle(env, N, max_deg, hubs, n_seeds, fanouts, sl
                 assert got["col_ids"][l] == want["col_ids"][l]
 
 
+@pytest.mark.parametrize("N,max_deg,n_seeds,fanout,bound,seed", [
+    (9000, 30, 1024, 11, 1024, 0), (9000, 30, 1023, 11, 1024, 1),      # the largest layer of one workgroup, nearly every draw new
+    (9000, 30, 1025, 11, 1025, 2), (9000, 30, 1000, 12, 1000, 3),       # one row, one draw more
+    (40, 60, 40, 11, 1024, 4), (3000, 3, 1, 1, 1, 5), (3000, 40, 0, 5, 7, 6),      # many repeats, one row, none
+    (5000, 50, 1500, 8, 1501, 7), (5000, 50, 1500, 9, 1600, 8), (5000, 50, 1500, 16, 1500, 9), (5000, 50, 1500, 17, 1500, 10),
+    (4000, 40, 2600, 15, 600_000, 11)])                                 # a bound beyond what a workgroup adds up for itself
+def test_sample_block_routes_match_oracle(env, N, max_deg, n_seeds, fanout, bound, seed):
+    """One block at the sizes where fg_sample_block changes its launches (one workgroup or several, 8, 16 or 32 lanes per row,
+    the counts of the candidates' workgroups added up by each or once), bit for bit."""
+    torch, B = env
+    from oracle import sampler_oracle as S
+    indptr, indices = _random_multigraph(N, max_deg, seed, hubs=3)
+    seeds = np.random.default_rng(seed).permutation(N)[:n_seeds]
+    want = S.sample_minibatch(indptr, indices, seeds, (fanout,), 77 + seed)
+    got = _device_sample(torch, B, dev(torch, indptr), dev(torch, indices), N, seeds, (fanout,), 77 + seed, bound - n_seeds)
+    for key, l in (("ids", 0), ("start", 1), ("end", 1), ("col", 1), ("col_ids", 1)):
+        assert got[key][l] == want[key][l], key
+
+
+@pytest.mark.parametrize("n,n_src,deg,src_bound,nnz_bound", [
+    (1500, 12288, 8, 12288, 12288), (1500, 12288, 8, 12288, 12289), (1500, 12288, 8, 12289, 12288), (2500, 5, 4, 9, 12000),
+    (1, 1, 1, 1, 1), (900, 7000, 21, 131_073, 20_000), (900, 7000, 21, 131_072, 20_000)])
+def test_transpose_block_routes(env, n, n_src, deg, src_bound, nnz_bound):
+    """The transpose at the sizes where fg_transpose_block changes its launches: one workgroup or several, counters added up
+    directly or through per-workgroup sums. Every row names `deg` sources; few sources make lists of thousands."""
+    torch, B = env
+    from oracle import sampler_oracle as S
+    r = np.random.default_rng(n)
+    start, end = (np.arange(n) * deg).astype(np.int32), (np.arange(n) * deg + deg).astype(np.int32)
+    col = r.integers(0, n_src, size=n * deg).astype(np.int32)
+    want = S.transpose_block(start, end, col, n_src)
+    t_start, t_end = (torch.full((src_bound,), -3, dtype=torch.int32, device="cuda") for _ in range(2))
+    t_row = torch.full((nnz_bound,), -3, dtype=torch.int32, device="cuda")
+    cnt = torch.tensor([n, n_src], dtype=torch.int64, device="cuda")
+    wsb = B.fg_transpose_block_workspace_bytes(src_bound)
+    ws = torch.full((wsb,), 255, dtype=torch.uint8, device="cuda")
+    col_t = torch.zeros(nnz_bound, dtype=torch.int32, device="cuda")
+    col_t[:len(col)] = dev(torch, col)
+    B.fg_transpose_block(dev(torch, start), dev(torch, end), col_t, cnt.data_ptr(), n, cnt.data_ptr() + 8, src_bound, nnz_bound,
+                         t_start, t_end, t_row, ws, wsb)
+    assert t_start.cpu().numpy()[:n_src].tolist() == want[0] and t_end.cpu().numpy()[:n_src].tolist() == want[1]
+    assert t_row.cpu().numpy()[:n * deg].tolist() == want[2] and set(t_row.cpu().numpy()[n * deg:].tolist()) <= {-3}
+    assert set(t_start.cpu().numpy()[n_src:].tolist() + t_end.cpu().numpy()[n_src:].tolist()) <= {n * deg}
+
+
 @pytest.mark.parametrize("n,n_src,max_deg,slack,seed", [(0, 4, 3, 2, 0), (1, 1, 0, 0, 1), (700, 3000, 12, 50, 2), (6000, 40000, 15, 0, 3),
                                                         (3000, 40, 10, 7, 4)])
 def test_transpose_block_matches_oracle(env, n, n_src, max_deg, slack, seed):
