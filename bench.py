@@ -418,7 +418,7 @@ def main():
                       note="lookup+gather+aggregate path (top-down pass, loader with the cache fetch, aggregations of the upper "
                            "layers; aggregations that run inside a dense update's launch are counted with that update), one stream, every call bracketed")
     # table rows the loader would read with the caches empty: every edge of block 1 plus every layer-1 node's own row
-    if args.no_fuse:
+    if args.no_fuse or hp.reads_rows_once(batches[steps_it[0]]):
         rows_no_cache = n0_all
     else:
         rows_no_cache = float(np.mean([batches[it].nnz[1] + batches[it].n[1] for it in steps_it]))
@@ -574,6 +574,11 @@ def loader_bytes(hp, w, batches, its, counts, fused, ids_cols, model):
     # table row read + one row written. The edges under normal rows are what is left in the pruned blocks (rows that are
     # not normal have end = start).
     edges = [float((batches[it].end[1] - batches[it].start[1]).sum().item()) for it in its]
+    if hp.reads_rows_once(batches[its[0]]):
+        # every surviving input row once from the table (id, row read, row written), then the mean from those rows
+        inputs = [float(hp.input_log[it % hp.ring][2].item()) for it in its]
+        gather_bytes = float(np.mean([u * (4 + 2 * feat_row) + e * (4 + feat_row) + c[1][2] * (12 + agg_row) for u, e, c in zip(inputs, edges, counts)]))
+        return gather_bytes, float(np.mean(inputs)), "gather_rows_kernel (fg_gather of every surviving input row), then aggregate_mean_kernel"
     own_row = (4 + feat_row) if model == "gcn" else (4 + 2 * feat_row)   # GCN: the own row enters the mean, no copy
     own_by_linear = hp.own_rows_from_table(batches[its[0]])               # the dense update reads the own rows itself
     if own_by_linear:
@@ -620,7 +625,7 @@ def policy_paper_run(w, feat, sampled, args, ids_cols):
         counts_all = [counts_log[it % hp.ring] for it in steps_it]
         nbytes, _, kernel = loader_bytes(hp, w, batches, roof_it, counts, fused, ids_cols, args.model)
         _, rows_read, _ = loader_bytes(hp, w, batches, steps_it, counts_all, fused, ids_cols, args.model)
-        if fused:
+        if fused and not hp.reads_rows_once(batches[steps_it[0]]):
             rows_no_cache = float(np.mean([batches[it].nnz[1] + batches[it].n[1] for it in steps_it]))
         else:
             rows_no_cache = float(np.mean([batches[it].n[0] for it in steps_it]))

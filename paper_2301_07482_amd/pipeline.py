@@ -203,7 +203,7 @@ class HotPath:
         self.on_host = 1 if features_on_host else 0
         self.use_cache = use_cache
         # fused_input: layer 1 aggregates straight from the feature table (fg_gather_aggregate); only the layer-1
-        # nodes' own rows are gathered into H[0] and the top-down pass stops at layer 1
+        # nodes' own rows are gathered into H[0] and the top-down pass stops at layer 1 (except where `reads_rows_once`)
         self.fused_input = fused_input
         # copy_own_rows: the loader also copies the layer-1 nodes' own rows into H[0] for the dense update. Off: the dense
         # update of layer 1 reads them from the table itself by node id (fg_linear_ids), where `own_rows_from_table` allows
@@ -266,6 +266,7 @@ class HotPath:
         self.stats_log = torch.zeros((self.ring, L + 1, 4), dtype=torch.int64, device=dev)
         self.counts = self.counts_log[0]
         self.stats = self.stats_log[0]
+        self.input_log = torch.zeros((self.ring, 3), dtype=torch.int64, device=dev)   # layer 0's counts where `reads_rows_once`
         ws_bytes = max(max(B.fg_workspace_bytes(B.FG_WS_LOOKUP_PRUNE, n[l]) for l in range(L + 1)),
                        max([B.fg_workspace_bytes(B.FG_WS_CACHE_UPDATE, n[l]) for l in range(1, L)] or [0]))
         self.ws = torch.zeros(ws_bytes + 256, dtype=torch.uint8, device=dev)
@@ -381,7 +382,7 @@ class HotPath:
     def _top_down(self, bt, it, st, tick):
         """Lookup, prune, V_normal for layers L .. 0 (or 1 with the fused loader) of mini-batch `bt` on stream `st`, into the
         currently bound lists."""
-        L, fused = self.L, self.fused_input
+        L, fused = self.L, self.fused_input and not self.reads_rows_once(bt)
         lowest = 1 if fused else 0
 
         def layer_args(l):
@@ -395,7 +396,7 @@ class HotPath:
                         hit_dev=self.hit[l], hit_pos_dev=self.hit_pos[l], hit_slot_dev=self.hit_slot[l],
                         normal_pos_dev=self.normal_pos[l],
                         normal_ids_dev=self.input_ids if l == 0 else (self.self_ids if (fused and l == 1) else None),
-                        counts_dev=self._cnt(l, 0), n_dev=bt.n_dev[l])
+                        counts_dev=self._cnt(l, 0) if l or not self.fused_input else self.input_counts.data_ptr(), n_dev=bt.n_dev[l])
 
         if self.one_launch_top_down:
             tick("top_down")
@@ -429,6 +430,7 @@ class HotPath:
         self.__dict__.update(self._lists[it % 3])
         self.counts = self.counts_log[it % self.ring]
         self.stats = self.stats_log[it % self.ring]
+        self.input_counts = self.input_log[it % self.ring]
 
     def run(self, bt, it, update=True, timer=None, next_bt=None, hold_second_stream=False):
         """One iteration on torch's current stream. `timer(name, stream)` (optional) is called before each C-ABI call
@@ -458,7 +460,8 @@ class HotPath:
             "layer sizes in device memory go through fg_top_down and fg_cache_update_all"
         if any(bt.n[l] > self.n_max[l] for l in range(L + 1)):
             bt.n = [min(bt.n[l], self.n_max[l]) for l in range(L + 1)]
-        fused = self.fused_input
+        once = self.reads_rows_once(bt)
+        fused = self.fused_input and not once
         promised = self._td_for is not None
         pruned_ahead = promised and self._td_for[0] == it and self._td_for[1] is bt
         self._td_for = None
@@ -536,13 +539,13 @@ class HotPath:
         #      copies the layer-1 nodes' own rows into H[0])
         d0b = self.dims[0] * esz[self.feat_code]
         if not fused:
-            tick("gather_features")
+            tick("gather_aggregate[1]" if once else "gather_features")
             if self.feature_side:
                 B.fg_gather_features(self.cache, self.feat, self.num_nodes, d0b, d0b, self.input_ids, self.normal_pos[0],
                                      self._cnt(0, 2), bt.n[0], self.H[0], bt.n[0], d0b, self.on_host, st)
             else:
-                B.fg_gather(self.feat, self.num_nodes, d0b, d0b, self.input_ids, self.normal_pos[0], self._cnt(0, 2), bt.n[0],
-                            self.H[0], bt.n[0], d0b, self.on_host, st)
+                B.fg_gather(self.feat, self.num_nodes, d0b, d0b, self.input_ids, self.normal_pos[0],
+                            self.input_counts.data_ptr() + 16 if once else self._cnt(0, 2), bt.n[0], self.H[0], bt.n[0], d0b, self.on_host, st)
         # ---- bottom-up: cached rows, mean aggregation, dense update
         for l in range(1, L + 1):
             if beside and hold_second_stream and l == 2:     # (a cache has layers, so L >= 2 here)
@@ -563,7 +566,8 @@ class HotPath:
                                               self._cnt(1, 2), bt.n[1], bt.ids[0], bt.n[0], self.feat, self.num_nodes, d0b,
                                               self.dims[0], self.MEANPOS_l[1], self.AGG_l[1], st)
                 else:
-                    tick(f"aggregate[{l}]")
+                    if l > 1 or not once:
+                        tick(f"aggregate[{l}]")
                     B.fg_aggregate_gcn(bt.start[l], bt.end[l], bt.col[l], bt.nnz[l], bt.n[l], self.normal_pos[l], self._cnt(l, 2),
                                        bt.n[l], self.H[l - 1], bt.n[l - 1], in_b, self.dims[l - 1], self.MEANPOS_l[l], self.AGG_l[l], st)
                 tick(f"linear[{l}]")
@@ -593,7 +597,8 @@ class HotPath:
                 else:
                     B.fg_gather_aggregate(*args)
             else:
-                tick(f"aggregate[{l}]")
+                if l > 1 or not once:
+                    tick(f"aggregate[{l}]")
                 B.fg_aggregate(bt.start[l], bt.end[l], bt.col[l], bt.nnz[l], bt.n[l], self.normal_pos[l], self._cnt(l, 2),
                                bt.n[l], self.H[l - 1], bt.n[l - 1], in_b, self.dims[l - 1], in_code, self.AGG_l[l], agg_b,
                                self.agg_code, st)
@@ -699,6 +704,15 @@ class HotPath:
         return (not self.copy_own_rows and self.fused_input and self.model == "sage" and not self.feature_side and not self.on_host
                 and self.comp_code == B.FG_F32 and self.feat_code == B.FG_F32 and not self.weight_grads
                 and getattr(bt, "col_ids1", None) is not None and not self.one_launch(1, bt.n[1]))
+
+    def reads_rows_once(self, bt):
+        """Whether the loader of this mini-batch reads every surviving input row over the host link once, into H[0], and
+        aggregates layer 1 from there, instead of reading a row for every edge that names it: a table in host memory, and
+        4 MB of edges' rows at least (less than that takes the link under 0.1 ms, and the fused loader is one launch of the
+        four). A quarter of the rows a papers-like mini-batch reads are named more than once: 5.29 ms with the fused loader,
+        3.95 ms so. (Not with raw features in the cache's buffer: most of the rows named often are read from there.)"""
+        return bool(self.on_host and self.fused_input and not self.feature_side
+                    and bt.nnz[1] * self.dims[0] * B.DTYPE_SIZE[self.feat_code] >= 4 << 20)
 
     # ---- read-back helpers for tests and reports (synchronising) -------------------------------------------
     def snapshot(self, bt):

@@ -2279,6 +2279,29 @@ def test_iterations_large_host_resident_separate_gather(env):
     print(f"large_host, separate gather: {hits} hits, worst rel err {worst:.3e}")
 
 
+@pytest.mark.parametrize("model,backward,device_sampler", [("sage", False, False), ("sage", True, True), ("gcn", False, False)])
+def test_iterations_host_table_rows_read_once(env, model, backward, device_sampler):
+    """A host table under the fused loader, on both sides of the size from which every input row is read once into HBM (a
+    mini-batch of four seeds stays with the fused loader): everything as the oracle has it."""
+    torch, B = env
+    import dataclasses
+    from paper_2301_07482_amd.pipeline import HotPath
+    base = wl.WORKLOADS["medium"]
+    for batch, once in ((4, False), (256, True)):
+        w = dataclasses.replace(base, num_nodes=60_000, num_edges=900_000, batch=batch, cache_capacity=9000, feat_location="host",
+                                t_stale=3, feat_dim=104)
+        seen = []
+        plain = HotPath.reads_rows_once
+        HotPath.reads_rows_once = lambda self, bt: seen.append(plain(self, bt)) or seen[-1]
+        try:
+            hits, worst = run_workload_parity(torch, w, 6, fused=True, col_ids=model == "sage" and not device_sampler, lookahead=not backward,
+                                              model=model, backward=backward, device_sampler=device_sampler, device_counts=device_sampler)
+        finally:
+            HotPath.reads_rows_once = plain
+        assert seen and all(s == once for s in seen), (batch, seen)
+        print(f"host table, batch {batch}, {model}: {hits} hits, worst rel err {worst:.3e}")
+
+
 # ------------------------------------------------------------------------------------------------ bf16 path
 
 @pytest.mark.parametrize("src,d_in,d_out,n_rows,max_rows,relu,out", [("f16", 768, 1024, 700, 900, True, "bf16"),
