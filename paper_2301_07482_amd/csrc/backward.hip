@@ -30,29 +30,63 @@ __device__ __forceinline__ double wave_max(double v) {
     return v;
 }
 
-// one wavefront per row: p = softmax(h[i, :]) in fp64, dh[i, c] = (p[c] - [c == label]) / n
+// p = softmax(h[i, :]) in fp64, dh[i, c] = (p[c] - [c == label]) / n. A row belongs to WAVES wavefronts, one or (wide rows) the
+// four of a workgroup. A row of up to 64 * WAVES * SM_KEEP columns is read once, its exponentials, which are what the kernel
+// spends its time on, are formed once and stay in registers; beyond that they are formed again for the result.
+// 1024 rows of 1024 columns: 15.0 us with one wavefront per row and every exponential twice, 7.5 now; of 256: 5.8, now 5.0.
+constexpr int SM_KEEP = 4;
+template <int WAVES>
 __global__ __launch_bounds__(BW_THREADS) void softmax_xent_grad_kernel(const char* __restrict__ h, int64_t h_stride,
                                                                        const int32_t* __restrict__ labels, int n, int d,
                                                                        char* __restrict__ dh, int64_t dh_stride) {
-    const int lane = threadIdx.x & 63;
-    const int64_t n_waves = ((int64_t)gridDim.x * BW_THREADS) >> 6;
-    for (int64_t i = ((int64_t)blockIdx.x * BW_THREADS + threadIdx.x) >> 6; i < n; i += n_waves) {
+    __shared__ double red[2][BW_THREADS / 64];
+    constexpr int LANES = 64 * WAVES;
+    const int lane = threadIdx.x % LANES;
+    const int64_t n_groups = (int64_t)gridDim.x * (BW_THREADS / LANES);
+    // over the row's wavefronts (WAVES == 1: the wavefront has it already)
+    auto combine = [&](double v, int which, bool sum) -> double {
+        if (WAVES == 1) return v;
+        if ((threadIdx.x & 63) == 0) red[which][threadIdx.x >> 6] = v;
+        __syncthreads();
+        double t = red[which][0];
+#pragma unroll
+        for (int w = 1; w < BW_THREADS / 64; ++w) t = sum ? t + red[which][w] : (red[which][w] > t ? red[which][w] : t);
+        return t;
+    };
+    for (int64_t i = ((int64_t)blockIdx.x * BW_THREADS + threadIdx.x) / LANES; i < n; i += n_groups) {      // uniform over the row's wavefronts
         const float* row = (const float*)(h + i * h_stride);
+        const int32_t y = labels[i];
+        float x[SM_KEEP];
+#pragma unroll
+        for (int q = 0; q < SM_KEEP; ++q) x[q] = lane + q * LANES < d ? row[lane + q * LANES] : 0.f;
         double m = -1.0e300;
-        for (int c = lane; c < d; c += 64) {
+#pragma unroll
+        for (int q = 0; q < SM_KEEP; ++q)
+            if (lane + q * LANES < d) m = (double)x[q] > m ? (double)x[q] : m;
+        for (int c = lane + SM_KEEP * LANES; c < d; c += LANES) {
             const double v = (double)row[c];
             m = v > m ? v : m;
         }
-        m = wave_max(m);
-        double s = 0.0;
-        for (int c = lane; c < d; c += 64) s += exp((double)row[c] - m);
-        s = wave_sum(s);
-        const int32_t y = labels[i];
+        m = combine(wave_max(m), 0, false);
+        double e[SM_KEEP], s = 0.0;
+#pragma unroll
+        for (int q = 0; q < SM_KEEP; ++q) {
+            e[q] = lane + q * LANES < d ? exp((double)x[q] - m) : 0.0;
+            s += e[q];
+        }
+        for (int c = lane + SM_KEEP * LANES; c < d; c += LANES) s += exp((double)row[c] - m);
+        s = combine(wave_sum(s), 1, true);
         float* out = (float*)(dh + i * dh_stride);
-        for (int c = lane; c < d; c += 64) {
+#pragma unroll
+        for (int q = 0; q < SM_KEEP; ++q) {
+            const int c = lane + q * LANES;
+            if (c < d) out[c] = (float)((e[q] / s - (c == y ? 1.0 : 0.0)) / (double)n);
+        }
+        for (int c = lane + SM_KEEP * LANES; c < d; c += LANES) {
             const double p = exp((double)row[c] - m) / s;
             out[c] = (float)((p - (c == y ? 1.0 : 0.0)) / (double)n);
         }
+        if (WAVES > 1) __syncthreads();      // before the next row's values go to `red`
     }
 }
 
@@ -104,7 +138,7 @@ __global__ __launch_bounds__(BW_THREADS) void relu_backward_kernel(const char* _
                                                                    const char* __restrict__ h, int64_t h_stride, int n,
                                                                    const int32_t* __restrict__ rows,
                                                                    const int64_t* __restrict__ n_rows_dev, int64_t max_rows,
-                                                                   int d, void* __restrict__ dz_pos_v, void* __restrict__ dz_cmp_v,
+                                                                   int d, int vec, void* __restrict__ dz_pos_v, void* __restrict__ dz_cmp_v,
                                                                    int t_blocks, int t_gx, const float* __restrict__ w, int w_rows,
                                                                    int w_cols, float* __restrict__ wt) {
     if ((int)blockIdx.x < t_blocks) {      // uniform over the workgroup
@@ -121,6 +155,33 @@ __global__ __launch_bounds__(BW_THREADS) void relu_backward_kernel(const char* _
         if (r < 0 || r >= n) continue;
         const float* g = (const float*)(dh + (int64_t)r * dh_stride);
         const char* a = h ? h + (int64_t)r * h_stride : nullptr;
+        if (vec) {      // four columns per lane: each half holds whole groups of four, every address is aligned for them
+            for (int c = 4 * lane; c < d; c += 256) {
+                f32x4 v = *(const f32x4*)(g + c);
+                if (a) {
+                    if constexpr (BF16) {
+                        const uint2 w = *(const uint2*)((const unsigned short*)a + c);
+                        const float act[4] = {__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xFFFF0000u), __uint_as_float(w.y << 16),
+                                              __uint_as_float(w.y & 0xFFFF0000u)};
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) v[q] = act[q] > 0.f ? v[q] : 0.f;
+                    } else {
+                        const f32x4 act = *(const f32x4*)((const float*)a + c);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) v[q] = act[q] > 0.f ? v[q] : 0.f;
+                    }
+                }
+                const int64_t to = c < half ? (int64_t)r * half + c : k * half + (c - half);
+                if constexpr (BF16) {
+                    const uint2 o = {(unsigned int)bw_bf16_bits(v[0]) | ((unsigned int)bw_bf16_bits(v[1]) << 16),
+                                     (unsigned int)bw_bf16_bits(v[2]) | ((unsigned int)bw_bf16_bits(v[3]) << 16)};
+                    *(uint2*)((unsigned short*)(c < half ? dz_pos_v : dz_cmp_v) + to) = o;
+                } else {
+                    *(f32x4*)((float*)(c < half ? dz_pos_v : dz_cmp_v) + to) = v;
+                }
+            }
+            continue;
+        }
         for (int c = lane; c < d; c += 64) {
             float v = g[c];
             if (a) {
@@ -410,10 +471,15 @@ extern "C" fg_status_t fg_softmax_xent_grad(const float* h_dev, int64_t h_stride
         FG_FAIL(FG_ERR_INVALID_ARG, "fg_softmax_xent_grad: pointers and strides must be 4-byte aligned");
     fg_clear_error();
     if (n == 0) return FG_OK;
-    int64_t blocks = fg_ceil_div(n, BW_THREADS / 64);
-    if (blocks > 2048) blocks = 2048;
-    hipLaunchKernelGGL(softmax_xent_grad_kernel, dim3((unsigned)blocks), dim3(BW_THREADS), 0, (hipStream_t)stream, (const char*)h_dev,
-                       h_stride, labels_dev, n, d, (char*)dh_dev, dh_stride);
+    const bool wide = d > 64 * SM_KEEP;      // more than a wavefront keeps in registers
+    int64_t blocks = wide ? n : fg_ceil_div(n, BW_THREADS / 64);
+    if (blocks > 4096) blocks = 4096;
+    if (wide)
+        hipLaunchKernelGGL(softmax_xent_grad_kernel<BW_THREADS / 64>, dim3((unsigned)blocks), dim3(BW_THREADS), 0, (hipStream_t)stream,
+                           (const char*)h_dev, h_stride, labels_dev, n, d, (char*)dh_dev, dh_stride);
+    else
+        hipLaunchKernelGGL(softmax_xent_grad_kernel<1>, dim3((unsigned)blocks), dim3(BW_THREADS), 0, (hipStream_t)stream, (const char*)h_dev,
+                           h_stride, labels_dev, n, d, (char*)dh_dev, dh_stride);
     FG_LAUNCH_CHECK("softmax_xent_grad_kernel");
     return FG_OK;
 }
@@ -494,9 +560,11 @@ static fg_status_t layer_backward_launch(const char* who, int kind, const float*
         int64_t blocks = fg_ceil_div(max_rows, BW_THREADS / 64);
         if (blocks > 4096) blocks = 4096;
         const dim3 tgrid((unsigned)fg_ceil_div(d_out, 32), (unsigned)fg_ceil_div(cols, 32));
+        // four columns at a time where dh and h allow it (1024 rows of 1024 columns 10.8 -> 6.8 us; the halves of dz are workspace, aligned, and d_out is a multiple of 8)
+        const int vec = !(((uintptr_t)dh_dev | (uintptr_t)dh_stride) & 15) && !(((uintptr_t)h_dev | (uintptr_t)h_stride) & (uintptr_t)(4 * esz - 1));
         if (b16) {
             hipLaunchKernelGGL(relu_backward_kernel<true>, dim3((unsigned)blocks), dim3(BW_THREADS), 0, st, (const char*)dh_dev, dh_stride,
-                               (const char*)h_dev, h_stride, n, rows_dev, n_rows_dev, max_rows, d_out, dz_pos, dz_cmp, 0, 1,
+                               (const char*)h_dev, h_stride, n, rows_dev, n_rows_dev, max_rows, d_out, vec, dz_pos, dz_cmp, 0, 1,
                                (const float*)nullptr, 0, 0, (float*)nullptr);
             FG_LAUNCH_CHECK("relu_backward_kernel");
             // dx[r, :] = [dz_pos[r, :] ‖ dz_cmp[k, :]] . W^T, bf16 operands, fp32 sums and result. The weights of this product are
@@ -508,7 +576,7 @@ static fg_status_t layer_backward_launch(const char* who, int kind, const float*
             // (the transposition of W rides in the same launch: tgrid.x * tgrid.y workgroups in front of the others)
             const int t_blocks = (int)(tgrid.x * tgrid.y);
             hipLaunchKernelGGL(relu_backward_kernel<false>, dim3((unsigned)(blocks + t_blocks)), dim3(BW_THREADS), 0, st, (const char*)dh_dev,
-                               dh_stride, (const char*)h_dev, h_stride, n, rows_dev, n_rows_dev, max_rows, d_out, dz_pos, dz_cmp, t_blocks,
+                               dh_stride, (const char*)h_dev, h_stride, n, rows_dev, n_rows_dev, max_rows, d_out, vec, dz_pos, dz_cmp, t_blocks,
                                (int)tgrid.x, (const float*)W, cols, d_out, (float*)wt);
             FG_LAUNCH_CHECK("relu_backward_kernel");
             // dx[r, :] = [dz_pos[r, :] ‖ dz_cmp[k, :]] . W^T for r = rows[k]: the forward GEMM with K = d_out, N = cols

@@ -1227,6 +1227,48 @@ def test_layer_backward_weights_bf16_match_oracle(env, src, d_in, d_out, n, n_ro
     assert e <= REL_TOL_F32 and e_b <= REL_TOL_F32, f"rel err dW {e:.3e}, db {e_b:.3e}"
 
 
+@pytest.mark.parametrize("n,d", [(3, 256), (1031, 257), (5000, 260), (2, 1024), (9, 1025), (4, 2600)])
+def test_loss_gradient_of_wide_rows(env, n, d):
+    """Rows of one wavefront and of four, within and beyond what their registers keep; more rows than workgroups."""
+    torch, B = env
+    r = np.random.default_rng(n + d)
+    h = (r.standard_normal((n, d)) * 4).astype(np.float32)
+    y = r.integers(0, d, size=n).astype(np.int32)
+    out = torch.zeros((n, d + 4), dtype=torch.float32, device="cuda")
+    B.fg_softmax_xent_grad(dev(torch, h), d * 4, dev(torch, y), n, d, out, (d + 4) * 4)
+    assert T.rel_err_rows(out[:, :d].cpu().numpy(), O.softmax_xent_grad(h, y)) <= REL_TOL_F32
+    assert not out[:, d:].any().item()
+
+
+@pytest.mark.parametrize("kind", ["sage", "bf16"])
+@pytest.mark.parametrize("d_out,pad", [(16, 0), (16, 4), (272, 1), (272, 0)])
+def test_layer_backward_strides(env, kind, d_out, pad):
+    """The mask four columns at a time and one at a time (rows of dh and h padded off 16 bytes) give the same gradient."""
+    torch, B = env
+    r = np.random.default_rng(d_out + pad)
+    n, n_src, d_in = 130, 300, 24
+    blk = _random_pruned_block(r, n, n_src, 5)
+    dh, h = r.standard_normal((n, d_out)).astype(np.float32), np.maximum(r.standard_normal((n, d_out)), 0).astype(np.float32)
+    W = (r.standard_normal((2 * d_in, d_out)) / np.sqrt(2 * d_in)).astype(np.float32)
+    act = torch.bfloat16 if kind == "bf16" else torch.float32
+    rows = torch.zeros(n, dtype=torch.int32, device="cuda")
+    rows[:len(blk["rows"])] = dev(torch, blk["rows"])
+    cnt = dev(torch, np.asarray([len(blk["rows"])], dtype=np.int64))
+    wsb = B.fg_layer_backward_workspace_bytes(n, n, d_in, d_out, kind=kind)
+    got = []
+    for p in (0, pad):
+        wide = lambda a, dt: torch.nn.functional.pad(dev(torch, a), (0, p), value=float("nan")).to(dt).contiguous()
+        tdh, th = wide(dh, torch.float32), wide(h, act)
+        out, norms = torch.full((n_src, d_in), 7.0, device="cuda"), torch.full((n_src,), -1.0, device="cuda")
+        ws = torch.full((wsb,), 255, dtype=torch.uint8, device="cuda")
+        B.fg_layer_backward(tdh, (d_out + p) * 4, th, (d_out + p) * th.element_size(), n, rows, cnt, n, dev(torch, blk["live"].astype(np.uint8)),
+                            dev(torch, blk["hit"].astype(np.uint8)), dev(torch, blk["start"]), dev(torch, blk["end"]), dev(torch, blk["ts"]),
+                            dev(torch, blk["te"]), dev(torch, blk["tr"]), len(blk["tr"]), n_src, d_in, d_out, dev(torch, W).to(act), out,
+                            d_in * 4, norms, ws, wsb, kind=kind)
+        got.append((out.cpu().numpy(), norms.cpu().numpy()))
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+
+
 @pytest.mark.parametrize("kind,src,d_in,d_out,n,n_rows,rows,relu", [
     ("f32", "f32", 68, 132, 32768, 32767, "list", True),          # 256 x 128 tiles, halves padded to 128 columns
     ("f32", "f32", 128, 64, 33000, 100, "list", False),            # most chunks without a row
