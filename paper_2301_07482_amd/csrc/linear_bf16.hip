@@ -2,7 +2,7 @@
 // accumulation, bias and ReLU in fp32, output rounded once to bf16 (hidden layers) or kept in fp32 (last layer).
 // Used by the workload whose raw features are fp16 and whose embeddings, weights and cache rows are bf16.
 //
-// K is walked in steps of 64 = four 16-deep MFMA sub-steps. Both operands sit in LDS with k contiguous (rows of 72
+// K is walked in steps of 64 or 128, 16-deep MFMA sub-steps. Both operands sit in LDS with k contiguous (rows of 72 or 136
 // halfwords: 16-byte aligned, conflict-free for the 16-byte operand reads): a lane's MFMA operand is one 16-byte LDS
 // read. A is gathered on the fly (own rows from h_src at the listed positions, converted from fp16 to bf16 if needed;
 // mean rows from the compact agg array). The weights come either transposed, [N x K], and are then loaded and written
@@ -18,8 +18,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int HB_K = 64;
-constexpr int LDH = HB_K + 8;  // halfwords per LDS row: 144 bytes, so that the 16-byte reads of neighbouring rows fall on different banks
+// K per step, and halfwords per LDS row: 144 or 272 bytes, so that the 16-byte reads of neighbouring rows fall on different banks
+constexpr int hb_k(int hb_m, bool w_nk) { return hb_m < 128 && w_nk ? 128 : 64; }
+constexpr int hb_ldh(int hb_m, bool w_nk) { return hb_k(hb_m, w_nk) + 8; }
 
 __device__ __forceinline__ unsigned int f32_to_bf16_bits(float f) {
     const unsigned int b = __float_as_uint(f);
@@ -36,11 +37,13 @@ __device__ __forceinline__ u32x4 f16x8_to_bf16x8(u32x4 v) {
     return __builtin_bit_cast(u32x4, __builtin_convertvector(f, bf16x8));
 }
 
-// HB_M x HB_N: the workgroup's output tile (128 x 128 or 64 x 64). The small tile has four wavefronts as 2 x 2, each
-// owning one block of 32 x 32; it gives layers with few rows enough workgroups to hide the latency of the operand loads
-// behind each other. The 128 x 128 tile has eight wavefronts as 2 x 4, each owning
-// 64 x 32 of it: at under 128 registers a lane, two such workgroups (four wavefronts per SIMD) share a compute unit, and
-// it is wavefronts waiting on different things that keep the matrix cores fed.
+// HB_M x HB_N: the workgroup's output tile (128 x 128 or 64 x 64). The small tile gives layers with few rows enough
+// workgroups to hide the latency of the operand loads behind each other; with weights as [N x K] it has two times four
+// wavefronts (2 x 2, each owning one block of 32 x 32), which share the K of each step of 128: half the barriers and twice the
+// wavefronts (1024 rows x 2048 x 1024: 23.1 us with four and steps of 64, 17.3 so; 700 x 1024 x 512 12.0 -> 10.1; row-major
+// weights, whose reshuffling grows with the step, 19 -> 21, so they keep four). The 128 x 128 tile has eight wavefronts as
+// 2 x 4, each owning 64 x 32 of it: at under 128 registers a lane, two such workgroups (four wavefronts per SIMD) share a
+// compute unit, and it is wavefronts waiting on different things that keep the matrix cores fed.
 // W_NK: the weights are given transposed, [N x K] with k contiguous: their tile is then loaded and written to LDS like
 // the rows of A, 16 bytes at a time, with nothing to reshuffle.
 //
@@ -53,18 +56,18 @@ __device__ __forceinline__ u32x4 f16x8_to_bf16x8(u32x4 v) {
 // exist reads the tile's first row, a k beyond K reads k = 0). Rows and columns that do not exist need no zeroing: an
 // output depends on its own row of A and its own column of W only, and theirs are never written. Only the k values
 // beyond K of a last, partial step are written to LDS as zeros (both operands, so that nothing non-finite meets a zero).
-constexpr size_t hb_lds_bytes(int hb_m, int hb_n) { return (size_t)2 * (hb_m + hb_n) * LDH * 2 + (size_t)hb_m * 8; }
-
-constexpr int hb_waves(int hb_m, int hb_n) { return hb_m * hb_n >= 128 * 128 ? 8 : 4; }
+constexpr int hb_waves(int hb_m, bool w_nk) { return hb_m < 128 && !w_nk ? 4 : 8; }
+constexpr size_t hb_lds_bytes(int hb_m, int hb_n, bool w_nk) { return (size_t)2 * (hb_m + hb_n) * hb_ldh(hb_m, w_nk) * 2 + (size_t)hb_m * 8; }
 
 template <bool SRC_F16, bool OUT_BF16, int HB_M, int HB_N, bool W_NK>
-__global__ __launch_bounds__(64 * hb_waves(HB_M, HB_N), hb_waves(HB_M, HB_N) == 8 ? 4 : 2) void linear_bf16_kernel(
+__global__ __launch_bounds__(64 * hb_waves(HB_M, W_NK), hb_waves(HB_M, W_NK) == 8 ? 4 : 2) void linear_bf16_kernel(
     const char* __restrict__ h_src, int n_src, int64_t src_stride, const char* __restrict__ agg, int64_t agg_stride,
     const int32_t* __restrict__ rows, const int64_t* __restrict__ n_rows_dev, int64_t max_rows, int d_in, int d_out,
     const unsigned short* __restrict__ W, const float* __restrict__ bias, int relu, char* __restrict__ h_out, int n_out,
     int64_t out_stride, int n_tiles, const int32_t* __restrict__ src_ids) {
     extern __shared__ __attribute__((aligned(16))) unsigned short hb_lds[];
-    constexpr int HB_WAVES = hb_waves(HB_M, HB_N), HB_THREADS = 64 * HB_WAVES;
+    constexpr int HB_WAVES = hb_waves(HB_M, W_NK), HB_THREADS = 64 * HB_WAVES, HB_K = hb_k(HB_M, W_NK), LDH = hb_ldh(HB_M, W_NK);
+    constexpr int KW = HB_K / 64;       // wavefronts along K: each takes its part of every step
     constexpr int STAGE = (HB_M + HB_N) * LDH;    // halfwords per buffer: A rows, then the columns of W
     int32_t* row_of = (int32_t*)(hb_lds + 2 * STAGE);   // output position of each row of the tile, -1: none
     int32_t* src_of = row_of + HB_M;                     // the row of h_src with its own features: the position, or src_ids[position]
@@ -194,9 +197,11 @@ __global__ __launch_bounds__(64 * hb_waves(HB_M, HB_N), hb_waves(HB_M, HB_N) == 
     };
 
     const int lane = t & 63, wave = t >> 6;
-    constexpr int WN = HB_WAVES / 2;                           // wavefronts along N (two along M)
+    constexpr int WN = HB_WAVES / KW / 2;                      // wavefronts along N (two along M)
     constexpr int MB = HB_M / 64, NB = HB_N / (32 * WN);       // 32 x 32 blocks per wavefront
-    const int wm = (wave / WN) * (HB_M / 2), wn = (wave % WN) * (HB_N / WN);
+    constexpr int SUB = HB_K / 16 / KW;                        // matrix instructions deep per step and wavefront
+    const int wk = wave / (2 * WN);
+    const int wm = (wave / WN % 2) * (HB_M / 2), wn = (wave % WN) * (HB_N / WN);
     const int l32 = lane & 31, half = lane >> 5;
 
     f32x16 acc[MB][NB];
@@ -206,34 +211,27 @@ __global__ __launch_bounds__(64 * hb_waves(HB_M, HB_N), hb_waves(HB_M, HB_N) == 
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-    // the operands of sub-step kk + 1 are read from LDS while the matrix instructions of sub-step kk run
     auto multiply_step = [&](int buf) {
-        const unsigned short* As = hb_lds + buf * STAGE;
+        const unsigned short* As = hb_lds + buf * STAGE + 16 * SUB * wk;
         const unsigned short* Bt = As + HB_M * LDH;
+        // the operands of sub-step kk + 1 are read from LDS while the matrix instructions of sub-step kk run; with four wavefronts
+        // per SIMD the others cover the LDS latency and the second set of operand registers is not worth its cost
+        constexpr bool AHEAD = HB_WAVES == 4;
         bf16x8 av[2][MB], bv[2][NB];
         auto read_operands = [&](int kk, int set) {
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                const int m = wm + mb * 32 + l32;
-                av[set][mb] = *(const bf16x8*)(As + m * LDH + 16 * kk + 8 * half);
-            }
+            for (int mb = 0; mb < MB; ++mb) av[set][mb] = *(const bf16x8*)(As + (wm + mb * 32 + l32) * LDH + 16 * kk + 8 * half);
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int c = wn + nb * 32 + l32;
-                bv[set][nb] = *(const bf16x8*)(Bt + c * LDH + 16 * kk + 8 * half);
-            }
+            for (int nb = 0; nb < NB; ++nb) bv[set][nb] = *(const bf16x8*)(Bt + (wn + nb * 32 + l32) * LDH + 16 * kk + 8 * half);
         };
-        // with four wavefronts per SIMD the others cover the LDS latency and the second set of operand registers is not worth its cost
-        constexpr bool AHEAD = HB_WAVES == 4;
         if (AHEAD) read_operands(0, 0);
 #pragma unroll
-        for (int kk = 0; kk < HB_K / 16; ++kk) {
-            if (AHEAD) {
-                if (kk + 1 < HB_K / 16) read_operands(kk + 1, (kk + 1) & 1);
-            } else {
-                read_operands(kk, 0);
-            }
+        for (int kk = 0; kk < SUB; ++kk) {
             const int set = AHEAD ? (kk & 1) : 0;
+            if (!AHEAD)
+                read_operands(kk, 0);
+            else if (kk + 1 < SUB)
+                read_operands(kk + 1, (kk + 1) & 1);
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -266,6 +264,21 @@ __global__ __launch_bounds__(64 * hb_waves(HB_M, HB_N), hb_waves(HB_M, HB_N) == 
         __syncthreads();
     }
 
+    if constexpr (KW > 1) {      // the parts of K meet in LDS (the last step's barrier is behind every read of the operands)
+        float* part = (float*)hb_lds + ((wave % (2 * WN)) * MB * NB * 16) * 64 + lane;
+        static_assert((size_t)2 * WN * MB * NB * 16 * 64 * 4 <= (size_t)2 * STAGE * 2, "the partial sums fit in the operands' space");
+        if (wk == 1)
+#pragma unroll
+            for (int b = 0; b < MB * NB; ++b)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) part[(b * 16 + i) * 64] = acc[b / NB][b % NB][i];
+        __syncthreads();
+        if (wk == 1) return;
+#pragma unroll
+        for (int b = 0; b < MB * NB; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[b / NB][b % NB][i] += part[(b * 16 + i) * 64];
+    }
     // accumulator element i of a 32x32 block is row 8*(i/4) + 4*half + i%4, column l32
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
@@ -320,7 +333,7 @@ fg_status_t fg_launch_linear_bf16(const void* h_src, int32_t n_src, int64_t src_
     const int64_t m_tiles = fg_ceil_div(max_rows, tile);
     const unsigned grid = (unsigned)(fg_ceil_div(m_tiles, 8) * 8 * ny);
 #define FG_LB4(F16, OBF, TM, TN, NK)                                                                                       \
-    hipLaunchKernelGGL((linear_bf16_kernel<F16, OBF, TM, TN, NK>), dim3(grid), dim3(64 * hb_waves(TM, TN)), hb_lds_bytes(TM, TN), st, \
+    hipLaunchKernelGGL((linear_bf16_kernel<F16, OBF, TM, TN, NK>), dim3(grid), dim3(64 * hb_waves(TM, NK)), hb_lds_bytes(TM, TN, NK), st, \
                        (const char*)h_src, n_src, src_stride, (const char*)agg, agg_stride, rows_dev, n_rows_dev, max_rows, \
                        d_in, d_out, (const unsigned short*)W, bias, relu, (char*)h_out, n_out, out_stride, ny, src_ids_dev)
 #define FG_LB3(F16, OBF, TM, TN)         \

@@ -2388,6 +2388,36 @@ def test_linear_bf16_matches_oracle(env, src, d_in, d_out, n_rows, max_rows, rel
             assert np.array_equal(t2.cpu().numpy()[sel], ref)
 
 
+@pytest.mark.parametrize("d_in,d_out,n_rows", [(8, 8, 1), (56, 72, 63), (64, 64, 64), (72, 200, 65), (128, 136, 700), (264, 24, 130)])
+@pytest.mark.parametrize("src", ["f16", "bf16"])
+def test_linear_bf16_transposed_weights_small_tile(env, src, d_in, d_out, n_rows):
+    """The 64 x 64 tile with weights as [N x K], whose wavefronts share each step of 128 k values: contractions of a fraction of
+    a step, of whole steps and with a remainder in either half; exact on identity panels."""
+    torch, B = env
+    r = np.random.default_rng(d_in + d_out + n_rows)
+    n_src = n_rows + 9
+    tdt, code = (torch.float16, B.FG_F16) if src == "f16" else (torch.bfloat16, B.FG_BF16)
+    h = dev(torch, r.standard_normal((n_src, d_in)).astype(np.float32)).to(tdt)
+    agg = dev(torch, r.standard_normal((n_rows, d_in)).astype(np.float32)).bfloat16()
+    rows = dev(torch, np.sort(r.permutation(n_src)[:n_rows]).astype(np.int32))
+    bias = dev(torch, r.standard_normal(d_out).astype(np.float32))
+    x = torch.cat([h[rows.long()].bfloat16(), agg], 1).double()
+    W = dev(torch, (r.standard_normal((2 * d_in, d_out)) / np.sqrt(2 * d_in)).astype(np.float32)).bfloat16()
+    eye = torch.zeros((2 * d_in, d_out), device="cuda")
+    k = torch.arange(d_out, device="cuda")
+    eye[(k * 7) % (2 * d_in), k] = 1.0
+    for weights, exact in ((W, False), (eye.bfloat16(), True)):
+        out = torch.full((n_src, d_out), -3.0, device="cuda")
+        B.fg_linear_wt(h, n_src, d_in * 2, code, agg, d_in * 2, rows, None, n_rows, d_in, d_out, weights.t().contiguous(), B.FG_BF16,
+                       None if exact else bias, 0, out, n_src, d_out * 4, B.FG_F32)
+        want = x @ weights.double() + (0.0 if exact else bias.double())
+        got = out[rows.long()].double()
+        # bf16 products are exact in fp32; a sum of at most 528 of them, 16 at a time, is off by a few half-ulps
+        assert bool((got == want).all()) if exact else float((got - want).norm() / want.norm()) <= 8 * 2.0 ** -24
+        out[rows.long()] = -3.0
+        assert bool((out == -3.0).all())
+
+
 def test_iterations_very_large_bf16(env):
     """fp16 features in pinned host memory, bf16 embeddings/weights/cache, bf16 MFMA linear. The node count (and
     with it edges, training subset and cache slots) is divided by 8 so that the table (47 GB instead of 375 GB)
