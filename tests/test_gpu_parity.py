@@ -579,6 +579,34 @@ def test_cache_update_sizes_around_a_workgroups_share(env, n, p):
         B.fg_cache_destroy(cache)
 
 
+@pytest.mark.parametrize("n,d,p", [(1, 4, 1.0), (4096, 4, 1.0), (777, 12, 0.6), (1024, 64, 0.8), (3000, 20, 0.5),      # copied by the selection
+                                   (1024, 64, 0.9), (4096, 28, 0.6), (4097, 4, 0.3)])                               # by a launch of their own
+def test_cache_update_rows_of_small_layers(env, n, d, p):
+    """The rows a small layer's update puts into the cache, on both sides of the size up to which the selecting workgroup copies
+    them itself; a ring that wraps, rows of 16 to 256 bytes."""
+    torch, B = env
+    from paper_2301_07482_amd.pipeline import _tensor_from_ptr
+    r = np.random.default_rng(n + d)
+    N, cap = 9000, max(2, n // 2 + 3)
+    oc = O.HistoricalCache(N, cap, d, 5)
+    cache = B.fg_cache_create(N, [cap], [d], B.FG_F32, 5, None)
+    try:
+        for i in range(2):
+            ids = r.permutation(N)[:n].astype(np.int32)
+            live, gn = np.ones(n, bool), np.exp(r.standard_normal(n)).astype(np.float32)
+            rows = r.standard_normal((n, d)).astype(np.float32)
+            look = O.lookup_prune(oc, i, ids, live, None, None, None, 0)
+            _device_update(torch, B, cache, i, ids, live, gn, p, rows)
+            O.cache_update(oc, i, ids, live, look["hit"], gn, p, rows)
+            tab = _tensor_from_ptr(B.fg_cache_table(cache, 1), (cap, d), torch.float32, cap * d * 4, "cuda").cpu().numpy()
+            at = {int(v): k for k, v in enumerate(ids)}
+            new = [(slot, at[node]) for node, (slot, stamp) in oc.valid_entries(i + 1).items() if stamp == i]
+            assert len(new) == min(cap, int(np.floor(np.float32(p) * n)) if p < 1 else n) or i > 0
+            assert all(np.array_equal(tab[slot], rows[k]) for slot, k in new)
+    finally:
+        B.fg_cache_destroy(cache)
+
+
 def _export(torch, B, cache, cap, it, layer=1):
     t = [torch.zeros(cap, dtype=torch.int32, device="cuda") for _ in range(3)]
     cnt = torch.zeros(2, dtype=torch.int64, device="cuda")
