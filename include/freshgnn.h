@@ -672,9 +672,8 @@ fg_status_t fg_layer_backward_bf16(const float* dh_dev, int64_t dh_stride, const
  *   db[c]    = sum_k dz[k, c]                                                          (db_dev may be NULL)
  * h_src, agg, rows as given to fg_linear for this layer in the forward pass; dh, h (NULL = no activation) by position,
  * n rows. Every fp32 product is formed exactly, on the bf16 matrix cores from three-way splits of both operands as in
- * fg_linear (or on the fp32 matrix instructions where an operand ends beyond 4 GB); fp32 sums within a slice of the rows,
- * fp64 across slices; the slicing depends only on max_rows and the number of rows, so results do not depend on
- * scheduling. Input domain as for fg_linear.
+ * fg_linear; fp32 sums within a chunk of the rows, fp64 across chunks; the chunks depend only on max_rows, the widths and
+ * the number of rows, so results do not depend on scheduling. A workspace for max_rows serves fewer rows too. Input domain as for fg_linear.
  *   ws_dev, ws_bytes    device workspace >= fg_layer_backward_weights_workspace_bytes(max_rows, d_in, d_out), 16-byte aligned
  */
 size_t fg_layer_backward_weights_workspace_bytes(int64_t max_rows, int32_t d_in, int32_t d_out);
@@ -691,10 +690,8 @@ fg_status_t fg_layer_backward_weights(const float* h_src_dev, int32_t n_src, int
  *
  * fg_layer_backward_weights_bf16: the mixed-precision setting. agg and h are bf16, h_src is fp32, fp16 or bf16 (src_dtype;
  * rounded to bf16 as the forward product rounds it); dz is rounded to bf16 before it enters x^T dz, the bias gradient
- * sums the unrounded dz. With both operands bf16 the contraction over the computed rows runs on the bf16 matrix cores:
- * one launch writes x and dz transposed (the contraction index contiguous) into the workspace, the forward matrix-core
- * kernel multiplies them with fp32 sums over all rows (its loop stops at the device-side row count), a last launch adds
- * up the bias gradient's partial sums in fp64. d_in and d_out multiples of 8; pointers and strides 4-byte aligned, dw and
+ * sums the unrounded dz. Both operands are read in place and multiplied on the bf16 matrix cores, with fp32 sums within a
+ * chunk of the rows and fp64 across chunks, as for fp32. d_in and d_out multiples of 8; pointers and strides 4-byte aligned, dw and
  * db 16-byte. Deterministic.
  *   ws_dev, ws_bytes    device workspace >= fg_layer_backward_weights_bf16_workspace_bytes(max_rows, d_in, d_out), 16-byte aligned
  */
