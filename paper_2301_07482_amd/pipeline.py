@@ -379,9 +379,17 @@ class HotPath:
     def _cnt(self, l, k):
         return self.counts.data_ptr() + (l * 3 + k) * 8
 
+    def _fit(self, bt):
+        """Cut a mini-batch's sizes to what the lists and workspaces here are made for. Sizes still on the device are bounds on
+        the host, and a layer cannot outgrow the node count; sizes known on the host have to fit."""
+        assert all(n <= m or d is not None for n, m, d in zip(bt.n, self.n_max, bt.n_dev)), "mini-batch larger than the static bounds"
+        if any(n > m for n, m in zip(bt.n, self.n_max)):
+            bt.n = [min(n, m) for n, m in zip(bt.n, self.n_max)]
+
     def _top_down(self, bt, it, st, tick):
         """Lookup, prune, V_normal for layers L .. 0 (or 1 with the fused loader) of mini-batch `bt` on stream `st`, into the
         currently bound lists."""
+        self._fit(bt)      # an announced mini-batch comes here before the `run` that is for it
         L, fused = self.L, self.fused_input and not self.reads_rows_once(bt)
         lowest = 1 if fused else 0
 
@@ -454,12 +462,9 @@ class HotPath:
         main = torch.cuda.current_stream()      # asked for once: the query costs several microseconds of host time
         st = main.cuda_stream
         do_update = update and self.use_cache and self.cache is not None
-        # sizes still on the device: the host integers are bounds, and a layer cannot outgrow the node count
-        assert all(bt.n[l] <= self.n_max[l] or bt.n_dev[l] is not None for l in range(L + 1)), "mini-batch larger than the static bounds"
         assert all(d is None for d in bt.n_dev) or (self.one_launch_top_down and (self.update_all or not self.use_cache)), \
             "layer sizes in device memory go through fg_top_down and fg_cache_update_all"
-        if any(bt.n[l] > self.n_max[l] for l in range(L + 1)):
-            bt.n = [min(bt.n[l], self.n_max[l]) for l in range(L + 1)]
+        self._fit(bt)
         once = self.reads_rows_once(bt)
         fused = self.fused_input and not once
         promised = self._td_for is not None

@@ -2349,10 +2349,11 @@ def test_iterations_large_host_resident_separate_gather(env):
     print(f"large_host, separate gather: {hits} hits, worst rel err {worst:.3e}")
 
 
-@pytest.mark.parametrize("model,backward,device_sampler", [("sage", False, False), ("sage", True, True), ("gcn", False, False)])
+@pytest.mark.parametrize("model,backward,device_sampler", [("sage", False, False), ("sage", False, True), ("sage", True, True), ("gcn", False, False)])
 def test_iterations_host_table_rows_read_once(env, model, backward, device_sampler):
     """A host table under the fused loader, on both sides of the size from which every input row is read once into HBM (a
-    mini-batch of four seeds stays with the fused loader): everything as the oracle has it."""
+    mini-batch of four seeds stays with the fused loader): everything as the oracle has it. With the device's sampler the
+    larger mini-batch's bound on its input layer exceeds the node count (announced ahead in the case without backward pass)."""
     torch, B = env
     import dataclasses
     from paper_2301_07482_amd.pipeline import HotPath

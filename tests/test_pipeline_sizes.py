@@ -1,0 +1,44 @@
+"""Sizes the host side of the iteration hands to the C calls, checked without a GPU (the calls are recorded, not made)."""
+import types
+
+import pytest
+
+
+def _path(monkeypatch, n_max, on_host):
+    """A HotPath of two layers with lists of n_max positions, as far as its top-down pass looks at it, and the recorded specs."""
+    torch = pytest.importorskip("torch")
+    from paper_2301_07482_amd import pipeline as P
+    calls = []
+    monkeypatch.setattr(P.B, "top_down_layers", lambda specs: calls.append(specs) or specs)
+    monkeypatch.setattr(P.B, "fg_top_down", lambda *a: None)
+    hp = P.HotPath.__new__(P.HotPath)
+    lists = [torch.zeros(n, dtype=torch.int32) for n in n_max]
+    hp.__dict__.update(L=2, n_max=n_max, dims=[128, 16, 16], feat_code=P.B.FG_F32, on_host=on_host, fused_input=True, feature_side=False,
+                       use_cache=False, cache=None, one_launch_top_down=True, ws_td=None, ws_td_bytes=0, live=lists, hit=lists,
+                       hit_pos=lists, hit_slot=lists, normal_pos=lists, input_ids=lists[0], self_ids=lists[1],
+                       counts=torch.zeros((3, 3), dtype=torch.int64), input_counts=torch.zeros(3, dtype=torch.int64))
+    return P, hp, calls
+
+
+def _batch(n, nnz, n_dev):
+    return types.SimpleNamespace(n=list(n), nnz=list(nnz), n_dev=list(n_dev), ids=[None] * 3, start=[None] * 3, end=[None] * 3, col=[None] * 3)
+
+
+@pytest.mark.parametrize("on_host", [0, 1])
+def test_top_down_of_an_announced_mini_batch_stays_within_its_lists(monkeypatch, on_host):
+    """A mini-batch whose sizes are still on the device comes with the sampler's bounds, which may exceed the node count (500
+    here); the pass that runs ahead for it gets the sizes its lists were made for, with the input layer (host table) or without."""
+    P, hp, calls = _path(monkeypatch, [500, 330, 30], on_host)
+    bt = _batch([30 * 11 * 11, 330, 30], [0, 330 * 40, 300], [1, 1, None])
+    hp._top_down(bt, 1, None, P._no_tick)
+    assert len(calls[0]) == (3 if on_host else 2)
+    for spec, n_max in zip(calls[0], reversed(hp.n_max)):
+        assert spec["n"] <= n_max
+    assert [s["n_src"] for s in calls[0] if s["n_src"]] == [330, 500]
+
+
+def test_top_down_refuses_host_sizes_beyond_its_lists(monkeypatch):
+    P, hp, calls = _path(monkeypatch, [500, 330, 30], 1)
+    with pytest.raises(AssertionError):
+        hp._top_down(_batch([501, 330, 30], [0, 13200, 300], [None] * 3), 1, None, P._no_tick)
+    assert not calls
