@@ -267,6 +267,7 @@ class HotPath:
         self.counts = self.counts_log[0]
         self.stats = self.stats_log[0]
         self.input_log = torch.zeros((self.ring, 3), dtype=torch.int64, device=dev)   # layer 0's counts where `reads_rows_once`
+        self.input_slot = 0
         ws_bytes = max(max(B.fg_workspace_bytes(B.FG_WS_LOOKUP_PRUNE, n[l]) for l in range(L + 1)),
                        max([B.fg_workspace_bytes(B.FG_WS_CACHE_UPDATE, n[l]) for l in range(1, L)] or [0]))
         self.ws = torch.zeros(ws_bytes + 256, dtype=torch.uint8, device=dev)
@@ -379,12 +380,19 @@ class HotPath:
     def _cnt(self, l, k):
         return self.counts.data_ptr() + (l * 3 + k) * 8
 
+    def _input_cnt(self, k):
+        return self.input_log.data_ptr() + (self.input_slot * 3 + k) * 8
+
     def _fit(self, bt):
         """Cut a mini-batch's sizes to what the lists and workspaces here are made for. Sizes still on the device are bounds on
         the host, and a layer cannot outgrow the node count; sizes known on the host have to fit."""
+        for n, m in zip(bt.n, self.n_max):      # (as a rule all fit: a loop costs a third of the two generator expressions it stands for)
+            if n > m:
+                break
+        else:
+            return
         assert all(n <= m or d is not None for n, m, d in zip(bt.n, self.n_max, bt.n_dev)), "mini-batch larger than the static bounds"
-        if any(n > m for n, m in zip(bt.n, self.n_max)):
-            bt.n = [min(n, m) for n, m in zip(bt.n, self.n_max)]
+        bt.n = [min(n, m) for n, m in zip(bt.n, self.n_max)]
 
     def _top_down(self, bt, it, st, tick):
         """Lookup, prune, V_normal for layers L .. 0 (or 1 with the fused loader) of mini-batch `bt` on stream `st`, into the
@@ -404,7 +412,7 @@ class HotPath:
                         hit_dev=self.hit[l], hit_pos_dev=self.hit_pos[l], hit_slot_dev=self.hit_slot[l],
                         normal_pos_dev=self.normal_pos[l],
                         normal_ids_dev=self.input_ids if l == 0 else (self.self_ids if (fused and l == 1) else None),
-                        counts_dev=self._cnt(l, 0) if l or not self.fused_input else self.input_counts.data_ptr(), n_dev=bt.n_dev[l])
+                        counts_dev=self._cnt(l, 0) if l or not self.fused_input else self._input_cnt(0), n_dev=bt.n_dev[l])
 
         if self.one_launch_top_down:
             tick("top_down")
@@ -438,7 +446,7 @@ class HotPath:
         self.__dict__.update(self._lists[it % 3])
         self.counts = self.counts_log[it % self.ring]
         self.stats = self.stats_log[it % self.ring]
-        self.input_counts = self.input_log[it % self.ring]
+        self.input_slot = it % self.ring      # (an address below, not a view: a view is 2.5 us of host time, three times an iteration)
 
     def run(self, bt, it, update=True, timer=None, next_bt=None, hold_second_stream=False):
         """One iteration on torch's current stream. `timer(name, stream)` (optional) is called before each C-ABI call
@@ -550,7 +558,7 @@ class HotPath:
                                      self._cnt(0, 2), bt.n[0], self.H[0], bt.n[0], d0b, self.on_host, st)
             else:
                 B.fg_gather(self.feat, self.num_nodes, d0b, d0b, self.input_ids, self.normal_pos[0],
-                            self.input_counts.data_ptr() + 16 if once else self._cnt(0, 2), bt.n[0], self.H[0], bt.n[0], d0b, self.on_host, st)
+                            self._input_cnt(2) if once else self._cnt(0, 2), bt.n[0], self.H[0], bt.n[0], d0b, self.on_host, st)
         # ---- bottom-up: cached rows, mean aggregation, dense update
         for l in range(1, L + 1):
             if beside and hold_second_stream and l == 2:     # (a cache has layers, so L >= 2 here)

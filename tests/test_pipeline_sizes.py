@@ -16,7 +16,7 @@ def _path(monkeypatch, n_max, on_host):
     hp.__dict__.update(L=2, n_max=n_max, dims=[128, 16, 16], feat_code=P.B.FG_F32, on_host=on_host, fused_input=True, feature_side=False,
                        use_cache=False, cache=None, one_launch_top_down=True, ws_td=None, ws_td_bytes=0, live=lists, hit=lists,
                        hit_pos=lists, hit_slot=lists, normal_pos=lists, input_ids=lists[0], self_ids=lists[1],
-                       counts=torch.zeros((3, 3), dtype=torch.int64), input_counts=torch.zeros(3, dtype=torch.int64))
+                       counts=torch.zeros((3, 3), dtype=torch.int64), input_log=torch.zeros((4, 3), dtype=torch.int64), input_slot=0)
     return P, hp, calls
 
 
@@ -42,3 +42,20 @@ def test_top_down_refuses_host_sizes_beyond_its_lists(monkeypatch):
     with pytest.raises(AssertionError):
         hp._top_down(_batch([501, 330, 30], [0, 13200, 300], [None] * 3), 1, None, P._no_tick)
     assert not calls
+
+
+def test_binding_an_iteration_makes_no_view_of_the_input_layers_counts(monkeypatch):
+    """`_bind` runs up to three times per iteration on the host's critical path; the input layer's counts, which only a table
+    in host memory uses, are named by their address alone."""
+    P, hp, _ = _path(monkeypatch, [500, 330, 30], 1)
+    import torch
+
+    class Log:      # anything but its address is too much
+        base = torch.zeros((4, 3), dtype=torch.int64)
+
+        def data_ptr(self):
+            return self.base.data_ptr()
+
+    hp.__dict__.update(ring=4, _lists=[{}, {}, {}], counts_log=torch.zeros((4, 3, 3)), stats_log=torch.zeros((4, 3, 4)), input_log=Log())
+    hp._bind(7)
+    assert hp._input_cnt(2) == Log.base[3, 2].data_ptr()
