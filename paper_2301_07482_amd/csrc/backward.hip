@@ -219,7 +219,8 @@ __global__ __launch_bounds__(BW_THREADS) void relu_backward_kernel(const char* _
 // of dx and is dropped by a select: rows that were not computed hold anything). Measured per layer call (with the matrix
 // product in front), against one walk of the whole chain per piece and one wavefront per hub: 6.1 k rows -> 66 k positions of
 // 256 columns, at most 13 edges each: 47 us (58); the same with hubs of 76: 47 (96); 26 k positions of 88 columns, hubs of
-// 84: 23 (51); 14 k positions of 128 columns, hubs of 639: 41 (648); 7 k positions of 1024 columns: 38 (45).
+// 84: 23 (51); 14 k positions of 128 columns, hubs of 639: 41 (648); 7 k positions of 1024 columns: 38 (45). Layers whose
+// average is beyond a dozen edges: at the rule for the hubs' workgroups.
 struct BwAgg {
     const char* dx;
     int64_t dx_stride;
@@ -265,7 +266,7 @@ __device__ __forceinline__ void bw_add(double* acc, const f32x4 v, const double 
     for (int e = 0; e < 4; ++e) acc[e] += w > 0.0 ? (double)v[e] * w : 0.0;
 }
 
-constexpr int BW_MANY = 16;   // incoming edges from which on a position is taken by a whole workgroup
+constexpr int BW_WAVES = BW_THREADS / 64;
 
 // position j by a group of `lanes` lanes (this lane: `lane`); s0 .. e0 is its range of the transposed block
 // PU: 16-byte pieces of the row a lane holds at a time
@@ -332,14 +333,15 @@ __device__ __forceinline__ void aggregate_backward_row(const BwAgg& A, const int
     }
 }
 
-// A position with many incoming edges by a whole workgroup: its wavefronts take blocks of 64 edges in turn and, where a row
-// has fewer than 64 pieces, the sub-groups of a wavefront take the block's edges in turn; the partial sums meet by
-// shuffles and in LDS, in a fixed order.
-template <bool GCN>
+// A position with many incoming edges by a wavefront, or (JOINT) by a whole workgroup, whose wavefronts take equal blocks of at most
+// 64 edges in turn. Where a row has fewer than 64 pieces, the sub-groups of a wavefront take a block's edges in turn; the
+// partial sums meet by shuffles (and in LDS), in a fixed order.
+template <bool GCN, bool JOINT>
 __device__ __forceinline__ void aggregate_backward_hub(const BwAgg& A, const int64_t j, const int32_t s0, const int32_t e0,
                                                        double (*part)[64 * 4]) {
-    constexpr int WAVES = BW_THREADS / 64;
-    const int wl = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int WAVES = JOINT ? BW_WAVES : 1;
+    const int wl = threadIdx.x & 63, wave = JOINT ? (int)threadIdx.x >> 6 : 0;
+    const int share = (e0 - s0 + WAVES - 1) / WAVES, block = share < 64 ? share : 64;
     int hl = 1;
     while (hl < A.pieces && hl < 64) hl <<= 1;
     const int lane = wl & (hl - 1), sub = wl / hl, subs = 64 / hl;
@@ -350,8 +352,8 @@ __device__ __forceinline__ void aggregate_backward_hub(const BwAgg& A, const int
         const int piece = p0 + lane;
         const int64_t off = piece < A.pieces ? (int64_t)piece * 16 : 0;
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int c = s0 + wave * 64; c < e0; c += WAVES * 64) {
-            const int m = e0 - c < 64 ? e0 - c : 64;
+        for (int c = s0 + wave * block; c < e0; c += WAVES * block) {
+            const int m = e0 - c < block ? e0 - c : block;
             int32_t r;
             double w;
             bw_edge<GCN>(A, c + wl, wl < m, r, w);
@@ -374,22 +376,24 @@ __device__ __forceinline__ void aggregate_backward_hub(const BwAgg& A, const int
         for (int o = hl; o < 64; o <<= 1)
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
-        if (sub == 0)
+        if constexpr (JOINT) {
+            if (sub == 0)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) part[wave][lane * 4 + e] = acc[e];
-        __syncthreads();
+                for (int e = 0; e < 4; ++e) part[wave][lane * 4 + e] = acc[e];
+            __syncthreads();
+        }
         if (wave == 0 && sub == 0 && piece < A.pieces) {
             double sum[4] = {0.0, 0.0, 0.0, 0.0};
             if (own) bw_add(sum, *(const f32x4*)(A.dx + j * A.dx_stride + off), own_w);
 #pragma unroll
             for (int v = 0; v < WAVES; ++v)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) sum[e] += part[v][lane * 4 + e];
+                for (int e = 0; e < 4; ++e) sum[e] += JOINT ? part[v][lane * 4 + e] : acc[e];
             const f32x4 o = {(float)sum[0], (float)sum[1], (float)sum[2], (float)sum[3]};
             *(f32x4*)(A.out + j * A.out_stride + off) = o;
             ss += (double)o.x * o.x + (double)o.y * o.y + (double)o.z * o.z + (double)o.w * o.w;
         }
-        __syncthreads();      // the partial sums are read
+        if constexpr (JOINT) __syncthreads();      // the partial sums are read
     }
     if (A.norms && wave == 0) {
         ss = wave_sum(ss);
@@ -397,14 +401,16 @@ __device__ __forceinline__ void aggregate_backward_hub(const BwAgg& A, const int
     }
 }
 
-// Groups of 2^lanes_log2 lanes take the source positions in turn, except those with more than BW_MANY incoming edges: the
-// first hub_blocks workgroups look at 64 positions each, spread over the whole layer (the hubs of a power-law graph are
-// drawn early and lie together at its front), and take such a position with all their wavefronts. Every position is
-// written by exactly one group.
+// Groups of 2^lanes_log2 lanes take the source positions in turn, except those with more than `many` incoming edges: the
+// first hub_blocks workgroups look at hub_per positions each, spread over the whole layer (the hubs of a power-law graph are
+// drawn early and lie together at its front), and take such positions a wavefront each, or with all wavefronts where it has more
+// edges than one wavefront takes in a block (four blocks where there are positions for all of them). Every position is written by
+// exactly one group.
 template <bool GCN, int PU>
-__global__ __launch_bounds__(BW_THREADS) void aggregate_backward_kernel(BwAgg A, int lanes_log2, int hub_blocks) {
-    __shared__ double part[BW_THREADS / 64][64 * 4];
-    __shared__ unsigned long long s_big;
+__global__ __launch_bounds__(BW_THREADS) void aggregate_backward_kernel(BwAgg A, int lanes_log2, int many, int hub_blocks,
+                                                                        int hub_per) {
+    __shared__ double part[BW_WAVES][64 * 4];
+    __shared__ unsigned long long s_big, s_joint;
     __shared__ int32_t s_range[2][64];
     auto range_of = [&](int64_t j, int32_t& s, int32_t& e) {
         s = A.t_start[j];
@@ -415,16 +421,26 @@ __global__ __launch_bounds__(BW_THREADS) void aggregate_backward_kernel(BwAgg A,
         if (threadIdx.x < 64) {
             const int64_t j = (int64_t)threadIdx.x * hub_blocks + blockIdx.x;
             int32_t s = 0, e = 0;
-            if (j < A.n_src) range_of(j, s, e);
+            if ((int)threadIdx.x < hub_per && j < A.n_src) range_of(j, s, e);
             s_range[0][threadIdx.x] = s;
             s_range[1][threadIdx.x] = e;
-            const unsigned long long big = __ballot(e - s > BW_MANY);
-            if (threadIdx.x == 0) s_big = big;
+            const unsigned long long big = __ballot(e - s > many);
+            const unsigned long long joint = __ballot(e - s > (__popcll(big) < BW_WAVES ? 64 : 256));
+            if (threadIdx.x == 0) {
+                s_big = big & ~joint;
+                s_joint = joint;
+            }
         }
         __syncthreads();
-        for (unsigned long long big = s_big; big; big &= big - 1) {      // uniform over the workgroup
+        int k = 0;
+        for (unsigned long long big = s_big; big; big &= big - 1, ++k) {
+            if (k % BW_WAVES != (int)threadIdx.x >> 6) continue;      // uniform over the wavefront
             const int b = __ffsll((long long)big) - 1;
-            aggregate_backward_hub<GCN>(A, (int64_t)b * hub_blocks + blockIdx.x, s_range[0][b], s_range[1][b], part);
+            aggregate_backward_hub<GCN, false>(A, (int64_t)b * hub_blocks + blockIdx.x, s_range[0][b], s_range[1][b], part);
+        }
+        for (unsigned long long big = s_joint; big; big &= big - 1) {      // uniform over the workgroup
+            const int b = __ffsll((long long)big) - 1;
+            aggregate_backward_hub<GCN, true>(A, (int64_t)b * hub_blocks + blockIdx.x, s_range[0][b], s_range[1][b], part);
         }
         return;
     }
@@ -434,7 +450,7 @@ __global__ __launch_bounds__(BW_THREADS) void aggregate_backward_kernel(BwAgg A,
     for (int64_t j = block * gpb + (threadIdx.x >> lanes_log2); j < A.n_src; j += n_blocks * gpb) {
         int32_t s0, e0;
         range_of(j, s0, e0);
-        if (e0 - s0 > BW_MANY) continue;
+        if (e0 - s0 > many) continue;
         aggregate_backward_row<GCN, PU>(A, j, s0, e0, threadIdx.x & (lanes - 1), lanes);
     }
 }
@@ -596,7 +612,17 @@ static fg_status_t layer_backward_launch(const char* who, int kind, const float*
     const int gpb = BW_THREADS >> lg;
     int64_t blocks = fg_ceil_div(n_src, gpb);
     if (blocks > 256 * 16) blocks = 256 * 16;
-    const int hub_blocks = nnz > BW_MANY ? (int)fg_ceil_div(n_src, 64) : 0;
+    // A row wider than a small group is walked by a whole wavefront in any case: only from 64 edges on it gains from more.
+    // Positions per hub workgroup: 64 where hubs are few, but a layer whose positions average a dozen edges and more is all hubs, and
+    // one of few positions has too few workgroups to share them. 3 k positions of 256 columns with 20 edges each: 29 us with a
+    // wavefront per position, 217 with 64 positions in turn by one workgroup, 26 now; 300 of 1024 columns 61, 604, 24; 8 k of 512
+    // columns with 100 edges 242, 958, 135. (Fewer positions per workgroup everywhere: 5 % on layers of one to six edges each.)
+    const int many = lg < 6 ? 16 : 64;
+    const double average = n_src > 0 ? (double)nnz / (double)n_src : 0.0;
+    int64_t hub_per = n_src / 128;
+    if ((double)hub_per * average * average > 1024.0) hub_per = (int64_t)(1024.0 / (average * average));
+    hub_per = hub_per < BW_WAVES ? BW_WAVES : (hub_per > 64 ? 64 : hub_per);
+    const int hub_blocks = nnz > many ? (int)fg_ceil_div(n_src, hub_per) : 0;
     const BwAgg A = {(const char*)dx, (int64_t)cols * 4, n, gcn ? 0 : d_in * 4, pieces, live_dev, hit_dev, row_start_dev, row_end_dev,
                      t_start_dev, t_end_dev, t_row_dev, nnz, n_src, (char*)dh_src_dev, dh_src_stride, norms_src_dev};
     const dim3 agrid((unsigned)(blocks + hub_blocks));
@@ -604,9 +630,9 @@ static fg_status_t layer_backward_launch(const char* who, int kind, const float*
 #define FG_AGG_BW(P)                                                                                                           \
     do {                                                                                                                       \
         if (gcn)                                                                                                               \
-            hipLaunchKernelGGL((aggregate_backward_kernel<true, P>), agrid, dim3(BW_THREADS), 0, st, A, lg, hub_blocks);        \
+            hipLaunchKernelGGL((aggregate_backward_kernel<true, P>), agrid, dim3(BW_THREADS), 0, st, A, lg, many, hub_blocks, (int)hub_per); \
         else                                                                                                                   \
-            hipLaunchKernelGGL((aggregate_backward_kernel<false, P>), agrid, dim3(BW_THREADS), 0, st, A, lg, hub_blocks);       \
+            hipLaunchKernelGGL((aggregate_backward_kernel<false, P>), agrid, dim3(BW_THREADS), 0, st, A, lg, many, hub_blocks, (int)hub_per); \
     } while (0)
     if (pu <= 1)
         FG_AGG_BW(1);

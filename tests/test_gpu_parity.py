@@ -1094,6 +1094,46 @@ def test_layer_backward_with_hubs_matches_oracle(env, kind, d_in, d_out):
     assert (np.abs(got - want) <= tol).all(), np.abs(got - want).max()
 
 
+@pytest.mark.parametrize("kind,d_in,d_out,n,n_src,degrees", [
+    ("sage", 256, 16, 300, 333, (20, 24)), ("gcn", 88, 16, 300, 1030, (0, 40)), ("sage", 260, 8, 300, 333, (60, 70)),
+    ("sage", 68, 8, 300, 1030, (250, 260)), ("gcn", 1028, 8, 80, 90, (16, 80)), ("sage", 4, 8, 300, 333, (10, 300))])
+def test_layer_backward_where_most_positions_are_hubs_matches_oracle(env, kind, d_in, d_out, n, n_src, degrees):
+    """Layers whose positions have many incoming edges on average: a hub workgroup holds few positions, several of them hubs,
+    taken a wavefront each or (beyond 64 edges, or 256 where there are hubs for every wavefront) by all four."""
+    torch, B = env
+    from fg_inputs.sampler import transpose_block
+    r = np.random.default_rng(d_in + n_src)
+    cols = [[] for _ in range(n)]
+    for pos in range(n_src):
+        for row in r.choice(n, size=min(n, int(r.integers(degrees[0], degrees[1] + 1))), replace=False):
+            cols[row].append(pos)
+    deg = np.asarray([len(c) for c in cols])
+    start = np.concatenate([[0], np.cumsum(deg)[:-1]]).astype(np.int32)
+    end, col = (start + deg).astype(np.int32), np.concatenate(cols).astype(np.int32)
+    ts, te, tr = transpose_block(start, end, col, n_src)
+    rows = np.arange(n, dtype=np.int32)
+    dh, h = r.standard_normal((n, d_out)).astype(np.float32), np.maximum(r.standard_normal((n, d_out)), 0).astype(np.float32)
+    k_w = d_in if kind == "gcn" else 2 * d_in
+    W = (r.standard_normal((k_w, d_out)) / np.sqrt(k_w)).astype(np.float32)
+    dummy = np.zeros((n, d_in))
+    if kind == "gcn":
+        want = O.layer_backward_gcn(start, end, col, rows, dh, h, dummy, W, n_src, relu=True)[0]
+    else:
+        want = O.layer_backward(start, end, col, rows, dh, h, dummy, dummy, W, n_src, relu=True)[0]
+    out, norms = torch.full((n_src, d_in), 7.0, device="cuda"), torch.full((n_src,), -1.0, device="cuda")
+    wsb = B.fg_layer_backward_workspace_bytes(n, n, d_in, d_out, kind=kind)
+    ws = torch.full((wsb,), 0xFF, dtype=torch.uint8, device="cuda")
+    B.fg_layer_backward(dev(torch, dh), d_out * 4, dev(torch, h), d_out * 4, n, dev(torch, rows), None, n, None, None, dev(torch, start),
+                        dev(torch, end), dev(torch, ts), dev(torch, te), dev(torch, tr), len(tr), n_src, d_in, d_out, dev(torch, W), out,
+                        d_in * 4, norms, ws, wsb, kind=kind)
+    got = out.cpu().numpy()
+    np.testing.assert_allclose(norms.cpu().numpy(), O.row_norms(got).astype(np.float32), rtol=5e-7, atol=1e-37)
+    # a product of 8 or 16 terms, rounded once, then sums of up to 300 of them in fp64: as in the test above
+    scale = np.abs(dh).max() * np.abs(W).sum(axis=1).max()
+    tol = np.maximum(REL_TOL_F32 * np.maximum(np.abs(want), np.abs(want).max(axis=1, keepdims=True) / 16), 4 * 2.0 ** -24 * scale)
+    assert (np.abs(got - want) <= tol).all(), np.abs(got - want).max()
+
+
 @pytest.mark.parametrize("variant", [0, 32])
 @pytest.mark.parametrize("d_in,d_out,n,n_rows,relu,seed", [(128, 256, 5000, 4100, True, 0), (256, 256, 700, 700, True, 1),
                                                          (64, 64, 300, 250, False, 2), (24, 72, 130, 77, True, 3),
