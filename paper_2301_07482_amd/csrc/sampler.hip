@@ -338,30 +338,34 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void sample_columns_kernel(SmpArgs A
     if (q == k && at < A.max_below) A.below[at] = A.col_ids[k];
 }
 
-// A layer of at most 1024 rows and 11 draws per row (the seeds) in one workgroup and one launch: the candidates, the table
+// A layer of few draws (the seeds) in one workgroup and one launch: the candidates, the table
 // (order numbers only: the node of an order number is in LDS too) and the ranks stay in LDS. Reads from memory are three
 // rounds: ids, row ranges, neighbours. One compute unit does all the arithmetic, so what belongs to a row is computed once
-// per row and no lane is left idle beside a row's draws. 1024 rows x 5 of a 27 M-node graph: six launches, 30 us, now 26.
-constexpr int SMP_SMALL_ROWS = 1024, SMP_SMALL_FANOUT = 11;
-constexpr int SMP_SMALL_ITEMS = SMP_SMALL_ROWS * (SMP_SMALL_FANOUT + 1);      // own nodes and candidates
+// per row and no lane is left idle beside a row's draws. Against the four launches, graph of 2 M nodes: 256 rows x 5 11 us
+// (29), 1024 x 5 24 (27), 512 x 11 27 (29), 640 x 10 32 (29), 777 x 8 33 (33), 1024 x 8 44 (28), 1024 x 11 111 (31): up to
+// 5632 draws.
+constexpr int SMP_SMALL_ROWS = 1024, SMP_SMALL_FANOUT = 11, SMP_SMALL_DRAWS = 5632;
+constexpr int SMP_SMALL_ITEMS = SMP_SMALL_ROWS + SMP_SMALL_DRAWS;      // own nodes and candidates
 constexpr int SMP_SMALL_TABLE = 16384;
-constexpr size_t SMP_SMALL_LDS = (size_t)SMP_SMALL_TABLE * 4 + SMP_SMALL_ITEMS * 4 + SMP_SMALL_ITEMS * 2;
+constexpr size_t SMP_SMALL_ROW_BYTES = 36;                             // what a row keeps while its neighbours are drawn
+constexpr size_t SMP_SMALL_NODES = SMP_SMALL_ITEMS * 4 > SMP_SMALL_ROWS * SMP_SMALL_ROW_BYTES ? SMP_SMALL_ITEMS * 4 : SMP_SMALL_ROWS * SMP_SMALL_ROW_BYTES;
+constexpr size_t SMP_SMALL_LDS = (size_t)SMP_SMALL_TABLE * 4 + SMP_SMALL_NODES + SMP_SMALL_ITEMS * 2;
 
 __global__ __launch_bounds__(SMP_THREADS) void sample_small_kernel(SmpArgs A) {
     extern __shared__ __attribute__((aligned(16))) int smem[];
     __shared__ int wave_sum[SMP_THREADS / FG_WAVE];
     int* table = smem;                                             // order number of the first item with the node
     int* nodes = table + SMP_SMALL_TABLE;                          // node of an order number
-    unsigned short* found = (unsigned short*)(nodes + SMP_SMALL_ITEMS);
+    unsigned short* found = (unsigned short*)((char*)nodes + SMP_SMALL_NODES);
     // before they are needed their space holds what the draws read and write: per row the range, the derived word and turn
     uint64_t* r_word = (uint64_t*)nodes;                           // [1024]
     int64_t* r_lo = (int64_t*)(r_word + SMP_SMALL_ROWS);
     int64_t* r_deg = r_lo + SMP_SMALL_ROWS;
     int64_t* r_turn = r_deg + SMP_SMALL_ROWS;
     int32_t* r_node = (int32_t*)(r_turn + SMP_SMALL_ROWS);
-    int32_t* raw = table;                                          // [1024 * 11]
-    static_assert((size_t)SMP_SMALL_ROWS * 36 <= (size_t)SMP_SMALL_ITEMS * 4, "the rows' values lie in the nodes' space");
-    static_assert(SMP_SMALL_ROWS * SMP_SMALL_FANOUT <= SMP_SMALL_TABLE && SMP_SMALL_ITEMS < SMP_SMALL_TABLE, "the table is never full");
+    int32_t* raw = table;                                          // [SMP_SMALL_DRAWS]
+    static_assert(SMP_SMALL_DRAWS <= SMP_SMALL_TABLE && SMP_SMALL_ITEMS < SMP_SMALL_TABLE, "the table is never full");
+    static_assert(SMP_SMALL_ITEMS < 0x8000, "an order number leaves the top bit of `found` free");
     const int n = (int)smp_rows(A), f = A.fanout, t = threadIdx.x;
     int32_t v = -1;
     if (t < n) {
@@ -447,7 +451,7 @@ __global__ __launch_bounds__(SMP_THREADS) void sample_small_kernel(SmpArgs A) {
     }
     // found[k]: the rank among the first occurrences of its 64 candidates (top bit set), or the order number of the first
     // occurrence; s_new: first occurrences per 64 candidates, then before each
-    constexpr int GROUPS = SMP_SMALL_ROWS * SMP_SMALL_FANOUT / FG_WAVE;
+    constexpr int GROUPS = SMP_SMALL_DRAWS / FG_WAVE;
     __shared__ int s_new[GROUPS];
     if (t < GROUPS) s_new[t] = 0;
     __syncthreads();      // (also behind the last insertion)
@@ -576,7 +580,7 @@ extern "C" fg_status_t fg_sample_block(const int64_t* indptr_dev, const int32_t*
     int lg = 0;
     while ((1u << lg) < w.entries) ++lg;
     A.shift = 32 - lg;
-    if (max_rows <= SMP_SMALL_ROWS && fanout <= SMP_SMALL_FANOUT) {
+    if (max_rows <= SMP_SMALL_ROWS && fanout <= SMP_SMALL_FANOUT && max_rows * fanout <= SMP_SMALL_DRAWS) {
         hipLaunchKernelGGL(sample_small_kernel, dim3(1), dim3(SMP_THREADS), SMP_SMALL_LDS, st, A);
         FG_LAUNCH_CHECK("sample_small_kernel");
         return FG_OK;
