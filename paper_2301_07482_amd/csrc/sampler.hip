@@ -628,7 +628,10 @@ namespace {
 constexpr int TR_THREADS = 256;
 constexpr int TR_LANES = 8;          // lanes per row
 constexpr int TR_DIRECT = 128;       // workgroups of counters that are added up directly
-constexpr int TR_SMALL = 12288;      // sources, edges and rows of a block that fits one workgroup
+// Sources, edges and rows of a block that one workgroup transposes. Rows x draws: 1024 x 5 one workgroup 11 us against 13 in five
+// launches, 1024 x 6 12 against 14, 1024 x 7 (8192 sources, whose counters then share their banks) 18 against 14, 1024 x 11
+// 22 against 15; 1500 x 2 12 against 14, 2000 x 1 14 against 13, 3000 x 2 22 against 14.
+constexpr int TR_SMALL = 7168, TR_SMALL_ROWS = 1536;
 
 struct TrArgs {
     const int32_t* row_start;
@@ -852,7 +855,7 @@ extern "C" fg_status_t fg_transpose_block(const int32_t* row_start_dev, const in
     hipStream_t st = (hipStream_t)stream;
     TrArgs A{row_start_dev, row_end_dev, col_dev, n_dev, max_rows, n_src_dev, max_src, max_nnz, t_start_dev, t_end_dev, t_row_dev,
              (int32_t*)ws_dev, (int32_t*)((char*)ws_dev + blk_at)};
-    if (max_src <= TR_SMALL && max_nnz <= TR_SMALL && max_rows <= TR_SMALL) {
+    if (max_src <= TR_SMALL && max_nnz <= TR_SMALL && max_rows <= TR_SMALL_ROWS) {
         hipLaunchKernelGGL(transpose_small_kernel, dim3(1), dim3(FG_SCAN_BLOCK), (size_t)(max_src + max_nnz) * 4, st, A);
         FG_LAUNCH_CHECK("transpose_small_kernel");
         return FG_OK;

@@ -810,6 +810,8 @@ def test_sample_block_routes_match_oracle(env, N, max_deg, n_seeds, fanout, boun
 
 @pytest.mark.parametrize("n,n_src,deg,src_bound,nnz_bound", [
     (1500, 12288, 8, 12288, 12288), (1500, 12288, 8, 12288, 12289), (1500, 12288, 8, 12289, 12288), (2500, 5, 4, 9, 12000),
+    (1024, 7168, 7, 7168, 7168), (1024, 7168, 7, 7168, 7169), (1024, 7168, 7, 7169, 7168), (1536, 6000, 4, 7168, 7168),
+    (1537, 6000, 4, 7168, 7168), (1400, 5, 4, 9, 7000),
     (1, 1, 1, 1, 1), (900, 7000, 21, 131_073, 20_000), (900, 7000, 21, 131_072, 20_000)])
 def test_transpose_block_routes(env, n, n_src, deg, src_bound, nnz_bound):
     """The transpose at the sizes where fg_transpose_block changes its launches: one workgroup or several, counters added up
