@@ -552,8 +552,8 @@ def test_cache_update_sequences_match_oracle(env, cap, t_stale, p, nmax):
         B.fg_cache_destroy(cache)
 
 
-@pytest.mark.parametrize("n", [1, 3, 4, 5, 63, 4095, 4096, 4097, 8187, 8191, 8192, 8193])
-@pytest.mark.parametrize("p", [0.0, 0.37, 1.0])
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 63, 4095, 4096, 4097, 6144, 6145, 8187, 8191, 8192, 8193])
+@pytest.mark.parametrize("p", [0.0, 0.37, 0.75, 1.0])
 def test_cache_update_sizes_around_a_workgroups_share(env, n, p):
     """Layers on both sides of what one workgroup takes in one and in two steps of four positions a thread, cut quads included;
     a ring that some of them wrap, two updates in a row (the second overwrites the first's entries and checks hits out)."""
@@ -579,8 +579,8 @@ def test_cache_update_sizes_around_a_workgroups_share(env, n, p):
         B.fg_cache_destroy(cache)
 
 
-@pytest.mark.parametrize("n,d,p", [(1, 4, 1.0), (4096, 4, 1.0), (777, 12, 0.6), (1024, 64, 0.8), (3000, 20, 0.5),      # copied by the selection
-                                   (1024, 64, 0.9), (4096, 28, 0.6), (4097, 4, 0.3)])                               # by a launch of their own
+@pytest.mark.parametrize("n,d,p", [(1, 4, 1.0), (4096, 4, 1.0), (777, 12, 0.6), (1024, 64, 0.6), (3000, 20, 0.5), (4096, 20, 0.5),      # copied by the selection
+                                   (1024, 64, 0.8), (4096, 20, 0.51), (1024, 64, 0.9), (4096, 28, 0.6), (4097, 4, 0.3)])                               # by a launch of their own
 def test_cache_update_rows_of_small_layers(env, n, d, p):
     """The rows a small layer's update puts into the cache, on both sides of the size up to which the selecting workgroup copies
     them itself; a ring that wraps, rows of 16 to 256 bytes."""
