@@ -31,11 +31,10 @@ __device__ __forceinline__ double wave_max(double v) {
 }
 
 // p = softmax(h[i, :]) in fp64, dh[i, c] = (p[c] - [c == label]) / n. A row belongs to WAVES wavefronts, one or (wide rows) the
-// four of a workgroup. A row of up to 64 * WAVES * SM_KEEP columns is read once, its exponentials, which are what the kernel
+// four of a workgroup. A row of up to 64 * WAVES * KEEP columns is read once, its exponentials, which are what the kernel
 // spends its time on, are formed once and stay in registers; beyond that they are formed again for the result.
-// 1024 rows of 1024 columns: 15.0 us with one wavefront per row and every exponential twice, 7.5 now; of 256: 5.8, now 5.0.
-constexpr int SM_KEEP = 4;
-template <int WAVES>
+// 1024 rows of 1024 columns: 13.7 us with one wavefront per row and every exponential twice, 7.8 now; of 256: 5.8, now 5.1.
+template <int WAVES, int KEEP>
 __global__ __launch_bounds__(BW_THREADS) void softmax_xent_grad_kernel(const char* __restrict__ h, int64_t h_stride,
                                                                        const int32_t* __restrict__ labels, int n, int d,
                                                                        char* __restrict__ dh, int64_t dh_stride) {
@@ -56,33 +55,33 @@ __global__ __launch_bounds__(BW_THREADS) void softmax_xent_grad_kernel(const cha
     for (int64_t i = ((int64_t)blockIdx.x * BW_THREADS + threadIdx.x) / LANES; i < n; i += n_groups) {      // uniform over the row's wavefronts
         const float* row = (const float*)(h + i * h_stride);
         const int32_t y = labels[i];
-        float x[SM_KEEP];
+        float x[KEEP];
 #pragma unroll
-        for (int q = 0; q < SM_KEEP; ++q) x[q] = lane + q * LANES < d ? row[lane + q * LANES] : 0.f;
+        for (int q = 0; q < KEEP; ++q) x[q] = lane + q * LANES < d ? row[lane + q * LANES] : 0.f;
         double m = -1.0e300;
 #pragma unroll
-        for (int q = 0; q < SM_KEEP; ++q)
+        for (int q = 0; q < KEEP; ++q)
             if (lane + q * LANES < d) m = (double)x[q] > m ? (double)x[q] : m;
-        for (int c = lane + SM_KEEP * LANES; c < d; c += LANES) {
+        for (int c = lane + KEEP * LANES; c < d; c += LANES) {
             const double v = (double)row[c];
             m = v > m ? v : m;
         }
         m = combine(wave_max(m), 0, false);
-        double e[SM_KEEP], s = 0.0;
+        double e[KEEP], s = 0.0;
 #pragma unroll
-        for (int q = 0; q < SM_KEEP; ++q) {
+        for (int q = 0; q < KEEP; ++q) {
             e[q] = lane + q * LANES < d ? exp((double)x[q] - m) : 0.0;
             s += e[q];
         }
-        for (int c = lane + SM_KEEP * LANES; c < d; c += LANES) s += exp((double)row[c] - m);
+        for (int c = lane + KEEP * LANES; c < d; c += LANES) s += exp((double)row[c] - m);
         s = combine(wave_sum(s), 1, true);
         float* out = (float*)(dh + i * dh_stride);
 #pragma unroll
-        for (int q = 0; q < SM_KEEP; ++q) {
+        for (int q = 0; q < KEEP; ++q) {
             const int c = lane + q * LANES;
             if (c < d) out[c] = (float)((e[q] / s - (c == y ? 1.0 : 0.0)) / (double)n);
         }
-        for (int c = lane + SM_KEEP * LANES; c < d; c += LANES) {
+        for (int c = lane + KEEP * LANES; c < d; c += LANES) {
             const double p = exp((double)row[c] - m) / s;
             out[c] = (float)((p - (c == y ? 1.0 : 0.0)) / (double)n);
         }
@@ -487,15 +486,22 @@ extern "C" fg_status_t fg_softmax_xent_grad(const float* h_dev, int64_t h_stride
         FG_FAIL(FG_ERR_INVALID_ARG, "fg_softmax_xent_grad: pointers and strides must be 4-byte aligned");
     fg_clear_error();
     if (n == 0) return FG_OK;
-    const bool wide = d > 64 * SM_KEEP;      // more than a wavefront keeps in registers
+    // A workgroup per row pays two barriers: worth it where a wavefront would form exponentials twice, or where there are few rows.
+    // One wavefront / four, us: 1024 rows of 300 columns 5.7 / 5.8, of 512 6.9 / 6.4; 2048 of 300 6.6 / 7.8, of 512 8.1 / 8.6; 4096
+    // of 300 8.3 / 11.4, of 640 13.2 / 14.4, of 1024 20.3 / 17.9 (before: 10.2, 16.2, 24.2).
+    const bool wide = d > (n <= 1536 ? 256 : 640);
     int64_t blocks = wide ? n : fg_ceil_div(n, BW_THREADS / 64);
     if (blocks > 4096) blocks = 4096;
+#define FG_SM(WAVES, KEEP)                                                                                                         \
+    hipLaunchKernelGGL((softmax_xent_grad_kernel<WAVES, KEEP>), dim3((unsigned)blocks), dim3(BW_THREADS), 0, (hipStream_t)stream,    \
+                       (const char*)h_dev, h_stride, labels_dev, n, d, (char*)dh_dev, dh_stride)
     if (wide)
-        hipLaunchKernelGGL(softmax_xent_grad_kernel<BW_THREADS / 64>, dim3((unsigned)blocks), dim3(BW_THREADS), 0, (hipStream_t)stream,
-                           (const char*)h_dev, h_stride, labels_dev, n, d, (char*)dh_dev, dh_stride);
+        FG_SM(BW_THREADS / 64, 4);
+    else if (d > 256)
+        FG_SM(1, 8);
     else
-        hipLaunchKernelGGL(softmax_xent_grad_kernel<1>, dim3((unsigned)blocks), dim3(BW_THREADS), 0, (hipStream_t)stream, (const char*)h_dev,
-                           h_stride, labels_dev, n, d, (char*)dh_dev, dh_stride);
+        FG_SM(1, 4);
+#undef FG_SM
     FG_LAUNCH_CHECK("softmax_xent_grad_kernel");
     return FG_OK;
 }

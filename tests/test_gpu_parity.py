@@ -1299,7 +1299,8 @@ def test_layer_backward_weights_bf16_match_oracle(env, src, d_in, d_out, n, n_ro
     assert e <= REL_TOL_F32 and e_b <= REL_TOL_F32, f"rel err dW {e:.3e}, db {e_b:.3e}"
 
 
-@pytest.mark.parametrize("n,d", [(3, 256), (1031, 257), (5000, 260), (2, 1024), (9, 1025), (4, 2600)])
+@pytest.mark.parametrize("n,d", [(3, 256), (1031, 257), (5000, 260), (2, 1024), (9, 1025), (4, 2600), (1536, 300), (1537, 300),
+                                 (1600, 512), (1600, 513), (1600, 640), (1600, 641), (4100, 700)])
 def test_loss_gradient_of_wide_rows(env, n, d):
     """Rows of one wavefront and of four, within and beyond what their registers keep; more rows than workgroups."""
     torch, B = env
