@@ -19,8 +19,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // K per step, and halfwords per LDS row: 144 or 272 bytes, so that the 16-byte reads of neighbouring rows fall on different banks
-constexpr int hb_k(int hb_m, bool w_nk) { return hb_m < 128 && w_nk ? 128 : 64; }
-constexpr int hb_ldh(int hb_m, bool w_nk) { return hb_k(hb_m, w_nk) + 8; }
+constexpr int hb_k(bool k_split) { return k_split ? 128 : 64; }
+constexpr int hb_ldh(bool k_split) { return hb_k(k_split) + 8; }
 
 __device__ __forceinline__ unsigned int f32_to_bf16_bits(float f) {
     const unsigned int b = __float_as_uint(f);
@@ -38,9 +38,9 @@ __device__ __forceinline__ u32x4 f16x8_to_bf16x8(u32x4 v) {
 }
 
 // HB_M x HB_N: the workgroup's output tile (128 x 128 or 64 x 64). The small tile gives layers with few rows enough
-// workgroups to hide the latency of the operand loads behind each other; with weights as [N x K] it has two times four
-// wavefronts (2 x 2, each owning one block of 32 x 32), which share the K of each step of 128: half the barriers and twice the
-// wavefronts (1024 rows x 2048 x 1024: 23.1 us with four and steps of 64, 17.3 so; 700 x 1024 x 512 12.0 -> 10.1; row-major
+// workgroups to hide the latency of the operand loads behind each other: four wavefronts, 2 x 2, each owning one block of 32 x 32.
+// K_SPLIT (weights as [N x K], few workgroups): two times four, which share the K of each step of 128: half the barriers and
+// twice the wavefronts (1024 rows x 2048 x 1024: 23.1 us with four and steps of 64, 17.3 so; 700 x 1024 x 512 12.0 -> 10.1; row-major
 // weights, whose reshuffling grows with the step, 19 -> 21, so they keep four). The 128 x 128 tile has eight wavefronts as
 // 2 x 4, each owning 64 x 32 of it: at under 128 registers a lane, two such workgroups (four wavefronts per SIMD) share a
 // compute unit, and it is wavefronts waiting on different things that keep the matrix cores fed.
@@ -56,17 +56,17 @@ __device__ __forceinline__ u32x4 f16x8_to_bf16x8(u32x4 v) {
 // exist reads the tile's first row, a k beyond K reads k = 0). Rows and columns that do not exist need no zeroing: an
 // output depends on its own row of A and its own column of W only, and theirs are never written. Only the k values
 // beyond K of a last, partial step are written to LDS as zeros (both operands, so that nothing non-finite meets a zero).
-constexpr int hb_waves(int hb_m, bool w_nk) { return hb_m < 128 && !w_nk ? 4 : 8; }
-constexpr size_t hb_lds_bytes(int hb_m, int hb_n, bool w_nk) { return (size_t)2 * (hb_m + hb_n) * hb_ldh(hb_m, w_nk) * 2 + (size_t)hb_m * 8; }
+constexpr int hb_waves(int hb_m, bool k_split) { return hb_m < 128 && !k_split ? 4 : 8; }
+constexpr size_t hb_lds_bytes(int hb_m, int hb_n, bool k_split) { return (size_t)2 * (hb_m + hb_n) * hb_ldh(k_split) * 2 + (size_t)hb_m * 8; }
 
-template <bool SRC_F16, bool OUT_BF16, int HB_M, int HB_N, bool W_NK>
-__global__ __launch_bounds__(64 * hb_waves(HB_M, W_NK), hb_waves(HB_M, W_NK) == 8 ? 4 : 2) void linear_bf16_kernel(
+template <bool SRC_F16, bool OUT_BF16, int HB_M, int HB_N, bool W_NK, bool K_SPLIT>
+__global__ __launch_bounds__(64 * hb_waves(HB_M, K_SPLIT), hb_waves(HB_M, K_SPLIT) == 8 ? 4 : 2) void linear_bf16_kernel(
     const char* __restrict__ h_src, int n_src, int64_t src_stride, const char* __restrict__ agg, int64_t agg_stride,
     const int32_t* __restrict__ rows, const int64_t* __restrict__ n_rows_dev, int64_t max_rows, int d_in, int d_out,
     const unsigned short* __restrict__ W, const float* __restrict__ bias, int relu, char* __restrict__ h_out, int n_out,
     int64_t out_stride, int n_tiles, const int32_t* __restrict__ src_ids) {
     extern __shared__ __attribute__((aligned(16))) unsigned short hb_lds[];
-    constexpr int HB_WAVES = hb_waves(HB_M, W_NK), HB_THREADS = 64 * HB_WAVES, HB_K = hb_k(HB_M, W_NK), LDH = hb_ldh(HB_M, W_NK);
+    constexpr int HB_WAVES = hb_waves(HB_M, K_SPLIT), HB_THREADS = 64 * HB_WAVES, HB_K = hb_k(K_SPLIT), LDH = hb_ldh(K_SPLIT);
     constexpr int KW = HB_K / 64;       // wavefronts along K: each takes its part of every step
     constexpr int STAGE = (HB_M + HB_N) * LDH;    // halfwords per buffer: A rows, then the columns of W
     int32_t* row_of = (int32_t*)(hb_lds + 2 * STAGE);   // output position of each row of the tile, -1: none
@@ -332,21 +332,28 @@ fg_status_t fg_launch_linear_bf16(const void* h_src, int32_t n_src, int64_t src_
     const int ny = (int)fg_ceil_div(d_out, tile);
     const int64_t m_tiles = fg_ceil_div(max_rows, tile);
     const unsigned grid = (unsigned)(fg_ceil_div(m_tiles, 8) * 8 * ny);
-#define FG_LB4(F16, OBF, TM, TN, NK)                                                                                       \
-    hipLaunchKernelGGL((linear_bf16_kernel<F16, OBF, TM, TN, NK>), dim3(grid), dim3(64 * hb_waves(TM, NK)), hb_lds_bytes(TM, TN, NK), st, \
+    // The wavefronts of the small tile share each step's K where a workgroup's own chain of steps is what the launch lasts: at most two
+    // workgroups per compute unit (more do not fit beside each other with eight wavefronts and 70 KB), two steps and more. Shared /
+    // not, us: 6 k rows x 512 x 256 (376 workgroups) 15.3 / 16.9, 8 k x 256 x 256 (500) 11.4 / 12.4; 6 k x 384 x 384 (564) 19.4 / 16.9,
+    // 12 k x 128 x 256 (752) 13.6 / 10.7; 10 k x 88 x 88 (314) 8.8 / 8.5.
+    const bool k_split = w_nk && tile == 64 && m_tiles * ny <= 512 && d_in >= 128;
+#define FG_LB4(F16, OBF, TM, TN, NK, KS)                                                                                   \
+    hipLaunchKernelGGL((linear_bf16_kernel<F16, OBF, TM, TN, NK, KS>), dim3(grid), dim3(64 * hb_waves(TM, KS)), hb_lds_bytes(TM, TN, KS), st, \
                        (const char*)h_src, n_src, src_stride, (const char*)agg, agg_stride, rows_dev, n_rows_dev, max_rows, \
                        d_in, d_out, (const unsigned short*)W, bias, relu, (char*)h_out, n_out, out_stride, ny, src_ids_dev)
-#define FG_LB3(F16, OBF, TM, TN)         \
-    do {                                 \
-        if (w_nk)                        \
-            FG_LB4(F16, OBF, TM, TN, true);  \
-        else                             \
-            FG_LB4(F16, OBF, TM, TN, false); \
+#define FG_LB3(F16, OBF, TM, TN)                    \
+    do {                                            \
+        if (w_nk)                                   \
+            FG_LB4(F16, OBF, TM, TN, true, false);  \
+        else                                        \
+            FG_LB4(F16, OBF, TM, TN, false, false); \
     } while (0)
 #define FG_LB(F16, OBF)                    \
     do {                                   \
         if (tile == 128)                   \
             FG_LB3(F16, OBF, 128, 128);    \
+        else if (k_split)                  \
+            FG_LB4(F16, OBF, 64, 64, true, true); \
         else                               \
             FG_LB3(F16, OBF, 64, 64);      \
     } while (0)

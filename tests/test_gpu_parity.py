@@ -2462,11 +2462,13 @@ def test_linear_bf16_matches_oracle(env, src, d_in, d_out, n_rows, max_rows, rel
             assert np.array_equal(t2.cpu().numpy()[sel], ref)
 
 
-@pytest.mark.parametrize("d_in,d_out,n_rows", [(8, 8, 1), (56, 72, 63), (64, 64, 64), (72, 200, 65), (128, 136, 700), (264, 24, 130)])
+@pytest.mark.parametrize("d_in,d_out,n_rows", [(8, 8, 1), (56, 72, 63), (64, 64, 64), (72, 200, 65), (128, 136, 700), (264, 24, 130),
+                                               (128, 64, 65), (136, 200, 65), (192, 72, 1), (120, 72, 100), (128, 256, 8192), (128, 256, 8193)])
 @pytest.mark.parametrize("src", ["f16", "bf16"])
 def test_linear_bf16_transposed_weights_small_tile(env, src, d_in, d_out, n_rows):
-    """The 64 x 64 tile with weights as [N x K], whose wavefronts share each step of 128 k values: contractions of a fraction of
-    a step, of whole steps and with a remainder in either half; exact on identity panels."""
+    """The 64 x 64 tile with weights as [N x K], whose wavefronts share each step of 128 k values (128 input columns and more, at
+    most 512 workgroups) or not: contractions of a fraction of a step, of whole steps and with a remainder in either half; exact on
+    identity panels."""
     torch, B = env
     r = np.random.default_rng(d_in + d_out + n_rows)
     n_src = n_rows + 9
