@@ -712,16 +712,20 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 // operands go through LDS transposed: a step is 32 rows; a thread loads 8 rows of its column (or of a pair of 16-bit
 // columns; each load coalesced over the columns), masks and splits them and writes 16-byte fragments where the lane that
 // needs them for (column, 8 rows) reads them back with one LDS load: [term][group of 8 rows][column]. Rows are the same for
-// a whole wavefront, so their positions and addresses are scalars. Two LDS buffers, one barrier per step; the values of
-// step s + 2 are in flight while step s is multiplied.
+// a whole wavefront, so their addresses are scalars. Two LDS buffers, one barrier per step; while step s is multiplied the
+// values of step s + 1 are in flight and the positions of step s + 2 are there (values two steps ahead: a second set of registers,
+// steps 6 % shorter, the first one later: not faster below some 30 steps).
 //
 // Split: every chunk of rows leaves a partial result of 2*d_in x d_out that the reduction reads again, and every tile of
 // the result reads the operands again, so the tile is as large as LDS and registers allow.
 //
-// What bounds it: reading the operands (52 k rows x 256 x 256: 160 MB and 33 MB of partial results). Measured with its
-// reduction, before (one 256 x 256 tile; mixed precision: a transposing pass, then a product that did not split the rows) and
-// now: fp32 52 k rows x 256 x 256 75 -> 68 us, 6 k x 512 x 256 38 -> 29, 1 k x 512 x 256 26 -> 17, 19 k x 104 x 88 31 -> 22;
-// mixed 5.9 k x 1536 x 1024 104 -> 69, 30 k x 512 x 256 323 -> 49, 6 k x 256 x 128 74 -> 19.
+// What bounds it: issuing the loads and forming their addresses (a step of a 128 x 128 tile is 1.9 us in fp32, 1.15 mixed; with the
+// offsets multiplied out on the scalar unit for each row, not once per lane, it was 2.1 and 1.45), then reading the operands
+// (52 k rows x 256 x 256: 160 MB and 33 MB of partial results). Measured with its reduction, before (one 256 x 256 tile;
+// mixed precision: a transposing pass, then a product that did not split the rows) and now, rows x 2*d_in x d_out: fp32 52 k x 256 x 256
+// 67 -> 61 us, 6 k x 512 x 256 37 -> 27, 1 k x 1024 x 256 27 -> 21; mixed 5.9 k x 1536 x 1024 93 -> 62, 52 k x 512 x 256
+// 528 -> 52, 1 k x 1024 x 1024 30 -> 28; 1 k x 2048 x 1024 35 -> 37 and 700 rows 29 -> 33 remain slower, a short contraction with
+// a large result, where the transposing pass had little to do.
 typedef unsigned int wu32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 wbf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 wbf16x2 __attribute__((ext_vector_type(2)));
@@ -757,10 +761,10 @@ struct WgIn {
     int n_src, n, d_in, d_pad, d_out, n_chunks, tiles_m, tiles_n;
 };
 
-// row * stride on the scalar unit (both are the same in all lanes; left to itself the compiler multiplies on the vector unit)
-__device__ __forceinline__ int64_t wx_row_offset(int32_t row, int64_t stride) {
-    const uint32_t r = (uint32_t)row, lo = (uint32_t)stride, hi = (uint32_t)((uint64_t)stride >> 32);
-    return (int64_t)(((uint64_t)(__umulhi(r, lo) + r * hi) << 32) | (uint64_t)(r * lo));
+// the offset that lane `from` holds, as a scalar
+__device__ __forceinline__ int64_t wx_lane_offset(int64_t at, int from) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)at, from), hi = (uint32_t)__builtin_amdgcn_readlane((int)(at >> 32), from);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
 // TM x TN: the tile of the result, 8 wavefronts as 4 x 2. SRC: element type of h_src (TERMS = 3: fp32).
@@ -823,8 +827,8 @@ __global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_tile_kernel(WgIn A,
         const int32_t raw = list[A.rows ? ks : 0];
         return A.rows ? raw : ks;
     };
-    // Values of step s from the positions loaded for it. The rows of a group are the same for the whole wavefront: their
-    // positions are read out of the lanes that hold them and the address arithmetic is scalar. Rows that do not exist read
+    // Values of step s from the positions loaded for it. The rows of a group are the same for the whole wavefront: a lane forms
+    // its row's offsets, once per step, and each is read out of the lane that holds it. Rows that do not exist read
     // row 0 / the last entry and are masked when they are staged (with masks, not branches: a branch per row would make the
     // wavefront wait for each load by itself).
     auto load_values = [&](int s, int32_t raw, Vals& V) {
@@ -833,13 +837,14 @@ __global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_tile_kernel(WgIn A,
         const bool z_ok = kk < ke && raw >= 0 && raw < A.n && (TERMS == 1 || raw < A.n_src);
         const bool x_ok = z_ok && (x_agg || raw < A.n_src);
         const int32_t pos = z_ok ? raw : 0, x_row = x_agg ? (kk < ke ? kk : ke - 1) : (x_ok ? raw : 0);
+        const int64_t x_at = (int64_t)x_row * x_stride, g_at = (int64_t)pos * A.dh_stride, o_at = (int64_t)pos * hm_stride;
         V.x_in = (unsigned int)__ballot(x_ok);
         V.z_in = (unsigned int)__ballot(z_ok);
 #pragma unroll
         for (int i = 0; i < XU; ++i)
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const char* p = x_base + wx_row_offset(__builtin_amdgcn_readlane(x_row, 8 * (xg + i * (WG_THREADS / XT)) + e), x_stride);
+                const char* p = x_base + wx_lane_offset(x_at, 8 * (xg + i * (WG_THREADS / XT)) + e);
                 if constexpr (TERMS == 3 || W == 2) {
                     V.x[i][e][0] = *(const unsigned int*)(p + x_off);
                     if constexpr (XR == 2) V.x[i][e][1] = *(const unsigned int*)(p + (x_off + (x_agg ? 0 : 4)));
@@ -853,11 +858,11 @@ __global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_tile_kernel(WgIn A,
         for (int i = 0; i < ZU; ++i)
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int32_t r = __builtin_amdgcn_readlane(pos, 8 * (zg + i * (WG_THREADS / ZT)) + e);
-                const char* gp = A.dh + wx_row_offset(r, A.dh_stride);
+                const int from = 8 * (zg + i * (WG_THREADS / ZT)) + e;
+                const char* gp = A.dh + wx_lane_offset(g_at, from);
 #pragma unroll
                 for (int w = 0; w < W; ++w) V.g[i][e][w] = *(const float*)(gp + (z_off + 4 * w));
-                const char* hp = hm + wx_row_offset(r, hm_stride);
+                const char* hp = hm + wx_lane_offset(o_at, from);
                 if constexpr (TERMS == 3 || W == 2)
                     V.o[i][e] = *(const unsigned int*)(hp + h_off);
                 else
@@ -999,8 +1004,8 @@ __global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_tile_kernel(WgIn A,
         __syncthreads();
         for (int s = 0; s < n_steps; ++s) {
             const int b = s & 1;
-            // step s + 1 goes to the other buffer (last read a step ago, before the previous barrier), then the registers take
-            // step s + 2, and step s is multiplied with those loads in flight (past the chunk: rows that count as zero)
+            // Step s is multiplied with the loads of step s + 1 in flight; then that one goes to the other buffer (last read a step
+            // ago, before the previous barrier) and the registers take step s + 2 (past the chunk: rows that count as zero)
             multiply(b);
             stage(b ^ 1, V);
             load_values(s + 2, p2, V);
@@ -1114,18 +1119,27 @@ WgPlan wg_plan(int64_t max_rows, int64_t d_in, int64_t d_out, bool mixed) {
         if (by_rows < by_step) by_rows = by_step;
     }
     if (chunks > by_rows) chunks = by_rows;
+    // One chunk writes the result itself. Several save it steps (the times of one by tile, us) but leave partial results, which are
+    // written, read and added up by a second launch: few rows of a wide layer are better off as one chunk. Mixed precision, one /
+    // several: 300 rows x 2048 x 1024 19 / 29 us, 700 32 / 34, 1024 42 / 37; 300 x 1024 x 1024 18 / 21, 700 31 / 25.
+    const double step_us = mixed ? (large ? 1.7 : 1.15) : (large ? 2.75 : 1.9);
+    const double saved = (double)fg_ceil_div(some, WX_STEP) * (1.0 - 1.0 / (double)chunks) * step_us;
+    if (saved < 5.0 + (double)(2 * chunks + 1) * (double)(2 * d_in * d_out * 4) / 4.5e6) chunks = 1;
     p.n_chunks = (int)chunks;
     p.part_b = fg_align_up((size_t)p.n_chunks * 2 * d_in * d_out * 4, 256);
     p.total = p.part_b + fg_align_up((size_t)p.n_chunks * d_out * 4, 256);
     return p;
 }
 
-// partial products of every chunk, then their sum
+// partial products of every chunk, then their sum; of one chunk the sums themselves
 template <typename Kernel>
 fg_status_t wg_launch(Kernel kernel, int terms, const WgPlan& P, const WgIn& A, float* part_w, float* part_b, float* dw, float* db, hipStream_t st) {
     const unsigned grid = (unsigned)(fg_ceil_div((int64_t)P.n_chunks * P.tiles_m * P.tiles_n, 8) * 8);
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(WG_THREADS), wx_lds_bytes(P.tm, P.tn, terms), st, A, part_w, part_b);
+    const bool direct = P.n_chunks == 1;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(WG_THREADS), wx_lds_bytes(P.tm, P.tn, terms), st, A, direct ? dw : part_w,
+                       direct && db ? db : part_b);
     FG_LAUNCH_CHECK("weight_grad_tile_kernel");
+    if (direct) return FG_OK;
     const int64_t mn = (int64_t)2 * A.d_in * A.d_out;
     const int w_blocks = (int)fg_ceil_div(mn, 128), b_blocks = (int)fg_ceil_div(A.d_out, 128);
     hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3((unsigned)(w_blocks + b_blocks)), dim3(BW_THREADS), 0, st, part_w, part_b, P.n_chunks,

@@ -1350,7 +1350,9 @@ def test_layer_backward_strides(env, kind, d_out, pad):
     ("bf16", "f16", 136, 264, 12000, 11111, "list", True),         # 256 x 256 tiles, ragged in both directions
     ("bf16", "bf16", 136, 264, 12000, 12000, "all", False), ("bf16", "f32", 136, 264, 12000, 65, "bad", True),
     ("bf16", "f16", 520, 136, 5500, 5400, "bad", True), ("bf16", "f32", 72, 40, 1000, 999, "bad", True),
-    ("f32", "f32", 64, 64, 500, 480, "short", True), ("bf16", "bf16", 64, 64, 500, 480, "short", True)])
+    ("f32", "f32", 64, 64, 500, 480, "short", True), ("bf16", "bf16", 64, 64, 500, 480, "short", True),
+    ("f32", "f32", 1024, 1020, 96, 95, "bad", True), ("bf16", "bf16", 1024, 1032, 300, 290, "list", True),      # one chunk
+    ("bf16", "f16", 520, 1024, 1500, 33, "short", True), ("f32", "f32", 36, 52, 5, 3, "list", False)])
 def test_weight_gradients_tiles_and_chunks(env, kind, src, d_in, d_out, n, n_rows, rows, relu):
     """Both tile sizes of the weight gradients, at sizes that no tile, chunk or step divides; lists that name every position
     ("all": no list at all), some, positions that do not exist ("bad": they contribute nothing) and positions without own
@@ -1396,6 +1398,46 @@ def test_weight_gradients_tiles_and_chunks(env, kind, src, d_in, d_out, n, n_row
     # random products: a sum of k of them in fp32 steps of 16 is off by about sqrt(k / 16) half-ulps of its own size at most,
     # 32 of them for the longest chunk here (a chunk has at most 512 rows); the bias sums are fp64 over fp32 sums of eight
     assert e <= 32 * 2.0 ** -24 and e_b <= 8 * 2.0 ** -24, f"rel err dW {e:.3e}, db {e_b:.3e}"
+
+
+@pytest.mark.parametrize("kind,d_in,d_out", [("f32", 68, 132), ("bf16", 136, 264)])
+def test_weight_gradients_of_operands_beyond_4_gb(env, kind, d_in, d_out):
+    """Rows 128 MB apart, the last ones beyond 2^32 bytes from the first: the same bits as from rows close together, with and
+    without a bias gradient."""
+    torch, B = env
+    n, stride, bf = 40, 1 << 27, kind == "bf16"
+    far = torch.empty(n * stride, dtype=torch.uint8, device="cuda")
+    r = np.random.default_rng(d_in)
+    lst, cnt = dev(torch, np.sort(r.permutation(n)[:37]).astype(np.int32)), dev(torch, np.asarray([37], dtype=np.int64))
+    at, near, wide = 0, [], []
+    for cols, dt in ((d_in, torch.bfloat16 if bf else torch.float32), (d_in, torch.bfloat16 if bf else torch.float32), (d_out, torch.float32),
+                     (d_out, torch.bfloat16 if bf else torch.float32)):
+        a = dev(torch, r.standard_normal((n, cols)).astype(np.float32)).to(dt)
+        size = cols * a.element_size()
+        view = far.view(n, stride)[:, at:at + size]
+        view.copy_(a.view(torch.uint8))
+        near.append((a, size))
+        wide.append((view, stride))
+        at += 4096
+    size = B.fg_layer_backward_weights_bf16_workspace_bytes if bf else B.fg_layer_backward_weights_workspace_bytes
+    wsb = size(n, d_in, d_out)
+    ws = torch.full((wsb,), 255, dtype=torch.uint8, device="cuda")
+    got = []
+    for (h_src, agg, dh, h), bias in ((near, True), (wide, True), (wide, False)):
+        dw, db = torch.full((2 * d_in, d_out), 3.0, device="cuda"), torch.full((d_out,), 3.0, device="cuda")
+        tail = (agg[0].data_ptr(), agg[1], dh[0].data_ptr(), dh[1], h[0].data_ptr(), h[1], n, lst, cnt, n, d_in, d_out, dw, db if bias else None, ws, wsb)
+        if bf:
+            B.fg_layer_backward_weights_bf16(h_src[0].data_ptr(), n, h_src[1], B.FG_BF16, *tail)
+        else:
+            B.fg_layer_backward_weights(h_src[0].data_ptr(), n, h_src[1], *tail)
+        got.append((dw.cpu().numpy(), db.cpu().numpy()))
+    pos = lst.cpu().long()
+    x = torch.cat([near[0][0].cpu()[pos].double(), near[1][0].cpu()[:37].double()], 1)
+    dz = torch.where(near[3][0].cpu()[pos] > 0, near[2][0].cpu()[pos], torch.zeros(1))
+    want = x.t() @ (dz.to(torch.bfloat16) if bf else dz).double()
+    assert np.linalg.norm(got[0][0] - want.numpy()) <= 32 * 2.0 ** -24 * np.linalg.norm(want.numpy())
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+    assert np.array_equal(got[0][0], got[2][0]) and (got[2][1] == 3.0).all()
 
 
 def test_iterations_gcn_layers_with_backward_pass(env):
