@@ -1096,10 +1096,11 @@ struct WgPlan {
 WgPlan wg_plan(int64_t max_rows, int64_t d_in, int64_t d_out, bool mixed) {
     WgPlan p;
     // Large tiles halve the reads of the operands; small ones fill the chip with fewer chunks, whose partial results have to be
-    // written and read. fp32, 256 result rows and columns: 68 us against 74 at 52 k rows, 34 = 34 at 20 k, 28 against 26 at 12 k.
-    // Mixed precision, rows x 128-wide tiles: 42 us against 58 at 240 k, 30 = 30 at 84 k, 30 against 24 at 33 k.
+    // written and read. What counts is rows x 128-wide tiles. fp32, large / small: 4 k rows x 16 tiles 33.0 / 32.7 us, 8 tiles 28.8 / 26.1,
+    // 33 k x 2 31.7 = 31.7, 4 k x 32 46 / 51, 33 k x 8 72 / 85, 1 k x 128 47 / 51, 33 k x 128 816 / 1030. Mixed precision: 42 / 58 at
+    // 240 k, 30 = 30 at 84 k, 30 / 24 at 33 k.
     const int64_t tiles128 = fg_ceil_div(2 * fg_ceil_div(d_in, 64) * 64, 128) * fg_ceil_div(d_out, 128);
-    const bool large = mixed ? d_in > 64 && d_out > 128 && tiles128 * max_rows >= 98304 : d_in > 64 && max_rows >= 32768;
+    const bool large = mixed ? d_in > 64 && d_out > 128 && tiles128 * max_rows >= 98304 : d_in > 64 && tiles128 * max_rows >= 73728;
     p.tm = large ? 256 : 128;
     p.tn = large && mixed ? 256 : 128;
     const int wide = mixed && p.tm == 256 ? 128 : 64;      // columns of a wavefront
@@ -1107,9 +1108,15 @@ WgPlan wg_plan(int64_t max_rows, int64_t d_in, int64_t d_out, bool mixed) {
     p.tiles_m = (int)fg_ceil_div(2 * p.d_pad, p.tm);
     p.tiles_n = (int)fg_ceil_div(d_out, p.tn);
     // One workgroup fills a compute unit. 32 of them are left to the launches this one runs beside: with all 256 taken the cache
-    // update waited for the whole product (its second launch 63 us instead of 9; large SAGE iteration 453 -> 441 us).
-    int64_t chunks = 224 / (p.tiles_m * p.tiles_n);
-    if (chunks < 1) chunks = 1;
+    // update waited for the whole product (its second launch 63 us instead of 9; large SAGE iteration 453 -> 441 us). Not where that
+    // leaves a quarter of the chip idle (64 tiles, 4 k rows: 118 us with four chunks, 141 with three) nor in a product of 150 us and more,
+    // whose eighth is worth more than what waits (33 k x 1024 x 512 212 us, 232 with 224 workgroups; 100 k 625 and 678). In fp32 a
+    // chunk has at most 4096 rows if 512 workgroups suffice for that: its sums are fp32, and with all-positive operands 33 k x 2048 x
+    // 1024 is off by 8.4e-7 in one chunk, 1.1e-7 in eight (816 us, four chunks 798).
+    const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
+    auto fill = [&](int64_t workgroups) { return workgroups / tiles > 1 ? workgroups / tiles : 1; };
+    int64_t chunks = fill(tiles > 32 || max_rows > 2048 * fill(224) ? 256 : 224);
+    if (!mixed && max_rows > 4096 * chunks) chunks = fill(512);
     // at least two steps per chunk, one where there are few tiles and rows (64 / 32 rows: 1024 rows x 512 x 256 17 / 22 us,
     // 777 rows x 176 x 88 13 / 11 us); more rows never make fewer chunks: a workspace for them serves fewer rows too
     const int64_t some = max_rows > 0 ? max_rows : 1;

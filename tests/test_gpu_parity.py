@@ -1395,9 +1395,32 @@ def test_weight_gradients_tiles_and_chunks(env, kind, src, d_in, d_out, n, n_row
         B.fg_layer_backward_weights(h_src, n_src, d_in * 4, agg, d_in * 4, dh, d_out * 4, act_arg, d_out * asz, n, lst_arg, cnt, n,
                                     d_in, d_out, dw, db, ws, wsb)
     e, e_b = float((dw.double() - want).norm() / want.norm()), float((db.double() - want_b).norm() / want_b.norm())
-    # random products: a sum of k of them in fp32 steps of 16 is off by about sqrt(k / 16) half-ulps of its own size at most,
-    # 32 of them for the longest chunk here (a chunk has at most 512 rows); the bias sums are fp64 over fp32 sums of eight
+    # the chunks of these shapes have at most 512 rows, summed in fp32 steps of 16: at most 32 roundings of half an ulp each, of
+    # sums that grow to the size of the chunk's result; the bias sums are fp64 over fp32 sums of eight
     assert e <= 32 * 2.0 ** -24 and e_b <= 8 * 2.0 ** -24, f"rel err dW {e:.3e}, db {e_b:.3e}"
+
+
+@pytest.mark.parametrize("d_in,d_out,n", [(1024, 1024, 9000), (512, 512, 33000), (256, 1020, 70000), (64, 512, 66000)])
+def test_weight_gradients_of_long_chunks(env, d_in, d_out, n):
+    """fp32, wide results over many rows of all-positive operands, where the roundings of a running sum add up: chunks of up to
+    4096 rows."""
+    torch, B = env
+    g = torch.Generator(device="cuda").manual_seed(n)
+    rnd = lambda *shape: torch.rand(*shape, device="cuda", generator=g)
+    h_src, agg, dh, h = rnd(n, d_in), rnd(n, d_in), rnd(n, d_out), torch.randn(n, d_out, device="cuda", generator=g)
+    cnt = dev(torch, np.asarray([n], dtype=np.int64))
+    wsb = B.fg_layer_backward_weights_workspace_bytes(n, d_in, d_out)
+    assert wsb >= -(-n // 4096) * 2 * d_in * d_out * 4      # a partial result for every 4096 rows
+    ws = torch.full((wsb,), 255, dtype=torch.uint8, device="cuda")
+    dw, db = torch.full((2 * d_in, d_out), 3.0, device="cuda"), torch.full((d_out,), 3.0, device="cuda")
+    B.fg_layer_backward_weights(h_src, n, d_in * 4, agg, d_in * 4, dh, d_out * 4, h, d_out * 4, n, None, cnt, n, d_in, d_out, dw, db, ws, wsb)
+    want = torch.zeros((2 * d_in, d_out), dtype=torch.float64, device="cuda")
+    dz = torch.where(h > 0, dh, torch.zeros_like(dh))
+    for k in range(0, n, 8192):
+        want += torch.cat([h_src[k:k + 8192], agg[k:k + 8192]], 1).double().t().contiguous() @ dz[k:k + 8192].double()
+    e, e_b = float((dw.double() - want).norm() / want.norm()), float((db.double() - dz.double().sum(0)).norm() / dz.double().sum(0).norm())
+    # a chunk's sum grows by 256 steps of 16 rows, each rounded once: sqrt(256) half-ulps if the roundings are independent
+    assert e <= 16 * 2.0 ** -24 and e_b <= 8 * 2.0 ** -24, f"rel err dW {e:.3e}, db {e_b:.3e}"
 
 
 @pytest.mark.parametrize("kind,d_in,d_out", [("f32", 68, 132), ("bf16", 136, 264)])
