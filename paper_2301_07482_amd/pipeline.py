@@ -729,13 +729,17 @@ class HotPath:
 
     # ---- read-back helpers for tests and reports (synchronising) -------------------------------------------
     def snapshot(self, bt):
-        """Host copies of what one `run` produced (lists cut to their device-side counts)."""
+        """Host copies of what one `run` produced (lists cut to their device-side counts), layer 0 among them where it was looked up."""
         self.flush()
         L = self.L
         torch.cuda.synchronize()
         counts = self.counts.cpu().numpy()
+        once = self.reads_rows_once(bt)
+        fused = self.fused_input and not once
+        if once:
+            counts[0] = self.input_log[self.input_slot].cpu().numpy()
         out = dict(counts=counts, stats=self.stats.cpu().numpy(), layers={})
-        for l in range(1 if self.fused_input else 0, L + 1):
+        for l in range(1 if fused else 0, L + 1):
             n = bt.n[l]
             n_hit, n_norm = int(counts[l, 1]), int(counts[l, 2])
             out["layers"][l] = dict(
@@ -744,7 +748,7 @@ class HotPath:
                 hit_pos=self.hit_pos[l][:n_hit].cpu().numpy(), hit_slot=self.hit_slot[l][:n_hit].cpu().numpy(),
                 normal_pos=self.normal_pos[l][:n_norm].cpu().numpy(),
                 end=None if l == 0 else bt.end[l].cpu().numpy())
-        if not self.fused_input:
+        if not fused:
             out["input_ids"] = self.input_ids[:int(counts[0, 2])].cpu().numpy()
         return out
 

@@ -178,6 +178,19 @@ def test_zero_sized_calls_are_noops_without_gpu(B):
     B.fg_cache_destroy(None)
 
 
+@pytest.mark.parametrize("kind", ["f32", "bf16"])
+def test_weight_gradient_workspace_serves_fewer_rows_too(B, kind):
+    """A caller keeps one workspace for its largest layer: the size for a bound on the rows never falls as the bound grows, across
+    every change of tile and of the number of chunks."""
+    size = B.fg_layer_backward_weights_bf16_workspace_bytes if kind == "bf16" else B.fg_layer_backward_weights_workspace_bytes
+    rows = sorted({int(1.05 ** k) for k in range(270)} | {32 * k + d for k in range(1, 260) for d in (0, 1)}
+                  | {4096 * k + d for k in range(1, 60) for d in (0, 1)} | {m // t + d for m in (73728, 98304) for t in range(1, 140) for d in (0, 1)})
+    for d_in in (8, 64, 72, 128, 256, 768, 1024):
+        for d_out in (8, 64, 136, 256, 512, 1024, 2048):
+            sizes = [size(r, d_in, d_out) for r in rows]
+            assert sizes == sorted(sizes), (d_in, d_out)
+
+
 def test_header_is_plain_c(tmp_path):
     """include/freshgnn.h compiles as C99 and as C++17 on its own (no torch or HIP types in the boundary)."""
     import shutil
