@@ -355,7 +355,7 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void classify_update_kernel(UpdBatch
 // histograms are kept four times (by lane mod 4): norms share their leading digits, and equal bins of a wavefront are
 // added one after the other. Measured, whole update with its row copy of 256 bytes, p_grad 0.4: 1.2 k positions 17 us against 31, 4096: 19
 // (31), 8192: 28 (33; with p_grad 0.9 35 against 34); 12 288: 34 (33) and 16 384: 40 (34), where one compute unit's
-// random accesses to the index are the bound: the four launches from 8193 positions, or some 6000 admissions, on.
+// random accesses to the index are the bound: the four launches from 8193 positions on.
 constexpr int ONE_COPIES = 4;
 constexpr int ONE_MAX_STEPS = 2;      // 8192 positions
 
@@ -1033,14 +1033,14 @@ fg_status_t launch_update(UpdBatch& B, hipStream_t st, bool select = true, bool 
     const unsigned n_sel = (unsigned)B.sel_first[B.n_layers], n_scan = (unsigned)B.scan_first[B.n_layers];
     // One workgroup per layer where the layers fit its registers, their arrays can be read four at a time and no layer ranks by
     // saved accesses (that needs the counts of all its admissible nodes first).
-    // Each admission is three writes and three reads at random of one compute unit: beyond some 6000 the four launches, which
-    // spread them, are level or faster (8192 positions, p_grad 0.9: 35 us against 34; 0.5: 31 against 33; 7000 and 0.9: 33.5 both).
+    // (Each admission is three writes and three reads at random of one compute unit: from some 6000 the four launches, which
+    // spread them, are level on the device (8192 positions, p_grad 0.9: 35 us against 34; 0.5: 31 against 33; 7000 and 0.9: 33.5 both),
+    // but the host queues three launches more: a training iteration on a bound of 7308, 0.9, 256 to 259 us so, 270 with them.)
     int64_t n_most = 0;
     bool one = true;
     for (int i = 0; i < B.n_layers; ++i) {
         const UpdLayer& u = B.l[i];
         if (u.n > n_most) n_most = u.n;
-        one = one && (double)u.p_grad * (double)u.n <= 6144.0;
         one = one && !u.saving && !(((uintptr_t)u.gnorm | (uintptr_t)u.ids) & 15) && !(((uintptr_t)u.live | (uintptr_t)u.hit) & 3);
     }
     const int steps = (int)fg_ceil_div(n_most, 4 * SEL_THREADS);
@@ -1051,10 +1051,11 @@ fg_status_t launch_update(UpdBatch& B, hipStream_t st, bool select = true, bool 
         // them at some 60 GB/s, which up to there costs the device about what the launch it saves costs it, and the host is spared that
         // launch (512 positions of 256 bytes, p_grad 0.9, 115 KB: 17.9 us against 18.4 with a launch for the rows; 1024, 0.5, 128 KB:
         // 17.8 and 18.2; 1500 of 1024 bytes, 0.1, 150 KB: 18.7 and 17.9; 1500, 0.5, 188 KB: 20.2 and 18.8; 2048, 0.9, 461 KB: 29.6
-        // and 21.0). A step of 1.2 k such positions, 150 KB: 59 us and 62; a training iteration on a bound of 196 KB 106 and 105.
+        // and 21.0). A step of 1.2 k such positions, 150 KB: 59 us and 62. A bound on a count in device memory may say 200 KB: a sampler's is
+        // never reached, since nodes repeat; training iteration on one of 196 KB 100 to 102 us, 103 to 105 with a launch for the rows.
         bool copy = commit && steps <= 1;
         for (int i = 0; i < B.n_layers; ++i)
-            copy = copy && B.l[i].row_bytes % 16 == 0 && (double)B.l[i].p_grad * (double)B.l[i].n * (double)B.l[i].row_bytes <= 160.0 * 1024.0;
+            copy = copy && B.l[i].row_bytes % 16 == 0 && (double)B.l[i].p_grad * (double)B.l[i].n * (double)B.l[i].row_bytes <= (B.l[i].n_dev ? 200.0 : 160.0) * 1024.0;
         if (copy)
             hipLaunchKernelGGL((update_one_kernel<1, true>), grid, block, 0, st, B);
         else if (steps <= 1)
