@@ -341,10 +341,11 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void sample_columns_kernel(SmpArgs A
 // A layer of few draws (the seeds) in one workgroup and one launch: the candidates, the table
 // (order numbers only: the node of an order number is in LDS too) and the ranks stay in LDS. Reads from memory are three
 // rounds: ids, row ranges, neighbours. One compute unit does all the arithmetic, so what belongs to a row is computed once
-// per row and no lane is left idle beside a row's draws. Against the four launches, graph of 2 M nodes: 256 rows x 5 11 us
-// (29), 1024 x 5 24 (27), 512 x 11 27 (29), 640 x 10 32 (29), 777 x 8 33 (33), 1024 x 8 44 (28), 1024 x 11 111 (31): up to
-// 5632 draws.
-constexpr int SMP_SMALL_ROWS = 1024, SMP_SMALL_FANOUT = 11, SMP_SMALL_DRAWS = 5632;
+// per row and no lane is left idle beside a row's draws. Against the four launches, by themselves, graph of 2 M nodes: 256 rows x 5
+// 11 us (29), 1024 x 5 24 (27), 512 x 11 27 (29), 640 x 10 32 (29), 777 x 8 33 (33), 1024 x 8 44 (28), 1024 x 11 111 (31).
+// In a mini-batch, where launches also cost their gaps and host time: 1024 seeds x 6 x 10 105 us (110), x 7 114 to 116 (116 to 118), 777 x 9
+// 114 (114), 1024 x 8 115 (106), x 11 138 (115): up to 7168 draws.
+constexpr int SMP_SMALL_ROWS = 1024, SMP_SMALL_FANOUT = 11, SMP_SMALL_DRAWS = 7168;
 constexpr int SMP_SMALL_ITEMS = SMP_SMALL_ROWS + SMP_SMALL_DRAWS;      // own nodes and candidates
 constexpr int SMP_SMALL_TABLE = 16384;
 constexpr size_t SMP_SMALL_ROW_BYTES = 36;                             // what a row keeps while its neighbours are drawn
@@ -628,10 +629,12 @@ namespace {
 constexpr int TR_THREADS = 256;
 constexpr int TR_LANES = 8;          // lanes per row
 constexpr int TR_DIRECT = 128;       // workgroups of counters that are added up directly
-// Sources, edges and rows of a block that one workgroup transposes. Rows x draws: 1024 x 5 one workgroup 11 us against 13 in five
-// launches, 1024 x 6 12 against 14, 1024 x 7 (8192 sources, whose counters then share their banks) 18 against 14, 1024 x 11
-// 22 against 15; 1500 x 2 12 against 14, 2000 x 1 14 against 13, 3000 x 2 22 against 14.
-constexpr int TR_SMALL = 7168, TR_SMALL_ROWS = 1536;
+// Sources, edges and rows of a block that one workgroup transposes: what fits its LDS. By itself it is level with the five launches
+// at about half of that (rows x draws 1024 x 5 11 us against 13, 1024 x 7 18 against 14, 1024 x 11 22 against 15, 3000 x 2 22
+// against 14), but five launches also cost the gaps between them and the host's time. A whole mini-batch, one workgroup / five
+// launches for its block: 600 seeds x 3 x 4 x 5, the block of 2400 rows x 4, 146 us / 177; 1024 x 8 x 10 106 / 132; 1024 x 11 x 10 x 15,
+// where the device is the bound, 742 / 752.
+constexpr int TR_SMALL = 12288;
 
 struct TrArgs {
     const int32_t* row_start;
@@ -855,7 +858,7 @@ extern "C" fg_status_t fg_transpose_block(const int32_t* row_start_dev, const in
     hipStream_t st = (hipStream_t)stream;
     TrArgs A{row_start_dev, row_end_dev, col_dev, n_dev, max_rows, n_src_dev, max_src, max_nnz, t_start_dev, t_end_dev, t_row_dev,
              (int32_t*)ws_dev, (int32_t*)((char*)ws_dev + blk_at)};
-    if (max_src <= TR_SMALL && max_nnz <= TR_SMALL && max_rows <= TR_SMALL_ROWS) {
+    if (max_src <= TR_SMALL && max_nnz <= TR_SMALL && max_rows <= TR_SMALL) {
         hipLaunchKernelGGL(transpose_small_kernel, dim3(1), dim3(FG_SCAN_BLOCK), (size_t)(max_src + max_nnz) * 4, st, A);
         FG_LAUNCH_CHECK("transpose_small_kernel");
         return FG_OK;

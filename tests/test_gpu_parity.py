@@ -790,8 +790,10 @@ def test_sample_block_matches_oracle(env, N, max_deg, hubs, n_seeds, fanouts, sl
 @pytest.mark.parametrize("N,max_deg,n_seeds,fanout,bound,seed", [
     (9000, 30, 1024, 11, 1024, 0), (9000, 30, 1023, 11, 1024, 1),      # nearly every draw new
     (9000, 30, 1025, 11, 1025, 2), (9000, 30, 1000, 12, 1000, 3),       # one row, one draw more
-    (9000, 30, 512, 11, 512, 12), (9000, 30, 704, 8, 704, 13), (9000, 30, 1024, 5, 1024, 14), (9000, 30, 700, 8, 704, 15),      # the most draws
-    (9000, 30, 513, 11, 513, 16), (9000, 30, 1024, 6, 1024, 17), (9000, 30, 704, 8, 705, 18),      # of one workgroup, and more
+    (9000, 30, 512, 11, 512, 12), (9000, 30, 704, 8, 704, 13), (9000, 30, 1024, 5, 1024, 14), (9000, 30, 700, 8, 704, 15),
+    (9000, 30, 513, 11, 513, 16), (9000, 30, 1024, 6, 1024, 17), (9000, 30, 704, 8, 705, 18),
+    (9000, 30, 1024, 7, 1024, 19), (9000, 30, 890, 8, 896, 20), (9000, 30, 651, 11, 651, 21),      # the most draws of one workgroup
+    (9000, 30, 1024, 8, 1024, 23), (9000, 30, 896, 8, 897, 22), (9000, 30, 652, 11, 652, 24),      # and more
     (40, 60, 40, 11, 1024, 4), (3000, 3, 1, 1, 1, 5), (3000, 40, 0, 5, 7, 6),      # many repeats, one row, none
     (5000, 50, 1500, 8, 1501, 7), (5000, 50, 1500, 9, 1600, 8), (5000, 50, 1500, 16, 1500, 9), (5000, 50, 1500, 17, 1500, 10),
     (4000, 40, 2600, 15, 600_000, 11)])                                 # a bound beyond what a workgroup adds up for itself
