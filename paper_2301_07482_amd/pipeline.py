@@ -721,11 +721,12 @@ class HotPath:
     def reads_rows_once(self, bt):
         """Whether the loader of this mini-batch reads every surviving input row over the host link once, into H[0], and
         aggregates layer 1 from there, instead of reading a row for every edge that names it: a table in host memory, and
-        4 MB of edges' rows at least (less than that takes the link under 0.1 ms, and the fused loader is one launch of the
-        four). A quarter of the rows a papers-like mini-batch reads are named more than once: 5.29 ms with the fused loader,
-        3.95 ms so. (Not with raw features in the cache's buffer: most of the rows named often are read from there.)"""
+        12 MB of edges' rows at least (with less, what the link is spared is less than the three further launches and the lookup of the input
+        layer cost). A quarter of the rows a papers-like mini-batch reads are named more than once: 5.29 ms with the fused loader,
+        3.95 ms so. Step of 16 seeds x 15, 10, 5 (5.4 MB) 171 us fused, 207 so; 200 x 15, 10 (10.4 MB) 264, 274; 512 x 10, 5 (13.7 MB) 340, 329;
+        44 x 15, 10, 5, few of them named twice (14.6 MB), 360, 373; 64 of them (21 MB) 479, 446. (Not with raw features in the cache's buffer: most of the rows named often are read from there.)"""
         return bool(self.on_host and self.fused_input and not self.feature_side
-                    and bt.nnz[1] * self.dims[0] * B.DTYPE_SIZE[self.feat_code] >= 4 << 20)
+                    and bt.nnz[1] * self.dims[0] * B.DTYPE_SIZE[self.feat_code] >= 12 << 20)
 
     # ---- read-back helpers for tests and reports (synchronising) -------------------------------------------
     def snapshot(self, bt):

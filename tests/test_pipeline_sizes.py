@@ -29,7 +29,7 @@ def test_top_down_of_an_announced_mini_batch_stays_within_its_lists(monkeypatch,
     """A mini-batch whose sizes are still on the device comes with the sampler's bounds, which may exceed the node count (500
     here); the pass that runs ahead for it gets the sizes its lists were made for, with the input layer (host table) or without."""
     P, hp, calls = _path(monkeypatch, [500, 330, 30], on_host)
-    bt = _batch([30 * 11 * 11, 330, 30], [0, 330 * 40, 300], [1, 1, None])
+    bt = _batch([30 * 11 * 11, 330, 30], [0, 330 * 80, 300], [1, 1, None])
     hp._top_down(bt, 1, None, P._no_tick)
     assert len(calls[0]) == (3 if on_host else 2)
     for spec, n_max in zip(calls[0], reversed(hp.n_max)):
