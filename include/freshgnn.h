@@ -672,7 +672,7 @@ fg_status_t fg_layer_backward_bf16(const float* dh_dev, int64_t dh_stride, const
  *   db[c]    = sum_k dz[k, c]                                                          (db_dev may be NULL)
  * h_src, agg, rows as given to fg_linear for this layer in the forward pass; dh, h (NULL = no activation) by position,
  * n rows. Every fp32 product is formed exactly, on the bf16 matrix cores from three-way splits of both operands as in
- * fg_linear; fp32 sums within a chunk of the rows, fp64 across chunks; the chunks depend only on max_rows, the widths and
+ * fg_linear; fp32 sums within a chunk of the rows (4096 of them at most where 512 workgroups suffice for that), fp64 across chunks; the chunks depend only on max_rows, the widths and
  * the number of rows, so results do not depend on scheduling. A workspace for max_rows serves fewer rows too. Input domain as for fg_linear.
  *   ws_dev, ws_bytes    device workspace >= fg_layer_backward_weights_workspace_bytes(max_rows, d_in, d_out), 16-byte aligned
  */

@@ -389,8 +389,9 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32x3_panel_kernel(
     // half-wavefront `half` feeds to matrix instruction m of the chunk. A thread takes a block of 8 k x 4 columns of W:
     // eight 16-byte loads, all issued before the first value is used (one memory round trip per pass, and the layers
     // of the workloads need a single pass), then the four columns' fragments.
-    // The first pass is on its way before the count of rows is needed, and the row lists are filled before its values are: 52 k
-    // rows with table rows 47.7 -> 46.3 us, 6 k x 512 x 256 19.2 -> 18.1, 1 k x 256 x 512 10.2 -> 9.4.
+    // The first pass is on its way before the count of rows is needed, and the row lists are filled before its values are: 6 k x 512 x
+    // 256 19.2 -> 18.1 us, 1 k x 256 x 512 10.2 -> 9.4, 52 k rows with table rows 47.7 -> 46.3 called again and again on operands that
+    // are in cache (in an iteration, from memory: 53 before and after).
     struct Piece {
         f32x4 w4[8];
         bool k_in[8];
