@@ -181,6 +181,15 @@ class DeviceSampler:
         return bt.finish() if finish else bt
 
 
+def weight_grad_workspace_bytes(kind, n, d_in, d_out):
+    """Workspace of a layer's weight gradients (kind "sage", "gcn" or "bf16") for at most n rows. A GCN layer hands its one input row
+    over as two halves: its contraction is that of a layer of half the width, whose split over the rows may need more
+    partial results than the full width's."""
+    if kind == "bf16":
+        return B.fg_layer_backward_weights_bf16_workspace_bytes(n, d_in, d_out)
+    return B.fg_layer_backward_weights_workspace_bytes(n, d_in // 2 if kind == "gcn" else d_in, d_out)
+
+
 def _no_tick(name, stream=None):
     return None
 
@@ -322,8 +331,7 @@ class HotPath:
                 w_rows = [None] + [(1 if model == "gcn" else 2) * dims[l - 1] for l in range(1, L + 1)]
                 self.dW = [None] + [torch.zeros((w_rows[l], dims[l]), dtype=torch.float32, device=dev) for l in range(1, L + 1)]
                 self.db = [None] + [torch.zeros(dims[l], dtype=torch.float32, device=dev) for l in range(1, L + 1)]
-                wg_bytes = B.fg_layer_backward_weights_bf16_workspace_bytes if self.bw_kind == "bf16" else B.fg_layer_backward_weights_workspace_bytes
-                self.ws_wg_bytes = max(wg_bytes(n[l], dims[l - 1], dims[l]) for l in range(1, L + 1))
+                self.ws_wg_bytes = max(weight_grad_workspace_bytes(self.bw_kind, n[l], dims[l - 1], dims[l]) for l in range(1, L + 1))
                 self.ws_wg = torch.zeros(self.ws_wg_bytes + 256, dtype=torch.uint8, device=dev)
         self.cache = None
         self.feature_side = False

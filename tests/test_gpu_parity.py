@@ -1469,6 +1469,9 @@ def test_iterations_gcn_layers_with_backward_pass(env):
     w3 = dataclasses.replace(wl.WORKLOADS["large_hbm"], name="large_hbm/small", num_nodes=200_000, num_edges=4_000_000, batch=128,
                              train_nodes=20_000, cache_capacity=20_000, t_stale=6)
     assert run_workload_parity(torch, w3, 8, p_grad=0.7, model="gcn", backward=True, fused=True)[0] > 0
+    # half of the input columns fit one tile of the weight gradients, all of them do not
+    w4 = dataclasses.replace(w3, feat_dim=104, hidden=72, num_nodes=30_000, num_edges=500_000, batch=256, train_nodes=None)
+    assert run_workload_parity(torch, w4, 4, p_grad=0.7, model="gcn", backward=True, fused=True, device_sampler=True, device_counts=True)[0] > 0
 
 
 def test_iterations_bf16_with_backward_pass(env):

@@ -59,3 +59,17 @@ def test_binding_an_iteration_makes_no_view_of_the_input_layers_counts(monkeypat
     hp.__dict__.update(ring=4, _lists=[{}, {}, {}], counts_log=torch.zeros((4, 3, 3)), stats_log=torch.zeros((4, 3, 4)), input_log=Log())
     hp._bind(7)
     assert hp._input_cnt(2) == Log.base[3, 2].data_ptr()
+
+
+@pytest.mark.parametrize("n", [1, 589, 1767, 15903, 52000])
+@pytest.mark.parametrize("kind", ["sage", "gcn", "bf16"])
+def test_weight_gradient_workspace_is_that_of_the_widths_the_call_gets(kind, n):
+    """The workspace a model is set up with serves every layer's call: a GCN layer's goes with half its input width, whose split may
+    leave more partial results (15903 rows of 104 columns x 72: the call was refused)."""
+    pytest.importorskip("torch")
+    from paper_2301_07482_amd import pipeline as P
+    size = P.B.fg_layer_backward_weights_bf16_workspace_bytes if kind == "bf16" else P.B.fg_layer_backward_weights_workspace_bytes
+    for d_in in range(8, 520, 8):
+        for d_out in (8, 72, 128, 136, 256, 512):
+            width = d_in // 2 if kind == "gcn" else d_in
+            assert P.weight_grad_workspace_bytes(kind, n, d_in, d_out) >= size(n, width, d_out), (d_in, d_out)
