@@ -532,7 +532,8 @@ fg_status_t fg_cache_update_commit(fg_cache_t* cache, int64_t iter, int32_t n_la
  *   counts_dev [2] int64                  out: nodes of the layer below, edges of the block
  *   ws_dev, ws_bytes                      device workspace, >= fg_sample_block_workspace_bytes(max_rows, fanout) (0 for
  *                                         sizes the call rejects); 16-byte aligned
- * Six launches on `stream`, no host synchronisation. Node ids outside [0, num_nodes) get empty rows.
+ * Four launches on `stream` (one for a block of few draws), no host synchronisation. Node ids outside [0, num_nodes) get
+ * empty rows.
  */
 size_t fg_sample_block_workspace_bytes(int64_t max_rows, int32_t fanout);
 fg_status_t fg_sample_block(const int64_t* indptr_dev, const int32_t* indices_dev, int64_t num_nodes, int64_t num_edges,
@@ -557,6 +558,37 @@ fg_status_t fg_transpose_block(const int32_t* row_start_dev, const int32_t* row_
                                const int64_t* n_dev, int64_t max_rows, const int64_t* n_src_dev, int64_t max_src, int64_t max_nnz,
                                int32_t* t_start_dev, int32_t* t_end_dev, int32_t* t_row_dev, void* ws_dev, size_t ws_bytes,
                                void* stream);
+
+/*
+ * All blocks of a mini-batch, from the seeds down, in one call: fg_sample_block for layers[0], then for layers[1] on the list and
+ * the count layers[0] left, and so on, with the same results. A layer with t_start_dev also gets its block's transpose
+ * (fg_transpose_block, with max_src = max_below and max_nnz = max_rows * fanout): its stages share the launches of the next
+ * block, so that one comes first on the stream.
+ *   ids_dev, n_dev            the seeds: layers[0]'s distinct node ids, and their count on the device (NULL = layers[0].max_rows)
+ *   n_layers, layers          1..8 layers, top-down; every max_rows at most the max_below of the layer before
+ *   ws_dev, ws_bytes          device workspace, >= fg_sample_minibatch_workspace_bytes(n_layers, layers), which looks at the sizes and
+ *                             at whether t_start_dev is NULL (0 for sizes the call rejects); 16-byte aligned
+ * Three launches per block (one for a block of few draws), at most one more in front, no host synchronisation.
+ */
+typedef struct fg_sample_layer {
+    int32_t layer, fanout;       /* as in fg_sample_block */
+    int64_t max_rows;
+    int32_t* row_start_dev;      /* [max_rows] */
+    int32_t* row_end_dev;        /* [max_rows] */
+    int32_t* col_dev;            /* [max_rows * fanout] */
+    int32_t* col_ids_dev;        /* [max_rows * fanout], optional */
+    int32_t* ids_below_dev;      /* [max_below] */
+    int64_t max_below;
+    int64_t* counts_dev;         /* [2]: nodes of the layer below, edges */
+    int32_t* t_start_dev;        /* [max_below], optional, and with it ... */
+    int32_t* t_end_dev;          /* [max_below] */
+    int32_t* t_row_dev;          /* [max_rows * fanout] */
+} fg_sample_layer_t;
+
+size_t fg_sample_minibatch_workspace_bytes(int32_t n_layers, const fg_sample_layer_t* layers);
+fg_status_t fg_sample_minibatch(const int64_t* indptr_dev, const int32_t* indices_dev, int64_t num_nodes, int64_t num_edges,
+                                const int32_t* ids_dev, const int64_t* n_dev, int32_t n_layers, const fg_sample_layer_t* layers,
+                                uint64_t key, void* ws_dev, size_t ws_bytes, void* stream);
 
 /*
  * The estimate the access-aware admission ranks by: the rows read to produce each node's embedding in this mini-batch,

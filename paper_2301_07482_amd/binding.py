@@ -108,6 +108,16 @@ class FetchLayer(C.Structure):
                 ("h_dev", _p), ("h_rows", _i64), ("h_stride", _i64)]
 
 
+class SampleLayer(C.Structure):
+    """fg_sample_layer_t"""
+    _fields_ = [("layer", _i32), ("fanout", _i32), ("max_rows", _i64), ("row_start_dev", _p), ("row_end_dev", _p), ("col_dev", _p),
+                ("col_ids_dev", _p), ("ids_below_dev", _p), ("max_below", _i64), ("counts_dev", _p), ("t_start_dev", _p), ("t_end_dev", _p),
+                ("t_row_dev", _p)]
+
+
+FG_SAMPLE_MAX_LAYERS = 8
+SIGNATURES["fg_sample_minibatch_workspace_bytes"] = (_sz, [_i32, C.POINTER(SampleLayer)])
+SIGNATURES["fg_sample_minibatch"] = (_i32, [_p, _p, _i64, _i64, _p, _p, _i32, C.POINTER(SampleLayer), C.c_uint64, _p, _sz, _p])
 SIGNATURES["fg_cache_fetch_all"] = (_i32, [_p, _i32, C.POINTER(FetchLayer), _p])
 SIGNATURES["fg_cache_update_all"] = (_i32, [_p, _i64, _f, _i32, C.POINTER(UpdateLayer), _p, _sz, _p])
 SIGNATURES["fg_cache_update_select"] = (_i32, [_p, _i64, _f, _i32, C.POINTER(UpdateLayer), _p, _sz, _p])
@@ -435,6 +445,20 @@ def fg_sample_block(indptr, indices, num_nodes, num_edges, ids, n_dev, max_rows,
     _check(_lib.fg_sample_block(ptr(indptr), ptr(indices), num_nodes, num_edges, ptr(ids), ptr(n_dev), max_rows, fanout, key, layer,
                                 ptr(row_start), ptr(row_end), ptr(col), ptr(col_ids), ptr(ids_below), max_below, ptr(counts),
                                 ptr(ws), ws_bytes, stream))
+
+
+def sample_layers(specs):
+    """ctypes array of fg_sample_layer_t from dicts keyed by the field names (tensors or addresses for pointers)."""
+    return _struct_array(SampleLayer, specs)
+
+
+def fg_sample_minibatch_workspace_bytes(layers):
+    return int(_lib.fg_sample_minibatch_workspace_bytes(len(layers), layers))
+
+
+def fg_sample_minibatch(indptr, indices, num_nodes, num_edges, ids, n_dev, layers, key, ws, ws_bytes, stream=None):
+    _check(_lib.fg_sample_minibatch(ptr(indptr), ptr(indices), num_nodes, num_edges, ptr(ids), ptr(n_dev), len(layers), layers, key,
+                                    ptr(ws), ws_bytes, stream))
 
 
 def fg_transpose_block_workspace_bytes(max_src):

@@ -101,37 +101,57 @@ class SampledBatch:
 
 
 class DeviceSampler:
-    """Samples whole mini-batches with fg_sample_block over an in-neighbour CSR in HBM: one call per block, each layer's
-    device-side count feeding the next call. `sample(..., finish=False)` returns at once with the sizes still on the device
+    """Samples whole mini-batches over an in-neighbour CSR in HBM with one call (fg_sample_minibatch), each layer's device-side
+    count feeding the next block's launches. `sample(..., finish=False)` returns at once with the sizes still on the device
     (the path takes them from there); `finish()` reads them back for callers that want host integers."""
 
     def __init__(self, indptr, indices, num_nodes, fanouts, batch, device="cuda", transposes=False):
-        """transposes: also build the transposed blocks of layers 2..L (fg_transpose_block), which the backward pass walks."""
+        """transposes: also build the transposed blocks of layers 2..L, which the backward pass walks."""
         self.indptr, self.indices = indptr, indices
         self.num_nodes, self.num_edges = int(num_nodes), int(indices.numel())
         self.fanouts = [int(f) for f in fanouts]
         self.L = L = len(self.fanouts)
         self.device = device
+        self.transposes = transposes
         self.bound = [0] * (L + 1)
         self.bound[L] = int(batch)
         for l in range(L, 0, -1):
             self.bound[l - 1] = self.bound[l] * (1 + self.fanouts[l - 1])
-        self.out_at, at = {}, 0
-        for l in range(L, 0, -1):      # where each output array of a mini-batch starts in its one allocation (256-byte aligned)
+        # where each output array of a mini-batch lies in its one allocation (256-byte aligned), and the allocation as the sequence of
+        # pieces it is split into: every array, then the gap behind it
+        self.out_at, self.pieces, at = {}, [], 0
+        for l in range(L, 0, -1):
             rows, f = self.bound[l], self.fanouts[l - 1]
             offs = []
             tr = transposes and l >= 2      # t_start, t_end over the layer below, t_row over the edges
             for size in (rows, rows, rows * f, self.bound[l - 1], rows * f if l == 1 else 0,
                          self.bound[l - 1] if tr else 0, self.bound[l - 1] if tr else 0, rows * f if tr else 0):
                 offs.append(at)
-                at += -(-max(size, 1) // 64) * 64
+                room = -(-max(size, 1) // 64) * 64
+                self.pieces += [max(size, 1), room - max(size, 1)]
+                at += room
             self.out_at[l] = offs
         self.out_elems = at
-        self.ws_bytes = max(B.fg_sample_block_workspace_bytes(self.bound[l], self.fanouts[l - 1]) for l in range(1, L + 1))
-        self.transposes = transposes
-        if transposes:
-            self.ws_bytes = max([self.ws_bytes] + [B.fg_transpose_block_workspace_bytes(self.bound[l - 1]) for l in range(2, L + 1)])
+        # (more layers than a call takes are sampled by several calls, on one workspace)
+        self.ws_bytes = max([B.fg_sample_minibatch_workspace_bytes(g) for _, g in self._layers(self.bound[L], 4096, 4096)] or [0])
         self.ws = torch.zeros(self.ws_bytes, dtype=torch.uint8, device=device)
+
+    def _layers(self, n_seeds, base, cp):
+        """(top layer, descriptors) of each call, for outputs at address `base` and counts at `cp`."""
+        calls = []
+        for top in range(self.L, 0, -B.FG_SAMPLE_MAX_LAYERS):
+            layers = (B.SampleLayer * min(top, B.FG_SAMPLE_MAX_LAYERS))()
+            for l, y in zip(range(top, 0, -1), layers):
+                o = self.out_at[l]
+                y.layer, y.fanout, y.max_rows, y.max_below = l, self.fanouts[l - 1], self.bound[l] if l < self.L else n_seeds, self.bound[l - 1]
+                y.row_start_dev, y.row_end_dev, y.col_dev, y.ids_below_dev = base + 4 * o[0], base + 4 * o[1], base + 4 * o[2], base + 4 * o[3]
+                y.counts_dev = cp + 16 * (l - 1)
+                if l == 1:
+                    y.col_ids_dev = base + 4 * o[4]
+                if self.transposes and l >= 2:
+                    y.t_start_dev, y.t_end_dev, y.t_row_dev = base + 4 * o[5], base + 4 * o[6], base + 4 * o[7]
+            calls.append((top, layers))
+        return calls
 
     def buffers(self):
         """The output memory of one mini-batch (`sample(..., out=...)`): allocate it ahead of time, or reuse a consumed one."""
@@ -143,31 +163,29 @@ class DeviceSampler:
         finish=False: only the launches; `SampledBatch.finish()` later reads the counts back (sampling ahead of the
         consumer needs no synchronisation per mini-batch that way). ready=False: no event is recorded behind the launches
         (the caller sets the mini-batch's `ready` itself, behind whatever it adds on the device)."""
-        L, dev = self.L, self.device
-        st = torch.cuda.current_stream().cuda_stream
+        L = self.L
+        main = torch.cuda.current_stream()
         bt = SampledBatch(L)
         n_seeds = int(seeds.numel())
         assert n_seeds <= self.bound[L]
         buf, counts = out if out is not None else self.buffers()   # every output array; counts row l: nodes of layer l, edges of block l + 1
-        bt.ids[L] = seeds
         cp = counts.data_ptr()
-        for l in range(L, 0, -1):
-            f = self.fanouts[l - 1]
-            rows = self.bound[l] if l < L else n_seeds
-            o = self.out_at[l]
-            bt.start[l], bt.end[l] = buf[o[0]:o[0] + max(rows, 1)], buf[o[1]:o[1] + max(rows, 1)]
-            bt.col[l], bt.ids[l - 1] = buf[o[2]:o[2] + max(rows * f, 1)], buf[o[3]:o[3] + self.bound[l - 1]]
-            col_ids = buf[o[4]:o[4] + max(rows * f, 1)] if l == 1 else None
-            B.fg_sample_block(self.indptr, self.indices, self.num_nodes, self.num_edges, bt.ids[l], None if l == L else cp + 16 * l,
-                              rows, f, int(key), l, bt.start[l], bt.end[l], bt.col[l], col_ids, bt.ids[l - 1], self.bound[l - 1],
-                              cp + 16 * (l - 1), self.ws, self.ws_bytes, st)
+        for top, layers in self._layers(n_seeds, buf.data_ptr(), cp):
+            B.fg_sample_minibatch(self.indptr, self.indices, self.num_nodes, self.num_edges, seeds if top == L else ids_below,
+                                  None if top == L else cp + 16 * top, layers, int(key), self.ws, self.ws_bytes, main.cuda_stream)
+            ids_below = layers[len(layers) - 1].ids_below_dev
+        views = buf.split_with_sizes(self.pieces) if L else ()
+        bt.ids[L] = seeds
+        for i, l in enumerate(range(L, 0, -1)):
+            v = views[16 * i:16 * i + 16:2]
+            if l == L and n_seeds < self.bound[L]:
+                rows, f = max(n_seeds, 1), self.fanouts[l - 1]
+                v = (v[0][:rows], v[1][:rows], v[2][:max(n_seeds * f, 1)], v[3], v[4][:max(n_seeds * f, 1)], v[5], v[6], v[7][:max(n_seeds * f, 1)])
+            bt.start[l], bt.end[l], bt.col[l], bt.ids[l - 1] = v[0], v[1], v[2], v[3]
             if l == 1:
-                bt.col_ids1 = col_ids
+                bt.col_ids1 = v[4]
             if self.transposes and l >= 2:
-                nb = self.bound[l - 1]
-                bt.t_start[l], bt.t_end[l], bt.t_row[l] = buf[o[5]:o[5] + nb], buf[o[6]:o[6] + nb], buf[o[7]:o[7] + max(rows * f, 1)]
-                B.fg_transpose_block(bt.start[l], bt.end[l], bt.col[l], None if l == L else cp + 16 * l, rows, cp + 16 * (l - 1), nb,
-                                     rows * f, bt.t_start[l], bt.t_end[l], bt.t_row[l], self.ws, self.ws_bytes, st)
+                bt.t_start[l], bt.t_end[l], bt.t_row[l] = v[5], v[6], v[7]
         bt._counts, bt._bound, bt._n_seeds = counts, self.bound, n_seeds
         # until the sizes are read back: the bounds, and where each layer's count lives
         for l in range(L + 1):
@@ -177,7 +195,7 @@ class DeviceSampler:
             bt.nnz[l] = (self.bound[l] if l < L else n_seeds) * self.fanouts[l - 1]
         if ready:
             bt.ready = torch.cuda.Event()
-            bt.ready.record(torch.cuda.current_stream())
+            bt.ready.record(main)
         return bt.finish() if finish else bt
 
 

@@ -104,6 +104,12 @@ def test_argument_validation_needs_no_gpu(B):
     assert code(B.fg_transpose_block, None, 4096, 4096, None, 10, None, 30, 50, 4096, 4096, 4096, 4096, 1 << 20) == B.FG_ERR_INVALID_ARG
     assert code(B.fg_transpose_block, 4096, 4096, 4096, None, 10, None, 30, 50, 4096, 4096, None, 4096, 1 << 20) == B.FG_ERR_INVALID_ARG
     assert code(B.fg_transpose_block, 4096, 4096, 4096, None, 10, None, 30, 50, 4096, 4096, 4096, 4096, 16) == B.FG_ERR_SHAPE
+    smb = lambda n=1, **k: B.fg_sample_minibatch(4096, 4096, 100, 500, 4096, None, B.sample_layers([{**dict(
+        layer=1, fanout=5, max_rows=10, row_start_dev=4096, row_end_dev=4096, col_dev=4096, ids_below_dev=4096, max_below=60, counts_dev=4096),
+        **k}] * n), 7, 4096, 1 << 30)
+    assert code(smb, fanout=33) == B.FG_ERR_INVALID_ARG and code(smb, t_start_dev=4096) == B.FG_ERR_INVALID_ARG and code(smb, 9) == B.FG_ERR_INVALID_ARG
+    assert code(smb, max_below=9) == B.FG_ERR_SHAPE and code(smb, 2, max_rows=70, max_below=60) == B.FG_ERR_SHAPE
+    assert B.fg_sample_minibatch_workspace_bytes(B.sample_layers([dict(fanout=40, max_rows=1)])) == 0
     assert B.fg_transpose_block_workspace_bytes(5000) >= 5000 * 4 and B.fg_transpose_block_workspace_bytes(-1) == 0
     assert B.fg_cache_feature_rows(None) == 0 and B.fg_cache_buffer(None) == (None, 0) and B.fg_cache_ring_offset(None, 1) == -1
     assert code(B.fg_softmax_xent_grad, None, 64, 4096, 4, 16, 4096, 64) == B.FG_ERR_INVALID_ARG

@@ -796,7 +796,9 @@ def test_sample_block_matches_oracle(env, N, max_deg, hubs, n_seeds, fanouts, sl
     (9000, 30, 1024, 8, 1024, 23), (9000, 30, 896, 8, 897, 22), (9000, 30, 652, 11, 652, 24),      # and more
     (40, 60, 40, 11, 1024, 4), (3000, 3, 1, 1, 1, 5), (3000, 40, 0, 5, 7, 6),      # many repeats, one row, none
     (5000, 50, 1500, 8, 1501, 7), (5000, 50, 1500, 9, 1600, 8), (5000, 50, 1500, 16, 1500, 9), (5000, 50, 1500, 17, 1500, 10),
-    (4000, 40, 2600, 15, 600_000, 11)])                                 # a bound beyond what a workgroup adds up for itself
+    (4000, 40, 2600, 15, 600_000, 11), (4000, 40, 300, 32, 1_048_577, 31),     # (the second: beyond what a workgroup adds up for itself)
+    (9000, 30, 512, 8, 512, 25), (9000, 30, 512, 8, 513, 26), (9000, 30, 372, 11, 372, 27),      # one workgroup up to 4096 draws
+    (6000, 40, 5000, 15, 34_816, 28), (6000, 40, 5000, 15, 34_817, 29), (6000, 40, 5000, 1, 524_289, 30)])   # one slot per thread or four
 def test_sample_block_routes_match_oracle(env, N, max_deg, n_seeds, fanout, bound, seed):
     """One block at the sizes where fg_sample_block changes its launches (one workgroup or several, 8, 16 or 32 lanes per row,
     the counts of the candidates' workgroups added up by each or once), bit for bit."""
@@ -808,6 +810,41 @@ def test_sample_block_routes_match_oracle(env, N, max_deg, n_seeds, fanout, boun
     got = _device_sample(torch, B, dev(torch, indptr), dev(torch, indices), N, seeds, (fanout,), 77 + seed, bound - n_seeds)
     for key, l in (("ids", 0), ("start", 1), ("end", 1), ("col", 1), ("col_ids", 1)):
         assert got[key][l] == want[key][l], key
+
+
+@pytest.mark.parametrize("N,max_deg,hubs,batch,n_seeds,fanouts,seed", [
+    (9000, 30, 3, 200, 200, (3, 4, 5), 0),          # the seeds' block by one workgroup, its transpose rides behind it
+    (9000, 30, 3, 1024, 1000, (10, 5), 1),          # ... by three launches, fewer seeds than the bound
+    (300, 30, 40, 64, 64, (10, 10), 2),             # both blocks by one workgroup, few nodes
+    (6000, 40, 20, 1100, 1100, (15, 32), 3),        # four slots per thread
+    (6000, 40, 3, 4100, 700, (2, 32), 4),           # more than 131 072 sources: four stages for three launches
+    (3000, 20, 3, 5, 5, (1,) * 10, 5), (3000, 20, 3, 40, 40, (7,), 6), (3000, 20, 3, 8, 0, (3, 2, 2), 7)])
+def test_sample_minibatch_matches_oracle(env, N, max_deg, hubs, batch, n_seeds, fanouts, seed):
+    """fg_sample_minibatch with the transposes riding in the next block's launches, two mini-batches behind each other in the same
+    workspace and memory, against the oracle's sampler and transpose, bit for bit."""
+    torch, B = env
+    from oracle import sampler_oracle as S
+    from paper_2301_07482_amd.pipeline import DeviceSampler
+    indptr, indices = _random_multigraph(N, max_deg, seed, hubs)
+    sampler = DeviceSampler(dev(torch, indptr), dev(torch, indices), N, fanouts, batch, transposes=True)
+    r, L, out = np.random.default_rng(seed), len(fanouts), sampler.buffers()
+    for rep in range(2):
+        seeds, key = r.permutation(N)[:n_seeds], int(r.integers(0, 2 ** 62))
+        want = S.sample_minibatch(indptr, indices, seeds, fanouts, key)
+        bt = sampler.sample(dev(torch, seeds.astype(np.int32)), key, out=out)
+        for l in range(L, 0, -1):
+            n, nb, nnz = bt.n[l], bt.n[l - 1], bt.nnz[l]
+            assert (n, nb, nnz) == (len(want["ids"][l]), len(want["ids"][l - 1]), len(want["col"][l]))
+            assert bt.ids[l - 1].cpu().numpy()[:nb].tolist() == want["ids"][l - 1], f"nodes of layer {l - 1}"
+            for name in ("start", "end"):
+                assert getattr(bt, name)[l].cpu().numpy()[:n].tolist() == want[name][l], f"rows of block {l}"
+            assert bt.col[l].cpu().numpy()[:nnz].tolist() == want["col"][l], f"columns of block {l}"
+            if l == 1:
+                assert bt.col_ids1.cpu().numpy()[:nnz].tolist() == want["col_ids"][1]
+            if l >= 2:
+                t = S.transpose_block(want["start"][l], want["end"][l], want["col"][l], nb)
+                assert [x[l].cpu().numpy()[:m].tolist() for x, m in ((bt.t_start, nb), (bt.t_end, nb), (bt.t_row, nnz))] == [list(x) for x in t], \
+                    f"transpose of block {l}"
 
 
 @pytest.mark.parametrize("n,n_src,deg,src_bound,nnz_bound", [
