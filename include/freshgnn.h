@@ -734,6 +734,36 @@ fg_status_t fg_layer_backward_weights_bf16(const void* h_src_dev, int32_t n_src,
                                            const int64_t* n_rows_dev, int64_t max_rows, int32_t d_in, int32_t d_out,
                                            float* dw_dev, float* db_dev, void* ws_dev, size_t ws_bytes, void* stream);
 
+/*
+ * The weight gradients of several layers of one model in two launches (products, sums over the chunks): the results of
+ * fg_layer_backward_weights (compute_dtype FG_F32) or fg_layer_backward_weights_bf16 (FG_BF16) for every layer, up to where
+ * the rows are cut: the layers share the chip's workgroups. No fp32 sum has more rows than in the call for one layer.
+ * 1..8 layers; in bf16 the h_src of all layers are bf16 but for those of one other type.
+ *   ws_dev, ws_bytes    device workspace >= fg_backward_weights_all_workspace_bytes(...), which looks at max_rows, d_in and d_out
+ *                       (0 for sizes the call rejects); one for larger max_rows serves too; 16-byte aligned
+ */
+typedef struct fg_weight_grad_layer {
+    const void* h_src_dev;      /* all as in the calls for one layer */
+    int64_t src_stride;
+    const void* agg_dev;
+    int64_t agg_stride;
+    const float* dh_dev;
+    int64_t dh_stride;
+    const void* h_dev;
+    int64_t h_stride;
+    const int32_t* rows_dev;
+    const int64_t* n_rows_dev;
+    int64_t max_rows;
+    float* dw_dev;
+    float* db_dev;
+    fg_dtype_t src_dtype;
+    int32_t n_src, n, d_in, d_out;
+} fg_weight_grad_layer_t;
+
+size_t fg_backward_weights_all_workspace_bytes(fg_dtype_t compute_dtype, int32_t n_layers, const fg_weight_grad_layer_t* layers);
+fg_status_t fg_backward_weights_all(fg_dtype_t compute_dtype, int32_t n_layers, const fg_weight_grad_layer_t* layers, void* ws_dev,
+                                    size_t ws_bytes, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -115,7 +115,16 @@ class SampleLayer(C.Structure):
                 ("t_row_dev", _p)]
 
 
-FG_SAMPLE_MAX_LAYERS = 8
+class WeightGradLayer(C.Structure):
+    """fg_weight_grad_layer_t"""
+    _fields_ = [("h_src_dev", _p), ("src_stride", _i64), ("agg_dev", _p), ("agg_stride", _i64), ("dh_dev", _p), ("dh_stride", _i64),
+                ("h_dev", _p), ("h_stride", _i64), ("rows_dev", _p), ("n_rows_dev", _p), ("max_rows", _i64), ("dw_dev", _p), ("db_dev", _p),
+                ("src_dtype", _i32), ("n_src", _i32), ("n", _i32), ("d_in", _i32), ("d_out", _i32)]
+
+
+SIGNATURES["fg_backward_weights_all_workspace_bytes"] = (_sz, [_i32, _i32, C.POINTER(WeightGradLayer)])
+SIGNATURES["fg_backward_weights_all"] = (_i32, [_i32, _i32, C.POINTER(WeightGradLayer), _p, _sz, _p])
+FG_SAMPLE_MAX_LAYERS = FG_WEIGHT_GRAD_MAX_LAYERS = 8
 SIGNATURES["fg_sample_minibatch_workspace_bytes"] = (_sz, [_i32, C.POINTER(SampleLayer)])
 SIGNATURES["fg_sample_minibatch"] = (_i32, [_p, _p, _i64, _i64, _p, _p, _i32, C.POINTER(SampleLayer), C.c_uint64, _p, _sz, _p])
 SIGNATURES["fg_cache_fetch_all"] = (_i32, [_p, _i32, C.POINTER(FetchLayer), _p])
@@ -404,6 +413,19 @@ def fg_layer_backward_weights_bf16(h_src, n_src, src_stride, src_dtype, agg, agg
     _check(_lib.fg_layer_backward_weights_bf16(ptr(h_src), n_src, src_stride, src_dtype, ptr(agg), agg_stride, ptr(dh), dh_stride, ptr(h),
                                                h_stride, n, ptr(rows), ptr(n_rows), max_rows, d_in, d_out, ptr(dw), ptr(db), ptr(ws),
                                                ws_bytes, stream))
+
+
+def weight_grad_layers(specs):
+    """ctypes array of fg_weight_grad_layer_t from dicts keyed by the field names (tensors or addresses for pointers)."""
+    return _struct_array(WeightGradLayer, specs)
+
+
+def fg_backward_weights_all_workspace_bytes(compute_dtype, layers):
+    return int(_lib.fg_backward_weights_all_workspace_bytes(compute_dtype, len(layers), layers))
+
+
+def fg_backward_weights_all(compute_dtype, layers, ws, ws_bytes, stream=None):
+    _check(_lib.fg_backward_weights_all(compute_dtype, len(layers), layers, ptr(ws), ws_bytes, stream))
 
 
 _POINTER_FIELDS = {}

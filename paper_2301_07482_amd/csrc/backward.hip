@@ -709,47 +709,38 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 // mask; the bias gradient sums the unrounded dz), one product each.
 //
 // v_mfma_f32_32x32x16_bf16 wants its contraction index contiguous in a lane, which for X^T . dz is the row index, so both
-// operands go through LDS transposed: a step is 32 rows; a thread loads 8 rows of its column (or of a pair of 16-bit
-// columns; each load coalesced over the columns), masks and splits them and writes 16-byte fragments where the lane that
-// needs them for (column, 8 rows) reads them back with one LDS load: [term][group of 8 rows][column]. Rows are the same for
-// a whole wavefront, so their addresses are scalars. Two LDS buffers, one barrier per step; while step s is multiplied the
-// values of step s + 1 are in flight and the positions of step s + 2 are there (values two steps ahead: a second set of registers,
-// steps 6 % shorter, the first one later: not faster below some 30 steps).
+// operands go through LDS and are transposed on the way out of it (ds_read_b64_tr_b16): a step is 32 rows; a thread loads 16 bytes
+// of a row, coalesced over the columns, masks and splits them and writes each term's bf16 values row by row. Two LDS buffers,
+// one barrier per step; while step s is multiplied the values of step s + 1 are in flight and the positions of step s + 2 are
+// there (values two steps ahead: a second set of registers, which are all taken).
 //
 // Split: every chunk of rows leaves a partial result of 2*d_in x d_out that the reduction reads again, and every tile of
 // the result reads the operands again, so the tile is as large as LDS and registers allow.
 //
-// What bounds it: issuing the loads and forming their addresses (a step of a 128 x 128 tile is 1.9 us in fp32, 1.15 mixed; with the
-// offsets multiplied out on the scalar unit for each row, not once per lane, it was 2.1 and 1.45), then reading the operands
-// (52 k rows x 256 x 256: 160 MB and 33 MB of partial results). Measured with its reduction, before (one 256 x 256 tile;
-// mixed precision: a transposing pass, then a product that did not split the rows) and now, rows x 2*d_in x d_out: fp32 52 k x 256 x 256
-// 67 -> 61 us, 6 k x 512 x 256 37 -> 27, 1 k x 1024 x 256 27 -> 21; mixed 5.9 k x 1536 x 1024 93 -> 62, 52 k x 512 x 256
-// 528 -> 52, 1 k x 1024 x 1024 30 -> 28; 1 k x 2048 x 1024 35 -> 37 and 700 rows 29 -> 33 remain slower, a short contraction with
-// a large result, where the transposing pass had little to do.
+// What bounds it: reading the operands. 55 k rows x 256 x 256 in fp32 are 169 MB (X, dh, and h for its mask), 33 us at the rate of
+// a large copy; a step of a 256 x 128 tile takes 2.7 us (2.8 with 4-byte loads of eight rows per thread, transposed by what a
+// thread wrote), in mixed precision, where tiles find the rows in L2 and one step of look-ahead does not cover its latency, a
+// step of 256 x 256 1.35 (1.7). Measured with its reduction, before and now, rows x 2*d_in x d_out: fp32 55 k x 256 x 256 68.5 -> 64.5 us,
+// 6 k x 512 x 256 28.4 -> 26.7, 1 k x 512 x 172 14.9 -> 14.5; mixed 7 k (bound 16 k) x 1536 x 1024 69.8 -> 61.1, 1 k x 2048 x 1024 36.6 ->
+// 35.5, 16 k x 1536 x 1024 125 -> 105.
 typedef unsigned int wu32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 wbf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 wbf16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 wf16x8 __attribute__((ext_vector_type(8)));
+typedef short ws16x4 __attribute__((ext_vector_type(4)));
+typedef wu32x4 wu32x4a __attribute__((aligned(4)));      // 16 bytes from an address that is a multiple of 4
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 
 constexpr int WX_STEP = 32;             // rows per step: two matrix instructions deep
-constexpr int WX_GROUPS = WX_STEP / 8;  // groups of 8 rows: one 16-byte fragment per column and term
-constexpr size_t wx_lds_bytes(int tm, int tn, int terms) { return (size_t)2 * terms * WX_GROUPS * (tm + tn) * 16; }
+constexpr size_t wx_lds_bytes(int tm, int tn, int terms) { return (size_t)2 * terms * WX_STEP * (tm + tn) * 2; }
 
-// v[0..7] -> three fragments of eight bf16 (element j in half j % 2 of word j / 2)
-__device__ __forceinline__ void wx_split8(const float* v, wu32x4& t1, wu32x4& t2, wu32x4& t3) {
+// two values -> their three bf16 terms, a word each (the first value in its lower half)
+__device__ __forceinline__ void wx_split2(float a, float b, unsigned int (&u)[3]) {
+    f32x2 x = {a, b};
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const f32x2 x = {v[2 * p], v[2 * p + 1]};
-        const wbf16x2 b1 = __builtin_convertvector(x, wbf16x2);
-        const unsigned int u1 = __builtin_bit_cast(unsigned int, b1);
-        const f32x2 r1 = {x[0] - __uint_as_float(u1 << 16), x[1] - __uint_as_float(u1 & 0xFFFF0000u)};
-        const wbf16x2 b2 = __builtin_convertvector(r1, wbf16x2);
-        const unsigned int u2 = __builtin_bit_cast(unsigned int, b2);
-        const f32x2 r2 = {r1[0] - __uint_as_float(u2 << 16), r1[1] - __uint_as_float(u2 & 0xFFFF0000u)};
-        const wbf16x2 b3 = __builtin_convertvector(r2, wbf16x2);
-        t1[p] = u1;
-        t2[p] = u2;
-        t3[p] = __builtin_bit_cast(unsigned int, b3);
+    for (int term = 0; term < 3; ++term) {
+        u[term] = __builtin_bit_cast(unsigned int, __builtin_convertvector(x, wbf16x2));
+        x = f32x2{x[0] - __uint_as_float(u[term] << 16), x[1] - __uint_as_float(u[term] & 0xFFFF0000u)};
     }
 }
 
@@ -758,30 +749,36 @@ struct WgIn {
     int64_t src_stride, agg_stride, dh_stride, h_stride, max_rows;
     const int32_t* rows;
     const int64_t* n_rows_dev;
-    int n_src, n, d_in, d_pad, d_out, n_chunks, tiles_m, tiles_n;
+    int n_src, n, d_in, d_pad, d_out, n_chunks, parts, tiles_m, tiles_n;      // parts: partial results of a chunk
+    int src, tm;                           // element type of h_src; rows of a tile
+    float *part_w, *part_b;                // partial results of every chunk; of a single chunk the result (part_b of a call without db: workspace)
+    float *dw, *db;
 };
 
-// the offset that lane `from` holds, as a scalar
-__device__ __forceinline__ int64_t wx_lane_offset(int64_t at, int from) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)at, from), hi = (uint32_t)__builtin_amdgcn_readlane((int)(at >> 32), from);
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
+// The layers of one call: their products share a launch, each with its share of the workgroups, and their reductions another. By
+// itself a layer of few rows fills the chip only with chunks so short that starting them costs more than the products.
+constexpr int WG_MAX_LAYERS = 8;
+struct WgBatch {
+    int n;
+    int first[WG_MAX_LAYERS + 1];          // first workgroup of each layer: products ...
+    int red_first[WG_MAX_LAYERS + 1];      // ... and reduction
+    WgIn l[WG_MAX_LAYERS];
+};
 
-// TM x TN: the tile of the result, 8 wavefronts as 4 x 2. SRC: element type of h_src (TERMS = 3: fp32).
+// TM x TN: the tile of the result, 8 wavefronts as 4 x 2. SRC: element type of h_src (TERMS = 3: fp32). unit: which chunk and tile.
 template <int TM, int TN, int TERMS, int SRC>
-__global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_tile_kernel(WgIn A, float* __restrict__ part_w, float* __restrict__ part_b) {
-    constexpr int W = (TERMS == 1 && TM == 256) ? 2 : 1;          // adjacent columns per thread
-    constexpr int XT = TM / W, ZT = TN / W;                       // threads side by side on a row
-    constexpr int XU = XT * WX_GROUPS / WG_THREADS, ZU = ZT * WX_GROUPS / WG_THREADS;      // groups of 8 rows per thread
-    constexpr int XR = (TERMS == 1 && W == 2 && SRC == FG_F32) ? 2 : 1;                    // words per loaded piece of h_src
-    constexpr int XFRAGS = TERMS * WX_GROUPS * TM, BUF = TERMS * WX_GROUPS * (TM + TN);
+__device__ __forceinline__ void weight_grad_tile(const WgIn& A, const int unit) {
+    constexpr int CPT = TERMS == 3 ? 4 : 8;                       // adjacent columns per thread: 16 bytes of an operand
+    constexpr int XT = TM / CPT, ZT = TN / CPT;                   // threads side by side on a row
+    constexpr int XS = WG_THREADS / XT, ZS = WG_THREADS / ZT;     // rows of a step that are loaded together
+    constexpr int XU = WX_STEP / XS, ZU = WX_STEP / ZS;           // rows per thread
+    constexpr int XW = (TERMS == 1 && SRC == FG_F32) ? 2 : 1;     // 16-byte words per loaded piece of h_src
+    constexpr int XP = WX_STEP * TM * 2, ZP = WX_STEP * TN * 2, BUF = TERMS * (XP + ZP);      // bytes of a term's rows, of a buffer
     constexpr int MB = TM / 128, NB = TN / 64;                    // 32 x 32 blocks per wavefront
     constexpr int ESZ = SRC == FG_F32 ? 4 : 2, ASZ = TERMS == 3 ? 4 : 2;                   // bytes per element: h_src; agg and h
-    extern __shared__ __attribute__((aligned(16))) wu32x4 wx_lds[];   // [buffer][X, then dz][term][group][column]
-    // A chunk's tiles read the same rows: the workgroups of one XCD (ids congruent mod 8) take consecutive (chunk, tile) pairs
+    static_assert(XS % 4 == 0 && ZS % 4 == 0, "a thread's rows have the same place in their group of four");
+    extern __shared__ __attribute__((aligned(16))) char wx_lds[];   // [buffer][X, then dz][term][row][column]
     const int tiles = A.tiles_m * A.tiles_n;
-    const int unit = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
-    if (unit >= A.n_chunks * tiles) return;       // uniform over the workgroup, before any barrier
     const int chunk = unit / tiles, tile = unit % tiles;
     const int m_tile = (tile / A.tiles_n) * TM, n_tile = (tile % A.tiles_n) * TN;
     int64_t n_rows = A.n_rows_dev ? *A.n_rows_dev : A.max_rows;
@@ -798,26 +795,31 @@ __global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_tile_kernel(WgIn A,
     if (k_end > n_rows) k_end = n_rows;
     const int n_steps = (int)((k_end - k_begin + WX_STEP - 1) / WX_STEP);
 
-    // Staging role of this thread: W adjacent columns of X and of dz, rows 8 * group .. + 7 of a step for its groups xg + .., zg + ..:
-    // the same for all lanes of a wavefront. Each half of X is walked as if it were d_pad columns wide, so that a wavefront's
-    // columns lie in one half. (A column that does not exist reads another one: its products go to outputs that are not stored.)
-    const int xp = (t % XT) * W, zp = (t % ZT) * W;
-    const int xg = __builtin_amdgcn_readfirstlane(t / XT), zg = __builtin_amdgcn_readfirstlane(t / ZT);
-    const bool x_agg = __builtin_amdgcn_readfirstlane(m_tile + xp) >= A.d_pad;
+    // Staging role of this thread: CPT adjacent columns of X and of dz, rows xr + i * XS and zr + i * ZS of a step. Each half of X is walked
+    // as if it were d_pad columns wide. (A column that does not exist reads another one: its products go to outputs that are
+    // not stored.)
+    const int xp = (t % XT) * CPT, zp = (t % ZT) * CPT;
+    const int xr = XT == 64 ? wave : t / XT, zr = ZT == 64 ? wave : t / ZT;
+    const bool x_agg = m_tile + xp >= A.d_pad;
     const int xc = m_tile + xp - (x_agg ? A.d_pad : 0), zc = n_tile + zp;
-    const char* x_base = x_agg ? A.agg : A.h_src;
+    const char* x_base = (x_agg ? A.agg : A.h_src) + (xc < d_in ? xc : 0) * (x_agg ? ASZ : ESZ);
     const int64_t x_stride = x_agg ? A.agg_stride : A.src_stride;
-    const int x_off = (xc < d_in ? xc : 0) * (x_agg ? ASZ : ESZ), z_off = (zc < N ? zc : 0) * 4, h_off = (zc < N ? zc : 0) * (A.h ? ASZ : 4);
-    const char* hm = A.h ? A.h : A.dh;                       // without a mask: the words of dh again, replaced by 1
-    const int64_t hm_stride = A.h ? A.h_stride : A.dh_stride;
-    const unsigned int h_and = A.h ? 0xFFFFFFFFu : 0u, h_or = A.h ? 0u : 0x3F800000u;
+    const char* g_base = A.dh + (zc < N ? zc : 0) * 4;
+    const char* o_base = (A.h ? A.h : A.dh) + (zc < N ? zc : 0) * ASZ;      // without a mask: words of dh again, replaced by ones
+    const int64_t o_stride = A.h ? A.h_stride : A.dh_stride;
+    const unsigned int o_and = A.h ? 0xFFFFFFFFu : 0u, o_or = A.h ? 0u : 0x3F803F80u;
+    const int x_second = x_agg ? 0 : 16;
     const int kb = (int)k_begin, ke = (int)k_end;            // list entries are positions: below 2^31
+    // Where its pieces go: the 64-byte windows of a row (32 columns, a matrix instruction's block) are exchanged by the row's place in
+    // its group of four, so that the four rows a transposing read takes 64 bytes of lie in different banks.
+    const int x_to = xr * (TM * 2) + (((xp >> 5) ^ (xr & 3)) << 6) + ((xp & 31) << 1);
+    const int z_to = zr * (TN * 2) + (((zp >> 5) ^ (zr & 3)) << 6) + ((zp & 31) << 1);
 
     struct Vals {
-        unsigned int x[XU][8][XR];
-        float g[ZU][8][W];
-        unsigned int o[ZU][8];
-        unsigned int x_in, z_in;      // bit e: row e of the step exists for this thread's columns of X, for dz (scalars)
+        wu32x4 x[XU][XW];
+        wu32x4 g[ZU][CPT / 4];
+        wu32x4 o[ZU];
+        unsigned int x_in, z_in;      // bit e: row e of the step has own features, exists (scalars)
     };
     // position of row `l32` of step s; one load for the whole step, one register
     const int32_t* list = A.rows ? A.rows : (const int32_t*)A.dh;
@@ -827,127 +829,108 @@ __global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_tile_kernel(WgIn A,
         const int32_t raw = list[A.rows ? ks : 0];
         return A.rows ? raw : ks;
     };
-    // Values of step s from the positions loaded for it. The rows of a group are the same for the whole wavefront: a lane forms
-    // its row's offsets, once per step, and each is read out of the lane that holds it. Rows that do not exist read
-    // row 0 / the last entry and are masked when they are staged (with masks, not branches: a branch per row would make the
-    // wavefront wait for each load by itself).
+    auto of_row = [](int v, int row, bool uniform) { return uniform ? __builtin_amdgcn_readlane(v, row) : __shfl(v, row, 64); };
+    // Values of step s from the positions loaded for it. Rows that do not exist read row 0 / the last entry and are masked when they
+    // are staged (with masks, not branches: a branch per row would make the wavefront wait for each load by itself).
     auto load_values = [&](int s, int32_t raw, Vals& V) {
         const int kk = kb + s * WX_STEP + l32;
         // a position without own features: the fp32 product leaves the row out, the mixed one takes zeros for them
         const bool z_ok = kk < ke && raw >= 0 && raw < A.n && (TERMS == 1 || raw < A.n_src);
-        const bool x_ok = z_ok && (x_agg || raw < A.n_src);
-        const int32_t pos = z_ok ? raw : 0, x_row = x_agg ? (kk < ke ? kk : ke - 1) : (x_ok ? raw : 0);
-        const int64_t x_at = (int64_t)x_row * x_stride, g_at = (int64_t)pos * A.dh_stride, o_at = (int64_t)pos * hm_stride;
+        const bool x_ok = z_ok && raw < A.n_src;
+        const int32_t pos = z_ok ? raw : 0, own = x_ok ? raw : 0;
         V.x_in = (unsigned int)__ballot(x_ok);
         V.z_in = (unsigned int)__ballot(z_ok);
 #pragma unroll
-        for (int i = 0; i < XU; ++i)
+        for (int i = 0; i < XU; ++i) {
+            const int r = xr + i * XS, at = kb + s * WX_STEP + r;
+            const int32_t own_r = of_row(own, r, XT == 64), x_row = x_agg ? (at < ke ? at : ke - 1) : own_r;
+            const char* p = x_base + (int64_t)x_row * x_stride;
+            V.x[i][0] = *(const wu32x4a*)p;
+            if constexpr (XW == 2) V.x[i][1] = *(const wu32x4a*)(p + x_second);
+        }
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const char* p = x_base + wx_lane_offset(x_at, 8 * (xg + i * (WG_THREADS / XT)) + e);
-                if constexpr (TERMS == 3 || W == 2) {
-                    V.x[i][e][0] = *(const unsigned int*)(p + x_off);
-                    if constexpr (XR == 2) V.x[i][e][1] = *(const unsigned int*)(p + (x_off + (x_agg ? 0 : 4)));
-                } else if constexpr (SRC == FG_F32) {
-                    V.x[i][e][0] = *(const unsigned int*)(p + (x_off & ~3));      // a mean (bf16): the word it lies in
-                } else {
-                    V.x[i][e][0] = *(const unsigned short*)(p + x_off);
-                }
-            }
+        for (int i = 0; i < ZU; ++i) {
+            const int64_t pos_r = of_row(pos, zr + i * ZS, ZT == 64);
+            const char* p = g_base + pos_r * A.dh_stride;
 #pragma unroll
-        for (int i = 0; i < ZU; ++i)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int from = 8 * (zg + i * (WG_THREADS / ZT)) + e;
-                const char* gp = A.dh + wx_lane_offset(g_at, from);
-#pragma unroll
-                for (int w = 0; w < W; ++w) V.g[i][e][w] = *(const float*)(gp + (z_off + 4 * w));
-                const char* hp = hm + wx_lane_offset(o_at, from);
-                if constexpr (TERMS == 3 || W == 2)
-                    V.o[i][e] = *(const unsigned int*)(hp + h_off);
-                else
-                    V.o[i][e] = *(const unsigned short*)(hp + h_off);
-            }
-    };
-    // rows that do not exist become zeros (only a chunk's last step, or a list with bad entries, has any)
-    auto mask_rows = [&](Vals& V) {
-        if ((V.x_in & V.z_in) == 0xFFFFFFFFu) return;      // uniform
-#pragma unroll
-        for (int i = 0; i < XU; ++i)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const unsigned int m = 0u - ((V.x_in >> (8 * (xg + i * (WG_THREADS / XT)) + e)) & 1u);
-#pragma unroll
-                for (int q = 0; q < XR; ++q) V.x[i][e][q] &= m;
-            }
-#pragma unroll
-        for (int i = 0; i < ZU; ++i)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const unsigned int m = 0u - ((V.z_in >> (8 * (zg + i * (WG_THREADS / ZT)) + e)) & 1u);
-#pragma unroll
-                for (int w = 0; w < W; ++w) V.g[i][e][w] = __uint_as_float(__float_as_uint(V.g[i][e][w]) & m);
-            }
-    };
-    double colsum[W];
-#pragma unroll
-    for (int w = 0; w < W; ++w) colsum[w] = 0.0;
-    auto put = [&](wu32x4* to, int tile_w, int group, int col, const float* v) {
-        if constexpr (TERMS == 3) {
-            wu32x4 a1, a2, a3;
-            wx_split8(v, a1, a2, a3);
-            to[(0 * WX_GROUPS + group) * tile_w + col] = a1;
-            to[(1 * WX_GROUPS + group) * tile_w + col] = a2;
-            to[(2 * WX_GROUPS + group) * tile_w + col] = a3;
-        } else {
-            const f32x8 f = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]};
-            to[group * tile_w + col] = __builtin_bit_cast(wu32x4, __builtin_convertvector(f, wbf16x8));
+            for (int w = 0; w < CPT / 4; ++w) V.g[i][w] = *(const wu32x4a*)(p + 16 * w);
+            V.o[i] = *(const wu32x4a*)(o_base + pos_r * o_stride);
         }
     };
-    // mask, split and write the loaded step to buffer b
+    double colsum[CPT];
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) colsum[c] = 0.0;
+    // the bf16 terms of CPT values to their places in the term's rows
+    auto put = [&](char* to, int term_bytes, const float* v) {
+        if constexpr (TERMS == 3) {
+            unsigned int lo[3], hi[3];
+            wx_split2(v[0], v[1], lo);
+            wx_split2(v[2], v[3], hi);
+#pragma unroll
+            for (int term = 0; term < 3; ++term) *(uint2*)(to + term * term_bytes) = uint2{lo[term], hi[term]};
+        } else {
+            const f32x8 f = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]};
+            *(wu32x4*)to = __builtin_bit_cast(wu32x4, __builtin_convertvector(f, wbf16x8));
+        }
+    };
+    // mask, split and write the loaded step to buffer b; rows that do not exist become zeros (only a chunk's last step, or a list
+    // with bad entries, has any)
     auto stage = [&](int b, Vals& V) {
-        mask_rows(V);
-        wu32x4* X = wx_lds + b * BUF;
-        wu32x4* Z = X + XFRAGS;
+        char* X = wx_lds + b * BUF;
+        char* Z = X + TERMS * XP;
+        const bool whole = (V.x_in & V.z_in) == 0xFFFFFFFFu;      // uniform
+        const unsigned int x_in = x_agg ? V.z_in : V.x_in;
 #pragma unroll
-        for (int i = 0; i < XU; ++i)
+        for (int i = 0; i < XU; ++i) {
+            if (!whole) {
+                const unsigned int m = 0u - ((x_in >> (xr + i * XS)) & 1u);
 #pragma unroll
-            for (int w = 0; w < W; ++w) {
-                float v[8];
+                for (int w = 0; w < XW; ++w) V.x[i][w] &= m;
+            }
+            float v[CPT];
+            if constexpr (TERMS == 3) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const unsigned int raw = V.x[i][e][0];
-                    float f;
-                    if constexpr (TERMS == 3) {
-                        f = __uint_as_float(raw);
+                for (int c = 0; c < 4; ++c) v[c] = __uint_as_float(V.x[i][0][c]);
+                put(X + x_to + i * XS * TM * 2, XP, v);
+            } else {
+                // the means, and own embeddings, are bf16 already
+                wu32x4 u = V.x[i][0];
+                if constexpr (SRC != FG_BF16) {
+                    if constexpr (SRC == FG_F16) {
+                        const f32x8 f = __builtin_convertvector(__builtin_bit_cast(wf16x8, u), f32x8);
+#pragma unroll
+                        for (int c = 0; c < 8; ++c) v[c] = f[c];
                     } else {
-                        const unsigned short own16 = (unsigned short)(W == 2 ? raw >> (16 * w) : raw);
-                        const unsigned short agg16 = (unsigned short)((W == 2 ? w : (SRC == FG_F32 ? (x_off & 2) : 0)) ? raw >> 16 : raw);
-                        const float self = SRC == FG_F32   ? __uint_as_float(XR == 2 && w ? V.x[i][e][XR - 1] : raw)
-                                           : SRC == FG_F16 ? __half2float(__ushort_as_half(own16))
-                                                           : bw_bf16_value(own16);
-                        f = x_agg ? bw_bf16_value(agg16) : self;
+#pragma unroll
+                        for (int c = 0; c < 8; ++c) v[c] = __uint_as_float(V.x[i][c / 4][c % 4]);
                     }
-                    v[e] = f;
+                    const f32x8 f = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]};
+                    const wu32x4 own = __builtin_bit_cast(wu32x4, __builtin_convertvector(f, wbf16x8));
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) u[q] = x_agg ? u[q] : own[q];
                 }
-                put(X, TM, xg + i * (WG_THREADS / XT), xp + w, v);
+                *(wu32x4*)(X + x_to + i * XS * TM * 2) = u;
             }
+        }
 #pragma unroll
-        for (int i = 0; i < ZU; ++i)
+        for (int i = 0; i < ZU; ++i) {
+            if (!whole) {
+                const unsigned int m = 0u - ((V.z_in >> (zr + i * ZS)) & 1u);
 #pragma unroll
-            for (int w = 0; w < W; ++w) {
-                float v[8], s8 = 0.f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const unsigned int raw = V.o[i][e];
-                    const float o = TERMS == 3 ? __uint_as_float(raw) : bw_bf16_value((unsigned short)(w ? raw >> 16 : raw));
-                    const float act = __uint_as_float((__float_as_uint(o) & h_and) | h_or);
-                    v[e] = act > 0.f ? V.g[i][e][w] : 0.f;
-                    s8 += v[e];
-                }
-                colsum[w] += (double)s8;
-                put(Z, TN, zg + i * (WG_THREADS / ZT), zp + w, v);
+                for (int w = 0; w < CPT / 4; ++w) V.g[i][w] &= m;
             }
+            float v[CPT];
+#pragma unroll
+            for (int c = 0; c < CPT; ++c) {
+                const unsigned int raw = (V.o[i][TERMS == 3 ? c : c / 2] & o_and) | o_or;
+                const float act = __uint_as_float(TERMS == 3 ? raw : (c & 1 ? raw & 0xFFFF0000u : raw << 16));
+                v[c] = act > 0.f ? __uint_as_float(V.g[i][c / 4][c % 4]) : 0.f;
+            }
+            if (m_tile == 0)      // uniform: the bias gradient is summed by the tiles of the first rows
+#pragma unroll
+                for (int c = 0; c < CPT; ++c) colsum[c] += (double)v[c];
+            put(Z + z_to + i * ZS * TN * 2, ZP, v);
+        }
     };
 
     // `lead` takes the products of the leading terms, `rest` the others (TERMS = 3 only)
@@ -961,22 +944,33 @@ __global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_tile_kernel(WgIn A,
                 lead[i][j][e] = 0.f;
                 if constexpr (TERMS == 3) rest[i][j][e] = 0.f;
             }
+    // A fragment (column l32 of a block, 8 rows from 8 * half on) is two transposing reads: of the 16 lanes of a group, lane 4 * j + c reads
+    // columns 4 c .. 4 c + 3 of row j, and lane i gets column i of the four rows.
+    const int place = (lane >> 2) & 3, row_from = 8 * half + place, in_window = ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+    int x_from[MB], z_from[NB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) x_from[mb] = row_from * (TM * 2) + ((((wm >> 5) + mb) ^ place) << 6) + in_window;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) z_from[nb] = TERMS * XP + row_from * (TN * 2) + ((((wn >> 5) + nb) ^ place) << 6) + in_window;
+    auto fragment = [&](int at, int row_bytes) -> wbf16x8 {
+        typedef __attribute__((address_space(3))) ws16x4* lds_s16x4;
+        const ws16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(wx_lds + at));
+        const ws16x4 c = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(wx_lds + at + 4 * row_bytes));
+        return __builtin_bit_cast(wbf16x8, __builtin_shufflevector(a, c, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
     auto multiply = [&](int b) {
-        const wu32x4* X = wx_lds + b * BUF;
-        const wu32x4* Z = X + XFRAGS;
 #pragma unroll
         for (int ph = 0; ph < WX_STEP / 16; ++ph) {
-            const int g = 2 * ph + half;
-            wu32x4 ax[MB][TERMS];
+            wbf16x8 ax[MB][TERMS];
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int term = 0; term < TERMS; ++term) ax[mb][term] = X[(term * WX_GROUPS + g) * TM + wm + mb * 32 + l32];
+                for (int term = 0; term < TERMS; ++term) ax[mb][term] = fragment(b * BUF + x_from[mb] + term * XP + ph * 16 * TM * 2, TM * 2);
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                wu32x4 bz[TERMS];
+                wbf16x8 bz[TERMS];
 #pragma unroll
-                for (int term = 0; term < TERMS; ++term) bz[term] = Z[(term * WX_GROUPS + g) * TN + wn + nb * 32 + l32];
+                for (int term = 0; term < TERMS; ++term) bz[term] = fragment(b * BUF + z_from[nb] + term * ZP + ph * 16 * TN * 2, TN * 2);
                 if constexpr (TERMS == 3) {      // (X term, dz term) pairs, smallest products first
                     constexpr int TA[5] = {2, 0, 1, 1, 0};
                     constexpr int TZ[5] = {0, 2, 1, 0, 1};
@@ -984,16 +978,39 @@ __global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_tile_kernel(WgIn A,
                     for (int e = 0; e < 5; ++e)
 #pragma unroll
                         for (int mb = 0; mb < MB; ++mb)
-                            rest[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(wbf16x8, ax[mb][TA[e]]),
-                                                                                   __builtin_bit_cast(wbf16x8, bz[TZ[e]]), rest[mb][nb], 0, 0, 0);
+                            rest[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ax[mb][TA[e]], bz[TZ[e]], rest[mb][nb], 0, 0, 0);
                 }
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-                    lead[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(wbf16x8, ax[mb][0]),
-                                                                           __builtin_bit_cast(wbf16x8, bz[0]), lead[mb][nb], 0, 0, 0);
+                for (int mb = 0; mb < MB; ++mb) lead[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ax[mb][0], bz[0], lead[mb][nb], 0, 0, 0);
             }
         }
     };
+
+    // A partial result: accumulator element e of a block is its row 8 * (e / 4) + 4 * half + e % 4, column l32. (The addresses are formed
+    // on the spot: hoisted out of the loop over the steps they would take registers the loop has not got.)
+    auto store_part = [&](int part) {
+        int m0 = m_tile + wm + 4 * half, c0 = n_tile + wn + l32;
+        asm volatile("" : "+v"(m0), "+v"(c0));
+        float* pw = A.part_w + ((int64_t)chunk * A.parts + part) * M * N;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int mp = m0 + mb * 32 + 8 * (e >> 2) + (e & 3);
+                const int m = mp < A.d_pad ? (mp < d_in ? mp : M) : d_in + mp - A.d_pad;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    const int c = c0 + nb * 32;
+                    float v = lead[mb][nb][e];
+                    if constexpr (TERMS == 3) v += rest[mb][nb][e];
+                    if (m < M && c < N) pw[(int64_t)m * N + c] = v;
+                    lead[mb][nb][e] = 0.f;
+                    if constexpr (TERMS == 3) rest[mb][nb][e] = 0.f;
+                }
+            }
+    };
+    const int part_steps = (n_steps + A.parts - 1) / A.parts;
+    int part = 0;
 
     if (n_steps > 0) {      // uniform over the workgroup
         Vals V;
@@ -1011,52 +1028,74 @@ __global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_tile_kernel(WgIn A,
             load_values(s + 2, p2, V);
             p2 = load_positions(s + 3);
             __syncthreads();
+            if (s + 1 == (part + 1) * part_steps || s + 1 == n_steps) store_part(part++);      // uniform
         }
     }
-    // partial result of this chunk (zeros if the chunk lies beyond the rows there are): accumulator element e of a block is
-    // its row 8 * (e / 4) + 4 * half + e % 4, column l32
-    float* pw = part_w + (int64_t)chunk * M * N;
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int mp = m_tile + wm + mb * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
-            const int m = mp < A.d_pad ? (mp < d_in ? mp : M) : d_in + mp - A.d_pad;
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int c = n_tile + wn + nb * 32 + l32;
-                float v = lead[mb][nb][e];
-                if constexpr (TERMS == 3) v += rest[mb][nb][e];
-                if (m < M && c < N) pw[(int64_t)m * N + c] = v;
-            }
+    for (; part < A.parts; ++part) {      // zeros for those without rows
+        float* pw = A.part_w + ((int64_t)chunk * A.parts + part) * M * N;
+        for (int q = t; q < TM * TN; q += WG_THREADS) {
+            const int mp = m_tile + q / TN, m = mp < A.d_pad ? (mp < d_in ? mp : M) : d_in + mp - A.d_pad, c = n_tile + q % TN;
+            if (m < M && c < N) pw[(int64_t)m * N + c] = 0.f;
         }
+    }
     if (m_tile == 0) {      // column sums of dz: the threads of a column meet in LDS
         double* red = (double*)wx_lds;
 #pragma unroll
-        for (int w = 0; w < W; ++w) red[t * W + w] = colsum[w];
+        for (int c = 0; c < CPT; ++c) red[t * CPT + c] = colsum[c];
         __syncthreads();
         if (t < TN && n_tile + t < N) {
             double sum = 0.0;
-            for (int j = 0; j < WG_THREADS / ZT; ++j) sum += red[(t / W + j * ZT) * W + t % W];
-            part_b[(int64_t)chunk * N + n_tile + t] = (float)sum;
+            for (int j = 0; j < ZS; ++j) sum += red[(t / CPT + j * ZT) * CPT + t % CPT];
+            A.part_b[(int64_t)chunk * N + n_tile + t] = (float)sum;
         }
+    }
+}
+
+// SRC: element type of a layer's h_src; TERMS = 1: that or bf16 (a model's input layer has the features' type, the others bf16)
+template <int TERMS, int SRC>
+__global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_kernel(WgBatch B) {
+    // A chunk's tiles read the same rows: the workgroups of one XCD (ids congruent mod 8) take consecutive (chunk, tile) pairs
+    const int at = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+    if (at >= B.first[B.n]) return;       // uniform over the workgroup, before any barrier
+    int i = 0;
+    while (at >= B.first[i + 1]) ++i;
+    const WgIn& A = B.l[i];
+    const int unit = at - B.first[i];
+    if constexpr (TERMS == 3) {
+        if (A.tm == 256)
+            weight_grad_tile<256, 128, 3, SRC>(A, unit);
+        else
+            weight_grad_tile<128, 128, 3, SRC>(A, unit);
+    } else if (A.src == SRC) {
+        if (A.tm == 256)
+            weight_grad_tile<256, 256, 1, SRC>(A, unit);
+        else
+            weight_grad_tile<128, 128, 1, SRC>(A, unit);
+    } else if constexpr (SRC != FG_BF16) {
+        if (A.tm == 256)
+            weight_grad_tile<256, 256, 1, FG_BF16>(A, unit);
+        else
+            weight_grad_tile<128, 128, 1, FG_BF16>(A, unit);
     }
 }
 
 // dw[i] = sum over the chunks of part_w[chunk][i] in fp64. A workgroup owns 128 consecutive elements (32 lanes x 4) and
 // splits the chunks over its 8 wavefront halves; db (the last workgroups) likewise.
 constexpr int RED_GROUPS = BW_THREADS / 32;
-__global__ __launch_bounds__(BW_THREADS) void weight_grad_reduce_kernel(const float* __restrict__ part_w,
-                                                                        const float* __restrict__ part_b, int n_chunks,
-                                                                        int64_t mn, int n_cols, int w_blocks,
-                                                                        float* __restrict__ dw, float* __restrict__ db) {
+__global__ __launch_bounds__(BW_THREADS) void weight_grad_reduce_kernel(WgBatch B) {
     __shared__ double red[RED_GROUPS][32][4];
+    int layer = 0;
+    while ((int)blockIdx.x >= B.red_first[layer + 1]) ++layer;
+    const WgIn& A = B.l[layer];
+    const int64_t mn = (int64_t)2 * A.d_in * A.d_out;
+    const int block = (int)blockIdx.x - B.red_first[layer], w_blocks = (int)((mn + 127) / 128);
     const int tx = threadIdx.x & 31, g = threadIdx.x >> 5;
-    const bool is_w = (int)blockIdx.x < w_blocks;
-    const float* part = is_w ? part_w : part_b;
-    const int64_t len = is_w ? mn : n_cols;  // both multiples of 4
-    float* out = is_w ? dw : db;
-    const int64_t i = ((int64_t)(is_w ? blockIdx.x : blockIdx.x - w_blocks) * 32 + tx) * 4;
+    const bool is_w = block < w_blocks;
+    const int n_chunks = is_w ? A.n_chunks * A.parts : A.n_chunks;
+    const float* part = is_w ? A.part_w : A.part_b;
+    const int64_t len = is_w ? mn : A.d_out;  // both multiples of 4
+    float* out = is_w ? A.dw : A.db;
+    const int64_t i = ((int64_t)(is_w ? block : block - w_blocks) * 32 + tx) * 4;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
     if (i < len) {
         for (int c = g; c < n_chunks; c += 4 * RED_GROUPS) {
@@ -1090,9 +1129,22 @@ __global__ __launch_bounds__(BW_THREADS) void weight_grad_reduce_kernel(const fl
 
 // How a contraction is split: tiles of the result, times chunks of rows.
 struct WgPlan {
-    int tm, tn, d_pad, n_chunks, tiles_m, tiles_n;
+    int tm, tn, d_pad, n_chunks, parts, tiles_m, tiles_n;
     size_t part_b, total;
+    void set_bytes(int64_t d_in, int64_t d_out) {
+        part_b = fg_align_up((size_t)n_chunks * parts * 2 * d_in * d_out * 4, 256);
+        total = part_b + fg_align_up((size_t)n_chunks * d_out * 4, 256);
+    }
 };
+// of a step of 32 rows, by tile
+double wg_step_us(bool mixed, bool large) { return mixed ? (large ? 1.7 : 1.15) : (large ? 2.75 : 1.9); }
+// One chunk writes the result itself. Several save it steps but leave partial results, which are
+// written, read and added up by a second launch: few rows of a wide layer are better off as one chunk. Mixed precision, one /
+// several: 300 rows x 2048 x 1024 19 / 29 us, 700 32 / 34, 1024 42 / 37; 300 x 1024 x 1024 18 / 21, 700 31 / 25.
+bool wg_worth_splitting(int64_t max_rows, int64_t d_in, int64_t d_out, int64_t chunks, double step_us) {
+    const double saved = (double)fg_ceil_div(max_rows > 0 ? max_rows : 1, WX_STEP) * (1.0 - 1.0 / (double)chunks) * step_us;
+    return saved >= 5.0 + (double)(2 * chunks + 1) * (double)(2 * d_in * d_out * 4) / 4.5e6;
+}
 WgPlan wg_plan(int64_t max_rows, int64_t d_in, int64_t d_out, bool mixed) {
     WgPlan p;
     // Large tiles halve the reads of the operands; small ones fill the chip with fewer chunks, whose partial results have to be
@@ -1126,48 +1178,117 @@ WgPlan wg_plan(int64_t max_rows, int64_t d_in, int64_t d_out, bool mixed) {
         if (by_rows < by_step) by_rows = by_step;
     }
     if (chunks > by_rows) chunks = by_rows;
-    // One chunk writes the result itself. Several save it steps (the times of one by tile, us) but leave partial results, which are
-    // written, read and added up by a second launch: few rows of a wide layer are better off as one chunk. Mixed precision, one /
-    // several: 300 rows x 2048 x 1024 19 / 29 us, 700 32 / 34, 1024 42 / 37; 300 x 1024 x 1024 18 / 21, 700 31 / 25.
-    const double step_us = mixed ? (large ? 1.7 : 1.15) : (large ? 2.75 : 1.9);
-    const double saved = (double)fg_ceil_div(some, WX_STEP) * (1.0 - 1.0 / (double)chunks) * step_us;
-    if (saved < 5.0 + (double)(2 * chunks + 1) * (double)(2 * d_in * d_out * 4) / 4.5e6) chunks = 1;
-    p.n_chunks = (int)chunks;
-    p.part_b = fg_align_up((size_t)p.n_chunks * 2 * d_in * d_out * 4, 256);
-    p.total = p.part_b + fg_align_up((size_t)p.n_chunks * d_out * 4, 256);
+    p.n_chunks = wg_worth_splitting(max_rows, d_in, d_out, chunks, wg_step_us(mixed, large)) ? (int)chunks : 1;
+    p.parts = 1;
+    p.set_bytes(d_in, d_out);
     return p;
 }
 
-// partial products of every chunk, then their sum; of one chunk the sums themselves
-template <typename Kernel>
-fg_status_t wg_launch(Kernel kernel, int terms, const WgPlan& P, const WgIn& A, float* part_w, float* part_b, float* dw, float* db, hipStream_t st) {
-    const unsigned grid = (unsigned)(fg_ceil_div((int64_t)P.n_chunks * P.tiles_m * P.tiles_n, 8) * 8);
-    const bool direct = P.n_chunks == 1;
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(WG_THREADS), wx_lds_bytes(P.tm, P.tn, terms), st, A, direct ? dw : part_w,
-                       direct && db ? db : part_b);
-    FG_LAUNCH_CHECK("weight_grad_tile_kernel");
-    if (direct) return FG_OK;
-    const int64_t mn = (int64_t)2 * A.d_in * A.d_out;
-    const int w_blocks = (int)fg_ceil_div(mn, 128), b_blocks = (int)fg_ceil_div(A.d_out, 128);
-    hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3((unsigned)(w_blocks + b_blocks)), dim3(BW_THREADS), 0, st, part_w, part_b, P.n_chunks,
-                       mn, A.d_out, w_blocks, dw, db);
+// Chunks of several layers that share a launch: 224 workgroups in all (32 compute units are left to what runs beside, as above), 256 from
+// 150 us on, handed out one chunk at a time to the layer whose workgroups take longest, never more than the layer would have by
+// itself. A chunk that is longer than by itself leaves several partial results, so that an fp32 sum has no more rows than there
+// (relative error of 6 k rows x 512 x 256 8.7e-8 by itself, 1.9e-7 with one sum per chunk of the shared launch, 8.6e-8 so).
+// The three fp32 layers above: 106 us behind each other, 84.5 together; of 24 k x 104 x 88, 4 k x 176 x 88 and 777 x 176 x 48 rows 49 and 28.
+void wg_share(WgPlan* p, const fg_weight_grad_layer_t* y, int n, bool mixed) {
+    int64_t steps[WG_MAX_LAYERS], most[WG_MAX_LAYERS], total = 0;
+    double step_us[WG_MAX_LAYERS], work = 0.0;
+    for (int i = 0; i < n; ++i) {
+        steps[i] = fg_ceil_div(y[i].max_rows > 0 ? y[i].max_rows : 1, WX_STEP);
+        step_us[i] = wg_step_us(mixed, p[i].tm == 256);
+        most[i] = p[i].n_chunks;
+        p[i].n_chunks = 1;
+        total += (int64_t)p[i].tiles_m * p[i].tiles_n;
+        work += (double)(steps[i] * p[i].tiles_m * p[i].tiles_n) * step_us[i];
+    }
+    const int64_t target = work < 224.0 * 150.0 ? 224 : 256;
+    // a workgroup's steps and the partial results it leaves on the way (3 or 5 us each)
+    auto time_of = [&](int i) {
+        return (double)fg_ceil_div(steps[i], p[i].n_chunks) * step_us[i] + (double)fg_ceil_div(most[i], p[i].n_chunks) * (p[i].tm == 256 ? 5.0 : 3.0);
+    };
+    for (;;) {
+        int longest = 0;
+        for (int i = 1; i < n; ++i)
+            if (time_of(i) > time_of(longest)) longest = i;
+        const int64_t tiles = (int64_t)p[longest].tiles_m * p[longest].tiles_n;
+        if (p[longest].n_chunks >= most[longest] || total + tiles > target) break;
+        ++p[longest].n_chunks;
+        total += tiles;
+    }
+    for (int i = 0; i < n; ++i) {
+        p[i].parts = (int)fg_ceil_div(most[i], p[i].n_chunks);
+        p[i].set_bytes(y[i].d_in, y[i].d_out);
+    }
+}
+
+// What the partial results of a layer take at most there, for up to max_rows rows: fewer than twice those of its own call.
+size_t wg_share_bytes(const fg_weight_grad_layer_t& y, bool mixed) {
+    WgPlan p = wg_plan(y.max_rows, y.d_in, y.d_out, mixed);
+    p.parts = p.n_chunks == 1 ? 1 : 2;
+    p.set_bytes(y.d_in, y.d_out);
+    return p.total;
+}
+
+
+// Partial products of every chunk of every layer, then their sums; of one chunk the sums themselves. The layers' workspaces lie
+// behind each other in ws.
+fg_status_t wg_launch(WgIn* in, const WgPlan* p, int n, bool mixed, char* ws, hipStream_t st) {
+    WgBatch B{};
+    B.n = n;
+    size_t lds = 0;
+    int order[WG_MAX_LAYERS];
+    double time[WG_MAX_LAYERS];
+    for (int i = 0; i < n; ++i) {
+        WgIn& A = in[i];
+        A.part_w = (float*)ws;
+        A.part_b = (float*)(ws + p[i].part_b);
+        ws += p[i].total;
+        A.d_pad = p[i].d_pad;
+        A.n_chunks = p[i].n_chunks;
+        A.parts = p[i].parts;
+        A.tiles_m = p[i].tiles_m;
+        A.tiles_n = p[i].tiles_n;
+        A.tm = p[i].tm;
+        if (p[i].n_chunks * p[i].parts == 1) {
+            A.part_w = A.dw;
+            if (A.db) A.part_b = A.db;
+        }
+        // without rows (or without anything they could index) every chunk is empty and the partials are zeros
+        time[i] = (double)(A.max_rows / p[i].n_chunks) * wg_step_us(mixed, p[i].tm == 256);
+        if (A.n <= 0 || A.n_src <= 0) A.max_rows = 0;
+        const size_t need = wx_lds_bytes(p[i].tm, p[i].tn, mixed ? 1 : 3);
+        lds = need > lds ? need : lds;
+        int at = i;      // the longest first
+        for (; at > 0 && time[order[at - 1]] < time[i]; --at) order[at] = order[at - 1];
+        order[at] = i;
+    }
+    int src = FG_BF16;
+    for (int q = 0; q < n; ++q) {
+        const WgIn& A = B.l[q] = in[order[q]];
+        if (A.src != FG_BF16) src = A.src;
+        B.first[q + 1] = B.first[q] + A.n_chunks * A.tiles_m * A.tiles_n;
+        B.red_first[q + 1] = B.red_first[q] + (A.n_chunks * A.parts > 1 ? (int)(fg_ceil_div((int64_t)2 * A.d_in * A.d_out, 128) + fg_ceil_div(A.d_out, 128)) : 0);
+    }
+    const dim3 grid((unsigned)(fg_ceil_div(B.first[n], 8) * 8));
+    if (!mixed)
+        hipLaunchKernelGGL((weight_grad_kernel<3, FG_F32>), grid, dim3(WG_THREADS), lds, st, B);
+    else if (src == FG_F32)
+        hipLaunchKernelGGL((weight_grad_kernel<1, FG_F32>), grid, dim3(WG_THREADS), lds, st, B);
+    else if (src == FG_F16)
+        hipLaunchKernelGGL((weight_grad_kernel<1, FG_F16>), grid, dim3(WG_THREADS), lds, st, B);
+    else
+        hipLaunchKernelGGL((weight_grad_kernel<1, FG_BF16>), grid, dim3(WG_THREADS), lds, st, B);
+    FG_LAUNCH_CHECK("weight_grad_kernel");
+    if (B.red_first[n] == 0) return FG_OK;
+    hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3((unsigned)B.red_first[n]), dim3(BW_THREADS), 0, st, B);
     FG_LAUNCH_CHECK("weight_grad_reduce_kernel");
     return FG_OK;
 }
 
 }  // namespace
 
-extern "C" size_t fg_layer_backward_weights_workspace_bytes(int64_t max_rows, int32_t d_in, int32_t d_out) {
-    if (max_rows < 0 || d_in <= 0 || d_out <= 0) return 0;
-    return wg_plan(max_rows, d_in, d_out, false).total;
-}
-
-extern "C" fg_status_t fg_layer_backward_weights(const float* h_src_dev, int32_t n_src, int64_t src_stride, const float* agg_dev,
-                                                 int64_t agg_stride, const float* dh_dev, int64_t dh_stride, const float* h_dev,
-                                                 int64_t h_stride, int32_t n, const int32_t* rows_dev, const int64_t* n_rows_dev,
-                                                 int64_t max_rows, int32_t d_in, int32_t d_out, float* dw_dev, float* db_dev,
-                                                 void* ws_dev, size_t ws_bytes, void* stream) {
-    const char* who = "fg_layer_backward_weights";
+static fg_status_t wg_check_f32(const char* who, const float* h_src_dev, int32_t n_src, int64_t src_stride, const float* agg_dev, int64_t agg_stride,
+                                const float* dh_dev, int64_t dh_stride, const float* h_dev, int64_t h_stride, int32_t n, int64_t max_rows, int32_t d_in,
+                                int32_t d_out, const float* dw_dev, const float* db_dev) {
     if (n < 0 || n_src < 0 || max_rows < 0 || d_in <= 0 || d_out <= 0)
         FG_FAIL(FG_ERR_INVALID_ARG, "%s: bad size (n %d, n_src %d, max_rows %lld, d_in %d, d_out %d)", who, n, n_src, (long long)max_rows, d_in, d_out);
     if (!dw_dev) FG_FAIL(FG_ERR_INVALID_ARG, "%s: dw_dev is NULL", who);
@@ -1180,32 +1301,12 @@ extern "C" fg_status_t fg_layer_backward_weights(const float* h_src_dev, int32_t
     if (((uintptr_t)h_src_dev | (uintptr_t)agg_dev | (uintptr_t)dh_dev | (uintptr_t)h_dev | (uintptr_t)src_stride | (uintptr_t)agg_stride |
          (uintptr_t)dh_stride | (uintptr_t)h_stride) & 15)
         FG_FAIL(FG_ERR_INVALID_ARG, "%s: h_src, agg, dh, h and their strides must be 16-byte aligned", who);
-    const WgPlan P = wg_plan(max_rows, d_in, d_out, false);
-    if (!ws_dev || ws_bytes < P.total) FG_FAIL(FG_ERR_SHAPE, "%s: workspace of %zu bytes given, %zu needed", who, ws_bytes, P.total);
-    if ((uintptr_t)ws_dev & 15) FG_FAIL(FG_ERR_INVALID_ARG, "%s: the workspace must be 16-byte aligned", who);
-    fg_clear_error();
-    hipStream_t st = (hipStream_t)stream;
-    float* part_w = (float*)ws_dev;
-    float* part_b = (float*)((char*)ws_dev + P.part_b);
-    // without rows (or without anything they could index) every chunk is empty and the partials are zeros
-    const int64_t rows_bound = (n > 0 && n_src > 0) ? max_rows : 0;
-    const WgIn A = {(const char*)h_src_dev, (const char*)agg_dev, (const char*)dh_dev, (const char*)h_dev, src_stride, agg_stride, dh_stride,
-                    h_stride, rows_bound, rows_dev, n_rows_dev, n_src, n, d_in, P.d_pad, d_out, P.n_chunks, P.tiles_m, P.tiles_n};
-    if (P.tm == 256) return wg_launch(weight_grad_tile_kernel<256, 128, 3, FG_F32>, 3, P, A, part_w, part_b, dw_dev, db_dev, st);
-    return wg_launch(weight_grad_tile_kernel<128, 128, 3, FG_F32>, 3, P, A, part_w, part_b, dw_dev, db_dev, st);
+    return FG_OK;
 }
 
-extern "C" size_t fg_layer_backward_weights_bf16_workspace_bytes(int64_t max_rows, int32_t d_in, int32_t d_out) {
-    if (max_rows < 0 || d_in <= 0 || d_out <= 0) return 0;
-    return wg_plan(max_rows, d_in, d_out, true).total;
-}
-
-extern "C" fg_status_t fg_layer_backward_weights_bf16(const void* h_src_dev, int32_t n_src, int64_t src_stride, fg_dtype_t src_dtype,
-                                                      const void* agg_dev, int64_t agg_stride, const float* dh_dev, int64_t dh_stride,
-                                                      const void* h_dev, int64_t h_stride, int32_t n, const int32_t* rows_dev,
-                                                      const int64_t* n_rows_dev, int64_t max_rows, int32_t d_in, int32_t d_out,
-                                                      float* dw_dev, float* db_dev, void* ws_dev, size_t ws_bytes, void* stream) {
-    const char* who = "fg_layer_backward_weights_bf16";
+static fg_status_t wg_check_bf16(const char* who, const void* h_src_dev, int32_t n_src, int64_t src_stride, fg_dtype_t src_dtype, const void* agg_dev,
+                                 int64_t agg_stride, const float* dh_dev, int64_t dh_stride, const void* h_dev, int64_t h_stride, int32_t n,
+                                 int64_t max_rows, int32_t d_in, int32_t d_out, const float* dw_dev, const float* db_dev) {
     if (n < 0 || n_src < 0 || max_rows < 0 || d_in <= 0 || d_out <= 0)
         FG_FAIL(FG_ERR_INVALID_ARG, "%s: bad size (n %d, n_src %d, max_rows %lld, d_in %d, d_out %d)", who, n, n_src, (long long)max_rows, d_in, d_out);
     if (!dw_dev) FG_FAIL(FG_ERR_INVALID_ARG, "%s: dw_dev is NULL", who);
@@ -1219,21 +1320,100 @@ extern "C" fg_status_t fg_layer_backward_weights_bf16(const void* h_src_dev, int
     if (((uintptr_t)h_src_dev | (uintptr_t)agg_dev | (uintptr_t)dh_dev | (uintptr_t)h_dev | (uintptr_t)src_stride | (uintptr_t)agg_stride |
          (uintptr_t)dh_stride | (uintptr_t)h_stride) & 3)
         FG_FAIL(FG_ERR_INVALID_ARG, "%s: h_src, agg, dh, h and their strides must be 4-byte aligned", who);
+    return FG_OK;
+}
+
+extern "C" size_t fg_layer_backward_weights_workspace_bytes(int64_t max_rows, int32_t d_in, int32_t d_out) {
+    if (max_rows < 0 || d_in <= 0 || d_out <= 0) return 0;
+    return wg_plan(max_rows, d_in, d_out, false).total;
+}
+
+extern "C" fg_status_t fg_layer_backward_weights(const float* h_src_dev, int32_t n_src, int64_t src_stride, const float* agg_dev,
+                                                 int64_t agg_stride, const float* dh_dev, int64_t dh_stride, const float* h_dev,
+                                                 int64_t h_stride, int32_t n, const int32_t* rows_dev, const int64_t* n_rows_dev,
+                                                 int64_t max_rows, int32_t d_in, int32_t d_out, float* dw_dev, float* db_dev,
+                                                 void* ws_dev, size_t ws_bytes, void* stream) {
+    const char* who = "fg_layer_backward_weights";
+    const fg_status_t rc = wg_check_f32(who, h_src_dev, n_src, src_stride, agg_dev, agg_stride, dh_dev, dh_stride, h_dev, h_stride, n, max_rows, d_in, d_out,
+                                        dw_dev, db_dev);
+    if (rc != FG_OK) return rc;
+    const WgPlan P = wg_plan(max_rows, d_in, d_out, false);
+    if (!ws_dev || ws_bytes < P.total) FG_FAIL(FG_ERR_SHAPE, "%s: workspace of %zu bytes given, %zu needed", who, ws_bytes, P.total);
+    if ((uintptr_t)ws_dev & 15) FG_FAIL(FG_ERR_INVALID_ARG, "%s: the workspace must be 16-byte aligned", who);
+    fg_clear_error();
+    WgIn A = {(const char*)h_src_dev, (const char*)agg_dev, (const char*)dh_dev, (const char*)h_dev, src_stride, agg_stride, dh_stride,
+              h_stride, max_rows, rows_dev, n_rows_dev, n_src, n, d_in, 0, d_out, 0, 0, 0, 0, FG_F32, 0, nullptr, nullptr, dw_dev, db_dev};
+    return wg_launch(&A, &P, 1, false, (char*)ws_dev, (hipStream_t)stream);
+}
+
+extern "C" size_t fg_layer_backward_weights_bf16_workspace_bytes(int64_t max_rows, int32_t d_in, int32_t d_out) {
+    if (max_rows < 0 || d_in <= 0 || d_out <= 0) return 0;
+    return wg_plan(max_rows, d_in, d_out, true).total;
+}
+
+extern "C" fg_status_t fg_layer_backward_weights_bf16(const void* h_src_dev, int32_t n_src, int64_t src_stride, fg_dtype_t src_dtype,
+                                                      const void* agg_dev, int64_t agg_stride, const float* dh_dev, int64_t dh_stride,
+                                                      const void* h_dev, int64_t h_stride, int32_t n, const int32_t* rows_dev,
+                                                      const int64_t* n_rows_dev, int64_t max_rows, int32_t d_in, int32_t d_out,
+                                                      float* dw_dev, float* db_dev, void* ws_dev, size_t ws_bytes, void* stream) {
+    const char* who = "fg_layer_backward_weights_bf16";
+    const fg_status_t rc = wg_check_bf16(who, h_src_dev, n_src, src_stride, src_dtype, agg_dev, agg_stride, dh_dev, dh_stride, h_dev, h_stride, n, max_rows,
+                                         d_in, d_out, dw_dev, db_dev);
+    if (rc != FG_OK) return rc;
     const WgPlan P = wg_plan(max_rows, d_in, d_out, true);
     if (!ws_dev || ws_bytes < P.total) FG_FAIL(FG_ERR_SHAPE, "%s: workspace of %zu bytes given, %zu needed", who, ws_bytes, P.total);
     if ((uintptr_t)ws_dev & 15) FG_FAIL(FG_ERR_INVALID_ARG, "%s: the workspace must be 16-byte aligned", who);
     fg_clear_error();
-    hipStream_t st = (hipStream_t)stream;
-    float* part_w = (float*)ws_dev;
-    float* part_b = (float*)((char*)ws_dev + P.part_b);
-    // without rows (or without anything they could index) every chunk is empty and the partials are zeros
-    const int64_t rows_bound = (n > 0 && n_src > 0) ? max_rows : 0;
-    const WgIn A = {(const char*)h_src_dev, (const char*)agg_dev, (const char*)dh_dev, (const char*)h_dev, src_stride, agg_stride, dh_stride,
-                    h_stride, rows_bound, rows_dev, n_rows_dev, n_src, n, d_in, P.d_pad, d_out, P.n_chunks, P.tiles_m, P.tiles_n};
-#define FG_WG(SRC)                                                                                                                        \
-    (P.tm == 256 ? wg_launch(weight_grad_tile_kernel<256, 256, 1, SRC>, 1, P, A, part_w, part_b, dw_dev, db_dev, st)                      \
-                 : wg_launch(weight_grad_tile_kernel<128, 128, 1, SRC>, 1, P, A, part_w, part_b, dw_dev, db_dev, st))
-    if (src_dtype == FG_F32) return FG_WG(FG_F32);
-    return src_dtype == FG_F16 ? FG_WG(FG_F16) : FG_WG(FG_BF16);
-#undef FG_WG
+    WgIn A = {(const char*)h_src_dev, (const char*)agg_dev, (const char*)dh_dev, (const char*)h_dev, src_stride, agg_stride, dh_stride,
+              h_stride, max_rows, rows_dev, n_rows_dev, n_src, n, d_in, 0, d_out, 0, 0, 0, 0, (int)src_dtype, 0, nullptr, nullptr, dw_dev, db_dev};
+    return wg_launch(&A, &P, 1, true, (char*)ws_dev, (hipStream_t)stream);
+}
+
+static fg_status_t wg_check(const char* who, const fg_weight_grad_layer_t& y, bool mixed) {
+    if (mixed)
+        return wg_check_bf16(who, y.h_src_dev, y.n_src, y.src_stride, y.src_dtype, y.agg_dev, y.agg_stride, y.dh_dev, y.dh_stride, y.h_dev, y.h_stride,
+                             y.n, y.max_rows, y.d_in, y.d_out, y.dw_dev, y.db_dev);
+    if (y.src_dtype != FG_F32) FG_FAIL(FG_ERR_DTYPE, "%s: h_src must be fp32", who);
+    return wg_check_f32(who, (const float*)y.h_src_dev, y.n_src, y.src_stride, (const float*)y.agg_dev, y.agg_stride, y.dh_dev, y.dh_stride,
+                        (const float*)y.h_dev, y.h_stride, y.n, y.max_rows, y.d_in, y.d_out, y.dw_dev, y.db_dev);
+}
+
+extern "C" size_t fg_backward_weights_all_workspace_bytes(fg_dtype_t compute_dtype, int32_t n_layers, const fg_weight_grad_layer_t* layers) {
+    if ((compute_dtype != FG_F32 && compute_dtype != FG_BF16) || n_layers < 1 || n_layers > WG_MAX_LAYERS || !layers) return 0;
+    size_t total = 0;
+    for (int i = 0; i < n_layers; ++i) {
+        if (layers[i].max_rows < 0 || layers[i].d_in <= 0 || layers[i].d_out <= 0) return 0;
+        total += wg_share_bytes(layers[i], compute_dtype == FG_BF16);
+    }
+    return total;
+}
+
+extern "C" fg_status_t fg_backward_weights_all(fg_dtype_t compute_dtype, int32_t n_layers, const fg_weight_grad_layer_t* layers, void* ws_dev,
+                                               size_t ws_bytes, void* stream) {
+    const char* who = "fg_backward_weights_all";
+    if (compute_dtype != FG_F32 && compute_dtype != FG_BF16) FG_FAIL(FG_ERR_DTYPE, "%s: compute_dtype must be F32 or BF16", who);
+    if (n_layers < 1 || n_layers > WG_MAX_LAYERS || !layers)
+        FG_FAIL(FG_ERR_INVALID_ARG, "%s: n_layers = %d must be in 1..%d and layers non-NULL", who, n_layers, WG_MAX_LAYERS);
+    const bool mixed = compute_dtype == FG_BF16;
+    WgIn in[WG_MAX_LAYERS];
+    WgPlan p[WG_MAX_LAYERS];
+    int src = FG_BF16;      // the one type besides it
+    for (int i = 0; i < n_layers; ++i) {
+        const fg_weight_grad_layer_t& y = layers[i];
+        fg_status_t rc = wg_check(who, y, mixed);
+        if (rc != FG_OK) return rc;
+        if (mixed && y.src_dtype != FG_BF16 && src != FG_BF16 && y.src_dtype != src)
+            FG_FAIL(FG_ERR_DTYPE, "%s: the layers' h_src have more than one type besides bf16", who);
+        if (y.src_dtype != FG_BF16) src = (int)y.src_dtype;
+        p[i] = wg_plan(y.max_rows, y.d_in, y.d_out, mixed);
+        in[i] = {(const char*)y.h_src_dev, (const char*)y.agg_dev, (const char*)y.dh_dev, (const char*)y.h_dev, y.src_stride, y.agg_stride, y.dh_stride,
+                 y.h_stride, y.max_rows, y.rows_dev, y.n_rows_dev, y.n_src, y.n, y.d_in, 0, y.d_out, 0, 0, 0, 0, (int)y.src_dtype, 0, nullptr, nullptr,
+                 y.dw_dev, y.db_dev};
+    }
+    const size_t need = fg_backward_weights_all_workspace_bytes(compute_dtype, n_layers, layers);
+    if (!ws_dev || ws_bytes < need) FG_FAIL(FG_ERR_SHAPE, "%s: workspace of %zu bytes given, %zu needed", who, ws_bytes, need);
+    if ((uintptr_t)ws_dev & 15) FG_FAIL(FG_ERR_INVALID_ARG, "%s: the workspace must be 16-byte aligned", who);
+    fg_clear_error();
+    wg_share(p, layers, n_layers, mixed);
+    return wg_launch(in, p, n_layers, mixed, (char*)ws_dev, (hipStream_t)stream);
 }

@@ -200,12 +200,11 @@ class DeviceSampler:
 
 
 def weight_grad_workspace_bytes(kind, n, d_in, d_out):
-    """Workspace of a layer's weight gradients (kind "sage", "gcn" or "bf16") for at most n rows. A GCN layer hands its one input row
-    over as two halves: its contraction is that of a layer of half the width, whose split over the rows may need more
-    partial results than the full width's."""
-    if kind == "bf16":
-        return B.fg_layer_backward_weights_bf16_workspace_bytes(n, d_in, d_out)
-    return B.fg_layer_backward_weights_workspace_bytes(n, d_in // 2 if kind == "gcn" else d_in, d_out)
+    """Workspace of a layer's share of the weight gradients (kind "sage", "gcn" or "bf16") for at most n rows. A GCN layer hands its one
+    input row over as two halves: its contraction is that of a layer of half the width, whose split over the rows may need
+    more partial results than the full width's."""
+    layer = B.weight_grad_layers([dict(max_rows=n, d_in=d_in // 2 if kind == "gcn" else d_in, d_out=d_out)])
+    return B.fg_backward_weights_all_workspace_bytes(B.FG_BF16 if kind == "bf16" else B.FG_F32, layer)
 
 
 def _no_tick(name, stream=None):
@@ -349,8 +348,8 @@ class HotPath:
                 w_rows = [None] + [(1 if model == "gcn" else 2) * dims[l - 1] for l in range(1, L + 1)]
                 self.dW = [None] + [torch.zeros((w_rows[l], dims[l]), dtype=torch.float32, device=dev) for l in range(1, L + 1)]
                 self.db = [None] + [torch.zeros(dims[l], dtype=torch.float32, device=dev) for l in range(1, L + 1)]
-                self.ws_wg_bytes = max(weight_grad_workspace_bytes(self.bw_kind, n[l], dims[l - 1], dims[l]) for l in range(1, L + 1))
-                self.ws_wg = torch.zeros(self.ws_wg_bytes + 256, dtype=torch.uint8, device=dev)
+                self.ws_wg_bytes = sum(weight_grad_workspace_bytes(self.bw_kind, n[l], dims[l - 1], dims[l]) for l in range(1, L + 1))
+                self.ws_wg = torch.empty(self.ws_wg_bytes + 256, dtype=torch.uint8, device=dev)
         self.cache = None
         self.feature_side = False
         if L > 1:
@@ -399,6 +398,24 @@ class HotPath:
                                      saving_dev=self.saving[l] if self.admit_budget else None,
                                      max_admit=int(self.admit_budget.get(l, 0)) if self.admit_budget else 0, n_dev=bt.n_dev[l])
                                 for l in range(1, self.L)])
+
+    def _weight_grads(self, bt, st, first, last):
+        """The weight gradients of layers first .. last, from the means, embeddings and output gradients this iteration left."""
+        esz, L, gcn = B.DTYPE_SIZE, self.L, self.bw_kind == "gcn"
+        for lo in range(first, last + 1, B.FG_WEIGHT_GRAD_MAX_LAYERS):
+            layers = (B.WeightGradLayer * min(last + 1 - lo, B.FG_WEIGHT_GRAD_MAX_LAYERS))()
+            for l, y in enumerate(layers, lo):
+                # (a GCN layer's input rows are the propagated rows: by-position half ‖ list-order half)
+                src, n_src, width = (self.MEANPOS_l[l], bt.n[l], self.dims[l - 1] // 2) if gcn else (self.H[l - 1], bt.n[l - 1], self.dims[l - 1])
+                code = B.FG_F32 if gcn else self.h_code[l - 1]
+                y.h_src_dev, y.src_stride, y.src_dtype, y.n_src = src.data_ptr(), width * esz[code], code, n_src
+                y.agg_dev, y.agg_stride = self.AGG_l[l].data_ptr(), width * esz[self.agg_code]
+                y.dh_dev, y.dh_stride = self.dH[l].data_ptr(), self.dims[l] * 4
+                if l < L:
+                    y.h_dev, y.h_stride = self.H[l].data_ptr(), self.dims[l] * esz[self.h_code[l]]
+                y.rows_dev, y.n_rows_dev, y.max_rows, y.n = self.normal_pos[l].data_ptr(), self._cnt(l, 2), bt.n[l], bt.n[l]
+                y.dw_dev, y.db_dev, y.d_in, y.d_out = self.dW[l].data_ptr(), self.db[l].data_ptr(), width, self.dims[l]
+            B.fg_backward_weights_all(self.comp_code, layers, self.ws_wg, self.ws_wg_bytes, st)
 
     def _ws_upd(self, it):
         return self.ws_upd.data_ptr() + (it % 2) * self.ws_upd_stride
@@ -654,56 +671,36 @@ class HotPath:
         # ---- loss and backward pass down to layer 1: the gradient norms the update admits and checks out by
         gnorm = bt.gnorm
         if self.backward:
-            def weight_grads(l, stream):
-                act = self.H[l] if l < L else None
-                tail = (bt.n[l], self.normal_pos[l], self._cnt(l, 2), bt.n[l])
-                if self.bw_kind == "gcn":    # the layer's input rows are the propagated rows: by-position half ‖ list-order half
-                    half = self.dims[l - 1] // 2
-                    B.fg_layer_backward_weights(self.MEANPOS_l[l], bt.n[l], half * 4, self.AGG_l[l], half * 4, self.dH[l],
-                                                self.dims[l] * 4, act, self.dims[l] * 4, *tail, half, self.dims[l],
-                                                self.dW[l], self.db[l], self.ws_wg, self.ws_wg_bytes, stream)
-                elif self.bw_kind == "bf16":
-                    B.fg_layer_backward_weights_bf16(self.H[l - 1], bt.n[l - 1], self.dims[l - 1] * esz[self.h_code[l - 1]],
-                                                     self.h_code[l - 1], self.AGG_l[l], self.dims[l - 1] * 2, self.dH[l],
-                                                     self.dims[l] * 4, act, self.dims[l] * 2, *tail, self.dims[l - 1],
-                                                     self.dims[l], self.dW[l], self.db[l], self.ws_wg, self.ws_wg_bytes, stream)
-                else:
-                    B.fg_layer_backward_weights(self.H[l - 1], bt.n[l - 1], self.dims[l - 1] * 4, self.AGG_l[l],
-                                                self.dims[l - 1] * 4, self.dH[l], self.dims[l] * 4, act, self.dims[l] * 4,
-                                                *tail, self.dims[l - 1], self.dims[l], self.dW[l], self.db[l], self.ws_wg,
-                                                self.ws_wg_bytes, stream)
-
-            # The weight gradients of a layer need that layer's output gradient and nothing later: with a second stream they
-            # run there, each as soon as its dH exists, beside the rest of the backward chain and the cache update.
+            # The weight gradients of all layers are one call behind the last layer's gradient (two launches that fill the chip
+            # by themselves); with a second stream it runs there, beside the cache update. Wide mixed layers, whose partial results are
+            # what a chunk costs, gain nothing from sharing a launch: the upper layers' go ahead there, beside the rest of the backward
+            # chain (16 k x 1024 output values 299 us against 332 in one call; 10 k x 512 224 both ways; in fp32 one call is faster, large
+            # SAGE iteration 400 against 406).
             wg_beside = self.weight_grads and self.overlap_update and timer is None
+            ahead = wg_beside and L > 1 and self.bw_kind == "bf16" and bt.n[1] * self.dims[1] >= 1 << 23
 
-            # (both streams are named in every call: making the second one torch's current stream and asking for the current
-            # one costs about 20 us of host time per layer, more than the launches it is for)
-            side_st = self.side.cuda_stream if wg_beside else None
-
-            def weight_grads_beside(l):
-                self.ev_bw[l].record(main)
-                self.side.wait_event(self.ev_bw[l])
-                weight_grads(l, side_st)
+            def weight_grads_beside(first, last):
+                self.ev_bw[first].record(main)
+                self.side.wait_event(self.ev_bw[first])
+                self._weight_grads(bt, self.side.cuda_stream, first, last)      # (named in the call: making it torch's current stream costs the host 20 us)
 
             tick("loss_grad")
             B.fg_softmax_xent_grad(self.H[L], self.dims[L] * 4, bt.labels, bt.n[L], self.dims[L], self.dH[L], self.dims[L] * 4, st)
-            if wg_beside:
-                weight_grads_beside(L)
             for l in range(L, 1, -1):
+                if l == 2 and ahead:
+                    weight_grads_beside(2, L)
                 tick(f"layer_backward[{l}]")
                 B.fg_layer_backward(self.dH[l], self.dims[l] * 4, self.H[l] if l < L else None, self.dims[l] * esz[self.h_code[l]],
                                     bt.n[l], self.normal_pos[l], self._cnt(l, 2), bt.n[l], self.live[l] if l < L else None,
                                     self.hit[l], bt.start[l], bt.end[l], bt.t_start[l], bt.t_end[l], bt.t_row[l], bt.nnz[l],
                                     bt.n[l - 1], self.dims[l - 1], self.dims[l], self.W[l], self.dH[l - 1], self.dims[l - 1] * 4,
                                     self.gnorm[l - 1], self.ws_bw, self.ws_bw_bytes, st, kind=self.bw_kind)   # with the row norms of dH[l-1]
-                if wg_beside:
-                    weight_grads_beside(l - 1)
             gnorm = self.gnorm
-            if self.weight_grads and not wg_beside:
-                for l in range(L, 0, -1):
-                    tick(f"weight_grads[{l}]")
-                    weight_grads(l, st)
+            if wg_beside:
+                weight_grads_beside(1, 1 if ahead else L)
+            elif self.weight_grads:
+                tick("weight_grads")
+                self._weight_grads(bt, st, 1, L)
         # ---- update of the caches
         if held["due"]:           # no timed call came after layer 1
             held["due"] = False

@@ -142,6 +142,11 @@ def test_argument_validation_needs_no_gpu(B):
     assert B.fg_layer_backward_workspace_bytes(10, 10, 128, 256, kind="gcn") < B.fg_layer_backward_workspace_bytes(10, 10, 128, 256)
     assert B.fg_layer_backward_workspace_bytes(10, 10, 128, 256, kind="bf16") < B.fg_layer_backward_workspace_bytes(10, 10, 128, 256)
     assert B.fg_layer_backward_workspace_bytes(10, 10, 128, 256, kind="bf16") >= 10 * 2 * 128 * 4 + 10 * 256 * 2
+    wga = lambda dt=B.FG_F32, n=1, wsb=1 << 30, **k: B.fg_backward_weights_all(dt, B.weight_grad_layers([{**dict(
+        h_src_dev=4096, src_stride=512, agg_dev=4096, agg_stride=512, dh_dev=4096, dh_stride=1024, max_rows=10, dw_dev=4096, src_dtype=B.FG_F32,
+        n_src=10, n=10, d_in=128, d_out=256), **k}] * n), 4096, wsb)
+    assert code(wga, dw_dev=None) == B.FG_ERR_INVALID_ARG and code(wga, n=9) == B.FG_ERR_INVALID_ARG and code(wga, d_in=126) == B.FG_ERR_SHAPE
+    assert code(wga, wsb=64) == B.FG_ERR_SHAPE and code(wga, src_dtype=B.FG_F16) == B.FG_ERR_DTYPE and code(wga, dt=B.FG_F16) == B.FG_ERR_DTYPE
     wg16 = lambda **k: B.fg_layer_backward_weights_bf16(**{**dict(h_src=4096, n_src=10, src_stride=256, src_dtype=B.FG_BF16, agg=4096,
                                                                    agg_stride=256, dh=4096, dh_stride=1024, h=None, h_stride=0, n=10,
                                                                    rows=4096, n_rows=None, max_rows=10, d_in=128, d_out=256, dw=4096,

@@ -1211,6 +1211,44 @@ def test_layer_backward_weights_match_oracle(env, d_in, d_out, n, n_rows, relu, 
     assert e <= REL_TOL_F32 and e_b <= REL_TOL_F32, f"rel err dW {e:.3e}, db {e_b:.3e}"
 
 
+@pytest.mark.parametrize("kind,layers", [
+    ("f32", [(128, 256, 30000, 29001, True), (256, 256, 3000, 2999, True), (256, 64, 300, 250, False)]),       # both tiles, many chunks and few
+    ("f32", [(24, 72, 130, 77, True), (72, 8, 40, 0, False)]), ("f32", [(8, 8, 9, 1, False)]),                # one chunk each; an empty layer
+    ("bf16", [("f16", 384, 512, 9000, 8000, True), ("bf16", 512, 512, 1024, 1024, True), ("bf16", 512, 64, 100, 90, False)]),
+    ("bf16", [("f32", 64, 128, 700, 650, True), ("bf16", 128, 264, 300, 300, False)]), ("bf16", [("bf16", 16, 16, 40, 33, False)] * 8)])
+def test_weight_gradients_of_all_layers_in_one_call(env, kind, layers):
+    """fg_backward_weights_all against 64-bit sums, layer by layer, with the tolerance of the call for one layer, in the smallest
+    workspace that is accepted, filled with NaN patterns: every partial result that is read must have been written."""
+    torch, B = env
+    r = np.random.default_rng(len(layers))
+    bf = kind == "bf16"
+    tdt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
+    code = {"f32": B.FG_F32, "f16": B.FG_F16, "bf16": B.FG_BF16}
+    act, specs, keep, want = tdt["bf16" if bf else "f32"], [], [], []
+    for y in layers:
+        src, (d_in, d_out, n, n_rows, relu) = (y[0], y[1:]) if bf else ("f32", y)
+        rows = torch.from_numpy(np.sort(r.permutation(n)[:n_rows])).cuda()
+        h_src, agg = (torch.randn(m, d_in, device="cuda").to(t) for m, t in ((n + 7, tdt[src]), (n, act)))
+        dh, h = torch.randn(n, d_out, device="cuda"), torch.randn(n, d_out, device="cuda").relu().to(act)
+        lst, cnt = torch.zeros(n, dtype=torch.int32, device="cuda"), torch.tensor([n_rows], dtype=torch.int64, device="cuda")
+        lst[:n_rows] = rows.int()
+        dw, db = torch.full((2 * d_in, d_out), 3.0, device="cuda"), torch.full((d_out,), 3.0, device="cuda")
+        x = torch.cat([h_src[rows].to(act), agg[:n_rows]], 1).double()
+        dz = dh[rows] * (h[rows].float() > 0) if relu else dh[rows]
+        want.append((x.t() @ dz.to(act).double(), dz.double().sum(0), dw, db))
+        keep.append((h_src, agg, dh, h, lst, cnt))
+        specs.append(dict(h_src_dev=h_src, src_stride=d_in * h_src.element_size(), agg_dev=agg, agg_stride=d_in * agg.element_size(), dh_dev=dh,
+                          dh_stride=d_out * 4, h_dev=h if relu else None, h_stride=d_out * h.element_size(), rows_dev=lst, n_rows_dev=cnt, max_rows=n,
+                          dw_dev=dw, db_dev=db, src_dtype=code[src], n_src=n + 7, n=n, d_in=d_in, d_out=d_out))
+    arr = B.weight_grad_layers(specs)
+    wsb = B.fg_backward_weights_all_workspace_bytes(B.FG_BF16 if bf else B.FG_F32, arr)
+    ws = torch.full((wsb,), 255, dtype=torch.uint8, device="cuda")
+    B.fg_backward_weights_all(B.FG_BF16 if bf else B.FG_F32, arr, ws, wsb)
+    for i, (w, b, dw, db) in enumerate(want):
+        e, e_b = T.rel_err_rows(dw.cpu().numpy(), w.cpu().numpy()), T.rel_err_rows(db.cpu().numpy()[None], b.cpu().numpy()[None])
+        assert e <= REL_TOL_F32 and e_b <= REL_TOL_F32, f"layer {i}: rel err dW {e:.3e}, db {e_b:.3e}"
+
+
 def _random_pruned_block(r, n, n_src, max_deg):
     """A random block with its transpose, flags, the computed rows and the row ends after pruning."""
     from oracle.sampler_oracle import transpose_block
