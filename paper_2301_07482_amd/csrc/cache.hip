@@ -11,8 +11,8 @@
 // touches the previous owner's map entry, a check-out only writes the node's own map entry, and the slots
 // handed out in one update are distinct. The result is therefore the same as the sequential procedure.
 //
-// Update = 5 launches for any number of layers (a workgroup finds its layer from its index), or 2 where all of them are
-// small (update_one_kernel does the first four; of few and short rows all five, 1 launch), no host synchronisation and no waiting between workgroups:
+// Update = 5 launches for any number of layers (a workgroup finds its layer from its index), or 2 up to 262 144 positions
+// (update_group_kernel does the first four; of few and short rows all five, 1 launch), no host synchronisation:
 //   1. digit 0       histogram of the top 11 bits of the order-preserving integer image of the live nodes' norms
 //   2. digit 1       every workgroup derives m, k = floor(p_grad*m) and the first digit of the norm of rank k from
 //                    the finished histogram, then histograms the next 11 bits of its keys that carry that digit
@@ -56,12 +56,14 @@ constexpr int SEL_BPT = SEL_BINS / SEL_THREADS;  // bins owned by a thread in th
 constexpr int SEL_CHUNK = 4 * SEL_THREADS;       // keys per workgroup in the histogram launches
 constexpr int FG_MAX_UPD_LAYERS = 8;
 
-// Selection scratch of a layer, owned by the cache. All-zero between updates: launch 4 clears it again.
+// Selection scratch of a layer, owned by the cache. All-zero between updates: launch 4, or the last of the group, clears it again.
 struct SelState {
     unsigned int hist0[SEL_BINS];
     unsigned int hist1[SEL_BINS];
     unsigned int n_surv;
-    unsigned int pad[3];
+    unsigned int arrived[2];       // workgroups that have reached a meeting point (update_group_kernel)
+    unsigned int done;             // ... and that have left the scratch alone
+    unsigned int admits[64];       // a workgroup's admissible nodes, published
     unsigned int hist2[SEL_BINS];  // estimates of saved accesses of the admissible nodes (access-aware policy)
 };
 
@@ -346,27 +348,33 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void classify_update_kernel(UpdBatch
     }
 }
 
-// ---- launches 1 to 4 as one: a whole layer by one workgroup -------------------------------------------------------------------
+// ---- launches 1 to 4 as one: a layer by one workgroup per 4096 positions --------------------------------------------------------
 //
-// What bounds the four launches on a small layer is not their work but their chain: each is a few dependent reads, barriers
-// and scans long (6 + 9 + 13 + 6 us at 1.2 k positions, hardly more at 54 k). A workgroup of 1024 threads holds the keys of up
-// to 8192 positions in registers (four per thread and step), so it reads them once, finds tau by the same three digits in
-// LDS, classifies, ranks the admissible nodes and hands out their slots, with no other workgroup to wait for. The
-// histograms are kept four times (by lane mod 4): norms share their leading digits, and equal bins of a wavefront are
-// added one after the other. Measured, whole update with its row copy of 256 bytes, p_grad 0.4: 1.2 k positions 17 us against 31, 4096: 19
-// (31), 8192: 28 (33; with p_grad 0.9 35 against 34); 12 288: 34 (33) and 16 384: 40 (34), where one compute unit's
-// random accesses to the index are the bound: the four launches from 8193 positions on.
+// What bounds the four launches is not their work but their chain: each is a few dependent reads, barriers
+// and scans long (6 + 9 + 13 + 6 us at 1.2 k positions, hardly more at 54 k), and workgroups of 1024 threads wait for room beside the
+// weight gradients (the third launch, 72 of them at 67 k positions, 33 us there). A workgroup of 1024 threads holds the keys of
+// 4096 positions in registers (four per thread), so it reads them once, finds tau by three digits,
+// classifies, ranks the admissible nodes and hands out their slots. By itself it finds the digits in LDS; the workgroups of a larger
+// layer meet three times: behind the histogram of the first digit, behind the list of the keys that carry it (from which each finds the
+// other two for itself), and behind the check-outs, with the numbers of admissible nodes. The histograms are
+// kept four times (by lane mod 4): norms share their leading digits, and equal bins of a wavefront are
+// added one after the other.
+// Who waits needs no more than that the other workgroups start: they are at most 64 in all, so that they are all there together on a chip
+// with room for 512 of their size, and a launch they have to wait behind ends without them. The polls are bounded all the same.
+// Measured, the four launches and now: 28 k positions 36 us and their gaps, 30; 74 k beside the weight gradients of 55 k rows 66, 43; 1.2 k with
+// its row copy 31, 17 (one workgroup). GCN iteration of 55 k rows 349 us, 335.
 constexpr int ONE_COPIES = 4;
-constexpr int ONE_MAX_STEPS = 2;      // 8192 positions
+constexpr int GRP_CHUNK = 4 * SEL_THREADS;      // positions of a workgroup
+constexpr int GRP_MAX = 64;                     // workgroups of a launch
+constexpr int GRP_SPIN_LIMIT = 1 << 20;         // polls before a workgroup gives up (never reached)
+constexpr uint32_t GRP_PUBLISHED = 0x80000000u;
 
 __device__ __attribute__((aligned(16))) uint32_t upd_spare[4];      // what is read where a layer has no quad
 
-// Finds the bin holding rank *s_rank among hist[bin * ONE_COPIES + copy], stores it in *s_bin and rebases *s_rank to that bin.
-__device__ __forceinline__ void select_bin_copies(const uint32_t* hist, long long* red, uint32_t* s_bin, long long* s_rank) {
-    static_assert(SEL_BPT == 2 && ONE_COPIES == 4, "two bins of four counters per thread");
+// bin holding rank *s_rank, from this thread's two of 2048 counters, into *s_bin; *s_rank is rebased to that bin
+__device__ __forceinline__ void select_bin_two(long long c0, long long c1, long long* red, uint32_t* s_bin, long long* s_rank) {
+    static_assert(SEL_BPT == 2, "two bins per thread");
     const int t = threadIdx.x;
-    const uint4 a = ((const uint4*)hist)[2 * t], b = ((const uint4*)hist)[2 * t + 1];
-    const long long c0 = (long long)a.x + a.y + a.z + a.w, c1 = (long long)b.x + b.y + b.z + b.w;
     long long incl = c0 + c1;
     for (int off = 1; off < FG_WAVE; off <<= 1) {
         const long long v = __shfl_up(incl, off, FG_WAVE);
@@ -386,81 +394,153 @@ __device__ __forceinline__ void select_bin_copies(const uint32_t* hist, long lon
     __syncthreads();
 }
 
-// COPY: the admitted rows are copied here as well (a launch less) instead of by the row copy behind it.
-template <int STEPS, bool COPY>
-__global__ __launch_bounds__(SEL_THREADS) void update_one_kernel(UpdBatch B) {
+// This thread's two counters of hist[bin * ONE_COPIES + copy]
+__device__ __forceinline__ void two_bins(const uint32_t* hist, long long& c0, long long& c1) {
+    static_assert(ONE_COPIES == 4, "four counters per bin");
+    const uint4 a = ((const uint4*)hist)[2 * threadIdx.x], b = ((const uint4*)hist)[2 * threadIdx.x + 1];
+    c0 = (long long)a.x + a.y + a.z + a.w;
+    c1 = (long long)b.x + b.y + b.z + b.w;
+}
+
+// What the workgroups of a layer tell each other goes past the caches of their XCDs, word by word (atomics of agent scope); before a
+// workgroup says that it is there, each of its wavefronts waits until its own have arrived. (Release and acquire fences instead
+// write back and invalidate whole L2s: 28 k positions 39 us instead of 30, 99 instead of 43 of 74 k beside the weight gradients.)
+template <typename T>
+__device__ __forceinline__ T grp_load(const T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void grp_store(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void grp_arrive() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+}
+
+// All `n` workgroups of a layer have come here. false: given up.
+__device__ __forceinline__ bool grp_meet(unsigned int* arrived, unsigned int n, int* s_ok) {
+    grp_arrive();
+    if (threadIdx.x == 0) {
+        __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int polls = 0;
+        while (grp_load(arrived) < n && ++polls < GRP_SPIN_LIMIT) __builtin_amdgcn_s_sleep(1);
+        *s_ok = polls < GRP_SPIN_LIMIT;
+    }
+    __syncthreads();
+    return *s_ok != 0;
+}
+
+// COPY (every layer has one workgroup): the admitted rows are copied here as well (a launch less) instead of by the row copy behind it.
+template <bool COPY>
+__global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
     __shared__ __attribute__((aligned(16))) uint32_t hist[SEL_BINS * ONE_COPIES];
-    __shared__ int wave_count[STEPS][SEL_THREADS / FG_WAVE];
+    __shared__ int wave_count[SEL_THREADS / FG_WAVE];
     __shared__ long long red[16];
     __shared__ uint32_t s_bin;
     __shared__ long long s_rank;
-    __shared__ int s_evicted, s_over;
-    const UpdLayer& L = B.l[blockIdx.x];
+    __shared__ int s_evicted, s_over, s_ok, s_before, s_all;
+    __shared__ unsigned int s_count, s_base;
+    int part;
+    const int layer = layer_of_block(B.sel_first, B.n_layers, blockIdx.x, part);
+    const UpdLayer& L = B.l[layer];
     const CacheRW& c = L.c;
+    const unsigned int parts = (unsigned int)(B.sel_first[layer + 1] - B.sel_first[layer]);
     const int t = threadIdx.x, lane = fg_lane(), wave = fg_wave();
-    const int n = upd_count(L);
+    const int n_all = upd_count(L), base = part * GRP_CHUNK;
+    const int n = n_all - base < 0 ? 0 : (n_all - base < GRP_CHUNK ? n_all - base : GRP_CHUNK);      // positions of this workgroup
     const int64_t head = *c.head;
-    // Position of element e of step k: 4 * (k * 1024 + t) + e. Every read is unconditional (the first quad, or 16 bytes of the
-    // library's own, where a quad is not wholly there) so that a batch of steps is in flight together; the one quad that the end of the layer
+    // Position of element e: base + 4 * t + e. Every read is unconditional (the first quad, or 16 bytes of the
+    // library's own, where a quad is not wholly there) so that they are in flight together; the one quad that the end of the layer
     // cuts is read one by one by the thread that owns it, and joins below.
     const int n_quads = n >> 2;
-    const bool cut_mine = (n & 3) != 0 && n_quads % SEL_THREADS == t;
-    const int cut_step = n_quads / SEL_THREADS;
-    uint32_t cut_key[4] = {0, 0, 0, 0}, cut_live = 0, cut_hit = 0;
-    int32_t cut_id[4] = {-1, -1, -1, -1};
-    if (cut_mine)
-        for (int e = 0; e < 3; ++e) {
-            const int j = 4 * n_quads + e;
-            if (j >= n) break;
-            cut_key[e] = order_key(L.gnorm[j]);
-            cut_id[e] = L.ids[j];
-            if (L.live ? L.live[j] != 0 : true) cut_live |= 1u << e;
-            if (L.hit[j] != 0) cut_hit |= 1u << e;
-        }
-    const char* gnorm_base = n_quads > 0 ? (const char*)L.gnorm : (const char*)upd_spare;
-    const char* hit_base = n_quads > 0 ? (const char*)L.hit : (const char*)upd_spare;
-    const char* live_base = n_quads > 0 && L.live ? (const char*)L.live : hit_base;
-    const char* ids_base = n_quads > 0 ? (const char*)L.ids : (const char*)upd_spare;
-    const uint32_t all_live = L.live ? 0u : 0x01010101u;
-    uint32_t key[4 * STEPS];
-    uint32_t is_live = 0, is_hit = 0;      // four bits per step
-#pragma unroll
-    for (int k = 0; k < STEPS; ++k) {
-        const int q = k * SEL_THREADS + t;
-        const bool whole = q < n_quads;
+    const bool cut = (n & 3) != 0 && n_quads == t, whole = t < n_quads;
+    uint32_t key[4], is_live = 0, is_hit = 0;      // a bit per element
+    int32_t id[4];
+    {
         typedef float f4 __attribute__((ext_vector_type(4)));
-        const uint32_t at = whole ? (uint32_t)q : 0u;
-        const f4 g = *(const f4*)(gnorm_base + 16u * at);
-        const uint32_t l4 = *(const uint32_t*)(live_base + 4u * at) | all_live;
+        const bool any = n_quads > 0;
+        const uint32_t at = whole ? (uint32_t)t : 0u;
+        const char* none = (const char*)upd_spare;
+        const char* hit_base = any ? (const char*)L.hit + base : none;
+        const f4 g = *(const f4*)((any ? (const char*)L.gnorm + 4 * (int64_t)base : none) + 16u * at);
+        const uint32_t l4 = *(const uint32_t*)((any && L.live ? (const char*)L.live + base : hit_base) + 4u * at) | (L.live ? 0u : 0x01010101u);
         const uint32_t h4 = *(const uint32_t*)(hit_base + 4u * at);
-        const bool cut = cut_mine && cut_step == k;
-        uint32_t lb = 0, hb = 0;
+        const int4 v4 = *(const int4*)((any ? (const char*)L.ids + 4 * (int64_t)base : none) + 16u * at);
+        id[0] = v4.x;
+        id[1] = v4.y;
+        id[2] = v4.z;
+        id[3] = v4.w;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            key[4 * k + e] = cut ? cut_key[e] : order_key(g[e]);
-            lb |= ((l4 >> (8 * e)) & 0xFFu) ? 1u << e : 0u;
-            hb |= ((h4 >> (8 * e)) & 0xFFu) ? 1u << e : 0u;
+            key[e] = order_key(g[e]);
+            is_live |= ((l4 >> (8 * e)) & 0xFFu) ? 1u << e : 0u;
+            is_hit |= ((h4 >> (8 * e)) & 0xFFu) ? 1u << e : 0u;
         }
-        lb = cut ? cut_live : (whole ? lb : 0u);
-        hb = cut ? cut_hit : (whole ? hb : 0u);
-        is_live |= lb << (4 * k);
-        is_hit |= hb << (4 * k);
+        if (!whole) is_live = is_hit = 0;
+        if (cut)
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                const int j = base + 4 * n_quads + e;
+                if (j >= n_all) continue;
+                key[e] = order_key(L.gnorm[j]);
+                id[e] = L.ids[j];
+                if (L.live ? L.live[j] != 0 : true) is_live |= 1u << e;
+                if (L.hit[j] != 0) is_hit |= 1u << e;
+            }
     }
-    auto live_bit = [&](int k, int e) { return ((is_live >> (4 * k + e)) & 1u) != 0; };
-    auto hit_bit = [&](int k, int e) { return ((is_hit >> (4 * k + e)) & 1u) != 0; };
     auto clear_hist = [&]() {
         for (int b = t; b < SEL_BINS * ONE_COPIES / 4; b += SEL_THREADS) ((uint4*)hist)[b] = uint4{0, 0, 0, 0};
     };
-    if (t == 0) s_evicted = s_over = 0;
+    auto count_key = [&](uint32_t bin) { atomicAdd(&hist[bin * ONE_COPIES + (lane & (ONE_COPIES - 1))], 1u); };
+    if (t == 0) {
+        s_evicted = s_over = 0;
+        s_count = 0;
+    }
     clear_hist();
-    const long long m = fg_block_sum((long long)__popc(is_live), red);      // (its barriers also end the clearing)
+    bool lost = false;
+    long long m, c0, c1;
+    uint32_t tau_key = 0, n_list = 0;
+    uint32_t* list = (uint32_t*)L.apos;      // the keys with the first digit of tau (parts > 1); at most n of them
+    if (parts == 1) {
+        m = fg_block_sum((long long)__popc(is_live), red);      // (its barriers also end the clearing)
+    } else {
+        if (part == 0 && t < 4 && L.stats) grp_store(&L.stats[t], (int64_t)0);
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if ((is_live >> e) & 1u) count_key(key[e] >> 21);
+        __syncthreads();
+        two_bins(hist, c0, c1);
+        if (c0) atomicAdd(&L.sel->hist0[2 * t], (unsigned int)c0);
+        if (c1) atomicAdd(&L.sel->hist0[2 * t + 1], (unsigned int)c1);
+        lost = !grp_meet(&L.sel->arrived[0], parts, &s_ok);
+        c0 = grp_load(&L.sel->hist0[2 * t]);
+        c1 = grp_load(&L.sel->hist0[2 * t + 1]);
+        m = fg_block_sum(c0 + c1, red);
+    }
     const long long k_rank = (long long)floor((double)L.p_grad * (double)m);
-    const int mode = k_rank <= 0 ? 0 : (k_rank >= m ? 2 : 1);
-    uint32_t tau_key = 0;
+    const int mode = lost || k_rank <= 0 ? 0 : (k_rank >= m ? 2 : 1);
+    if (mode == 1 && t == 0) s_rank = k_rank;
+    if (parts > 1) {      // (every workgroup of the layer finds the same digit, and takes both meetings whatever the mode)
+        if (mode == 1) {
+            __syncthreads();
+            select_bin_two(c0, c1, red, &s_bin, &s_rank);
+            tau_key = s_bin << 21;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (((is_live >> e) & 1u) && (key[e] >> 21) == s_bin) hist[atomicAdd(&s_count, 1u)] = key[e];
+            __syncthreads();
+            if (t == 0 && s_count) s_base = atomicAdd(&L.sel->n_surv, s_count);
+            __syncthreads();
+            for (unsigned int i = t; i < s_count; i += SEL_THREADS) grp_store(&list[s_base + i], hist[i]);
+        }
+        if (!grp_meet(&L.sel->arrived[1], parts, &s_ok)) lost = true;
+        n_list = grp_load(&L.sel->n_surv);
+    }
     if (mode == 1) {      // uniform over the workgroup: tau is the key of rank k, found digit by digit (11 + 11 + 10 bits)
-        if (t == 0) s_rank = k_rank;
 #pragma unroll 1
-        for (int pass = 0; pass < 3; ++pass) {
+        for (int pass = parts == 1 ? 0 : 1; pass < 3; ++pass) {
             const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
             const uint32_t bins = pass == 2 ? 1023u : 2047u;
             const uint32_t above = pass == 0 ? 0u : (pass == 1 ? 0xFFE00000u : 0xFFFFFC00u);      // the digits found so far
@@ -468,90 +548,99 @@ __global__ __launch_bounds__(SEL_THREADS) void update_one_kernel(UpdBatch B) {
                 clear_hist();
                 __syncthreads();
             }
+            if (parts == 1) {
 #pragma unroll
-            for (int k = 0; k < STEPS; ++k) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const uint32_t x = key[4 * k + e];
-                    if (live_bit(k, e) && (x & above) == tau_key)
-                        atomicAdd(&hist[((x >> shift) & bins) * ONE_COPIES + (lane & (ONE_COPIES - 1))], 1u);
+                for (int e = 0; e < 4; ++e)
+                    if (((is_live >> e) & 1u) && (key[e] & above) == tau_key) count_key((key[e] >> shift) & bins);
+            } else {
+                for (uint32_t i = t; i < n_list; i += SEL_THREADS) {
+                    const uint32_t x = grp_load(&list[i]);
+                    if ((x & above) == tau_key) count_key((x >> shift) & bins);
                 }
             }
             __syncthreads();
-            select_bin_copies(hist, red, &s_bin, &s_rank);
+            two_bins(hist, c0, c1);
+            select_bin_two(c0, c1, red, &s_bin, &s_rank);
             tau_key |= s_bin << shift;
         }
     }
     // check-outs and admissible nodes
-    int32_t id[4 * STEPS];
-    uint32_t admit_bits = 0;      // four bits per step
+    uint32_t admit_bits = 0;
     int evicted = 0;
 #pragma unroll
-    for (int k = 0; k < STEPS; ++k) {
-        const int j = 4 * (k * SEL_THREADS + t);
-        const bool whole = k * SEL_THREADS + t < n_quads, cut = cut_mine && cut_step == k;
-        int32_t* v = id + 4 * k;
-        const int4 v4 = *(const int4*)(ids_base + (whole ? 4u * (uint32_t)j : 0u));
-        v[0] = cut ? cut_id[0] : v4.x;
-        v[1] = cut ? cut_id[1] : v4.y;
-        v[2] = cut ? cut_id[2] : v4.z;
-        v[3] = cut ? cut_id[3] : v4.w;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const bool low = mode == 2 || (mode == 1 && key[4 * k + e] < tau_key);
-            if (!live_bit(k, e) || v[e] < 0 || v[e] >= c.num_nodes || hit_bit(k, e) == low) continue;
-            if (low) {
-                admit_bits |= 1u << (4 * k + e);
-            } else {
-                c.map[v[e]] = -1;
-                ++evicted;
-            }
+    for (int e = 0; e < 4; ++e) {
+        const bool low = mode == 2 || (mode == 1 && key[e] < tau_key);
+        if (lost || !((is_live >> e) & 1u) || id[e] < 0 || id[e] >= c.num_nodes || (((is_hit >> e) & 1u) != 0) == low) continue;
+        if (low) {
+            admit_bits |= 1u << e;
+        } else {
+            grp_store(&c.map[id[e]], -1);
+            ++evicted;
         }
     }
     for (int off = FG_WAVE / 2; off > 0; off >>= 1) evicted += __shfl_down(evicted, off, FG_WAVE);
     if (lane == 0 && evicted) atomicAdd(&s_evicted, evicted);
-    // ranks in position order: steps first, then threads, then a thread's elements
-    int before[STEPS];
-#pragma unroll
-    for (int k = 0; k < STEPS; ++k) {
-        const int own = __popc((admit_bits >> (4 * k)) & 15u);
-        int incl = own;
-        for (int off = 1; off < FG_WAVE; off <<= 1) {
-            const int v = __shfl_up(incl, off, FG_WAVE);
-            if (lane >= off) incl += v;
-        }
-        if (lane == FG_WAVE - 1) wave_count[k][wave] = incl;
-        before[k] = incl - own;
+    // ranks in position order: workgroups first, then threads, then a thread's elements
+    const int own = __popc(admit_bits);
+    int incl = own;
+    for (int off = 1; off < FG_WAVE; off <<= 1) {
+        const int v = __shfl_up(incl, off, FG_WAVE);
+        if (lane >= off) incl += v;
     }
+    if (lane == FG_WAVE - 1) wave_count[wave] = incl;
     __syncthreads();
-    int total = 0;
-#pragma unroll
-    for (int k = 0; k < STEPS; ++k) {
-        before[k] += total;
-        for (int w = 0; w < SEL_THREADS / FG_WAVE; ++w) {
-            const int x = wave_count[k][w];
-            if (w < wave) before[k] += x;
-            total += x;
-        }
+    int before = incl - own, total = 0;
+    for (int w = 0; w < SEL_THREADS / FG_WAVE; ++w) {
+        if (w < wave) before += wave_count[w];
+        total += wave_count[w];
     }
+    if (parts > 1) {      // what the other workgroups admit, behind all check-outs
+        grp_arrive();
+        if (wave == 0) {
+            uint32_t w = GRP_PUBLISHED;
+            if (t == 0) grp_store(&L.sel->admits[part], GRP_PUBLISHED | (uint32_t)total);
+            if (t < (int)parts) {
+                int polls = 0;
+                do {
+                    w = grp_load(&L.sel->admits[t]);
+                    if (w & GRP_PUBLISHED) break;
+                    __builtin_amdgcn_s_sleep(1);
+                } while (++polls < GRP_SPIN_LIMIT);
+            }
+            int there = (int)(w & ~GRP_PUBLISHED), ahead = t < part ? there : 0;
+            for (int off = FG_WAVE / 2; off > 0; off >>= 1) {
+                there += __shfl_xor(there, off, FG_WAVE);
+                ahead += __shfl_xor(ahead, off, FG_WAVE);
+            }
+            const bool all_there = __all((w & GRP_PUBLISHED) != 0);
+            if (t == 0) {
+                s_before = ahead;
+                s_all = there;
+                s_ok = all_there;
+            }
+        }
+        __syncthreads();
+        before += s_before;
+        total = s_all;
+        if (!s_ok) lost = true;
+    }
+    if (lost) admit_bits = 0;
     int over = 0;
-#pragma unroll
-    for (int k = 0; k < STEPS; ++k) {
-        const int j = 4 * (k * SEL_THREADS + t);
+    {
         int32_t slot[4], old[4], old_map[4], old_stamp[4];
         int rank[4];
         bool in[4];
         // the four chains slot -> owner -> its map entry side by side (reads of slot 0 / node 0 where there is nothing to do)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            rank[e] = before[k] + __popc((admit_bits >> (4 * k)) & ((1u << e) - 1u));
-            in[e] = ((admit_bits >> (4 * k + e)) & 1u) != 0 && rank[e] < L.room;
+            rank[e] = before + __popc(admit_bits & ((1u << e) - 1u));
+            in[e] = ((admit_bits >> e) & 1u) != 0 && rank[e] < L.room;
             slot[e] = in[e] ? (int32_t)((head + rank[e]) % c.capacity) : 0;
             old[e] = c.slot_node[slot[e]];
             old_stamp[e] = c.slot_stamp[slot[e]];
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) old_map[e] = c.map[old[e] >= 0 && old[e] < c.num_nodes ? old[e] : 0];
+        for (int e = 0; e < 4; ++e) old_map[e] = grp_load(&c.map[old[e] >= 0 && old[e] < c.num_nodes ? old[e] : 0]);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             if (!in[e]) continue;
@@ -559,32 +648,51 @@ __global__ __launch_bounds__(SEL_THREADS) void update_one_kernel(UpdBatch B) {
                 const int64_t age = c.iter + 1 - (int64_t)old_stamp[e];
                 over += age >= 1 && age <= (int64_t)c.t_stale ? 1 : 0;
             }
-            c.slot_node[slot[e]] = id[4 * k + e];
+            c.slot_node[slot[e]] = id[e];
             c.slot_stamp[slot[e]] = (int32_t)c.iter;
-            c.map[id[4 * k + e]] = slot[e];
-            L.apos[rank[e]] = j + e;
+            c.map[id[e]] = slot[e];
+            L.apos[rank[e]] = base + 4 * t + e;
             L.aslot[rank[e]] = slot[e];
-            if (COPY) ((int2*)hist)[rank[e]] = int2{j + e, slot[e]};      // (the histograms are not needed any more)
+            if (COPY) ((int2*)hist)[rank[e]] = int2{4 * t + e, slot[e]};      // (the histograms are not needed any more)
         }
     }
     for (int off = FG_WAVE / 2; off > 0; off >>= 1) over += __shfl_down(over, off, FG_WAVE);
     if (lane == 0 && over) atomicAdd(&s_over, over);
     __syncthreads();
     if (t == 0) {
-        const int64_t in = total < L.room ? total : L.room;
-        L.hdr->mode = mode;
-        L.hdr->tau_key = tau_key;
-        L.hdr->m_live = m;
-        finish_header(L, head, in);
+        const int64_t in = lost ? 0 : (total < L.room ? total : L.room);
+        if (part == 0) {
+            L.hdr->mode = mode;
+            L.hdr->tau_key = tau_key;
+            L.hdr->m_live = m;
+            finish_header(L, head, in);
+        }
         if (L.stats) {
-            L.stats[0] = in;
-            L.stats[1] = s_evicted;
-            L.stats[2] = s_over;
-            L.stats[3] = total - in;
+            if (part == 0) {
+                L.stats[0] = lost ? -1 : in;
+                L.stats[3] = lost ? -1 : total - in;
+            }
+            if (parts == 1) {
+                L.stats[1] = s_evicted;
+                L.stats[2] = s_over;
+            } else {
+                if (s_evicted) atomicAdd((unsigned long long*)&L.stats[1], (unsigned long long)s_evicted);
+                if (s_over) atomicAdd((unsigned long long*)&L.stats[2], (unsigned long long)s_over);
+            }
+        }
+        // the last to come here clears the scratch: nobody reads it any more
+        if (parts > 1) s_ok = __hip_atomic_fetch_add(&L.sel->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
+    }
+    if (parts > 1) {
+        __syncthreads();
+        if (s_ok) {
+            for (int b = t; b < SEL_BINS; b += SEL_THREADS) L.sel->hist0[b] = 0;
+            if (t < 64) L.sel->admits[t] = 0;
+            if (t == 0) L.sel->n_surv = L.sel->arrived[0] = L.sel->arrived[1] = L.sel->done = 0;
         }
     }
     if constexpr (COPY) {
-        static_assert(STEPS == 1 && sizeof(hist) >= 4 * SEL_THREADS * sizeof(int2), "every position may be admitted");
+        static_assert(sizeof(hist) >= GRP_CHUNK * sizeof(int2), "every position may be admitted");
         typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
         const int pieces = (int)(L.row_bytes >> 4), items = (int)(total < L.room ? total : L.room) * pieces;
         constexpr int TOGETHER = 4;
@@ -1031,38 +1139,31 @@ fg_status_t launch_update(UpdBatch& B, hipStream_t st, bool select = true, bool 
         B.scan_first[i + 1] = B.scan_first[i] + (int)fg_ceil_div(n, FG_SCAN_BLOCK);
     }
     const unsigned n_sel = (unsigned)B.sel_first[B.n_layers], n_scan = (unsigned)B.scan_first[B.n_layers];
-    // One workgroup per layer where the layers fit its registers, their arrays can be read four at a time and no layer ranks by
-    // saved accesses (that needs the counts of all its admissible nodes first).
-    // (Each admission is three writes and three reads at random of one compute unit: from some 6000 the four launches, which
-    // spread them, are level on the device (8192 positions, p_grad 0.9: 35 us against 34; 0.5: 31 against 33; 7000 and 0.9: 33.5 both),
-    // but the host queues three launches more: a training iteration on a bound of 7308, 0.9, 256 to 259 us so, 270 with them.)
-    int64_t n_most = 0;
-    bool one = true;
+    // A workgroup per 4096 positions in one launch where the layers' arrays can be read four at a time, no layer ranks by saved accesses
+    // (that needs the counts of all its admissible nodes first) and the workgroups are few enough to wait for each other. A selection by
+    // itself runs beside the layers, where four short launches are in nobody's way, and workgroups that wait are: one per layer there
+    // (large step 215 us with the four launches, 224 with the group).
+    bool group = n_sel <= (unsigned)(commit ? GRP_MAX : B.n_layers);
     for (int i = 0; i < B.n_layers; ++i) {
         const UpdLayer& u = B.l[i];
-        if (u.n > n_most) n_most = u.n;
-        one = one && !u.saving && !(((uintptr_t)u.gnorm | (uintptr_t)u.ids) & 15) && !(((uintptr_t)u.live | (uintptr_t)u.hit) & 3);
+        group = group && !u.saving && !(((uintptr_t)u.gnorm | (uintptr_t)u.ids) & 15) && !(((uintptr_t)u.live | (uintptr_t)u.hit) & 3);
     }
-    const int steps = (int)fg_ceil_div(n_most, 4 * SEL_THREADS);
-    one = one && steps <= ONE_MAX_STEPS;
-    if (select && one) {
-        const dim3 grid((unsigned)B.n_layers), block(SEL_THREADS);
+    if (select && group) {
+        const dim3 grid(n_sel), block(SEL_THREADS);
         // About p_grad of the positions are admitted. Up to 160 KB of their rows go with the selection: one compute unit copies
         // them at some 60 GB/s, which up to there costs the device about what the launch it saves costs it, and the host is spared that
         // launch (512 positions of 256 bytes, p_grad 0.9, 115 KB: 17.9 us against 18.4 with a launch for the rows; 1024, 0.5, 128 KB:
         // 17.8 and 18.2; 1500 of 1024 bytes, 0.1, 150 KB: 18.7 and 17.9; 1500, 0.5, 188 KB: 20.2 and 18.8; 2048, 0.9, 461 KB: 29.6
         // and 21.0). A step of 1.2 k such positions, 150 KB: 59 us and 62. A bound on a count in device memory may say 200 KB: a sampler's is
         // never reached, since nodes repeat; training iteration on one of 196 KB 100 to 102 us, 103 to 105 with a launch for the rows.
-        bool copy = commit && steps <= 1;
+        bool copy = commit && n_sel == (unsigned)B.n_layers;
         for (int i = 0; i < B.n_layers; ++i)
             copy = copy && B.l[i].row_bytes % 16 == 0 && (double)B.l[i].p_grad * (double)B.l[i].n * (double)B.l[i].row_bytes <= (B.l[i].n_dev ? 200.0 : 160.0) * 1024.0;
         if (copy)
-            hipLaunchKernelGGL((update_one_kernel<1, true>), grid, block, 0, st, B);
-        else if (steps <= 1)
-            hipLaunchKernelGGL((update_one_kernel<1, false>), grid, block, 0, st, B);
+            hipLaunchKernelGGL(update_group_kernel<true>, grid, block, 0, st, B);
         else
-            hipLaunchKernelGGL((update_one_kernel<ONE_MAX_STEPS, false>), grid, block, 0, st, B);
-        FG_LAUNCH_CHECK("update_one_kernel");
+            hipLaunchKernelGGL(update_group_kernel<false>, grid, block, 0, st, B);
+        FG_LAUNCH_CHECK("update_group_kernel");
         if (copy) return FG_OK;
     } else if (select) {
         hipLaunchKernelGGL(update_digit0_kernel, dim3(n_sel), dim3(SEL_THREADS), 0, st, B);

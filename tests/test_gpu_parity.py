@@ -552,21 +552,40 @@ def test_cache_update_sequences_match_oracle(env, cap, t_stale, p, nmax):
         B.fg_cache_destroy(cache)
 
 
-@pytest.mark.parametrize("n", [1, 3, 4, 5, 63, 4095, 4096, 4097, 6144, 6145, 8187, 8191, 8192, 8193])
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 63, 4095, 4096, 4097, 6144, 6145, 8187, 8191, 8192, 8193, 12289, 262_144, 262_145])
 @pytest.mark.parametrize("p", [0.0, 0.37, 0.75, 1.0])
 def test_cache_update_sizes_around_a_workgroups_share(env, n, p):
-    """Layers on both sides of what one workgroup takes in one and in two steps of four positions a thread, cut quads included;
+    """Layers on both sides of what one workgroup takes, and of what workgroups that wait for each other do, cut quads included;
     a ring that some of them wrap, two updates in a row (the second overwrites the first's entries and checks hits out)."""
+    _check_update_sizes(env, n, p, lambda r: np.round(np.exp(r.standard_normal(n)), 2))      # ties occur
+
+
+@pytest.mark.parametrize("n", [4096, 4097, 30_001])
+@pytest.mark.parametrize("norms", ["equal", "two values", "one digit apart", "with zeros and infinities"])
+def test_cache_update_of_norms_that_share_their_digits(env, n, norms):
+    """Every key in the list of those with the threshold's first digit, thresholds in the second and the third digit, both ends."""
+    def draw(r):
+        if norms == "equal":
+            return np.full(n, 0.7)
+        if norms == "two values":
+            return np.where(r.random(n) < 0.5, 1.0, 1.0 + 2.0 ** -23)
+        if norms == "one digit apart":
+            return 1.0 + r.integers(0, 200, n) * 2.0 ** -13
+        return np.choose(r.integers(0, 3, n), [np.zeros(n), np.full(n, np.inf), np.exp(r.standard_normal(n))])
+    _check_update_sizes(env, n, 0.37, draw)
+
+
+def _check_update_sizes(env, n, p, norms):
     torch, B = env
     r = np.random.default_rng(n)
-    N, cap, d = 20000, 4500, 8
+    N, cap, d = max(20000, 3 * n), 4500, 8
     oc = O.HistoricalCache(N, cap, d, 5)
     cache = B.fg_cache_create(N, [cap], [d], B.FG_F32, 5, None)
     try:
         for i in range(2):
             ids = r.permutation(min(N, 2 * n + 8))[:n].astype(np.int32)
             live = r.random(n) < (0.9 if i else 1.1)
-            gn = np.round(np.exp(r.standard_normal(n)), 2).astype(np.float32)      # ties occur
+            gn = norms(r).astype(np.float32)
             rows = r.standard_normal((n, d)).astype(np.float32)
             look = O.lookup_prune(oc, i, ids, live, None, None, None, 0)
             _, _, stats = _device_update(torch, B, cache, i, ids, live, gn, p, rows, misalign=False)
