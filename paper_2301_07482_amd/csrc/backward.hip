@@ -477,6 +477,9 @@ fg_status_t fg_launch_linear_bf16(const void* h_src, int32_t n_src, int64_t src_
                                   int32_t n_out, int64_t out_stride, fg_dtype_t out_dtype, hipStream_t st, bool w_nk,
                                   const int32_t* src_ids_dev = nullptr);
 
+fg_status_t fg_launch_linear_masked(const float* dh, int64_t dh_stride, const float* h, int64_t h_stride, int32_t n, const int32_t* rows_dev,
+                                    const int64_t* n_rows_dev, int64_t max_rows, int32_t d_out, int32_t cols, const float* W, float* dx, hipStream_t st, bool* done);
+
 extern "C" fg_status_t fg_softmax_xent_grad(const float* h_dev, int64_t h_stride, const int32_t* labels_dev, int32_t n, int32_t d,
                                             float* dh_dev, int64_t dh_stride, void* stream) {
     if (n < 0 || d <= 0) FG_FAIL(FG_ERR_INVALID_ARG, "fg_softmax_xent_grad: bad size (n %d, d %d)", n, d);
@@ -539,8 +542,8 @@ extern "C" size_t fg_layer_backward_bf16_workspace_bytes(int32_t n, int64_t max_
     return layer_backward_ws(BW_SAGE_BF16, n, max_rows, d_in, d_out);
 }
 
-// The three layer kinds share the sequence: mask (+ rounding), transposed weights, dz . W^T on the forward GEMM path, transposed
-// aggregation with the row norms.
+// The three layer kinds share the sequence: dz . W^T, transposed aggregation with the row norms. In fp32 the product masks and
+// transposes for itself; in bf16, and for rows too wide for it, a launch forms the masked (and rounded) operand for the forward GEMM.
 static fg_status_t layer_backward_launch(const char* who, int kind, const float* dh_dev, int64_t dh_stride, const void* h_dev,
                                          int64_t h_stride, int32_t n, const int32_t* rows_dev, const int64_t* n_rows_dev,
                                          int64_t max_rows, const uint8_t* live_dev, const uint8_t* hit_dev,
@@ -582,6 +585,7 @@ static fg_status_t layer_backward_launch(const char* who, int kind, const float*
         int64_t blocks = fg_ceil_div(max_rows, BW_THREADS / 64);
         if (blocks > 4096) blocks = 4096;
         const dim3 tgrid((unsigned)fg_ceil_div(d_out, 32), (unsigned)fg_ceil_div(cols, 32));
+        bool multiplied = false;
         // four columns at a time where dh and h allow it (1024 rows of 1024 columns 10.8 -> 6.8 us; the halves of dz are workspace, aligned, and d_out is a multiple of 8)
         const int vec = !(((uintptr_t)dh_dev | (uintptr_t)dh_stride) & 15) && !(((uintptr_t)h_dev | (uintptr_t)h_stride) & (uintptr_t)(4 * esz - 1));
         if (b16) {
@@ -594,7 +598,12 @@ static fg_status_t layer_backward_launch(const char* who, int kind, const float*
             fg_status_t rc = fg_launch_linear_bf16(dz_pos, n, (int64_t)half * 2, FG_BF16, dz_cmp, (int64_t)half * 2, rows_dev, n_rows_dev,
                                                    max_rows, half, cols, W, nullptr, 0, dx, n, (int64_t)cols * 4, FG_F32, st, true);
             if (rc != FG_OK) return rc;
-        } else {
+        } else if (fg_tuning(FG_TUNE_LINEAR_TILE) == 0) {
+            fg_status_t rc = fg_launch_linear_masked(dh_dev, dh_stride, (const float*)h_dev, h_stride, n, rows_dev, n_rows_dev, max_rows, d_out, cols,
+                                                     (const float*)W, dx, st, &multiplied);
+            if (rc != FG_OK) return rc;
+        }
+        if (!b16 && !multiplied) {
             // (the transposition of W rides in the same launch: tgrid.x * tgrid.y workgroups in front of the others)
             const int t_blocks = (int)(tgrid.x * tgrid.y);
             hipLaunchKernelGGL(relu_backward_kernel<false>, dim3((unsigned)(blocks + t_blocks)), dim3(BW_THREADS), 0, st, (const char*)dh_dev,

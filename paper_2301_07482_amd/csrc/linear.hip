@@ -340,6 +340,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4a __attribute__((aligned(4)));      // 16 bytes from an address that is a multiple of 4
 constexpr int X3_LIST = 8;                                  // tasks whose rows a wavefront lists ahead in LDS
 constexpr int X3_LIST_BYTES = PL_WAVES * X3_LIST * 32 * 4;  // the lists of a workgroup (twice that with src_ids)
 
@@ -366,12 +367,17 @@ __device__ __forceinline__ void split8(const float* v, u32x4& t1, u32x4& t2, u32
 // lie there are read from 16 bytes of zeros instead (a piece lies wholly inside or wholly outside the row's d_in values).
 __device__ __attribute__((aligned(16))) float x3_zero[4];
 
-template <int NB, bool RAGGED>
+// MASKED: the product of the backward pass, h_out[r, :] = (h_src[r, :] where agg[r, :] > 0) . W^T. Both operands lie by position (h_src: the
+// output gradient, agg: the layer's output, NULL for no activation) and a row's 2 * d_in values behind each other; W is the
+// layer's own [d_out x 2 * d_in] (k_real values a row, the rest of the walk is padding), read along its rows. Masking and transposing
+// here spares a launch and a trip of the operand through memory in front of every product: 6 k rows of 256 x 512 6.3 + 15.6 us, now 20;
+// 1 k rows 4.9 + 8.9, now 12.
+template <int NB, bool RAGGED, bool MASKED = false>
 __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32x3_panel_kernel(
     const char* __restrict__ h_src, int n_src, int64_t src_stride, const char* __restrict__ agg, int64_t agg_stride,
     const int32_t* __restrict__ rows, const int64_t* __restrict__ n_rows_dev, int64_t max_rows, int d_in, int d_out,
     const float* __restrict__ W, const float* __restrict__ bias, int relu, char* __restrict__ h_out, int n_out,
-    int64_t out_stride, int n_panels, int n_groups, int near_out, const int32_t* __restrict__ src_ids) {
+    int64_t out_stride, int n_panels, int n_groups, int near_out, const int32_t* __restrict__ src_ids, int k_real = 0) {
     constexpr int BNW = PL_BN * NB;
     extern __shared__ __attribute__((aligned(16))) u32x4 bfrag[];  // [3 terms][K / 8 groups of k][BNW columns]
     const int d_pad = RAGGED ? (d_in + KC - 1) / KC * KC : d_in;
@@ -399,6 +405,16 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32x3_panel_kernel(
     auto load_piece = [&](int q, Piece& P) {
         const int c4 = (q % (BNW / 4)) * 4, gi = q / (BNW / 4);
         const int k0 = 32 * (gi >> 2) + 16 * (gi & 1) + 8 * ((gi >> 1) & 1);
+        if constexpr (MASKED) {      // four rows of W (d_out is a multiple of 4: they exist together), eight values of each
+            const float* wp = W + (int64_t)(n0 + c4 < d_out ? n0 + c4 : 0) * k_real;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int k = k0 + 4 * (e & 1);
+                P.k_in[e] = k < k_real;      // k_real is a multiple of 4
+                P.w4[e] = *(const f32x4a*)(wp + (int64_t)(e >> 1) * k_real + (P.k_in[e] ? k : 0));
+            }
+            return;
+        }
         const float* wp = W + (n0 + c4 < d_out ? n0 + c4 : 0);      // d_out is a multiple of 4: the four columns exist together
 #pragma unroll
         for (int e = 0; e < 8; ++e) {     // walked k -> row of W: the second half starts at d_in; padding rows read row 0
@@ -415,7 +431,8 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32x3_panel_kernel(
         for (int cc = 0; cc < 4; ++cc) {
             float v[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = (in && P.k_in[e]) ? P.w4[e][cc] : 0.f;
+            for (int e = 0; e < 8; ++e)
+                v[e] = MASKED ? ((in && P.k_in[2 * cc + (e >> 2)]) ? P.w4[2 * cc + (e >> 2)][e & 3] : 0.f) : ((in && P.k_in[e]) ? P.w4[e][cc] : 0.f);
             u32x4 t1, t2, t3;
             split8(v, t1, t2, t3);
             bfrag[(0 * ngr + gi) * BNW + c4 + cc] = t1;
@@ -490,18 +507,28 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32x3_panel_kernel(
         if (rb0 != rb_first) fill_list(rb0);
         int32_t r = rowlist[l32], s = srclist[l32];
         const float* a_self = (const float*)(h_src + (r >= 0 ? (int64_t)s * src_stride : 0)) + 16 * half;
-        const float* a_agg = (const float*)(agg + (r >= 0 ? (rb0 * 32 + l32) * agg_stride : 0)) + 16 * half;
+        // (MASKED: the row of the mask; the gradient's own where there is none, and its values then count as positive)
+        const char* mask = agg ? agg : h_src;
+        const int64_t mask_stride = agg ? agg_stride : src_stride;
+        const unsigned int m_and = agg ? 0xFFFFFFFFu : 0u, m_or = agg ? 0u : 0x3F800000u;
+        const float* a_agg = (const float*)(MASKED ? mask + (r >= 0 ? (int64_t)r * mask_stride : 0) : agg + (r >= 0 ? (rb0 * 32 + l32) * agg_stride : 0)) + 16 * half;
         // the four 16-byte pieces of chunk `c` of one half of a row (base = that half's first value + 16 * half)
         auto load_chunk = [&](const float* base, int c, f32x4* a) {
             const float* p = base + c * KC;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const bool there = !RAGGED || c * KC + 16 * half + 4 * q < d_in;
-                a[q] = *(const f32x4*)(there ? p + 4 * q : (const float*)x3_zero);
+                if constexpr (MASKED) {
+                    const bool there = !RAGGED || c * KC + 16 * half + 4 * q < k_real;
+                    a[q] = *(const f32x4a*)(there ? p + 4 * q : (const float*)x3_zero);
+                } else {
+                    const bool there = !RAGGED || c * KC + 16 * half + 4 * q < d_in;
+                    a[q] = *(const f32x4*)(there ? p + 4 * q : (const float*)x3_zero);
+                }
             }
         };
-        f32x4 a0[4], a1[4];
+        f32x4 a0[4], a1[4], m0[MASKED ? 4 : 1], m1[MASKED ? 4 : 1];
         load_chunk(a_self, 0, a0);  // step 0 of the first task of the list
+        if constexpr (MASKED) load_chunk(a_agg, 0, m0);
         for (int tk = 0; tk < X3_LIST; ++tk) {
             const int64_t rb = rb0 + tk * stride;
             if (rb >= n_blocks) break;
@@ -520,10 +547,16 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32x3_panel_kernel(
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) big[nb][i] = small[nb][i] = 0.f;
-            auto compute = [&](int step, const f32x4* a) {
+            auto compute = [&](int step, const f32x4* a, const f32x4* m) {
                 float av[16];
 #pragma unroll
-                for (int q = 0; q < 16; ++q) av[q] = a[q >> 2][q & 3];
+                for (int q = 0; q < 16; ++q) {
+                    av[q] = a[q >> 2][q & 3];
+                    if constexpr (MASKED) {
+                        const float act = __uint_as_float((__float_as_uint(m[q >> 2][q & 3]) & m_and) | m_or);
+                        av[q] = act > 0.f ? av[q] : 0.f;
+                    }
+                }
                 u32x4 A[3][2];  // [term][m]
                 split8(av, A[0][0], A[1][0], A[2][0]);
                 split8(av + 8, A[0][1], A[1][1], A[2][1]);
@@ -554,12 +587,23 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32x3_panel_kernel(
             for (int step = 0; step < nk; step += 2) {
                 {
                     const int s1 = step + 1;
-                    const bool own = s1 < nk_self;
-                    load_chunk(own ? a_self : a_agg, own ? s1 : s1 - nk_self, a1);
+                    if constexpr (MASKED) {
+                        load_chunk(a_self, s1, a1);
+                        load_chunk(a_agg, s1, m1);
+                    } else {
+                        const bool own = s1 < nk_self;
+                        load_chunk(own ? a_self : a_agg, own ? s1 : s1 - nk_self, a1);
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                compute(step, a0);
-                {
+                compute(step, a0, m0);
+                if constexpr (MASKED) {      // past the last step: step 0 of the next task's row
+                    const int s2 = step + 2;
+                    const float* nxt = (const float*)(h_src + (r_next >= 0 ? (int64_t)s_next * src_stride : 0)) + 16 * half;
+                    const float* nxt_m = (const float*)(mask + (r_next >= 0 ? (int64_t)r_next * mask_stride : 0)) + 16 * half;
+                    load_chunk(s2 < nk ? a_self : nxt, s2 < nk ? s2 : 0, a0);
+                    load_chunk(s2 < nk ? a_agg : nxt_m, s2 < nk ? s2 : 0, m0);
+                } else {
                     const int s2 = step + 2;
                     const float* nxt = (const float*)(h_src + (r_next >= 0 ? (int64_t)s_next * src_stride : 0)) + 16 * half;
                     // past the last step: step 0 of the next task's own half
@@ -568,7 +612,7 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32x3_panel_kernel(
                     load_chunk(base, c, a0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                compute(step + 1, a1);
+                compute(step + 1, a1, m1);
             }
             // accumulator element i is row 8*(i/4) + 4*half + i%4 of the block, column l32 of its column block: the
             // destination rows of elements 4q .. 4q+3 are four consecutive entries of the list
@@ -622,7 +666,8 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32x3_panel_kernel(
             r = r_next;
             s = s_next;
             a_self = (const float*)(h_src + (r >= 0 ? (int64_t)s * src_stride : 0)) + 16 * half;
-            a_agg = (const float*)(agg + (r >= 0 ? ((rb + stride) * 32 + l32) * agg_stride : 0)) + 16 * half;
+            a_agg = (const float*)(MASKED ? mask + (r >= 0 ? (int64_t)r * mask_stride : 0)
+                                          : agg + (r >= 0 ? ((rb + stride) * 32 + l32) * agg_stride : 0)) + 16 * half;
         }
     }
 }
@@ -639,7 +684,8 @@ constexpr int SK_PART_BYTES = PL_WAVES * 16 * 64 * 8;  // partial sums: [wavefro
 
 // FUSE: the neighbour means are not read from `agg` but formed here from the block (fg_aggregate's arithmetic: fp64 sum
 // in neighbour order, one division, one rounding to fp32), so a layer with few rows needs one launch instead of two.
-template <bool FUSE>
+// MASKED: the product of the backward pass, as in the panel kernel (2 * d_in values a row, a multiple of 64).
+template <bool FUSE, bool MASKED = false>
 __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
     const char* __restrict__ h_src, int n_src, int64_t src_stride, const char* __restrict__ agg, int64_t agg_stride,
     const int32_t* __restrict__ rows, const int64_t* __restrict__ n_rows_dev, int64_t max_rows, int d_in, int d_out,
@@ -678,6 +724,12 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
     f32x4 w_piece[W_PIECES];
 #pragma unroll
     for (int u = 0; u < W_PIECES; ++u) {
+        if constexpr (MASKED) {      // four values of a row of W: column (lane + 64 u) % 32 of the panel
+            const int col = lane & 31, kq = (lane + 64 * u) >> 5, i = kq / (KC / 4);
+            const int kk = i < cnt ? chunk_of(i) * KC + kq % (KC / 4) * 4 : 0;
+            w_piece[u] = *(const f32x4a*)(W + (int64_t)(n0 + col < d_out ? n0 + col : 0) * K + kk);
+            continue;
+        }
         const int idx = (lane + 64 * u) >> 3, c4 = ((lane + 64 * u) & 7) * 4, i = idx / KC;
         const int kk = i < cnt ? chunk_of(i) * KC + idx % KC : 0;
         w_piece[u] = *(const f32x4*)(W + (int64_t)kk * d_out + (n0 + c4 < d_out ? n0 + c4 : 0));
@@ -694,7 +746,10 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
         if (s_own < 0) r = -1;
     }
     const float* a_self = (const float*)(h_src + (r >= 0 ? (int64_t)s_own * src_stride : 0)) + 16 * half;
-    const float* a_agg = (const float*)(agg + (r >= 0 ? g * agg_stride : 0)) + 16 * half;
+    const char* mask = agg ? agg : h_src;      // MASKED
+    const int64_t mask_stride = agg ? agg_stride : src_stride;
+    const unsigned int m_and = agg ? 0xFFFFFFFFu : 0u, m_or = agg ? 0u : 0x3F800000u;
+    const float* a_agg = (const float*)(MASKED ? mask + (r >= 0 ? (int64_t)r * mask_stride : 0) : agg + (r >= 0 ? g * agg_stride : 0)) + 16 * half;
     auto a_ptr = [&](int s) { return s < nk_self ? a_self + s * KC : a_agg + (s - nk_self) * KC; };
     // this lane's row of the block (FUSE): its sampled neighbours are col[e0 .. e1)
     int32_t e0 = 0, e1 = 0;
@@ -706,6 +761,20 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
     // the 16 values of chunk s this lane feeds to the matrix instructions
     constexpr int NBF = 5;  // neighbours whose pieces are in flight together (the seed layer's fan-out)
     auto load_chunk = [&](int s, f32x4* a) {
+        if constexpr (MASKED) {
+            f32x4 m[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                a[q] = *(const f32x4a*)(a_self + s * KC + 4 * q);
+                m[q] = *(const f32x4a*)(a_agg + s * KC + 4 * q);
+            }
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const float act = __uint_as_float((__float_as_uint(m[q >> 2][q & 3]) & m_and) | m_or);
+                a[q >> 2][q & 3] = act > 0.f ? a[q >> 2][q & 3] : 0.f;
+            }
+            return;
+        }
         if (!FUSE || s < nk_self) {
             const float* p = a_ptr(s);
 #pragma unroll
@@ -747,6 +816,13 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
     if (cnt > 1) load_chunk(chunk_of(1), a1);
 #pragma unroll
     for (int u = 0; u < W_PIECES; ++u) {
+        if constexpr (MASKED) {
+            const int col = lane & 31, kq = (lane + 64 * u) >> 5, i = kq / (KC / 4);
+            if (i < cnt)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) panel[(chunk_of(i) * KC + kq % (KC / 4) * 4 + e) * PL_BN + col] = n0 + col < d_out ? w_piece[u][e] : 0.f;
+            continue;
+        }
         const int idx = (lane + 64 * u) >> 3, c4 = ((lane + 64 * u) & 7) * 4, i = idx / KC;
         const f32x4 z = {0.f, 0.f, 0.f, 0.f};
         if (i < cnt) *(f32x4*)(panel + (chunk_of(i) * KC + idx % KC) * PL_BN + c4) = n0 + c4 < d_out ? w_piece[u] : z;
@@ -806,6 +882,50 @@ fg_status_t fg_launch_linear_bf16(const void* h_src, int32_t n_src, int64_t src_
                                   const int64_t* n_rows_dev, int64_t max_rows, int32_t d_in, int32_t d_out, const void* W,
                                   const float* bias, int32_t relu, void* h_out, int32_t n_out, int64_t out_stride,
                                   fg_dtype_t out_dtype, hipStream_t st, bool w_nk, const int32_t* src_ids_dev = nullptr);
+
+// dx[r, :] = (dh[r, :] where h[r, :] > 0) . W^T for r = rows[k], W [cols x d_out]: the product of the backward pass straight from its operands.
+// *done = false: a shape that these kernels do not take (the caller forms the masked operand and goes through fg_linear).
+fg_status_t fg_launch_linear_masked(const float* dh, int64_t dh_stride, const float* h, int64_t h_stride, int32_t n, const int32_t* rows_dev,
+                                    const int64_t* n_rows_dev, int64_t max_rows, int32_t d_out, int32_t cols, const float* W, float* dx, hipStream_t st, bool* done) {
+    const int64_t n_tasks = fg_ceil_div(max_rows, 32) * fg_ceil_div(cols, PL_BN);
+    const size_t panel_bytes = (size_t)d_out * PL_BN * sizeof(float);
+    const int k_pad = (int)(fg_ceil_div(d_out, 2 * KC) * 2 * KC);      // the loop over K takes two chunks at a time
+    const size_t x3_bytes = (size_t)k_pad * 192;
+    *done = true;
+    const int64_t out_stride = (int64_t)cols * 4;
+    if (d_out % (2 * KC) == 0 && panel_bytes <= 64 * 1024 && n_tasks <= 288) {      // (as fg_linear chooses)
+        const int n_panels = (int)fg_ceil_div(cols, PL_BN);
+        const size_t lds = panel_bytes > (size_t)SK_PART_BYTES ? panel_bytes : (size_t)SK_PART_BYTES;
+        const unsigned grid = (unsigned)(fg_ceil_div(fg_ceil_div(max_rows, 32), 8) * 8 * n_panels);
+        hipLaunchKernelGGL((linear_f32_splitk_kernel<false, true>), dim3(grid), dim3(PL_THREADS), lds, st, (const char*)dh, n, dh_stride,
+                           (const char*)h, h_stride, rows_dev, n_rows_dev, max_rows, d_out / 2, cols, W, nullptr, 0, (char*)dx, n, out_stride,
+                           n_panels, nullptr, nullptr, nullptr, (int64_t)0, 0, nullptr);
+        FG_LAUNCH_CHECK("linear_f32_splitk_kernel (masked)");
+        return FG_OK;
+    }
+    if (x3_bytes + X3_LIST_BYTES > 160 * 1024 || x3_bytes > 144 * 1024) {
+        *done = false;
+        return FG_OK;
+    }
+    const int nb = 2 * x3_bytes <= 144 * 1024 ? 2 : 1;
+    const size_t lds = x3_bytes * nb + X3_LIST_BYTES;
+    const int n_panels = (int)fg_ceil_div(cols, PL_BN * nb);
+    int q = 256 / (8 * n_panels);
+    if (q < 1) q = 1;
+    const int64_t blocks32 = fg_ceil_div(max_rows, 32);
+    while (q > 1 && (int64_t)8 * (q - 1) >= blocks32) --q;
+    const int n_groups = 8 * q;
+    const int near_out = ((int64_t)n * out_stride < (1ll << 31) && n < (1 << 24) && out_stride < (1 << 24)) ? 1 : 0;
+#define FG_X3M(NBV, RAG)                                                                                                                     hipLaunchKernelGGL((linear_f32x3_panel_kernel<NBV, RAG, true>), dim3((unsigned)(n_groups * n_panels)), dim3(PL_THREADS), lds, st,                             (const char*)dh, n, dh_stride, (const char*)h, h_stride, rows_dev, n_rows_dev, max_rows, k_pad / 2, cols, W, nullptr, 0,                        (char*)dx, n, out_stride, n_panels, n_groups, near_out, nullptr, d_out)
+    if (nb == 2) {
+        if (k_pad != d_out) FG_X3M(2, true); else FG_X3M(2, false);
+    } else {
+        if (k_pad != d_out) FG_X3M(1, true); else FG_X3M(1, false);
+    }
+#undef FG_X3M
+    FG_LAUNCH_CHECK("linear_f32x3_panel_kernel (masked)");
+    return FG_OK;
+}
 
 // fg_linear (src_ids_dev == NULL: the own features of position r are row r of h_src) and fg_linear_ids (row src_ids_dev[r])
 static fg_status_t linear_launch(const char* who, const void* h_src, int32_t n_src, int64_t src_stride, fg_dtype_t in_dtype,

@@ -1230,6 +1230,46 @@ def test_layer_backward_weights_match_oracle(env, d_in, d_out, n, n_rows, relu, 
     assert e <= REL_TOL_F32 and e_b <= REL_TOL_F32, f"rel err dW {e:.3e}, db {e_b:.3e}"
 
 
+@pytest.mark.parametrize("d_in,d_out,n,relu", [
+    (64, 64, 300, True), (64, 512, 200, True), (32, 576, 40, False),      # split over K; just beyond what it takes
+    (16, 8, 33, True), (40, 72, 700, True), (256, 256, 1500, True), (128, 384, 900, False), (24, 392, 65, True),      # panels of 64, then of 32 columns
+    (40, 768, 130, True), (40, 776, 130, True)])                           # the widest, and one that is masked by a launch of its own
+@pytest.mark.parametrize("apart", [0, 1])
+def test_layer_backward_reads_its_operands_in_place(env, d_in, d_out, n, relu, apart):
+    """The input gradient straight from dh, h and W, at the widths where its product changes kernels; `apart`: rows that are one float
+    apart and start one float into their memory, so that no 16-byte piece is aligned."""
+    torch, B = env
+    r = np.random.default_rng(d_out + n)
+    n_src = n + 90
+    blk = _random_pruned_block(r, n, n_src, 4)
+    dh = r.standard_normal((n, d_out)).astype(np.float32)
+    h = np.maximum(r.standard_normal((n, d_out)), 0).astype(np.float32)
+    W = (r.standard_normal((2 * d_in, d_out)) / np.sqrt(2 * d_in)).astype(np.float32)
+    dummy = np.zeros((len(blk["rows"]), d_in))
+    want, _, _ = O.layer_backward(blk["start"], blk["end"], blk["col"], blk["rows"], dh, h, dummy, dummy, W, n_src, relu=relu)
+
+    def shifted(a, gap):      # (address, bytes per row, the memory)
+        mem = torch.full((a.shape[0] * (a.shape[1] + gap) + gap,), float("nan"), device="cuda")
+        mem[gap:].view(a.shape[0], a.shape[1] + gap)[:, :a.shape[1]] = dev(torch, a)
+        return mem.data_ptr() + 4 * gap, 4 * (a.shape[1] + gap), mem
+
+    t = lambda a: dev(torch, a) if len(a) else torch.zeros(1, dtype=torch.int32, device="cuda")
+    (g, g_stride, m0), (a, a_stride, m1) = shifted(dh, apart), shifted(h, apart)
+    w_mem = torch.full((W.size + apart,), float("nan"), device="cuda")
+    w_mem[apart:] = dev(torch, W.reshape(-1))
+    rows = torch.zeros(n, dtype=torch.int32, device="cuda")
+    rows[:len(blk["rows"])] = dev(torch, blk["rows"])
+    cnt = dev(torch, np.asarray([len(blk["rows"])], dtype=np.int64))
+    out, norms = torch.full((n_src, d_in), 7.0, device="cuda"), torch.full((n_src,), -1.0, device="cuda")
+    wsb = B.fg_layer_backward_workspace_bytes(n, n, d_in, d_out)
+    ws = torch.full((wsb,), 255, dtype=torch.uint8, device="cuda")
+    B.fg_layer_backward(g, g_stride, a if relu else None, a_stride, n, rows, cnt, n, dev(torch, blk["live"].astype(np.uint8)),
+                        dev(torch, blk["hit"].astype(np.uint8)), dev(torch, blk["start"]), dev(torch, blk["end"]), dev(torch, blk["ts"]),
+                        dev(torch, blk["te"]), t(blk["tr"]), len(blk["tr"]), n_src, d_in, d_out, w_mem.data_ptr() + 4 * apart, out, d_in * 4, norms, ws, wsb)
+    e = T.rel_err_rows(out.cpu().numpy(), want)
+    assert e <= REL_TOL_F32, f"rel err {e:.3e}"
+
+
 @pytest.mark.parametrize("kind,layers", [
     ("f32", [(128, 256, 30000, 29001, True), (256, 256, 3000, 2999, True), (256, 64, 300, 250, False)]),       # both tiles, many chunks and few
     ("f32", [(24, 72, 130, 77, True), (72, 8, 40, 0, False)]), ("f32", [(8, 8, 9, 1, False)]),                # one chunk each; an empty layer
