@@ -764,6 +764,84 @@ size_t fg_backward_weights_all_workspace_bytes(fg_dtype_t compute_dtype, int32_t
 fg_status_t fg_backward_weights_all(fg_dtype_t compute_dtype, int32_t n_layers, const fg_weight_grad_layer_t* layers, void* ws_dev,
                                     size_t ws_bytes, void* stream);
 
+/*
+ * ---- One iteration in one call ----
+ * fg_path_run queues the launches of one iteration on call->stream (and P->side) in the order a training loop makes the calls above:
+ * the row copy that is still due, top-down pass, fetch, loader, layers, loss and backward pass, weight gradients, cache update. The
+ * results are those of the single calls. It keeps nothing between calls: what an iteration leaves to the next is in *call.
+ *
+ * fg_path_t: the model's buffers. Arrays are indexed by layer (entry 0 = input layer where a layer 0 exists). lists: what the top-down
+ * pass writes, three sets (iteration it uses it % 3); the logs are rings of `ring` iterations: counts [ring][layers + 1][3], stats
+ * [ring][layers + 1][4], input [ring][3] (the counts of the input layer where fused_input is set). ws_update: two halves,
+ * ws_update_stride bytes apart. ev_*, side: hipEvent_t and hipStream_t of the caller (side may be NULL where call->overlap is 0).
+ * agg, mean_pos: one buffer per layer, which may be one and the same where weight_grads is 0.
+ * fg_path_batch_t: a mini-batch, the arguments of the calls above; n_dev as in fg_top_down; gnorm_dev of layers 1 .. L-1 without
+ * backward; labels_dev and the transposes of layers 2 .. L with it; col_ids1_dev: block 1's columns as node ids, or NULL.
+ * `next` (or NULL): the mini-batch of iteration iter + 1, whose top-down pass may then run beside this iteration.
+ */
+#define FG_PATH_MAX_LAYERS 8
+typedef enum { FG_PATH_SAGE = 0, FG_PATH_GCN = 1 } fg_path_model_t;
+typedef struct fg_path_lists {
+    uint8_t *live[FG_PATH_MAX_LAYERS + 1], *hit[FG_PATH_MAX_LAYERS + 1];
+    int32_t *hit_pos[FG_PATH_MAX_LAYERS + 1], *hit_slot[FG_PATH_MAX_LAYERS + 1], *normal_pos[FG_PATH_MAX_LAYERS + 1];
+    int32_t *input_ids, *self_ids;
+} fg_path_lists_t;
+typedef struct fg_path {
+    int32_t n_layers, model, feat_dtype, compute_dtype, on_host, fused_input, fuse_small_layers, backward, weight_grads, ring;
+    int64_t num_nodes;
+    int32_t dims[FG_PATH_MAX_LAYERS + 1], n_max[FG_PATH_MAX_LAYERS + 1];
+    void *h[FG_PATH_MAX_LAYERS + 1], *agg[FG_PATH_MAX_LAYERS + 1];
+    float *mean_pos[FG_PATH_MAX_LAYERS + 1], *dh[FG_PATH_MAX_LAYERS + 1], *gnorm[FG_PATH_MAX_LAYERS + 1], *dw[FG_PATH_MAX_LAYERS + 1],
+        *db[FG_PATH_MAX_LAYERS + 1];
+    fg_path_lists_t lists[3];
+    int64_t *counts_log, *stats_log, *input_log;
+    void *ws_top_down, *ws_update, *ws_backward, *ws_weights;
+    size_t ws_top_down_bytes, ws_update_bytes, ws_update_stride, ws_backward_bytes, ws_weights_bytes;
+    void *side, *ev_pruned, *ev_selected, *ev_next_pruned, *ev_done[2], *ev_gradients, *ev_weights;
+} fg_path_t;
+typedef struct fg_path_layer {
+    int64_t n, nnz;
+    const int32_t *ids_dev, *start_dev;
+    int32_t* end_dev;
+    const int32_t* col_dev;
+    const int64_t* n_dev;
+    const int32_t *t_start_dev, *t_end_dev, *t_row_dev;
+    const float* gnorm_dev;
+} fg_path_layer_t;
+typedef struct fg_path_batch {
+    const int32_t *labels_dev, *col_ids1_dev;
+    int64_t reads_rows_once;      /* fused_input: the input rows are gathered into h[0] once each, layer 1 aggregates from there */
+    int64_t own_rows_from_table;  /* fused_input, col_ids1_dev: layer 1's dense update reads the own rows by fg_linear_ids */
+    fg_path_layer_t layer[FG_PATH_MAX_LAYERS + 1];
+} fg_path_batch_t;
+typedef struct fg_path_call {
+    int64_t iter;
+    void* stream;
+    fg_cache_t* cache;    /* NULL = without a cache */
+    const void* feat;     /* the feature table, rows of dims[0] values */
+    const void *w[FG_PATH_MAX_LAYERS + 1], *wt[FG_PATH_MAX_LAYERS + 1]; /* wt[l]: the weights as fg_linear_wt takes them, or NULL */
+    const float* bias[FG_PATH_MAX_LAYERS + 1];
+    float p_grad;
+    int32_t update;            /* update the cache at the end */
+    int32_t overlap;           /* selection or weight gradients on P->side */
+    int32_t fetch_with_loader; /* the cached rows ride in the id-column loader's launch */
+    int32_t ahead;             /* the weight gradients of layers 2 .. L go to P->side before layer 2's backward pass */
+    int32_t promised;          /* the previous call ran a top-down pass ahead ... */
+    int32_t pruned_ahead;      /* ... and it was this mini-batch's, for this iteration */
+    const fg_update_layer_t* due; /* the selection whose rows are still to be copied (layers - 1 entries, iteration due_iter), or NULL */
+    int64_t due_iter;
+    fg_update_layer_t* specs;     /* out: this iteration's selection (may be the array `due`) */
+    int32_t selected;             /* out: 1 = its row copy is left to the next call (`due`) or to fg_cache_update_commit */
+    int32_t next_pruned;          /* out: 1 = the top-down pass of `next` is queued (`promised`) */
+} fg_path_call_t;
+fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t* batch, const fg_path_batch_t* next, fg_path_call_t* call);
+
+/* Events without timing, for fg_path_t and for callers that order two streams by themselves. */
+fg_status_t fg_event_create(void** event);
+fg_status_t fg_event_record(void* event, void* stream);
+fg_status_t fg_stream_wait_event(void* stream, void* event);
+fg_status_t fg_event_destroy(void* event);
+
 #ifdef __cplusplus
 }
 #endif

@@ -130,6 +130,54 @@ SIGNATURES["fg_sample_minibatch"] = (_i32, [_p, _p, _i64, _i64, _p, _p, _i32, C.
 SIGNATURES["fg_cache_fetch_all"] = (_i32, [_p, _i32, C.POINTER(FetchLayer), _p])
 SIGNATURES["fg_cache_update_all"] = (_i32, [_p, _i64, _f, _i32, C.POINTER(UpdateLayer), _p, _sz, _p])
 SIGNATURES["fg_cache_update_select"] = (_i32, [_p, _i64, _f, _i32, C.POINTER(UpdateLayer), _p, _sz, _p])
+
+
+FG_PATH_MAX_LAYERS = 8
+FG_PATH_SAGE, FG_PATH_GCN = 0, 1
+_per_layer = _p * (FG_PATH_MAX_LAYERS + 1)
+
+
+class PathLists(C.Structure):
+    """fg_path_lists_t"""
+    _fields_ = [("live", _per_layer), ("hit", _per_layer), ("hit_pos", _per_layer), ("hit_slot", _per_layer), ("normal_pos", _per_layer),
+                ("input_ids", _p), ("self_ids", _p)]
+
+
+class Path(C.Structure):
+    """fg_path_t"""
+    _fields_ = [(k, _i32) for k in ("n_layers", "model", "feat_dtype", "compute_dtype", "on_host", "fused_input", "fuse_small_layers", "backward",
+                                    "weight_grads", "ring")] \
+        + [("num_nodes", _i64), ("dims", _i32 * (FG_PATH_MAX_LAYERS + 1)), ("n_max", _i32 * (FG_PATH_MAX_LAYERS + 1))] \
+        + [(k, _per_layer) for k in ("h", "agg", "mean_pos", "dh", "gnorm", "dw", "db")] + [("lists", PathLists * 3)] \
+        + [(k, _p) for k in ("counts_log", "stats_log", "input_log", "ws_top_down", "ws_update", "ws_backward", "ws_weights")] \
+        + [(k, _sz) for k in ("ws_top_down_bytes", "ws_update_bytes", "ws_update_stride", "ws_backward_bytes", "ws_weights_bytes")] \
+        + [("side", _p), ("ev_pruned", _p), ("ev_selected", _p), ("ev_next_pruned", _p), ("ev_done", _p * 2), ("ev_gradients", _p), ("ev_weights", _p)]
+
+
+class PathLayer(C.Structure):
+    """fg_path_layer_t"""
+    _fields_ = [("n", _i64), ("nnz", _i64)] + [(k, _p) for k in ("ids_dev", "start_dev", "end_dev", "col_dev", "n_dev", "t_start_dev", "t_end_dev",
+                                                               "t_row_dev", "gnorm_dev")]
+
+
+class PathBatch(C.Structure):
+    """fg_path_batch_t"""
+    _fields_ = [("labels_dev", _p), ("col_ids1_dev", _p), ("reads_rows_once", _i64), ("own_rows_from_table", _i64),
+                ("layer", PathLayer * (FG_PATH_MAX_LAYERS + 1))]
+
+
+class PathCall(C.Structure):
+    """fg_path_call_t"""
+    _fields_ = [("iter", _i64), ("stream", _p), ("cache", _p), ("feat", _p), ("w", _per_layer), ("wt", _per_layer), ("bias", _per_layer),
+                ("p_grad", _f)] + [(k, _i32) for k in ("update", "overlap", "fetch_with_loader", "ahead", "promised", "pruned_ahead")] \
+        + [("due", C.POINTER(UpdateLayer)), ("due_iter", _i64), ("specs", C.POINTER(UpdateLayer)), ("selected", _i32), ("next_pruned", _i32)]
+
+
+SIGNATURES["fg_path_run"] = (_i32, [C.POINTER(Path), C.POINTER(PathBatch), C.POINTER(PathBatch), C.POINTER(PathCall)])
+SIGNATURES["fg_event_create"] = (_i32, [C.POINTER(_p)])
+SIGNATURES["fg_event_record"] = (_i32, [_p, _p])
+SIGNATURES["fg_stream_wait_event"] = (_i32, [_p, _p])
+SIGNATURES["fg_event_destroy"] = (_i32, [_p])
 SIGNATURES["fg_cache_update_commit"] = (_i32, [_p, _i64, _i32, C.POINTER(UpdateLayer), _p, _sz, _p])
 
 for _name, (_res, _args) in SIGNATURES.items():
@@ -511,3 +559,25 @@ def fg_cache_update_select(cache, it, p_grad, layers, ws, ws_bytes, stream=None)
 
 def fg_cache_update_commit(cache, it, layers, ws, ws_bytes, stream=None):
     _check(_lib.fg_cache_update_commit(cache, it, len(layers), layers, ptr(ws), ws_bytes, stream))
+
+
+def fg_path_run(path, batch, next_batch, call):
+    _check(_lib.fg_path_run(path, batch, next_batch, call))
+
+
+def fg_event_create():
+    handle = _p()
+    _check(_lib.fg_event_create(C.byref(handle)))
+    return handle.value
+
+
+def fg_event_record(event, stream):
+    _check(_lib.fg_event_record(event, stream))
+
+
+def fg_stream_wait_event(stream, event):
+    _check(_lib.fg_stream_wait_event(stream, event))
+
+
+def fg_event_destroy(event):
+    _check(_lib.fg_event_destroy(event))

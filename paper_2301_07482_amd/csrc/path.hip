@@ -1,0 +1,319 @@
+// fg_path_run: one iteration of the hot path, the sequence of the library's calls that a training loop makes per mini-batch, queued
+// from one call. Nothing here computes: it fills in what the calls take and orders two streams by events.
+//
+// A small iteration is bound by the host that queues it: from Python, a foreign call with 20 to 30 arguments per launch took 66 us for
+// an iteration of the smallest workload whose launches keep the GPU busy for 50. Queued from here the host needs 40 (10 k nodes, 256
+// seeds x 10 x 5: step 57 -> 50 us, training iteration 90 -> 78, both what the GPU needs).
+#include "common.h"
+
+namespace {
+
+#define FG_TRY(call)                  \
+    do {                              \
+        fg_status_t rc_ = (call);     \
+        if (rc_ != FG_OK) return rc_; \
+    } while (0)
+
+// an iteration's view of the model's buffers
+struct Iter {
+    const fg_path_t& P;
+    const fg_path_call_t& C;
+    const fg_path_lists_t& S;
+    int64_t* counts;      // [layers + 1][3]
+    int64_t* stats;       // [layers + 1][4]
+    int64_t* input_counts;
+    int64_t it;
+
+    Iter(const fg_path_t& p, const fg_path_call_t& c, int64_t iter)
+        : P(p), C(c), S(p.lists[iter % 3]), counts(p.counts_log + iter % p.ring * (p.n_layers + 1) * 3), stats(p.stats_log + iter % p.ring * (p.n_layers + 1) * 4),
+          input_counts(p.input_log + iter % p.ring * 3), it(iter) {}
+
+    int esz(int code) const { return code == FG_F32 ? 4 : 2; }
+    int h_code(int l) const { return l == 0 ? P.feat_dtype : (l < P.n_layers ? P.compute_dtype : (int)FG_F32); }
+    int64_t row_bytes(int l) const { return (int64_t)P.dims[l] * esz(h_code(l)); }
+    int agg_code() const { return P.compute_dtype == FG_F32 ? FG_F32 : FG_BF16; }
+    bool cached() const { return C.cache && P.n_layers > 1; }
+    bool gcn() const { return P.model == FG_PATH_GCN; }
+    // fg_aggregate_linear runs the layer as one launch (its rule)
+    bool one_launch(int l, int64_t n) const {
+        return P.fuse_small_layers && l >= 2 && P.dims[l - 1] % 32 == 0 && P.dims[l - 1] <= 256 && fg_ceil_div(n, 32) * fg_ceil_div(P.dims[l], 32) <= 768;
+    }
+    // lookup, prune, V_normal for layers L .. 0 (or 1 with the fused loader)
+    fg_status_t top_down(const fg_path_batch_t& b, void* stream) const {
+        const int L = P.n_layers;
+        const bool fused = P.fused_input && !b.reads_rows_once;
+        fg_top_down_layer_t y[FG_PATH_MAX_LAYERS + 1] = {};
+        int count = 0;
+        for (int l = L; l >= (fused ? 1 : 0); --l, ++count) {
+            fg_top_down_layer_t& t = y[count];
+            const fg_path_layer_t& B = b.layer[l];
+            t.cache_layer = cached() && l >= 1 && l < L ? l : 0;
+            t.ids_dev = B.ids_dev;
+            t.n = (int32_t)B.n;
+            t.live_dev = l == L ? nullptr : S.live[l];
+            if (l >= 1) {
+                t.row_start_dev = B.start_dev;
+                t.row_end_dev = B.end_dev;
+                t.col_dev = B.col_dev;
+                t.nnz = B.nnz;
+                t.n_src = (int32_t)b.layer[l - 1].n;
+                t.live_src_dev = fused && l == 1 ? nullptr : S.live[l - 1];
+            }
+            t.hit_dev = S.hit[l];
+            t.hit_pos_dev = S.hit_pos[l];
+            t.hit_slot_dev = S.hit_slot[l];
+            t.normal_pos_dev = S.normal_pos[l];
+            t.normal_ids_dev = l == 0 ? S.input_ids : (fused && l == 1 ? S.self_ids : nullptr);
+            t.counts_dev = l || !P.fused_input ? counts + 3 * l : input_counts;
+            t.n_dev = B.n_dev;
+        }
+        return fg_top_down(C.cache, it, count, y, P.ws_top_down, P.ws_top_down_bytes, stream);
+    }
+
+    void update_specs(const fg_path_batch_t& b, bool own_norms, fg_update_layer_t* y) const {
+        for (int l = 1; l < P.n_layers; ++l) {
+            fg_update_layer_t& u = y[l - 1];
+            u = fg_update_layer_t{};
+            u.layer = l;
+            u.n = (int32_t)b.layer[l].n;
+            u.ids_dev = b.layer[l].ids_dev;
+            u.live_dev = S.live[l];
+            u.hit_dev = S.hit[l];
+            u.gnorm_dev = own_norms ? P.gnorm[l] : b.layer[l].gnorm_dev;
+            u.h_dev = P.h[l];
+            u.h_stride = row_bytes(l);
+            u.stats_dev = stats + 4 * l;
+            u.n_dev = b.layer[l].n_dev;
+        }
+    }
+    void* ws_update() const { return (char*)P.ws_update + it % 2 * P.ws_update_stride; }
+
+    fg_status_t weight_grads(const fg_path_batch_t& b, int first, int last, void* stream) const {
+        fg_weight_grad_layer_t y[FG_PATH_MAX_LAYERS] = {};
+        for (int l = first; l <= last; ++l) {
+            fg_weight_grad_layer_t& w = y[l - first];
+            // (a GCN layer's input rows are the propagated rows: by-position half, then list-order half)
+            const int width = gcn() ? P.dims[l - 1] / 2 : P.dims[l - 1], code = gcn() ? (int)FG_F32 : h_code(l - 1);
+            w.h_src_dev = gcn() ? P.mean_pos[l] : P.h[l - 1];
+            w.src_stride = (int64_t)width * esz(code);
+            w.src_dtype = (fg_dtype_t)code;
+            w.n_src = (int32_t)(gcn() ? b.layer[l].n : b.layer[l - 1].n);
+            w.agg_dev = P.agg[l];
+            w.agg_stride = (int64_t)width * esz(agg_code());
+            w.dh_dev = P.dh[l];
+            w.dh_stride = (int64_t)P.dims[l] * 4;
+            if (l < P.n_layers) {
+                w.h_dev = P.h[l];
+                w.h_stride = row_bytes(l);
+            }
+            w.rows_dev = S.normal_pos[l];
+            w.n_rows_dev = counts + 3 * l + 2;
+            w.max_rows = b.layer[l].n;
+            w.n = (int32_t)b.layer[l].n;
+            w.dw_dev = P.dw[l];
+            w.db_dev = P.db[l];
+            w.d_in = width;
+            w.d_out = P.dims[l];
+        }
+        return fg_backward_weights_all((fg_dtype_t)P.compute_dtype, last - first + 1, y, P.ws_weights, P.ws_weights_bytes, stream);
+    }
+
+    fg_status_t forward(const fg_path_batch_t& b, bool once, const fg_fetch_layer_t* fetch, int n_fetch) const {
+        const int L = P.n_layers;
+        const bool fused = P.fused_input && !once;
+        void* st = C.stream;
+        const int64_t d0b = row_bytes(0);
+        if (!fused)
+            FG_TRY(fg_gather(C.feat, P.num_nodes, d0b, d0b, S.input_ids, S.normal_pos[0], (once ? input_counts : counts) + 2, b.layer[0].n, P.h[0],
+                             b.layer[0].n, d0b, P.on_host, st));
+        for (int l = 1; l <= L; ++l) {
+            const fg_path_layer_t& B = b.layer[l];
+            const int32_t n = (int32_t)B.n, n_in = (int32_t)b.layer[l - 1].n;
+            const int in_code = h_code(l - 1), out_code = h_code(l), relu = l < L ? 1 : 0;
+            const int64_t in_b = row_bytes(l - 1), out_b = row_bytes(l), agg_b = (int64_t)P.dims[l - 1] * esz(agg_code()), *n_normal = counts + 3 * l + 2;
+            if (gcn()) {
+                const int half = P.dims[l - 1] / 2;
+                if (fused && l == 1)
+                    FG_TRY(fg_gather_aggregate_gcn(B.start_dev, B.end_dev, B.col_dev, B.nnz, n, S.normal_pos[1], n_normal, n, b.layer[0].ids_dev, n_in,
+                                                   (const float*)C.feat, P.num_nodes, d0b, P.dims[0], P.mean_pos[1], (float*)P.agg[1], st));
+                else
+                    FG_TRY(fg_aggregate_gcn(B.start_dev, B.end_dev, B.col_dev, B.nnz, n, S.normal_pos[l], n_normal, n, (const float*)P.h[l - 1], n_in, in_b,
+                                            P.dims[l - 1], P.mean_pos[l], (float*)P.agg[l], st));
+                FG_TRY(fg_linear(P.mean_pos[l], n, half * 4, FG_F32, P.agg[l], half * 4, S.normal_pos[l], n_normal, n, half, P.dims[l], C.w[l], FG_F32,
+                                 C.bias[l], relu, P.h[l], n, out_b, (fg_dtype_t)out_code, st));
+                continue;
+            }
+            if (one_launch(l, B.n)) {
+                FG_TRY(fg_aggregate_linear(B.start_dev, B.end_dev, B.col_dev, B.nnz, n, S.normal_pos[l], n_normal, n, (const float*)P.h[l - 1], n_in, in_b,
+                                           P.dims[l - 1], P.dims[l], (const float*)C.w[l], C.bias[l], relu, nullptr, agg_b, (float*)P.h[l], n, out_b, st));
+                continue;
+            }
+            const bool own_rows = l == 1 && fused && b.own_rows_from_table;
+            if (fused && l == 1) {
+                if (b.col_ids1_dev)
+                    FG_TRY(fg_gather_aggregate_ids(B.start_dev, B.end_dev, b.col_ids1_dev, B.nnz, n, S.normal_pos[1], n_normal, n, B.ids_dev, C.feat, P.num_nodes, d0b,
+                                                   P.dims[0], (fg_dtype_t)in_code, P.agg[1], agg_b, (fg_dtype_t)agg_code(), own_rows ? nullptr : P.h[0], d0b, n_in,
+                                                   n_fetch ? C.cache : nullptr, n_fetch, n_fetch ? fetch : nullptr, st));
+                else
+                    FG_TRY(fg_gather_aggregate(B.start_dev, B.end_dev, B.col_dev, B.nnz, n, S.normal_pos[1], n_normal, n, b.layer[0].ids_dev, n_in, C.feat,
+                                               P.num_nodes, d0b, P.dims[0], (fg_dtype_t)in_code, P.agg[1], agg_b, (fg_dtype_t)agg_code(), P.h[0], d0b, n_in, st));
+            } else {
+                FG_TRY(fg_aggregate(B.start_dev, B.end_dev, B.col_dev, B.nnz, n, S.normal_pos[l], n_normal, n, P.h[l - 1], n_in, in_b, P.dims[l - 1],
+                                    (fg_dtype_t)in_code, P.agg[l], agg_b, (fg_dtype_t)agg_code(), st));
+            }
+            if (own_rows) {
+                FG_TRY(fg_linear_ids(C.feat, (int32_t)P.num_nodes, in_b, (fg_dtype_t)in_code, B.ids_dev, P.agg[1], agg_b, S.normal_pos[1], n_normal, n, P.dims[0],
+                                     P.dims[1], C.w[1], (fg_dtype_t)P.compute_dtype, C.bias[1], L > 1 ? 1 : 0, P.h[1], n, out_b, (fg_dtype_t)out_code, st));
+                continue;
+            }
+            FG_TRY((C.wt[l] ? fg_linear_wt : fg_linear)(P.h[l - 1], n_in, in_b, (fg_dtype_t)in_code, P.agg[l], agg_b, S.normal_pos[l], n_normal, n, P.dims[l - 1],
+                                                        P.dims[l], C.wt[l] ? C.wt[l] : C.w[l], (fg_dtype_t)P.compute_dtype, C.bias[l], relu, P.h[l], n, out_b,
+                                                        (fg_dtype_t)out_code, st));
+        }
+        return FG_OK;
+    }
+
+    // the embedding gradients and their norms; weight gradients on the second stream (`beside`) or here
+    fg_status_t backward(const fg_path_batch_t& b, bool beside) const {
+        const int L = P.n_layers;
+        void* st = C.stream;
+        auto weights_beside = [&](int first, int last) -> fg_status_t {
+            FG_HIP(hipEventRecord((hipEvent_t)P.ev_gradients, (hipStream_t)st));
+            FG_HIP(hipStreamWaitEvent((hipStream_t)P.side, (hipEvent_t)P.ev_gradients, 0));
+            return weight_grads(b, first, last, P.side);
+        };
+        const bool ahead = beside && C.ahead && L > 1;
+        FG_TRY(fg_softmax_xent_grad((const float*)P.h[L], (int64_t)P.dims[L] * 4, b.labels_dev, (int32_t)b.layer[L].n, P.dims[L], P.dh[L], (int64_t)P.dims[L] * 4, st));
+        const auto layer_backward = gcn() ? fg_layer_backward_gcn : fg_layer_backward;
+        for (int l = L; l > 1; --l) {
+            if (l == 2 && ahead) FG_TRY(weights_beside(2, L));
+            const fg_path_layer_t& B = b.layer[l];
+            const int32_t n = (int32_t)B.n, n_in = (int32_t)b.layer[l - 1].n;
+            const void* h = l < L ? P.h[l] : nullptr;
+            const int64_t h_stride = (int64_t)P.dims[l] * esz(h_code(l)), *n_normal = counts + 3 * l + 2;
+            const uint8_t* live = l < L ? S.live[l] : nullptr;
+            const int64_t dh_b = (int64_t)P.dims[l] * 4, dh_in_b = (int64_t)P.dims[l - 1] * 4;
+            if (!gcn() && P.compute_dtype == FG_BF16)
+                FG_TRY(fg_layer_backward_bf16(P.dh[l], dh_b, h, h_stride, n, S.normal_pos[l], n_normal, n, live, S.hit[l], B.start_dev, B.end_dev, B.t_start_dev,
+                                              B.t_end_dev, B.t_row_dev, B.nnz, n_in, P.dims[l - 1], P.dims[l], C.w[l], P.dh[l - 1], dh_in_b, P.gnorm[l - 1],
+                                              P.ws_backward, P.ws_backward_bytes, st));
+            else
+                FG_TRY(layer_backward(P.dh[l], dh_b, (const float*)h, h_stride, n, S.normal_pos[l], n_normal, n, live, S.hit[l], B.start_dev, B.end_dev, B.t_start_dev,
+                                      B.t_end_dev, B.t_row_dev, B.nnz, n_in, P.dims[l - 1], P.dims[l], (const float*)C.w[l], P.dh[l - 1], dh_in_b, P.gnorm[l - 1],
+                                      P.ws_backward, P.ws_backward_bytes, st));
+        }
+        if (!P.weight_grads) return FG_OK;
+        return beside ? weights_beside(1, ahead ? 1 : L) : weight_grads(b, 1, L, st);
+    }
+};
+
+fg_status_t check_batch(const fg_path_t& P, const fg_path_batch_t& b) {
+    for (int l = 0; l <= P.n_layers; ++l)
+        if (b.layer[l].n < 0 || b.layer[l].n > P.n_max[l] || b.layer[l].nnz < 0)
+            FG_FAIL(FG_ERR_SHAPE, "fg_path_run: layer %d has %lld positions (%lld edges), its lists hold %d", l, (long long)b.layer[l].n, (long long)b.layer[l].nnz, P.n_max[l]);
+    return FG_OK;
+}
+
+}  // namespace
+
+extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t* batch, const fg_path_batch_t* next, fg_path_call_t* call) {
+    if (!path || !batch || !call) FG_FAIL(FG_ERR_INVALID_ARG, "fg_path_run: NULL pointer");
+    call->selected = call->next_pruned = 0;
+    const fg_path_t& P = *path;
+    if (P.n_layers < 1 || P.n_layers > FG_PATH_MAX_LAYERS || P.ring < 1) FG_FAIL(FG_ERR_INVALID_ARG, "fg_path_run: n_layers = %d must be in 1..%d", P.n_layers, FG_PATH_MAX_LAYERS);
+    if (call->iter < 0) FG_FAIL(FG_ERR_INVALID_ARG, "fg_path_run: iteration %lld is negative", (long long)call->iter);
+    FG_TRY(check_batch(P, *batch));
+    if (next) FG_TRY(check_batch(P, *next));
+    const Iter I(P, *call, call->iter);
+    const int L = P.n_layers;
+    const hipStream_t main = (hipStream_t)call->stream, side = (hipStream_t)P.side;
+    const bool do_update = call->update && I.cached();
+    if (call->promised) FG_HIP(hipStreamWaitEvent(main, (hipEvent_t)P.ev_next_pruned, 0));      // behind the previous selection on that stream
+    auto commit = [&](int64_t iter, int n, const fg_update_layer_t* y) -> fg_status_t {
+        FG_TRY(fg_cache_update_commit(call->cache, iter, n, y, (char*)P.ws_update + iter % 2 * P.ws_update_stride, P.ws_update_bytes, main));
+        FG_HIP(hipEventRecord((hipEvent_t)P.ev_done[iter % 2], main));
+        return FG_OK;
+    };
+    if (call->due) {      // the rows the previous iteration admitted
+        if (!call->promised) FG_HIP(hipStreamWaitEvent(main, (hipEvent_t)P.ev_selected, 0));
+        FG_TRY(commit(call->due_iter, L - 1, call->due));
+    }
+    if (!call->pruned_ahead) FG_TRY(I.top_down(*batch, main));
+    const bool beside = do_update && call->overlap && !P.backward;
+    if (beside) {      // the update's selection and the next top-down pass on the second stream
+        if (!call->pruned_ahead) {
+            FG_HIP(hipEventRecord((hipEvent_t)P.ev_pruned, main));
+            FG_HIP(hipStreamWaitEvent(side, (hipEvent_t)P.ev_pruned, 0));
+        }
+        // what it overwrites was last read by iteration it - 2 and its row copy, which recorded this event
+        FG_HIP(hipStreamWaitEvent(side, (hipEvent_t)P.ev_done[call->iter % 2], 0));
+        I.update_specs(*batch, false, call->specs);
+        FG_TRY(fg_cache_update_select(call->cache, call->iter, call->p_grad, L - 1, call->specs, I.ws_update(), P.ws_update_bytes, side));
+        FG_HIP(hipEventRecord((hipEvent_t)P.ev_selected, side));
+        call->selected = 1;
+        if (next) {
+            const Iter N(P, *call, call->iter + 1);
+            FG_TRY(N.top_down(*next, side));
+            FG_HIP(hipEventRecord((hipEvent_t)P.ev_next_pruned, side));
+            call->next_pruned = 1;
+        }
+    }
+    fg_fetch_layer_t fetch[FG_PATH_MAX_LAYERS] = {};
+    const bool once = batch->reads_rows_once != 0, fused = P.fused_input && !once;
+    int n_fetch = 0;
+    if (I.cached()) {
+        for (int l = 1; l < L; ++l) {
+            fg_fetch_layer_t& f = fetch[n_fetch++];
+            f.layer = l;
+            f.hit_slot_dev = I.S.hit_slot[l];
+            f.hit_pos_dev = I.S.hit_pos[l];
+            f.n_hit_dev = I.counts + 3 * l + 1;
+            f.max_hits = f.h_rows = batch->layer[l].n;
+            f.h_dev = P.h[l];
+            f.h_stride = I.row_bytes(l);
+        }
+        if (!(call->fetch_with_loader && fused && !I.gcn() && batch->col_ids1_dev)) {      // else the id-column loader takes the fetch along
+            FG_TRY(fg_cache_fetch_all(call->cache, n_fetch, fetch, main));
+            n_fetch = 0;
+        }
+    }
+    FG_TRY(I.forward(*batch, once, fetch, n_fetch));
+    const bool weights_beside = P.backward && P.weight_grads && call->overlap;
+    if (P.backward) FG_TRY(I.backward(*batch, weights_beside));
+    if (call->selected) {      // only the admitted rows are left to copy: by the next call, if its top-down pass is on the second stream
+        if (!call->next_pruned) {
+            FG_HIP(hipStreamWaitEvent(main, (hipEvent_t)P.ev_selected, 0));
+            FG_TRY(commit(call->iter, L - 1, call->specs));
+            call->selected = 0;
+        }
+    } else if (do_update) {
+        I.update_specs(*batch, P.backward != 0, call->specs);
+        FG_TRY(fg_cache_update_all(call->cache, call->iter, call->p_grad, L - 1, call->specs, I.ws_update(), P.ws_update_bytes, main));
+    }
+    if (weights_beside) {      // the next iteration overwrites what the weight gradients read
+        FG_HIP(hipEventRecord((hipEvent_t)P.ev_weights, side));
+        FG_HIP(hipStreamWaitEvent(main, (hipEvent_t)P.ev_weights, 0));
+    }
+    return FG_OK;
+}
+
+extern "C" fg_status_t fg_event_create(void** event) {
+    if (!event) FG_FAIL(FG_ERR_INVALID_ARG, "fg_event_create: NULL pointer");
+    FG_HIP(hipEventCreateWithFlags((hipEvent_t*)event, hipEventDisableTiming));
+    return FG_OK;
+}
+
+extern "C" fg_status_t fg_event_record(void* event, void* stream) {
+    FG_HIP(hipEventRecord((hipEvent_t)event, (hipStream_t)stream));
+    return FG_OK;
+}
+
+extern "C" fg_status_t fg_stream_wait_event(void* stream, void* event) {
+    FG_HIP(hipStreamWaitEvent((hipStream_t)stream, (hipEvent_t)event, 0));
+    return FG_OK;
+}
+
+extern "C" fg_status_t fg_event_destroy(void* event) {
+    FG_HIP(hipEventDestroy((hipEvent_t)event));
+    return FG_OK;
+}

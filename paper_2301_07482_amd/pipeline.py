@@ -4,6 +4,8 @@ This module only owns device buffers (torch tensors) and the order of the calls;
 done by the HIP kernels behind `binding`. Nothing is copied back to the host between calls: element
 counts stay in device memory and each call is launched over a static upper bound.
 """
+import struct
+
 import numpy as np
 import torch
 
@@ -211,6 +213,41 @@ def _no_tick(name, stream=None):
     return None
 
 
+class _Event:
+    """An event without timing that both this module and fg_path_run record and wait for. Made when it is first needed, in the
+    device that is current then; waiting for one that was never recorded is no wait."""
+
+    def __init__(self):
+        self._handle = None
+
+    @property
+    def handle(self):
+        if self._handle is None:
+            self._handle = B.fg_event_create()
+        return self._handle
+
+    def record(self, stream):
+        B.fg_event_record(self.handle, stream.cuda_stream)
+
+    def wait(self, stream):      # (what `torch.cuda.Stream.wait_event` calls)
+        if self._handle is not None:
+            B.fg_stream_wait_event(stream.cuda_stream, self._handle)
+
+    def __del__(self):
+        if self._handle is not None and B is not None:
+            B.fg_event_destroy(self._handle)
+
+
+def _addr(t):
+    """`B.ptr` with 0 for None."""
+    return 0 if t is None else t if isinstance(t, int) else t.data_ptr()
+
+
+_LAYERS = B.FG_PATH_MAX_LAYERS + 1
+_PACK_BATCH = [struct.Struct(f"4q{11 * (n + 1)}q") for n in range(_LAYERS)]      # fg_path_batch_t of n layers
+_PACK_CALL = struct.Struct(f"4q{3 * _LAYERS}qf6i")                               # fg_path_call_t as far as its flags
+
+
 class HotPath:
     """Work buffers, cache and weights of one model; `run(batch, it)` executes one iteration."""
 
@@ -311,9 +348,9 @@ class HotPath:
         overlap_update = overlap_update and self.n_max[0] >= overlap_min_rows
         self.overlap_update = overlap_update
         self.side = torch.cuda.Stream(device=device) if overlap_update else None
-        self.ev_pruned, self.ev_selected, self.ev_next_pruned = (torch.cuda.Event() for _ in range(3))
-        self.ev_done = [torch.cuda.Event(), torch.cuda.Event()]     # row copy of iteration it: ev_done[it % 2]
-        self.ev_bw = [torch.cuda.Event() for _ in range(L + 1)]
+        self.ev_pruned, self.ev_selected, self.ev_next_pruned = (_Event() for _ in range(3))
+        self.ev_done = [_Event(), _Event()]     # row copy of iteration it: ev_done[it % 2]
+        self.ev_bw = [_Event() for _ in range(L + 1)]
         self.admit_budget = dict(admit_budget) if admit_budget else None   # {layer: rows per update}: access-aware admission
         assert not (self.admit_budget and not update_all), "the access-aware admission needs fg_cache_update_all"
         self.ws_upd_bytes = sum(B.fg_workspace_bytes(B.FG_WS_CACHE_UPDATE, n[l]) for l in range(1, L))
@@ -350,6 +387,7 @@ class HotPath:
                 self.db = [None] + [torch.zeros(dims[l], dtype=torch.float32, device=dev) for l in range(1, L + 1)]
                 self.ws_wg_bytes = sum(weight_grad_workspace_bytes(self.bw_kind, n[l], dims[l - 1], dims[l]) for l in range(1, L + 1))
                 self.ws_wg = torch.empty(self.ws_wg_bytes + 256, dtype=torch.uint8, device=dev)
+        self._native = None      # (fg_path_t, fg_path_call_t, two fg_path_batch_t, update descriptors), made by the first call that needs them
         self.cache = None
         self.feature_side = False
         if L > 1:
@@ -484,6 +522,94 @@ class HotPath:
         B.fg_cache_update_commit(self.cache, it, specs, self._ws_upd(it), self.ws_upd_bytes, main.cuda_stream)
         self.ev_done[it % 2].record(main)
 
+    def _native_path(self):
+        """The model's buffers as fg_path_run takes them: they are allocated once and stay where they are."""
+        L, P = self.L, B.Path()
+        P.n_layers, P.model, P.feat_dtype, P.compute_dtype = L, B.FG_PATH_GCN if self.model == "gcn" else B.FG_PATH_SAGE, self.feat_code, self.comp_code
+        P.on_host, P.fused_input, P.fuse_small_layers = self.on_host, bool(self.fused_input), self.fuse_small_layers
+        P.backward, P.weight_grads, P.ring, P.num_nodes = bool(self.backward), self.weight_grads, self.ring, self.num_nodes
+        P.dims[:L + 1], P.n_max[:L + 1] = self.dims, self.n_max
+
+        def put(field, tensors):
+            for l, t in enumerate(tensors):
+                if t is not None:
+                    field[l] = t.data_ptr()
+        put(P.h, self.H)
+        put(P.agg, self.AGG_l)
+        if self.model == "gcn":
+            put(P.mean_pos, self.MEANPOS_l)
+        if self.backward:
+            put(P.dh, self.dH)
+            put(P.gnorm, self.gnorm)
+            P.ws_backward, P.ws_backward_bytes = self.ws_bw.data_ptr(), self.ws_bw_bytes
+        if self.weight_grads:
+            put(P.dw, self.dW)
+            put(P.db, self.db)
+            P.ws_weights, P.ws_weights_bytes = self.ws_wg.data_ptr(), self.ws_wg_bytes
+        for of, lists in zip(P.lists, self._lists):
+            for name in ("live", "hit", "hit_pos", "hit_slot", "normal_pos"):
+                put(getattr(of, name), lists[name])
+            of.input_ids, of.self_ids = lists["input_ids"].data_ptr(), lists["self_ids"].data_ptr()
+        P.counts_log, P.stats_log, P.input_log = self.counts_log.data_ptr(), self.stats_log.data_ptr(), self.input_log.data_ptr()
+        P.ws_top_down, P.ws_top_down_bytes = self.ws_td.data_ptr(), self.ws_td_bytes
+        P.ws_update, P.ws_update_bytes, P.ws_update_stride = self.ws_upd.data_ptr(), self.ws_upd_bytes, self.ws_upd_stride
+        P.side = self.side.cuda_stream if self.side is not None else None
+        P.ev_pruned, P.ev_selected, P.ev_next_pruned = self.ev_pruned.handle, self.ev_selected.handle, self.ev_next_pruned.handle
+        P.ev_done[0], P.ev_done[1], P.ev_gradients, P.ev_weights = self.ev_done[0].handle, self.ev_done[1].handle, self.ev_bw[1].handle, self.ev_bw[0].handle
+        specs, call = (B.UpdateLayer * max(L - 1, 1))(), B.PathCall()
+        call.specs = specs
+        return P, call, (B.PathBatch(), B.PathBatch()), specs
+
+    def _pack(self, into, bt, norms):
+        """A mini-batch as fg_path_run takes it; norms: the cache update's come with it."""
+        L = self.L
+        bw = self.backward
+        v = [_addr(bt.labels) if bw else 0, _addr(getattr(bt, "col_ids1", None)), self.reads_rows_once(bt), self.own_rows_from_table(bt)]
+        for l, n, nnz, ids, start, end, col, n_dev in zip(range(L + 1), bt.n, bt.nnz, bt.ids, bt.start, bt.end, bt.col, bt.n_dev):
+            v += n, nnz, _addr(ids), _addr(start), _addr(end), _addr(col), _addr(n_dev)
+            v += (_addr(bt.t_start[l]), _addr(bt.t_end[l]), _addr(bt.t_row[l])) if bw and l > 1 else (0, 0, 0)
+            v.append(_addr(bt.gnorm[l]) if norms and 0 < l < L else 0)
+        _PACK_BATCH[L].pack_into(into, 0, *v)
+
+    def _run_native(self, bt, it, main, update, next_bt, promised, pruned_ahead):
+        """`run` from its row copy on, as one call."""
+        if self._native is None:
+            self._native = self._native_path()
+        P, call, (now, later), specs = self._native
+        L = self.L
+        cache = self.cache if self.use_cache else None
+        do_update = update and cache is not None
+        beside = do_update and self.overlap_update and not self.backward
+        if beside:
+            for b in (bt, next_bt):      # (as in `run`)
+                if b is not None and b is not self._ready_waited and getattr(b, "ready", None) is not None:
+                    self.side.wait_event(b.ready)
+            self._ready_waited = next_bt
+        self._pack(now, bt, do_update and not self.backward)
+        ahead = beside and next_bt is not None
+        if ahead:
+            self._fit(next_bt)
+            self._pack(later, next_bt, False)
+        P.fused_input, P.fuse_small_layers, P.backward, P.weight_grads = bool(self.fused_input), self.fuse_small_layers, bool(self.backward), self.weight_grads
+        rest = (0,) * (B.FG_PATH_MAX_LAYERS - L)
+        v = [it, main.cuda_stream, cache.value if cache is not None else 0, _addr(self.feat)]
+        for of in (self.W, self.Wt, self.bias):
+            v.append(0)
+            v += [_addr(of.get(l)) for l in range(1, L + 1)]
+            v += rest
+        _PACK_CALL.pack_into(call, 0, *v, self.p_grad, bool(do_update), bool(self.overlap_update), bool(self.fetch_with_loader),
+                             self.weight_grads_ahead(bt), promised, pruned_ahead)
+        due = self._row_copy_due
+        call.due_iter, call.due = due if due is not None else (0, None)
+        self._row_copy_due = self._td_for = None
+        try:
+            B.fg_path_run(P, now, later if ahead else None, call)
+        finally:
+            if call.next_pruned:
+                self._td_for = (it + 1, next_bt)
+        if call.selected:
+            self._row_copy_due = (it, specs)
+
     def _bind(self, it):
         """Point the per-iteration state (lists of the top-down pass, counters, statistics) at iteration `it`'s copies."""
         self.__dict__.update(self._lists[it % 3])
@@ -520,9 +646,11 @@ class HotPath:
         fused = self.fused_input and not once
         promised = self._td_for is not None
         pruned_ahead = promised and self._td_for[0] == it and self._td_for[1] is bt
-        self._td_for = None
         if not pruned_ahead and getattr(bt, "ready", None) is not None:
             main.wait_event(bt.ready)      # this call's own launches are the first to read the mini-batch
+        if timer is None and not hold_second_stream and self.runs_in_one_call():
+            return self._run_native(bt, it, main, update, next_bt, promised, pruned_ahead)
+        self._td_for = None
         if promised:      # (also when the promise was not kept: that pass writes the lists this call is about to use)
             main.wait_event(self.ev_next_pruned)   # behind the previous selection on that stream
         self.flush(selection_done=promised, main=main)
@@ -672,12 +800,9 @@ class HotPath:
         gnorm = bt.gnorm
         if self.backward:
             # The weight gradients of all layers are one call behind the last layer's gradient (two launches that fill the chip
-            # by themselves); with a second stream it runs there, beside the cache update. Wide mixed layers, whose partial results are
-            # what a chunk costs, gain nothing from sharing a launch: the upper layers' go ahead there, beside the rest of the backward
-            # chain (16 k x 1024 output values 299 us against 332 in one call; 10 k x 512 224 both ways; in fp32 one call is faster, large
-            # SAGE iteration 400 against 406).
+            # by themselves); with a second stream it runs there, beside the cache update (`weight_grads_ahead`: the upper layers' sooner)
             wg_beside = self.weight_grads and self.overlap_update and timer is None
-            ahead = wg_beside and L > 1 and self.bw_kind == "bf16" and bt.n[1] * self.dims[1] >= 1 << 23
+            ahead = wg_beside and self.weight_grads_ahead(bt)
 
             def weight_grads_beside(first, last):
                 self.ev_bw[first].record(main)
@@ -728,6 +853,19 @@ class HotPath:
             self.ev_bw[0].record(self.side)       # the next iteration overwrites what the weight gradients read
             main.wait_event(self.ev_bw[0])
         tick(None)
+
+    def runs_in_one_call(self):
+        """Whether an iteration without a timer is queued by one call (fg_path_run): every configuration but those kept for
+        comparison (a call per layer), the access-aware admission and raw features in the cache's buffer."""
+        return (self.one_launch_top_down and self.update_all and self.fetch_all and not self.admit_budget and not self.feature_side
+                and self.L <= B.FG_PATH_MAX_LAYERS and (self.side is not None or not self.overlap_update))
+
+    def weight_grads_ahead(self, bt):
+        """Whether the upper layers' weight gradients are a call of their own, on the second stream beside the rest of the backward chain,
+        instead of one call with layer 1's. Wide mixed layers, whose partial results are what a chunk costs, gain nothing from
+        sharing a launch (16 k x 1024 output values 299 us against 332 in one call; 10 k x 512 224 both ways; in fp32 one call is faster,
+        large SAGE iteration 400 against 406)."""
+        return self.backward and self.L > 1 and self.bw_kind == "bf16" and bt.n[1] * self.dims[1] >= 1 << 23
 
     def holds_second_stream(self):
         """Whether `run(..., hold_second_stream=True)` has work on a second stream to hold back."""

@@ -2071,6 +2071,79 @@ def test_iterations_queued_back_to_back_match_one_at_a_time(env):
         ref.close()
 
 
+@pytest.mark.parametrize("workload,kwargs", [
+    ("tiny", dict(fused_input=True)),
+    ("tiny", dict(fused_input=True, copy_own_rows=True, fetch_with_loader=False)),
+    ("tiny", dict(use_cache=False, fuse_small_layers=True)),
+    ("tiny", dict(fused_input=True, overlap_update=False, fuse_small_layers=True)),
+    ("tiny", dict(fused_input=True, backward=True, weight_grads=True)),
+    ("tiny", dict(backward=True, weight_grads=True, overlap_update=False)),
+    ("tiny", dict(fused_input=True, backward=True, fuse_small_layers=True)),
+    ("tiny", dict(fused_input=True, backward=True, weight_grads=True, model="gcn")),
+    ("tiny", dict(model="gcn")),
+    ("host", dict(fused_input=True)),
+    ("mixed", dict(fused_input=True)),
+    ("mixed", dict(fused_input=True, backward=True, weight_grads=True)),
+])
+@pytest.mark.parametrize("col_ids", [True, False])
+def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, kwargs, col_ids):
+    """`run` through fg_path_run and through the calls one by one: the same launches, so the same bits everywhere (embeddings, counters,
+    statistics, gradients, cached rows). Announced mini-batches, one of them a promise that is not kept, one iteration without update."""
+    torch, B = env
+    import dataclasses
+    from paper_2301_07482_amd.pipeline import DeviceBatch
+    w = wl.WORKLOADS["tiny"]
+    if workload == "host":       # 512 x 10 x 5 edges of 128 values: every input row is read once
+        w = dataclasses.replace(w, feat_location="host", feat_dim=256, batch=512)
+    if workload == "mixed":      # wide enough for the upper layers' weight gradients to go ahead (8 Mi values in layer 1)
+        w = dataclasses.replace(w, num_nodes=40_000, num_edges=1_200_000, feat_dim=72, feat_dtype="f16", compute_dtype="bf16", hidden=1280,
+                                fanouts=(4, 22), batch=512)
+    g = wl.make_graph(w)
+    L, K, backward = w.num_layers, 7, kwargs.get("backward", False)
+    paths = [G.make_hotpath(w, **kwargs)[0] for _ in range(2)]
+    paths[1].runs_in_one_call = lambda: False
+    try:
+        assert paths[0].runs_in_one_call()
+        mbs = [wl.minibatch(w, g, it) for it in range(K + 1)]
+
+        def batch(it):
+            mb = mbs[it]
+            if backward:
+                return DeviceBatch(mb, None, labels=wl.node_labels(w, mb.ids[L]), col_ids=col_ids)
+            return DeviceBatch(mb, {l: wl.grad_norms(w, it, l, mb.ids[l]) for l in range(1, L)}, col_ids=col_ids)
+        state = []
+        for hp in paths:
+            batches = [batch(it) for it in range(K + 1)]
+            if workload == "host":
+                assert hp.reads_rows_once(batches[0])
+            if workload == "mixed":
+                assert hp.weight_grads_ahead(batches[0]) == backward
+            rec = []
+            for it in range(K):
+                hp.run(batches[it], it, update=it != 4, next_bt=batches[K if it == 2 else it + 1] if it + 1 < K else None)
+                n = mbs[it].ids
+                rec += [hp.H[l][:len(n[l])].clone() for l in range(1, L + 1)]
+                if backward:
+                    rec += [hp.dH[l][:len(n[l])].clone() for l in range(1, L + 1)] + [x[:len(n[l])].clone() for l, x in enumerate(hp.gnorm) if l]
+                if hp.weight_grads:
+                    rec += [x.clone() for x in hp.dW[1:] + hp.db[1:]]
+                rec += [hp.live[l][:len(n[l])].clone() for l in range(1, L)] + [hp.counts.clone(), hp.stats.clone()]
+            torch.cuda.synchronize()
+            rec += [hp.counts_log, hp.stats_log, hp.input_log]
+            if kwargs.get("use_cache", True):
+                for l in range(1, L):
+                    e = hp.export_cache(l, K)
+                    rec += [torch.as_tensor(np.asarray(e[k])) for k in ("head", "nodes", "slots", "stamps")]
+                    rec.append(torch.from_numpy(hp.cache_rows(l, e["slots"])))
+            state.append(rec)
+        assert len(state[0]) == len(state[1])
+        for i, (a, b) in enumerate(zip(*state)):
+            assert torch.equal(a, b), f"record {i} of {len(state[0])}"
+    finally:
+        for hp in paths:
+            hp.close()
+
+
 def test_device_sampled_iterations_queued_back_to_back(env):
     """Mini-batches sampled on the device (and their norms made there) on the current stream right before the call that
     announces them, twelve iterations queued without a synchronisation: the second stream, which runs ahead of the current
