@@ -5,6 +5,7 @@ done by the HIP kernels behind `binding`. Nothing is copied back to the host bet
 counts stay in device memory and each call is launched over a static upper bound.
 """
 import struct
+import sys
 
 import numpy as np
 import torch
@@ -233,8 +234,8 @@ class _Event:
         if self._handle is not None:
             B.fg_stream_wait_event(stream.cuda_stream, self._handle)
 
-    def __del__(self):
-        if self._handle is not None and B is not None:
+    def __del__(self, finalizing=sys.is_finalizing):      # (the modules are being taken apart then, and the process ends)
+        if self._handle is not None and not finalizing():
             B.fg_event_destroy(self._handle)
 
 
