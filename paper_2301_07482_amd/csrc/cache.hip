@@ -61,10 +61,10 @@ struct SelState {
     unsigned int hist0[SEL_BINS];
     unsigned int hist1[SEL_BINS];
     unsigned int n_surv;
-    unsigned int arrived[2];       // workgroups that have reached a meeting point (update_group_kernel)
+    unsigned int arrived[3];       // workgroups that have counted their keys' digit (update_group_kernel)
     unsigned int done;             // ... and that have left the scratch alone
     unsigned int admits[64];       // a workgroup's admissible nodes, published
-    unsigned int hist2[SEL_BINS];  // estimates of saved accesses of the admissible nodes (access-aware policy)
+    unsigned int hist2[SEL_BINS];  // estimates of saved accesses of the admissible nodes (access-aware policy), or the third digit
 };
 
 static_assert(SEL_BINS == 2048, "clamp_saving saturates the estimates at the last bin");
@@ -122,14 +122,14 @@ struct UpdBatch {
 };
 
 // leaves the number of admitted rows, the advanced ring header and how far the ring has ever been written
-__device__ __forceinline__ void finish_header(const UpdLayer& L, int64_t head, int64_t in) {
+__device__ __forceinline__ void finish_header(const UpdLayer& L, int64_t head, int64_t used, int64_t in) {
     const CacheRW& c = L.c;
     L.hdr->n_admit = in;
-    *c.head_next = (head + in) % c.capacity;
-    const int64_t reach = head + in;  // the ring fills slots upwards until it first wraps
+    const int64_t reach = head + in;  // the ring fills slots upwards until it first wraps (head < capacity, in <= capacity)
+    *c.head_next = reach < c.capacity ? reach : reach - c.capacity;
     if (reach >= c.capacity)
         *c.used = c.capacity;
-    else if (reach > *c.used)
+    else if (reach > used)
         *c.used = reach;
 }
 
@@ -355,15 +355,20 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void classify_update_kernel(UpdBatch
 // weight gradients (the third launch, 72 of them at 67 k positions, 33 us there). A workgroup of 1024 threads holds the keys of
 // 4096 positions in registers (four per thread), so it reads them once, finds tau by three digits,
 // classifies, ranks the admissible nodes and hands out their slots. By itself it finds the digits in LDS; the workgroups of a larger
-// layer meet three times: behind the histogram of the first digit, behind the list of the keys that carry it (from which each finds the
-// other two for itself), and behind the check-outs, with the numbers of admissible nodes. The histograms are
-// kept four times (by lane mod 4): norms share their leading digits, and equal bins of a wavefront are
+// layer meet four times: behind the histogram of each digit, and behind the check-outs, with the numbers of admissible nodes. (The keys that
+// carry the first digit as a list, from which each workgroup finds the other two for itself: a meeting less, but up to a third of
+// a layer's norms share a digit, and at 67 k positions the list took 5 + 6 us, 5 + 11 in a GCN, for 9 of two meetings.) The
+// histograms are kept four times (by lane mod 4): norms share their leading digits, and equal bins of a wavefront are
 // added one after the other.
 // Who waits needs no more than that the other workgroups start: they are at most 64 in all, so that they are all there together on a chip
 // with room for 512 of their size, and a launch they have to wait behind ends without them. The polls are bounded all the same.
-// Measured, the four launches and now: 28 k positions 36 us and their gaps, 30; 74 k beside the weight gradients of 55 k rows 66, 43; 1.2 k with
-// its row copy 31, 17 (one workgroup). GCN iteration of 55 k rows 349 us, 335.
+// Between the barriers the chain is kept short: prefix sums inside the vector registers, a wavefront's place among the others' totals from
+// four wide LDS reads, each thread clearing the counters it read, no division (with shuffles, a loop over the wavefronts and 64-bit
+// remainders 17.6 us at 1.2 k positions, 14.2 so; a third of what is left is the row copy and the first reads).
+// Measured, the four launches and now: 28 k positions 36 us and their gaps, 24; 74 k beside the weight gradients of 55 k rows 66, 27; 1.2 k with
+// its row copy 31, 14 (one workgroup).
 constexpr int ONE_COPIES = 4;
+constexpr int SEL_WAVES = SEL_THREADS / FG_WAVE;
 constexpr int GRP_CHUNK = 4 * SEL_THREADS;      // positions of a workgroup
 constexpr int GRP_MAX = 64;                     // workgroups of a launch
 constexpr int GRP_SPIN_LIMIT = 1 << 20;         // polls before a workgroup gives up (never reached)
@@ -371,40 +376,39 @@ constexpr uint32_t GRP_PUBLISHED = 0x80000000u;
 
 __device__ __attribute__((aligned(16))) uint32_t upd_spare[4];      // what is read where a layer has no quad
 
-// bin holding rank *s_rank, from this thread's two of 2048 counters, into *s_bin; *s_rank is rebased to that bin
-__device__ __forceinline__ void select_bin_two(long long c0, long long c1, long long* red, uint32_t* s_bin, long long* s_rank) {
+// Place of a thread's two of 2048 counters: c0 + c1 of the threads before it, and of all. `red` needs SEL_WAVES words and is read until the
+// next barrier.
+__device__ __forceinline__ uint32_t scan_two(uint32_t c0, uint32_t c1, uint32_t* red, uint32_t& all) {
     static_assert(SEL_BPT == 2, "two bins per thread");
-    const int t = threadIdx.x;
-    long long incl = c0 + c1;
-    for (int off = 1; off < FG_WAVE; off <<= 1) {
-        const long long v = __shfl_up(incl, off, FG_WAVE);
-        if (fg_lane() >= off) incl += v;
-    }
+    const uint32_t incl = (uint32_t)fg_wave_scan((int)(c0 + c1));
     if (fg_lane() == FG_WAVE - 1) red[fg_wave()] = incl;
     __syncthreads();
-    long long lo = incl - c0 - c1;
-    for (int w = 0; w < fg_wave(); ++w) lo += red[w];
-    const long long rank = *s_rank;
-    __syncthreads();      // everybody has read the rank and the wavefronts' totals
-    if (rank >= lo && rank < lo + c0 + c1) {      // true for exactly one thread
-        const bool second = rank >= lo + c0;
-        *s_bin = 2 * t + (second ? 1 : 0);
-        *s_rank = rank - (second ? lo + c0 : lo);
-    }
-    __syncthreads();
+    uint32_t before;
+    fg_wave_totals<SEL_WAVES>((const int*)red, (int&)before, (int&)all);
+    return before + incl - c0 - c1;
 }
 
-// This thread's two counters of hist[bin * ONE_COPIES + copy]
-__device__ __forceinline__ void two_bins(const uint32_t* hist, long long& c0, long long& c1) {
+// The thread whose two bins hold the key of rank `rank` leaves the bin and the rank within it; c0, c1 and lo as scan_two has them.
+__device__ __forceinline__ void find_bin(uint32_t c0, uint32_t c1, uint32_t lo, uint32_t rank, uint2* out) {
+    if (rank >= lo && rank < lo + c0 + c1) {
+        const bool second = rank >= lo + c0;
+        *out = uint2{2 * threadIdx.x + (second ? 1u : 0u), rank - (second ? lo + c0 : lo)};
+    }
+}
+
+// This thread's two counters of hist[bin * ONE_COPIES + copy], which are zero again afterwards
+__device__ __forceinline__ void take_bins(uint32_t* hist, uint32_t& c0, uint32_t& c1) {
     static_assert(ONE_COPIES == 4, "four counters per bin");
-    const uint4 a = ((const uint4*)hist)[2 * threadIdx.x], b = ((const uint4*)hist)[2 * threadIdx.x + 1];
-    c0 = (long long)a.x + a.y + a.z + a.w;
-    c1 = (long long)b.x + b.y + b.z + b.w;
+    uint4* mine = (uint4*)hist + 2 * threadIdx.x;
+    const uint4 a = mine[0], b = mine[1];
+    mine[0] = mine[1] = uint4{0, 0, 0, 0};
+    c0 = a.x + a.y + a.z + a.w;
+    c1 = b.x + b.y + b.z + b.w;
 }
 
 // What the workgroups of a layer tell each other goes past the caches of their XCDs, word by word (atomics of agent scope); before a
 // workgroup says that it is there, each of its wavefronts waits until its own have arrived. (Release and acquire fences instead
-// write back and invalidate whole L2s: 28 k positions 39 us instead of 30, 99 instead of 43 of 74 k beside the weight gradients.)
+// write back and invalidate whole L2s: some 3 us more for each meeting, 15 beside the weight gradients.)
 template <typename T>
 __device__ __forceinline__ T grp_load(const T* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -435,12 +439,10 @@ __device__ __forceinline__ bool grp_meet(unsigned int* arrived, unsigned int n, 
 template <bool COPY>
 __global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
     __shared__ __attribute__((aligned(16))) uint32_t hist[SEL_BINS * ONE_COPIES];
-    __shared__ int wave_count[SEL_THREADS / FG_WAVE];
-    __shared__ long long red[16];
-    __shared__ uint32_t s_bin;
-    __shared__ long long s_rank;
+    __shared__ __attribute__((aligned(16))) int wave_count[SEL_WAVES];
+    __shared__ __attribute__((aligned(16))) uint32_t red[2][SEL_WAVES];      // alternating: read while the next pass writes
+    __shared__ uint2 s_found[3];      // by digit: its value, and the rank of tau among the keys that carry it and those before
     __shared__ int s_evicted, s_over, s_ok, s_before, s_all;
-    __shared__ unsigned int s_count, s_base;
     int part;
     const int layer = layer_of_block(B.sel_first, B.n_layers, blockIdx.x, part);
     const UpdLayer& L = B.l[layer];
@@ -449,7 +451,7 @@ __global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
     const int t = threadIdx.x, lane = fg_lane(), wave = fg_wave();
     const int n_all = upd_count(L), base = part * GRP_CHUNK;
     const int n = n_all - base < 0 ? 0 : (n_all - base < GRP_CHUNK ? n_all - base : GRP_CHUNK);      // positions of this workgroup
-    const int64_t head = *c.head;
+    const int64_t head = *c.head, used = *c.used;
     // Position of element e: base + 4 * t + e. Every read is unconditional (the first quad, or 16 bytes of the
     // library's own, where a quad is not wholly there) so that they are in flight together; the one quad that the end of the layer
     // cuts is read one by one by the thread that owns it, and joins below.
@@ -489,79 +491,53 @@ __global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
                 if (L.hit[j] != 0) is_hit |= 1u << e;
             }
     }
-    auto clear_hist = [&]() {
-        for (int b = t; b < SEL_BINS * ONE_COPIES / 4; b += SEL_THREADS) ((uint4*)hist)[b] = uint4{0, 0, 0, 0};
-    };
     auto count_key = [&](uint32_t bin) { atomicAdd(&hist[bin * ONE_COPIES + (lane & (ONE_COPIES - 1))], 1u); };
-    if (t == 0) {
-        s_evicted = s_over = 0;
-        s_count = 0;
-    }
-    clear_hist();
+    if (t == 0) s_evicted = s_over = 0;
+    for (int b = t; b < SEL_BINS * ONE_COPIES / 4; b += SEL_THREADS) ((uint4*)hist)[b] = uint4{0, 0, 0, 0};
     bool lost = false;
-    long long m, c0, c1;
-    uint32_t tau_key = 0, n_list = 0;
-    uint32_t* list = (uint32_t*)L.apos;      // the keys with the first digit of tau (parts > 1); at most n of them
-    if (parts == 1) {
-        m = fg_block_sum((long long)__popc(is_live), red);      // (its barriers also end the clearing)
-    } else {
-        if (part == 0 && t < 4 && L.stats) grp_store(&L.stats[t], (int64_t)0);
-        __syncthreads();
+    uint32_t m = 0, tau_key = 0;
+    int mode = 1;
+    if (parts > 1 && part == 0 && t < 4 && L.stats) grp_store(&L.stats[t], (int64_t)0);
+    __syncthreads();
+    // tau is the key of rank k, found digit by digit (11 + 11 + 10 bits); mode is the same for all workgroups of the layer
+#pragma unroll 1
+    for (int pass = 0; pass < 3 && mode == 1; ++pass) {
+        const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
+        const uint32_t bins = pass == 2 ? 1023u : 2047u;
+        const uint32_t above = pass == 0 ? 0u : (pass == 1 ? 0xFFE00000u : 0xFFFFFC00u);      // the digits found so far
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            if ((is_live >> e) & 1u) count_key(key[e] >> 21);
+            if (((is_live >> e) & 1u) && (key[e] & above) == tau_key) count_key((key[e] >> shift) & bins);
         __syncthreads();
-        two_bins(hist, c0, c1);
-        if (c0) atomicAdd(&L.sel->hist0[2 * t], (unsigned int)c0);
-        if (c1) atomicAdd(&L.sel->hist0[2 * t + 1], (unsigned int)c1);
-        lost = !grp_meet(&L.sel->arrived[0], parts, &s_ok);
-        c0 = grp_load(&L.sel->hist0[2 * t]);
-        c1 = grp_load(&L.sel->hist0[2 * t + 1]);
-        m = fg_block_sum(c0 + c1, red);
-    }
-    const long long k_rank = (long long)floor((double)L.p_grad * (double)m);
-    const int mode = lost || k_rank <= 0 ? 0 : (k_rank >= m ? 2 : 1);
-    if (mode == 1 && t == 0) s_rank = k_rank;
-    if (parts > 1) {      // (every workgroup of the layer finds the same digit, and takes both meetings whatever the mode)
-        if (mode == 1) {
-            __syncthreads();
-            select_bin_two(c0, c1, red, &s_bin, &s_rank);
-            tau_key = s_bin << 21;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (((is_live >> e) & 1u) && (key[e] >> 21) == s_bin) hist[atomicAdd(&s_count, 1u)] = key[e];
-            __syncthreads();
-            if (t == 0 && s_count) s_base = atomicAdd(&L.sel->n_surv, s_count);
-            __syncthreads();
-            for (unsigned int i = t; i < s_count; i += SEL_THREADS) grp_store(&list[s_base + i], hist[i]);
+        uint32_t c0, c1, all;
+        take_bins(hist, c0, c1);
+        if (parts > 1) {
+            unsigned int* shared = pass == 0 ? L.sel->hist0 : (pass == 1 ? L.sel->hist1 : L.sel->hist2);
+            if (c0) atomicAdd(&shared[2 * t], c0);
+            if (c1) atomicAdd(&shared[2 * t + 1], c1);
+            lost = !grp_meet(&L.sel->arrived[pass], parts, &s_ok);
+            c0 = grp_load(&shared[2 * t]);
+            c1 = grp_load(&shared[2 * t + 1]);
         }
-        if (!grp_meet(&L.sel->arrived[1], parts, &s_ok)) lost = true;
-        n_list = grp_load(&L.sel->n_surv);
-    }
-    if (mode == 1) {      // uniform over the workgroup: tau is the key of rank k, found digit by digit (11 + 11 + 10 bits)
-#pragma unroll 1
-        for (int pass = parts == 1 ? 0 : 1; pass < 3; ++pass) {
-            const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
-            const uint32_t bins = pass == 2 ? 1023u : 2047u;
-            const uint32_t above = pass == 0 ? 0u : (pass == 1 ? 0xFFE00000u : 0xFFFFFC00u);      // the digits found so far
-            if (pass > 0) {
-                clear_hist();
-                __syncthreads();
-            }
-            if (parts == 1) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (((is_live >> e) & 1u) && (key[e] & above) == tau_key) count_key((key[e] >> shift) & bins);
-            } else {
-                for (uint32_t i = t; i < n_list; i += SEL_THREADS) {
-                    const uint32_t x = grp_load(&list[i]);
-                    if ((x & above) == tau_key) count_key((x >> shift) & bins);
-                }
-            }
+        const uint32_t lo = scan_two(c0, c1, red[pass & 1], all);
+        uint32_t rank;
+        if (pass == 0) {
+            m = all;
+            const long long k = (long long)floor((double)L.p_grad * (double)m);
+            mode = k <= 0 ? 0 : (k >= (long long)m ? 2 : 1);
+            rank = (uint32_t)k;
+        } else {
+            rank = s_found[pass - 1].y;
+        }
+        if (lost) {      // (who still waits further on must not wait for this workgroup)
+            mode = 0;
+            if (t == 0)
+                for (int p = pass + 1; p < 3; ++p) __hip_atomic_fetch_add(&L.sel->arrived[p], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (mode == 1) {
+            find_bin(c0, c1, lo, rank, &s_found[pass]);
             __syncthreads();
-            two_bins(hist, c0, c1);
-            select_bin_two(c0, c1, red, &s_bin, &s_rank);
-            tau_key |= s_bin << shift;
+            tau_key |= s_found[pass].x << shift;
         }
     }
     // check-outs and admissible nodes
@@ -578,22 +554,17 @@ __global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
             ++evicted;
         }
     }
-    for (int off = FG_WAVE / 2; off > 0; off >>= 1) evicted += __shfl_down(evicted, off, FG_WAVE);
-    if (lane == 0 && evicted) atomicAdd(&s_evicted, evicted);
     // ranks in position order: workgroups first, then threads, then a thread's elements
     const int own = __popc(admit_bits);
-    int incl = own;
-    for (int off = 1; off < FG_WAVE; off <<= 1) {
-        const int v = __shfl_up(incl, off, FG_WAVE);
-        if (lane >= off) incl += v;
+    const int both = fg_wave_scan(own | evicted << 16), incl = both & 0xFFFF;      // (at most 256 of each in a wavefront)
+    if (lane == FG_WAVE - 1) {
+        wave_count[wave] = incl;
+        if (both >> 16) atomicAdd(&s_evicted, both >> 16);
     }
-    if (lane == FG_WAVE - 1) wave_count[wave] = incl;
     __syncthreads();
-    int before = incl - own, total = 0;
-    for (int w = 0; w < SEL_THREADS / FG_WAVE; ++w) {
-        if (w < wave) before += wave_count[w];
-        total += wave_count[w];
-    }
+    int before, total;
+    fg_wave_totals<SEL_WAVES>(wave_count, before, total);
+    before += incl - own;
     if (parts > 1) {      // what the other workgroups admit, behind all check-outs
         grp_arrive();
         if (wave == 0) {
@@ -635,7 +606,8 @@ __global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
         for (int e = 0; e < 4; ++e) {
             rank[e] = before + __popc(admit_bits & ((1u << e) - 1u));
             in[e] = ((admit_bits >> e) & 1u) != 0 && rank[e] < L.room;
-            slot[e] = in[e] ? (int32_t)((head + rank[e]) % c.capacity) : 0;
+            const int64_t at = head + rank[e];      // head < capacity, rank < room <= capacity
+            slot[e] = in[e] ? (int32_t)(at < c.capacity ? at : at - c.capacity) : 0;
             old[e] = c.slot_node[slot[e]];
             old_stamp[e] = c.slot_stamp[slot[e]];
         }
@@ -656,8 +628,8 @@ __global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
             if (COPY) ((int2*)hist)[rank[e]] = int2{4 * t + e, slot[e]};      // (the histograms are not needed any more)
         }
     }
-    for (int off = FG_WAVE / 2; off > 0; off >>= 1) over += __shfl_down(over, off, FG_WAVE);
-    if (lane == 0 && over) atomicAdd(&s_over, over);
+    over = fg_wave_scan(over);
+    if (lane == FG_WAVE - 1 && over) atomicAdd(&s_over, over);
     __syncthreads();
     if (t == 0) {
         const int64_t in = lost ? 0 : (total < L.room ? total : L.room);
@@ -665,7 +637,7 @@ __global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
             L.hdr->mode = mode;
             L.hdr->tau_key = tau_key;
             L.hdr->m_live = m;
-            finish_header(L, head, in);
+            finish_header(L, head, used, in);
         }
         if (L.stats) {
             if (part == 0) {
@@ -686,9 +658,10 @@ __global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
     if (parts > 1) {
         __syncthreads();
         if (s_ok) {
-            for (int b = t; b < SEL_BINS; b += SEL_THREADS) L.sel->hist0[b] = 0;
+            for (int b = t; b < SEL_BINS; b += SEL_THREADS) L.sel->hist0[b] = L.sel->hist1[b] = L.sel->hist2[b] = 0;
             if (t < 64) L.sel->admits[t] = 0;
-            if (t == 0) L.sel->n_surv = L.sel->arrived[0] = L.sel->arrived[1] = L.sel->done = 0;
+            if (t < 3) L.sel->arrived[t] = 0;
+            if (t == 0) L.sel->done = 0;
         }
     }
     if constexpr (COPY) {
@@ -821,7 +794,7 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void assign_slots_kernel(UpdBatch B)
             const long long ties = before + total;
             const long long in = sure_all + (ties < room ? ties : room);
             const long long all = n_cand >= 0 ? n_cand : ties;
-            finish_header(L, head, in);
+            finish_header(L, head, *c.used, in);
             if (L.stats) {
                 L.stats[0] = in;
                 L.stats[3] = all - in;
@@ -1141,9 +1114,9 @@ fg_status_t launch_update(UpdBatch& B, hipStream_t st, bool select = true, bool 
     const unsigned n_sel = (unsigned)B.sel_first[B.n_layers], n_scan = (unsigned)B.scan_first[B.n_layers];
     // A workgroup per 4096 positions in one launch where the layers' arrays can be read four at a time, no layer ranks by saved accesses
     // (that needs the counts of all its admissible nodes first) and the workgroups are few enough to wait for each other. A selection by
-    // itself runs beside the layers, where four short launches are in nobody's way, and workgroups that wait are: one per layer there
-    // (large step 215 us with the four launches, 224 with the group).
-    bool group = n_sel <= (unsigned)(commit ? GRP_MAX : B.n_layers);
+    // itself runs beside the layers, where four short launches are in nobody's way, and workgroups that wait are: up to five of them
+    // there (step of 9 k positions 77 us with the four launches, 75.5 with the group; 15 k 100, 97; 24 k 98, 99.5; 67 k 200, 207).
+    bool group = n_sel <= (unsigned)(commit ? GRP_MAX : (B.n_layers > 5 ? B.n_layers : 5));
     for (int i = 0; i < B.n_layers; ++i) {
         const UpdLayer& u = B.l[i];
         group = group && !u.saving && !(((uintptr_t)u.gnorm | (uintptr_t)u.ids) & 15) && !(((uintptr_t)u.live | (uintptr_t)u.hit) & 3);

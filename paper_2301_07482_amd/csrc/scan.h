@@ -12,6 +12,33 @@ constexpr int FG_WAVE = 64;
 __device__ __forceinline__ int fg_lane() { return threadIdx.x & (FG_WAVE - 1); }
 __device__ __forceinline__ int fg_wave() { return threadIdx.x >> 6; }
 
+// Inclusive prefix sum over a wavefront, all 64 lanes active. The lanes' values move inside the vector registers (DPP: shifts by 1, 2, 4, 8
+// within rows of 16 lanes, then a row's last lane to the next row and the last of the lower half to the upper), where a shuffle
+// goes through the LDS unit: six dependent additions instead of six round trips.
+__device__ __forceinline__ int fg_wave_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
+// Of the totals that WAVES wavefronts left in `totals` (16-byte aligned): the sum of those before this one, and of all.
+template <int WAVES>
+__device__ __forceinline__ void fg_wave_totals(const int* totals, int& before, int& all) {
+    static_assert(WAVES % 4 == 0, "read four at a time");
+    before = all = 0;
+    const int wave = fg_wave();
+#pragma unroll
+    for (int w = 0; w < WAVES; w += 4) {
+        const int4 v = *(const int4*)(totals + w);
+        all += v.x + v.y + v.z + v.w;
+        before += (w < wave ? v.x : 0) + (w + 1 < wave ? v.y : 0) + (w + 2 < wave ? v.z : 0) + (w + 3 < wave ? v.w : 0);
+    }
+}
+
 // Number of lanes below this one for which `flag` holds; `total` = lanes of the wave for which it holds.
 __device__ __forceinline__ int fg_wave_rank(bool flag, int& total) {
     const unsigned long long m = __ballot(flag);

@@ -207,7 +207,7 @@ def test_top_down_clears_liveness_of_the_smallest_batches(env):
         assert lists[0][3][:n_in].cpu().numpy().tolist() == [[7, 3, 9][j] for j in range(3) if want_live[j]]
 
 
-def _device_update(torch, B, cache, i, ids, live, gn, p, rows, misalign=False):
+def _device_update(torch, B, cache, i, ids, live, gn, p, rows, misalign=False, two_parts=False):
     """Lookup (no block) followed by the update on the device; returns the hit flags. `misalign` puts the norms
     and the liveness flags at addresses that are not multiples of 16 and 4 bytes."""
     n = len(ids)
@@ -226,8 +226,14 @@ def _device_update(torch, B, cache, i, ids, live, gn, p, rows, misalign=False):
     B.fg_lookup_prune(cache, 1, i, t_ids, n, t_live, None, None, None, 0, 0, None, t_hit, t_l[0], t_l[1], t_l[2], None,
                       t_cnt, ws, wsb, None)
     t_stats = torch.zeros(4, dtype=torch.int64, device="cuda")
-    B.fg_cache_update(cache, 1, i, t_ids, n, t_live, t_hit, t_gn, p, dev(torch, rows), rows.shape[1] * 4, t_stats,
-                      ws, wsb, None)
+    t_rows = dev(torch, rows)
+    if two_parts:
+        specs = B.update_layers([dict(layer=1, n=n, ids_dev=t_ids, live_dev=t_live, hit_dev=t_hit, gnorm_dev=t_gn, h_dev=t_rows,
+                                      h_stride=rows.shape[1] * 4, stats_dev=t_stats)])
+        B.fg_cache_update_select(cache, i, p, specs, ws, wsb, None)
+        B.fg_cache_update_commit(cache, i, specs, ws, wsb, None)
+    else:
+        B.fg_cache_update(cache, 1, i, t_ids, n, t_live, t_hit, t_gn, p, t_rows, rows.shape[1] * 4, t_stats, ws, wsb, None)
     return t_hit.cpu().numpy()[:n].astype(bool), t_l[1].cpu().numpy(), t_stats.cpu().numpy().tolist()
 
 
@@ -575,7 +581,13 @@ def test_cache_update_of_norms_that_share_their_digits(env, n, norms):
     _check_update_sizes(env, n, 0.37, draw)
 
 
-def _check_update_sizes(env, n, p, norms):
+@pytest.mark.parametrize("n", [4096, 4097, 20_480, 20_481])
+def test_cache_update_in_two_parts_on_both_sides_of_its_launches(env, n):
+    """fg_cache_update_select and _commit: up to five workgroups of 4096 positions wait for each other, beyond that four launches."""
+    _check_update_sizes(env, n, 0.4, lambda r: np.exp(r.standard_normal(n)), two_parts=True)
+
+
+def _check_update_sizes(env, n, p, norms, two_parts=False):
     torch, B = env
     r = np.random.default_rng(n)
     N, cap, d = max(20000, 3 * n), 4500, 8
@@ -588,7 +600,7 @@ def _check_update_sizes(env, n, p, norms):
             gn = norms(r).astype(np.float32)
             rows = r.standard_normal((n, d)).astype(np.float32)
             look = O.lookup_prune(oc, i, ids, live, None, None, None, 0)
-            _, _, stats = _device_update(torch, B, cache, i, ids, live, gn, p, rows, misalign=False)
+            _, _, stats = _device_update(torch, B, cache, i, ids, live, gn, p, rows, misalign=False, two_parts=two_parts)
             st = O.cache_update(oc, i, ids, live, look["hit"], gn, p, rows)
             assert stats == [st["admitted"], st["evicted_by_gradient"], st["overwritten"], st["dropped_overflow"]]
             exp = _export(torch, B, cache, cap, i + 1)
