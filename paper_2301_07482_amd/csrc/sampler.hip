@@ -210,8 +210,8 @@ __device__ __forceinline__ int smp_prefix(const int32_t* v, int n, int32_t* out)
 // For every position j of the layer below: the rows that sampled it, ascending, back to back. Stages: count the edges per
 // source (a sampled block's last launch does it in passing); exclusive scan (t_start, t_end; a workgroup adds up the counters
 // before its own itself, or per-workgroup sums of a stage of their own where there are many); every edge takes a free place
-// of its source's list (the order of arrival is arbitrary); every list is sorted (lists are short: a source is sampled by a
-// handful of rows), which makes the result independent of that order. Rows are read by groups of lanes: one lane per row
+// of its source's list (the order of arrival is arbitrary); every list is sorted (by its length, see tr_sort_lists: a source is sampled by a
+// handful of rows; a hub by many), which makes the result independent of that order. Rows are read by groups of lanes: one lane per row
 // walked a chain of dependent atomics on a few compute units.
 // The stages of a block that was just sampled ride in the launches of the next one (a few dozen workgroups in front of them, which
 // leave the chip to it): five launches and 24 us less for 6 k rows x 10 and 54 k sources. By themselves they are a launch each.
@@ -275,6 +275,130 @@ __device__ __forceinline__ void tr_sort(int32_t* list, int64_t b, int64_t e) {  
     }
 }
 
+// Sorts one list of rows per thread, list[b .. e), in place; every thread of the workgroup calls it, b >= e: none. Most sources have a few rows,
+// but a hub of a graph with skewed degrees has one for every other row of the block, and a thread that sorts such a list
+// by insertion takes n^2 / 4 dependent steps through memory while the launch waits for it. So by length:
+//   up to 8 (TR_SHORT)   a thread, in registers: one round of loads, a network of 19 exchanges
+//   up to 64             a wavefront, an entry per lane: its place is the number of entries below it
+//   more                 a set of rows in LDS, a bit per row, read out in order: by a wavefront for blocks of up to 8192 rows (TR_WORDS),
+//                        by the workgroup for up to 128 rows per thread; beyond that, and where a row names a source twice, by insertion
+// The longer lists are handed out to the workgroup's wavefronts by a queue. Mini-batches with transposes, the whole call, before and now:
+// 988 seeds x 8 x 9 of a graph of 11 k nodes 323 -> 84 us, 598 x 5 x 6 x 9 of 161 k nodes 415 -> 111; 1024 x 5 x 10 x 15 of 28 M nodes, whose lists
+// are short, 153 both ways.
+constexpr int TR_SHORT = 8, TR_WORDS = 256;
+template <int THREADS>
+__device__ __forceinline__ void tr_sort_lists(int32_t* list, int64_t b, int64_t e, int64_t max_rows) {
+    __shared__ __attribute__((aligned(16))) uint32_t s_rows[THREADS / FG_WAVE * TR_WORDS];
+    __shared__ int2 s_queue[THREADS];      // first entry and length
+    __shared__ int s_queued, s_odd, s_sum[THREADS / FG_WAVE];
+    constexpr int WAVES = THREADS / FG_WAVE, GROUP_WORDS = WAVES * TR_WORDS / THREADS;      // per thread
+    static_assert(GROUP_WORDS == 4, "a thread's words are read as one");
+    const int t = (int)threadIdx.x, lane = fg_lane(), wave = fg_wave();
+    const int n = e > b ? (int)(e - b) : 0;
+    const bool by_wave = max_rows <= TR_WORDS * 32, by_group = !by_wave && max_rows <= THREADS * GROUP_WORDS * 32;
+    __syncthreads();      // an earlier call's queue is read
+    if (t == 0) s_queued = 0;
+    __syncthreads();
+    if (n > TR_SHORT) {
+        if (n <= FG_WAVE || by_wave || by_group)
+            s_queue[atomicAdd(&s_queued, 1)] = int2{(int)b, n};
+        else
+            tr_sort(list, b, e);
+    } else if (n > 1) {
+        int32_t v[TR_SHORT];
+#pragma unroll
+        for (int i = 0; i < TR_SHORT; ++i) v[i] = i < n ? list[b + i] : INT32_MAX;
+        auto order = [&](int i, int k) {
+            const int32_t lo = v[i] < v[k] ? v[i] : v[k];
+            v[k] = v[i] < v[k] ? v[k] : v[i];
+            v[i] = lo;
+        };
+        order(0, 1), order(2, 3), order(4, 5), order(6, 7);
+        order(0, 2), order(1, 3), order(4, 6), order(5, 7);
+        order(1, 2), order(5, 6);
+        order(0, 4), order(1, 5), order(2, 6), order(3, 7);
+        order(2, 4), order(3, 5);
+        order(1, 2), order(3, 4), order(5, 6);
+#pragma unroll
+        for (int i = 0; i < TR_SHORT; ++i)
+            if (i < n) list[b + i] = v[i];
+    }
+    __syncthreads();
+    const int queued = s_queued;
+    // Sets the bits of the list's entries; false: an entry is there twice or is no row of the block
+    auto set_bits = [&](uint32_t* rows, int first, int len, int from, int step) {
+        bool fine = true;
+        for (int i = from; i < len; i += step) {
+            const uint32_t r = (uint32_t)list[first + i];
+            if ((int64_t)r >= max_rows)
+                fine = false;
+            else
+                fine = fine && !((atomicOr(&rows[r >> 5], 1u << (r & 31u)) >> (r & 31u)) & 1u);
+        }
+        return fine;
+    };
+    uint32_t* mine = s_rows + wave * TR_WORDS;
+    int2 next = wave < queued ? s_queue[wave] : int2{0, 0};
+    int32_t next_v = lane < next.y ? list[next.x + lane] : 0;
+    for (int q = wave; q < queued; q += WAVES) {      // uniform over the wavefront
+        const int first = __builtin_amdgcn_readfirstlane(next.x), len = __builtin_amdgcn_readfirstlane(next.y);
+        const int32_t v = next_v;
+        next = q + WAVES < queued ? s_queue[q + WAVES] : int2{0, 0};      // the next list's first entries are on their way meanwhile
+        next_v = lane < next.y ? list[next.x + lane] : 0;
+        if (len <= FG_WAVE) {
+            int below = 0;
+            for (int i = 0; i < len; ++i) {
+                const int32_t x = __builtin_amdgcn_readlane(v, i);
+                below += x < v || (x == v && i < lane) ? 1 : 0;
+            }
+            if (lane < len) list[first + below] = v;
+        } else if (by_wave) {
+            const int words = (int)((max_rows + 31) >> 5);
+            for (int w = lane; w < words; w += FG_WAVE) mine[w] = 0;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const bool fine = __all(set_bits(mine, first, len, lane, FG_WAVE));
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (!fine) {
+                if (lane == 0) tr_sort(list, first, (int64_t)first + len);
+                continue;
+            }
+            int at = first;
+            for (int w0 = 0; w0 < words; w0 += FG_WAVE) {
+                uint32_t bits = w0 + lane < words ? mine[w0 + lane] : 0u;
+                const int here = __popc(bits), incl = fg_wave_scan(here);
+                int to = at + incl - here;
+                for (; bits; bits &= bits - 1) list[to++] = 32 * (w0 + lane) + __ffs((int)bits) - 1;
+                at += __builtin_amdgcn_readlane(incl, FG_WAVE - 1);
+            }
+        }
+    }
+    if (!by_group) return;      // uniform over the workgroup
+    for (int q = 0; q < queued; ++q) {
+        const int first = s_queue[q].x, len = s_queue[q].y;
+        if (len <= FG_WAVE) continue;
+        __syncthreads();      // the bits and sums of the list before are read
+        if (t == 0) s_odd = 0;
+        ((uint4*)s_rows)[t] = uint4{0, 0, 0, 0};
+        __syncthreads();
+        if (!set_bits(s_rows, first, len, t, THREADS)) s_odd = 1;
+        __syncthreads();
+        if (s_odd) {
+            if (t == 0) tr_sort(list, first, (int64_t)first + len);
+            continue;
+        }
+        const uint4 set = ((const uint4*)s_rows)[t];
+        const uint32_t word[4] = {set.x, set.y, set.z, set.w};
+        const int here = __popc(set.x) + __popc(set.y) + __popc(set.z) + __popc(set.w), incl = fg_wave_scan(here);
+        if (lane == FG_WAVE - 1) s_sum[wave] = incl;
+        __syncthreads();
+        int to = first + incl - here;
+        for (int w = 0; w < wave; ++w) to += s_sum[w];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            for (uint32_t bits = word[u]; bits; bits &= bits - 1) list[to++] = 32 * (4 * t + u) + __ffs((int)bits) - 1;
+    }
+}
+
 // exclusive scan of one value per thread over the workgroup; `total`: their sum
 __device__ __forceinline__ int tr_block_scan(int c, int& total) {
     __shared__ int wave_sum[TR_THREADS / FG_WAVE];
@@ -294,10 +418,11 @@ __device__ __forceinline__ int tr_block_scan(int c, int& total) {
     return earlier + incl - c;
 }
 
-// one workgroup of a stage
+// one workgroup, of THREADS threads, of a stage
+template <int THREADS>
 __device__ __forceinline__ void tr_stage(const TrArgs& A, int stage, int block) {
     __shared__ long long red[16];
-    const int threads = (int)blockDim.x;
+    constexpr int threads = THREADS;
     const int64_t j = (int64_t)block * threads + threadIdx.x;
     if (stage == TR_COUNT || stage == TR_FILL) {
         const int64_t n = tr_count(A.n_dev, A.max_rows), n_src = tr_count(A.n_src_dev, A.max_src), i = j / TR_LANES;
@@ -310,7 +435,14 @@ __device__ __forceinline__ void tr_stage(const TrArgs& A, int stage, int block) 
                 if (at < A.max_nnz) A.t_row[at] = row;
             });
     } else if (stage == TR_SORT) {
-        if (j < A.max_src) tr_sort(A.t_row, A.t_start[j], A.t_end[j] < A.max_nnz ? A.t_end[j] : A.max_nnz);
+        // (sixteen sources in turn to every workgroup: those with long lists are the first ones of the layer below)
+        const int64_t blocks = (A.max_src + threads - 1) / threads, s = ((threadIdx.x >> 4) * blocks + block) * 16 + (threadIdx.x & 15);
+        int64_t b = 0, e = 0;
+        if (s < A.max_src) {
+            b = A.t_start[s];
+            e = A.t_end[s] < A.max_nnz ? A.t_end[s] : A.max_nnz;
+        }
+        tr_sort_lists<THREADS>(A.t_row, b, e, A.max_rows);
     } else if (stage == TR_SUM) {
         const int64_t q = (int64_t)block * TR_THREADS + threadIdx.x;      // of TR_THREADS counters in any case
         long long s = 0;
@@ -342,12 +474,13 @@ __device__ __forceinline__ void tr_stage(const TrArgs& A, int stage, int block) 
 }
 
 // Whether this workgroup belongs to a riding stage (which it then does); `block`: its number among the launch's own, if not.
+template <int THREADS = SMP_THREADS>
 __device__ __forceinline__ bool tr_rides(const TrRides& T, int& block, int b = (int)blockIdx.x) {
     static_assert(TR_MAX_RIDES == 2, "two rides are told apart here");
     block = b - T.blocks;
     if (block >= 0) return false;
     const int second = b >= T.end[0] ? 1 : 0;
-    tr_stage(T.a[second], T.stage[second], b - (second ? T.end[0] : 0));
+    tr_stage<THREADS>(T.a[second], T.stage[second], b - (second ? T.end[0] : 0));
     return true;
 }
 
@@ -405,7 +538,7 @@ __device__ __forceinline__ SmpSlot smp_slot(const SmpArgs& A, int64_t first_row,
 __global__ __launch_bounds__(SMP_DRAW_THREADS) void sample_draw_kernel(SmpArgs A, TrRides T, SmpClear C) {
     __shared__ int32_t s_nb[SMP_DRAW_THREADS];
     int block;
-    if (tr_rides(T, block)) return;
+    if (tr_rides<SMP_DRAW_THREADS>(T, block)) return;
     if (block >= A.draw_blocks + A.own_blocks) {
         const int ahead = A.draw_blocks + A.own_blocks;
         smp_clear(C, block - ahead, (int)gridDim.x - T.blocks - ahead);
@@ -817,7 +950,10 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void transpose_small_kernel(TrArgs A
         const int to = atomicAdd(&cnt[c], 1);
         if (to < nnz) list[to] = row;
     });      // cnt[j]: now the end of list j
-    for (int j = t; j < src; j += FG_SCAN_BLOCK) tr_sort(list, j ? cnt[j - 1] : 0, cnt[j] < nnz ? cnt[j] : nnz);
+    for (int j0 = 0; j0 < src; j0 += FG_SCAN_BLOCK) {
+        const int j = j0 + t;
+        tr_sort_lists<FG_SCAN_BLOCK>(list, j > 0 && j < src ? cnt[j - 1] : 0, j < src ? (cnt[j] < nnz ? cnt[j] : nnz) : 0, A.max_rows);
+    }
     __syncthreads();
     const int stored = total < nnz ? total : nnz;
     for (int k = t; k < stored; k += FG_SCAN_BLOCK) A.t_row[k] = list[k];

@@ -937,6 +937,36 @@ def test_transpose_block_matches_oracle(env, n, n_src, max_deg, slack, seed):
     assert t_start.cpu().numpy()[n_src:src_b].tolist() == [total] * slack == t_end.cpu().numpy()[n_src:src_b].tolist()
 
 
+@pytest.mark.parametrize("twice", [False, True])
+@pytest.mark.parametrize("n,pad", [(700, 0), (700, 20_000), (8192, 20_000), (8193, 20_000), (131_072, 0), (131_073, 0)])
+def test_transpose_sorts_lists_by_length(env, n, pad, twice):
+    """Sources sampled by 1 to 700 rows (the lengths and sizes of a block at which another sort takes over, by one workgroup and by
+    several); twice: some rows name such a source twice."""
+    torch, B = env
+    from oracle import sampler_oracle as S
+    r = np.random.default_rng(n + pad)
+    lens = [1, 2, 7, 8, 9, 10, 63, 64, 65, 66, 128, 257, 700] * 3 + [0] * 5 + [3] * 1200
+    rows = [r.permutation(n)[:m] for m in lens]
+    if twice:
+        rows = [np.concatenate([x, x[:2]]) if j % 2 and len(x) > 8 else x for j, x in enumerate(rows)]
+    src = np.repeat(np.arange(len(lens)), [len(x) for x in rows])
+    rows = np.concatenate(rows)
+    order = r.permutation(len(rows))
+    order = order[np.argsort(rows[order], kind="stable")]      # a row's sources in any order
+    col = src[order].astype(np.int32)
+    end = np.cumsum(np.bincount(rows, minlength=n)).astype(np.int32)
+    start = np.concatenate([[0], end[:-1]]).astype(np.int32)
+    want = S.transpose_block(start, end, col, len(lens))
+    nnz = len(col) + pad
+    t_start, t_end = (torch.zeros(len(lens), dtype=torch.int32, device="cuda") for _ in range(2))
+    t_row = torch.zeros(nnz, dtype=torch.int32, device="cuda")
+    wsb = B.fg_transpose_block_workspace_bytes(len(lens))
+    ws = torch.zeros(wsb, dtype=torch.uint8, device="cuda")
+    col_t = dev(torch, np.concatenate([col, np.zeros(pad, dtype=np.int32)]))
+    B.fg_transpose_block(dev(torch, start), dev(torch, end), col_t, None, n, None, len(lens), nnz, t_start, t_end, t_row, ws, wsb)
+    assert t_start.tolist() == want[0] and t_end.tolist() == want[1] and t_row.tolist()[:len(col)] == want[2]
+
+
 # ------------------------------------------------------------------------------------------------ access-aware admission
 
 @pytest.mark.parametrize("n,n_src,max_deg,seed", [(0, 5, 3, 0), (1, 1, 0, 1), (700, 3000, 12, 2), (5000, 40000, 30, 3), (300, 300, 2500, 4)])
