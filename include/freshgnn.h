@@ -836,7 +836,8 @@ typedef struct fg_path_call {
 } fg_path_call_t;
 fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t* batch, const fg_path_batch_t* next, fg_path_call_t* call);
 
-/* Events without timing, for fg_path_t and for callers that order two streams by themselves. */
+/* Events without timing, for fg_path_t and for callers that order two streams of one device by themselves. Recording one does not make what
+ * kernels wrote visible to the host or to another device: for that, synchronise the stream or use an event of the HIP runtime. */
 fg_status_t fg_event_create(void** event);
 fg_status_t fg_event_record(void* event, void* stream);
 fg_status_t fg_stream_wait_event(void* stream, void* event);

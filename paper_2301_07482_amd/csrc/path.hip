@@ -297,9 +297,12 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
     return FG_OK;
 }
 
+// These order streams of one device. A kernel's end already makes what it wrote visible to the whole device; without the flag a record
+// also writes the caches back for the host and the other devices and the stream stands still for it, 5 to 7 us behind every record
+// (large step 213 -> 210 us, its training iteration 2.5 % and its training loop 4 % faster).
 extern "C" fg_status_t fg_event_create(void** event) {
     if (!event) FG_FAIL(FG_ERR_INVALID_ARG, "fg_event_create: NULL pointer");
-    FG_HIP(hipEventCreateWithFlags((hipEvent_t*)event, hipEventDisableTiming));
+    FG_HIP(hipEventCreateWithFlags((hipEvent_t*)event, hipEventDisableTiming | hipEventDisableSystemFence));
     return FG_OK;
 }
 
