@@ -823,7 +823,7 @@ typedef struct fg_path_call {
     const float* bias[FG_PATH_MAX_LAYERS + 1];
     float p_grad;
     int32_t update;            /* update the cache at the end */
-    int32_t overlap;           /* selection or weight gradients on P->side */
+    int32_t overlap;           /* selection, weight gradients or the update beside them on P->side */
     int32_t fetch_with_loader; /* the cached rows ride in the id-column loader's launch */
     int32_t ahead;             /* the weight gradients of layers 2 .. L go to P->side before layer 2's backward pass */
     int32_t promised;          /* the previous call ran a top-down pass ahead ... */

@@ -88,8 +88,9 @@ struct Iter {
     }
     void* ws_update() const { return (char*)P.ws_update + it % 2 * P.ws_update_stride; }
 
-    fg_status_t weight_grads(const fg_path_batch_t& b, int first, int last, void* stream) const {
-        fg_weight_grad_layer_t y[FG_PATH_MAX_LAYERS] = {};
+    // `behind`: layers whose weight gradients may still be under way on the other stream; theirs is the front of the workspace
+    fg_status_t weight_grads(const fg_path_batch_t& b, int first, int last, void* stream, int behind = 0) const {
+        fg_weight_grad_layer_t y[FG_PATH_MAX_LAYERS] = {}, up[FG_PATH_MAX_LAYERS] = {};
         for (int l = first; l <= last; ++l) {
             fg_weight_grad_layer_t& w = y[l - first];
             // (a GCN layer's input rows are the propagated rows: by-position half, then list-order half)
@@ -115,7 +116,28 @@ struct Iter {
             w.d_in = width;
             w.d_out = P.dims[l];
         }
-        return fg_backward_weights_all((fg_dtype_t)P.compute_dtype, last - first + 1, y, P.ws_weights, P.ws_weights_bytes, stream);
+        for (int i = 0; i < behind; ++i) {
+            up[i].max_rows = b.layer[last + 1 + i].n;
+            up[i].d_in = gcn() ? P.dims[last + i] / 2 : P.dims[last + i];
+            up[i].d_out = P.dims[last + 1 + i];
+        }
+        size_t front = behind ? fg_backward_weights_all_workspace_bytes((fg_dtype_t)P.compute_dtype, behind, up) : 0;
+        if (front > P.ws_weights_bytes) front = P.ws_weights_bytes;      // (refused by the call)
+        return fg_backward_weights_all((fg_dtype_t)P.compute_dtype, last - first + 1, y, (char*)P.ws_weights + front, P.ws_weights_bytes - front, stream);
+    }
+
+    // Whether the weight gradients take longer than the cache update beside them: 17 us and 18.5 per 10^9 products (in bf16 six times as
+    // many) against 25 us and 1.2 per MB of admitted rows, from traces. Iterations with the update / with the weight gradients on the
+    // second stream, us: 67 k x 256 x 256 377 / 385, GCN 313 / 317, mixed 16 k x 1536 x 1024 289 / 295, training loop 403 / 414, 30 k x 192 x 144
+    // 189 / 198; where the rule says no 31 k x 104 x 88 181 / 175, 34 k x 116 x 64 172 / 166, GCN 37 k x 96 x 256 admitting 0.9 of its rows 194 / 191.
+    bool weights_last(const fg_path_batch_t& b) const {
+        double products = 0.0, admitted = 0.0;
+        for (int l = 1; l <= P.n_layers; ++l) {
+            const double n = (double)b.layer[l].n;
+            products += n * (gcn() ? 1 : 2) * P.dims[l - 1] * P.dims[l] / (P.compute_dtype == FG_BF16 ? 6.0 : 1.0);
+            if (l < P.n_layers) admitted += (double)C.p_grad * n * (double)row_bytes(l);
+        }
+        return 17.0 + 18.5e-9 * products > 25.0 + 1.2e-6 * admitted;
     }
 
     fg_status_t forward(const fg_path_batch_t& b, bool once, const fg_fetch_layer_t* fetch, int n_fetch) const {
@@ -173,20 +195,23 @@ struct Iter {
         return FG_OK;
     }
 
-    // the embedding gradients and their norms; weight gradients on the second stream (`beside`) or here
-    fg_status_t backward(const fg_path_batch_t& b, bool beside) const {
+    // the second stream goes on behind what this one has queued
+    fg_status_t side_follows() const {
+        FG_HIP(hipEventRecord((hipEvent_t)P.ev_gradients, (hipStream_t)C.stream));
+        FG_HIP(hipStreamWaitEvent((hipStream_t)P.side, (hipEvent_t)P.ev_gradients, 0));
+        return FG_OK;
+    }
+    // the embedding gradients and their norms; `ahead`: with the weight gradients of the upper layers on the second stream
+    fg_status_t backward(const fg_path_batch_t& b, bool ahead) const {
         const int L = P.n_layers;
         void* st = C.stream;
-        auto weights_beside = [&](int first, int last) -> fg_status_t {
-            FG_HIP(hipEventRecord((hipEvent_t)P.ev_gradients, (hipStream_t)st));
-            FG_HIP(hipStreamWaitEvent((hipStream_t)P.side, (hipEvent_t)P.ev_gradients, 0));
-            return weight_grads(b, first, last, P.side);
-        };
-        const bool ahead = beside && C.ahead && L > 1;
         FG_TRY(fg_softmax_xent_grad((const float*)P.h[L], (int64_t)P.dims[L] * 4, b.labels_dev, (int32_t)b.layer[L].n, P.dims[L], P.dh[L], (int64_t)P.dims[L] * 4, st));
         const auto layer_backward = gcn() ? fg_layer_backward_gcn : fg_layer_backward;
         for (int l = L; l > 1; --l) {
-            if (l == 2 && ahead) FG_TRY(weights_beside(2, L));
+            if (l == 2 && ahead) {
+                FG_TRY(side_follows());
+                FG_TRY(weight_grads(b, 2, L, P.side));
+            }
             const fg_path_layer_t& B = b.layer[l];
             const int32_t n = (int32_t)B.n, n_in = (int32_t)b.layer[l - 1].n;
             const void* h = l < L ? P.h[l] : nullptr;
@@ -202,8 +227,7 @@ struct Iter {
                                       B.t_end_dev, B.t_row_dev, B.nnz, n_in, P.dims[l - 1], P.dims[l], (const float*)C.w[l], P.dh[l - 1], dh_in_b, P.gnorm[l - 1],
                                       P.ws_backward, P.ws_backward_bytes, st));
         }
-        if (!P.weight_grads) return FG_OK;
-        return beside ? weights_beside(1, ahead ? 1 : L) : weight_grads(b, 1, L, st);
+        return FG_OK;
     }
 };
 
@@ -278,8 +302,13 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
         }
     }
     FG_TRY(I.forward(*batch, once, fetch, n_fetch));
-    const bool weights_beside = P.backward && P.weight_grads && call->overlap;
-    if (P.backward) FG_TRY(I.backward(*batch, weights_beside));
+    // A training iteration ends with its weight gradients and the cache update beside each other. The longer of the two stays on this stream,
+    // where it does not wait for an event to be seen by the other one.
+    const bool train = P.backward && P.weight_grads, two_streams = train && call->overlap, ahead = two_streams && call->ahead && L > 1;
+    if (P.backward) FG_TRY(I.backward(*batch, ahead));
+    const bool update_beside = two_streams && do_update && I.weights_last(*batch), weights_beside = two_streams && !update_beside;
+    if (two_streams) FG_TRY(I.side_follows());
+    if (train) FG_TRY(I.weight_grads(*batch, 1, ahead ? 1 : L, weights_beside ? side : main, ahead ? L - 1 : 0));
     if (call->selected) {      // only the admitted rows are left to copy: by the next call, if its top-down pass is on the second stream
         if (!call->next_pruned) {
             FG_HIP(hipStreamWaitEvent(main, (hipEvent_t)P.ev_selected, 0));
@@ -288,9 +317,9 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
         }
     } else if (do_update) {
         I.update_specs(*batch, P.backward != 0, call->specs);
-        FG_TRY(fg_cache_update_all(call->cache, call->iter, call->p_grad, L - 1, call->specs, I.ws_update(), P.ws_update_bytes, main));
+        FG_TRY(fg_cache_update_all(call->cache, call->iter, call->p_grad, L - 1, call->specs, I.ws_update(), P.ws_update_bytes, update_beside ? side : main));
     }
-    if (weights_beside) {      // the next iteration overwrites what the weight gradients read
+    if (two_streams) {      // the next iteration reads the cache, and overwrites what the weight gradients read
         FG_HIP(hipEventRecord((hipEvent_t)P.ev_weights, side));
         FG_HIP(hipStreamWaitEvent(main, (hipEvent_t)P.ev_weights, 0));
     }

@@ -2126,6 +2126,8 @@ def test_iterations_queued_back_to_back_match_one_at_a_time(env):
     ("host", dict(fused_input=True)),
     ("mixed", dict(fused_input=True)),
     ("mixed", dict(fused_input=True, backward=True, weight_grads=True)),
+    ("mixed, few admitted", dict(fused_input=True, backward=True, weight_grads=True)),      # these two: the update beside the weight gradients
+    ("wide", dict(fused_input=True, backward=True, weight_grads=True)),
 ])
 @pytest.mark.parametrize("col_ids", [True, False])
 def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, kwargs, col_ids):
@@ -2137,6 +2139,10 @@ def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, k
     w = wl.WORKLOADS["tiny"]
     if workload == "host":       # 512 x 10 x 5 edges of 128 values: every input row is read once
         w = dataclasses.replace(w, feat_location="host", feat_dim=256, batch=512)
+    if workload == "wide":       # weight gradients that take longer than the update (3 * 10^9 products, 2 MB of rows)
+        w = dataclasses.replace(w, num_nodes=40_000, num_edges=1_200_000, feat_dim=256, hidden=512, fanouts=(4, 22), batch=512, p_grad=0.1)
+    if workload == "mixed, few admitted":
+        workload, w = "mixed", dataclasses.replace(w, p_grad=0.02)
     if workload == "mixed":      # wide enough for the upper layers' weight gradients to go ahead (8 Mi values in layer 1)
         w = dataclasses.replace(w, num_nodes=40_000, num_edges=1_200_000, feat_dim=72, feat_dtype="f16", compute_dtype="bf16", hidden=1280,
                                 fanouts=(4, 22), batch=512)
