@@ -35,7 +35,7 @@
 namespace {
 
 struct UpdHeader {        // lives at the start of a layer's update workspace
-    uint32_t tau_key;     // order-preserving key of tau
+    uint32_t tau_key;     // order-preserving key of tau, or its leading digits where no smaller key shares them
     int32_t mode;         // 0: nothing is below tau, 1: compare with tau_key, 2: everything is below tau
     int64_t n_admit;      // rows to copy (<= capacity)
     int64_t m_live;
@@ -499,9 +499,12 @@ __global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
     int mode = 1;
     if (parts > 1 && part == 0 && t < 4 && L.stats) grp_store(&L.stats[t], (int64_t)0);
     __syncthreads();
-    // tau is the key of rank k, found digit by digit (11 + 11 + 10 bits); mode is the same for all workgroups of the layer
+    // tau is the key of rank k, found digit by digit (11 + 11 + 10 bits); mode is the same for all workgroups of the layer. A key that is the
+    // smallest of those with its digits so far divides the others as these digits with zeros behind them do: of a few thousand norms
+    // two digits are as good as always enough.
+    bool exact = false;
 #pragma unroll 1
-    for (int pass = 0; pass < 3 && mode == 1; ++pass) {
+    for (int pass = 0; pass < 3 && mode == 1 && !exact; ++pass) {
         const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
         const uint32_t bins = pass == 2 ? 1023u : 2047u;
         const uint32_t above = pass == 0 ? 0u : (pass == 1 ? 0xFFE00000u : 0xFFFFFC00u);      // the digits found so far
@@ -538,6 +541,7 @@ __global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
             find_bin(c0, c1, lo, rank, &s_found[pass]);
             __syncthreads();
             tau_key |= s_found[pass].x << shift;
+            exact = s_found[pass].y == 0;
         }
     }
     // check-outs and admissible nodes
@@ -668,7 +672,7 @@ __global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
         static_assert(sizeof(hist) >= GRP_CHUNK * sizeof(int2), "every position may be admitted");
         typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
         const int pieces = (int)(L.row_bytes >> 4), items = (int)(total < L.room ? total : L.room) * pieces;
-        constexpr int TOGETHER = 4;
+        constexpr int TOGETHER = 8;
         for (int i0 = t; i0 < items; i0 += TOGETHER * SEL_THREADS) {
             u32x4 v[TOGETHER];
 #pragma unroll
