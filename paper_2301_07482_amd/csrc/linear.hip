@@ -684,8 +684,11 @@ constexpr int SK_PART_BYTES = PL_WAVES * 16 * 64 * 8;  // partial sums: [wavefro
 
 // FUSE: the neighbour means are not read from `agg` but formed here from the block (fg_aggregate's arithmetic: fp64 sum
 // in neighbour order, one division, one rounding to fp32), so a layer with few rows needs one launch instead of two.
-// MASKED: the product of the backward pass, as in the panel kernel (2 * d_in values a row, a multiple of 64).
-template <bool FUSE, bool MASKED = false>
+// MASKED: the product of the backward pass, as in the panel kernel (2 * d_in values a row).
+// RAGGED (not with FUSE): d_in (MASKED: 2 * d_in) is not a multiple of 32 and is walked as the next one, with zeros for weights and values; products
+// are those of the panel kernel, which took these widths before: 777 rows x 176 x 88 10.2 -> 6.4 us, masked 10.0 -> 6.3, and 3.8e-8 from
+// the exact result (2-norm; 400 to 1024 rows of 36 to 248 columns) instead of 5e-8 to 13e-8, since 32 k values at a time are folded into fp64.
+template <bool FUSE, bool MASKED = false, bool RAGGED = false>
 __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
     const char* __restrict__ h_src, int n_src, int64_t src_stride, const char* __restrict__ agg, int64_t agg_stride,
     const int32_t* __restrict__ rows, const int64_t* __restrict__ n_rows_dev, int64_t max_rows, int d_in, int d_out,
@@ -693,8 +696,20 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
     int64_t out_stride, int n_panels, const int32_t* __restrict__ row_start, const int32_t* __restrict__ row_end,
     const int32_t* __restrict__ col, int64_t nnz, int n_block_rows, const int32_t* __restrict__ src_ids) {
     extern __shared__ __attribute__((aligned(16))) float panel[];  // [K][32], later the partial sums
+    static_assert(!(FUSE && RAGGED), "means are formed a whole chunk at a time");
     const int K = 2 * d_in;
-    const int nk = K / KC, nk_self = d_in / KC;
+    const int nk_self = RAGGED && !MASKED ? (d_in + KC - 1) / KC : d_in / KC;
+    const int nk = !RAGGED ? K / KC : (MASKED ? (K + KC - 1) / KC : 2 * nk_self);
+    // walked k -> whether it exists, and its row of W
+    auto real_k = [&](int kw, int& wrow) {
+        if constexpr (MASKED) {
+            wrow = kw < K ? kw : 0;
+            return kw < K;
+        }
+        const int hf = kw >= nk_self * KC ? 1 : 0, kk = kw - hf * nk_self * KC;
+        wrow = kk < d_in ? hf * d_in + kk : 0;
+        return kk < d_in;
+    };
     const int xcd = blockIdx.x & 7;
     const int j = blockIdx.x >> 3;
     const int n0 = (j % n_panels) * PL_BN;
@@ -722,16 +737,19 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
     // this wavefront's rows of the panel: two chunks of 32 x 32 at most (the panel is at most 64 KB)
     constexpr int W_PIECES = 2 * KC * 8 / 64;
     f32x4 w_piece[W_PIECES];
+    bool w_in[W_PIECES];      // RAGGED
 #pragma unroll
     for (int u = 0; u < W_PIECES; ++u) {
         if constexpr (MASKED) {      // four values of a row of W: column (lane + 64 u) % 32 of the panel
             const int col = lane & 31, kq = (lane + 64 * u) >> 5, i = kq / (KC / 4);
-            const int kk = i < cnt ? chunk_of(i) * KC + kq % (KC / 4) * 4 : 0;
+            int kk = i < cnt ? chunk_of(i) * KC + kq % (KC / 4) * 4 : 0;
+            if constexpr (RAGGED) w_in[u] = real_k(kk, kk);
             w_piece[u] = *(const f32x4a*)(W + (int64_t)(n0 + col < d_out ? n0 + col : 0) * K + kk);
             continue;
         }
         const int idx = (lane + 64 * u) >> 3, c4 = ((lane + 64 * u) & 7) * 4, i = idx / KC;
-        const int kk = i < cnt ? chunk_of(i) * KC + idx % KC : 0;
+        int kk = i < cnt ? chunk_of(i) * KC + idx % KC : 0;
+        if constexpr (RAGGED) w_in[u] = real_k(kk, kk);
         w_piece[u] = *(const f32x4*)(W + (int64_t)kk * d_out + (n0 + c4 < d_out ? n0 + c4 : 0));
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -765,8 +783,9 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
             f32x4 m[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                a[q] = *(const f32x4a*)(a_self + s * KC + 4 * q);
-                m[q] = *(const f32x4a*)(a_agg + s * KC + 4 * q);
+                const bool there = !RAGGED || s * KC + 16 * half + 4 * q < K;
+                a[q] = *(const f32x4a*)(there ? a_self + s * KC + 4 * q : (const float*)x3_zero);
+                m[q] = *(const f32x4a*)(there ? a_agg + s * KC + 4 * q : (const float*)x3_zero);
             }
 #pragma unroll
             for (int q = 0; q < 16; ++q) {
@@ -778,7 +797,10 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
         if (!FUSE || s < nk_self) {
             const float* p = a_ptr(s);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) a[q] = *(const f32x4*)(p + 4 * q);
+            for (int q = 0; q < 4; ++q) {
+                const bool there = !RAGGED || (s < nk_self ? s : s - nk_self) * KC + 16 * half + 4 * q < d_in;
+                a[q] = *(const f32x4*)(there ? p + 4 * q : (const float*)x3_zero);
+            }
             return;
         }
         double acc[16];
@@ -820,12 +842,12 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
             const int col = lane & 31, kq = (lane + 64 * u) >> 5, i = kq / (KC / 4);
             if (i < cnt)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) panel[(chunk_of(i) * KC + kq % (KC / 4) * 4 + e) * PL_BN + col] = n0 + col < d_out ? w_piece[u][e] : 0.f;
+                for (int e = 0; e < 4; ++e) panel[(chunk_of(i) * KC + kq % (KC / 4) * 4 + e) * PL_BN + col] = n0 + col < d_out && (!RAGGED || w_in[u]) ? w_piece[u][e] : 0.f;
             continue;
         }
         const int idx = (lane + 64 * u) >> 3, c4 = ((lane + 64 * u) & 7) * 4, i = idx / KC;
         const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-        if (i < cnt) *(f32x4*)(panel + (chunk_of(i) * KC + idx % KC) * PL_BN + c4) = n0 + c4 < d_out ? w_piece[u] : z;
+        if (i < cnt) *(f32x4*)(panel + (chunk_of(i) * KC + idx % KC) * PL_BN + c4) = n0 + c4 < d_out && (!RAGGED || w_in[u]) ? w_piece[u] : z;
     }
     double sum[16];
 #pragma unroll
@@ -837,6 +859,29 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[i] = 0.f;
         const float* brow = bcol + s * KC * PL_BN;
+        if constexpr (RAGGED) {      // the panel kernel's products, so that no width is further from the exact ones than there
+            f32x16 rest = acc;
+            float av[16], bw[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                av[q] = a[q >> 2][q & 3];
+                bw[q] = brow[q * PL_BN];
+            }
+            constexpr int TA[5] = {2, 0, 1, 1, 0}, TW[5] = {0, 2, 1, 0, 1};
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                u32x4 A[3], F[3];
+                split8(av + 8 * m, A[0], A[1], A[2]);
+                split8(bw + 8 * m, F[0], F[1], F[2]);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, A[0]), __builtin_bit_cast(bf16x8, F[0]), acc, 0, 0, 0);
+#pragma unroll
+                for (int e = 0; e < 5; ++e)
+                    rest = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, A[TA[e]]), __builtin_bit_cast(bf16x8, F[TW[e]]), rest, 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sum[i] += (double)acc[i] + (double)rest[i];
+            return;
+        }
 #pragma unroll
         for (int q = 0; q < 16; ++q)
             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q >> 2][q & 3], brow[q * PL_BN], acc, 0, 0, 0);
@@ -888,16 +933,18 @@ fg_status_t fg_launch_linear_bf16(const void* h_src, int32_t n_src, int64_t src_
 fg_status_t fg_launch_linear_masked(const float* dh, int64_t dh_stride, const float* h, int64_t h_stride, int32_t n, const int32_t* rows_dev,
                                     const int64_t* n_rows_dev, int64_t max_rows, int32_t d_out, int32_t cols, const float* W, float* dx, hipStream_t st, bool* done) {
     const int64_t n_tasks = fg_ceil_div(max_rows, 32) * fg_ceil_div(cols, PL_BN);
-    const size_t panel_bytes = (size_t)d_out * PL_BN * sizeof(float);
+    const bool whole = d_out % KC == 0;
+    const size_t panel_bytes = (size_t)fg_ceil_div(d_out, KC) * KC * PL_BN * sizeof(float);
     const int k_pad = (int)(fg_ceil_div(d_out, 2 * KC) * 2 * KC);      // the loop over K takes two chunks at a time
     const size_t x3_bytes = (size_t)k_pad * 192;
     *done = true;
     const int64_t out_stride = (int64_t)cols * 4;
-    if (d_out % (2 * KC) == 0 && panel_bytes <= 64 * 1024 && n_tasks <= 288) {      // (as fg_linear chooses)
+    if (panel_bytes <= 64 * 1024 && n_tasks <= 288) {      // (as fg_linear chooses)
         const int n_panels = (int)fg_ceil_div(cols, PL_BN);
         const size_t lds = panel_bytes > (size_t)SK_PART_BYTES ? panel_bytes : (size_t)SK_PART_BYTES;
         const unsigned grid = (unsigned)(fg_ceil_div(fg_ceil_div(max_rows, 32), 8) * 8 * n_panels);
-        hipLaunchKernelGGL((linear_f32_splitk_kernel<false, true>), dim3(grid), dim3(PL_THREADS), lds, st, (const char*)dh, n, dh_stride,
+        hipLaunchKernelGGL((whole ? linear_f32_splitk_kernel<false, true> : linear_f32_splitk_kernel<false, true, true>), dim3(grid),
+                           dim3(PL_THREADS), lds, st, (const char*)dh, n, dh_stride,
                            (const char*)h, h_stride, rows_dev, n_rows_dev, max_rows, d_out / 2, cols, W, nullptr, 0, (char*)dx, n, out_stride,
                            n_panels, nullptr, nullptr, nullptr, (int64_t)0, 0, nullptr);
         FG_LAUNCH_CHECK("linear_f32_splitk_kernel (masked)");
@@ -953,14 +1000,15 @@ static fg_status_t linear_launch(const char* who, const void* h_src, int32_t n_s
         fg_clear_error();
         if (max_rows == 0) return FG_OK;
         const int64_t forced = fg_tuning(FG_TUNE_LINEAR_TILE);
-        const size_t panel_bytes = (size_t)2 * d_in * PL_BN * sizeof(float);
+        const size_t panel_bytes = (size_t)2 * fg_ceil_div(d_in, KC) * KC * PL_BN * sizeof(float);
         if (n_src == 0 || n_out == 0) return FG_OK;  // no row can be in range
         const int64_t n_tasks = fg_ceil_div(max_rows, 32) * fg_ceil_div(d_out, PL_BN);
-        if (d_in % KC == 0 && panel_bytes <= 64 * 1024 && (forced == 8 || (forced == 0 && n_tasks <= 288))) {
+        if (panel_bytes <= 64 * 1024 && ((forced == 8 && d_in % KC == 0) || (forced == 0 && n_tasks <= 288))) {
             const int n_panels = (int)fg_ceil_div(d_out, PL_BN);
             const size_t lds = panel_bytes > (size_t)SK_PART_BYTES ? panel_bytes : (size_t)SK_PART_BYTES;
             const unsigned grid = (unsigned)(fg_ceil_div(fg_ceil_div(max_rows, 32), 8) * 8 * n_panels);
-            hipLaunchKernelGGL(linear_f32_splitk_kernel<false>, dim3(grid), dim3(PL_THREADS), lds, st, (const char*)h_src, n_src,
+            hipLaunchKernelGGL((d_in % KC == 0 ? linear_f32_splitk_kernel<false> : linear_f32_splitk_kernel<false, false, true>), dim3(grid),
+                               dim3(PL_THREADS), lds, st, (const char*)h_src, n_src,
                                src_stride, (const char*)agg, agg_stride, rows_dev, n_rows_dev, max_rows, d_in, d_out,
                                (const float*)W, bias, relu, (char*)h_out, n_out, out_stride, n_panels, nullptr, nullptr, nullptr,
                                (int64_t)0, 0, src_ids_dev);

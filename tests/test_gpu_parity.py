@@ -370,6 +370,16 @@ def test_linear_matches_oracle(env, d_in, d_out, n_rows, max_rows, relu, variant
     assert err <= REL_TOL_F32
 
 
+@pytest.mark.parametrize("max_rows", [1, 1024, 1025])      # 9 column panels: up to 1024 rows a workgroup per 32 x 32 results
+@pytest.mark.parametrize("d_in", [4, 28, 36, 132, 224, 228, 252, 260])
+def test_linear_of_few_rows_of_any_width(env, d_in, max_rows):
+    """Widths around multiples of 32 whose K is shared out between the wavefronts of a workgroup (one or two chunks each, some none), the
+    widest that is and the next, on both sides of the number of rows up to which they are."""
+    torch, B = env
+    got, want, _, _ = _linear_case(torch, B, np.random.default_rng(d_in), max_rows + 50, max(1, max_rows - 7), max_rows, d_in, 260, False)
+    assert T.rel_err_rows(got, want) <= REL_TOL_F32
+
+
 @pytest.mark.parametrize("variant", [0, 301, 302, 32, 64])
 @pytest.mark.parametrize("d_in,d_out", [(100, 256), (36, 64), (4, 32), (28, 96)])
 def test_linear_width_not_a_multiple_of_32_ignores_what_follows_a_row(env, d_in, d_out, variant):
