@@ -688,6 +688,7 @@ constexpr int SK_PART_BYTES = PL_WAVES * 16 * 64 * 8;  // partial sums: [wavefro
 // RAGGED (not with FUSE): d_in (MASKED: 2 * d_in) is not a multiple of 32 and is walked as the next one, with zeros for weights and values; products
 // are those of the panel kernel, which took these widths before: 777 rows x 176 x 88 10.2 -> 6.4 us, masked 10.0 -> 6.3, and 3.8e-8 from
 // the exact result (2-norm; 400 to 1024 rows of 36 to 248 columns) instead of 5e-8 to 13e-8, since 32 k values at a time are folded into fp64.
+// Beyond 288 tasks the panel kernel stays the faster one for these widths too (up to 768 here: iterations of 64 to 174 us 2 to 6 % slower).
 template <bool FUSE, bool MASKED = false, bool RAGGED = false>
 __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
     const char* __restrict__ h_src, int n_src, int64_t src_stride, const char* __restrict__ agg, int64_t agg_stride,
