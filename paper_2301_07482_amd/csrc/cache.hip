@@ -353,9 +353,9 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void classify_update_kernel(UpdBatch
 // What bounds the four launches is not their work but their chain: each is a few dependent reads, barriers
 // and scans long (6 + 9 + 13 + 6 us at 1.2 k positions, hardly more at 54 k), and workgroups of 1024 threads wait for room beside the
 // weight gradients (the third launch, 72 of them at 67 k positions, 33 us there). A workgroup of 1024 threads holds the keys of
-// 4096 positions in registers (four per thread), so it reads them once, finds tau by three digits,
+// 4096 positions in registers (four per thread), so it reads them once, finds tau by up to three digits,
 // classifies, ranks the admissible nodes and hands out their slots. By itself it finds the digits in LDS; the workgroups of a larger
-// layer meet four times: behind the histogram of each digit, and behind the check-outs, with the numbers of admissible nodes. (The keys that
+// layer meet up to four times: behind the histogram of each digit, and behind the check-outs, with the numbers of admissible nodes. (The keys that
 // carry the first digit as a list, from which each workgroup finds the other two for itself: a meeting less, but up to a third of
 // a layer's norms share a digit, and at 67 k positions the list took 5 + 6 us, 5 + 11 in a GCN, for 9 of two meetings.) The
 // histograms are kept four times (by lane mod 4): norms share their leading digits, and equal bins of a wavefront are
@@ -364,9 +364,9 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void classify_update_kernel(UpdBatch
 // with room for 512 of their size, and a launch they have to wait behind ends without them. The polls are bounded all the same.
 // Between the barriers the chain is kept short: prefix sums inside the vector registers, a wavefront's place among the others' totals from
 // four wide LDS reads, each thread clearing the counters it read, no division (with shuffles, a loop over the wavefronts and 64-bit
-// remainders 17.6 us at 1.2 k positions, 14.2 so; a third of what is left is the row copy and the first reads).
+// remainders 17.6 us at 1.2 k positions, 14.2 so, 12.9 with two digits where they decide; a third of what is left is the row copy and the first reads).
 // Measured, the four launches and now: 28 k positions 36 us and their gaps, 24; 74 k beside the weight gradients of 55 k rows 66, 27; 1.2 k with
-// its row copy 31, 14 (one workgroup).
+// its row copy 31, 13 (one workgroup).
 constexpr int ONE_COPIES = 4;
 constexpr int SEL_WAVES = SEL_THREADS / FG_WAVE;
 constexpr int GRP_CHUNK = 4 * SEL_THREADS;      // positions of a workgroup
