@@ -30,6 +30,7 @@
 // for and waited for: 204 us, now 154.
 #include "common.h"
 #include "scan.h"
+#include "stage_queue.h"
 
 namespace {
 
@@ -1020,43 +1021,35 @@ SmpWs smp_layout(int32_t n_layers, const fg_sample_layer_t* layers) {
     return w;
 }
 
-// The stages of the transposes that are still to be done, oldest first. Every launch of the sampler takes the next stage of the
-// first TR_MAX_RIDES of them along.
+// The stages of the transposes that are still to be done. Every launch of the sampler takes the next stage of the first
+// TR_MAX_RIDES of them along.
 struct TrQueue {
-    struct Entry {
-        TrArgs a;
-        int32_t stage[4];
-        int n, next;
-    } e[SMP_MAX_LAYERS];
-    int first = 0, count = 0;
+    FgStageQueue<TrArgs, SMP_MAX_LAYERS, 4> q;
 
+    bool empty() const { return q.empty(); }
     static int64_t blocks_of(const TrArgs& a, int stage, int threads) {
         if (stage == TR_COUNT || stage == TR_FILL) return fg_ceil_div(a.max_rows, threads / TR_LANES);
         return fg_ceil_div(a.max_src, stage == TR_SUM ? TR_THREADS : threads);
     }
     void add(const TrArgs& a) {      // the edges are counted
         if (a.max_src == 0) return;
-        Entry& q = e[first + count++];
-        q.a = a;
-        q.n = q.next = 0;
+        auto& e = q.add(a);
         const bool direct = a.max_src <= TR_DIRECT;
-        if (!direct) q.stage[q.n++] = TR_SUM;
-        q.stage[q.n++] = direct ? TR_SCAN : TR_SCAN_SUMS;
+        if (!direct) e.then(TR_SUM);
+        e.then(direct ? TR_SCAN : TR_SCAN_SUMS);
         if (a.max_rows > 0) {
-            q.stage[q.n++] = TR_FILL;
-            q.stage[q.n++] = TR_SORT;
+            e.then(TR_FILL);
+            e.then(TR_SORT);
         }
     }
     TrRides take(int threads) {      // for a launch with workgroups of that size
         TrRides r{};
-        for (int i = first; i < first + count && r.n < TR_MAX_RIDES; ++i) {
-            Entry& q = e[i];
-            r.a[r.n] = q.a;
-            r.stage[r.n] = q.stage[q.next++];
-            r.blocks += (int32_t)blocks_of(q.a, r.stage[r.n], threads);
+        q.take(TR_MAX_RIDES, [&](const TrArgs& a, int stage) {
+            r.a[r.n] = a;
+            r.stage[r.n] = stage;
+            r.blocks += (int32_t)blocks_of(a, stage, threads);
             r.end[r.n++] = r.blocks;
-        }
-        while (count > 0 && e[first].next == e[first].n) ++first, --count;
+        });
         return r;
     }
 };
@@ -1202,7 +1195,7 @@ fg_status_t smp_launch(const char* who, const int64_t* indptr, const int32_t* in
             queue.add(TrArgs{y.row_start_dev, y.row_end_dev, y.col_dev, rows_dev, y.max_rows, y.counts_dev, y.max_below,
                              y.max_rows * y.fanout, y.t_start_dev, y.t_end_dev, y.t_row_dev, (int32_t*)(ws + w.cnt[i]), (int32_t*)(ws + w.blk[i])});
     }
-    while (queue.count > 0) {      // the last block's transpose has nothing left to ride in
+    while (!queue.empty()) {      // the last block's transpose has nothing left to ride in
         fg_status_t rc = tr_launch(queue.take(TR_THREADS), st);
         if (rc != FG_OK) return rc;
     }
@@ -1288,6 +1281,6 @@ extern "C" fg_status_t fg_transpose_block(const int32_t* row_start_dev, const in
     rc = tr_launch(count, st);
     TrQueue queue;
     queue.add(A);
-    while (rc == FG_OK && queue.count > 0) rc = tr_launch(queue.take(TR_THREADS), st);
+    while (rc == FG_OK && !queue.empty()) rc = tr_launch(queue.take(TR_THREADS), st);
     return rc;
 }

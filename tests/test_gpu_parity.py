@@ -888,6 +888,43 @@ def test_sample_minibatch_matches_oracle(env, N, max_deg, hubs, batch, n_seeds, 
                     f"transpose of block {l}"
 
 
+@pytest.mark.parametrize("first,empty", [((100, 600), [(50, True)]), ((0, 200_000), [(50, True)]), ((100, 600), [(200_000, True), (50, True), (7, False)])])
+def test_sample_minibatch_with_an_empty_block_behind_another(env, first, empty):
+    """A block without rows has fewer transpose stages than what is left of the block before it, and no launches of its own: the lists of
+    both are complete, those of the empty one empty, and the call ends."""
+    torch, B = env
+    from oracle import sampler_oracle as S
+    N, fanout, key = 3000, 5, 99
+    indptr, indices = _random_multigraph(N, 20, 1, hubs=2)
+    rows, below = first
+    seeds = np.random.default_rng(0).permutation(N)[:rows]
+    full = lambda n, v=-3, dt=torch.int32: torch.full((max(n, 1),), v, dtype=dt, device="cuda")
+    out, specs = [], []
+    for i, (r, nb, tr) in enumerate([(rows, below, True)] + [(0, nb, tr) for nb, tr in empty]):
+        o = dict(row_start_dev=full(r), row_end_dev=full(r), col_dev=full(r * fanout), ids_below_dev=full(nb), counts_dev=full(2, dt=torch.int64))
+        if tr:
+            o.update(t_start_dev=full(nb), t_end_dev=full(nb), t_row_dev=full(r * fanout))
+        out.append(o)
+        specs.append(dict(o, layer=9 - i, fanout=fanout, max_rows=r, max_below=nb))
+    layers = B.sample_layers(specs)
+    wsb = B.fg_sample_minibatch_workspace_bytes(layers)
+    ws = torch.zeros(wsb, dtype=torch.uint8, device="cuda")
+    B.fg_sample_minibatch(dev(torch, indptr), dev(torch, indices), N, len(indices), dev(torch, seeds.astype(np.int32)) if rows else full(1), None, layers, key,
+                          ws, wsb)
+    torch.cuda.synchronize()
+    for o, (nb, tr) in zip(out[1:], empty):
+        assert o["counts_dev"].tolist() == [0, 0]
+        if tr:
+            assert not o["t_start_dev"].any() and not o["t_end_dev"].any()
+    if rows == 0:
+        assert out[0]["counts_dev"].tolist() == [0, 0] and not out[0]["t_start_dev"].any() and not out[0]["t_end_dev"].any()
+        return
+    nb, nnz = out[0]["counts_dev"].tolist()
+    start, end, col = (out[0][k].cpu().numpy()[:m].tolist() for k, m in (("row_start_dev", rows), ("row_end_dev", rows), ("col_dev", nnz)))
+    t = S.transpose_block(start, end, col, nb)
+    assert [out[0][k].cpu().numpy()[:m].tolist() for k, m in (("t_start_dev", nb), ("t_end_dev", nb), ("t_row_dev", nnz))] == [list(x) for x in t]
+
+
 @pytest.mark.parametrize("n,n_src,deg,src_bound,nnz_bound", [
     (1500, 12288, 8, 12288, 12288), (1500, 12288, 8, 12288, 12289), (1500, 12288, 8, 12289, 12288), (2500, 5, 4, 9, 12000),
     (1024, 7168, 7, 7168, 7168), (1024, 7168, 7, 7168, 7169), (1024, 7168, 7, 7169, 7168), (1536, 6000, 4, 7168, 7168),
