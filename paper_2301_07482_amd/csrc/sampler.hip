@@ -974,8 +974,16 @@ bool smp_is_small(int64_t max_rows, int64_t fanout) {
 }
 
 // Slots per thread of launches 2 and 3: four where one would be more workgroups than the chip holds at a time (two per compute unit)
-int smp_slots(int64_t max_rows, int32_t fanout) { return fg_ceil_div(max_rows, SMP_THREADS / fanout) > 512 ? 4 : 1; }
+constexpr int64_t SMP_ONE_SLOT = 512;
+int smp_slots(int64_t max_rows, int32_t fanout) { return fg_ceil_div(max_rows, SMP_THREADS / fanout) > SMP_ONE_SLOT ? 4 : 1; }
 int64_t smp_blocks(int64_t max_rows, int32_t fanout) { return fg_ceil_div(max_rows, smp_slots(max_rows, fanout) * SMP_THREADS / fanout); }
+// ... and the most workgroups of any number of rows up to max_rows: a workspace serves every call of fewer rows, where one slot per thread may
+// be four times as many workgroups
+int64_t smp_most_blocks(int64_t max_rows, int32_t fanout) {
+    const int64_t one_slot = fg_ceil_div(max_rows, SMP_THREADS / fanout), now = smp_blocks(max_rows, fanout);
+    const int64_t most = one_slot < SMP_ONE_SLOT ? one_slot : SMP_ONE_SLOT;
+    return now > most ? now : most;
+}
 
 size_t tr_layout(int64_t max_src, size_t* blk_at) {
     const size_t src = (size_t)(max_src > 0 ? max_src : 1);
@@ -993,7 +1001,7 @@ SmpWs smp_layout(int32_t n_layers, const fg_sample_layer_t* layers) {
     };
     for (int i = 0; i < n_layers; ++i) {
         const size_t rows = (size_t)(layers[i].max_rows > 0 ? layers[i].max_rows : 1), c = rows * (size_t)layers[i].fanout;
-        const size_t b = (size_t)smp_blocks((int64_t)rows, layers[i].fanout);
+        const size_t b = (size_t)smp_most_blocks((int64_t)rows, layers[i].fanout);
         if (!smp_is_small(layers[i].max_rows, layers[i].fanout)) {
             cands = c > cands ? c : cands;
             blocks = b > blocks ? b : blocks;

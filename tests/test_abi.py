@@ -32,6 +32,20 @@ def test_library_exports_every_declared_symbol(B):
     assert B.fg_version() >= 100
 
 
+@pytest.mark.parametrize("fanout", [1, 2, 3, 5, 7, 8, 10, 11, 12, 15, 16, 25, 31, 32])
+def test_sampling_workspace_of_a_bound_serves_every_smaller_call(B, fanout):
+    """Around the sizes where a block changes its launches (one workgroup or several, one slot per thread or four), and in between."""
+    switch = 512 * (1024 // fanout)      # rows of 512 workgroups with a slot per thread
+    sizes = sorted({*range(0, 1100), *range(switch - 80, switch + 200), *range(3 * switch, 4 * switch + 400, max(switch // 50, 1)), 8 * switch})
+    minibatch = lambda *layers: B.fg_sample_minibatch_workspace_bytes(B.sample_layers([dict(fanout=f, max_rows=n, max_below=n * (1 + f), t_start_dev=t)
+                                                                                      for f, n, t in layers]))
+    for size in (lambda n: B.fg_sample_block_workspace_bytes(n, fanout), lambda n: minibatch((fanout, n, None)),
+                 lambda n: minibatch((fanout, n, 4096), (5, 3000, 4096))):
+        needed = [size(n) for n in sizes]
+        for n, smaller, larger in zip(sizes[1:], needed, needed[1:]):
+            assert larger >= smaller, f"{n} rows need {larger} bytes, fewer {smaller}"
+
+
 def test_argument_validation_needs_no_gpu(B):
     def code(fn, *a, **k):
         with pytest.raises(B.FgError) as e:

@@ -858,6 +858,7 @@ def test_sample_block_routes_match_oracle(env, N, max_deg, n_seeds, fanout, boun
     (9000, 30, 3, 1024, 1000, (10, 5), 1),          # ... by three launches, fewer seeds than the bound
     (300, 30, 40, 64, 64, (10, 10), 2),             # both blocks by one workgroup, few nodes
     (6000, 40, 20, 1100, 1100, (15, 32), 3),        # four slots per thread
+    (20000, 8, 3, 16385, 16384, (32,), 8),          # four slots in the bound, one in the call
     (6000, 40, 3, 4100, 700, (2, 32), 4),           # more than 131 072 sources: four stages for three launches
     (3000, 20, 3, 5, 5, (1,) * 10, 5), (3000, 20, 3, 40, 40, (7,), 6), (3000, 20, 3, 8, 0, (3, 2, 2), 7)])
 def test_sample_minibatch_matches_oracle(env, N, max_deg, hubs, batch, n_seeds, fanouts, seed):
