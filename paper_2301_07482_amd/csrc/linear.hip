@@ -685,7 +685,8 @@ constexpr int SK_PART_BYTES = PL_WAVES * 16 * 64 * 8;  // partial sums: [wavefro
 // FUSE: the neighbour means are not read from `agg` but formed here from the block (fg_aggregate's arithmetic: fp64 sum
 // in neighbour order, one division, one rounding to fp32), so a layer with few rows needs one launch instead of two.
 // MASKED: the product of the backward pass, as in the panel kernel (2 * d_in values a row).
-// RAGGED (not with FUSE): d_in (MASKED: 2 * d_in) is not a multiple of 32 and is walked as the next one, with zeros for weights and values; products
+// RAGGED (not with FUSE): d_in is not a multiple of 32 and is walked as the next one, with zeros for weights and values (MASKED: 2 * d_in is not a
+// multiple of 64 and is walked as the next one of 32); products
 // are those of the panel kernel, which took these widths before: 777 rows x 176 x 88 10.2 -> 6.4 us, masked 10.0 -> 6.3, and 3.8e-8 from
 // the exact result (2-norm; 400 to 1024 rows of 36 to 248 columns) instead of 5e-8 to 13e-8, since 32 k values at a time are folded into fp64.
 // Beyond 288 tasks the panel kernel stays the faster one for these widths too (up to 768 here: iterations of 64 to 174 us 2 to 6 % slower).
@@ -934,7 +935,10 @@ fg_status_t fg_launch_linear_bf16(const void* h_src, int32_t n_src, int64_t src_
 fg_status_t fg_launch_linear_masked(const float* dh, int64_t dh_stride, const float* h, int64_t h_stride, int32_t n, const int32_t* rows_dev,
                                     const int64_t* n_rows_dev, int64_t max_rows, int32_t d_out, int32_t cols, const float* W, float* dx, hipStream_t st, bool* done) {
     const int64_t n_tasks = fg_ceil_div(max_rows, 32) * fg_ceil_div(cols, PL_BN);
-    const bool whole = d_out % KC == 0;
+    // Two whole chunks at a time take plain fp32 instructions, as fg_linear does for halves of whole chunks; other widths the three-way
+    // products, which went to the panel kernel before: 3.3e-8 from exact (2-norm) where that left 3.3e-8 (32 columns) to 8.2e-8 (352) and fp32
+    // instructions leave 7.9e-8
+    const bool whole = d_out % (2 * KC) == 0;
     const size_t panel_bytes = (size_t)fg_ceil_div(d_out, KC) * KC * PL_BN * sizeof(float);
     const int k_pad = (int)(fg_ceil_div(d_out, 2 * KC) * 2 * KC);      // the loop over K takes two chunks at a time
     const size_t x3_bytes = (size_t)k_pad * 192;

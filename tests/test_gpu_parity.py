@@ -1360,6 +1360,27 @@ def test_layer_backward_reads_its_operands_in_place(env, d_in, d_out, n, relu, a
     assert e <= REL_TOL_F32, f"rel err {e:.3e}"
 
 
+@pytest.mark.parametrize("d_in,n", [(48, 300), (88, 900)])
+@pytest.mark.parametrize("d_out", [32, 72, 96, 160, 224, 288, 352])
+def test_layer_backward_of_few_rows_rounds_no_more_than_the_panel_kernel(env, d_in, n, d_out):
+    """Input gradient of few rows whose width is no multiple of 64 against 64-bit sums (a block without edges: the product itself). Values of
+    the three-way products are rounded when 16 of them are added to the 16 before, and as the result: three times 2^-24 / sqrt(3) of a
+    value whose square over its power of two's is 7/3 on average, 3.9e-8 in the 2-norm. A chain of two values at a time would leave 7.5e-8."""
+    torch, B = env
+    r = np.random.default_rng(d_out + n)
+    dh, h = (r.standard_normal((n, d_out)).astype(np.float32) for _ in range(2))
+    W = (r.standard_normal((2 * d_in, d_out)) / np.sqrt(d_in)).astype(np.float32)
+    zero, flags = torch.zeros(n, dtype=torch.int32, device="cuda"), torch.zeros((2, n), dtype=torch.uint8, device="cuda")
+    flags[0] = 1
+    wsb = B.fg_layer_backward_workspace_bytes(n, n, d_in, d_out)
+    ws, out = torch.full((wsb,), 255, dtype=torch.uint8, device="cuda"), torch.full((n, d_in), 7.0, device="cuda")
+    B.fg_layer_backward(dev(torch, dh), d_out * 4, dev(torch, h), d_out * 4, n, torch.arange(n, dtype=torch.int32, device="cuda"), None, n, flags[0], flags[1],
+                        zero, zero, zero, zero, zero, 0, n, d_in, d_out, dev(torch, W), out, d_in * 4, None, ws, wsb)
+    want = np.where(h > 0, dh, 0).astype(np.float64) @ W[:d_in].astype(np.float64).T
+    e = np.linalg.norm(out.cpu().numpy() - want) / np.linalg.norm(want)
+    assert e <= 5e-8, f"rel err {e:.2e}"
+
+
 @pytest.mark.parametrize("kind,layers", [
     ("f32", [(128, 256, 30000, 29001, True), (256, 256, 3000, 2999, True), (256, 64, 300, 250, False)]),       # both tiles, many chunks and few
     ("f32", [(24, 72, 130, 77, True), (72, 8, 40, 0, False)]), ("f32", [(8, 8, 9, 1, False)]),                # one chunk each; an empty layer
