@@ -4,6 +4,7 @@ This module only owns device buffers (torch tensors) and the order of the calls;
 done by the HIP kernels behind `binding`. Nothing is copied back to the host between calls: element
 counts stay in device memory and each call is launched over a static upper bound.
 """
+import ctypes
 import struct
 import sys
 
@@ -246,6 +247,10 @@ def _addr(t):
 
 _LAYERS = B.FG_PATH_MAX_LAYERS + 1
 _PACK_BATCH = [struct.Struct(f"4q{11 * (n + 1)}q") for n in range(_LAYERS)]      # fg_path_batch_t of n layers
+_PACK_MODEL = [struct.Struct(f"{n + 1}q{8 * (_LAYERS - n - 1)}x" * 7) for n in range(_LAYERS)]      # fg_path_t: h .. db
+_PACK_LISTS = [struct.Struct(f"{n + 1}q{8 * (_LAYERS - n - 1)}x" * 5 + "2q") for n in range(_LAYERS)]      # fg_path_lists_t
+_PACK_LOGS = struct.Struct("7q")                                                 # fg_path_t: counts_log .. ws_weights
+_LISTS_BYTES = ctypes.sizeof(B.PathLists)
 _PACK_CALL = struct.Struct(f"4q{3 * _LAYERS}qf6i")                               # fg_path_call_t as far as its flags
 
 
@@ -524,42 +529,43 @@ class HotPath:
         self.ev_done[it % 2].record(main)
 
     def _native_path(self):
-        """The model's buffers as fg_path_run takes them: they are allocated once and stay where they are."""
+        """The structures of fg_path_run, with what of the model stays as it is made here."""
         L, P = self.L, B.Path()
         P.n_layers, P.model, P.feat_dtype, P.compute_dtype = L, B.FG_PATH_GCN if self.model == "gcn" else B.FG_PATH_SAGE, self.feat_code, self.comp_code
-        P.on_host, P.fused_input, P.fuse_small_layers = self.on_host, bool(self.fused_input), self.fuse_small_layers
-        P.backward, P.weight_grads, P.ring, P.num_nodes = bool(self.backward), self.weight_grads, self.ring, self.num_nodes
         P.dims[:L + 1], P.n_max[:L + 1] = self.dims, self.n_max
-
-        def put(field, tensors):
-            for l, t in enumerate(tensors):
-                if t is not None:
-                    field[l] = t.data_ptr()
-        put(P.h, self.H)
-        put(P.agg, self.AGG_l)
-        if self.model == "gcn":
-            put(P.mean_pos, self.MEANPOS_l)
-        if self.backward:
-            put(P.dh, self.dH)
-            put(P.gnorm, self.gnorm)
-            P.ws_backward, P.ws_backward_bytes = self.ws_bw.data_ptr(), self.ws_bw_bytes
-        if self.weight_grads:
-            put(P.dw, self.dW)
-            put(P.db, self.db)
-            P.ws_weights, P.ws_weights_bytes = self.ws_wg.data_ptr(), self.ws_wg_bytes
-        for of, lists in zip(P.lists, self._lists):
-            for name in ("live", "hit", "hit_pos", "hit_slot", "normal_pos"):
-                put(getattr(of, name), lists[name])
-            of.input_ids, of.self_ids = lists["input_ids"].data_ptr(), lists["self_ids"].data_ptr()
-        P.counts_log, P.stats_log, P.input_log = self.counts_log.data_ptr(), self.stats_log.data_ptr(), self.input_log.data_ptr()
-        P.ws_top_down, P.ws_top_down_bytes = self.ws_td.data_ptr(), self.ws_td_bytes
-        P.ws_update, P.ws_update_bytes, P.ws_update_stride = self.ws_upd.data_ptr(), self.ws_upd_bytes, self.ws_upd_stride
+        P.ws_top_down_bytes, P.ws_update_bytes, P.ws_update_stride = self.ws_td_bytes, self.ws_upd_bytes, self.ws_upd_stride
         P.side = self.side.cuda_stream if self.side is not None else None
         P.ev_pruned, P.ev_selected, P.ev_next_pruned = self.ev_pruned.handle, self.ev_selected.handle, self.ev_next_pruned.handle
         P.ev_done[0], P.ev_done[1], P.ev_gradients, P.ev_weights = self.ev_done[0].handle, self.ev_done[1].handle, self.ev_bw[1].handle, self.ev_bw[0].handle
         specs, call = (B.UpdateLayer * max(L - 1, 1))(), B.PathCall()
         call.specs = specs
         return P, call, (B.PathBatch(), B.PathBatch()), specs
+
+    def _pack_model(self, P, it, ahead):
+        """The model's switches and the addresses of its tensors, looked up for every call as the single calls do: a caller may have put
+        another tensor in the place of one. ahead: the lists of the next iteration are used too."""
+        L, a, bw, wg = self.L, torch.Tensor.data_ptr, self.backward, self.weight_grads
+        P.on_host, P.fused_input, P.fuse_small_layers, P.backward, P.weight_grads = self.on_host, bool(self.fused_input), self.fuse_small_layers, bool(bw), wg
+        P.ring, P.num_nodes = self.ring, self.num_nodes
+        none = (0,) * (L + 1)
+        v = [*map(a, self.H), 0, *map(a, self.AGG_l[1:])]
+        for there, tensors in ((self.model == "gcn", "MEANPOS_l"), (bw, "dH"), (bw, "gnorm"), (wg, "dW"), (wg, "db")):
+            if there:
+                t = getattr(self, tensors)      # (no tensor for layer 0; of the norms none for layer L)
+                v.append(0)
+                v += map(a, t[1:])
+                if len(t) <= L:
+                    v.append(0)
+            else:
+                v += none
+        _PACK_MODEL[L].pack_into(P, B.Path.h.offset, *v)
+        for k in (it % 3, (it + 1) % 3) if ahead else (it % 3,):
+            s = self._lists[k]
+            _PACK_LISTS[L].pack_into(P, B.Path.lists.offset + k * _LISTS_BYTES, *map(a, (*s["live"], *s["hit"], *s["hit_pos"], *s["hit_slot"],
+                                                                                        *s["normal_pos"], s["input_ids"], s["self_ids"])))
+        _PACK_LOGS.pack_into(P, B.Path.counts_log.offset, *map(a, (self.counts_log, self.stats_log, self.input_log, self.ws_td, self.ws_upd)),
+                             self.ws_bw.data_ptr() if bw else 0, self.ws_wg.data_ptr() if wg else 0)
+        P.ws_backward_bytes, P.ws_weights_bytes = self.ws_bw_bytes if bw else 0, self.ws_wg_bytes if wg else 0
 
     def _pack(self, into, bt, norms):
         """A mini-batch as fg_path_run takes it; norms: the cache update's come with it."""
@@ -591,7 +597,7 @@ class HotPath:
         if ahead:
             self._fit(next_bt)
             self._pack(later, next_bt, False)
-        P.fused_input, P.fuse_small_layers, P.backward, P.weight_grads = bool(self.fused_input), self.fuse_small_layers, bool(self.backward), self.weight_grads
+        self._pack_model(P, it, ahead)
         rest = (0,) * (B.FG_PATH_MAX_LAYERS - L)
         v = [it, main.cuda_stream, cache.value if cache is not None else 0, _addr(self.feat)]
         for of in (self.W, self.Wt, self.bias):

@@ -2261,6 +2261,53 @@ def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, k
             hp.close()
 
 
+@pytest.mark.parametrize("kwargs", [dict(fused_input=True), dict(fused_input=True, backward=True, weight_grads=True),
+                                    dict(backward=True, weight_grads=True, model="gcn")])
+def test_iteration_as_one_call_uses_the_tensors_that_are_there(env, kwargs):
+    """A caller puts other tensors in the places of a model's (its outputs, gradients, lists and logs) between two iterations: the next
+    one reads and writes those, through fg_path_run as through the single calls, and leaves the earlier ones alone."""
+    torch, B = env
+    from paper_2301_07482_amd.pipeline import DeviceBatch
+    w = wl.WORKLOADS["tiny"]
+    g = wl.make_graph(w)
+    L, backward = w.num_layers, kwargs.get("backward", False)
+    paths = [G.make_hotpath(w, **kwargs)[0] for _ in range(2)]
+    paths[1].runs_in_one_call = lambda: False
+    names = ["H", "AGG_l"] + (["dH", "gnorm", "dW", "db"] if backward else []) + (["MEANPOS_l"] if kwargs.get("model") == "gcn" else [])
+    try:
+        records = []
+        for hp in paths:
+            def batch(it):
+                mb = wl.minibatch(w, g, it)
+                return DeviceBatch(mb, None, labels=wl.node_labels(w, mb.ids[L])) if backward else \
+                    DeviceBatch(mb, {l: wl.grad_norms(w, it, l, mb.ids[l]) for l in range(1, L)})
+            batches = [batch(it) for it in range(6)]
+            for it in range(3):
+                hp.run(batches[it], it)
+            hp.flush()
+            torch.cuda.synchronize()
+            holders = [(getattr(hp, n), l) for n in names for l in range(len(getattr(hp, n)))]
+            holders += [(lists[k], l) for lists in hp._lists for k in ("live", "hit", "hit_pos", "hit_slot", "normal_pos") for l in range(L + 1)]
+            holders += [(lists, k) for lists in hp._lists for k in ("input_ids", "self_ids")]
+            holders += [(hp.__dict__, k) for k in ("counts_log", "stats_log", "input_log", "ws_td", "ws_upd")]
+            earlier = [(h[k], h[k].clone()) for h, k in holders if h[k] is not None]      # (kept: what may be written must stay allocated)
+            for h, k in holders:
+                if h[k] is not None:
+                    h[k] = h[k].clone()
+            for it in range(3, 6):
+                hp.run(batches[it], it, next_bt=batches[it + 1] if it + 1 < 6 else None)
+            hp.flush()
+            torch.cuda.synchronize()
+            assert all(torch.equal(was, now) for now, was in earlier), "a tensor that is not the model's any more was written"
+            records.append([h[k].clone() for h, k in holders if h[k] is not None][:-2] + [torch.from_numpy(hp.cache_rows(l, hp.export_cache(l, 6)["slots"]))
+                                                                                         for l in range(1, L)])
+        for i, (a, b) in enumerate(zip(*records)):
+            assert torch.equal(a, b), f"record {i} of {len(records[0])}"
+    finally:
+        for hp in paths:
+            hp.close()
+
+
 def test_device_sampled_iterations_queued_back_to_back(env):
     """Mini-batches sampled on the device (and their norms made there) on the current stream right before the call that
     announces them, twelve iterations queued without a synchronisation: the second stream, which runs ahead of the current
