@@ -170,7 +170,7 @@ class PathCall(C.Structure):
     """fg_path_call_t"""
     _fields_ = [("iter", _i64), ("stream", _p), ("cache", _p), ("feat", _p), ("w", _per_layer), ("wt", _per_layer), ("bias", _per_layer),
                 ("p_grad", _f)] + [(k, _i32) for k in ("update", "overlap", "fetch_with_loader", "ahead", "promised", "pruned_ahead")] \
-        + [("due", C.POINTER(UpdateLayer)), ("due_iter", _i64), ("specs", C.POINTER(UpdateLayer)), ("selected", _i32), ("next_pruned", _i32)]
+        + [("due", C.POINTER(UpdateLayer)), ("due_iter", _i64), ("specs", C.POINTER(UpdateLayer)), ("selected", _i32), ("next_pruned", _i32), ("begun", _i32)]
 
 
 SIGNATURES["fg_path_run"] = (_i32, [C.POINTER(Path), C.POINTER(PathBatch), C.POINTER(PathBatch), C.POINTER(PathCall)])

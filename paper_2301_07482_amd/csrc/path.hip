@@ -242,7 +242,7 @@ fg_status_t check_batch(const fg_path_t& P, const fg_path_batch_t& b) {
 
 extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t* batch, const fg_path_batch_t* next, fg_path_call_t* call) {
     if (!path || !batch || !call) FG_FAIL(FG_ERR_INVALID_ARG, "fg_path_run: NULL pointer");
-    call->selected = call->next_pruned = 0;
+    call->selected = call->next_pruned = call->begun = 0;
     const fg_path_t& P = *path;
     if (P.n_layers < 1 || P.n_layers > FG_PATH_MAX_LAYERS || P.ring < 1) FG_FAIL(FG_ERR_INVALID_ARG, "fg_path_run: n_layers = %d must be in 1..%d", P.n_layers, FG_PATH_MAX_LAYERS);
     if (call->iter < 0) FG_FAIL(FG_ERR_INVALID_ARG, "fg_path_run: iteration %lld is negative", (long long)call->iter);
@@ -262,6 +262,7 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
         if (!call->promised) FG_HIP(hipStreamWaitEvent(main, (hipEvent_t)P.ev_selected, 0));
         FG_TRY(commit(call->due_iter, L - 1, call->due));
     }
+    call->begun = 1;
     if (!call->pruned_ahead) FG_TRY(I.top_down(*batch, main));
     const bool beside = do_update && call->overlap && !P.backward;
     if (beside) {      // the update's selection and the next top-down pass on the second stream

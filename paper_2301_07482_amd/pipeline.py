@@ -608,10 +608,11 @@ class HotPath:
                              self.weight_grads_ahead(bt), promised, pruned_ahead)
         due = self._row_copy_due
         call.due_iter, call.due = due if due is not None else (0, None)
-        self._row_copy_due = self._td_for = None
         try:
             B.fg_path_run(P, now, later if ahead else None, call)
         finally:
+            if call.begun:      # (a call that was refused before has queued nothing: both are still due)
+                self._row_copy_due = self._td_for = None
             if call.next_pruned:
                 self._td_for = (it + 1, next_bt)
         if call.selected:

@@ -258,3 +258,15 @@ def test_three_way_bf16_split_is_exact_on_the_documented_input_domain():
         x = (mant * np.float32(2.0 ** e)).astype(np.float32)
         assert split_error(x).max() == 0.0, e
     assert split_error((mant * np.float32(2.0 ** -114)).astype(np.float32)).max() > 2.0 ** -20
+
+
+def test_a_refused_iteration_says_that_nothing_of_it_is_queued(B):
+    """fg_path_run with sizes or an iteration number that it refuses, a row copy due and a pass promised: neither is waited for or copied."""
+    path, batch, call = B.Path(), B.PathBatch(), B.PathCall()
+    due = (B.UpdateLayer * 1)()
+    path.n_layers, path.ring = 2, 4
+    for iteration, n in ((-1, 0), (3, 9)):      # lists of no positions
+        batch.layer[1].n, call.iter, call.due, call.promised, call.begun = n, iteration, due, 1, 1
+        with pytest.raises(B.FgError):
+            B.fg_path_run(path, batch, None, call)
+        assert call.begun == 0 and call.promised == 1 and call.due

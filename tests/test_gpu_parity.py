@@ -2308,6 +2308,40 @@ def test_iteration_as_one_call_uses_the_tensors_that_are_there(env, kwargs):
             hp.close()
 
 
+def test_refused_iteration_leaves_the_due_rows_and_the_announced_pass(env):
+    """A call that is refused between two iterations (an iteration number that no call takes) changes nothing: the rows the one before admitted
+    are copied by whoever comes next, a read-back or an iteration, and the next iteration waits for the pass announced."""
+    torch, B = env
+    from paper_2301_07482_amd.pipeline import DeviceBatch
+    w = wl.WORKLOADS["tiny"]
+    g = wl.make_graph(w)
+    L, K = w.num_layers, 6
+    hp, ref = (G.make_hotpath(w, fused_input=True)[0] for _ in range(2))
+    try:
+        def batch(it):
+            mb = wl.minibatch(w, g, it)
+            return DeviceBatch(mb, {l: wl.grad_norms(w, it, l, mb.ids[l]) for l in range(1, L)})
+        mine, theirs = [batch(it) for it in range(K)], [batch(it) for it in range(K)]
+        for it in range(K):
+            nxt = it + 1 if it + 1 < K else None
+            hp.run(mine[it], it, next_bt=mine[nxt] if nxt else None)
+            ref.run(theirs[it], it, next_bt=theirs[nxt] if nxt else None)
+            if nxt:
+                assert hp._row_copy_due is not None
+                with pytest.raises(B.FgError):
+                    hp.run(mine[it], -1)
+                assert hp._row_copy_due is not None
+            if it % 2:
+                hp.flush()
+            assert torch.equal(hp.H[L], ref.H[L]) and torch.equal(hp.counts_log[it], ref.counts_log[it])
+        for l in range(1, L):
+            slots = [x.export_cache(l, K)["slots"] for x in (hp, ref)]
+            assert np.array_equal(*slots) and np.array_equal(hp.cache_rows(l, slots[0]), ref.cache_rows(l, slots[1]))
+    finally:
+        hp.close()
+        ref.close()
+
+
 def test_device_sampled_iterations_queued_back_to_back(env):
     """Mini-batches sampled on the device (and their norms made there) on the current stream right before the call that
     announces them, twelve iterations queued without a synchronisation: the second stream, which runs ahead of the current

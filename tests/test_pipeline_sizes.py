@@ -73,3 +73,30 @@ def test_weight_gradient_workspace_is_that_of_the_widths_the_call_gets(kind, n):
         for d_out in (8, 72, 128, 136, 256, 512):
             width = d_in // 2 if kind == "gcn" else d_in
             assert P.weight_grad_workspace_bytes(kind, n, d_in, d_out) >= size(n, width, d_out), (d_in, d_out)
+
+
+@pytest.mark.parametrize("begun", [0, 1])
+def test_a_refused_iteration_keeps_what_the_one_before_left_to_it(monkeypatch, begun):
+    """The row copy of the previous selection, whose rows the index names already, and the wait for the top-down pass that runs ahead
+    stay due until a call has queued them."""
+    pytest.importorskip("torch")
+    from paper_2301_07482_amd import pipeline as P
+    hp = P.HotPath.__new__(P.HotPath)
+    call, specs = P.B.PathCall(), (P.B.UpdateLayer * 1)()
+    hp.__dict__.update(L=2, use_cache=True, cache=P.B._p(4096), overlap_update=True, backward=False, feat=None, W={}, Wt={}, bias={}, p_grad=0.5,
+                       fetch_with_loader=True, _row_copy_due=(3, specs), _td_for=(4, "announced"), _ready_waited=None,
+                       _native=(P.B.Path(), call, (P.B.PathBatch(), P.B.PathBatch()), specs),
+                       _pack=lambda *a: None, _pack_model=lambda *a: None, weight_grads_ahead=lambda bt: False)
+    seen = []
+
+    def refuse(path, batch, later, c):
+        seen.append((bool(c.due), c.due_iter, c.promised))
+        c.begun, c.selected, c.next_pruned = begun, 0, 0
+        raise P.B.FgError(P.B.FG_ERR_INVALID_ARG, "refused")
+
+    monkeypatch.setattr(P.B, "fg_path_run", refuse)
+    main = types.SimpleNamespace(cuda_stream=0)
+    with pytest.raises(P.B.FgError):
+        hp._run_native(_batch([1, 1, 1], [0, 0, 0], [None] * 3), 4, main, True, None, True, False)
+    assert seen == [(True, 3, 1)]
+    assert (hp._row_copy_due, hp._td_for) == ((None, None) if begun else ((3, specs), (4, "announced")))
