@@ -606,6 +606,8 @@ class HotPath:
             v += rest
         _PACK_CALL.pack_into(call, 0, *v, self.p_grad, bool(do_update), bool(self.overlap_update), bool(self.fetch_with_loader),
                              self.weight_grads_ahead(bt), promised, pruned_ahead)
+        if cache is None:      # the rows an earlier iteration admitted, if the caller has switched the cache off since
+            self.flush(main=main)
         due = self._row_copy_due
         call.due_iter, call.due = due if due is not None else (0, None)
         try:

@@ -2342,6 +2342,35 @@ def test_refused_iteration_leaves_the_due_rows_and_the_announced_pass(env):
         ref.close()
 
 
+def test_cache_switched_off_while_admitted_rows_are_due(env):
+    """`use_cache` off for one iteration behind one whose admitted rows are not copied yet: they are, and that iteration computes every row."""
+    torch, B = env
+    from paper_2301_07482_amd.pipeline import DeviceBatch
+    w = wl.WORKLOADS["tiny"]
+    g = wl.make_graph(w)
+    L = w.num_layers
+    paths = [G.make_hotpath(w, fused_input=True)[0] for _ in range(2)]
+    paths[1].runs_in_one_call = lambda: False
+    try:
+        def batch(it):
+            mb = wl.minibatch(w, g, it)
+            return DeviceBatch(mb, {l: wl.grad_norms(w, it, l, mb.ids[l]) for l in range(1, L)})
+        state = []
+        for hp in paths:
+            rec = []
+            for it in range(5):
+                hp.use_cache = it != 3
+                hp.run(batch(it), it, next_bt=batch(it + 1) if it == 2 else None)      # (announced, but another object comes)
+                assert (hp._row_copy_due is not None) == (it == 2)
+                rec += [hp.H[L].clone(), hp.counts.clone()]
+            assert int(rec[7][1:L, 1].sum()) == 0
+            state.append(rec + [torch.from_numpy(hp.cache_rows(l, hp.export_cache(l, 5)["slots"])) for l in range(1, L)])
+        assert all(torch.equal(a, b) for a, b in zip(*state))
+    finally:
+        for hp in paths:
+            hp.close()
+
+
 def test_device_sampled_iterations_queued_back_to_back(env):
     """Mini-batches sampled on the device (and their norms made there) on the current stream right before the call that
     announces them, twelve iterations queued without a synchronisation: the second stream, which runs ahead of the current

@@ -100,3 +100,25 @@ def test_a_refused_iteration_keeps_what_the_one_before_left_to_it(monkeypatch, b
         hp._run_native(_batch([1, 1, 1], [0, 0, 0], [None] * 3), 4, main, True, None, True, False)
     assert seen == [(True, 3, 1)]
     assert (hp._row_copy_due, hp._td_for) == ((None, None) if begun else ((3, specs), (4, "announced")))
+
+
+def test_rows_that_are_due_are_copied_when_the_cache_is_switched_off(monkeypatch):
+    pytest.importorskip("torch")
+    from paper_2301_07482_amd import pipeline as P
+    hp = P.HotPath.__new__(P.HotPath)
+    call, specs, order = P.B.PathCall(), (P.B.UpdateLayer * 1)(), []
+    hp.__dict__.update(L=2, use_cache=False, cache=P.B._p(4096), overlap_update=True, backward=False, feat=None, W={}, Wt={}, bias={}, p_grad=0.5,
+                       fetch_with_loader=True, _row_copy_due=(3, specs), _td_for=None, _ready_waited=None, ev_selected="selected", ws_upd_bytes=64,
+                       ev_done=[None, types.SimpleNamespace(record=lambda st: order.append("recorded"))], _ws_upd=lambda it: 4096,
+                       _native=(P.B.Path(), call, (P.B.PathBatch(), P.B.PathBatch()), specs),
+                       _pack=lambda *a: None, _pack_model=lambda *a: None, weight_grads_ahead=lambda bt: False)
+    monkeypatch.setattr(P.B, "fg_cache_update_commit", lambda cache, it, y, *a: order.append((cache.value, it, y is specs)))
+
+    def run(path, batch, later, c):
+        order.append((c.cache, bool(c.due)))
+        c.begun = 1
+
+    monkeypatch.setattr(P.B, "fg_path_run", run)
+    main = types.SimpleNamespace(cuda_stream=0, wait_event=order.append)
+    hp._run_native(_batch([1, 1, 1], [0, 0, 0], [None] * 3), 4, main, True, None, False, False)
+    assert order == ["selected", (4096, 3, True), "recorded", (None, False)] and hp._row_copy_due is None
