@@ -178,7 +178,7 @@ class DeviceSampler:
             B.fg_sample_minibatch(self.indptr, self.indices, self.num_nodes, self.num_edges, seeds if top == L else ids_below,
                                   None if top == L else cp + 16 * top, layers, int(key), self.ws, self.ws_bytes, main.cuda_stream)
             ids_below = layers[len(layers) - 1].ids_below_dev
-        views = buf.split_with_sizes(self.pieces) if L else ()
+        views = (buf if buf.numel() == self.out_elems else buf[:self.out_elems]).split_with_sizes(self.pieces) if L else ()
         bt.ids[L] = seeds
         for i, l in enumerate(range(L, 0, -1)):
             v = views[16 * i:16 * i + 16:2]

@@ -926,6 +926,26 @@ def test_sample_minibatch_with_an_empty_block_behind_another(env, first, empty):
     assert [out[0][k].cpu().numpy()[:m].tolist() for k, m in (("t_start_dev", nb), ("t_end_dev", nb), ("t_row_dev", nnz))] == [list(x) for x in t]
 
 
+def test_sampler_writes_into_memory_larger_than_it_needs(env):
+    """`out` of another sampler, which was made for larger mini-batches: the arrays lie at its front, what is behind stays as it is."""
+    torch, B = env
+    from paper_2301_07482_amd.pipeline import DeviceSampler
+    N = 3000
+    indptr, indices = _random_multigraph(N, 20, 3, hubs=2)
+    args = (dev(torch, indptr), dev(torch, indices), N)
+    small, large = DeviceSampler(*args, (4, 3), 20, transposes=True), DeviceSampler(*args, (4, 3), 50, transposes=True)
+    seeds = dev(torch, np.arange(20, dtype=np.int32))
+    buf, counts = large.buffers()
+    buf.fill_(-5)
+    got, want = small.sample(seeds, 7, out=(buf, counts)), small.sample(seeds, 7)
+    for name in ("start", "end", "col", "ids", "t_start", "t_end", "t_row"):
+        for l in range(3):
+            a, b = getattr(got, name)[l], getattr(want, name)[l]
+            n = want.nnz[l] if name in ("col", "t_row") else want.n[l - 1] if name.startswith("t_") else want.n[l]
+            assert (a is None) == (b is None) and (a is None or torch.equal(a[:n], b[:n])), (name, l)
+    assert (buf[small.out_elems:] == -5).all()
+
+
 @pytest.mark.parametrize("n,n_src,deg,src_bound,nnz_bound", [
     (1500, 12288, 8, 12288, 12288), (1500, 12288, 8, 12288, 12289), (1500, 12288, 8, 12289, 12288), (2500, 5, 4, 9, 12000),
     (1024, 7168, 7, 7168, 7168), (1024, 7168, 7, 7168, 7169), (1024, 7168, 7, 7169, 7168), (1536, 6000, 4, 7168, 7168),
