@@ -146,7 +146,8 @@ fg_status_t fg_cache_export(const fg_cache_t* cache, int32_t layer, int64_t iter
 /*
  * Launch-shape overrides for measurements (defaults are tuned for MI355X and need no call). Keys:
  * "gather_wg_per_cu", "gather_host_wg_per_cu", "gather_unroll" (1, 2, 4, 8), "gather_nontemporal" (0/1),
- * "aggregate_wg_per_cu", "top_down_walk" (fg_top_down: 1 = its first launch walks the first two blocks down from the seeds, 0 = one layer per launch), "linear_tile" (fp32 GEMM variant: 0 = default, 8 = one task per workgroup with K split over its wavefronts, 32 = panel kernel, 64 / 128 = LDS-tiled kernel with that many rows; bf16 weights: 1064 / 1128 = the 64 x 64 or the 128 x 128 tile). Process-wide, not thread-safe against concurrent launches. Results never depend on them.
+ * "aggregate_wg_per_cu", "top_down_walk" (fg_top_down: 1 = its first launch walks the first two blocks down from the seeds, 0 = one layer per launch), "linear_tile" (fp32 GEMM variant: 0 = default, 8 = one task per workgroup with K split over its wavefronts, 32 = panel kernel, 64 / 128 = LDS-tiled kernel with that many rows; bf16 weights: 1064 / 1128 = the 64 x 64 or the 128 x 128 tile). Process-wide, not thread-safe against concurrent launches. Results never depend on them,
+ * but for "wait_polls" (0 = default, 2^20), for tests of giving up: polls of a wait between the workgroups of a launch before it gives up.
  */
 fg_status_t fg_set_tuning(const char* key, int64_t value);
 
@@ -448,7 +449,8 @@ fg_status_t fg_aggregate_linear(const int32_t* row_start_dev, const int32_t* row
  *   ids_dev[n], live_dev[n] (NULL = all live), hit_dev[n]   as given to / produced by fg_lookup_prune
  *   gnorm_dev[n]        float, L2 norm of the loss gradient w.r.t. each node's embedding; finite and >= 0
  *   h_dev, h_stride     embeddings of the layer by position (type = the cache's dtype, width = its dim)
- *   stats_dev           out, int64[4] device or NULL: admitted, evicted_by_gradient, overwritten, dropped_overflow
+ *   stats_dev           out, int64[4] device or NULL: admitted, evicted_by_gradient, overwritten, dropped_overflow. -1 for the first and the
+ *                       last: the layer's workgroups gave up waiting for each other (not seen yet); nothing is admitted then
  *   ws_dev, ws_bytes    device workspace, >= fg_workspace_bytes(FG_WS_CACHE_UPDATE, n, 0)
  * `iter` must not decrease between updates of a layer (FG_ERR_STATE).
  */

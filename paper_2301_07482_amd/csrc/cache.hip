@@ -30,6 +30,7 @@
 // re-flags every admissible node as in / tie / out and counts per workgroup; launch 4 then lets the first ties in
 // position order fill what the larger estimates leave of the room.
 #include "common.h"
+#include "meeting.h"
 #include "scan.h"
 
 namespace {
@@ -63,7 +64,7 @@ struct SelState {
     unsigned int n_surv;
     unsigned int arrived[3];       // workgroups that have counted their keys' digit (update_group_kernel)
     unsigned int done;             // ... and that have left the scratch alone
-    unsigned int admits[64];       // a workgroup's admissible nodes, published
+    unsigned int admits[64];       // a workgroup's admissible nodes, published (meeting.h)
     unsigned int hist2[SEL_BINS];  // estimates of saved accesses of the admissible nodes (access-aware policy), or the third digit
 };
 
@@ -116,6 +117,7 @@ __device__ __forceinline__ int upd_count(const UpdLayer& L) {
 
 struct UpdBatch {
     int32_t n_layers;
+    int32_t polls;                              // before a workgroup that waits for others gives up
     int32_t sel_first[FG_MAX_UPD_LAYERS + 1];   // first workgroup of each layer in launches 1 and 2
     int32_t scan_first[FG_MAX_UPD_LAYERS + 1];  // the same for launches 3 and 4
     UpdLayer l[FG_MAX_UPD_LAYERS];
@@ -361,7 +363,9 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void classify_update_kernel(UpdBatch
 // histograms are kept four times (by lane mod 4): norms share their leading digits, and equal bins of a wavefront are
 // added one after the other.
 // Who waits needs no more than that the other workgroups start: they are at most 64 in all, so that they are all there together on a chip
-// with room for 512 of their size, and a launch they have to wait behind ends without them. The polls are bounded all the same.
+// with room for 512 of their size, and a launch they have to wait behind ends without them. The polls are bounded all the same: a workgroup
+// that gives up takes its whole layer along (meeting.h), which then admits nothing and says so in its statistics; what it has checked
+// out until then stays out.
 // Between the barriers the chain is kept short: prefix sums inside the vector registers, a wavefront's place among the others' totals from
 // four wide LDS reads, each thread clearing the counters it read, no division (with shuffles, a loop over the wavefronts and 64-bit
 // remainders 17.6 us at 1.2 k positions, 14.2 so, 12.9 with two digits where they decide; a third of what is left is the row copy and the first reads).
@@ -371,8 +375,6 @@ constexpr int ONE_COPIES = 4;
 constexpr int SEL_WAVES = SEL_THREADS / FG_WAVE;
 constexpr int GRP_CHUNK = 4 * SEL_THREADS;      // positions of a workgroup
 constexpr int GRP_MAX = 64;                     // workgroups of a launch
-constexpr int GRP_SPIN_LIMIT = 1 << 20;         // polls before a workgroup gives up (never reached)
-constexpr uint32_t GRP_PUBLISHED = 0x80000000u;
 
 __device__ __attribute__((aligned(16))) uint32_t upd_spare[4];      // what is read where a layer has no quad
 
@@ -422,15 +424,10 @@ __device__ __forceinline__ void grp_arrive() {
     __syncthreads();
 }
 
-// All `n` workgroups of a layer have come here. false: given up.
-__device__ __forceinline__ bool grp_meet(unsigned int* arrived, unsigned int n, int* s_ok) {
+// All `n` workgroups of a layer have come here and none has given up.
+__device__ __forceinline__ bool grp_meet(unsigned int* arrived, unsigned int n, int polls, int* s_ok) {
     grp_arrive();
-    if (threadIdx.x == 0) {
-        __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        int polls = 0;
-        while (grp_load(arrived) < n && ++polls < GRP_SPIN_LIMIT) __builtin_amdgcn_s_sleep(1);
-        *s_ok = polls < GRP_SPIN_LIMIT;
-    }
+    if (threadIdx.x == 0) *s_ok = fg_meet(FgAgentMem{}, arrived, n, polls);
     __syncthreads();
     return *s_ok != 0;
 }
@@ -518,7 +515,7 @@ __global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
             unsigned int* shared = pass == 0 ? L.sel->hist0 : (pass == 1 ? L.sel->hist1 : L.sel->hist2);
             if (c0) atomicAdd(&shared[2 * t], c0);
             if (c1) atomicAdd(&shared[2 * t + 1], c1);
-            lost = !grp_meet(&L.sel->arrived[pass], parts, &s_ok);
+            lost = !grp_meet(&L.sel->arrived[pass], parts, B.polls, &s_ok);
             c0 = grp_load(&shared[2 * t]);
             c1 = grp_load(&shared[2 * t + 1]);
         }
@@ -532,10 +529,10 @@ __global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
         } else {
             rank = s_found[pass - 1].y;
         }
-        if (lost) {      // (who still waits further on must not wait for this workgroup)
+        if (lost) {
             mode = 0;
             if (t == 0)
-                for (int p = pass + 1; p < 3; ++p) __hip_atomic_fetch_add(&L.sel->arrived[p], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                for (int p = pass + 1; p < 3; ++p) fg_lost_ahead(FgAgentMem{}, &L.sel->arrived[p]);
         }
         if (mode == 1) {
             find_bin(c0, c1, lo, rank, &s_found[pass]);
@@ -572,22 +569,15 @@ __global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
     if (parts > 1) {      // what the other workgroups admit, behind all check-outs
         grp_arrive();
         if (wave == 0) {
-            uint32_t w = GRP_PUBLISHED;
-            if (t == 0) grp_store(&L.sel->admits[part], GRP_PUBLISHED | (uint32_t)total);
-            if (t < (int)parts) {
-                int polls = 0;
-                do {
-                    w = grp_load(&L.sel->admits[t]);
-                    if (w & GRP_PUBLISHED) break;
-                    __builtin_amdgcn_s_sleep(1);
-                } while (++polls < GRP_SPIN_LIMIT);
-            }
-            int there = (int)(w & ~GRP_PUBLISHED), ahead = t < part ? there : 0;
+            uint32_t w = FG_PUBLISHED;
+            if (t == 0) fg_publish(FgAgentMem{}, &L.sel->admits[part], lost ? FG_GIVEN_UP : (uint32_t)total);
+            if (t < (int)parts && !lost) w = fg_settled(FgAgentMem{}, &L.sel->admits[t], B.polls);
+            int there = (int)(w & ~(FG_PUBLISHED | FG_GIVEN_UP)), ahead = t < part ? there : 0;
             for (int off = FG_WAVE / 2; off > 0; off >>= 1) {
                 there += __shfl_xor(there, off, FG_WAVE);
                 ahead += __shfl_xor(ahead, off, FG_WAVE);
             }
-            const bool all_there = __all((w & GRP_PUBLISHED) != 0);
+            const bool all_there = __all((w & FG_GIVEN_UP) == 0) && !lost;
             if (t == 0) {
                 s_before = ahead;
                 s_all = there;
@@ -1110,6 +1100,7 @@ fg_status_t prepare_update_layer(fg_cache_t* cache, const char* who, int32_t lay
 // four (five with the access-aware ranking) launches that decide and write the cache's index, `commit` = the row copy.
 fg_status_t launch_update(UpdBatch& B, hipStream_t st, bool select = true, bool commit = true) {
     B.sel_first[0] = B.scan_first[0] = 0;
+    B.polls = fg_polls();
     for (int i = 0; i < B.n_layers; ++i) {  // at least one workgroup per layer: it resets the statistics and writes the header
         const int64_t n = B.l[i].n > 0 ? B.l[i].n : 1;
         B.sel_first[i + 1] = B.sel_first[i] + (int)fg_ceil_div(n, SEL_CHUNK);

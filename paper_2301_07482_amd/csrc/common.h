@@ -110,9 +110,11 @@ enum fg_tune_id {
     FG_TUNE_AGG_WG_PER_CU,
     FG_TUNE_LINEAR_TILE,  // 0: choose by problem size; 8: split-K kernel, 32: panel kernel, 64 or 128: LDS-tiled kernel; bf16: 1064, 1128
     FG_TUNE_TOP_DOWN_WALK,  // 1: fg_top_down walks the first two blocks from the seeds in its first launch; 0: one layer per launch
+    FG_TUNE_WAIT_POLLS,     // polls of a wait between workgroups before it gives up; 0: as many as meeting.h says
     FG_TUNE_COUNT
 };
 int64_t fg_tuning(fg_tune_id id);
+int fg_polls();             // ... as a number
 
 // internal row copy used by fg_gather and by the cache update; feat (may be NULL, else 16-byte rows) makes
 // src_index node ids whose rows are taken from the feature side where they are still there

@@ -620,6 +620,55 @@ def _check_update_sizes(env, n, p, norms, two_parts=False):
         B.fg_cache_destroy(cache)
 
 
+@pytest.mark.parametrize("n", [4097, 30_001, 200_000])
+def test_cache_update_whose_workgroups_give_up_changes_no_slot(env, n):
+    """Waits of one to three polls: an update either is the one with patient workgroups, or says that its workgroups gave up; then nothing is
+    admitted, the ring's header stands, the rows in the cache are those of before, less some check-outs, and the next update is whole."""
+    torch, B = env
+    r = np.random.default_rng(n)
+    N, cap, d = 3 * n, n, 4
+    rows = [r.standard_normal((n, d)).astype(np.float32) for _ in range(3)]
+    ids = [r.permutation(min(N, 2 * n))[:n].astype(np.int32) for _ in range(3)]
+    gn = [np.exp(r.standard_normal(n)).astype(np.float32) for _ in range(3)]
+    live = np.ones(n, bool)
+    gave_up = 0
+
+    def entries(cache, it):
+        e = _export(torch, B, cache, cap, it)
+        tab = _table(torch, B, cache, cap, d)
+        return e["head"], {int(v): (int(s), int(q), tab[s].tobytes()) for v, s, q in zip(e["nodes"], e["slots"], e["stamps"])}
+
+    def updates(polls):
+        cache = B.fg_cache_create(N, [cap], [d], B.FG_F32, 5, None)
+        try:
+            out = []
+            for i in range(3):
+                B.fg_set_tuning("wait_polls", polls if i == 1 else 0)
+                stats = _device_update(torch, B, cache, i, ids[i], live, gn[i], 0.4, rows[i])[2]
+                out.append((stats, *entries(cache, i + 1)))
+            return out
+        finally:
+            B.fg_set_tuning("wait_polls", 0)
+            B.fg_cache_destroy(cache)
+
+    whole = updates(0)
+    assert all(s[0] > 0 for s, _, _ in whole)
+    for trial in range(9):
+        got = updates(1 + trial % 3)
+        assert got[0] == whole[0]
+        if got[1][0][0] >= 0:
+            assert got == whole
+            continue
+        gave_up += 1
+        stats, head, there = got[1]
+        assert stats[0] == stats[3] == -1 and stats[2] == 0 and head == got[0][1]
+        assert there.items() <= got[0][2].items() and len(there) >= len(got[0][2]) - stats[1]
+        hit = np.asarray([int(v) in there for v in ids[2]])
+        low = gn[2] < np.sort(gn[2])[int(np.floor(np.float32(0.4) * n))]
+        assert got[2][0][0] == min(cap, int((low & ~hit).sum())) and got[2][0][1] == int((~low & hit).sum())
+    print(f"{gave_up} of 9 gave up")
+
+
 @pytest.mark.parametrize("n,d,p", [(1, 4, 1.0), (4096, 4, 1.0), (777, 12, 0.6), (1024, 64, 0.6), (3000, 20, 0.5), (4096, 20, 0.5),      # copied by the selection
                                    (1024, 64, 0.8), (4096, 20, 0.51), (1024, 64, 0.9), (4096, 28, 0.6), (4097, 4, 0.3)])                               # by a launch of their own
 def test_cache_update_rows_of_small_layers(env, n, d, p):
@@ -656,6 +705,11 @@ def _export(torch, B, cache, cap, it, layer=1):
     B.fg_cache_export(cache, layer, it, t[0], t[1], t[2], cnt.data_ptr(), cnt.data_ptr() + 8, ws, wsb, None)
     c = int(cnt[0].item())
     return dict(nodes=t[0][:c].cpu().numpy(), slots=t[1][:c].cpu().numpy(), stamps=t[2][:c].cpu().numpy(), head=int(cnt[1].item()))
+
+
+def _table(torch, B, cache, cap, d):
+    from paper_2301_07482_amd.pipeline import _tensor_from_ptr
+    return _tensor_from_ptr(B.fg_cache_table(cache, 1), (cap, d), torch.float32, cap * d * 4, "cuda").cpu().numpy()
 
 
 def test_iteration_counter_must_not_go_backwards(env):
