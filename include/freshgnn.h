@@ -209,9 +209,10 @@ fg_status_t fg_lookup_prune_static(const fg_cache_t* cache, int32_t layer, int64
  * pass is a chain of dependent random reads, and every launch boundary adds to it; here the cache lookups of all
  * layers, which do not depend on liveness, are done in the first launch, where one wavefront per seed also walks the
  * first two blocks down (a seed's neighbours, and their neighbours unless they are cached), so that the liveness of
- * the two layers below the seeds is settled at once; the layers so settled are classified by one launch, and every
- * further layer by one launch that also compacts the lists of the layers above it. Three launches for three layers.
- * Same results as calling fg_lookup_prune layer by layer.
+ * the two layers below the seeds is settled at once; the layers so settled are classified and their lists compacted by one
+ * launch, and every further layer by another: two launches for three layers. (Of more than 256 Ki positions the lists are
+ * compacted beside the classification of the layer below: three.) Same results as calling fg_lookup_prune layer by layer.
+ * A layer's counts of -1 say that the workgroups of its launch gave up waiting for each other (not seen yet): its lists are not there.
  *
  * layers[0] is the seed layer, layers[i+1] the layer below layers[i]; each entry carries the arguments of
  * fg_lookup_prune for its layer (same meaning, same NULL rules). cache_layer = 0: no lookup for this layer;

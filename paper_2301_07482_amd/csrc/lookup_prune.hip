@@ -11,6 +11,7 @@
 #include <atomic>
 
 #include "common.h"
+#include "meeting.h"
 #include "scan.h"
 
 namespace {
@@ -175,9 +176,7 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void compact_lists_kernel(
 // classification of their layer, so nothing has to be cleared ahead of the marking.
 constexpr int TD_MAX_LAYERS = 8;
 constexpr int TD_WALK_THREADS = 256;
-constexpr uint32_t TD_PUBLISHED = 0x80000000u;   // a chunk's counts as one word: this bit, live count << 12, hit count
 constexpr int TD_FUSED_MAX_BLOCKS = 256;         // workgroups of a launch whose chunks wait for each other: all resident at once
-constexpr int TD_SPIN_LIMIT = 1 << 20;           // polls of a predecessor's word before a chunk gives up (never reached)
 
 struct TdLayer {
     CacheView cv;
@@ -349,6 +348,7 @@ struct TdPhase {
     int mark_from;             // those at or beyond this index also mark the layer below
     int cmp_first, cmp_last;   // layers compacted by this launch
     int cls_blocks;            // workgroups that classify; the rest compact
+    int polls;                 // of a chunk's word before who waits for it gives up
 };
 
 __global__ __launch_bounds__(FG_SCAN_BLOCK) void td_phase_kernel(TdArgs a, TdPhase p) {
@@ -398,9 +398,10 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void td_phase_kernel(TdArgs a, TdPha
 }
 
 // Classification and compaction of a group of layers in one launch. A chunk's lists start where those of the chunks before
-// it end, so a chunk publishes its counts as one word (zero before the launch: cleared by launch 1) and then polls the words
-// of its predecessors in the same layer. The launch is small enough for all of its workgroups to be resident at once
-// (the host checks), a chunk waits only for chunks with a smaller index, and the poll is bounded anyway.
+// it end, so a chunk publishes its counts as one word (live count << 12, hit count; zero before the launch: cleared by launch 1) and
+// then polls the words of its predecessors in the same layer. The launch is small enough for all of its workgroups to be resident
+// at once (the host checks), a chunk waits only for chunks with a smaller index, and the poll is bounded anyway: a chunk that one has
+// waited for too long is given up for all (meeting.h), the layer's last chunk included, whose counts are then -1.
 //
 // A chain of a few dependent reads and two barriers: a chunk's ranks come from one ballot per class and the totals of its
 // wavefronts, the sum over its predecessors from prefix sums in the vector registers. With a barrier pair for every count, sum and
@@ -438,20 +439,12 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void td_fused_kernel(TdArgs a, TdPha
         const int t_hit = all & 0xFFFF, t_norm = all >> 16;
         r_hit += before & 0xFFFF;
         r_norm += before >> 16;
-        if (threadIdx.x == 0)
-            __hip_atomic_store((uint32_t*)&L.blk[3 * b], TD_PUBLISHED | ((uint32_t)(t_hit + t_norm) << 12) | (uint32_t)t_hit, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) fg_publish(FgAgentMem{}, (uint32_t*)&L.blk[3 * b], ((uint32_t)(t_hit + t_norm) << 12) | (uint32_t)t_hit);
         int p_live = 0, p_hit = 0;
         bool lost = false;
         for (int q = threadIdx.x; q < b; q += FG_SCAN_BLOCK) {
-            uint32_t w = 0;
-            int polls = 0;
-            do {
-                w = __hip_atomic_load((const uint32_t*)&L.blk[3 * q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (w & TD_PUBLISHED) break;
-                __builtin_amdgcn_s_sleep(2);
-            } while (++polls < TD_SPIN_LIMIT);
-            lost = lost || !(w & TD_PUBLISHED);
+            const uint32_t w = fg_settled(FgAgentMem{}, (uint32_t*)&L.blk[3 * q], p.polls);
+            lost = lost || (w & FG_GIVEN_UP) != 0;
             p_live += (w >> 12) & 0xFFFu;
             p_hit += w & 0xFFFu;
         }
@@ -784,6 +777,7 @@ extern "C" fg_status_t fg_top_down(const fg_cache_t* cache, int64_t iter, int32_
             p.cls_first = first;
             p.cls_last = last;
             p.mark_from = mark_from;
+            p.polls = fg_polls();
             hipLaunchKernelGGL(td_fused_kernel, dim3((unsigned)group_blocks(first, last)), dim3(FG_SCAN_BLOCK), 0, st, a, p);
             FG_LAUNCH_CHECK("td_fused_kernel");
         } else {

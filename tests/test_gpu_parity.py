@@ -207,6 +207,39 @@ def test_top_down_clears_liveness_of_the_smallest_batches(env):
         assert lists[0][3][:n_in].cpu().numpy().tolist() == [[7, 3, 9][j] for j in range(3) if want_live[j]]
 
 
+@pytest.mark.parametrize("n", [1025, 30_001, 262_144])
+def test_top_down_whose_chunks_give_up_counts_nothing(env, n):
+    """Waits of one to three polls: a layer's lists are those of patient chunks, or all its counts say that some gave up. The pass behind it, in the
+    same workspace, is whole again."""
+    torch, B = env
+    r = np.random.default_rng(n)
+    live = r.random(n) < 0.6
+    want = np.flatnonzero(live)
+    t_live, ids = dev(torch, live.astype(np.uint8)), dev(torch, r.permutation(n).astype(np.int32))
+    hit = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    lists = [torch.zeros(n, dtype=torch.int32, device="cuda") for _ in range(4)]
+    cnt = torch.zeros(3, dtype=torch.int64, device="cuda")
+    layers = B.top_down_layers([dict(cache_layer=0, ids_dev=ids, n=n, live_dev=t_live, hit_dev=hit, hit_pos_dev=lists[0], hit_slot_dev=lists[1],
+                                     normal_pos_dev=lists[2], normal_ids_dev=lists[3], counts_dev=cnt)])
+    wsb = B.fg_top_down_workspace_bytes(layers)
+    ws = torch.zeros(wsb, dtype=torch.uint8, device="cuda")
+    gave_up = 0
+    try:
+        for polls in [1, 2, 3, 0] * 5:
+            lists[2].fill_(-9)
+            B.fg_set_tuning("wait_polls", polls)
+            B.fg_top_down(None, 0, layers, ws, wsb, None)
+            counts = cnt.tolist()
+            if counts == [-1] * 3 and polls:
+                gave_up += 1
+                continue
+            assert counts == [len(want), 0, len(want)]
+            assert np.array_equal(lists[2].cpu().numpy()[:len(want)], want) and torch.equal(lists[3][:len(want)], ids[lists[2][:len(want)].long()])
+    finally:
+        B.fg_set_tuning("wait_polls", 0)
+    print(f"{gave_up} of 15 gave up")
+
+
 def _device_update(torch, B, cache, i, ids, live, gn, p, rows, misalign=False, two_parts=False):
     """Lookup (no block) followed by the update on the device; returns the hit flags. `misalign` puts the norms
     and the liveness flags at addresses that are not multiples of 16 and 4 bytes."""
