@@ -5,6 +5,7 @@ done by the HIP kernels behind `binding`. Nothing is copied back to the host bet
 counts stay in device memory and each call is launched over a static upper bound.
 """
 import ctypes
+import functools
 import struct
 import sys
 
@@ -247,9 +248,10 @@ def _addr(t):
 
 _LAYERS = B.FG_PATH_MAX_LAYERS + 1
 _PACK_BATCH = [struct.Struct(f"4q{11 * (n + 1)}q") for n in range(_LAYERS)]      # fg_path_batch_t of n layers
-_PACK_MODEL = [struct.Struct(f"{n + 1}q{8 * (_LAYERS - n - 1)}x" * 7) for n in range(_LAYERS)]      # fg_path_t: h .. db
+_PACK_ROWS = [struct.Struct(f"{n + 1}q") for n in range(_LAYERS)]                # an array of fg_path_t, layers 0 .. n
 _PACK_LISTS = [struct.Struct(f"{n + 1}q{8 * (_LAYERS - n - 1)}x" * 5 + "2q") for n in range(_LAYERS)]      # fg_path_lists_t
-_PACK_LOGS = struct.Struct("7q")                                                 # fg_path_t: counts_log .. ws_weights
+_PACK_LOGS = struct.Struct("5q")                                                 # fg_path_t: counts_log .. ws_update
+_PATH_AT = {name: getattr(B.Path, name).offset for name, *_ in B.Path._fields_}
 _LISTS_BYTES = ctypes.sizeof(B.PathLists)
 _PACK_CALL = struct.Struct(f"4q{3 * _LAYERS}qf6i")                               # fg_path_call_t as far as its flags
 
@@ -333,8 +335,6 @@ class HotPath:
         self.ring = int(log_ring)
         self.counts_log = torch.zeros((self.ring, L + 1, 3), dtype=torch.int64, device=dev)
         self.stats_log = torch.zeros((self.ring, L + 1, 4), dtype=torch.int64, device=dev)
-        self.counts = self.counts_log[0]
-        self.stats = self.stats_log[0]
         self.input_log = torch.zeros((self.ring, 3), dtype=torch.int64, device=dev)   # layer 0's counts where `reads_rows_once`
         self.input_slot = 0
         ws_bytes = max(max(B.fg_workspace_bytes(B.FG_WS_LOOKUP_PRUNE, n[l]) for l in range(L + 1)),
@@ -547,35 +547,40 @@ class HotPath:
         L, a, bw, wg = self.L, torch.Tensor.data_ptr, self.backward, self.weight_grads
         P.on_host, P.fused_input, P.fuse_small_layers, P.backward, P.weight_grads = self.on_host, bool(self.fused_input), self.fuse_small_layers, bool(bw), wg
         P.ring, P.num_nodes = self.ring, self.num_nodes
-        none = (0,) * (L + 1)
-        v = [*map(a, self.H), 0, *map(a, self.AGG_l[1:])]
-        for there, tensors in ((self.model == "gcn", "MEANPOS_l"), (bw, "dH"), (bw, "gnorm"), (wg, "dW"), (wg, "db")):
-            if there:
-                t = getattr(self, tensors)      # (no tensor for layer 0; of the norms none for layer L)
-                v.append(0)
-                v += map(a, t[1:])
-                if len(t) <= L:
-                    v.append(0)
-            else:
-                v += none
-        _PACK_MODEL[L].pack_into(P, B.Path.h.offset, *v)
+        rows, at = _PACK_ROWS[L], _PATH_AT
+        rows.pack_into(P, at["h"], *map(a, self.H))
+        inner = _PACK_ROWS[L - 1]      # (no tensor for layer 0; of the norms none for layer L)
+        inner.pack_into(P, at["agg"] + 8, *map(a, self.AGG_l[1:]))
+        if self.model == "gcn":
+            inner.pack_into(P, at["mean_pos"] + 8, *map(a, self.MEANPOS_l[1:]))
+        if bw:
+            inner.pack_into(P, at["dh"] + 8, *map(a, self.dH[1:]))
+            if L > 1:
+                _PACK_ROWS[L - 2].pack_into(P, at["gnorm"] + 8, *map(a, self.gnorm[1:]))
+            P.ws_backward, P.ws_backward_bytes = self.ws_bw.data_ptr(), self.ws_bw_bytes
+        if wg:
+            inner.pack_into(P, at["dw"] + 8, *map(a, self.dW[1:]))
+            inner.pack_into(P, at["db"] + 8, *map(a, self.db[1:]))
+            P.ws_weights, P.ws_weights_bytes = self.ws_wg.data_ptr(), self.ws_wg_bytes
         for k in (it % 3, (it + 1) % 3) if ahead else (it % 3,):
             s = self._lists[k]
-            _PACK_LISTS[L].pack_into(P, B.Path.lists.offset + k * _LISTS_BYTES, *map(a, (*s["live"], *s["hit"], *s["hit_pos"], *s["hit_slot"],
-                                                                                        *s["normal_pos"], s["input_ids"], s["self_ids"])))
-        _PACK_LOGS.pack_into(P, B.Path.counts_log.offset, *map(a, (self.counts_log, self.stats_log, self.input_log, self.ws_td, self.ws_upd)),
-                             self.ws_bw.data_ptr() if bw else 0, self.ws_wg.data_ptr() if wg else 0)
-        P.ws_backward_bytes, P.ws_weights_bytes = self.ws_bw_bytes if bw else 0, self.ws_wg_bytes if wg else 0
+            _PACK_LISTS[L].pack_into(P, at["lists"] + k * _LISTS_BYTES, *map(a, s["live"]), *map(a, s["hit"]), *map(a, s["hit_pos"]), *map(a, s["hit_slot"]),
+                                     *map(a, s["normal_pos"]), a(s["input_ids"]), a(s["self_ids"]))
+        _PACK_LOGS.pack_into(P, at["counts_log"], a(self.counts_log), a(self.stats_log), a(self.input_log), a(self.ws_td), a(self.ws_upd))
 
     def _pack(self, into, bt, norms):
         """A mini-batch as fg_path_run takes it; norms: the cache update's come with it."""
         L = self.L
         bw = self.backward
         v = [_addr(bt.labels) if bw else 0, _addr(getattr(bt, "col_ids1", None)), self.reads_rows_once(bt), self.own_rows_from_table(bt)]
-        for l, n, nnz, ids, start, end, col, n_dev in zip(range(L + 1), bt.n, bt.nnz, bt.ids, bt.start, bt.end, bt.col, bt.n_dev):
-            v += n, nnz, _addr(ids), _addr(start), _addr(end), _addr(col), _addr(n_dev)
-            v += (_addr(bt.t_start[l]), _addr(bt.t_end[l]), _addr(bt.t_row[l])) if bw and l > 1 else (0, 0, 0)
-            v.append(_addr(bt.gnorm[l]) if norms and 0 < l < L else 0)
+        for l, n, nnz, *arrays in zip(range(L + 1), bt.n, bt.nnz, bt.ids, bt.start, bt.end, bt.col, bt.n_dev):
+            v += n, nnz
+            if bw and l > 1:
+                arrays += bt.t_start[l], bt.t_end[l], bt.t_row[l]
+            else:
+                arrays += None, None, None
+            arrays.append(bt.gnorm[l] if norms and 0 < l < L else None)
+            v += [0 if t is None else t if t.__class__ is int else t.data_ptr() for t in arrays]      # (`_addr`, without its calls)
         _PACK_BATCH[L].pack_into(into, 0, *v)
 
     def _run_native(self, bt, it, main, update, next_bt, promised, pruned_ahead):
@@ -622,10 +627,19 @@ class HotPath:
 
     def _bind(self, it):
         """Point the per-iteration state (lists of the top-down pass, counters, statistics) at iteration `it`'s copies."""
-        self.__dict__.update(self._lists[it % 3])
-        self.counts = self.counts_log[it % self.ring]
-        self.stats = self.stats_log[it % self.ring]
-        self.input_slot = it % self.ring      # (an address below, not a view: a view is 2.5 us of host time, three times an iteration)
+        mine = self.__dict__
+        mine.update(self._lists[it % 3])
+        mine.pop("counts", None)      # (views below, made when they are asked for: a view is 2.5 us of host time)
+        mine.pop("stats", None)
+        self.input_slot = it % self.ring
+
+    @functools.cached_property
+    def counts(self):
+        return self.counts_log[self.input_slot]
+
+    @functools.cached_property
+    def stats(self):
+        return self.stats_log[self.input_slot]
 
     def run(self, bt, it, update=True, timer=None, next_bt=None, hold_second_stream=False):
         """One iteration on torch's current stream. `timer(name, stream)` (optional) is called before each C-ABI call
