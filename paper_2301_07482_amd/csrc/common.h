@@ -101,6 +101,11 @@ constexpr int FG_SCAN_BLOCK = 1024;  // elements (= threads) per block in the co
 static inline int64_t fg_ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static inline size_t fg_align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// fg_aggregate_linear runs a layer of this shape as one launch
+static inline bool fg_one_launch_layer(int64_t max_rows, int64_t d_in, int64_t d_out) {
+    return d_in % 32 == 0 && d_in <= 256 && fg_ceil_div(max_rows, 32) * fg_ceil_div(d_out, 32) <= 768;
+}
+
 // launch-shape parameters (defaults tuned on MI355X; fg_set_tuning overrides them for measurements)
 enum fg_tune_id {
     FG_TUNE_GATHER_WG_PER_CU = 0,

@@ -1139,10 +1139,10 @@ extern "C" fg_status_t fg_aggregate_linear(const int32_t* row_start_dev, const i
     if (src_stride < (int64_t)d_in * 4 || out_stride < (int64_t)d_out * 4) FG_FAIL(FG_ERR_SHAPE, "%s: a row stride is smaller than its row", who);
     if (((uintptr_t)h_src | (uintptr_t)W | (uintptr_t)src_stride) & 15) FG_FAIL(FG_ERR_INVALID_ARG, "%s: h_src, W and src_stride must be 16-byte aligned", who);
     if (((uintptr_t)h_out | (uintptr_t)out_stride | (uintptr_t)bias) & 3) FG_FAIL(FG_ERR_INVALID_ARG, "%s: h_out, its stride and bias must be 4-byte aligned", who);
-    const size_t panel_bytes = (size_t)2 * d_in * PL_BN * sizeof(float);
-    const int64_t n_tasks = fg_ceil_div(max_rows, 32) * fg_ceil_div(d_out, PL_BN);
     const int64_t forced = fg_tuning(FG_TUNE_LINEAR_TILE);
-    if (d_in % KC == 0 && panel_bytes <= 64 * 1024 && n_tasks <= 768 && (forced == 0 || forced == 8)) {
+    if (fg_one_launch_layer(max_rows, d_in, d_out) && (forced == 0 || forced == 8)) {
+        static_assert(KC == 32 && PL_BN == 32 && 2 * 256 * PL_BN * sizeof(float) <= 64 * 1024, "the rule's 32 and 256");
+        const size_t panel_bytes = (size_t)2 * d_in * PL_BN * sizeof(float);
         fg_clear_error();
         if (max_rows == 0 || n_src == 0 || n_out == 0) return FG_OK;
         const int n_panels = (int)fg_ceil_div(d_out, PL_BN);

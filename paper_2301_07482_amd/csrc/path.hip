@@ -34,10 +34,7 @@ struct Iter {
     int agg_code() const { return P.compute_dtype == FG_F32 ? FG_F32 : FG_BF16; }
     bool cached() const { return C.cache && P.n_layers > 1; }
     bool gcn() const { return P.model == FG_PATH_GCN; }
-    // fg_aggregate_linear runs the layer as one launch (its rule)
-    bool one_launch(int l, int64_t n) const {
-        return P.fuse_small_layers && l >= 2 && P.dims[l - 1] % 32 == 0 && P.dims[l - 1] <= 256 && fg_ceil_div(n, 32) * fg_ceil_div(P.dims[l], 32) <= 768;
-    }
+    bool one_launch(int l, int64_t n) const { return P.fuse_small_layers && l >= 2 && fg_one_launch_layer(n, P.dims[l - 1], P.dims[l]); }
     // lookup, prune, V_normal for layers L .. 0 (or 1 with the fused loader)
     fg_status_t top_down(const fg_path_batch_t& b, void* stream) const {
         const int L = P.n_layers;
