@@ -535,8 +535,8 @@ fg_status_t fg_cache_update_commit(fg_cache_t* cache, int64_t iter, int32_t n_la
  *   counts_dev [2] int64                  out: nodes of the layer below, edges of the block
  *   ws_dev, ws_bytes                      device workspace, >= fg_sample_block_workspace_bytes(max_rows, fanout) (0 for
  *                                         sizes the call rejects); 16-byte aligned
- * Four launches on `stream` (one for a block of few draws), no host synchronisation. Node ids outside [0, num_nodes) get
- * empty rows.
+ * Four launches on `stream` (one for a block of few draws, five for one of more than 8192 workgroups of slots), no host
+ * synchronisation. Node ids outside [0, num_nodes) get empty rows.
  */
 size_t fg_sample_block_workspace_bytes(int64_t max_rows, int32_t fanout);
 fg_status_t fg_sample_block(const int64_t* indptr_dev, const int32_t* indices_dev, int64_t num_nodes, int64_t num_edges,
@@ -554,7 +554,8 @@ fg_status_t fg_sample_block(const int64_t* indptr_dev, const int32_t* indices_de
  *                                          columns outside [0, count) are ignored
  *   t_start_dev, t_end_dev [max_src], t_row_dev [max_nnz]      out; positions at and beyond the count get empty lists
  *   ws_dev, ws_bytes                       device workspace, >= fg_transpose_block_workspace_bytes(max_src); 16-byte aligned
- * Six launches, no host synchronisation; the result does not depend on the order in which threads run.
+ * One launch for a small block, else five, six of more than 131 072 sources; no host synchronisation; the result does not
+ * depend on the order in which threads run.
  */
 size_t fg_transpose_block_workspace_bytes(int64_t max_src);
 fg_status_t fg_transpose_block(const int32_t* row_start_dev, const int32_t* row_end_dev, const int32_t* col_dev,
@@ -571,7 +572,9 @@ fg_status_t fg_transpose_block(const int32_t* row_start_dev, const int32_t* row_
  *   n_layers, layers          1..8 layers, top-down; every max_rows at most the max_below of the layer before
  *   ws_dev, ws_bytes          device workspace, >= fg_sample_minibatch_workspace_bytes(n_layers, layers), which looks at the sizes and
  *                             at whether t_start_dev is NULL (0 for sizes the call rejects); 16-byte aligned
- * Three launches per block (one for a block of few draws), at most one more in front, no host synchronisation.
+ * Launches: three per block (one for a block of few draws; four for one of more than 8192 workgroups of slots; for one without rows
+ * one that clears its counts), one more in front unless the first block is one of few draws, and behind the last block the
+ * stages of transposes that no later launch took along (three or four for a transpose of the last block). No host synchronisation.
  */
 typedef struct fg_sample_layer {
     int32_t layer, fanout;       /* as in fg_sample_block */

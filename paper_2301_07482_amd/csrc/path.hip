@@ -2,8 +2,9 @@
 // from one call. Nothing here computes: it fills in what the calls take and orders two streams by events.
 //
 // A small iteration is bound by the host that queues it: from Python, a foreign call with 20 to 30 arguments per launch took 66 us for
-// an iteration of the smallest workload whose launches keep the GPU busy for 50. Queued from here the host needs 40 (10 k nodes, 256
-// seeds x 10 x 5: step 57 -> 50 us, training iteration 90 -> 78, both what the GPU needs).
+// an iteration of the smallest workload (10 k nodes, 256 seeds x 10 x 5) whose launches kept the GPU busy for 50. Queued from here the
+// host needed 40: step 57 -> 50 us, training iteration 90 -> 78 with the kernels of that time, which was what the GPU needed; with
+// shorter ones it is 42 and 71.
 #include "common.h"
 
 namespace {

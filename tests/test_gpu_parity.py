@@ -612,7 +612,7 @@ def test_cache_update_sizes_around_a_workgroups_share(env, n, p):
 @pytest.mark.parametrize("n", [4096, 4097, 30_001])
 @pytest.mark.parametrize("norms", ["equal", "two values", "one digit apart", "with zeros and infinities"])
 def test_cache_update_of_norms_that_share_their_digits(env, n, norms):
-    """Every key in the list of those with the threshold's first digit, thresholds in the second and the third digit, both ends."""
+    """Thresholds that one, two or all three digits decide, equal keys on both sides of a workgroup's share, and both ends of the range."""
     def draw(r):
         if norms == "equal":
             return np.full(n, 0.7)
