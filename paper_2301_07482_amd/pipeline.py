@@ -249,11 +249,24 @@ def _addr(t):
 _LAYERS = B.FG_PATH_MAX_LAYERS + 1
 _PACK_BATCH = [struct.Struct(f"4q{11 * (n + 1)}q") for n in range(_LAYERS)]      # fg_path_batch_t of n layers
 _PACK_ROWS = [struct.Struct(f"{n + 1}q") for n in range(_LAYERS)]                # an array of fg_path_t, layers 0 .. n
-_PACK_LISTS = [struct.Struct(f"{n + 1}q{8 * (_LAYERS - n - 1)}x" * 5 + "2q") for n in range(_LAYERS)]      # fg_path_lists_t
+_PACK_IDS = struct.Struct("2q")                                                  # fg_path_lists_t: input_ids, self_ids
 _PACK_LOGS = struct.Struct("5q")                                                 # fg_path_t: counts_log .. ws_update
 _PATH_AT = {name: getattr(B.Path, name).offset for name, *_ in B.Path._fields_}
+_LISTS_AT = {name: getattr(B.PathLists, name).offset for name, *_ in B.PathLists._fields_}
 _LISTS_BYTES = ctypes.sizeof(B.PathLists)
 _PACK_CALL = struct.Struct(f"4q{3 * _LAYERS}qf6i")                               # fg_path_call_t as far as its flags
+
+
+class _Places(list):
+    """Tensors of a model by layer. A caller may put another one in a place; set `k` of the packed ones is then packed anew."""
+
+    def __init__(self, tensors, packed, k):
+        super().__init__(tensors)
+        self.packed, self.k = packed, k
+
+    def __setitem__(self, place, tensor):
+        super().__setitem__(place, tensor)
+        self.packed.discard(self.k)
 
 
 class HotPath:
@@ -311,23 +324,17 @@ class HotPath:
                 shared_pos = torch.zeros(max(n[l] * (dims[l - 1] // 2) for l in range(1, L + 1)), dtype=torch.float32, device=dev)
                 self.MEANPOS_l = [None] + [shared_pos] * L
             self.MEANPOS = self.MEANPOS_l[L]
-        self.live = [torch.zeros(n[l], dtype=torch.uint8, device=dev) for l in range(L + 1)]
-        self.hit = [torch.zeros(n[l], dtype=torch.uint8, device=dev) for l in range(L + 1)]
         self.saving = [torch.zeros(n[l] if admit_budget else 0, dtype=torch.int32, device=dev) for l in range(L + 1)]
-        self.hit_pos = [torch.zeros(n[l], dtype=torch.int32, device=dev) for l in range(L + 1)]
-        self.hit_slot = [torch.zeros(n[l], dtype=torch.int32, device=dev) for l in range(L + 1)]
-        self.normal_pos = [torch.zeros(n[l], dtype=torch.int32, device=dev) for l in range(L + 1)]
-        self.input_ids = torch.zeros(n[0], dtype=torch.int32, device=dev)
-        self.self_ids = torch.zeros(n[1], dtype=torch.int32, device=dev)
         # what the top-down pass writes exists three times (iteration it uses set it % 3), so that the pass for the next
         # mini-batch can run while this one's layers are computed (`run(..., next_bt=...)`) and the previous one's
         # admitted rows are still being copied: the second stream then waits for nothing younger than the row copy of
         # two iterations ago, and its chain selection -> next top-down pass can start before this iteration's loader
-        mk = lambda dt: [torch.zeros(n[l], dtype=dt, device=dev) for l in range(L + 1)]
-        more = lambda: dict(live=mk(torch.uint8), hit=mk(torch.uint8), hit_pos=mk(torch.int32), hit_slot=mk(torch.int32),
-                            normal_pos=mk(torch.int32), input_ids=torch.zeros_like(self.input_ids), self_ids=torch.zeros_like(self.self_ids))
-        self._lists = [dict(live=self.live, hit=self.hit, hit_pos=self.hit_pos, hit_slot=self.hit_slot, normal_pos=self.normal_pos,
-                            input_ids=self.input_ids, self_ids=self.self_ids), more(), more()]
+        self._packed = set()     # the sets whose addresses fg_path_run's descriptor holds
+        mk = lambda k, dt: _Places((torch.zeros(n[l], dtype=dt, device=dev) for l in range(L + 1)), self._packed, k)
+        self._lists = [dict(live=mk(k, torch.uint8), hit=mk(k, torch.uint8), hit_pos=mk(k, torch.int32), hit_slot=mk(k, torch.int32),
+                            normal_pos=mk(k, torch.int32), input_ids=torch.zeros(n[0], dtype=torch.int32, device=dev),
+                            self_ids=torch.zeros(n[1], dtype=torch.int32, device=dev)) for k in range(3)]
+        self.__dict__.update(self._lists[0])
         self._td_for = None      # (iteration, mini-batch) whose top-down pass has already been launched on the second stream
         self._ready_waited = None  # the mini-batch whose `ready` event the second stream waited for in the previous call
         self._row_copy_due = None  # (iteration, descriptors) of a selection whose rows are not copied yet
@@ -543,7 +550,8 @@ class HotPath:
 
     def _pack_model(self, P, it, ahead):
         """The model's switches and the addresses of its tensors, looked up for every call as the single calls do: a caller may have put
-        another tensor in the place of one. ahead: the lists of the next iteration are used too."""
+        another tensor in the place of one. (The top-down pass's lists, two thirds of the tensors, say when that happens; looking them up
+        too is 1.5 us of host time.) ahead: the lists of the next iteration are used too."""
         L, a, bw, wg = self.L, torch.Tensor.data_ptr, self.backward, self.weight_grads
         P.on_host, P.fused_input, P.fuse_small_layers, P.backward, P.weight_grads = self.on_host, bool(self.fused_input), self.fuse_small_layers, bool(bw), wg
         P.ring, P.num_nodes = self.ring, self.num_nodes
@@ -563,9 +571,12 @@ class HotPath:
             inner.pack_into(P, at["db"] + 8, *map(a, self.db[1:]))
             P.ws_weights, P.ws_weights_bytes = self.ws_wg.data_ptr(), self.ws_wg_bytes
         for k in (it % 3, (it + 1) % 3) if ahead else (it % 3,):
-            s = self._lists[k]
-            _PACK_LISTS[L].pack_into(P, at["lists"] + k * _LISTS_BYTES, *map(a, s["live"]), *map(a, s["hit"]), *map(a, s["hit_pos"]), *map(a, s["hit_slot"]),
-                                     *map(a, s["normal_pos"]), a(s["input_ids"]), a(s["self_ids"]))
+            s, here = self._lists[k], at["lists"] + k * _LISTS_BYTES
+            if k not in self._packed:
+                for name in ("live", "hit", "hit_pos", "hit_slot", "normal_pos"):
+                    rows.pack_into(P, here + _LISTS_AT[name], *map(a, s[name]))
+                self._packed.add(k)
+            _PACK_IDS.pack_into(P, here + _LISTS_AT["input_ids"], a(s["input_ids"]), a(s["self_ids"]))
         _PACK_LOGS.pack_into(P, at["counts_log"], a(self.counts_log), a(self.stats_log), a(self.input_log), a(self.ws_td), a(self.ws_upd))
 
     def _pack(self, into, bt, norms):
