@@ -35,7 +35,7 @@
 namespace {
 
 constexpr int SMP_THREADS = 1024;
-constexpr int SMP_LANES = 32;                           // the largest fan-out, and the most lanes per row
+constexpr int SMP_LANES = 32;                           // the largest fan-out
 constexpr int SMP_PREFIX = 8192;                        // workgroups of candidates whose counts a workgroup adds up for itself
 constexpr unsigned long long SMP_EMPTY = ~0ull;
 constexpr uint32_t SMP_LINE = 8;                        // entries of the table that are probed together
@@ -991,7 +991,8 @@ size_t tr_layout(int64_t max_src, size_t* blk_at) {
     return *blk_at + fg_align_up((size_t)fg_ceil_div((int64_t)src, FG_SCAN_BLOCK) * 4, 256);
 }
 
-SmpWs smp_layout(int32_t n_layers, const fg_sample_layer_t* layers) {
+// `bound`: for every call of up to as many rows, else for a call of just these
+SmpWs smp_layout(int32_t n_layers, const fg_sample_layer_t* layers, bool bound) {
     SmpWs w{};
     size_t at = 0, cands = 1, blocks = 1;
     auto take = [&](size_t bytes) {
@@ -1001,7 +1002,7 @@ SmpWs smp_layout(int32_t n_layers, const fg_sample_layer_t* layers) {
     };
     for (int i = 0; i < n_layers; ++i) {
         const size_t rows = (size_t)(layers[i].max_rows > 0 ? layers[i].max_rows : 1), c = rows * (size_t)layers[i].fanout;
-        const size_t b = (size_t)smp_most_blocks((int64_t)rows, layers[i].fanout);
+        const size_t b = (size_t)(bound ? smp_most_blocks : smp_blocks)((int64_t)rows, layers[i].fanout);
         if (!smp_is_small(layers[i].max_rows, layers[i].fanout)) {
             cands = c > cands ? c : cands;
             blocks = b > blocks ? b : blocks;
@@ -1097,7 +1098,7 @@ fg_status_t smp_launch(const char* who, const int64_t* indptr, const int32_t* in
             FG_FAIL(FG_ERR_SHAPE, "%s: layers[%d].max_rows = %lld exceeds the list of layers[%d], %lld", who, i, (long long)layers[i].max_rows, i - 1,
                     (long long)layers[i - 1].max_below);
     }
-    const SmpWs w = smp_layout(n_layers, layers);
+    const SmpWs w = smp_layout(n_layers, layers, false);
     bool any = false;
     for (int i = 0; i < n_layers; ++i) any = any || layers[i].max_rows > 0 || layers[i].t_start_dev;
     if (any && (!ws_dev || ws_bytes < w.total)) FG_FAIL(FG_ERR_SHAPE, "%s: workspace of %zu bytes given, %zu needed", who, ws_bytes, w.total);
@@ -1218,7 +1219,7 @@ extern "C" size_t fg_sample_minibatch_workspace_bytes(int32_t n_layers, const fg
         if (layers[i].max_rows < 0 || layers[i].fanout < 1 || layers[i].fanout > SMP_LANES || layers[i].max_rows > (int64_t)INT32_MAX / SMP_LANES ||
             layers[i].max_below < 0 || (layers[i].t_start_dev && layers[i].max_below > INT32_MAX))
             return 0;
-    return smp_layout(n_layers, layers).total;
+    return smp_layout(n_layers, layers, true).total;
 }
 
 extern "C" fg_status_t fg_sample_minibatch(const int64_t* indptr_dev, const int32_t* indices_dev, int64_t num_nodes, int64_t num_edges,
@@ -1235,7 +1236,7 @@ extern "C" size_t fg_sample_block_workspace_bytes(int64_t max_rows, int32_t fano
     fg_sample_layer_t y{};
     y.max_rows = max_rows;
     y.fanout = fanout;
-    return smp_layout(1, &y).total;
+    return smp_layout(1, &y, true).total;
 }
 
 extern "C" fg_status_t fg_sample_block(const int64_t* indptr_dev, const int32_t* indices_dev, int64_t num_nodes, int64_t num_edges,
