@@ -928,8 +928,8 @@ def test_sample_block_matches_oracle(env, N, max_deg, hubs, n_seeds, fanouts, sl
     (9000, 30, 512, 8, 512, 25), (9000, 30, 512, 8, 513, 26), (9000, 30, 372, 11, 372, 27),      # one workgroup up to 4096 draws
     (6000, 40, 5000, 15, 34_816, 28), (6000, 40, 5000, 15, 34_817, 29), (6000, 40, 5000, 1, 524_289, 30)])   # one slot per thread or four
 def test_sample_block_routes_match_oracle(env, N, max_deg, n_seeds, fanout, bound, seed):
-    """One block at the sizes where fg_sample_block changes its launches (one workgroup or several, 8, 16 or 32 lanes per row,
-    the counts of the candidates' workgroups added up by each or once), bit for bit."""
+    """One block at the sizes where fg_sample_block changes its launches (one workgroup or several, one slot per thread or four,
+    the workgroups' counts added up by each or once), bit for bit."""
     torch, B = env
     from oracle import sampler_oracle as S
     indptr, indices = _random_multigraph(N, max_deg, seed, hubs=3)
@@ -1430,6 +1430,7 @@ def test_layer_backward_weights_match_oracle(env, d_in, d_out, n, n_rows, relu, 
 @pytest.mark.parametrize("d_in,d_out,n,relu", [
     (64, 64, 300, True), (64, 512, 200, True), (32, 576, 40, False),      # split over K; just beyond what it takes
     (16, 8, 33, True), (40, 72, 700, True), (256, 256, 1500, True), (128, 384, 900, False), (24, 392, 65, True),      # panels of 64, then of 32 columns
+    (24, 96, 130, True), (40, 224, 300, False),                            # whole chunks of 32 values, but not pairs of them
     (40, 768, 130, True), (40, 776, 130, True)])                           # the widest, and one that is masked by a launch of its own
 @pytest.mark.parametrize("apart", [0, 1])
 def test_layer_backward_reads_its_operands_in_place(env, d_in, d_out, n, relu, apart):
