@@ -296,6 +296,22 @@ fg_status_t fg_gather_aggregate_ids(const int32_t* row_start_dev, const int32_t*
                                     void* stream);
 
 /*
+ * fg_gather_aggregate_ids (no copy of the own rows) and the dense update of the same layer behind it (fg_linear_ids) in one call, fp32. A layer
+ * for which fg_one_launch_load says so (at least 16384 rows, d_in <= 128, d_out <= 256, at most 15 neighbours a row on average) runs as one
+ * launch: the rows of the next block are read while a block is multiplied. Other shapes run as the two launches, with the means in agg_ws_dev
+ * between them ([max_rows, agg_stride]; what it holds afterwards is not specified). The same results as the two calls up to the rounding of the
+ * products' sums.
+ */
+int32_t fg_one_launch_load(int64_t nnz, int64_t max_rows, int32_t d_in, int32_t d_out);
+fg_status_t fg_gather_aggregate_linear_ids(const int32_t* row_start_dev, const int32_t* row_end_dev, const int32_t* col_ids_dev,
+                                           int64_t nnz, int32_t n_block_rows, const int32_t* rows_dev, const int64_t* n_rows_dev,
+                                           int64_t max_rows, const int32_t* row_ids_dev, const float* table, int64_t table_rows,
+                                           int64_t src_stride, int32_t d_in, int32_t d_out, const float* W, const float* bias,
+                                           int32_t relu, float* agg_ws_dev, int64_t agg_stride, float* h_out, int32_t n_out,
+                                           int64_t out_stride, const fg_cache_t* cache, int32_t n_fetch_layers,
+                                           const struct fg_fetch_layer* fetch_layers, void* stream);
+
+/*
  * Load_feature through the feature side of the bidirectional cache (Section 4.2): fg_gather with node ids as
  * src_index, where the row of a node that fg_feature_lookup would find is read from the shared buffer in HBM
  * instead of from `table`. The result is the same bit copy as fg_gather's; only where the bytes come from differs.

@@ -62,6 +62,9 @@ SIGNATURES = {
     "fg_linear": (_i32, [_p, _i32, _i64, _i32, _p, _i64, _p, _p, _i64, _i32, _i32, _p, _i32, _p, _i32, _p, _i32, _i64, _i32, _p]),
     "fg_linear_wt": (_i32, [_p, _i32, _i64, _i32, _p, _i64, _p, _p, _i64, _i32, _i32, _p, _i32, _p, _i32, _p, _i32, _i64, _i32, _p]),
     "fg_linear_ids": (_i32, [_p, _i32, _i64, _i32, _p, _p, _i64, _p, _p, _i64, _i32, _i32, _p, _i32, _p, _i32, _p, _i32, _i64, _i32, _p]),
+    "fg_one_launch_load": (_i32, [_i64, _i64, _i32, _i32]),
+    "fg_gather_aggregate_linear_ids": (_i32, [_p, _p, _p, _i64, _i32, _p, _p, _i64, _p, _p, _i64, _i64, _i32, _i32, _p, _p, _i32, _p, _i64, _p, _i32,
+                                              _i64, _p, _i32, _p, _p]),
     "fg_aggregate_linear": (_i32, [_p, _p, _p, _i64, _i32, _p, _p, _i64, _p, _i32, _i64, _i32, _i32, _p, _p, _i32, _p, _i64, _p, _i32,
                                    _i64, _p]),
     "fg_cache_update": (_i32, [_p, _i32, _i64, _p, _i32, _p, _p, _p, _f, _p, _i64, _p, _p, _sz, _p]),
@@ -398,6 +401,20 @@ def fg_aggregate_linear(row_start, row_end, col, nnz, n_block_rows, rows, n_rows
     _check(_lib.fg_aggregate_linear(ptr(row_start), ptr(row_end), ptr(col), nnz, n_block_rows, ptr(rows), ptr(n_rows), max_rows,
                                     ptr(h_src), n_src, src_stride, d_in, d_out, ptr(W), ptr(bias), relu, ptr(agg_ws), agg_stride,
                                     ptr(h_out), n_out, out_stride, stream))
+
+
+def fg_gather_aggregate_linear_ids(row_start, row_end, col_ids, nnz, n_block_rows, rows, n_rows, max_rows, row_ids, table, table_rows, src_stride,
+                                   d_in, d_out, W, bias, relu, agg_ws, agg_stride, h_out, n_out, out_stride, cache=None, fetch_layers=None, stream=None):
+    n_fetch = len(fetch_layers) if fetch_layers is not None else 0
+    _check(_lib.fg_gather_aggregate_linear_ids(ptr(row_start), ptr(row_end), ptr(col_ids), nnz, n_block_rows, ptr(rows), ptr(n_rows), max_rows,
+                                               ptr(row_ids), ptr(table), table_rows, src_stride, d_in, d_out, ptr(W), ptr(bias), relu, ptr(agg_ws),
+                                               agg_stride, ptr(h_out), n_out, out_stride, cache, n_fetch,
+                                               C.cast(fetch_layers, _p) if n_fetch else None, stream))
+
+
+def one_launch_load(nnz, max_rows, d_in, d_out):
+    """Whether fg_gather_aggregate_linear_ids runs a layer of this shape as one launch (the rule stated in freshgnn.h)."""
+    return bool(_lib.fg_one_launch_load(nnz, max_rows, d_in, d_out))
 
 
 def one_launch_layer(max_rows, d_in, d_out):

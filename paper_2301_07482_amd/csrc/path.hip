@@ -138,6 +138,13 @@ struct Iter {
         return 17.0 + 18.5e-9 * products > 25.0 + 1.2e-6 * admitted;
     }
 
+    // Whether the loader and the dense update of layer 1 are one call: where nobody reads the means and the nodes' own rows later. (A training
+    // iteration does; with both written from the one launch it took what the two take, 122 us against 121.)
+    bool loads_and_multiplies(const fg_path_batch_t& b, int l) const {
+        return l == 1 && P.fused_input && !b.reads_rows_once && b.own_rows_from_table && b.col_ids1_dev && h_code(0) == FG_F32 && h_code(1) == FG_F32 &&
+               P.compute_dtype == FG_F32 && fg_one_launch_load(b.layer[1].nnz, b.layer[1].n, P.dims[0], P.dims[1]);
+    }
+
     fg_status_t forward(const fg_path_batch_t& b, bool once, const fg_fetch_layer_t* fetch, int n_fetch) const {
         const int L = P.n_layers;
         const bool fused = P.fused_input && !once;
@@ -169,6 +176,12 @@ struct Iter {
                 continue;
             }
             const bool own_rows = l == 1 && fused && b.own_rows_from_table;
+            if (loads_and_multiplies(b, l)) {
+                FG_TRY(fg_gather_aggregate_linear_ids(B.start_dev, B.end_dev, b.col_ids1_dev, B.nnz, n, S.normal_pos[1], n_normal, n, B.ids_dev, (const float*)C.feat,
+                                                      P.num_nodes, d0b, P.dims[0], P.dims[1], (const float*)C.w[1], C.bias[1], relu, (float*)P.agg[1], agg_b,
+                                                      (float*)P.h[1], n, out_b, n_fetch ? C.cache : nullptr, n_fetch, n_fetch ? fetch : nullptr, st));
+                continue;
+            }
             if (fused && l == 1) {
                 if (b.col_ids1_dev)
                     FG_TRY(fg_gather_aggregate_ids(B.start_dev, B.end_dev, b.col_ids1_dev, B.nnz, n, S.normal_pos[1], n_normal, n, B.ids_dev, C.feat, P.num_nodes, d0b,

@@ -800,6 +800,12 @@ class HotPath:
                                       bt.n[l], self.H[l - 1], bt.n[l - 1], in_b, self.dims[l - 1], self.dims[l], self.W[l],
                                       self.bias[l], 1 if l < L else 0, None, agg_b, self.H[l], bt.n[l], out_b, st)
                 continue
+            if l == 1 and fused and timer is None and self.loads_and_multiplies(bt):      # (the timed sequence tells the two apart)
+                B.fg_gather_aggregate_linear_ids(bt.start[1], bt.end[1], bt.col_ids1, bt.nnz[1], bt.n[1], self.normal_pos[1], self._cnt(1, 2), bt.n[1],
+                                                 bt.ids[1], self.feat, self.num_nodes, d0b, self.dims[0], self.dims[1], self.W[1], self.bias[1],
+                                                 1 if L > 1 else 0, self.AGG_l[1], agg_b, self.H[1], bt.n[1], out_b,
+                                                 self.cache if fetch_specs is not None else None, fetch_specs, st)
+                continue
             if fused and l == 1:
                 tick("gather_aggregate[1]")
                 args = (bt.start[1], bt.end[1], bt.col[1], bt.nnz[1], bt.n[1], self.normal_pos[1], self._cnt(1, 2), bt.n[1],
@@ -916,6 +922,11 @@ class HotPath:
         return (not self.copy_own_rows and self.fused_input and self.model == "sage" and not self.feature_side and not self.on_host
                 and self.comp_code == B.FG_F32 and self.feat_code == B.FG_F32 and not self.weight_grads
                 and getattr(bt, "col_ids1", None) is not None and not self.one_launch(1, bt.n[1]))
+
+    def loads_and_multiplies(self, bt):
+        """Whether the loader and the dense update of layer 1 of this mini-batch are one call and one launch of it."""
+        return bool(self.own_rows_from_table(bt) and self.h_code[1] == B.FG_F32
+                    and B.one_launch_load(bt.nnz[1], bt.n[1], self.dims[0], self.dims[1]))
 
     def reads_rows_once(self, bt):
         """Whether the loader of this mini-batch reads every surviving input row over the host link once, into H[0], and

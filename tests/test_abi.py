@@ -191,6 +191,18 @@ def test_argument_validation_needs_no_gpu(B):
     assert code(B.fg_aggregate_linear, 4096, 4096, 4096, 5, 50000, None, None, 50000, 4096, 50000, 512, 128, 64, 4096, None, 0, None,
                 512, 4096, 50000, 256) == B.FG_ERR_INVALID_ARG                                              # two launches need agg_ws
     assert B.one_launch_layer(1024, 256, 256) and not B.one_launch_layer(6144, 256, 256) and not B.one_launch_layer(100, 100, 64)
+    one_load = lambda **k: B.fg_gather_aggregate_linear_ids(**{**dict(row_start=4096, row_end=4096, col_ids=4096, nnz=5, n_block_rows=20000, rows=None, n_rows=None,
+        max_rows=20000, row_ids=4096, table=4096, table_rows=90, src_stride=512, d_in=128, d_out=64, W=4096, bias=None, relu=1, agg_ws=4096, agg_stride=512,
+        h_out=4096, n_out=20000, out_stride=256), **k})
+    for k in ("row_start", "row_end", "col_ids", "row_ids", "table", "W", "agg_ws", "h_out"):
+        assert code(one_load, **{k: None}) == B.FG_ERR_INVALID_ARG, k
+    for k in ("table", "W", "agg_ws", "src_stride"):
+        assert code(one_load, **{k: 4100}) == B.FG_ERR_INVALID_ARG, k                                       # not 16-byte aligned
+    assert code(one_load, src_stride=496) == code(one_load, agg_stride=496) == code(one_load, out_stride=252) == code(one_load, d_in=126) == B.FG_ERR_SHAPE
+    assert code(one_load, n_block_rows=-1) == code(one_load, nnz=-1) == code(one_load, bias=4097) == B.FG_ERR_INVALID_ARG
+    assert code(one_load, fetch_layers=B.fetch_layers([dict(layer=1)])) == B.FG_ERR_INVALID_ARG             # a fetch needs a cache
+    assert B.one_launch_load(15 * 16384, 16384, 128, 256) and not B.one_launch_load(15 * 16384 + 1, 16384, 128, 256)
+    assert not any(B.one_launch_load(1, *shape) for shape in ((16383, 128, 256), (16384, 132, 256), (16384, 128, 260), (16384, 126, 64), (16384, 128, 62)))
     assert code(B.fg_set_tuning, "gather_unroll", -3) == B.FG_ERR_INVALID_ARG
     assert B.fg_workspace_bytes(B.FG_WS_LOOKUP_PRUNE, 1000) >= 1000 * 5
     assert B.fg_workspace_bytes(B.FG_WS_CACHE_UPDATE, 1000) >= 1000 * 9

@@ -506,6 +506,88 @@ def test_linear_ids_reads_own_rows_from_the_table(env, d_in, d_out, n_rows, max_
         assert err <= (2e-2 if sixteen else REL_TOL_F32)
 
 
+@pytest.mark.parametrize("d_in,d_out,fan,max_rows,n_rows,listed", [
+    (128, 256, 15, 16384, 16384, True), (128, 256, 7, 16421, 16389, True), (100, 252, 15, 17000, 33, True), (4, 4, 3, 16384, 8193, False),
+    (64, 88, 15, 20000, 19999, True), (68, 36, 6, 16400, 16400, False), (60, 256, 2, 16384, 0, True), (12, 32, 3, 150000, 149985, True)])
+def test_loader_and_dense_update_as_one_launch(env, d_in, d_out, fan, max_rows, n_rows, listed):
+    """fg_gather_aggregate_linear_ids where it is one launch, against the means of fg_gather_aggregate_ids multiplied in double (the repository's
+    bar): partial blocks, more blocks than a workgroup lists at once, widths that are no multiple of a block's, rows without neighbours and with
+    more than a block's row has places for, positions, node ids and ranges that are out of range, a NaN row, outputs beside the listed ones, and a
+    fetch of cached rows in the same launch."""
+    torch, B = env
+    from paper_2301_07482_amd.pipeline import _tensor_from_ptr
+    g = torch.Generator(device="cuda").manual_seed(d_in * 7 + n_rows)
+    rand = lambda *shape: torch.randn(*shape, device="cuda", generator=g)
+    ints = lambda hi, n: torch.randint(0, hi, (n,), device="cuda", generator=g, dtype=torch.int32)
+    table_rows, n_block = 30011, max_rows + 50
+    stride = d_in + 4 * (d_in % 8 == 4)                              # rows further apart than they are long, too
+    table = rand(table_rows, stride)
+    deg = ints(fan + 1, n_block)
+    deg[11::1009] = 41
+    deg[20] = 2
+    end = deg.cumsum(0).to(torch.int32)
+    start = (end - deg).to(torch.int32)
+    nnz = int(end[-1])
+    ids, own = ints(table_rows, nnz), ints(table_rows, n_block)
+    ids[ids == 5] = 6                                                # node 5 is the NaN row: a neighbour of one row, its own row of another
+    table[5] = float("nan")
+    own[own == 5] = 6
+    ids[3::1013] = -1
+    ids[7::1013] = table_rows
+    ids[int(start[20])] = own[30] = 5
+    end[40] = start[40] - 1 if int(start[40]) else -1                # no range: a row without neighbours
+    rows = torch.arange(n_block, device="cuda", dtype=torch.int32)
+    if listed:
+        rows = torch.randperm(n_block, device="cuda", generator=g).to(torch.int32)
+        own[50] = table_rows                                         # (left alone)
+        first = torch.tensor([20, 30, 40, 50], device="cuda", dtype=torch.int32)
+        rows = torch.cat([first, rows[~torch.isin(rows, first)]])
+        rows[5:7] = torch.tensor([-1, n_block], device="cuda", dtype=torch.int32)
+    cnt = torch.tensor([n_rows], dtype=torch.int64, device="cuda")
+    W, bias = rand(2 * d_in, d_out) / (2 * d_in) ** 0.5, rand(d_out)
+    assert B.one_launch_load(nnz, max_rows, d_in, d_out)
+    cache = B.fg_cache_create(1000, [300], [d_out], B.FG_F32, 2, None)
+    try:
+        cached = _tensor_from_ptr(B.fg_cache_table(cache, 1), (300, d_out), torch.float32, 300 * d_out * 4, "cuda")
+        cached.copy_(rand(300, d_out))
+        slots, places, n_hit = ints(300, 77), torch.randperm(500, device="cuda")[:77].to(torch.int32), torch.tensor([61], dtype=torch.int64, device="cuda")
+        outs = []
+        for one in (True, False):
+            agg, fetched = torch.full((max_rows, d_in), 7.0, device="cuda"), torch.full((500, d_out), 7.0, device="cuda")
+            out = torch.full((n_block, d_out), 7.0, device="cuda")
+            specs = B.fetch_layers([dict(layer=1, hit_slot_dev=slots, hit_pos_dev=places, n_hit_dev=n_hit, max_hits=77, h_dev=fetched, h_rows=500,
+                                         h_stride=d_out * 4)])
+            at = rows if listed else None
+            if one:
+                B.fg_gather_aggregate_linear_ids(start, end, ids, nnz, n_block, at, cnt, max_rows, own, table, table_rows, stride * 4, d_in, d_out, W, bias, 1,
+                                                 agg, d_in * 4, out, n_block, d_out * 4, cache, specs)
+            else:
+                B.fg_gather_aggregate_ids(start, end, ids, nnz, n_block, at, cnt, max_rows, own, table, table_rows, stride * 4, d_in, B.FG_F32, agg, d_in * 4,
+                                          B.FG_F32, None, 0, 0, cache, specs)
+            torch.cuda.synchronize()
+            outs.append((agg, out, fetched))
+    finally:
+        B.fg_cache_destroy(cache)
+    (_, out1, f1), (agg2, _, f2) = outs
+    assert torch.equal(f1, f2) and int((f1 != 7.0).any(1).sum()) == 61
+    listed_rows = rows[:n_rows].long()
+    good = (listed_rows >= 0) & (listed_rows < n_block)
+    r = listed_rows[good]
+    ok = (own[r] >= 0) & (own[r] < table_rows)
+    r, mean = r[ok], agg2[:n_rows][good][ok]
+    x = torch.cat([table[own[r].long(), :d_in], mean], 1).double()
+    want = torch.relu(x @ W.double() + bias.double()).cpu().numpy()
+    got = out1[r].cpu().numpy()
+    bad = ~np.isfinite(x.sum(1).cpu().numpy())
+    assert int(bad.sum()) == (2 if n_rows else 0)
+    err = T.rel_err_rows(got[~bad], want[~bad]) if (~bad).any() else 0.0
+    print(f"loader and dense update {d_in}x{d_out} fan-out {fan} rows {n_rows} of {max_rows}: rel err {err:.3e}")
+    assert err <= REL_TOL_F32
+    rest = torch.ones(n_block, dtype=torch.bool, device="cuda")
+    rest[r] = False
+    assert bool((out1[rest] == 7.0).all())
+
+
 @pytest.mark.parametrize("variant", [0, 301, 302, 32, 64])
 @pytest.mark.parametrize("case", ["rows scaled", "mixed within a row", "columns of W scaled", "near the upper limit", "near the lower limit"])
 def test_linear_operands_of_mixed_and_extreme_magnitude(env, case, variant):
