@@ -10,7 +10,7 @@
 //
 // Only rows that were computed (V_normal) pass gradient down; a fetched row receives its gradient and stops there.
 // All of it is small next to the forward pass: the layer below the lowest cached one needs no input gradient.
-#include "common.h"
+#include "update_group.h"
 #include <hip/hip_fp16.h>
 
 namespace {
@@ -1061,10 +1061,24 @@ __device__ __forceinline__ void weight_grad_tile(const WgIn& A, const int unit) 
 }
 
 // SRC: element type of a layer's h_src; TERMS = 1: that or bf16 (a model's input layer has the features' type, the others bf16)
+//
+// U: the cache update of the same iteration (n_layers 0: none), which needs the norms of the embedding gradients as this launch needs the
+// gradients. It is a chain of reads, scans and meetings by a few workgroups that leaves the chip idle; behind the weight gradients it was 14 us
+// of a small training iteration, and on a second stream it cost two waits for events (5 us each), its row copy (28 us beside the products, 9
+// by itself) taking memory time from the products. Its workgroups come first: they are the longer chain where there are few rows, and wait
+// for each other. A compute unit holds one workgroup of either kind, so a chunk of positions is 512 threads with twice the positions of
+// the update's own launch. Training iteration, own launches / here, us: 1.5 k positions 70.5 / 62.0, 28 k 168.5 / 150.0, 74 k 380 / 355, GCN 317 / 293,
+// mixed 288 / 278; the loop with a sampler beside it 410 / 411.
 template <int TERMS, int SRC>
-__global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_kernel(WgBatch B) {
+__global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_kernel(WgBatch B, UpdBatch U) {
+    const int beside = U.n_layers ? U.sel_first[U.n_layers] : 0, block = (int)blockIdx.x - beside;
+    if (block < 0) {
+        extern __shared__ __attribute__((aligned(16))) char wx_lds[];
+        update_group<WG_THREADS, GRP_CHUNK / 4 / WG_THREADS, false>(U, (int)blockIdx.x, *(GrpShared<WG_THREADS / FG_WAVE>*)wx_lds);
+        return;
+    }
     // A chunk's tiles read the same rows: the workgroups of one XCD (ids congruent mod 8) take consecutive (chunk, tile) pairs
-    const int at = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+    const int at = (block & 7) * ((int)(gridDim.x - beside) >> 3) + (block >> 3);
     if (at >= B.first[B.n]) return;       // uniform over the workgroup, before any barrier
     int i = 0;
     while (at >= B.first[i + 1]) ++i;
@@ -1090,14 +1104,21 @@ __global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_kernel(WgBatch B) {
 
 // dw[i] = sum over the chunks of part_w[chunk][i] in fp64. A workgroup owns 128 consecutive elements (32 lanes x 4) and
 // splits the chunks over its 8 wavefront halves; db (the last workgroups) likewise.
+// C: the rows that the update beside the products has admitted, copy_blocks workgroups for each of its layers, first in the grid.
 constexpr int RED_GROUPS = BW_THREADS / 32;
-__global__ __launch_bounds__(BW_THREADS) void weight_grad_reduce_kernel(WgBatch B) {
+__global__ __launch_bounds__(BW_THREADS) void weight_grad_reduce_kernel(WgBatch B, fg_row_copy_batch C, int copy_blocks) {
     __shared__ double red[RED_GROUPS][32][4];
+    const int at = (int)blockIdx.x - C.n * copy_blocks;
+    if (at < 0) {
+        const int part = (int)blockIdx.x % copy_blocks;
+        fg_copy_rows_part(C.c[blockIdx.x / copy_blocks], ((int64_t)part * BW_THREADS + threadIdx.x) >> 6, ((int64_t)copy_blocks * BW_THREADS) >> 6, threadIdx.x & 63);
+        return;
+    }
     int layer = 0;
-    while ((int)blockIdx.x >= B.red_first[layer + 1]) ++layer;
+    while (at >= B.red_first[layer + 1]) ++layer;
     const WgIn& A = B.l[layer];
     const int64_t mn = (int64_t)2 * A.d_in * A.d_out;
-    const int block = (int)blockIdx.x - B.red_first[layer], w_blocks = (int)((mn + 127) / 128);
+    const int block = at - B.red_first[layer], w_blocks = (int)((mn + 127) / 128);
     const int tx = threadIdx.x & 31, g = threadIdx.x >> 5;
     const bool is_w = block < w_blocks;
     const int n_chunks = is_w ? A.n_chunks * A.parts : A.n_chunks;
@@ -1198,7 +1219,8 @@ WgPlan wg_plan(int64_t max_rows, int64_t d_in, int64_t d_out, bool mixed) {
 // itself. A chunk that is longer than by itself leaves several partial results, so that an fp32 sum has no more rows than there
 // (relative error of 6 k rows x 512 x 256 8.7e-8 by itself, 1.9e-7 with one sum per chunk of the shared launch, 8.6e-8 so).
 // The three fp32 layers above: 106 us behind each other, 84.5 together; of 24 k x 104 x 88, 4 k x 176 x 88 and 777 x 176 x 48 rows 49 and 28.
-void wg_share(WgPlan* p, const fg_weight_grad_layer_t* y, int n, bool mixed) {
+// beside: workgroups of an update in the same launch, a compute unit each as well. Up to 32 have the ones left free.
+void wg_share(WgPlan* p, const fg_weight_grad_layer_t* y, int n, bool mixed, int beside) {
     int64_t steps[WG_MAX_LAYERS], most[WG_MAX_LAYERS], total = 0;
     double step_us[WG_MAX_LAYERS], work = 0.0;
     for (int i = 0; i < n; ++i) {
@@ -1209,7 +1231,7 @@ void wg_share(WgPlan* p, const fg_weight_grad_layer_t* y, int n, bool mixed) {
         total += (int64_t)p[i].tiles_m * p[i].tiles_n;
         work += (double)(steps[i] * p[i].tiles_m * p[i].tiles_n) * step_us[i];
     }
-    const int64_t target = work < 224.0 * 150.0 ? 224 : 256;
+    const int64_t free = 256 - beside, target = work < 224.0 * 150.0 && free > 224 ? 224 : free;
     // a workgroup's steps and the partial results it leaves on the way (3 or 5 us each)
     auto time_of = [&](int i) {
         return (double)fg_ceil_div(steps[i], p[i].n_chunks) * step_us[i] + (double)fg_ceil_div(most[i], p[i].n_chunks) * (p[i].tm == 256 ? 5.0 : 3.0);
@@ -1240,10 +1262,13 @@ size_t wg_share_bytes(const fg_weight_grad_layer_t& y, bool mixed) {
 
 // Partial products of every chunk of every layer, then their sums; of one chunk the sums themselves. The layers' workspaces lie
 // behind each other in ws.
-fg_status_t wg_launch(WgIn* in, const WgPlan* p, int n, bool mixed, char* ws, hipStream_t st) {
+fg_status_t wg_launch(WgIn* in, const WgPlan* p, int n, bool mixed, char* ws, hipStream_t st, const UpdBatch* update = nullptr) {
     WgBatch B{};
     B.n = n;
-    size_t lds = 0;
+    UpdBatch U;
+    U.n_layers = 0;
+    if (update) U = *update;
+    size_t lds = update ? sizeof(GrpShared<WG_THREADS / FG_WAVE>) : 0;
     int order[WG_MAX_LAYERS];
     double time[WG_MAX_LAYERS];
     for (int i = 0; i < n; ++i) {
@@ -1277,18 +1302,23 @@ fg_status_t wg_launch(WgIn* in, const WgPlan* p, int n, bool mixed, char* ws, hi
         B.first[q + 1] = B.first[q] + A.n_chunks * A.tiles_m * A.tiles_n;
         B.red_first[q + 1] = B.red_first[q] + (A.n_chunks * A.parts > 1 ? (int)(fg_ceil_div((int64_t)2 * A.d_in * A.d_out, 128) + fg_ceil_div(A.d_out, 128)) : 0);
     }
-    const dim3 grid((unsigned)(fg_ceil_div(B.first[n], 8) * 8));
+    const dim3 grid((unsigned)(fg_ceil_div(B.first[n], 8) * 8 + (update ? U.sel_first[U.n_layers] : 0)));
     if (!mixed)
-        hipLaunchKernelGGL((weight_grad_kernel<3, FG_F32>), grid, dim3(WG_THREADS), lds, st, B);
+        hipLaunchKernelGGL((weight_grad_kernel<3, FG_F32>), grid, dim3(WG_THREADS), lds, st, B, U);
     else if (src == FG_F32)
-        hipLaunchKernelGGL((weight_grad_kernel<1, FG_F32>), grid, dim3(WG_THREADS), lds, st, B);
+        hipLaunchKernelGGL((weight_grad_kernel<1, FG_F32>), grid, dim3(WG_THREADS), lds, st, B, U);
     else if (src == FG_F16)
-        hipLaunchKernelGGL((weight_grad_kernel<1, FG_F16>), grid, dim3(WG_THREADS), lds, st, B);
+        hipLaunchKernelGGL((weight_grad_kernel<1, FG_F16>), grid, dim3(WG_THREADS), lds, st, B, U);
     else
-        hipLaunchKernelGGL((weight_grad_kernel<1, FG_BF16>), grid, dim3(WG_THREADS), lds, st, B);
+        hipLaunchKernelGGL((weight_grad_kernel<1, FG_BF16>), grid, dim3(WG_THREADS), lds, st, B, U);
     FG_LAUNCH_CHECK("weight_grad_kernel");
-    if (B.red_first[n] == 0) return FG_OK;
-    hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3((unsigned)B.red_first[n]), dim3(BW_THREADS), 0, st, B);
+    fg_row_copy_batch copies;
+    copies.n = 0;
+    if (update) fg_update_row_copies(U, &copies);
+    if (B.red_first[n] == 0) return fg_launch_row_copies(copies, st);
+    const int copy_blocks = update ? fg_row_copy_blocks(copies) : 0;
+    if (copy_blocks == 0) copies.n = 0;
+    hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3((unsigned)(B.red_first[n] + copies.n * copy_blocks)), dim3(BW_THREADS), 0, st, B, copies, copy_blocks);
     FG_LAUNCH_CHECK("weight_grad_reduce_kernel");
     return FG_OK;
 }
@@ -1399,6 +1429,11 @@ extern "C" size_t fg_backward_weights_all_workspace_bytes(fg_dtype_t compute_dty
 
 extern "C" fg_status_t fg_backward_weights_all(fg_dtype_t compute_dtype, int32_t n_layers, const fg_weight_grad_layer_t* layers, void* ws_dev,
                                                size_t ws_bytes, void* stream) {
+    return fg_backward_weights_with(compute_dtype, n_layers, layers, ws_dev, ws_bytes, nullptr, stream);
+}
+
+fg_status_t fg_backward_weights_with(fg_dtype_t compute_dtype, int32_t n_layers, const fg_weight_grad_layer_t* layers, void* ws_dev, size_t ws_bytes,
+                                     const UpdBatch* update, void* stream) {
     const char* who = "fg_backward_weights_all";
     if (compute_dtype != FG_F32 && compute_dtype != FG_BF16) FG_FAIL(FG_ERR_DTYPE, "%s: compute_dtype must be F32 or BF16", who);
     if (n_layers < 1 || n_layers > WG_MAX_LAYERS || !layers)
@@ -1423,6 +1458,6 @@ extern "C" fg_status_t fg_backward_weights_all(fg_dtype_t compute_dtype, int32_t
     if (!ws_dev || ws_bytes < need) FG_FAIL(FG_ERR_SHAPE, "%s: workspace of %zu bytes given, %zu needed", who, ws_bytes, need);
     if ((uintptr_t)ws_dev & 15) FG_FAIL(FG_ERR_INVALID_ARG, "%s: the workspace must be 16-byte aligned", who);
     fg_clear_error();
-    wg_share(p, layers, n_layers, mixed);
-    return wg_launch(in, p, n_layers, mixed, (char*)ws_dev, (hipStream_t)stream);
+    wg_share(p, layers, n_layers, mixed, update ? update->sel_first[update->n_layers] : 0);
+    return wg_launch(in, p, n_layers, mixed, (char*)ws_dev, (hipStream_t)stream, update);
 }

@@ -29,118 +29,9 @@
 // admissible nodes and one more launch between 3 and 4 (rank_saving) finds the estimate of rank `room` from the top,
 // re-flags every admissible node as in / tie / out and counts per workgroup; launch 4 then lets the first ties in
 // position order fill what the larger estimates leave of the room.
-#include "common.h"
-#include "meeting.h"
-#include "scan.h"
+#include "update_group.h"
 
 namespace {
-
-struct UpdHeader {        // lives at the start of a layer's update workspace
-    uint32_t tau_key;     // order-preserving key of tau, or its leading digits where no smaller key shares them
-    int32_t mode;         // 0: nothing is below tau, 1: compare with tau_key, 2: everything is below tau
-    int64_t n_admit;      // rows to copy (<= capacity)
-    int64_t m_live;
-    int64_t n_cand;       // access-aware policy: admissible nodes, and how many of those whose estimate equals the
-    int64_t tie_room;     //   threshold estimate still fit (-1: every admissible node fits)
-};
-
-__device__ __forceinline__ int clamp_saving(int32_t a) { return a < 0 ? 0 : (a > 2047 ? 2047 : a); }
-
-__device__ __forceinline__ uint32_t order_key(float f) {
-    const uint32_t b = __float_as_uint(f);
-    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
-
-constexpr int SEL_THREADS = 1024;
-constexpr int SEL_BINS = 2048;
-constexpr int SEL_BPT = SEL_BINS / SEL_THREADS;  // bins owned by a thread in the scan
-constexpr int SEL_CHUNK = 4 * SEL_THREADS;       // keys per workgroup in the histogram launches
-constexpr int FG_MAX_UPD_LAYERS = 8;
-
-// Selection scratch of a layer, owned by the cache. All-zero between updates: launch 4, or the last of the group, clears it again.
-struct SelState {
-    unsigned int hist0[SEL_BINS];
-    unsigned int hist1[SEL_BINS];
-    unsigned int n_surv;
-    unsigned int arrived[3];       // workgroups that have counted their keys' digit (update_group_kernel)
-    unsigned int done;             // ... and that have left the scratch alone
-    unsigned int admits[64];       // a workgroup's admissible nodes, published (meeting.h)
-    unsigned int hist2[SEL_BINS];  // estimates of saved accesses of the admissible nodes (access-aware policy), or the third digit
-};
-
-static_assert(SEL_BINS == 2048, "clamp_saving saturates the estimates at the last bin");
-
-struct CacheRW {
-    int32_t* map;
-    int32_t* slot_node;
-    int32_t* slot_stamp;
-    const int64_t* head;  // current ring header
-    int64_t* head_next;   // where an update leaves the advanced header (the two swap roles after every update)
-    int64_t* used;        // slots written at least once (what the ring has overwritten of the shared buffer)
-    int64_t capacity;
-    int64_t num_nodes;
-    int64_t iter;
-    int32_t t_stale;
-};
-
-struct UpdLayer {
-    CacheRW c;
-    const int32_t* ids;
-    const uint8_t* live;
-    const uint8_t* hit;
-    const float* gnorm;
-    int64_t* stats;
-    SelState* sel;
-    UpdHeader* hdr;
-    uint8_t* flag;       // per position: 0 not admitted, 1 admissible (in position order while there is room), 2 in for sure
-    int32_t* blk;        // flag-1 nodes per workgroup of launch 3
-    int32_t* blk_sure;   // flag-2 nodes per workgroup (access-aware policy)
-    const int32_t* saving;  // estimates of saved accesses by position, or NULL
-    int64_t room;        // rows this update may admit (<= capacity)
-    int32_t* apos;       // admitted positions; before launch 4 the same memory holds the survivor keys
-    int32_t* aslot;      // their slots
-    const char* h;
-    int64_t h_stride;
-    char* table;
-    int64_t row_bytes;
-    int32_t n;           // positions of the layer: the caller's bound ...
-    const int64_t* n_dev;  // ... and, if non-null, the count in device memory (positions at or beyond it are not live)
-    float p_grad;
-};
-
-// positions of the layer that exist: the device-side count where the caller gave one, never above the bound
-__device__ __forceinline__ int upd_count(const UpdLayer& L) {
-    if (!L.n_dev) return L.n;
-    const int64_t c = *L.n_dev;
-    return c < 0 ? 0 : (c < (int64_t)L.n ? (int)c : L.n);
-}
-
-struct UpdBatch {
-    int32_t n_layers;
-    int32_t polls;                              // before a workgroup that waits for others gives up
-    int32_t sel_first[FG_MAX_UPD_LAYERS + 1];   // first workgroup of each layer in launches 1 and 2
-    int32_t scan_first[FG_MAX_UPD_LAYERS + 1];  // the same for launches 3 and 4
-    UpdLayer l[FG_MAX_UPD_LAYERS];
-};
-
-// leaves the number of admitted rows, the advanced ring header and how far the ring has ever been written
-__device__ __forceinline__ void finish_header(const UpdLayer& L, int64_t head, int64_t used, int64_t in) {
-    const CacheRW& c = L.c;
-    L.hdr->n_admit = in;
-    const int64_t reach = head + in;  // the ring fills slots upwards until it first wraps (head < capacity, in <= capacity)
-    *c.head_next = reach < c.capacity ? reach : reach - c.capacity;
-    if (reach >= c.capacity)
-        *c.used = c.capacity;
-    else if (reach > used)
-        *c.used = reach;
-}
-
-__device__ __forceinline__ int layer_of_block(const int32_t* first, int n_layers, int b, int& local) {
-    int l = 0;
-    while (l + 1 < n_layers && b >= first[l + 1]) ++l;
-    local = b - first[l];
-    return l;
-}
 
 // Finds the bin holding rank *s_rank in hist[] (counts), stores it in *s_bin and rebases *s_rank to that bin.
 __device__ __forceinline__ void select_bin(const unsigned int* hist, long long* red, uint32_t* s_bin, long long* s_rank) {
@@ -350,333 +241,11 @@ __global__ __launch_bounds__(FG_SCAN_BLOCK) void classify_update_kernel(UpdBatch
     }
 }
 
-// ---- launches 1 to 4 as one: a layer by one workgroup per 4096 positions --------------------------------------------------------
-//
-// What bounds the four launches is not their work but their chain: each is a few dependent reads, barriers
-// and scans long (6 + 9 + 13 + 6 us at 1.2 k positions, hardly more at 54 k), and workgroups of 1024 threads wait for room beside the
-// weight gradients (the third launch, 72 of them at 67 k positions, 33 us there). A workgroup of 1024 threads holds the keys of
-// 4096 positions in registers (four per thread), so it reads them once, finds tau by up to three digits,
-// classifies, ranks the admissible nodes and hands out their slots. By itself it finds the digits in LDS; the workgroups of a larger
-// layer meet up to four times: behind the histogram of each digit, and behind the check-outs, with the numbers of admissible nodes. (The keys that
-// carry the first digit as a list, from which each workgroup finds the other two for itself: a meeting less, but up to a third of
-// a layer's norms share a digit, and at 67 k positions the list took 5 + 6 us, 5 + 11 in a GCN, for 9 of two meetings.) The
-// histograms are kept four times (by lane mod 4): norms share their leading digits, and equal bins of a wavefront are
-// added one after the other.
-// Who waits needs no more than that the other workgroups start: they are at most 64 in all, so that they are all there together on a chip
-// with room for 512 of their size, and a launch they have to wait behind ends without them. The polls are bounded all the same: a workgroup
-// that gives up takes its whole layer along (meeting.h), which then admits nothing and says so in its statistics; what it has checked
-// out until then stays out.
-// Between the barriers the chain is kept short: prefix sums inside the vector registers, a wavefront's place among the others' totals from
-// four wide LDS reads, each thread clearing the counters it read, no division (with shuffles, a loop over the wavefronts and 64-bit
-// remainders 17.6 us at 1.2 k positions, 14.2 so, 12.9 with two digits where they decide; a third of what is left is the row copy and the first reads).
-// Measured, the four launches and now: 28 k positions 36 us and their gaps, 24; 74 k beside the weight gradients of 55 k rows 66, 27; 1.2 k with
-// its row copy 31, 13 (one workgroup).
-constexpr int ONE_COPIES = 4;
-constexpr int SEL_WAVES = SEL_THREADS / FG_WAVE;
-constexpr int GRP_CHUNK = 4 * SEL_THREADS;      // positions of a workgroup
-constexpr int GRP_MAX = 64;                     // workgroups of a launch
-
-__device__ __attribute__((aligned(16))) uint32_t upd_spare[4];      // what is read where a layer has no quad
-
-// Place of a thread's two of 2048 counters: c0 + c1 of the threads before it, and of all. `red` needs SEL_WAVES words and is read until the
-// next barrier.
-__device__ __forceinline__ uint32_t scan_two(uint32_t c0, uint32_t c1, uint32_t* red, uint32_t& all) {
-    static_assert(SEL_BPT == 2, "two bins per thread");
-    const uint32_t incl = (uint32_t)fg_wave_scan((int)(c0 + c1));
-    if (fg_lane() == FG_WAVE - 1) red[fg_wave()] = incl;
-    __syncthreads();
-    uint32_t before;
-    fg_wave_totals<SEL_WAVES>((const int*)red, (int&)before, (int&)all);
-    return before + incl - c0 - c1;
-}
-
-// The thread whose two bins hold the key of rank `rank` leaves the bin and the rank within it; c0, c1 and lo as scan_two has them.
-__device__ __forceinline__ void find_bin(uint32_t c0, uint32_t c1, uint32_t lo, uint32_t rank, uint2* out) {
-    if (rank >= lo && rank < lo + c0 + c1) {
-        const bool second = rank >= lo + c0;
-        *out = uint2{2 * threadIdx.x + (second ? 1u : 0u), rank - (second ? lo + c0 : lo)};
-    }
-}
-
-// This thread's two counters of hist[bin * ONE_COPIES + copy], which are zero again afterwards
-__device__ __forceinline__ void take_bins(uint32_t* hist, uint32_t& c0, uint32_t& c1) {
-    static_assert(ONE_COPIES == 4, "four counters per bin");
-    uint4* mine = (uint4*)hist + 2 * threadIdx.x;
-    const uint4 a = mine[0], b = mine[1];
-    mine[0] = mine[1] = uint4{0, 0, 0, 0};
-    c0 = a.x + a.y + a.z + a.w;
-    c1 = b.x + b.y + b.z + b.w;
-}
-
-// What the workgroups of a layer tell each other goes past the caches of their XCDs, word by word (atomics of agent scope); before a
-// workgroup says that it is there, each of its wavefronts waits until its own have arrived. (Release and acquire fences instead
-// write back and invalidate whole L2s: some 3 us more for each meeting, 15 beside the weight gradients.)
-template <typename T>
-__device__ __forceinline__ T grp_load(const T* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename T>
-__device__ __forceinline__ void grp_store(T* p, T v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void grp_arrive() {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-}
-
-// All `n` workgroups of a layer have come here and none has given up.
-__device__ __forceinline__ bool grp_meet(unsigned int* arrived, unsigned int n, int polls, int* s_ok) {
-    grp_arrive();
-    if (threadIdx.x == 0) *s_ok = fg_meet(FgAgentMem{}, arrived, n, polls);
-    __syncthreads();
-    return *s_ok != 0;
-}
-
-// COPY (every layer has one workgroup): the admitted rows are copied here as well (a launch less) instead of by the row copy behind it.
+// Launches 1 to 4 as one (update_group.h)
 template <bool COPY>
 __global__ __launch_bounds__(SEL_THREADS) void update_group_kernel(UpdBatch B) {
-    __shared__ __attribute__((aligned(16))) uint32_t hist[SEL_BINS * ONE_COPIES];
-    __shared__ __attribute__((aligned(16))) int wave_count[SEL_WAVES];
-    __shared__ __attribute__((aligned(16))) uint32_t red[2][SEL_WAVES];      // alternating: read while the next pass writes
-    __shared__ uint2 s_found[3];      // by digit: its value, and the rank of tau among the keys that carry it and those before
-    __shared__ int s_evicted, s_over, s_ok, s_before, s_all;
-    int part;
-    const int layer = layer_of_block(B.sel_first, B.n_layers, blockIdx.x, part);
-    const UpdLayer& L = B.l[layer];
-    const CacheRW& c = L.c;
-    const unsigned int parts = (unsigned int)(B.sel_first[layer + 1] - B.sel_first[layer]);
-    const int t = threadIdx.x, lane = fg_lane(), wave = fg_wave();
-    const int n_all = upd_count(L), base = part * GRP_CHUNK;
-    const int n = n_all - base < 0 ? 0 : (n_all - base < GRP_CHUNK ? n_all - base : GRP_CHUNK);      // positions of this workgroup
-    const int64_t head = *c.head, used = *c.used;
-    // Position of element e: base + 4 * t + e. Every read is unconditional (the first quad, or 16 bytes of the
-    // library's own, where a quad is not wholly there) so that they are in flight together; the one quad that the end of the layer
-    // cuts is read one by one by the thread that owns it, and joins below.
-    const int n_quads = n >> 2;
-    const bool cut = (n & 3) != 0 && n_quads == t, whole = t < n_quads;
-    uint32_t key[4], is_live = 0, is_hit = 0;      // a bit per element
-    int32_t id[4];
-    {
-        typedef float f4 __attribute__((ext_vector_type(4)));
-        const bool any = n_quads > 0;
-        const uint32_t at = whole ? (uint32_t)t : 0u;
-        const char* none = (const char*)upd_spare;
-        const char* hit_base = any ? (const char*)L.hit + base : none;
-        const f4 g = *(const f4*)((any ? (const char*)L.gnorm + 4 * (int64_t)base : none) + 16u * at);
-        const uint32_t l4 = *(const uint32_t*)((any && L.live ? (const char*)L.live + base : hit_base) + 4u * at) | (L.live ? 0u : 0x01010101u);
-        const uint32_t h4 = *(const uint32_t*)(hit_base + 4u * at);
-        const int4 v4 = *(const int4*)((any ? (const char*)L.ids + 4 * (int64_t)base : none) + 16u * at);
-        id[0] = v4.x;
-        id[1] = v4.y;
-        id[2] = v4.z;
-        id[3] = v4.w;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            key[e] = order_key(g[e]);
-            is_live |= ((l4 >> (8 * e)) & 0xFFu) ? 1u << e : 0u;
-            is_hit |= ((h4 >> (8 * e)) & 0xFFu) ? 1u << e : 0u;
-        }
-        if (!whole) is_live = is_hit = 0;
-        if (cut)
-#pragma unroll
-            for (int e = 0; e < 3; ++e) {
-                const int j = base + 4 * n_quads + e;
-                if (j >= n_all) continue;
-                key[e] = order_key(L.gnorm[j]);
-                id[e] = L.ids[j];
-                if (L.live ? L.live[j] != 0 : true) is_live |= 1u << e;
-                if (L.hit[j] != 0) is_hit |= 1u << e;
-            }
-    }
-    auto count_key = [&](uint32_t bin) { atomicAdd(&hist[bin * ONE_COPIES + (lane & (ONE_COPIES - 1))], 1u); };
-    if (t == 0) s_evicted = s_over = 0;
-    for (int b = t; b < SEL_BINS * ONE_COPIES / 4; b += SEL_THREADS) ((uint4*)hist)[b] = uint4{0, 0, 0, 0};
-    bool lost = false;
-    uint32_t m = 0, tau_key = 0;
-    int mode = 1;
-    if (parts > 1 && part == 0 && t < 4 && L.stats) grp_store(&L.stats[t], (int64_t)0);
-    __syncthreads();
-    // tau is the key of rank k, found digit by digit (11 + 11 + 10 bits); mode is the same for all workgroups of the layer. A key that is the
-    // smallest of those with its digits so far divides the others as these digits with zeros behind them do: of a few thousand norms
-    // two digits are as good as always enough.
-    bool exact = false;
-#pragma unroll 1
-    for (int pass = 0; pass < 3 && mode == 1 && !exact; ++pass) {
-        const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
-        const uint32_t bins = pass == 2 ? 1023u : 2047u;
-        const uint32_t above = pass == 0 ? 0u : (pass == 1 ? 0xFFE00000u : 0xFFFFFC00u);      // the digits found so far
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (((is_live >> e) & 1u) && (key[e] & above) == tau_key) count_key((key[e] >> shift) & bins);
-        __syncthreads();
-        uint32_t c0, c1, all;
-        take_bins(hist, c0, c1);
-        if (parts > 1) {
-            unsigned int* shared = pass == 0 ? L.sel->hist0 : (pass == 1 ? L.sel->hist1 : L.sel->hist2);
-            if (c0) atomicAdd(&shared[2 * t], c0);
-            if (c1) atomicAdd(&shared[2 * t + 1], c1);
-            lost = !grp_meet(&L.sel->arrived[pass], parts, B.polls, &s_ok);
-            c0 = grp_load(&shared[2 * t]);
-            c1 = grp_load(&shared[2 * t + 1]);
-        }
-        const uint32_t lo = scan_two(c0, c1, red[pass & 1], all);
-        uint32_t rank;
-        if (pass == 0) {
-            m = all;
-            const long long k = (long long)floor((double)L.p_grad * (double)m);
-            mode = k <= 0 ? 0 : (k >= (long long)m ? 2 : 1);
-            rank = (uint32_t)k;
-        } else {
-            rank = s_found[pass - 1].y;
-        }
-        if (lost) {
-            mode = 0;
-            if (t == 0)
-                for (int p = pass + 1; p < 3; ++p) fg_lost_ahead(FgAgentMem{}, &L.sel->arrived[p]);
-        }
-        if (mode == 1) {
-            find_bin(c0, c1, lo, rank, &s_found[pass]);
-            __syncthreads();
-            tau_key |= s_found[pass].x << shift;
-            exact = s_found[pass].y == 0;
-        }
-    }
-    // check-outs and admissible nodes
-    uint32_t admit_bits = 0;
-    int evicted = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const bool low = mode == 2 || (mode == 1 && key[e] < tau_key);
-        if (lost || !((is_live >> e) & 1u) || id[e] < 0 || id[e] >= c.num_nodes || (((is_hit >> e) & 1u) != 0) == low) continue;
-        if (low) {
-            admit_bits |= 1u << e;
-        } else {
-            grp_store(&c.map[id[e]], -1);
-            ++evicted;
-        }
-    }
-    // ranks in position order: workgroups first, then threads, then a thread's elements
-    const int own = __popc(admit_bits);
-    const int both = fg_wave_scan(own | evicted << 16), incl = both & 0xFFFF;      // (at most 256 of each in a wavefront)
-    if (lane == FG_WAVE - 1) {
-        wave_count[wave] = incl;
-        if (both >> 16) atomicAdd(&s_evicted, both >> 16);
-    }
-    __syncthreads();
-    int before, total;
-    fg_wave_totals<SEL_WAVES>(wave_count, before, total);
-    before += incl - own;
-    if (parts > 1) {      // what the other workgroups admit, behind all check-outs
-        grp_arrive();
-        if (wave == 0) {
-            uint32_t w = FG_PUBLISHED;
-            if (t == 0) fg_publish(FgAgentMem{}, &L.sel->admits[part], lost ? FG_GIVEN_UP : (uint32_t)total);
-            if (t < (int)parts && !lost) w = fg_settled(FgAgentMem{}, &L.sel->admits[t], B.polls);
-            int there = (int)(w & ~(FG_PUBLISHED | FG_GIVEN_UP)), ahead = t < part ? there : 0;
-            for (int off = FG_WAVE / 2; off > 0; off >>= 1) {
-                there += __shfl_xor(there, off, FG_WAVE);
-                ahead += __shfl_xor(ahead, off, FG_WAVE);
-            }
-            const bool all_there = __all((w & FG_GIVEN_UP) == 0) && !lost;
-            if (t == 0) {
-                s_before = ahead;
-                s_all = there;
-                s_ok = all_there;
-            }
-        }
-        __syncthreads();
-        before += s_before;
-        total = s_all;
-        if (!s_ok) lost = true;
-    }
-    if (lost) admit_bits = 0;
-    int over = 0;
-    {
-        int32_t slot[4], old[4], old_map[4], old_stamp[4];
-        int rank[4];
-        bool in[4];
-        // the four chains slot -> owner -> its map entry side by side (reads of slot 0 / node 0 where there is nothing to do)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            rank[e] = before + __popc(admit_bits & ((1u << e) - 1u));
-            in[e] = ((admit_bits >> e) & 1u) != 0 && rank[e] < L.room;
-            const int64_t at = head + rank[e];      // head < capacity, rank < room <= capacity
-            slot[e] = in[e] ? (int32_t)(at < c.capacity ? at : at - c.capacity) : 0;
-            old[e] = c.slot_node[slot[e]];
-            old_stamp[e] = c.slot_stamp[slot[e]];
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) old_map[e] = grp_load(&c.map[old[e] >= 0 && old[e] < c.num_nodes ? old[e] : 0]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (!in[e]) continue;
-            if (old[e] >= 0 && old[e] < c.num_nodes && old_map[e] == slot[e]) {
-                const int64_t age = c.iter + 1 - (int64_t)old_stamp[e];
-                over += age >= 1 && age <= (int64_t)c.t_stale ? 1 : 0;
-            }
-            c.slot_node[slot[e]] = id[e];
-            c.slot_stamp[slot[e]] = (int32_t)c.iter;
-            c.map[id[e]] = slot[e];
-            L.apos[rank[e]] = base + 4 * t + e;
-            L.aslot[rank[e]] = slot[e];
-            if (COPY) ((int2*)hist)[rank[e]] = int2{4 * t + e, slot[e]};      // (the histograms are not needed any more)
-        }
-    }
-    over = fg_wave_scan(over);
-    if (lane == FG_WAVE - 1 && over) atomicAdd(&s_over, over);
-    __syncthreads();
-    if (t == 0) {
-        const int64_t in = lost ? 0 : (total < L.room ? total : L.room);
-        if (part == 0) {
-            L.hdr->mode = mode;
-            L.hdr->tau_key = tau_key;
-            L.hdr->m_live = m;
-            finish_header(L, head, used, in);
-        }
-        if (L.stats) {
-            if (part == 0) {
-                L.stats[0] = lost ? -1 : in;
-                L.stats[3] = lost ? -1 : total - in;
-            }
-            if (parts == 1) {
-                L.stats[1] = s_evicted;
-                L.stats[2] = s_over;
-            } else {
-                if (s_evicted) atomicAdd((unsigned long long*)&L.stats[1], (unsigned long long)s_evicted);
-                if (s_over) atomicAdd((unsigned long long*)&L.stats[2], (unsigned long long)s_over);
-            }
-        }
-        // the last to come here clears the scratch: nobody reads it any more
-        if (parts > 1) s_ok = __hip_atomic_fetch_add(&L.sel->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
-    }
-    if (parts > 1) {
-        __syncthreads();
-        if (s_ok) {
-            for (int b = t; b < SEL_BINS; b += SEL_THREADS) L.sel->hist0[b] = L.sel->hist1[b] = L.sel->hist2[b] = 0;
-            if (t < 64) L.sel->admits[t] = 0;
-            if (t < 3) L.sel->arrived[t] = 0;
-            if (t == 0) L.sel->done = 0;
-        }
-    }
-    if constexpr (COPY) {
-        static_assert(sizeof(hist) >= GRP_CHUNK * sizeof(int2), "every position may be admitted");
-        typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-        const int pieces = (int)(L.row_bytes >> 4), items = (int)(total < L.room ? total : L.room) * pieces;
-        constexpr int TOGETHER = 8;
-        for (int i0 = t; i0 < items; i0 += TOGETHER * SEL_THREADS) {
-            u32x4 v[TOGETHER];
-#pragma unroll
-            for (int u = 0; u < TOGETHER; ++u) {
-                const int i = i0 + u * SEL_THREADS < items ? i0 + u * SEL_THREADS : i0, r = i / pieces;
-                v[u] = *((const u32x4*)(L.h + (int64_t)((const int2*)hist)[r].x * L.h_stride) + (i - r * pieces));
-            }
-#pragma unroll
-            for (int u = 0; u < TOGETHER; ++u) {
-                const int i = i0 + u * SEL_THREADS, r = i / pieces;
-                if (i < items) *((u32x4*)(L.table + (int64_t)((const int2*)hist)[r].y * L.row_bytes) + (i - r * pieces)) = v[u];
-            }
-        }
-    }
+    __shared__ GrpShared<SEL_THREADS / FG_WAVE> S;
+    update_group<SEL_THREADS, 1, COPY>(B, blockIdx.x, S);
 }
 
 // Access-aware policy, between classify and assign_slots: with T admissible nodes and room for R < T of them, the R
@@ -1096,9 +665,8 @@ fg_status_t prepare_update_layer(fg_cache_t* cache, const char* who, int32_t lay
     return FG_OK;
 }
 
-// The launches for the layers described in B (descriptors complete, first-workgroup tables not yet): `select` = the
-// four (five with the access-aware ranking) launches that decide and write the cache's index, `commit` = the row copy.
-fg_status_t launch_update(UpdBatch& B, hipStream_t st, bool select = true, bool commit = true) {
+// The first workgroup of each layer
+void place_workgroups(UpdBatch& B) {
     B.sel_first[0] = B.scan_first[0] = 0;
     B.polls = fg_polls();
     for (int i = 0; i < B.n_layers; ++i) {  // at least one workgroup per layer: it resets the statistics and writes the header
@@ -1106,17 +674,28 @@ fg_status_t launch_update(UpdBatch& B, hipStream_t st, bool select = true, bool 
         B.sel_first[i + 1] = B.sel_first[i] + (int)fg_ceil_div(n, SEL_CHUNK);
         B.scan_first[i + 1] = B.scan_first[i] + (int)fg_ceil_div(n, FG_SCAN_BLOCK);
     }
-    const unsigned n_sel = (unsigned)B.sel_first[B.n_layers], n_scan = (unsigned)B.scan_first[B.n_layers];
-    // A workgroup per 4096 positions in one launch where the layers' arrays can be read four at a time, no layer ranks by saved accesses
-    // (that needs the counts of all its admissible nodes first) and the workgroups are few enough to wait for each other. A selection by
-    // itself runs beside the layers, where four short launches are in nobody's way, and workgroups that wait are: up to five of them
-    // there (step of 9 k positions 77 us with the four launches, 75.5 with the group; 15 k 100, 97; 24 k 98, 99.5; 67 k 200, 207).
-    bool group = n_sel <= (unsigned)(commit ? GRP_MAX : (B.n_layers > 5 ? B.n_layers : 5));
+}
+
+// Whether at most `most` workgroups of 4096 positions can decide the update in one launch: where the layers' arrays can be read four at a
+// time, no layer ranks by saved accesses (that needs the counts of all its admissible nodes first) and the workgroups are few
+// enough to wait for each other.
+bool one_group(const UpdBatch& B, int most) {
+    bool group = B.sel_first[B.n_layers] <= most;
     for (int i = 0; i < B.n_layers; ++i) {
         const UpdLayer& u = B.l[i];
         group = group && !u.saving && !(((uintptr_t)u.gnorm | (uintptr_t)u.ids) & 15) && !(((uintptr_t)u.live | (uintptr_t)u.hit) & 3);
     }
-    if (select && group) {
+    return group;
+}
+
+// The launches for the layers described in B (descriptors complete, first-workgroup tables not yet): `select` = the
+// four (five with the access-aware ranking) launches that decide and write the cache's index, `commit` = the row copy.
+fg_status_t launch_update(UpdBatch& B, hipStream_t st, bool select = true, bool commit = true) {
+    place_workgroups(B);
+    const unsigned n_sel = (unsigned)B.sel_first[B.n_layers], n_scan = (unsigned)B.scan_first[B.n_layers];
+    // A selection by itself runs beside the layers, where four short launches are in nobody's way, and workgroups that wait are: up to five of them
+    // there (step of 9 k positions 77 us with the four launches, 75.5 with the group; 15 k 100, 97; 24 k 98, 99.5; 67 k 200, 207).
+    if (select && one_group(B, commit ? GRP_MAX : (B.n_layers > 5 ? B.n_layers : 5))) {
         const dim3 grid(n_sel), block(SEL_THREADS);
         // About p_grad of the positions are admitted. Up to 160 KB of their rows go with the selection: one compute unit copies
         // them at some 60 GB/s, which up to there costs the device about what the launch it saves costs it, and the host is spared that
@@ -1150,17 +729,22 @@ fg_status_t launch_update(UpdBatch& B, hipStream_t st, bool select = true, bool 
         FG_LAUNCH_CHECK("assign_slots_kernel");
     }
     if (!commit) return FG_OK;
-    fg_row_copy_batch copies;  // table[aslot[k], :] = h[apos[k], :] for the admitted rows of every layer
-    copies.n = B.n_layers;
-    for (int i = 0; i < B.n_layers; ++i) {
-        const UpdLayer& u = B.l[i];
-        const int64_t cap = u.n < u.c.capacity ? u.n : u.c.capacity;
-        copies.c[i] = fg_row_copy{u.h, u.n, u.h_stride, u.apos, u.aslot, &u.hdr->n_admit, cap, u.table, u.c.capacity, u.row_bytes, u.row_bytes};
-    }
+    fg_row_copy_batch copies;
+    fg_update_row_copies(B, &copies);
     return fg_launch_row_copies(copies, st);
 }
 
 }  // namespace
+
+// table[aslot[k], :] = h[apos[k], :] for the admitted rows of every layer
+void fg_update_row_copies(const UpdBatch& B, fg_row_copy_batch* copies) {
+    copies->n = B.n_layers;
+    for (int i = 0; i < B.n_layers; ++i) {
+        const UpdLayer& u = B.l[i];
+        const int64_t cap = u.n < u.c.capacity ? u.n : u.c.capacity;
+        copies->c[i] = fg_row_copy{u.h, u.n, u.h_stride, u.apos, u.aslot, &u.hdr->n_admit, cap, u.table, u.c.capacity, u.row_bytes, u.row_bytes};
+    }
+}
 
 extern "C" fg_status_t fg_cache_update(fg_cache_t* cache, int32_t layer, int64_t iter, const int32_t* ids_dev,
                                        int32_t n, const uint8_t* live_dev, const uint8_t* hit_dev,
@@ -1187,10 +771,9 @@ extern "C" fg_status_t fg_cache_update(fg_cache_t* cache, int32_t layer, int64_t
 
 namespace {
 
-// phase 0: the whole update; 1: selection and index only; 2: the row copy of a selection made by phase 1 with the same
-// descriptors and workspace (the ring headers have been swapped by then, so the descriptors are rebuilt without them)
-fg_status_t update_all(const char* who, int phase, fg_cache_t* cache, int64_t iter, float p_grad, int32_t n_layers,
-                       const fg_update_layer_t* layers, void* ws_dev, size_t ws_bytes, void* stream) {
+// Checks a call (phases as below) and describes its layers.
+fg_status_t describe_update(const char* who, int phase, fg_cache_t* cache, int64_t iter, float p_grad, int32_t n_layers,
+                            const fg_update_layer_t* layers, void* ws_dev, size_t ws_bytes, UpdBatch* B) {
     if (n_layers < 0 || n_layers > FG_MAX_UPD_LAYERS) FG_FAIL(FG_ERR_INVALID_ARG, "%s: n_layers = %d outside 0..%d", who, n_layers, FG_MAX_UPD_LAYERS);
     if (n_layers > 0 && !layers) FG_FAIL(FG_ERR_INVALID_ARG, "%s: layers is NULL", who);
     if ((uintptr_t)ws_dev & 15) FG_FAIL(FG_ERR_INVALID_ARG, "%s: workspace must be 16-byte aligned", who);
@@ -1203,8 +786,7 @@ fg_status_t update_all(const char* who, int phase, fg_cache_t* cache, int64_t it
                 FG_FAIL(FG_ERR_STATE, "%s: layer %d has no selection of iteration %lld waiting for its rows", who, layer, (long long)iter);
         }
     }
-    UpdBatch B;
-    B.n_layers = n_layers;
+    B->n_layers = n_layers;
     size_t off = 0;
     for (int i = 0; i < n_layers; ++i) {
         for (int k = 0; k < i; ++k)
@@ -1212,17 +794,18 @@ fg_status_t update_all(const char* who, int phase, fg_cache_t* cache, int64_t it
         const fg_update_layer_t& a = layers[i];
         if (phase != 2 && cache && a.layer >= 1 && a.layer <= cache->n_layers && cache->layers[a.layer - 1].copy_pending)
             FG_FAIL(FG_ERR_STATE, "%s: layer %d still waits for fg_cache_update_commit", who, a.layer);
-        fg_status_t rc = prepare_update_layer(cache, who, a.layer, phase == 2 ? cache->layers[a.layer - 1].last_iter : iter, a.ids_dev, a.n,
+        const fg_status_t rc = prepare_update_layer(cache, who, a.layer, phase == 2 ? cache->layers[a.layer - 1].last_iter : iter, a.ids_dev, a.n,
                                               a.live_dev, a.hit_dev, a.gnorm_dev, p_grad, a.h_dev, a.h_stride, a.stats_dev,
-                                              (char*)ws_dev + off, &B.l[i], a.saving_dev, a.max_admit, a.n_dev);
+                                              (char*)ws_dev + off, &B->l[i], a.saving_dev, a.max_admit, a.n_dev);
         if (rc != FG_OK) return rc;
         off += upd_layout(a.n).total;
     }
     if (n_layers > 0 && (!ws_dev || ws_bytes < off)) FG_FAIL(FG_ERR_SHAPE, "%s: workspace of %zu bytes given, %zu needed", who, ws_bytes, off);
-    fg_clear_error();
-    if (n_layers == 0) return FG_OK;
-    fg_status_t rc = launch_update(B, (hipStream_t)stream, phase != 2, phase != 1);
-    if (rc != FG_OK) return rc;
+    return FG_OK;
+}
+
+// its launches are queued
+void update_queued(int phase, fg_cache_t* cache, int64_t iter, int32_t n_layers, const fg_update_layer_t* layers) {
     for (int i = 0; i < n_layers; ++i) {
         fg_layer* l = &cache->layers[layers[i].layer - 1];
         if (phase != 2) {
@@ -1231,10 +814,34 @@ fg_status_t update_all(const char* who, int phase, fg_cache_t* cache, int64_t it
         }
         l->copy_pending = phase == 1;
     }
+}
+
+// phase 0: the whole update; 1: selection and index only; 2: the row copy of a selection made by phase 1 with the same
+// descriptors and workspace (the ring headers have been swapped by then, so the descriptors are rebuilt without them)
+fg_status_t update_all(const char* who, int phase, fg_cache_t* cache, int64_t iter, float p_grad, int32_t n_layers,
+                       const fg_update_layer_t* layers, void* ws_dev, size_t ws_bytes, void* stream) {
+    UpdBatch B;
+    fg_status_t rc = describe_update(who, phase, cache, iter, p_grad, n_layers, layers, ws_dev, ws_bytes, &B);
+    if (rc != FG_OK) return rc;
+    fg_clear_error();
+    if (n_layers == 0) return FG_OK;
+    rc = launch_update(B, (hipStream_t)stream, phase != 2, phase != 1);
+    if (rc != FG_OK) return rc;
+    update_queued(phase, cache, iter, n_layers, layers);
+    return FG_OK;
+}
+}  // namespace
+
+fg_status_t fg_update_describe(const char* who, const fg_update_call& c, UpdBatch* B, bool* rides) {
+    *rides = false;
+    const fg_status_t rc = describe_update(who, 0, c.cache, c.iter, c.p_grad, c.n_layers, c.layers, c.ws, c.ws_bytes, B);
+    if (rc != FG_OK) return rc;
+    place_workgroups(*B);
+    *rides = c.n_layers > 0 && one_group(*B, GRP_MAX);
     return FG_OK;
 }
 
-}  // namespace
+void fg_update_queued(const fg_update_call& c) { update_queued(0, c.cache, c.iter, c.n_layers, c.layers); }
 
 extern "C" fg_status_t fg_cache_update_all(fg_cache_t* cache, int64_t iter, float p_grad, int32_t n_layers,
                                            const fg_update_layer_t* layers, void* ws_dev, size_t ws_bytes, void* stream) {

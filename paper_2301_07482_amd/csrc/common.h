@@ -146,6 +146,7 @@ struct fg_row_copy_batch {
     fg_row_copy c[FG_MAX_COPIES];
 };
 fg_status_t fg_launch_row_copies(const fg_row_copy_batch& batch, hipStream_t stream);
+int fg_row_copy_blocks(const fg_row_copy_batch& batch);      // workgroups of 256 threads for each of them
 // the copy work of wavefront `wave` of `n_waves`: a wavefront moves a row in 16-byte pieces, two rows in flight
 __device__ __forceinline__ void fg_copy_rows_part(const fg_row_copy& C, int64_t wave, int64_t n_waves, int lane) {
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));

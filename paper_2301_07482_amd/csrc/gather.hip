@@ -135,13 +135,17 @@ void launch_gather_t(const void* table, int64_t table_rows, int64_t src_stride, 
 
 }  // namespace
 
-fg_status_t fg_launch_row_copies(const fg_row_copy_batch& batch, hipStream_t stream) {
+int fg_row_copy_blocks(const fg_row_copy_batch& batch) {
     int64_t most = 0;
     for (int i = 0; i < batch.n; ++i)
         if (batch.c[i].max_count > most) most = batch.c[i].max_count;
-    if (batch.n <= 0 || most <= 0) return FG_OK;
-    int64_t gx = fg_ceil_div(most, 2 * (COPY_THREADS / 64));
-    if (gx > 2048) gx = 2048;
+    const int64_t gx = fg_ceil_div(most, 2 * (COPY_THREADS / 64));
+    return (int)(gx < 2048 ? gx : 2048);
+}
+
+fg_status_t fg_launch_row_copies(const fg_row_copy_batch& batch, hipStream_t stream) {
+    const int gx = fg_row_copy_blocks(batch);
+    if (batch.n <= 0 || gx <= 0) return FG_OK;
     hipLaunchKernelGGL(copy_rows_batch_kernel, dim3((unsigned)gx, (unsigned)batch.n), dim3(COPY_THREADS), 0, stream, batch);
     FG_LAUNCH_CHECK("copy_rows_batch_kernel");
     return FG_OK;

@@ -5,7 +5,7 @@
 // an iteration of the smallest workload (10 k nodes, 256 seeds x 10 x 5) whose launches kept the GPU busy for 50. Queued from here the
 // host needed 40: step 57 -> 50 us, training iteration 90 -> 78 with the kernels of that time, which was what the GPU needed; with
 // shorter ones it is 42 and 71.
-#include "common.h"
+#include "update_group.h"
 
 namespace {
 
@@ -87,7 +87,8 @@ struct Iter {
     void* ws_update() const { return (char*)P.ws_update + it % 2 * P.ws_update_stride; }
 
     // `behind`: layers whose weight gradients may still be under way on the other stream; theirs is the front of the workspace
-    fg_status_t weight_grads(const fg_path_batch_t& b, int first, int last, void* stream, int behind = 0) const {
+    // update: described, to ride along
+    fg_status_t weight_grads(const fg_path_batch_t& b, int first, int last, void* stream, int behind = 0, const UpdBatch* update = nullptr) const {
         fg_weight_grad_layer_t y[FG_PATH_MAX_LAYERS] = {}, up[FG_PATH_MAX_LAYERS] = {};
         for (int l = first; l <= last; ++l) {
             fg_weight_grad_layer_t& w = y[l - first];
@@ -121,10 +122,11 @@ struct Iter {
         }
         size_t front = behind ? fg_backward_weights_all_workspace_bytes((fg_dtype_t)P.compute_dtype, behind, up) : 0;
         if (front > P.ws_weights_bytes) front = P.ws_weights_bytes;      // (refused by the call)
-        return fg_backward_weights_all((fg_dtype_t)P.compute_dtype, last - first + 1, y, (char*)P.ws_weights + front, P.ws_weights_bytes - front, stream);
+        return fg_backward_weights_with((fg_dtype_t)P.compute_dtype, last - first + 1, y, (char*)P.ws_weights + front, P.ws_weights_bytes - front, update, stream);
     }
 
-    // Whether the weight gradients take longer than the cache update beside them: 17 us and 18.5 per 10^9 products (in bf16 six times as
+    // Whether the weight gradients take longer than the cache update beside them, where it is launches of its own (the figures are from when
+    // it always was): 17 us and 18.5 per 10^9 products (in bf16 six times as
     // many) against 25 us and 1.2 per MB of admitted rows, from traces. Iterations with the update / with the weight gradients on the
     // second stream, us: 67 k x 256 x 256 377 / 385, GCN 313 / 317, mixed 16 k x 1536 x 1024 289 / 295, training loop 403 / 414, 30 k x 192 x 144
     // 189 / 198; where the rule says no 31 k x 104 x 88 181 / 175, 34 k x 116 x 64 172 / 166, GCN 37 k x 96 x 256 admitting 0.9 of its rows 194 / 191.
@@ -314,10 +316,27 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
         }
     }
     FG_TRY(I.forward(*batch, once, fetch, n_fetch));
-    // A training iteration ends with its weight gradients and the cache update beside each other. The longer of the two stays on this stream,
-    // where it does not wait for an event to be seen by the other one.
+    // A training iteration ends with its weight gradients and the cache update beside each other: in the same two launches where a group of
+    // workgroups decides the update, else on two streams, the longer of the two on this one, where it does not wait for an event to be
+    // seen by the other.
     const bool train = P.backward && P.weight_grads, two_streams = train && call->overlap, ahead = two_streams && call->ahead && L > 1;
     if (P.backward) FG_TRY(I.backward(*batch, ahead));
+    if (train && do_update && !call->selected) {
+        I.update_specs(*batch, true, call->specs);
+        const fg_update_call u = {call->cache, call->iter, call->p_grad, L - 1, call->specs, I.ws_update(), P.ws_update_bytes};
+        UpdBatch U;
+        bool rides;
+        FG_TRY(fg_update_describe("fg_cache_update_all", u, &U, &rides));
+        if (rides) {
+            FG_TRY(I.weight_grads(*batch, 1, ahead ? 1 : L, main, ahead ? L - 1 : 0, &U));
+            fg_update_queued(u);
+            if (ahead) {
+                FG_HIP(hipEventRecord((hipEvent_t)P.ev_weights, side));
+                FG_HIP(hipStreamWaitEvent(main, (hipEvent_t)P.ev_weights, 0));
+            }
+            return FG_OK;
+        }
+    }
     const bool update_beside = two_streams && do_update && I.weights_last(*batch), weights_beside = two_streams && !update_beside;
     if (two_streams) FG_TRY(I.side_follows());
     if (train) FG_TRY(I.weight_grads(*batch, 1, ahead ? 1 : L, weights_beside ? side : main, ahead ? L - 1 : 0));

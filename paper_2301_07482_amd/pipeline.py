@@ -898,9 +898,10 @@ class HotPath:
     def runs_in_one_call(self):
         """Whether an iteration without a timer is queued by one call (fg_path_run): every configuration but those kept for
         comparison (a call per layer), the access-aware admission and raw features in the cache's buffer. The results of the two ways are
-        the same; their schedules differ where a training iteration has a second stream: the one call puts the longer of weight gradients and
-        update on the current one, the single calls always the update, and with a timer everything, since a step that is
-        bracketed by events of one stream cannot run beside another."""
+        the same; their schedules differ at the end of a training iteration: the one call runs the update inside the weight gradients' two launches
+        (of more than 64 chunks of 4096 positions: beside them on the second stream, the longer of the two on the current one), the single
+        calls on the current stream with the weight gradients on the second, and with a timer one behind the other, since a
+        step that is bracketed by events of one stream cannot run beside another."""
         return (self.one_launch_top_down and self.update_all and self.fetch_all and not self.admit_budget and not self.feature_side
                 and self.L <= B.FG_PATH_MAX_LAYERS and (self.side is not None or not self.overlap_update))
 

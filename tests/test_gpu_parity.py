@@ -2385,8 +2385,15 @@ def test_iterations_queued_back_to_back_match_one_at_a_time(env):
     ("host", dict(fused_input=True)),
     ("mixed", dict(fused_input=True)),
     ("mixed", dict(fused_input=True, backward=True, weight_grads=True)),
-    ("mixed, few admitted", dict(fused_input=True, backward=True, weight_grads=True)),      # these two: the update beside the weight gradients
+    ("mixed, few admitted", dict(fused_input=True, backward=True, weight_grads=True)),
     ("wide", dict(fused_input=True, backward=True, weight_grads=True)),
+    # the update inside the weight gradients' launches: two of its workgroups for layer 1, nothing / everything admitted, more of them than
+    # compute units are left free (the weight gradients are split otherwise then), and more than may wait for each other (own launches)
+    ("two chunks", dict(fused_input=True, backward=True, weight_grads=True, overlap_update=False)),
+    ("two chunks", dict(fused_input=True, backward=True, weight_grads=True, p_grad=0.0)),
+    ("two chunks", dict(fused_input=True, backward=True, weight_grads=True, p_grad=1.0)),
+    ("many chunks", dict(fused_input=True, backward=True, weight_grads=True, overlap_update=False)),
+    ("too many chunks", dict(fused_input=True, backward=True, weight_grads=True)),
 ])
 @pytest.mark.parametrize("col_ids", [True, False])
 def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, kwargs, col_ids):
@@ -2400,6 +2407,11 @@ def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, k
         w = dataclasses.replace(w, feat_location="host", feat_dim=256, batch=512)
     if workload == "wide":       # weight gradients that take longer than the update (3 * 10^9 products, 2 MB of rows)
         w = dataclasses.replace(w, num_nodes=40_000, num_edges=1_200_000, feat_dim=256, hidden=512, fanouts=(4, 22), batch=512, p_grad=0.1)
+    if workload == "two chunks":
+        w = dataclasses.replace(w, num_nodes=40_000, num_edges=800_000, fanouts=(3, 2, 8), batch=301, cache_capacity=5_000)
+    if workload.endswith("many chunks"):
+        w = dataclasses.replace(w, num_nodes=700_000, num_edges=16_000_000, feat_dim=16, hidden=16, fanouts=(2, 15, 20) if workload == "many chunks" else (1, 20, 20),
+                                batch=1024 if workload == "many chunks" else 2048, cache_capacity=60_000)
     if workload == "mixed, few admitted":
         workload, w = "mixed", dataclasses.replace(w, p_grad=0.02)
     if workload == "mixed":      # wide enough for the upper layers' weight gradients to go ahead (8 Mi values in layer 1)
@@ -2418,7 +2430,7 @@ def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, k
             if backward:
                 return DeviceBatch(mb, None, labels=wl.node_labels(w, mb.ids[L]), col_ids=col_ids)
             return DeviceBatch(mb, {l: wl.grad_norms(w, it, l, mb.ids[l]) for l in range(1, L)}, col_ids=col_ids)
-        state = []
+        state, sums = [], []
         for hp in paths:
             batches = [batch(it) for it in range(K + 1)]
             if workload == "host":
@@ -2429,11 +2441,19 @@ def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, k
             for it in range(K):
                 hp.run(batches[it], it, update=it != 4, next_bt=batches[K if it == 2 else it + 1] if it + 1 < K else None)
                 n = mbs[it].ids
+                if workload == "two chunks":
+                    assert 4096 < len(n[1]) < 8192
+                if workload.endswith("many chunks"):
+                    groups = sum(-(-len(n[l]) // 4096) for l in range(1, L))
+                    assert 32 < groups <= 64 if workload == "many chunks" else groups > 64
                 rec += [hp.H[l][:len(n[l])].clone() for l in range(1, L + 1)]
                 if backward:
                     rec += [hp.dH[l][:len(n[l])].clone() for l in range(1, L + 1)] + [x[:len(n[l])].clone() for l, x in enumerate(hp.gnorm) if l]
                 if hp.weight_grads:
-                    rec += [x.clone() for x in hp.dW[1:] + hp.db[1:]]
+                    if workload == "many chunks":
+                        sums.append([x.clone() for x in hp.dW[1:] + hp.db[1:]])
+                    else:
+                        rec += [x.clone() for x in hp.dW[1:] + hp.db[1:]]
                 rec += [hp.live[l][:len(n[l])].clone() for l in range(1, L)] + [hp.counts.clone(), hp.stats.clone()]
             torch.cuda.synchronize()
             rec += [hp.counts_log, hp.stats_log, hp.input_log]
@@ -2446,6 +2466,9 @@ def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, k
         assert len(state[0]) == len(state[1])
         for i, (a, b) in enumerate(zip(*state)):
             assert torch.equal(a, b), f"record {i} of {len(state[0])}"
+        for it in range(len(sums) // 2):      # sums of the same products in another order: some 2^-24 of the result for each of a dozen additions in fp32
+            for a, b in zip(sums[it], sums[it + len(sums) // 2]):
+                assert (a - b).norm() <= 1e-6 * b.norm() and b.norm() > 0
     finally:
         for hp in paths:
             hp.close()
