@@ -2408,7 +2408,7 @@ def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, k
     if workload == "wide":       # weight gradients that take longer than the update (3 * 10^9 products, 2 MB of rows)
         w = dataclasses.replace(w, num_nodes=40_000, num_edges=1_200_000, feat_dim=256, hidden=512, fanouts=(4, 22), batch=512, p_grad=0.1)
     if workload == "two chunks":
-        w = dataclasses.replace(w, num_nodes=40_000, num_edges=800_000, fanouts=(3, 2, 8), batch=301, cache_capacity=5_000)
+        w = dataclasses.replace(w, num_nodes=40_000, num_edges=800_000, feat_dim=52, hidden=88, fanouts=(3, 2, 8), batch=301, cache_capacity=5_000)
     if workload.endswith("many chunks"):
         w = dataclasses.replace(w, num_nodes=700_000, num_edges=16_000_000, feat_dim=16, hidden=16, fanouts=(2, 15, 20) if workload == "many chunks" else (1, 20, 20),
                                 batch=1024 if workload == "many chunks" else 2048, cache_capacity=60_000)
