@@ -10,7 +10,7 @@
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 
-#include "common.h"
+#include "update_group.h"
 
 namespace {
 
@@ -121,7 +121,7 @@ __device__ __forceinline__ u32x4 load_piece(const char* p) {
 // [0, dim/2) to gcn_pos[r, :] (by position), columns [dim/2, dim) to agg[k, :] (list order).
 // COLIDS (with INDIRECT): col[] already holds table rows (node ids), so the position -> id step is skipped for the
 // neighbours; src_ids is then only used for the rows' own ids.
-template <int IN, int OUT, bool INDIRECT, bool FEAT, bool GCN = false, bool COLIDS = false>
+template <int IN, int OUT, bool INDIRECT, bool FEAT, bool GCN = false, bool COLIDS = false, int THREADS = AGG_THREADS>
 __device__ __forceinline__ void aggregate_mean_body(
     const int n_blocks, const int block,  // workgroups doing this work and this workgroup's number among them
     const int32_t* __restrict__ row_start, const int32_t* __restrict__ row_end, const int32_t* __restrict__ col,
@@ -135,7 +135,7 @@ __device__ __forceinline__ void aggregate_mean_body(
     int64_t n_rows = n_rows_dev ? *n_rows_dev : max_rows;
     if (n_rows > max_rows) n_rows = max_rows;
     const int lanes = 1 << lanes_log2;
-    const int gpb = AGG_THREADS >> lanes_log2;
+    const int gpb = THREADS >> lanes_log2;
     const int g_in_block = threadIdx.x >> lanes_log2;
     const int lane = threadIdx.x & (lanes - 1);
     int32_t* my_nb = nb_lds + g_in_block * AGG_MAX_STAGE;
@@ -290,6 +290,35 @@ __global__ __launch_bounds__(AGG_THREADS) void loader_fetch_kernel(
                                                           nullptr, 0);
 }
 
+// The same with the selection of the iteration's cache update (gradient norms given from outside: it depends on the top-down pass alone) as the
+// first workgroups, where the loader has few of its own. Behind the layers it was the longest launch of a small step; here its chain of reads,
+// scans and barriers runs beside the loader's, and the admitted rows are copied by the seed layer's launch.
+// Its workgroups have the 1024 threads of the update's own launch (with 256, and 16 positions in each thread's registers, 18 us against 10). Step of 1.5 k
+// positions 42.0 -> 33.5 us, 3.5 k (88 columns, rows copied by a launch of their own) 52.3 -> 46.3, 5.9 k 77.7 -> 69.8, mixed 3 k 56.9 -> 48.7.
+constexpr int RIDE_THREADS = 1024;
+template <int IN, int OUT>
+__global__ __launch_bounds__(RIDE_THREADS) void loader_fetch_update_kernel(
+    UpdBatch U, int copy_blocks, fg_row_copy_batch copies, const int32_t* __restrict__ row_start, const int32_t* __restrict__ row_end,
+    const int32_t* __restrict__ col, int64_t nnz, int n_block_rows, const int32_t* __restrict__ rows,
+    const int64_t* __restrict__ n_rows_dev, int64_t max_rows, const char* __restrict__ h_src, int64_t n_src, int64_t src_stride,
+    int pieces, char* __restrict__ agg, int64_t agg_stride, int lanes_log2, const int32_t* __restrict__ src_ids, int n_ids,
+    char* __restrict__ self_out, int64_t self_stride, int n_self) {
+    const int beside = U.sel_first[U.n_layers], block = (int)blockIdx.x - beside;
+    if (block < 0) {
+        extern __shared__ __attribute__((aligned(16))) char group_lds[];
+        update_group<RIDE_THREADS, GRP_CHUNK / 4 / RIDE_THREADS, false>(U, (int)blockIdx.x, *(GrpShared<RIDE_THREADS / FG_WAVE>*)group_lds);
+        return;
+    }
+    if (block < copy_blocks) {
+        const int64_t wave = ((int64_t)block * RIDE_THREADS + threadIdx.x) >> 6;
+        for (int c = 0; c < copies.n; ++c) fg_copy_rows_part(copies.c[c], wave, ((int64_t)copy_blocks * RIDE_THREADS) >> 6, threadIdx.x & 63);
+        return;
+    }
+    aggregate_mean_body<IN, OUT, true, false, false, true, RIDE_THREADS>((int)gridDim.x - beside - copy_blocks, block - copy_blocks, row_start, row_end, col, nnz, n_block_rows,
+                                                          rows, n_rows_dev, max_rows, h_src, n_src, src_stride, pieces, agg, agg_stride, lanes_log2, src_ids,
+                                                          n_ids, self_out, self_stride, n_self, fg_feat_side{}, nullptr, 0);
+}
+
 }  // namespace
 
 // Lanes (as a power of two) that share one row of `pieces` 16-byte pieces.  A row wider than a
@@ -301,6 +330,19 @@ static int lanes_log2_for(int pieces) {
     while ((1 << lg) < pieces && lg < 6) ++lg;
     if (lg == 6 && (pieces + 31) / 32 * 32 < (pieces + 63) / 64 * 64) lg = 5;
     return lg;
+}
+
+// Workgroups that copy cached rows, sized by the bound on the hits (their number is known on the device only): a wavefront copies two rows at a time
+static int64_t fetch_blocks(int64_t most) {
+    const int64_t blocks = fg_ceil_div(most, 8 * (AGG_THREADS / 64));
+    return blocks < 256 ? blocks : 256;
+}
+
+// Two workgroups of loader_fetch_update_kernel are on a compute unit at once, by their threads: only where that many are enough
+bool fg_loader_takes_update(int64_t max_rows, int32_t dim, fg_dtype_t dtype, int64_t most_hits, int update_blocks) {
+    const int lg = lanes_log2_for(dim * fg_dtype_size(dtype) / 16);
+    return max_rows > 0 && most_hits > 0 &&
+           fg_ceil_div(max_rows, RIDE_THREADS >> lg) + fg_ceil_div(fetch_blocks(most_hits) * AGG_THREADS, RIDE_THREADS) + update_blocks <= 512;
 }
 
 static fg_status_t aggregate_common(const char* who, const int32_t* row_start_dev, const int32_t* row_end_dev,
@@ -453,7 +495,19 @@ extern "C" fg_status_t fg_gather_aggregate_ids(const int32_t* row_start_dev, con
                                                fg_dtype_t out_dtype, void* h_self_out, int64_t h_self_stride, int32_t n_self_rows,
                                                const fg_cache_t* cache, int32_t n_fetch_layers, const fg_fetch_layer_t* fetch_layers,
                                                void* stream) {
+    return fg_gather_aggregate_ids_with(row_start_dev, row_end_dev, col_ids_dev, nnz, n_block_rows, rows_dev, n_rows_dev, max_rows, row_ids_dev, table,
+                                        table_rows, src_stride, dim, in_dtype, agg, agg_stride, out_dtype, h_self_out, h_self_stride, n_self_rows, cache,
+                                        n_fetch_layers, fetch_layers, nullptr, nullptr, stream);
+}
+
+fg_status_t fg_gather_aggregate_ids_with(const int32_t* row_start_dev, const int32_t* row_end_dev, const int32_t* col_ids_dev, int64_t nnz,
+                                         int32_t n_block_rows, const int32_t* rows_dev, const int64_t* n_rows_dev, int64_t max_rows,
+                                         const int32_t* row_ids_dev, const void* table, int64_t table_rows, int64_t src_stride, int32_t dim,
+                                         fg_dtype_t in_dtype, void* agg, int64_t agg_stride, fg_dtype_t out_dtype, void* h_self_out, int64_t h_self_stride,
+                                         int32_t n_self_rows, const fg_cache_t* cache, int32_t n_fetch_layers, const fg_fetch_layer_t* fetch_layers,
+                                         const UpdBatch* update, bool* rode, void* stream) {
     const char* who = "fg_gather_aggregate_ids";
+    if (rode) *rode = false;
     if (max_rows > 0 && !row_ids_dev) FG_FAIL(FG_ERR_INVALID_ARG, "%s: row_ids_dev is NULL", who);
     if (h_self_out) {
         if (n_self_rows < 0 || h_self_stride < (int64_t)dim * fg_dtype_size(in_dtype))
@@ -492,11 +546,21 @@ extern "C" fg_status_t fg_gather_aggregate_ids(const int32_t* row_start_dev, con
     int64_t blocks = fg_ceil_div(max_rows, gpb);
     const int64_t cap = 256 * fg_tuning(FG_TUNE_AGG_WG_PER_CU);
     if (blocks > cap) blocks = cap;
-    // sized by the bound on the hits (their number is known on the device only): a wavefront copies two rows at a time
-    int64_t copy_blocks = fg_ceil_div(most, 8 * (AGG_THREADS / 64));
-    if (copy_blocks > 256) copy_blocks = 256;
+    const int64_t copy_blocks = fetch_blocks(most);
     const size_t lds = (size_t)gpb * AGG_MAX_STAGE * sizeof(int32_t);
     hipStream_t st = (hipStream_t)stream;
+    if (update && fg_loader_takes_update(max_rows, dim, in_dtype, most, update->sel_first[update->n_layers])) {
+        const int64_t wide = fg_ceil_div(max_rows, RIDE_THREADS >> lg), wide_copies = fg_ceil_div(copy_blocks * AGG_THREADS, RIDE_THREADS);
+        const size_t stage = (size_t)(RIDE_THREADS >> lg) * AGG_MAX_STAGE * sizeof(int32_t), group = sizeof(GrpShared<RIDE_THREADS / FG_WAVE>);
+        const auto kernel = f32 ? loader_fetch_update_kernel<FG_F32, FG_F32> : loader_fetch_update_kernel<FG_F16, FG_BF16>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(update->sel_first[update->n_layers] + wide + wide_copies)), dim3(RIDE_THREADS), group > stage ? group : stage,
+                           st, *update, (int)wide_copies, copies, row_start_dev, row_end_dev, col_ids_dev, nnz, n_block_rows, rows_dev, n_rows_dev, max_rows,
+                           (const char*)table, table_rows, src_stride, pieces, (char*)agg, agg_stride, lg, row_ids_dev, n_block_rows, (char*)h_self_out,
+                           h_self_stride, n_self_rows);
+        FG_LAUNCH_CHECK("loader_fetch_update_kernel");
+        *rode = true;
+        return FG_OK;
+    }
     if (f32)
         hipLaunchKernelGGL((loader_fetch_kernel<FG_F32, FG_F32>), dim3((unsigned)(blocks + copy_blocks)), dim3(AGG_THREADS), lds, st,
                            (int)copy_blocks, copies, row_start_dev, row_end_dev, col_ids_dev, nnz, n_block_rows, rows_dev, n_rows_dev, max_rows,

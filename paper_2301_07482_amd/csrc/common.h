@@ -172,6 +172,12 @@ __device__ __forceinline__ void fg_copy_rows_part(const fg_row_copy& C, int64_t 
         }
     }
 }
+// fg_aggregate_linear with row copies beside it, where it is the one launch (*copied)
+fg_status_t fg_aggregate_linear_with(const int32_t* row_start_dev, const int32_t* row_end_dev, const int32_t* col_dev, int64_t nnz, int32_t n_block_rows,
+                                     const int32_t* rows_dev, const int64_t* n_rows_dev, int64_t max_rows, const float* h_src, int32_t n_src,
+                                     int64_t src_stride, int32_t d_in, int32_t d_out, const float* W, const float* bias, int32_t relu, float* agg_ws_dev,
+                                     int64_t agg_stride, float* h_out, int32_t n_out, int64_t out_stride, const fg_row_copy_batch* copies, bool* copied,
+                                     void* stream);
 // checks the layers of a cache fetch (as fg_cache_fetch_all does) and describes them as row copies
 fg_status_t fg_build_fetch_batch(const char* who, const fg_cache_t* cache, int32_t n_layers, const fg_fetch_layer_t* layers,
                                  fg_row_copy_batch* out);

@@ -691,8 +691,8 @@ constexpr int SK_PART_BYTES = PL_WAVES * 16 * 64 * 8;  // partial sums: [wavefro
 // the exact result (2-norm; 400 to 1024 rows of 36 to 248 columns) instead of 5e-8 to 13e-8, since 32 k values at a time are folded into fp64.
 // Beyond 288 tasks the panel kernel stays the faster one for these widths too (up to 768 here: iterations of 64 to 174 us 2 to 6 % slower).
 template <bool FUSE, bool MASKED = false, bool RAGGED = false>
-__global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
-    const char* __restrict__ h_src, int n_src, int64_t src_stride, const char* __restrict__ agg, int64_t agg_stride,
+__device__ __forceinline__ void linear_f32_splitk(
+    const int block, const char* __restrict__ h_src, int n_src, int64_t src_stride, const char* __restrict__ agg, int64_t agg_stride,
     const int32_t* __restrict__ rows, const int64_t* __restrict__ n_rows_dev, int64_t max_rows, int d_in, int d_out,
     const float* __restrict__ W, const float* __restrict__ bias, int relu, char* __restrict__ h_out, int n_out,
     int64_t out_stride, int n_panels, const int32_t* __restrict__ row_start, const int32_t* __restrict__ row_end,
@@ -712,8 +712,8 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
         wrow = kk < d_in ? hf * d_in + kk : 0;
         return kk < d_in;
     };
-    const int xcd = blockIdx.x & 7;
-    const int j = blockIdx.x >> 3;
+    const int xcd = block & 7;
+    const int j = block >> 3;
     const int n0 = (j % n_panels) * PL_BN;
     const int64_t rb = (int64_t)(j / n_panels) * 8 + xcd;  // the panels of a row block run on one XCD
     if (rb * 32 >= max_rows) return;                       // uniform over the workgroup, before any barrier
@@ -920,6 +920,33 @@ __global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
         if (relu) o = o > 0.f ? o : 0.f;
         *(float*)(h_out + (int64_t)rr * out_stride + (int64_t)c * 4) = o;
     }
+}
+
+template <bool FUSE, bool MASKED = false, bool RAGGED = false>
+__global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_kernel(
+    const char* __restrict__ h_src, int n_src, int64_t src_stride, const char* __restrict__ agg, int64_t agg_stride,
+    const int32_t* __restrict__ rows, const int64_t* __restrict__ n_rows_dev, int64_t max_rows, int d_in, int d_out,
+    const float* __restrict__ W, const float* __restrict__ bias, int relu, char* __restrict__ h_out, int n_out,
+    int64_t out_stride, int n_panels, const int32_t* __restrict__ row_start, const int32_t* __restrict__ row_end,
+    const int32_t* __restrict__ col, int64_t nnz, int n_block_rows, const int32_t* __restrict__ src_ids) {
+    linear_f32_splitk<FUSE, MASKED, RAGGED>((int)blockIdx.x, h_src, n_src, src_stride, agg, agg_stride, rows, n_rows_dev, max_rows, d_in, d_out, W, bias, relu,
+                                            h_out, n_out, out_stride, n_panels, row_start, row_end, col, nnz, n_block_rows, src_ids);
+}
+
+// <true> with row copies beside it (of layers computed before): copy_blocks workgroups for each of C's, behind those of the layer
+__global__ __launch_bounds__(PL_THREADS, 2) void linear_f32_splitk_copies_kernel(
+    int layer_blocks, fg_row_copy_batch C, int copy_blocks, const char* __restrict__ h_src, int n_src, int64_t src_stride, const int32_t* __restrict__ rows,
+    const int64_t* __restrict__ n_rows_dev, int64_t max_rows, int d_in, int d_out, const float* __restrict__ W, const float* __restrict__ bias, int relu,
+    char* __restrict__ h_out, int n_out, int64_t out_stride, int n_panels, const int32_t* __restrict__ row_start, const int32_t* __restrict__ row_end,
+    const int32_t* __restrict__ col, int64_t nnz, int n_block_rows) {
+    const int at = (int)blockIdx.x - layer_blocks;
+    if (at >= 0) {
+        const int part = at % copy_blocks;
+        fg_copy_rows_part(C.c[at / copy_blocks], ((int64_t)part * PL_THREADS + threadIdx.x) >> 6, ((int64_t)copy_blocks * PL_THREADS) >> 6, threadIdx.x & 63);
+        return;
+    }
+    linear_f32_splitk<true, false, false>((int)blockIdx.x, h_src, n_src, src_stride, h_src, src_stride, rows, n_rows_dev, max_rows, d_in, d_out, W, bias, relu,
+                                          h_out, n_out, out_stride, n_panels, row_start, row_end, col, nnz, n_block_rows, nullptr);
 }
 
 }  // namespace
@@ -1130,7 +1157,17 @@ extern "C" fg_status_t fg_aggregate_linear(const int32_t* row_start_dev, const i
                                            int64_t max_rows, const float* h_src, int32_t n_src, int64_t src_stride, int32_t d_in,
                                            int32_t d_out, const float* W, const float* bias, int32_t relu, float* agg_ws_dev,
                                            int64_t agg_stride, float* h_out, int32_t n_out, int64_t out_stride, void* stream) {
+    return fg_aggregate_linear_with(row_start_dev, row_end_dev, col_dev, nnz, n_block_rows, rows_dev, n_rows_dev, max_rows, h_src, n_src, src_stride, d_in,
+                                    d_out, W, bias, relu, agg_ws_dev, agg_stride, h_out, n_out, out_stride, nullptr, nullptr, stream);
+}
+
+fg_status_t fg_aggregate_linear_with(const int32_t* row_start_dev, const int32_t* row_end_dev, const int32_t* col_dev, int64_t nnz, int32_t n_block_rows,
+                                     const int32_t* rows_dev, const int64_t* n_rows_dev, int64_t max_rows, const float* h_src, int32_t n_src,
+                                     int64_t src_stride, int32_t d_in, int32_t d_out, const float* W, const float* bias, int32_t relu, float* agg_ws_dev,
+                                     int64_t agg_stride, float* h_out, int32_t n_out, int64_t out_stride, const fg_row_copy_batch* copies, bool* copied,
+                                     void* stream) {
     const char* who = "fg_aggregate_linear";
+    if (copied) *copied = false;
     if (max_rows < 0 || n_block_rows < 0 || n_src < 0 || n_out < 0 || nnz < 0 || d_in <= 0 || d_out <= 0)
         FG_FAIL(FG_ERR_INVALID_ARG, "%s: bad size", who);
     if (max_rows > 0 && (!row_start_dev || !row_end_dev || !h_src || !W || !h_out || (nnz > 0 && !col_dev)))
@@ -1148,6 +1185,15 @@ extern "C" fg_status_t fg_aggregate_linear(const int32_t* row_start_dev, const i
         const int n_panels = (int)fg_ceil_div(d_out, PL_BN);
         const size_t lds = panel_bytes > (size_t)SK_PART_BYTES ? panel_bytes : (size_t)SK_PART_BYTES;
         const unsigned grid = (unsigned)(fg_ceil_div(fg_ceil_div(max_rows, 32), 8) * 8 * n_panels);
+        const int copy_blocks = copies ? (int)fg_ceil_div(fg_row_copy_blocks(*copies), 2) : 0;      // (twice as many threads as there)
+        if (copy_blocks > 0) {
+            hipLaunchKernelGGL(linear_f32_splitk_copies_kernel, dim3(grid + (unsigned)(copies->n * copy_blocks)), dim3(PL_THREADS), lds, (hipStream_t)stream,
+                               (int)grid, *copies, copy_blocks, (const char*)h_src, n_src, src_stride, rows_dev, n_rows_dev, max_rows, d_in, d_out, W, bias, relu,
+                               (char*)h_out, n_out, out_stride, n_panels, row_start_dev, row_end_dev, col_dev, nnz, n_block_rows);
+            FG_LAUNCH_CHECK("linear_f32_splitk_copies_kernel");
+            *copied = true;
+            return FG_OK;
+        }
         hipLaunchKernelGGL(linear_f32_splitk_kernel<true>, dim3(grid), dim3(PL_THREADS), lds, (hipStream_t)stream, (const char*)h_src,
                            n_src, src_stride, (const char*)h_src, src_stride, rows_dev, n_rows_dev, max_rows, d_in, d_out, W, bias, relu,
                            (char*)h_out, n_out, out_stride, n_panels, row_start_dev, row_end_dev, col_dev, nnz, n_block_rows, nullptr);

@@ -147,7 +147,26 @@ struct Iter {
                P.compute_dtype == FG_F32 && fg_one_launch_load(b.layer[1].nnz, b.layer[1].n, P.dims[0], P.dims[1]);
     }
 
-    fg_status_t forward(const fg_path_batch_t& b, bool once, const fg_fetch_layer_t* fetch, int n_fetch) const {
+    // Whether the selection of a step's update goes with the loader's launch. It does not with the loader that multiplies too, whose workgroups fill the
+    // chip. With a second stream, up to four chunks of positions: the stream's two waits for events and the row copy between two steps cost
+    // more than a top-down pass in line. Step with the update on the second stream / with the loader, us: 6 k positions 56.4 / 47.1, 10.6 k
+    // 64.1 / 59.8, 10.8 k 67.6 / 67.7, mixed 10 k 123.9 / 112.1; 21 k 91.8 / 100.1, 23 k 124.9 / 139.2, 37 k 76.9 / 99.8.
+    bool selects_with_loader(const fg_path_batch_t& b) const {
+        if (!cached() || gcn() || !P.fused_input || b.reads_rows_once || !b.col_ids1_dev || !C.fetch_with_loader || loads_and_multiplies(b, 1)) return false;
+        if (!(h_code(0) == FG_F32 && agg_code() == FG_F32) && !(h_code(0) == FG_F16 && agg_code() == FG_BF16)) return false;
+        int chunks = 0;
+        int64_t most = 0;
+        for (int l = 1; l < P.n_layers; ++l) {
+            const int64_t n = b.layer[l].n;
+            chunks += (int)fg_ceil_div(n > 0 ? n : 1, GRP_CHUNK);
+            most = n > most ? n : most;
+        }
+        return (!C.overlap || chunks <= 4) && fg_loader_takes_update(b.layer[1].n, P.dims[0], (fg_dtype_t)h_code(0), most, chunks);
+    }
+
+    // ride: an update whose selection may go with the loader; *rode: it has. *rows_due: its rows are still to be copied (not by the seed layer's launch)
+    fg_status_t forward(const fg_path_batch_t& b, bool once, const fg_fetch_layer_t* fetch, int n_fetch, const fg_update_call* ride, const UpdBatch* selection,
+                        bool* rode, bool* rows_due) const {
         const int L = P.n_layers;
         const bool fused = P.fused_input && !once;
         void* st = C.stream;
@@ -173,8 +192,14 @@ struct Iter {
                 continue;
             }
             if (one_launch(l, B.n)) {
-                FG_TRY(fg_aggregate_linear(B.start_dev, B.end_dev, B.col_dev, B.nnz, n, S.normal_pos[l], n_normal, n, (const float*)P.h[l - 1], n_in, in_b,
-                                           P.dims[l - 1], P.dims[l], (const float*)C.w[l], C.bias[l], relu, nullptr, agg_b, (float*)P.h[l], n, out_b, st));
+                fg_row_copy_batch copies;
+                bool copied = false;
+                const bool due = *rows_due && l == L;
+                if (due) fg_update_row_copies(*selection, &copies);
+                FG_TRY(fg_aggregate_linear_with(B.start_dev, B.end_dev, B.col_dev, B.nnz, n, S.normal_pos[l], n_normal, n, (const float*)P.h[l - 1], n_in, in_b,
+                                                P.dims[l - 1], P.dims[l], (const float*)C.w[l], C.bias[l], relu, nullptr, agg_b, (float*)P.h[l], n, out_b,
+                                                due ? &copies : nullptr, due ? &copied : nullptr, st));
+                if (copied) *rows_due = false;
                 continue;
             }
             const bool own_rows = l == 1 && fused && b.own_rows_from_table;
@@ -185,11 +210,13 @@ struct Iter {
                 continue;
             }
             if (fused && l == 1) {
-                if (b.col_ids1_dev)
-                    FG_TRY(fg_gather_aggregate_ids(B.start_dev, B.end_dev, b.col_ids1_dev, B.nnz, n, S.normal_pos[1], n_normal, n, B.ids_dev, C.feat, P.num_nodes, d0b,
-                                                   P.dims[0], (fg_dtype_t)in_code, P.agg[1], agg_b, (fg_dtype_t)agg_code(), own_rows ? nullptr : P.h[0], d0b, n_in,
-                                                   n_fetch ? C.cache : nullptr, n_fetch, n_fetch ? fetch : nullptr, st));
-                else
+                if (b.col_ids1_dev) {
+                    FG_TRY(fg_gather_aggregate_ids_with(B.start_dev, B.end_dev, b.col_ids1_dev, B.nnz, n, S.normal_pos[1], n_normal, n, B.ids_dev, C.feat, P.num_nodes, d0b,
+                                                        P.dims[0], (fg_dtype_t)in_code, P.agg[1], agg_b, (fg_dtype_t)agg_code(), own_rows ? nullptr : P.h[0], d0b, n_in,
+                                                        n_fetch ? C.cache : nullptr, n_fetch, n_fetch ? fetch : nullptr, selection, rode, st));
+                    *rows_due = *rode;
+                    if (*rode) fg_update_queued(*ride);
+                } else
                     FG_TRY(fg_gather_aggregate(B.start_dev, B.end_dev, B.col_dev, B.nnz, n, S.normal_pos[1], n_normal, n, b.layer[0].ids_dev, n_in, C.feat,
                                                P.num_nodes, d0b, P.dims[0], (fg_dtype_t)in_code, P.agg[1], agg_b, (fg_dtype_t)agg_code(), P.h[0], d0b, n_in, st));
             } else {
@@ -277,7 +304,16 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
     }
     call->begun = 1;
     if (!call->pruned_ahead) FG_TRY(I.top_down(*batch, main));
-    const bool beside = do_update && call->overlap && !P.backward;
+    // With norms from outside the update's selection does not depend on the layers
+    UpdBatch selection;
+    fg_update_call ride = {};
+    bool may_ride = false, rode = false, rows_due = false;
+    if (do_update && !P.backward && I.selects_with_loader(*batch)) {
+        I.update_specs(*batch, false, call->specs);
+        ride = {call->cache, call->iter, call->p_grad, L - 1, call->specs, I.ws_update(), P.ws_update_bytes};
+        FG_TRY(fg_update_describe("fg_cache_update_all", ride, &selection, &may_ride));
+    }
+    const bool beside = do_update && call->overlap && !P.backward && !may_ride;
     if (beside) {      // the update's selection and the next top-down pass on the second stream
         if (!call->pruned_ahead) {
             FG_HIP(hipEventRecord((hipEvent_t)P.ev_pruned, main));
@@ -315,7 +351,13 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
             n_fetch = 0;
         }
     }
-    FG_TRY(I.forward(*batch, once, fetch, n_fetch));
+    FG_TRY(I.forward(*batch, once, fetch, n_fetch, &ride, may_ride ? &selection : nullptr, &rode, &rows_due));
+    if (rows_due) {
+        fg_row_copy_batch copies;
+        fg_update_row_copies(selection, &copies);
+        FG_TRY(fg_launch_row_copies(copies, main));
+    }
+    if (rode) return FG_OK;
     // A training iteration ends with its weight gradients and the cache update beside each other: in the same two launches where a group of
     // workgroups decides the update, else on two streams, the longer of the two on this one, where it does not wait for an event to be
     // seen by the other.

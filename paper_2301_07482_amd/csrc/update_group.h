@@ -488,3 +488,12 @@ void fg_update_queued(const fg_update_call& call);      // both are queued: the 
 // fg_backward_weights_all with an update that rides along (NULL: none)
 fg_status_t fg_backward_weights_with(fg_dtype_t compute_dtype, int32_t n_layers, const fg_weight_grad_layer_t* layers, void* ws_dev, size_t ws_bytes,
                                      const UpdBatch* update, void* stream);
+// fg_gather_aggregate_ids with an update's selection that rides along, if the launch is one for it (*rode; the row copies are then still due)
+fg_status_t fg_gather_aggregate_ids_with(const int32_t* row_start_dev, const int32_t* row_end_dev, const int32_t* col_ids_dev, int64_t nnz,
+                                         int32_t n_block_rows, const int32_t* rows_dev, const int64_t* n_rows_dev, int64_t max_rows,
+                                         const int32_t* row_ids_dev, const void* table, int64_t table_rows, int64_t src_stride, int32_t dim,
+                                         fg_dtype_t in_dtype, void* agg, int64_t agg_stride, fg_dtype_t out_dtype, void* h_self_out, int64_t h_self_stride,
+                                         int32_t n_self_rows, const fg_cache_t* cache, int32_t n_fetch_layers, const fg_fetch_layer_t* fetch_layers,
+                                         const UpdBatch* update, bool* rode, void* stream);
+// whether that launch is one for a loader of `max_rows` rows with at most most_hits cached rows of a layer to fetch
+bool fg_loader_takes_update(int64_t max_rows, int32_t dim, fg_dtype_t dtype, int64_t most_hits, int update_blocks);

@@ -2394,6 +2394,15 @@ def test_iterations_queued_back_to_back_match_one_at_a_time(env):
     ("two chunks", dict(fused_input=True, backward=True, weight_grads=True, p_grad=1.0)),
     ("many chunks", dict(fused_input=True, backward=True, weight_grads=True, overlap_update=False)),
     ("too many chunks", dict(fused_input=True, backward=True, weight_grads=True)),
+    # a step's update inside the loader's launch and the seed layer's: two of its workgroups for layer 1, nothing / everything admitted; more
+    # workgroups of the loader than are given its LDS
+    ("two chunks of a step", dict(fused_input=True, overlap_update=False, fuse_small_layers=True)),
+    ("two chunks of a step", dict(fused_input=True, overlap_update=False, fuse_small_layers=True, p_grad=0.0)),
+    ("two chunks of a step", dict(fused_input=True, overlap_update=False, fuse_small_layers=True, p_grad=1.0)),
+    ("two chunks of a step", dict(fused_input=True, overlap_update=False)),
+    ("two chunks of a step", dict(fused_input=True, fuse_small_layers=True)),
+    ("two chunks of a mixed step", dict(fused_input=True, overlap_update=False)),
+    ("many chunks of a step", dict(fused_input=True, overlap_update=False, fuse_small_layers=True)),
 ])
 @pytest.mark.parametrize("col_ids", [True, False])
 def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, kwargs, col_ids):
@@ -2407,6 +2416,13 @@ def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, k
         w = dataclasses.replace(w, feat_location="host", feat_dim=256, batch=512)
     if workload == "wide":       # weight gradients that take longer than the update (3 * 10^9 products, 2 MB of rows)
         w = dataclasses.replace(w, num_nodes=40_000, num_edges=1_200_000, feat_dim=256, hidden=512, fanouts=(4, 22), batch=512, p_grad=0.1)
+    if workload.endswith(" step"):
+        w = dataclasses.replace(w, num_nodes=40_000, num_edges=800_000, feat_dim=52, hidden=64, fanouts=(3, 2, 8), batch=301,
+                                cache_capacity=5_000)
+    if workload == "many chunks of a step":
+        w = dataclasses.replace(w, num_nodes=90_000, batch=4501)
+    if workload.endswith("mixed step"):
+        w = dataclasses.replace(w, feat_dtype="f16", feat_dim=72, compute_dtype="bf16")
     if workload == "two chunks":
         w = dataclasses.replace(w, num_nodes=40_000, num_edges=800_000, feat_dim=52, hidden=88, fanouts=(3, 2, 8), batch=301, cache_capacity=5_000)
     if workload.endswith("many chunks"):
@@ -2441,8 +2457,10 @@ def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, k
             for it in range(K):
                 hp.run(batches[it], it, update=it != 4, next_bt=batches[K if it == 2 else it + 1] if it + 1 < K else None)
                 n = mbs[it].ids
-                if workload == "two chunks":
+                if workload[:10] == "two chunks":
                     assert 4096 < len(n[1]) < 8192
+                if workload.endswith(" step"):      # (64 rows of layer 1 to a workgroup of the loader)
+                    assert (-(-len(n[1]) // 64) > 512) == (workload[:4] == "many")
                 if workload.endswith("many chunks"):
                     groups = sum(-(-len(n[l]) // 4096) for l in range(1, L))
                     assert 32 < groups <= 64 if workload == "many chunks" else groups > 64
