@@ -141,18 +141,19 @@ struct Iter {
     }
 
     // Whether the loader and the dense update of layer 1 are one call: where nobody reads the means and the nodes' own rows later. (A training
-    // iteration does; with both written from the one launch it took what the two take, 122 us against 121.)
+    // iteration does; with both written from the one launch it took what the two take, 122 us against 121.) Its workgroups fill the chip, so that
+    // work on a second stream waits for it, and the layers above have to be long enough to hide that: from 24 Ki positions on. Steps of positions x
+    // columns, two launches / one, us: 20.5 k x 72 77 / 84.5, 24.6 k x 96 83 / 81, x 256 103 / 102, 31 k x 256 119 / 109, 45 k x 96 125 / 117, 54 k x 176 158 / 145.
     bool loads_and_multiplies(const fg_path_batch_t& b, int l) const {
-        return l == 1 && P.fused_input && !b.reads_rows_once && b.own_rows_from_table && b.col_ids1_dev && h_code(0) == FG_F32 && h_code(1) == FG_F32 &&
+        return l == 1 && (!C.overlap || b.layer[1].n >= 24576) && P.fused_input && !b.reads_rows_once && b.own_rows_from_table && b.col_ids1_dev && h_code(0) == FG_F32 && h_code(1) == FG_F32 &&
                P.compute_dtype == FG_F32 && fg_one_launch_load(b.layer[1].nnz, b.layer[1].n, P.dims[0], P.dims[1]);
     }
 
-    // Whether the selection of a step's update goes with the loader's launch. It does not with the loader that multiplies too, whose workgroups fill the
-    // chip. With a second stream, up to four chunks of positions: the stream's two waits for events and the row copy between two steps cost
-    // more than a top-down pass in line. Step with the update on the second stream / with the loader, us: 6 k positions 56.4 / 47.1, 10.6 k
-    // 64.1 / 59.8, 10.8 k 67.6 / 67.7, mixed 10 k 123.9 / 112.1; 21 k 91.8 / 100.1, 23 k 124.9 / 139.2, 37 k 76.9 / 99.8.
+    // Whether the selection of a step's update goes with the loader's launch: in a step on one stream. (Beside the layers on a second stream, with the next
+    // top-down pass behind it, it is hidden: 11 to 14 k positions 63 to 71 us there, 67 to 88 with the loader.) It does not with the loader that
+    // multiplies too, whose workgroups fill the chip.
     bool selects_with_loader(const fg_path_batch_t& b) const {
-        if (!cached() || gcn() || !P.fused_input || b.reads_rows_once || !b.col_ids1_dev || !C.fetch_with_loader || loads_and_multiplies(b, 1)) return false;
+        if (C.overlap || !cached() || gcn() || !P.fused_input || b.reads_rows_once || !b.col_ids1_dev || !C.fetch_with_loader || loads_and_multiplies(b, 1)) return false;
         if (!(h_code(0) == FG_F32 && agg_code() == FG_F32) && !(h_code(0) == FG_F16 && agg_code() == FG_BF16)) return false;
         int chunks = 0;
         int64_t most = 0;
@@ -161,7 +162,7 @@ struct Iter {
             chunks += (int)fg_ceil_div(n > 0 ? n : 1, GRP_CHUNK);
             most = n > most ? n : most;
         }
-        return (!C.overlap || chunks <= 4) && fg_loader_takes_update(b.layer[1].n, P.dims[0], (fg_dtype_t)h_code(0), most, chunks);
+        return fg_loader_takes_update(b.layer[1].n, P.dims[0], (fg_dtype_t)h_code(0), most, chunks);
     }
 
     // ride: an update whose selection may go with the loader; *rode: it has. *rows_due: its rows are still to be copied (not by the seed layer's launch)

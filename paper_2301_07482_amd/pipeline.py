@@ -656,7 +656,7 @@ class HotPath:
         """One iteration on torch's current stream. `timer(name, stream)` (optional) is called before each C-ABI call
         and with name None after the last call of a stream (stream None = the current stream).
         next_bt: the mini-batch of iteration it + 1, if the caller has it: where the update's selection runs on the second
-        stream (see below; a step of few positions has it in the loader's launch instead), the top-down pass of that mini-batch follows it there, beside this iteration's layers, and
+        stream (see below), the top-down pass of that mini-batch follows it there, beside this iteration's layers, and
         the next call (which must be for that mini-batch and iteration) finds it done.
         hold_second_stream: what this call puts on the second stream starts only when layer 1 is done, so that the loader and
         the layer-1 dense update have the chip to themselves (for a caller that times these two launches).
@@ -898,8 +898,8 @@ class HotPath:
     def runs_in_one_call(self):
         """Whether an iteration without a timer is queued by one call (fg_path_run): every configuration but those kept for
         comparison (a call per layer), the access-aware admission and raw features in the cache's buffer. The results of the two ways are
-        the same; their schedules differ where the one call runs a step's selection inside the loader's launch and copies its rows in the seed
-        layer's, and at the end of a training iteration: the one call runs the update inside the weight gradients' two launches
+        the same; their schedules differ where the one call runs the selection of a step without a second stream inside the loader's launch and
+        copies its rows in the seed layer's, and at the end of a training iteration: the one call runs the update inside the weight gradients' two launches
         (of more than 64 chunks of 4096 positions: beside them on the second stream, the longer of the two on the current one), the single
         calls on the current stream with the weight gradients on the second, and with a timer one behind the other, since a
         step that is bracketed by events of one stream cannot run beside another."""
@@ -926,8 +926,9 @@ class HotPath:
                 and getattr(bt, "col_ids1", None) is not None and not self.one_launch(1, bt.n[1]))
 
     def loads_and_multiplies(self, bt):
-        """Whether the loader and the dense update of layer 1 of this mini-batch are one call and one launch of it."""
-        return bool(self.own_rows_from_table(bt) and self.h_code[1] == B.FG_F32
+        """Whether the loader and the dense update of layer 1 of this mini-batch are one call and one launch of it (with a second stream, whose work
+        waits for a launch that fills the chip, from 24 Ki positions on)."""
+        return bool(self.own_rows_from_table(bt) and (not self.overlap_update or bt.n[1] >= 24576) and self.h_code[1] == B.FG_F32
                     and B.one_launch_load(bt.nnz[1], bt.n[1], self.dims[0], self.dims[1]))
 
     def reads_rows_once(self, bt):
