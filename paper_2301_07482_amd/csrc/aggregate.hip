@@ -338,11 +338,11 @@ static int64_t fetch_blocks(int64_t most) {
     return blocks < 256 ? blocks : 256;
 }
 
-// Two workgroups of loader_fetch_update_kernel are on a compute unit at once, by their threads: only where that many are enough
+// (A loader of a million such workgroups would be a grid of more than 2^31 threads.)
 bool fg_loader_takes_update(int64_t max_rows, int32_t dim, fg_dtype_t dtype, int64_t most_hits, int update_blocks) {
     const int lg = lanes_log2_for(dim * fg_dtype_size(dtype) / 16);
     return max_rows > 0 && most_hits > 0 &&
-           fg_ceil_div(max_rows, RIDE_THREADS >> lg) + fg_ceil_div(fetch_blocks(most_hits) * AGG_THREADS, RIDE_THREADS) + update_blocks <= 512;
+           fg_ceil_div(max_rows, RIDE_THREADS >> lg) + fg_ceil_div(fetch_blocks(most_hits) * AGG_THREADS, RIDE_THREADS) + update_blocks <= 1 << 20;
 }
 
 static fg_status_t aggregate_common(const char* who, const int32_t* row_start_dev, const int32_t* row_end_dev,

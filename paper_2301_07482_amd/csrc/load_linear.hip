@@ -12,7 +12,7 @@
 // 57 k x (100 + 100) x 256 108 / 127; 54 k x (64 + 64) x 128 55 / 59; 31 k x (52 + 52) x 88 33 / 37. The matrix instructions of 54 k rows take
 // 22 us, the rows 62 at the rate of a copy; what is above is the first block's chain of reads and W's split (5 us), the multiplication's waits for
 // LDS and the part of it that the other half's reads do not cover.
-#include "common.h"
+#include "update_group.h"
 
 namespace {
 
@@ -30,6 +30,7 @@ constexpr int LL_SEG = 33;                    // 16-byte units a half-wavefront'
 constexpr int LL_UNIT = 4;                    // loads of 1 KB that are waited for together
 constexpr int LL_RING = 3;                    // such units of a wavefront that are under way
 constexpr int LL_LIST = 16;                   // row blocks whose rows a workgroup lists ahead (two halves, one filled while the other is used)
+constexpr int LL_UPD_CHUNK = 8192;            // positions of a workgroup of an update that rides along
 constexpr int LL_GROUPS = 256;                // workgroups: one on each compute unit, by its LDS
 constexpr size_t ll_lds_bytes(int ks) {
     return (size_t)ks * 6 * LL_SEG * 16 + (size_t)LL_WAVES * LL_RING * LL_UNIT * 1024 + (size_t)LL_WAVES * 2 * 64 * 8 + (size_t)2 * LL_LIST * 32 * 4 +
@@ -83,14 +84,24 @@ struct LoadLinear {
     const float *W, *bias;
     char* h_out;
     int64_t out_stride;
-    int n_out, relu;
+    int n_out, relu, groups;           // groups: workgroups, a multiple of 8
     fg_row_copy_batch copies;          // cached rows that are fetched beside it
 };
 
+// U: the selection of the iteration's cache update (n_layers 0: none), as the first workgroups, a compute unit each, which the loader then has
+// fewer of (large step with 16 fewer 194.4 us, 193.7 with all); hence twice the positions of the update's own workgroups
+// (with 4096 of them large 182.4 us, medium 188.9). On a second stream the selection found no compute unit before this launch ended, and the next
+// step waited for it and the top-down pass behind it: large step 194.5 -> 179.3 us, with the paper's thresholds 178.4 -> 166.5, medium 182.7 -> 179.0.
 // KS: steps of 16 of the contraction; SLOTS: rows of the table a block's row is given (its own and SLOTS - 1 neighbours; what is beyond is read in a
 // loop of its own); LP: lanes a table row takes.
 template <int KS, int SLOTS, int LP>
-__global__ __launch_bounds__(LL_THREADS, 2) void load_linear_kernel(LoadLinear A) {
+__global__ __launch_bounds__(LL_THREADS, 2) void load_linear_kernel(LoadLinear A, UpdBatch U) {
+    const int beside = U.n_layers ? U.sel_first[U.n_layers] : 0, block = (int)blockIdx.x - beside;
+    if (block < 0) {
+        extern __shared__ __attribute__((aligned(16))) char group_lds[];
+        update_group<LL_THREADS, LL_UPD_CHUNK / 4 / LL_THREADS, false>(U, (int)blockIdx.x, *(GrpShared<LL_WAVES>*)group_lds);
+        return;
+    }
     constexpr int RPI = 64 / LP;                    // table rows of a load instruction
     constexpr int IPR = SLOTS / RPI;                // load instructions of a block's row
     constexpr int RPW = 32 / LL_WAVES;              // rows of a block a wavefront gathers
@@ -108,23 +119,24 @@ __global__ __launch_bounds__(LL_THREADS, 2) void load_linear_kernel(LoadLinear A
     // Workgroups 8 .. 15 of every 16 (one and the other half of each die's compute units) are the later half: they start half a block later and
     // come last when blocks are given out, so where these do not come out even it is they who have one less.
     const int K = 2 * A.d_in, pieces = A.d_in >> 2;
-    const bool later = (blockIdx.x & 8) != 0;
-    const int group = (int)(blockIdx.x >> 4 << 3 | (blockIdx.x & 7)) + (later ? LL_GROUPS / 2 : 0);
+    const bool later = (block & 8) != 0;
+    const int earlier = (A.groups + 8) / 16 * 8;      // workgroups of the earlier half: half of them, or eight more than of the other
+    const int group = (block >> 4 << 3 | (block & 7)) + (later ? earlier : 0);
     int64_t n_rows = A.n_rows_dev ? *A.n_rows_dev : A.max_rows;
     if (n_rows > A.max_rows) n_rows = A.max_rows;
     uint64_t spent = __builtin_readcyclecounter();
     if (later)
         for (int c = 0; c < A.copies.n; ++c)
-            fg_copy_rows_part(A.copies.c[c], (int64_t)(group - LL_GROUPS / 2) * LL_WAVES + wave, (int64_t)LL_GROUPS / 2 * LL_WAVES, lane);
+            fg_copy_rows_part(A.copies.c[c], (int64_t)(group - earlier) * LL_WAVES + wave, (int64_t)(A.groups - earlier) * LL_WAVES, lane);
     spent = __builtin_readcyclecounter() - spent;
     const int n_blocks = (int)((n_rows + 31) >> 5);
     if (group >= n_blocks) return;                    // uniform over the workgroup, before any barrier
-    const int n_tasks = (n_blocks - group + LL_GROUPS - 1) / LL_GROUPS;
+    const int n_tasks = (n_blocks - group + A.groups - 1) / A.groups;
 
     // Rows of task first + t / 32 (a task is one row block) and where their own features are: -1 past the end or out of range
     auto list_rows = [&](int first) {
         const int task = first + (t >> 5), at = (task % LL_LIST) * 32 + (t & 31);
-        const int64_t g = ((int64_t)group + (int64_t)task * LL_GROUPS) * 32 + (t & 31);
+        const int64_t g = ((int64_t)group + (int64_t)task * A.groups) * 32 + (t & 31);
         int32_t r = -1, s = -1;
         if (g < n_rows) {
             r = A.rows ? A.rows[g] : (int32_t)g;
@@ -347,7 +359,19 @@ extern "C" fg_status_t fg_gather_aggregate_linear_ids(const int32_t* row_start_d
                                                       int32_t d_in, int32_t d_out, const float* W, const float* bias, int32_t relu, float* agg_ws,
                                                       int64_t agg_stride, float* h_out, int32_t n_out, int64_t out_stride, const fg_cache_t* cache,
                                                       int32_t n_fetch_layers, const fg_fetch_layer_t* fetch_layers, void* stream) {
+    return fg_gather_aggregate_linear_ids_with(row_start_dev, row_end_dev, col_ids_dev, nnz, n_block_rows, rows_dev, n_rows_dev, max_rows, row_ids_dev, table,
+                                               table_rows, src_stride, d_in, d_out, W, bias, relu, agg_ws, agg_stride, h_out, n_out, out_stride, cache,
+                                               n_fetch_layers, fetch_layers, nullptr, nullptr, stream);
+}
+
+fg_status_t fg_gather_aggregate_linear_ids_with(const int32_t* row_start_dev, const int32_t* row_end_dev, const int32_t* col_ids_dev, int64_t nnz,
+                                                int32_t n_block_rows, const int32_t* rows_dev, const int64_t* n_rows_dev, int64_t max_rows,
+                                                const int32_t* row_ids_dev, const float* table, int64_t table_rows, int64_t src_stride, int32_t d_in,
+                                                int32_t d_out, const float* W, const float* bias, int32_t relu, float* agg_ws, int64_t agg_stride,
+                                                float* h_out, int32_t n_out, int64_t out_stride, const fg_cache_t* cache, int32_t n_fetch_layers,
+                                                const fg_fetch_layer_t* fetch_layers, const UpdBatch* update, bool* rode, void* stream) {
     const char* who = "fg_gather_aggregate_linear_ids";
+    if (rode) *rode = false;
     if (max_rows > 0 && !agg_ws) FG_FAIL(FG_ERR_INVALID_ARG, "%s: agg_ws is NULL", who);
     if (table_rows > 0x7FFFFFFFll) FG_FAIL(FG_ERR_SHAPE, "%s: table_rows = %lld exceeds 2^31 - 1", who, (long long)table_rows);
     // the other checks are those of the two calls it stands for
@@ -388,7 +412,15 @@ extern "C" fg_status_t fg_gather_aggregate_linear_ids(const int32_t* row_start_d
     A.n_out = n_out;
     A.relu = relu;
     hipStream_t st = (hipStream_t)stream;
-#define FG_LL(KS, SLOTS, LP) hipLaunchKernelGGL((load_linear_kernel<KS, SLOTS, LP>), dim3(LL_GROUPS), dim3(LL_THREADS), ll_lds_bytes(KS), st, A)
+    UpdBatch U;
+    U.n_layers = 0;
+    if (update && update->sel_first[update->n_layers] <= fg_load_linear_update_chunks) {
+        U = *update;
+        for (int i = 0; i < U.n_layers; ++i) U.sel_first[i + 1] = U.sel_first[i] + (int)fg_ceil_div(U.l[i].n > 0 ? U.l[i].n : 1, LL_UPD_CHUNK);
+    }
+    const int beside = U.n_layers ? U.sel_first[U.n_layers] : 0;
+    A.groups = (LL_GROUPS - beside) / 8 * 8;
+#define FG_LL(KS, SLOTS, LP) hipLaunchKernelGGL((load_linear_kernel<KS, SLOTS, LP>), dim3(beside + A.groups), dim3(LL_THREADS), ll_lds_bytes(KS), st, A, U)
     if (d_in <= 64)
         FG_LL(8, 16, 16);
     else if (nnz <= 7 * max_rows)
@@ -397,5 +429,6 @@ extern "C" fg_status_t fg_gather_aggregate_linear_ids(const int32_t* row_start_d
         FG_LL(16, 16, 32);
 #undef FG_LL
     FG_LAUNCH_CHECK("load_linear_kernel");
+    if (beside) *rode = true;
     return FG_OK;
 }

@@ -24,6 +24,8 @@ struct Iter {
     int64_t* stats;       // [layers + 1][4]
     int64_t* input_counts;
     int64_t it;
+    const fg_path_batch_t* next = nullptr;      // a mini-batch whose top-down pass may run on the second stream behind a selection that goes with the loader
+    int32_t* next_pruned = nullptr;
 
     Iter(const fg_path_t& p, const fg_path_call_t& c, int64_t iter)
         : P(p), C(c), S(p.lists[iter % 3]), counts(p.counts_log + iter % p.ring * (p.n_layers + 1) * 3), stats(p.stats_log + iter % p.ring * (p.n_layers + 1) * 4),
@@ -149,11 +151,9 @@ struct Iter {
                P.compute_dtype == FG_F32 && fg_one_launch_load(b.layer[1].nnz, b.layer[1].n, P.dims[0], P.dims[1]);
     }
 
-    // Whether the selection of a step's update goes with the loader's launch: in a step on one stream. (Beside the layers on a second stream, with the next
-    // top-down pass behind it, it is hidden: 11 to 14 k positions 63 to 71 us there, 67 to 88 with the loader.) It does not with the loader that
-    // multiplies too, whose workgroups fill the chip.
+    // Whether the selection of a step's update goes with the loader's launch.
     bool selects_with_loader(const fg_path_batch_t& b) const {
-        if (C.overlap || !cached() || gcn() || !P.fused_input || b.reads_rows_once || !b.col_ids1_dev || !C.fetch_with_loader || loads_and_multiplies(b, 1)) return false;
+        if (!cached() || gcn() || !P.fused_input || b.reads_rows_once || !b.col_ids1_dev || !C.fetch_with_loader) return false;
         if (!(h_code(0) == FG_F32 && agg_code() == FG_F32) && !(h_code(0) == FG_F16 && agg_code() == FG_BF16)) return false;
         int chunks = 0;
         int64_t most = 0;
@@ -162,7 +162,22 @@ struct Iter {
             chunks += (int)fg_ceil_div(n > 0 ? n : 1, GRP_CHUNK);
             most = n > most ? n : most;
         }
-        return fg_loader_takes_update(b.layer[1].n, P.dims[0], (fg_dtype_t)h_code(0), most, chunks);
+        if (loads_and_multiplies(b, 1)) return chunks <= fg_load_linear_update_chunks;
+        return !C.overlap && fg_loader_takes_update(b.layer[1].n, P.dims[0], (fg_dtype_t)h_code(0), most, chunks);
+    }
+
+    // The selection has gone with the loader: the index is final for this iteration, and with a second stream the next mini-batch is looked up and pruned
+    // there beside the layers above. (What that pass overwrites was last read two iterations ago on this stream.)
+    fg_status_t selected(const fg_update_call* ride, bool* rows_due) const {
+        fg_update_queued(*ride);
+        *rows_due = true;
+        if (!next) return FG_OK;
+        FG_HIP(hipEventRecord((hipEvent_t)P.ev_pruned, (hipStream_t)C.stream));
+        FG_HIP(hipStreamWaitEvent((hipStream_t)P.side, (hipEvent_t)P.ev_pruned, 0));
+        FG_TRY(Iter(P, C, it + 1).top_down(*next, P.side));
+        FG_HIP(hipEventRecord((hipEvent_t)P.ev_next_pruned, (hipStream_t)P.side));
+        *next_pruned = 1;
+        return FG_OK;
     }
 
     // ride: an update whose selection may go with the loader; *rode: it has. *rows_due: its rows are still to be copied (not by the seed layer's launch)
@@ -205,9 +220,11 @@ struct Iter {
             }
             const bool own_rows = l == 1 && fused && b.own_rows_from_table;
             if (loads_and_multiplies(b, l)) {
-                FG_TRY(fg_gather_aggregate_linear_ids(B.start_dev, B.end_dev, b.col_ids1_dev, B.nnz, n, S.normal_pos[1], n_normal, n, B.ids_dev, (const float*)C.feat,
-                                                      P.num_nodes, d0b, P.dims[0], P.dims[1], (const float*)C.w[1], C.bias[1], relu, (float*)P.agg[1], agg_b,
-                                                      (float*)P.h[1], n, out_b, n_fetch ? C.cache : nullptr, n_fetch, n_fetch ? fetch : nullptr, st));
+                FG_TRY(fg_gather_aggregate_linear_ids_with(B.start_dev, B.end_dev, b.col_ids1_dev, B.nnz, n, S.normal_pos[1], n_normal, n, B.ids_dev,
+                                                           (const float*)C.feat, P.num_nodes, d0b, P.dims[0], P.dims[1], (const float*)C.w[1], C.bias[1], relu,
+                                                           (float*)P.agg[1], agg_b, (float*)P.h[1], n, out_b, n_fetch ? C.cache : nullptr, n_fetch,
+                                                           n_fetch ? fetch : nullptr, selection, rode, st));
+                if (*rode) FG_TRY(selected(ride, rows_due));
                 continue;
             }
             if (fused && l == 1) {
@@ -215,8 +232,7 @@ struct Iter {
                     FG_TRY(fg_gather_aggregate_ids_with(B.start_dev, B.end_dev, b.col_ids1_dev, B.nnz, n, S.normal_pos[1], n_normal, n, B.ids_dev, C.feat, P.num_nodes, d0b,
                                                         P.dims[0], (fg_dtype_t)in_code, P.agg[1], agg_b, (fg_dtype_t)agg_code(), own_rows ? nullptr : P.h[0], d0b, n_in,
                                                         n_fetch ? C.cache : nullptr, n_fetch, n_fetch ? fetch : nullptr, selection, rode, st));
-                    *rows_due = *rode;
-                    if (*rode) fg_update_queued(*ride);
+                    if (*rode) FG_TRY(selected(ride, rows_due));
                 } else
                     FG_TRY(fg_gather_aggregate(B.start_dev, B.end_dev, B.col_dev, B.nnz, n, S.normal_pos[1], n_normal, n, b.layer[0].ids_dev, n_in, C.feat,
                                                P.num_nodes, d0b, P.dims[0], (fg_dtype_t)in_code, P.agg[1], agg_b, (fg_dtype_t)agg_code(), P.h[0], d0b, n_in, st));
@@ -289,7 +305,7 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
     if (call->iter < 0) FG_FAIL(FG_ERR_INVALID_ARG, "fg_path_run: iteration %lld is negative", (long long)call->iter);
     FG_TRY(check_batch(P, *batch));
     if (next) FG_TRY(check_batch(P, *next));
-    const Iter I(P, *call, call->iter);
+    Iter I(P, *call, call->iter);
     const int L = P.n_layers;
     const hipStream_t main = (hipStream_t)call->stream, side = (hipStream_t)P.side;
     const bool do_update = call->update && I.cached();
@@ -315,6 +331,8 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
         FG_TRY(fg_update_describe("fg_cache_update_all", ride, &selection, &may_ride));
     }
     const bool beside = do_update && call->overlap && !P.backward && !may_ride;
+    if (may_ride && call->overlap) I.next = next;
+    I.next_pruned = &call->next_pruned;
     if (beside) {      // the update's selection and the next top-down pass on the second stream
         if (!call->pruned_ahead) {
             FG_HIP(hipEventRecord((hipEvent_t)P.ev_pruned, main));

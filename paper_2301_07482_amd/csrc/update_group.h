@@ -216,11 +216,11 @@ __device__ __forceinline__ bool grp_meet(unsigned int* arrived, unsigned int n, 
 }
 
 // COPY (every layer has one workgroup): the admitted rows are copied here as well (a launch less) instead of by the row copy behind it.
-// QUADS: four positions each, of a thread; THREADS * QUADS is what GRP_CHUNK needs. block: which of the group's workgroups this is.
+// QUADS: four positions each, of a thread. block: which of the group's workgroups this is.
 template <int THREADS, int QUADS, bool COPY>
 __device__ __forceinline__ void update_group(const UpdBatch& B, const int block, GrpShared<THREADS / FG_WAVE>& S) {
     constexpr int EL = 4 * QUADS, BPT = SEL_BINS / THREADS, WAVES = THREADS / FG_WAVE;
-    static_assert(THREADS * EL == GRP_CHUNK, "a chunk's positions are in its threads' registers");
+    constexpr int CHUNK = THREADS * EL;      // positions of a workgroup: B.sel_first counts such chunks
     uint32_t* const hist = S.hist;
     int part;
     const int layer = layer_of_block(B.sel_first, B.n_layers, block, part);
@@ -228,8 +228,8 @@ __device__ __forceinline__ void update_group(const UpdBatch& B, const int block,
     const CacheRW& c = L.c;
     const unsigned int parts = (unsigned int)(B.sel_first[layer + 1] - B.sel_first[layer]);
     const int t = threadIdx.x, lane = fg_lane(), wave = fg_wave();
-    const int n_all = upd_count(L), base = part * GRP_CHUNK;
-    const int n = n_all - base < 0 ? 0 : (n_all - base < GRP_CHUNK ? n_all - base : GRP_CHUNK);      // positions of this workgroup
+    const int n_all = upd_count(L), base = part * CHUNK;
+    const int n = n_all - base < 0 ? 0 : (n_all - base < CHUNK ? n_all - base : CHUNK);      // positions of this workgroup
     const int64_t head = *c.head, used = *c.used;
     // Position of element e: base + EL * t + e. Every read is unconditional (the first quad, or 16 bytes of the
     // library's own, where a quad is not wholly there) so that they are in flight together; the one quad that the end of the layer
@@ -348,7 +348,7 @@ __device__ __forceinline__ void update_group(const UpdBatch& B, const int block,
     }
     // ranks in position order: workgroups first, then threads, then a thread's elements
     const int own = __popc(admit_bits);
-    const int both = fg_wave_scan(own | evicted << 16), incl = both & 0xFFFF;      // (at most 512 of each in a wavefront)
+    const int both = fg_wave_scan(own | evicted << 16), incl = both & 0xFFFF;      // (at most 1024 of each in a wavefront)
     if (lane == FG_WAVE - 1) {
         S.wave_count[wave] = incl;
         if (both >> 16) atomicAdd(&S.evicted, both >> 16);
@@ -450,7 +450,7 @@ __device__ __forceinline__ void update_group(const UpdBatch& B, const int block,
         }
     }
     if constexpr (COPY) {
-        static_assert(sizeof(S.hist) >= GRP_CHUNK * sizeof(int2), "every position may be admitted");
+        static_assert(sizeof(S.hist) >= CHUNK * sizeof(int2), "every position may be admitted");
         typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
         const int pieces = (int)(L.row_bytes >> 4), items = (int)(total < L.room ? total : L.room) * pieces;
         constexpr int TOGETHER = 8;
@@ -497,3 +497,11 @@ fg_status_t fg_gather_aggregate_ids_with(const int32_t* row_start_dev, const int
                                          const UpdBatch* update, bool* rode, void* stream);
 // whether that launch is one for a loader of `max_rows` rows with at most most_hits cached rows of a layer to fetch
 bool fg_loader_takes_update(int64_t max_rows, int32_t dim, fg_dtype_t dtype, int64_t most_hits, int update_blocks);
+// fg_gather_aggregate_linear_ids likewise, for at most so many chunks of 4096 positions
+constexpr int fg_load_linear_update_chunks = 32;
+fg_status_t fg_gather_aggregate_linear_ids_with(const int32_t* row_start_dev, const int32_t* row_end_dev, const int32_t* col_ids_dev, int64_t nnz,
+                                                int32_t n_block_rows, const int32_t* rows_dev, const int64_t* n_rows_dev, int64_t max_rows,
+                                                const int32_t* row_ids_dev, const float* table, int64_t table_rows, int64_t src_stride, int32_t d_in,
+                                                int32_t d_out, const float* W, const float* bias, int32_t relu, float* agg_ws, int64_t agg_stride,
+                                                float* h_out, int32_t n_out, int64_t out_stride, const fg_cache_t* cache, int32_t n_fetch_layers,
+                                                const fg_fetch_layer_t* fetch_layers, const UpdBatch* update, bool* rode, void* stream);

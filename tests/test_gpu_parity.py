@@ -2394,8 +2394,7 @@ def test_iterations_queued_back_to_back_match_one_at_a_time(env):
     ("two chunks", dict(fused_input=True, backward=True, weight_grads=True, p_grad=1.0)),
     ("many chunks", dict(fused_input=True, backward=True, weight_grads=True, overlap_update=False)),
     ("too many chunks", dict(fused_input=True, backward=True, weight_grads=True)),
-    # a step's update inside the loader's launch and the seed layer's: two of its workgroups for layer 1, nothing / everything admitted; more
-    # workgroups of the loader than are given its LDS
+    # a step's update inside the loader's launch and the seed layer's: two of its workgroups for layer 1, nothing / everything admitted; fifteen
     ("two chunks of a step", dict(fused_input=True, overlap_update=False, fuse_small_layers=True)),
     ("two chunks of a step", dict(fused_input=True, overlap_update=False, fuse_small_layers=True, p_grad=0.0)),
     ("two chunks of a step", dict(fused_input=True, overlap_update=False, fuse_small_layers=True, p_grad=1.0)),
@@ -2403,6 +2402,7 @@ def test_iterations_queued_back_to_back_match_one_at_a_time(env):
     ("two chunks of a step", dict(fused_input=True, fuse_small_layers=True)),
     ("two chunks of a mixed step", dict(fused_input=True, overlap_update=False)),
     ("many chunks of a step", dict(fused_input=True, overlap_update=False, fuse_small_layers=True)),
+    ("many chunks of a step", dict(fused_input=True, fuse_small_layers=True)),      # (with node ids as columns: in the launch that multiplies too)
 ])
 @pytest.mark.parametrize("col_ids", [True, False])
 def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, kwargs, col_ids):
