@@ -845,7 +845,8 @@ typedef struct fg_path_call {
     const float* bias[FG_PATH_MAX_LAYERS + 1];
     float p_grad;
     int32_t update;            /* update the cache at the end */
-    int32_t overlap;           /* selection, weight gradients or the update beside them on P->side */
+    int32_t overlap;           /* what runs beside the layers goes to P->side: the selection (or, where that rides in the loader's launch, the top-down
+                                  pass behind it), weight gradients, or an update that does not ride in their launches */
     int32_t fetch_with_loader; /* the cached rows ride in the id-column loader's launch */
     int32_t ahead;             /* the weight gradients of layers 2 .. L go to P->side before layer 2's backward pass */
     int32_t promised;          /* the previous call ran a top-down pass ahead ... */
