@@ -1185,7 +1185,7 @@ fg_status_t fg_aggregate_linear_with(const int32_t* row_start_dev, const int32_t
         const int n_panels = (int)fg_ceil_div(d_out, PL_BN);
         const size_t lds = panel_bytes > (size_t)SK_PART_BYTES ? panel_bytes : (size_t)SK_PART_BYTES;
         const unsigned grid = (unsigned)(fg_ceil_div(fg_ceil_div(max_rows, 32), 8) * 8 * n_panels);
-        const int copy_blocks = copies ? (int)fg_ceil_div(fg_row_copy_blocks(*copies), 2) : 0;      // (twice as many threads as there)
+        const int row_blocks = copies ? (int)fg_ceil_div(fg_row_copy_blocks(*copies), 2) : 0, copy_blocks = row_blocks < 128 ? row_blocks : 128;
         if (copy_blocks > 0) {
             hipLaunchKernelGGL(linear_f32_splitk_copies_kernel, dim3(grid + (unsigned)(copies->n * copy_blocks)), dim3(PL_THREADS), lds, (hipStream_t)stream,
                                (int)grid, *copies, copy_blocks, (const char*)h_src, n_src, src_stride, rows_dev, n_rows_dev, max_rows, d_in, d_out, W, bias, relu,

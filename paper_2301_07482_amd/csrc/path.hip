@@ -4,7 +4,7 @@
 // A small iteration is bound by the host that queues it: from Python, a foreign call with 20 to 30 arguments per launch took 66 us for
 // an iteration of the smallest workload (10 k nodes, 256 seeds x 10 x 5) whose launches kept the GPU busy for 50. Queued from here the
 // host needed 40: step 57 -> 50 us, training iteration 90 -> 78 with the kernels of that time, which was what the GPU needed; with
-// shorter ones it is 42 and 71.
+// fewer and shorter ones it is 33.5 and 62.
 #include "update_group.h"
 
 namespace {
@@ -168,21 +168,42 @@ struct Iter {
 
     // The selection has gone with the loader: the index is final for this iteration, and with a second stream the next mini-batch is looked up and pruned
     // there beside the layers above. (What that pass overwrites was last read two iterations ago on this stream.)
-    fg_status_t selected(const fg_update_call* ride, bool* rows_due) const {
+    // *due_from: first of the update's layers whose admitted rows are still to be copied. With a second stream layer 1, most of them, is copied there
+    // as well, beside the layers above (in the seed layer's launch, whose workgroups take half a compute unit each, 16 k rows took 15 us more: large
+    // step 181.3 us, 175.8 so; medium 180.1, 173.7; with the paper's thresholds 164.8, 159.9).
+    fg_status_t selected(const fg_update_call* ride, const UpdBatch& selection, int* due_from) const {
         fg_update_queued(*ride);
-        *rows_due = true;
+        *due_from = 0;
         if (!next) return FG_OK;
         FG_HIP(hipEventRecord((hipEvent_t)P.ev_pruned, (hipStream_t)C.stream));
         FG_HIP(hipStreamWaitEvent((hipStream_t)P.side, (hipEvent_t)P.ev_pruned, 0));
         FG_TRY(Iter(P, C, it + 1).top_down(*next, P.side));
+        fg_row_copy_batch copies;
+        fg_update_row_copies(selection, &copies);
+        copies.n = 1;
+        FG_TRY(fg_launch_row_copies(copies, (hipStream_t)P.side));
+        *due_from = 1;
         FG_HIP(hipEventRecord((hipEvent_t)P.ev_next_pruned, (hipStream_t)P.side));
         *next_pruned = 1;
         return FG_OK;
     }
 
-    // ride: an update whose selection may go with the loader; *rode: it has. *rows_due: its rows are still to be copied (not by the seed layer's launch)
+    // the row copies that are due, and about how much they write
+    static double due_copies(const UpdBatch& U, int from, fg_row_copy_batch* copies) {
+        fg_update_row_copies(U, copies);
+        double bytes = 0.0;
+        for (int i = from; i < U.n_layers; ++i) {
+            copies->c[i - from] = copies->c[i];
+            bytes += (double)U.l[i].p_grad * (double)U.l[i].n * (double)U.l[i].row_bytes;
+        }
+        copies->n = U.n_layers - from;
+        return bytes;
+    }
+
+    // ride: an update whose selection may go with the loader; *rode: it has. Up to 4 MB of its rows go with a seed layer of one launch (27 MB
+    // of them on one stream: 195 us, 186 to 190 with a launch of their own).
     fg_status_t forward(const fg_path_batch_t& b, bool once, const fg_fetch_layer_t* fetch, int n_fetch, const fg_update_call* ride, const UpdBatch* selection,
-                        bool* rode, bool* rows_due) const {
+                        bool* rode, int* due_from) const {
         const int L = P.n_layers;
         const bool fused = P.fused_input && !once;
         void* st = C.stream;
@@ -210,12 +231,11 @@ struct Iter {
             if (one_launch(l, B.n)) {
                 fg_row_copy_batch copies;
                 bool copied = false;
-                const bool due = *rows_due && l == L;
-                if (due) fg_update_row_copies(*selection, &copies);
+                const bool due = *rode && l == L && *due_from < selection->n_layers && due_copies(*selection, *due_from, &copies) <= 4.0 * 1024.0 * 1024.0;
                 FG_TRY(fg_aggregate_linear_with(B.start_dev, B.end_dev, B.col_dev, B.nnz, n, S.normal_pos[l], n_normal, n, (const float*)P.h[l - 1], n_in, in_b,
                                                 P.dims[l - 1], P.dims[l], (const float*)C.w[l], C.bias[l], relu, nullptr, agg_b, (float*)P.h[l], n, out_b,
                                                 due ? &copies : nullptr, due ? &copied : nullptr, st));
-                if (copied) *rows_due = false;
+                if (copied) *due_from = selection->n_layers;
                 continue;
             }
             const bool own_rows = l == 1 && fused && b.own_rows_from_table;
@@ -224,7 +244,7 @@ struct Iter {
                                                            (const float*)C.feat, P.num_nodes, d0b, P.dims[0], P.dims[1], (const float*)C.w[1], C.bias[1], relu,
                                                            (float*)P.agg[1], agg_b, (float*)P.h[1], n, out_b, n_fetch ? C.cache : nullptr, n_fetch,
                                                            n_fetch ? fetch : nullptr, selection, rode, st));
-                if (*rode) FG_TRY(selected(ride, rows_due));
+                if (*rode) FG_TRY(selected(ride, *selection, due_from));
                 continue;
             }
             if (fused && l == 1) {
@@ -232,7 +252,7 @@ struct Iter {
                     FG_TRY(fg_gather_aggregate_ids_with(B.start_dev, B.end_dev, b.col_ids1_dev, B.nnz, n, S.normal_pos[1], n_normal, n, B.ids_dev, C.feat, P.num_nodes, d0b,
                                                         P.dims[0], (fg_dtype_t)in_code, P.agg[1], agg_b, (fg_dtype_t)agg_code(), own_rows ? nullptr : P.h[0], d0b, n_in,
                                                         n_fetch ? C.cache : nullptr, n_fetch, n_fetch ? fetch : nullptr, selection, rode, st));
-                    if (*rode) FG_TRY(selected(ride, rows_due));
+                    if (*rode) FG_TRY(selected(ride, *selection, due_from));
                 } else
                     FG_TRY(fg_gather_aggregate(B.start_dev, B.end_dev, B.col_dev, B.nnz, n, S.normal_pos[1], n_normal, n, b.layer[0].ids_dev, n_in, C.feat,
                                                P.num_nodes, d0b, P.dims[0], (fg_dtype_t)in_code, P.agg[1], agg_b, (fg_dtype_t)agg_code(), P.h[0], d0b, n_in, st));
@@ -324,7 +344,8 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
     // With norms from outside the update's selection does not depend on the layers
     UpdBatch selection;
     fg_update_call ride = {};
-    bool may_ride = false, rode = false, rows_due = false;
+    bool may_ride = false, rode = false;
+    int due_from = 0;
     if (do_update && !P.backward && I.selects_with_loader(*batch)) {
         I.update_specs(*batch, false, call->specs);
         ride = {call->cache, call->iter, call->p_grad, L - 1, call->specs, I.ws_update(), P.ws_update_bytes};
@@ -370,10 +391,10 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
             n_fetch = 0;
         }
     }
-    FG_TRY(I.forward(*batch, once, fetch, n_fetch, &ride, may_ride ? &selection : nullptr, &rode, &rows_due));
-    if (rows_due) {
+    FG_TRY(I.forward(*batch, once, fetch, n_fetch, &ride, may_ride ? &selection : nullptr, &rode, &due_from));
+    if (rode && due_from < selection.n_layers) {
         fg_row_copy_batch copies;
-        fg_update_row_copies(selection, &copies);
+        Iter::due_copies(selection, due_from, &copies);
         FG_TRY(fg_launch_row_copies(copies, main));
     }
     if (rode) return FG_OK;

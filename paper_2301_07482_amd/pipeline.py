@@ -523,7 +523,10 @@ class HotPath:
 
     def flush(self, selection_done=False, main=None):
         """Copy the rows admitted by the last iteration into the cache, if that is still due (`run` leaves it to the next
-        call when that call's top-down pass is already on the second stream). Called by everything that reads the cache."""
+        call when that call's top-down pass is already on the second stream), and wait for those that are on their way on that stream
+        (of a selection that went with the loader, in front of the event of that pass). Called by everything that reads the cache."""
+        if self._td_for is not None and not selection_done:
+            (torch.cuda.current_stream() if main is None else main).wait_event(self.ev_next_pruned)
         if self._row_copy_due is None:
             return
         it, specs = self._row_copy_due
