@@ -167,7 +167,8 @@ struct Iter {
     }
 
     // The selection has gone with the loader: the index is final for this iteration, and with a second stream the next mini-batch is looked up and pruned
-    // there beside the layers above. (What that pass overwrites was last read two iterations ago on this stream.)
+    // there beside the layers above. (What that pass overwrites was last read two iterations ago, in front of the event recorded here. The layers above
+    // and the row copies of this iteration are not: an iteration that puts its selection on the second stream next records them, see fg_path_run.)
     // *due_from: first of the update's layers whose admitted rows are still to be copied. With a second stream layer 1, most of them, is copied there
     // as well, beside the layers above (in the seed layer's launch, whose workgroups take half a compute unit each, 16 k rows took 15 us more: large
     // step 181.3 us, 175.8 so; medium 180.1, 173.7; with the paper's thresholds 164.8, 159.9).
@@ -358,8 +359,14 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
         if (!call->pruned_ahead) {
             FG_HIP(hipEventRecord((hipEvent_t)P.ev_pruned, main));
             FG_HIP(hipStreamWaitEvent(side, (hipEvent_t)P.ev_pruned, 0));
+        } else if (!call->due) {
+            // Iteration it - 1 announced this one and left no rows: its selection went with its loader. Its layers and row copies have recorded
+            // nothing; they are on this stream in front of here.
+            FG_HIP(hipEventRecord((hipEvent_t)P.ev_done[(call->iter + 1) % 2], main));
         }
-        // what it overwrites was last read by iteration it - 2 and its row copy, which recorded this event
+        // What it overwrites (half it % 2 of the workspace, set (it + 1) % 3 of the lists) was last read by iteration it - 2 and its row copy. If that
+        // iteration's rows were left to it - 1, or it - 1 found that its selection had gone with its loader, it - 1 recorded this event behind them;
+        // else they are in front of a wait of this stream: ev_pruned, of it - 1 or of this iteration.
         FG_HIP(hipStreamWaitEvent(side, (hipEvent_t)P.ev_done[call->iter % 2], 0));
         I.update_specs(*batch, false, call->specs);
         FG_TRY(fg_cache_update_select(call->cache, call->iter, call->p_grad, L - 1, call->specs, I.ws_update(), P.ws_update_bytes, side));

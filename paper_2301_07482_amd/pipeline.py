@@ -327,8 +327,8 @@ class HotPath:
         self.saving = [torch.zeros(n[l] if admit_budget else 0, dtype=torch.int32, device=dev) for l in range(L + 1)]
         # what the top-down pass writes exists three times (iteration it uses set it % 3), so that the pass for the next
         # mini-batch can run while this one's layers are computed (`run(..., next_bt=...)`) and the previous one's
-        # admitted rows are still being copied: the second stream then waits for nothing younger than the row copy of
-        # two iterations ago, and its chain selection -> next top-down pass can start before this iteration's loader
+        # admitted rows are still being copied: the second stream then waits for nothing younger than the layers and the row copy
+        # of two iterations ago, and its chain selection -> next top-down pass can start before this iteration's loader
         self._packed = set()     # the sets whose addresses fg_path_run's descriptor holds
         mk = lambda k, dt: _Places((torch.zeros(n[l], dtype=dt, device=dev) for l in range(L + 1)), self._packed, k)
         self._lists = [dict(live=mk(k, torch.uint8), hit=mk(k, torch.uint8), hit_pos=mk(k, torch.int32), hit_slot=mk(k, torch.int32),
@@ -362,7 +362,7 @@ class HotPath:
         self.overlap_update = overlap_update
         self.side = torch.cuda.Stream(device=device) if overlap_update else None
         self.ev_pruned, self.ev_selected, self.ev_next_pruned = (_Event() for _ in range(3))
-        self.ev_done = [_Event(), _Event()]     # row copy of iteration it: ev_done[it % 2]
+        self.ev_done = [_Event(), _Event()]     # layers and row copy of iteration it, where the next one found it pruned ahead: ev_done[it % 2]
         self.ev_bw = [_Event() for _ in range(L + 1)]
         self.admit_budget = dict(admit_budget) if admit_budget else None   # {layer: rows per update}: access-aware admission
         assert not (self.admit_budget and not update_all), "the access-aware admission needs fg_cache_update_all"
@@ -691,6 +691,7 @@ class HotPath:
         self._td_for = None
         if promised:      # (also when the promise was not kept: that pass writes the lists this call is about to use)
             main.wait_event(self.ev_next_pruned)   # behind the previous selection on that stream
+        rode = pruned_ahead and self._row_copy_due is None      # iteration it - 1's selection went with its loader (`_run_native`)
         self.flush(selection_done=promised, main=main)
         if not pruned_ahead:
             self._top_down(bt, it, st, tick)
@@ -712,9 +713,12 @@ class HotPath:
             if not pruned_ahead or hold_second_stream:
                 self.ev_pruned.record(main)
                 side.wait_event(self.ev_pruned)
+            if rode:      # its layers and row copies, in front of here, have recorded nothing
+                self.ev_done[(it - 1) % 2].record(main)
             # What this selection and the top-down pass behind it overwrite (half it % 2 of the workspace, set (it + 1) % 3
-            # of the lists) was last read by iteration it - 2 and its row copy, which recorded this event (the copy of
-            # iteration it - 1, just queued, recorded the other one).
+            # of the lists) was last read by iteration it - 2 and its row copy. If that iteration's rows were left to it - 1, or
+            # its selection had gone with its loader, it - 1 recorded this event behind them (the copy of iteration it - 1, just
+            # queued, recorded the other one); else they are in front of ev_pruned, recorded by it - 1 or here.
             side.wait_event(self.ev_done[it % 2])
             if self.admit_budget:
                 self._estimates(bt, side_st)
@@ -723,7 +727,7 @@ class HotPath:
             self.ev_selected.record(side)
             if next_bt is not None and self.one_launch_top_down:
                 # the cache's index is final for this iteration: the next mini-batch can be looked up and pruned now,
-                # into the next set of lists (free since the row copy of two iterations ago: ev_done above)
+                # into the next set of lists (free since the layers and the row copy of two iterations ago: ev_done above)
                 self._bind(it + 1)
                 self._top_down(next_bt, it + 1, side_st, _no_tick)
                 self.ev_next_pruned.record(side)

@@ -2372,6 +2372,50 @@ def test_iterations_queued_back_to_back_match_one_at_a_time(env):
         ref.close()
 
 
+@pytest.mark.parametrize("order", ["roorooror", "oroorrooo", "rtoruotro"])
+def test_steps_of_both_kinds_queued_back_to_back_match_one_at_a_time(env, order):
+    """Steps whose selection goes with the loader (r), steps that put it on the second stream (o) and timed ones of both sizes, a call per layer
+    (t, u), each announced to the one before it and queued without a synchronisation in between: the bits of the same steps run one at a time."""
+    torch, B = env
+    import dataclasses
+    from paper_2301_07482_amd.pipeline import DeviceBatch
+    w = dataclasses.replace(wl.WORKLOADS["tiny"], num_nodes=90_000, num_edges=1_800_000, feat_dim=52, hidden=128, fanouts=(3, 2, 8), batch=4501, cache_capacity=20_000)
+    g = wl.make_graph(w)
+    L = w.num_layers
+    mbs = [wl.minibatch(w if k in "rt" else dataclasses.replace(w, batch=900), g, it) for it, k in enumerate(order)]
+    paths = [G.make_hotpath(w, fused_input=True, fuse_small_layers=True)[0] for _ in range(2)]
+    try:
+        batches = [DeviceBatch(mb, {l: wl.grad_norms(w, it, l, mb.ids[l]) for l in range(1, L)}, col_ids=True) for it, mb in enumerate(mbs)]
+        ends = [[None if e is None else e.clone() for e in bt.end] for bt in batches]
+        outs = []
+        for hp, alone in zip(paths, (False, True)):
+            for bt, before in zip(batches, ends):      # (pruning empties rows of a mini-batch in place)
+                for e, b in zip(bt.end, before):
+                    if b is not None:
+                        e.copy_(b)
+            torch.cuda.synchronize()
+            out = []
+            for it, (k, bt) in enumerate(zip(order, batches)):
+                hp.run(bt, it, next_bt=batches[it + 1] if it + 1 < len(order) else None, timer=(lambda *a: None) if k in "tu" else None)
+                assert hp.loads_and_multiplies(bt) == (k in "rt")
+                assert (hp._row_copy_due is None) == (k == "r" or it + 1 == len(order)) and (hp._td_for is None) == (it + 1 == len(order))
+                out += [hp.H[l][:len(mbs[it].ids[l])].clone() for l in range(1, L + 1)]
+                if alone:
+                    torch.cuda.synchronize()
+            out += [hp.counts_log, hp.stats_log]
+            for l in range(1, L):
+                e = hp.export_cache(l, len(order))
+                out += [torch.as_tensor(np.asarray(e[k])) for k in ("head", "nodes", "slots", "stamps")] + [torch.from_numpy(hp.cache_rows(l, e["slots"]))]
+            assert int(hp.counts_log[:, 1:L, 1].sum()) > 1000, "the caches were hardly used"
+            outs.append(out)
+        assert len(outs[0]) == len(outs[1])
+        for i, (a, b) in enumerate(zip(*outs)):
+            assert torch.equal(a, b), f"record {i} of {len(outs[0])}"
+    finally:
+        for hp in paths:
+            hp.close()
+
+
 @pytest.mark.parametrize("workload,kwargs", [
     ("tiny", dict(fused_input=True)),
     ("tiny", dict(fused_input=True, copy_own_rows=True, fetch_with_loader=False)),

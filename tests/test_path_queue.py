@@ -1,0 +1,61 @@
+"""The order in which fg_path_run queues an iteration on its two streams, recorded without a device (tests/path_queue.py)."""
+import itertools
+
+import pytest
+
+from tests.path_queue import MAIN, SIDE, record
+
+DIMS = [32, 64, 64, 64]
+
+
+def sizes(n1):
+    return [60_000, n1, 5_000, 300]
+
+
+RIDES, OWN = dict(n=sizes(25_000)), dict(n=sizes(24_000))      # layer 1 as one launch beside a second stream: from 24576 positions on
+MODEL = ["model", dict(dims=DIMS, n_max=[80_000, 40_000, 8_000, 1_024])]
+
+
+def behind(calls):
+    """For every launch, in order: (index of the call, stream, kernel, launches known to have ended when it starts: {launch's number}), and per call
+    what it returned."""
+    clock, events, out = {MAIN: set(), SIDE: set()}, {}, []
+    n = 0
+    for i, (*_, lines) in enumerate(calls):
+        for op, stream, what, *_ in lines:
+            s = int(stream)
+            if op == "launch":
+                out.append((i, s, what, frozenset(clock[s])))
+                clock[s].add(n)
+                n += 1
+            elif op == "record":
+                events[what] = set(clock[s])
+            else:
+                clock[s] |= events.get(what, set())      # (an event that was never recorded holds nobody up)
+    return out
+
+
+@pytest.mark.parametrize("kinds", list(itertools.product("ro", repeat=6)) + [tuple("rxoror"), tuple("orxoor"), tuple("roorooroo")])
+def test_steps_of_both_kinds_in_any_order_follow_each_other(tmp_path_factory, kinds):
+    """Steps whose selection goes with the loader (r) and steps that put it on the second stream (o; x: whose announced successor is not the one that
+    comes), queued back to back: whatever a call queues waits for everything that the call before the last one queued, and for the copy of the
+    rows that it left to the last one. (Sets of lists and halves of the update's workspace are used again then.)"""
+    batches = [RIDES if k == "r" else OWN for k in kinds]
+    script = [MODEL] + [["run", dict(it=i, batch=b, next=None if i + 1 == len(kinds) else (dict(n=sizes(20_000)) if k == "x" else batches[i + 1]))]
+                        for i, (k, b) in enumerate(zip(kinds, batches))]
+    _, *calls = record(tmp_path_factory.getbasetemp(), script)
+    launches = behind(calls)
+    for i, k in enumerate(kinds):
+        rc, selected, next_pruned, begun, _ = calls[i]
+        mine = [name for j, _, name, _ in launches if j == i]
+        assert rc == 0 and begun == 1 and next_pruned == (i + 1 < len(kinds))
+        assert selected == (k != "r" and next_pruned)
+        assert any("load_linear" in name for name in mine) == (k == "r")
+    first = [min(n for n, x in enumerate(launches) if x[0] == i) for i in range(len(calls))] + [len(launches)]
+    for n, (i, stream, name, before) in enumerate(launches):
+        if i < 2:
+            continue
+        due = calls[i - 2][1] and "copy_rows" in launches[first[i - 1]][2]      # the first launch of the call before this one
+        assert due == calls[i - 2][1]
+        needed = set(range(first[i - 1] + (1 if due else 0)))
+        assert needed <= before, f"call {i}: {name} on stream {stream} does not wait for {[launches[m][2] for m in sorted(needed - before)]}"
