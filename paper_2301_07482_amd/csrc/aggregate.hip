@@ -296,6 +296,7 @@ __global__ __launch_bounds__(AGG_THREADS) void loader_fetch_kernel(
 // Its workgroups have the 1024 threads of the update's own launch (with 256, and 16 positions in each thread's registers, 18 us against 10). Step of 1.5 k
 // positions 42.0 -> 33.5 us, 3.5 k (88 columns, rows copied by a launch of their own) 52.3 -> 46.3, 5.9 k 77.7 -> 69.8, mixed 3 k 56.9 -> 48.7.
 constexpr int RIDE_THREADS = 1024;
+constexpr size_t RIDE_LDS_MAX = 160 * 1024;      // of a compute unit
 template <int IN, int OUT>
 __global__ __launch_bounds__(RIDE_THREADS) void loader_fetch_update_kernel(
     UpdBatch U, int copy_blocks, fg_row_copy_batch copies, const int32_t* __restrict__ row_start, const int32_t* __restrict__ row_end,
@@ -338,10 +339,18 @@ static int64_t fetch_blocks(int64_t most) {
     return blocks < 256 ? blocks : 256;
 }
 
-// (A loader of a million such workgroups would be a grid of more than 2^31 threads.)
+// LDS of a workgroup of the loader with the update's selection: the neighbours its rows have staged, or what the selection needs
+static size_t ride_lds(int lanes_log2) {
+    const size_t stage = (size_t)(RIDE_THREADS >> lanes_log2) * AGG_MAX_STAGE * sizeof(int32_t), group = sizeof(GrpShared<RIDE_THREADS / FG_WAVE>);
+    return group > stage ? group : stage;
+}
+
+// Not for rows of one piece: a workgroup's 1024 of them stage 256 KB, more than a compute unit's LDS holds. With the 128 KB of two pieces (one
+// workgroup on each) it is still the faster one: step of 1.3 k positions 39.8 us with own launches, 35.1 so; 10 k 56.6, 46.3; 16-bit 60.3, 51.1. (A loader of a million such workgroups would be a
+// grid of more than 2^31 threads.)
 bool fg_loader_takes_update(int64_t max_rows, int32_t dim, fg_dtype_t dtype, int64_t most_hits, int update_blocks) {
     const int lg = lanes_log2_for(dim * fg_dtype_size(dtype) / 16);
-    return max_rows > 0 && most_hits > 0 &&
+    return max_rows > 0 && most_hits > 0 && ride_lds(lg) <= RIDE_LDS_MAX &&
            fg_ceil_div(max_rows, RIDE_THREADS >> lg) + fg_ceil_div(fetch_blocks(most_hits) * AGG_THREADS, RIDE_THREADS) + update_blocks <= 1 << 20;
 }
 
@@ -551,9 +560,8 @@ fg_status_t fg_gather_aggregate_ids_with(const int32_t* row_start_dev, const int
     hipStream_t st = (hipStream_t)stream;
     if (update && fg_loader_takes_update(max_rows, dim, in_dtype, most, update->sel_first[update->n_layers])) {
         const int64_t wide = fg_ceil_div(max_rows, RIDE_THREADS >> lg), wide_copies = fg_ceil_div(copy_blocks * AGG_THREADS, RIDE_THREADS);
-        const size_t stage = (size_t)(RIDE_THREADS >> lg) * AGG_MAX_STAGE * sizeof(int32_t), group = sizeof(GrpShared<RIDE_THREADS / FG_WAVE>);
         const auto kernel = f32 ? loader_fetch_update_kernel<FG_F32, FG_F32> : loader_fetch_update_kernel<FG_F16, FG_BF16>;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(update->sel_first[update->n_layers] + wide + wide_copies)), dim3(RIDE_THREADS), group > stage ? group : stage,
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(update->sel_first[update->n_layers] + wide + wide_copies)), dim3(RIDE_THREADS), ride_lds(lg),
                            st, *update, (int)wide_copies, copies, row_start_dev, row_end_dev, col_ids_dev, nnz, n_block_rows, rows_dev, n_rows_dev, max_rows,
                            (const char*)table, table_rows, src_stride, pieces, (char*)agg, agg_stride, lg, row_ids_dev, n_block_rows, (char*)h_self_out,
                            h_self_stride, n_self_rows);

@@ -85,7 +85,7 @@ class Queue:
         return x
 
     def run(self, it, batch, next=None, update=1, overlap=1, commit=False):
-        """One call, with what the previous one left. commit: the caller commits what is due first. -> [code, selected, next_pruned, begun, lines]"""
+        """One call, with what the previous one left. commit: the caller commits what is due first. -> [0 or the error, selected, next_pruned, begun, lines]"""
         B, L = self.B, self.P.n_layers
         if commit and self.due is not None:
             assert B._lib.fg_cache_update_commit(self.cache, self.due, L - 1, self.specs, self.P.ws_update + self.due % 2 * self.P.ws_update_stride,
@@ -110,7 +110,7 @@ class Queue:
             self.ahead = [it + 1, next]
         if call.selected:
             self.due = it
-        return [rc, call.selected, call.next_pruned, call.begun, self._log()]
+        return [f"{rc}: {B.fg_last_error()}" if rc else 0, call.selected, call.next_pruned, call.begun, self._log()]
 
 
 if __name__ == "__main__":

@@ -2445,6 +2445,9 @@ def test_steps_of_both_kinds_queued_back_to_back_match_one_at_a_time(env, order)
     ("two chunks of a step", dict(fused_input=True, overlap_update=False)),
     ("two chunks of a step", dict(fused_input=True, fuse_small_layers=True)),
     ("two chunks of a mixed step", dict(fused_input=True, overlap_update=False)),
+    ("one piece a row, two chunks of a step", dict(fused_input=True, overlap_update=False, fuse_small_layers=True)),      # (own launches)
+    ("one piece a row, two chunks of a mixed step", dict(fused_input=True, overlap_update=False)),
+    ("two pieces a row, two chunks of a step", dict(fused_input=True, overlap_update=False, fuse_small_layers=True)),
     ("many chunks of a step", dict(fused_input=True, overlap_update=False, fuse_small_layers=True)),
     ("many chunks of a step", dict(fused_input=True, fuse_small_layers=True)),      # (with node ids as columns: in the launch that multiplies too)
 ])
@@ -2467,6 +2470,10 @@ def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, k
         w = dataclasses.replace(w, num_nodes=90_000, batch=4501)
     if workload.endswith("mixed step"):
         w = dataclasses.replace(w, feat_dtype="f16", feat_dim=72, compute_dtype="bf16")
+    pieces = {"one": 1, "two": 2}.get(workload.split(" ")[0], 0) if " a row" in workload else 0
+    if pieces:
+        w = dataclasses.replace(w, feat_dim=pieces * (8 if w.feat_dtype == "f16" else 4))
+        workload = workload.split(", ")[1]
     if workload == "two chunks":
         w = dataclasses.replace(w, num_nodes=40_000, num_edges=800_000, feat_dim=52, hidden=88, fanouts=(3, 2, 8), batch=301, cache_capacity=5_000)
     if workload.endswith("many chunks"):

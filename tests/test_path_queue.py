@@ -59,3 +59,20 @@ def test_steps_of_both_kinds_in_any_order_follow_each_other(tmp_path_factory, ki
         assert due == calls[i - 2][1]
         needed = set(range(first[i - 1] + (1 if due else 0)))
         assert needed <= before, f"call {i}: {name} on stream {stream} does not wait for {[launches[m][2] for m in sorted(needed - before)]}"
+
+
+@pytest.mark.parametrize("feat,compute", [("F32", "F32"), ("F16", "BF16")])
+def test_no_launch_asks_for_more_lds_than_a_compute_unit_has(tmp_path_factory, feat, compute):
+    """Rows of one 16-byte piece and up, on one stream and on two, below and above the sizes where layer 1 becomes one launch, forward and training."""
+    piece = 4 if feat == "F32" else 8
+    for d in (piece, 2 * piece, 4 * piece, 8 * piece):
+        for train in (0, 1):
+            script = [["model", dict(dims=[d, 64, 64, 64], n_max=[80_000, 40_000, 8_000, 1_024], feat=feat, compute=compute, fuse_small_layers=int(feat == "F32" and not train),
+                                backward=train, weight_grads=train)]]
+            script += [["run", dict(it=i, batch=dict(n=sizes(n1), own_rows_from_table=int(feat == "F32" and not train)), overlap=overlap)]
+                       for i, (n1, overlap) in enumerate((n1, o) for n1 in (5_000, 12_000, 25_000) for o in (0, 1))]
+            _, *calls = record(tmp_path_factory.getbasetemp(), script)
+            for rc, *_, lines in calls:
+                assert rc == 0, rc
+                for name, lds in ((x[2], int(x[3])) for x in lines if x[0] == "launch"):
+                    assert lds <= 160 * 1024, f"{name} asks for {lds} bytes, rows of {d} {feat}"
