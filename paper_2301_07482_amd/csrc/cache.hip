@@ -842,6 +842,8 @@ fg_status_t fg_update_describe(const char* who, const fg_update_call& c, UpdBatc
 }
 
 void fg_update_queued(const fg_update_call& c) { update_queued(0, c.cache, c.iter, c.n_layers, c.layers); }
+void fg_update_selected(const fg_update_call& c) { update_queued(1, c.cache, c.iter, c.n_layers, c.layers); }
+void fg_update_committed(const fg_update_call& c) { update_queued(2, c.cache, c.iter, c.n_layers, c.layers); }
 
 extern "C" fg_status_t fg_cache_update_all(fg_cache_t* cache, int64_t iter, float p_grad, int32_t n_layers,
                                            const fg_update_layer_t* layers, void* ws_dev, size_t ws_bytes, void* stream) {

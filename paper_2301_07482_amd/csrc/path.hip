@@ -25,7 +25,7 @@ struct Iter {
     int64_t* input_counts;
     int64_t it;
     const fg_path_batch_t* next = nullptr;      // a mini-batch whose top-down pass may run on the second stream behind a selection that goes with the loader
-    int32_t* next_pruned = nullptr;
+    int32_t *next_pruned = nullptr, *rows_due = nullptr;      // the call's `next_pruned` and `selected`
 
     Iter(const fg_path_t& p, const fg_path_call_t& c, int64_t iter)
         : P(p), C(c), S(p.lists[iter % 3]), counts(p.counts_log + iter % p.ring * (p.n_layers + 1) * 3), stats(p.stats_log + iter % p.ring * (p.n_layers + 1) * 4),
@@ -173,18 +173,25 @@ struct Iter {
     // as well, beside the layers above (in the seed layer's launch, whose workgroups take half a compute unit each, 16 k rows took 15 us more: large
     // step 181.3 us, 175.8 so; medium 180.1, 173.7; with the paper's thresholds 164.8, 159.9).
     fg_status_t selected(const fg_update_call* ride, const UpdBatch& selection, int* due_from) const {
-        fg_update_queued(*ride);
+        fg_update_selected(*ride);      // the rows are due until all their copies are queued: a call that fails in between leaves a cache that says so
+        *rows_due = 1;
         *due_from = 0;
         if (!next) return FG_OK;
         FG_HIP(hipEventRecord((hipEvent_t)P.ev_pruned, (hipStream_t)C.stream));
         FG_HIP(hipStreamWaitEvent((hipStream_t)P.side, (hipEvent_t)P.ev_pruned, 0));
-        FG_TRY(Iter(P, C, it + 1).top_down(*next, P.side));
-        fg_row_copy_batch copies;
-        fg_update_row_copies(selection, &copies);
-        copies.n = 1;
-        FG_TRY(fg_launch_row_copies(copies, (hipStream_t)P.side));
-        *due_from = 1;
+        fg_status_t rc = Iter(P, C, it + 1).top_down(*next, P.side);
+        if (rc == FG_OK) {
+            fg_row_copy_batch copies;
+            fg_update_row_copies(selection, &copies);
+            copies.n = 1;
+            rc = fg_launch_row_copies(copies, (hipStream_t)P.side);
+        }
         FG_HIP(hipEventRecord((hipEvent_t)P.ev_next_pruned, (hipStream_t)P.side));
+        if (rc != FG_OK) {      // nobody is told to wait for what did get there
+            FG_HIP(hipStreamWaitEvent((hipStream_t)C.stream, (hipEvent_t)P.ev_next_pruned, 0));
+            return rc;
+        }
+        *due_from = 1;
         *next_pruned = 1;
         return FG_OK;
     }
@@ -355,6 +362,7 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
     const bool beside = do_update && call->overlap && !P.backward && !may_ride;
     if (may_ride && call->overlap) I.next = next;
     I.next_pruned = &call->next_pruned;
+    I.rows_due = &call->selected;
     if (beside) {      // the update's selection and the next top-down pass on the second stream
         if (!call->pruned_ahead) {
             FG_HIP(hipEventRecord((hipEvent_t)P.ev_pruned, main));
@@ -399,12 +407,16 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
         }
     }
     FG_TRY(I.forward(*batch, once, fetch, n_fetch, &ride, may_ride ? &selection : nullptr, &rode, &due_from));
-    if (rode && due_from < selection.n_layers) {
-        fg_row_copy_batch copies;
-        Iter::due_copies(selection, due_from, &copies);
-        FG_TRY(fg_launch_row_copies(copies, main));
+    if (rode) {
+        if (due_from < selection.n_layers) {
+            fg_row_copy_batch copies;
+            Iter::due_copies(selection, due_from, &copies);
+            FG_TRY(fg_launch_row_copies(copies, main));
+        }
+        fg_update_committed(ride);
+        call->selected = 0;
+        return FG_OK;
     }
-    if (rode) return FG_OK;
     // A training iteration ends with its weight gradients and the cache update beside each other: in the same two launches where a group of
     // workgroups decides the update, else on two streams, the longer of the two on this one, where it does not wait for an event to be
     // seen by the other.

@@ -484,7 +484,9 @@ struct fg_update_call {
 // (512 threads, 2 quads each), and the row copies part of the one behind it; else B says nothing and fg_cache_update_all is to be called.
 fg_status_t fg_update_describe(const char* who, const fg_update_call& call, UpdBatch* B, bool* rides);
 void fg_update_row_copies(const UpdBatch& B, fg_row_copy_batch* copies);
-void fg_update_queued(const fg_update_call& call);      // both are queued: the cache's state moves on
+void fg_update_queued(const fg_update_call& call);      // both are queued: the cache's state moves on ...
+void fg_update_selected(const fg_update_call& call);    // ... or in two steps: the group is queued (until the other step the next update is refused)
+void fg_update_committed(const fg_update_call& call);   // ... and the row copies
 // fg_backward_weights_all with an update that rides along (NULL: none)
 fg_status_t fg_backward_weights_with(fg_dtype_t compute_dtype, int32_t n_layers, const fg_weight_grad_layer_t* layers, void* ws_dev, size_t ws_bytes,
                                      const UpdBatch* update, void* stream);

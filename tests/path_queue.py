@@ -74,27 +74,30 @@ class Queue:
         return e.value
 
     def _batch(self, b, L):
-        """b: dict(n=[...], and optionally own_rows_from_table, fault=a layer without node ids)"""
+        """b: dict(n=[...], and optionally own_rows_from_table, no_ids / no_weights: a layer that lacks them)"""
         x = self.B.PathBatch()
         x.labels_dev, x.col_ids1_dev, x.own_rows_from_table = self._mem(), self._mem(), b.get("own_rows_from_table", 1)
         for l, n in enumerate(b["n"]):
             y = x.layer[l]
             y.n, y.nnz = n, b["nnz"][l] if "nnz" in b else (b["n"][l - 1] if l else 0)
             for name in ("ids_dev", "start_dev", "end_dev", "col_dev", "gnorm_dev", "t_start_dev", "t_end_dev", "t_row_dev"):
-                setattr(y, name, None if name == "ids_dev" and l == b.get("fault") else self._mem())
+                setattr(y, name, None if name == "ids_dev" and l == b.get("no_ids") else self._mem())
         return x
 
-    def run(self, it, batch, next=None, update=1, overlap=1, commit=False):
-        """One call, with what the previous one left. commit: the caller commits what is due first. -> [0 or the error, selected, next_pruned, begun, lines]"""
+    def run(self, it, batch, next=None, update=1, overlap=1, commit=False, forget=False):
+        """One call, with what the previous one left. commit: the caller commits what is due first; forget: it drops that.
+        -> [0 or the error, selected, next_pruned, begun, lines]"""
         B, L = self.B, self.P.n_layers
         if commit and self.due is not None:
             assert B._lib.fg_cache_update_commit(self.cache, self.due, L - 1, self.specs, self.P.ws_update + self.due % 2 * self.P.ws_update_stride,
                                                  self.P.ws_update_bytes, MAIN) == 0
             self.due = None
+        if forget:
+            self.due = self.ahead = None
         call = B.PathCall()
         call.iter, call.stream, call.cache, call.feat = it, MAIN, self.cache, self.feat
         for l in range(1, L + 1):
-            call.w[l], _, call.bias[l] = self.weights[l]
+            call.w[l], _, call.bias[l] = self.weights[l] if l != batch.get("no_weights") else (None, None, None)
         if self.P.compute_dtype == B.FG_BF16:
             for l in range(1, L + 1):
                 call.wt[l] = self.weights[l][1]

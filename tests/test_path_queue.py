@@ -76,3 +76,33 @@ def test_no_launch_asks_for_more_lds_than_a_compute_unit_has(tmp_path_factory, f
                 assert rc == 0, rc
                 for name, lds in ((x[2], int(x[3])) for x in lines if x[0] == "launch"):
                     assert lds <= 160 * 1024, f"{name} asks for {lds} bytes, rows of {d} {feat}"
+
+
+# layer 1 as one launch, and the loader with the selection in it (on one stream, where nothing is pruned ahead)
+@pytest.mark.parametrize("n1,overlap,at", [(25_000, 1, "no_ids"), (25_000, 1, "no_weights"), (25_000, 0, "no_weights"), (12_000, 0, "no_weights")])
+def test_a_step_that_fails_behind_its_selection_leaves_its_rows_due(tmp_path_factory, n1, overlap, at):
+    """The next mini-batch, or an upper layer, is refused when the selection has gone with the loader: the index names slots whose rows are not
+    there, so the next update is refused until they are, nothing is promised, and the caller's stream is behind the second one."""
+    good = dict(n=sizes(n1))
+    now, later = (dict(good, no_weights=3), good) if at == "no_weights" else (good, dict(good, no_ids=2))
+    calls = record(tmp_path_factory.getbasetemp(), [MODEL, ["run", dict(it=0, batch=good, next=now, overlap=overlap)], ["run", dict(it=1, batch=now, next=later, overlap=overlap)],
+                                                    ["run", dict(it=2, batch=good, overlap=overlap, forget=True)]])[1:]
+    assert [c[0] for c in calls[:1]] == [0] and calls[0][1] == 0
+    rc, selected, next_pruned, begun, lines = calls[1]
+    assert str(rc)[:2] in ("1:", "2:") and selected == 1 and begun == 1
+    launches = behind(calls)
+    copies = [x for x in launches if x[0] == 1 and "copy_rows" in x[2]]
+    assert len(copies) == (at == "no_weights" and overlap) and next_pruned == len(copies)
+    if at == "no_ids":
+        waits = [x for x in lines if x[0] == "wait"]
+        assert waits[-1][1] == str(MAIN) and ["record", str(SIDE), waits[-1][2]] in lines
+    assert str(calls[2][0]).startswith("4:") and "fg_cache_update_commit" in calls[2][0]
+
+
+@pytest.mark.parametrize("n1,overlap", [(25_000, 1), (25_000, 0), (12_000, 0)])
+def test_rows_of_a_step_that_fails_can_be_committed(tmp_path_factory, n1, overlap):
+    good = dict(n=sizes(n1))
+    calls = record(tmp_path_factory.getbasetemp(), [MODEL, ["run", dict(it=0, batch=dict(good, no_weights=3), overlap=overlap)],
+                                                    ["run", dict(it=1, batch=good, overlap=overlap, commit=True)], ["run", dict(it=2, batch=good, overlap=overlap)]])[1:]
+    assert str(calls[0][0]).startswith("1:") and calls[0][1] == 1
+    assert [c[:2] for c in calls[1:]] == [[0, 0], [0, 0]]
