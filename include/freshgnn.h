@@ -298,8 +298,10 @@ fg_status_t fg_gather_aggregate_ids(const int32_t* row_start_dev, const int32_t*
 /*
  * fg_gather_aggregate_ids (no copy of the own rows) and the dense update of the same layer behind it (fg_linear_ids) in one call, fp32. A layer
  * for which fg_one_launch_load says so (at least 16384 rows, d_in <= 128, d_out <= 256, at most 15 neighbours a row on average) runs as one
- * launch: the rows of the next block are read while a block is multiplied. Other shapes run as the two launches, with the means in agg_ws_dev
- * between them ([max_rows, agg_stride]; what it holds afterwards is not specified). The same results as the two calls up to the rounding of the
+ * launch: the rows of the next block are read while a block is multiplied. That is where it can: where it pays depends on the widths and on how
+ * even the rows are (neighbours beyond a row's 15th, or its 7th where there are at most 7 on average and d_in > 64, are read one by one).
+ * Other shapes run as the two launches, with the means in agg_ws_dev between them ([max_rows, agg_stride]; what it holds afterwards is not
+ * specified). The same results as the two calls up to the rounding of the
  * products' sums.
  */
 int32_t fg_one_launch_load(int64_t nnz, int64_t max_rows, int32_t d_in, int32_t d_out);
@@ -833,7 +835,9 @@ typedef struct fg_path_layer {
 typedef struct fg_path_batch {
     const int32_t *labels_dev, *col_ids1_dev;
     int64_t reads_rows_once;      /* fused_input: the input rows are gathered into h[0] once each, layer 1 aggregates from there */
-    int64_t own_rows_from_table;  /* fused_input, col_ids1_dev: layer 1's dense update reads the own rows by fg_linear_ids */
+    int64_t own_rows_from_table;  /* fused_input, col_ids1_dev: layer 1's dense update reads the own rows by fg_linear_ids. 2 or more: besides, no row of
+                                     block 1 has more than so many neighbours (what fg_gather_aggregate_linear_ids is chosen by; a row that has
+                                     more all the same only takes longer) */
     fg_path_layer_t layer[FG_PATH_MAX_LAYERS + 1];
 } fg_path_batch_t;
 typedef struct fg_path_call {

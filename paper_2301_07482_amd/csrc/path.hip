@@ -143,12 +143,24 @@ struct Iter {
     }
 
     // Whether the loader and the dense update of layer 1 are one call: where nobody reads the means and the nodes' own rows later. (A training
-    // iteration does; with both written from the one launch it took what the two take, 122 us against 121.) Its workgroups fill the chip, so that
-    // work on a second stream waits for it, and the layers above have to be long enough to hide that: from 24 Ki positions on. Steps of positions x
-    // columns, two launches / one, us: 20.5 k x 72 77 / 84.5, 24.6 k x 96 83 / 81, x 256 103 / 102, 31 k x 256 119 / 109, 45 k x 96 125 / 117, 54 k x 176 158 / 145.
+    // iteration does; with both written from the one launch it took what the two take, 122 us against 121.)
+    // - Every row's neighbours have to have a slot (15 of them, 7 of rows of more than 64 values where there are no more than 7 on average): one by one behind
+    //   the slots they cost more than the launch saves. The layer by itself, 54 k rows x (128 + 128) x 256, two launches / one, us: 15 each 127 / 114,
+    //   8 or 20 122 / 140, 4 or 25 126 / 167, 7 each 90 / 76, 3 or 10 87 / 105; one row of 500 in 500 167 / 357.
+    // - Rows of more than 32 values: half of the operand is padding below that. Step of 71 k positions x 32 x 64, 6 neighbours, 82 / 99; 80 k x 64 96 / 95.
+    // - Beside a second stream from 24 Ki positions on: its workgroups fill the chip, so that work there waits for it, and the layers above have to be long
+    //   enough to hide that. Steps of positions x columns, us: 20.5 k x 72 77 / 84.5, 24.6 k x 96 83 / 81, x 256 103 / 102, 31 k x 256 119 / 109, 45 k x 96 125 / 117.
+    //   Of 4041 steps of 15 k to 110 k positions, 36 to 128 x 64 to 256 values and 5 to 15 neighbours one is the faster one by 10 us on average, and by more
+    //   than 5 % the slower one in 140.
+    // - On one stream the selection rides with either loader, and what is left is what the layer saves: not where 64 columns or fewer leave
+    //   most of its wavefronts without a product, nor for rows of at most 64 values with most positions admitted (their copies are a launch behind it). Of 2374
+    //   steps it is faster by 3.8 us on average, with the two exceptions by 5.2, and by more than 5 % the slower one in 16.
     bool loads_and_multiplies(const fg_path_batch_t& b, int l) const {
-        return l == 1 && (!C.overlap || b.layer[1].n >= 24576) && P.fused_input && !b.reads_rows_once && b.own_rows_from_table && b.col_ids1_dev && h_code(0) == FG_F32 && h_code(1) == FG_F32 &&
-               P.compute_dtype == FG_F32 && fg_one_launch_load(b.layer[1].nnz, b.layer[1].n, P.dims[0], P.dims[1]);
+        const int64_t n = b.layer[1].n, nnz = b.layer[1].nnz, most = b.own_rows_from_table, slots = P.dims[0] > 64 && nnz <= 7 * n ? 7 : 15;
+        if (l != 1 || !P.fused_input || b.reads_rows_once || !b.col_ids1_dev || most < 2 || most > slots) return false;
+        if (h_code(0) != FG_F32 || h_code(1) != FG_F32 || P.compute_dtype != FG_F32 || P.dims[0] <= 32) return false;
+        if (C.overlap ? n < 24576 : P.dims[1] <= 64 || (P.dims[0] <= 64 && C.p_grad > 0.5f)) return false;
+        return fg_one_launch_load(nnz, n, P.dims[0], P.dims[1]) != 0;
     }
 
     // Whether the selection of a step's update goes with the loader's launch.

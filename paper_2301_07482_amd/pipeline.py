@@ -280,6 +280,7 @@ class HotPath:
         self.L = L = len(fanouts)
         self.dims = list(dims)
         self.num_nodes = num_nodes
+        self.most_neighbours = max(2, fanouts[0])      # of a row of block 1, as fg_path_batch_t takes it
         self.p_grad = float(p_grad)
         self.feat = features
         self.feat_code = DTYPE_CODE[feat_dtype]
@@ -586,7 +587,7 @@ class HotPath:
         """A mini-batch as fg_path_run takes it; norms: the cache update's come with it."""
         L = self.L
         bw = self.backward
-        v = [_addr(bt.labels) if bw else 0, _addr(getattr(bt, "col_ids1", None)), self.reads_rows_once(bt), self.own_rows_from_table(bt)]
+        v = [_addr(bt.labels) if bw else 0, _addr(getattr(bt, "col_ids1", None)), self.reads_rows_once(bt), self.own_rows_from_table(bt) and self.most_neighbours]
         for l, n, nnz, *arrays in zip(range(L + 1), bt.n, bt.nnz, bt.ids, bt.start, bt.end, bt.col, bt.n_dev):
             v += n, nnz
             if bw and l > 1:
@@ -933,10 +934,13 @@ class HotPath:
                 and getattr(bt, "col_ids1", None) is not None and not self.one_launch(1, bt.n[1]))
 
     def loads_and_multiplies(self, bt):
-        """Whether the loader and the dense update of layer 1 of this mini-batch are one call and one launch of it (with a second stream, whose work
-        waits for a launch that fills the chip, from 24 Ki positions on)."""
-        return bool(self.own_rows_from_table(bt) and (not self.overlap_update or bt.n[1] >= 24576) and self.h_code[1] == B.FG_F32
-                    and B.one_launch_load(bt.nnz[1], bt.n[1], self.dims[0], self.dims[1]))
+        """Whether the loader and the dense update of layer 1 of this mini-batch are one call and one launch of it (path.hip has the reasons)."""
+        n, nnz, d_in, d_out = bt.n[1], bt.nnz[1], self.dims[0], self.dims[1]
+        if not self.own_rows_from_table(bt) or self.h_code[1] != B.FG_F32 or d_in <= 32 or self.most_neighbours > (7 if d_in > 64 and nnz <= 7 * n else 15):
+            return False
+        if n < 24576 if self.overlap_update else d_out <= 64 or (d_in <= 64 and self.p_grad > 0.5):
+            return False
+        return B.one_launch_load(nnz, n, d_in, d_out)
 
     def reads_rows_once(self, bt):
         """Whether the loader of this mini-batch reads every surviving input row over the host link once, into H[0], and

@@ -76,7 +76,7 @@ class Queue:
     def _batch(self, b, L):
         """b: dict(n=[...], and optionally own_rows_from_table, no_ids / no_weights: a layer that lacks them)"""
         x = self.B.PathBatch()
-        x.labels_dev, x.col_ids1_dev, x.own_rows_from_table = self._mem(), self._mem(), b.get("own_rows_from_table", 1)
+        x.labels_dev, x.col_ids1_dev, x.own_rows_from_table = self._mem(), self._mem(), b.get("own_rows_from_table", 5)
         for l, n in enumerate(b["n"]):
             y = x.layer[l]
             y.n, y.nnz = n, b["nnz"][l] if "nnz" in b else (b["n"][l - 1] if l else 0)
@@ -84,7 +84,7 @@ class Queue:
                 setattr(y, name, None if name == "ids_dev" and l == b.get("no_ids") else self._mem())
         return x
 
-    def run(self, it, batch, next=None, update=1, overlap=1, commit=False, forget=False):
+    def run(self, it, batch, next=None, update=1, overlap=1, commit=False, forget=False, p_grad=0.3):
         """One call, with what the previous one left. commit: the caller commits what is due first; forget: it drops that.
         -> [0 or the error, selected, next_pruned, begun, lines]"""
         B, L = self.B, self.P.n_layers
@@ -101,7 +101,7 @@ class Queue:
         if self.P.compute_dtype == B.FG_BF16:
             for l in range(1, L + 1):
                 call.wt[l] = self.weights[l][1]
-        call.p_grad, call.update, call.overlap, call.fetch_with_loader = 0.3, update, overlap, 1
+        call.p_grad, call.update, call.overlap, call.fetch_with_loader = p_grad, update, overlap, 1
         call.promised, call.pruned_ahead = self.ahead is not None, self.ahead == [it, batch]
         call.specs = self.specs
         if self.due is not None:

@@ -2449,7 +2449,8 @@ def test_steps_of_both_kinds_queued_back_to_back_match_one_at_a_time(env, order)
     ("one piece a row, two chunks of a mixed step", dict(fused_input=True, overlap_update=False)),
     ("two pieces a row, two chunks of a step", dict(fused_input=True, overlap_update=False, fuse_small_layers=True)),
     ("many chunks of a step", dict(fused_input=True, overlap_update=False, fuse_small_layers=True)),
-    ("many chunks of a step", dict(fused_input=True, fuse_small_layers=True)),      # (with node ids as columns: in the launch that multiplies too)
+    ("88 columns, many chunks of a step", dict(fused_input=True, overlap_update=False, fuse_small_layers=True)),
+    ("many chunks of a step", dict(fused_input=True, fuse_small_layers=True)),      # (these two: with node ids as columns: in the launch that multiplies too)
 ])
 @pytest.mark.parametrize("col_ids", [True, False])
 def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, kwargs, col_ids):
@@ -2466,6 +2467,8 @@ def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, k
     if workload.endswith(" step"):
         w = dataclasses.replace(w, num_nodes=40_000, num_edges=800_000, feat_dim=52, hidden=64, fanouts=(3, 2, 8), batch=301,
                                 cache_capacity=5_000)
+    if workload.startswith("88 columns"):
+        workload, w = workload[12:], dataclasses.replace(w, hidden=88)
     if workload == "many chunks of a step":
         w = dataclasses.replace(w, num_nodes=90_000, batch=4501)
     if workload.endswith("mixed step"):

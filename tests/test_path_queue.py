@@ -5,7 +5,7 @@ import pytest
 
 from tests.path_queue import MAIN, SIDE, record
 
-DIMS = [32, 64, 64, 64]
+DIMS = [64, 96, 96, 96]
 
 
 def sizes(n1):
@@ -69,7 +69,7 @@ def test_no_launch_asks_for_more_lds_than_a_compute_unit_has(tmp_path_factory, f
         for train in (0, 1):
             script = [["model", dict(dims=[d, 64, 64, 64], n_max=[80_000, 40_000, 8_000, 1_024], feat=feat, compute=compute, fuse_small_layers=int(feat == "F32" and not train),
                                 backward=train, weight_grads=train)]]
-            script += [["run", dict(it=i, batch=dict(n=sizes(n1), own_rows_from_table=int(feat == "F32" and not train)), overlap=overlap)]
+            script += [["run", dict(it=i, batch=dict(n=sizes(n1), own_rows_from_table=5 * int(feat == "F32" and not train)), overlap=overlap)]
                        for i, (n1, overlap) in enumerate((n1, o) for n1 in (5_000, 12_000, 25_000) for o in (0, 1))]
             _, *calls = record(tmp_path_factory.getbasetemp(), script)
             for rc, *_, lines in calls:
@@ -106,3 +106,25 @@ def test_rows_of_a_step_that_fails_can_be_committed(tmp_path_factory, n1, overla
                                                     ["run", dict(it=1, batch=good, overlap=overlap, commit=True)], ["run", dict(it=2, batch=good, overlap=overlap)]])[1:]
     assert str(calls[0][0]).startswith("1:") and calls[0][1] == 1
     assert [c[:2] for c in calls[1:]] == [[0, 0], [0, 0]]
+
+
+@pytest.mark.parametrize("one,d_in,d_out,most,nnz,n,overlap,p_grad", [
+    (1, 128, 256, 15, 13, 25_000, 1, 0.3), (0, 128, 256, 16, 13, 25_000, 1, 0.3), (0, 128, 256, 1, 1, 25_000, 1, 0.3),      # what the rows have at most
+    (1, 128, 256, 8, 8, 25_000, 1, 0.3), (0, 128, 256, 8, 7, 25_000, 1, 0.3), (1, 128, 256, 7, 7, 25_000, 1, 0.3),          # places of a row
+    (1, 64, 128, 15, 7, 25_000, 1, 0.3), (0, 68, 128, 15, 7, 25_000, 1, 0.3),
+    (1, 36, 64, 15, 13, 25_000, 1, 0.7), (0, 32, 64, 15, 13, 25_000, 1, 0.3),                                               # narrow rows
+    (1, 128, 256, 15, 13, 24_576, 1, 0.3), (0, 128, 256, 15, 13, 24_575, 1, 0.3),                                           # two streams
+    (1, 128, 256, 15, 13, 16_384, 0, 0.7), (0, 128, 256, 15, 13, 16_383, 0, 0.3), (0, 128, 64, 15, 13, 20_000, 0, 0.3),     # one
+    (1, 64, 68, 15, 13, 20_000, 0, 0.5), (0, 64, 68, 15, 13, 20_000, 0, 0.6), (1, 68, 68, 15, 13, 20_000, 0, 0.6)])
+def test_which_steps_load_and_multiply_in_one_launch(tmp_path_factory, one, d_in, d_out, most, nnz, n, overlap, p_grad):
+    """Around every line of the rule (`HotPath.loads_and_multiplies` is the same one)."""
+    from types import SimpleNamespace
+    from paper_2301_07482_amd import binding as B, pipeline
+    b = dict(n=[n, n, 1_000], nnz=[0, nnz * n, 5_000], own_rows_from_table=most)
+    _, (rc, *_, lines) = record(tmp_path_factory.getbasetemp(), [["model", dict(dims=[d_in, d_out, 64], n_max=[1 << 19, 40_000, 8_000])],
+                                                                ["run", dict(it=0, batch=b, overlap=overlap, p_grad=p_grad)]])
+    kernels = [x[2] for x in lines if x[0] == "launch"]
+    assert rc == 0 and any("load_linear" in k for k in kernels) == bool(one) != any("loader_fetch" in k for k in kernels)
+    hp = SimpleNamespace(own_rows_from_table=lambda bt: True, h_code=[B.FG_F32] * 3, dims=[d_in, d_out, 64], most_neighbours=max(most, 2) if most > 1 else 99,
+                         overlap_update=bool(overlap), p_grad=p_grad)
+    assert pipeline.HotPath.loads_and_multiplies(hp, SimpleNamespace(n=b["n"], nnz=b["nnz"])) == bool(one)
