@@ -18,6 +18,29 @@ def test_more_than_one_gpu_is_refused_with_a_message():
     assert p.returncode == 2 and "one GPU" in p.stderr
 
 
+@pytest.mark.parametrize("first_timed", [1, 2, 3, 21])
+def test_untimed_steps_are_of_every_kind_that_is_timed(first_timed):
+    """What the timed region launches has been launched before: plain steps, bracketed ones, and bracketed ones that hold the second stream."""
+    import bench
+
+    class Path:
+        calls = []
+
+        def holds_second_stream(self):
+            return True
+
+        def run(self, bt, it, next_bt=None, timer=None, hold_second_stream=False):
+            self.calls.append((bt, it, next_bt, timer is not None, hold_second_stream))
+
+    hp = Path()
+    hp.calls = []
+    bench.untimed_steps(hp, list(range(100, 130)), first_timed, True, ("linear[1]",))
+    assert [c[:2] for c in hp.calls] == [(100 + it, it) for it in range(first_timed)]
+    assert [c[2] for c in hp.calls] == [101 + it for it in range(first_timed - 1)] + [None]
+    assert [c[3:] for c in hp.calls][-3:] == [(True, True), (True, False), (False, False)][-first_timed:]
+    assert not any(c[3] for c in hp.calls[:-3])
+
+
 @pytest.mark.gpu
 def test_one_json_line_with_the_agreed_fields():
     p = subprocess.run([sys.executable, BENCH, "--workload", "tiny", "--steps", "6", "--warmup", "4", "--sample-workers", "2"],
