@@ -258,11 +258,15 @@ def main():
     replay_from_buffer = []
     replay = replay_batches if args.device_sampler else [make_batch(*sampled[total + k]) for k in range(extra)]
     overlapped = hp.overlap_update
+    one_launch_1 = hp.loads_and_multiplies(batches[first_timed])      # what the steps that are not bracketed launch for layer 1
+    one_events = []
     hp.overlap_update = False          # every call on the one stream here, so that each has a time of its own
     for k in range(extra):
         step_events = {}
         hp.run(replay[k], first_timed + args.steps + k, timer=timer_for(step_events))
         ev2.append(step_events)
+        if one_launch_1:
+            one_events.append(time_layer_1(hp, replay[k]))
         if hp.feature_side and args.no_fuse:   # the input list of this step, before the next one overwrites it
             ranks = torch.as_tensor(hp.feature_ranks(replay[k].ids[0], replay[k].n[0])[0], device="cuda")
             pos = hp.normal_pos[0][:int(hp.counts[0][2].item())].long()
@@ -336,14 +340,14 @@ def main():
         linear_roof = dict(bound="mfma", kernel="linear_bf16_kernel (fg_linear, layer 1, bf16 MFMA, fp32 accumulation)",
                            achieved=lin_tf, peak=BF16_MFMA_PEAK_TFLOPS, unit="TFLOP/s", frac=lin_tf / BF16_MFMA_PEAK_TFLOPS,
                            traffic=None, flops_per_launch=lin_flops[1], ms_per_launch=lin1_ms)
-    elif (hp.dims[0] // 2 if args.model == "gcn" else hp.dims[0]) % 32 == 0:
-        linear_roof = dict(bound="mfma", kernel="linear_f32x3_panel_kernel<2> (fg_linear, layer 1: fp32 products from 3-way bf16 "
+    elif (hp.dims[0] // 2 if args.model == "gcn" else hp.dims[0]) <= 384:      # what of W a workgroup holds, split, fits its LDS
+        linear_roof = dict(bound="mfma", kernel="linear_f32x3_panel_kernel (fg_linear, layer 1: fp32 products from 3-way bf16 "
                                                 "splits on the bf16 matrix cores)",
                            achieved=lin_tf, peak=FP32_MFMA_PEAK_TFLOPS, unit="TFLOP/s", frac=lin_tf / FP32_MFMA_PEAK_TFLOPS,
                            traffic=None, flops_per_launch=lin_flops[1], ms_per_launch=lin1_ms,
                            executed=dict(tflops=6 * lin_tf, peak=BF16_MFMA_PEAK_TFLOPS, frac=6 * lin_tf / BF16_MFMA_PEAK_TFLOPS,
                                          note="bf16 MFMA flops issued (6 partial products per fp32 product)"))
-    else:  # input width not a multiple of 32: the LDS-tiled fp32-MFMA kernel
+    else:  # wider: the LDS-tiled fp32-MFMA kernel
         linear_roof = dict(bound="mfma", kernel="linear_f32_kernel (fg_linear, layer 1, fp32 MFMA)",
                            achieved=lin_tf, peak=FP32_MFMA_PEAK_TFLOPS, unit="TFLOP/s", frac=lin_tf / FP32_MFMA_PEAK_TFLOPS,
                            traffic=None, flops_per_launch=lin_flops[1], ms_per_launch=lin1_ms)
@@ -358,6 +362,21 @@ def main():
         loader_roof["ms_per_launch_overlapped"] = timed_ovl_ms[LOADER]
         linear_roof["ms_per_launch_overlapped"] = timed_ovl_ms.get("linear[1]")
     roofline, roofline_2 = (loader_roof, linear_roof) if gather_ms >= lin1_ms else (linear_roof, loader_roof)
+    roofline_3 = None
+    if one_launch_1:      # the launch that takes both of these in every step that is not bracketed comes first
+        one_ms = float(np.mean([a.elapsed_time(b) for a, b in one_events]))
+        one_bytes, one_flops = (float(np.mean(x)) for x in zip(*(one_launch_work(w, replay[k], counts_log[(first_timed + args.steps + k) % hp.ring])
+                                                                 for k in range(extra))))
+        one_tf = one_flops / (one_ms * 1e-3) / 1e12
+        one_roof = dict(bound="hbm", kernel="load_linear_kernel (fg_gather_aggregate_linear_ids: loader, mean and dense update of layer 1 in one launch)",
+                        achieved=one_bytes / (one_ms * 1e-3) / 1e9, peak=HBM_PEAK_GBS, unit="GB/s", frac=one_bytes / (one_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
+                        traffic=None, bytes_per_launch=one_bytes, ms_per_launch=one_ms, flops_per_launch=one_flops,
+                        executed=dict(tflops=6 * one_tf, peak=BF16_MFMA_PEAK_TFLOPS, frac=6 * one_tf / BF16_MFMA_PEAK_TFLOPS,
+                                      note="bf16 MFMA flops issued (6 partial products per fp32 product)"),
+                        note="launched once more behind each step of the breakdown pass, without the selection and the cached rows that go with it inside a step")
+        for r in (loader_roof, linear_roof):
+            r["note"] = "a launch of the bracketed steps (and of training); the other steps take loader and dense update in one, see `roofline`"
+        roofline, roofline_2, roofline_3 = one_roof, roofline, roofline_2
 
     hits = {l: float(np.mean([c[l][1] for c in counts_all])) for l in range(1, L)}
     n0_all = float(np.mean([batches[it].n[0] for it in steps_it]))
@@ -432,6 +451,18 @@ def main():
     if not args.no_cpu_baseline:
         cpu_baseline = time_oracle(w, sampled, weights)
 
+    # where the update's selection runs in the steps that are not bracketed (fg_path_run's rules)
+    chunks = sum(-(-batches[first_timed].n[l] // 4096) for l in range(1, L))
+    if args.backward or args.no_cache or args.per_layer_update or hp.feature_side or not hp.runs_in_one_call():
+        update_selection = "second stream, beside the layers" if hp.holds_second_stream() else "after the layers"
+        if args.backward and args.weight_grads and hp.runs_in_one_call() and chunks <= 64:
+            update_selection = "inside the weight gradients' launch"
+    elif one_launch_1 and chunks <= 32:
+        update_selection = "inside the launch that loads and multiplies"
+    elif hp.overlap_update:
+        update_selection = "second stream, beside the layers"
+    else:
+        update_selection = "inside the loader's launch, where that takes it, else after the layers"
     hp.close()
     policy_paper = None
     if policy_w is not None:
@@ -453,14 +484,15 @@ def main():
                    "top_down": "of the next mini-batch on the second stream, beside this step's layers" if (
                        not args.no_lookahead and hp.overlap_update and not args.backward and not args.no_cache and not args.per_layer_update
                        and not hp.feature_side and hp.one_launch_top_down) else "at the start of the step",
-                   "update_selection": "second stream, beside the layers" if (hp.overlap_update and not args.backward and not args.no_cache
-                                                                              and not args.per_layer_update and not hp.feature_side) else "after the layers",
+                   "update_selection": update_selection,
                    "block1_columns": "node ids" if ids_cols else "positions",
-                   "own_rows_layer1": "read from the table by the dense update (fg_linear_ids)" if own_by_linear
+                   "own_rows_layer1": "read from the table by the launch that loads and multiplies" if one_launch_1
+                   else "read from the table by the dense update (fg_linear_ids)" if own_by_linear
                    else "copied out by the loader", "seed": w.seed},
         "prefill_steps": prefill,
         "roofline": roofline,
         "roofline_2": roofline_2,
+        "roofline_3": roofline_3,
         "path_a1_a6": path_a1_a6,
         "policy_paper": policy_paper,
         "cpu_baseline": cpu_baseline,
@@ -517,6 +549,27 @@ def alone_step(k, steps, bracket_every):
     of the steady state); step 0 where the region is shorter than that."""
     first = bracket_every // 2 if steps > bracket_every // 2 else 0
     return k >= first and (k - first) % bracket_every == 0
+
+
+def time_layer_1(hp, bt):
+    """Events around the launch that loads and multiplies, launched once more for the mini-batch that `hp.run` has just taken (same rows, same results)."""
+    import torch
+    from paper_2301_07482_amd import binding as B
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    d_in, d_out = hp.dims[0], hp.dims[1]
+    e0.record()
+    B.fg_gather_aggregate_linear_ids(bt.start[1], bt.end[1], bt.col_ids1, bt.nnz[1], bt.n[1], hp.normal_pos[1], hp._cnt(1, 2), bt.n[1], bt.ids[1], hp.feat,
+                                     hp.num_nodes, d_in * 4, d_in, d_out, hp.W[1], hp.bias[1], 1 if hp.L > 1 else 0, hp.AGG_l[1], d_in * 4, hp.H[1],
+                                     bt.n[1], d_out * 4, None, None, torch.cuda.current_stream().cuda_stream)
+    e1.record()
+    return e0, e1
+
+
+def one_launch_work(w, bt, counts):
+    """Algorithmic bytes and flops of that launch: per edge of a normal row a column and a table row; per normal row its position, range, id, table row
+    and output row; the weights once."""
+    edges, rows = float((bt.end[1] - bt.start[1]).sum().item()), float(counts[1][2])
+    return (edges * 4 * (1 + w.feat_dim) + rows * 4 * (4 + w.feat_dim + w.hidden) + 8 * w.feat_dim * w.hidden, 4.0 * rows * w.feat_dim * w.hidden)
 
 
 def untimed_steps(hp, batches, first_timed, lookahead, bracketed):
