@@ -160,7 +160,7 @@ struct Iter {
         if (l != 1 || !P.fused_input || b.reads_rows_once || !b.col_ids1_dev || most < 2 || most > slots) return false;
         if (h_code(0) != FG_F32 || h_code(1) != FG_F32 || P.compute_dtype != FG_F32 || P.dims[0] <= 32) return false;
         if (C.overlap ? n < 24576 : P.dims[1] <= 64 || (P.dims[0] <= 64 && C.p_grad > 0.5f)) return false;
-        return fg_one_launch_load(nnz, n, P.dims[0], P.dims[1]) != 0;
+        return fg_tuning(FG_TUNE_LINEAR_TILE) == 0 && fg_one_launch_load(nnz, n, P.dims[0], P.dims[1]) != 0;
     }
 
     // Whether the selection of a step's update goes with the loader's launch.

@@ -68,6 +68,9 @@ class Queue:
         self.due = self.ahead = None      # (iteration) whose rows are due; the mini-batch that has been pruned ahead
         return self._log()
 
+    def tune(self, key, value):
+        self.B.fg_set_tuning(key, value)
+
     def _event(self):
         e = C.c_void_p()
         assert self.B._lib.fg_event_create(C.byref(e)) == 0

@@ -128,3 +128,13 @@ def test_which_steps_load_and_multiply_in_one_launch(tmp_path_factory, one, d_in
     hp = SimpleNamespace(own_rows_from_table=lambda bt: True, h_code=[B.FG_F32] * 3, dims=[d_in, d_out, 64], most_neighbours=max(most, 2) if most > 1 else 99,
                          overlap_update=bool(overlap), p_grad=p_grad)
     assert pipeline.HotPath.loads_and_multiplies(hp, SimpleNamespace(n=b["n"], nnz=b["nnz"])) == bool(one)
+
+
+def test_a_chosen_dense_kernel_leaves_the_selection_where_it_was(tmp_path_factory):
+    """With a dense kernel chosen by `linear_tile` layer 1 is two launches; the selection and the next top-down pass are then on the second stream, as
+    in a step that is two launches by its sizes."""
+    calls = record(tmp_path_factory.getbasetemp(), [["model", dict(MODEL[1], fuse_small_layers=0)], ["tune", dict(key="linear_tile", value=32)], ["run", dict(it=0, batch=RIDES, next=OWN)],
+                                                    ["tune", dict(key="linear_tile", value=0)]])
+    rc, selected, next_pruned, _, lines = calls[2]
+    assert rc == 0 and selected == 1 and next_pruned == 1
+    assert {x[1] for x in lines if x[0] == "launch" and "update_digit" in x[2]} == {str(SIDE)}
