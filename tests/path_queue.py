@@ -92,6 +92,7 @@ class Queue:
         -> [0 or the error, selected, next_pruned, begun, lines]"""
         B, L = self.B, self.P.n_layers
         if commit and self.due is not None:
+            assert B._lib.fg_stream_wait_event(MAIN, self.P.ev_selected) == 0
             assert B._lib.fg_cache_update_commit(self.cache, self.due, L - 1, self.specs, self.P.ws_update + self.due % 2 * self.P.ws_update_stride,
                                                  self.P.ws_update_bytes, MAIN) == 0
             self.due = None

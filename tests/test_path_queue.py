@@ -1,5 +1,6 @@
 """The order in which fg_path_run queues an iteration on its two streams, recorded without a device (tests/path_queue.py)."""
 import itertools
+import random
 
 import pytest
 
@@ -35,24 +36,33 @@ def behind(calls):
     return out
 
 
-@pytest.mark.parametrize("kinds", list(itertools.product("ro", repeat=6)) + [tuple("rxoror"), tuple("orxoor"), tuple("roorooroo")])
+def orders():
+    r = random.Random(7)
+    return ["".join(k) for k in itertools.product("ro", repeat=6)] + ["rxoror", "orxoor", "roorooroo"] + ["".join(r.choices("rroooxnc", k=12)) for _ in range(40)]
+
+
+@pytest.mark.parametrize("kinds", orders())
 def test_steps_of_both_kinds_in_any_order_follow_each_other(tmp_path_factory, kinds):
     """Steps whose selection goes with the loader (r) and steps that put it on the second stream (o; x: whose announced successor is not the one that
-    comes), queued back to back: whatever a call queues waits for everything that the call before the last one queued, and for the copy of the
-    rows that it left to the last one. (Sets of lists and halves of the update's workspace are used again then.)"""
+    comes, n: without an update, c: in front of which the caller has copied the rows that were due), queued back to back: whatever a call queues waits
+    for everything that the call before the last one queued, and for the copy of the rows that it left to the last one. (Sets of lists and halves
+    of the update's workspace are used again then.)"""
     batches = [RIDES if k == "r" else OWN for k in kinds]
-    script = [MODEL] + [["run", dict(it=i, batch=b, next=None if i + 1 == len(kinds) else (dict(n=sizes(20_000)) if k == "x" else batches[i + 1]))]
-                        for i, (k, b) in enumerate(zip(kinds, batches))]
+    script = [MODEL] + [["run", dict(it=i, batch=b, next=None if i + 1 == len(kinds) else (dict(n=sizes(20_000)) if k == "x" else batches[i + 1]),
+                                     update=int(k != "n"), commit=k == "c")] for i, (k, b) in enumerate(zip(kinds, batches))]
     _, *calls = record(tmp_path_factory.getbasetemp(), script)
     launches = behind(calls)
     for i, k in enumerate(kinds):
         rc, selected, next_pruned, begun, _ = calls[i]
         mine = [name for j, _, name, _ in launches if j == i]
-        assert rc == 0 and begun == 1 and next_pruned == (i + 1 < len(kinds))
+        assert rc == 0 and begun == 1 and next_pruned == (i + 1 < len(kinds) and k != "n")
         assert selected == (k != "r" and next_pruned)
         assert any("load_linear" in name for name in mine) == (k == "r")
     first = [min(n for n, x in enumerate(launches) if x[0] == i) for i in range(len(calls))] + [len(launches)]
     for n, (i, stream, name, before) in enumerate(launches):
+        if i and stream == MAIN:      # the lists, the index and the rows that the call before this one put on the second stream
+            needed = {m for m in range(first[i - 1], first[i]) if launches[m][1] == SIDE}
+            assert needed <= before, f"call {i}: {name} does not wait for {[launches[m][2] for m in sorted(needed - before)]} on the second stream"
         if i < 2:
             continue
         due = calls[i - 2][1] and "copy_rows" in launches[first[i - 1]][2]      # the first launch of the call before this one
