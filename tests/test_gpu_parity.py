@@ -2513,8 +2513,12 @@ def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, k
                 n = mbs[it].ids
                 if workload[:10] == "two chunks":
                     assert 4096 < len(n[1]) < 8192
-                if workload.endswith(" step"):      # (64 rows of layer 1 to a workgroup of the loader)
-                    assert (-(-len(n[1]) // 64) > 512) == (workload[:4] == "many")
+                if workload.endswith(" step"):      # layer 1 as one launch from 24576 positions on; its selection in either loader: up to 32 chunks of 4096
+                    assert (len(n[1]) >= 24576) == (workload[:4] == "many") and sum(-(-len(n[l]) // 4096) for l in range(1, L)) <= 32
+                    one = workload[:4] == "many" and col_ids and w.feat_dtype == "f32" and (hp.overlap_update or w.hidden > 64)
+                    assert hp.loads_and_multiplies(batches[it]) == one
+                    if hp is paths[0] and hp.overlap_update and it != 4 and it + 1 < K:      # what is left to the next call says where the selection was
+                        assert hp._td_for is not None and (hp._row_copy_due is None) == one
                 if workload.endswith("many chunks"):
                     groups = sum(-(-len(n[l]) // 4096) for l in range(1, L))
                     assert 32 < groups <= 64 if workload == "many chunks" else groups > 64

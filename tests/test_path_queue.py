@@ -60,7 +60,9 @@ def test_steps_of_both_kinds_in_any_order_follow_each_other(tmp_path_factory, ki
         assert any("load_linear" in name for name in mine) == (k == "r")
     first = [min(n for n, x in enumerate(launches) if x[0] == i) for i in range(len(calls))] + [len(launches)]
     for n, (i, stream, name, before) in enumerate(launches):
-        if i and stream == MAIN:      # the lists, the index and the rows that the call before this one put on the second stream
+        # the lists, the index and the rows that the call before this one put on the second stream (a caller's own copy in front of the call needs
+        # the index only)
+        if i and stream == MAIN and not (kinds[i] == "c" and n == first[i]):
             needed = {m for m in range(first[i - 1], first[i]) if launches[m][1] == SIDE}
             assert needed <= before, f"call {i}: {name} does not wait for {[launches[m][2] for m in sorted(needed - before)]} on the second stream"
         if i < 2:
@@ -148,3 +150,22 @@ def test_a_chosen_dense_kernel_leaves_the_selection_where_it_was(tmp_path_factor
     rc, selected, next_pruned, _, lines = calls[2]
     assert rc == 0 and selected == 1 and next_pruned == 1
     assert {x[1] for x in lines if x[0] == "launch" and "update_digit" in x[2]} == {str(SIDE)}
+
+
+@pytest.mark.parametrize("kernel,n1,n2,overlap,kwargs", [
+    ("loader_fetch_update", 4_096, 300, 0, {}), ("loader_fetch_update", 16_000, 5_000, 0, {}), ("update_group", 0, 0, 0, {}),
+    ("loader_fetch_update", 257_000, 300, 0, dict(dims=[32, 64, 64, 64])), ("update_digit", 261_000, 300, 0, dict(dims=[32, 64, 64, 64])),      # 64 chunks, 65
+    ("loader_fetch_update", 8_000, 300, 0, dict(feat="F16", compute="BF16", fuse_small_layers=0)),
+    ("update_group", 8_000, 300, 1, {}), ("update_digit", 24_000, 300, 1, {}),                                                  # beside, on the second stream
+    ("load_linear", 20_000, 300, 0, {}), ("load_linear", 126_000, 300, 1, {}), ("update_digit", 131_000, 300, 1, {}),                    # 32 chunks, 33
+])
+def test_which_launch_takes_a_steps_selection(tmp_path_factory, kernel, n1, n2, overlap, kwargs):
+    """Both loaders and the update's own launches, on both sides of the rule's lines; a launch that takes the selection along is the only one for it."""
+    big = [1 << 20, 1 << 19, 1 << 17, 1 << 10]
+    _, (rc, selected, _, _, lines) = record(tmp_path_factory.getbasetemp(), [["model", dict(dict(dims=DIMS, n_max=big), **kwargs)],
+                                                                            ["run", dict(it=0, batch=dict(n=[2 * n1, n1, n2, min(n2, 300)]), overlap=overlap)]])
+    updates = ("loader_fetch_update", "load_linear", "update_group_kernel", "update_digit")
+    took = [x[2] for x in lines if x[0] == "launch" and any(u in x[2] for u in updates)]
+    if kernel != "load_linear":      # (its launch may also come without a selection)
+        took = [k for k in took if "load_linear" not in k]
+    assert rc == 0 and took and all(kernel in k for k in took)
