@@ -859,8 +859,7 @@ typedef struct fg_path_call {
     int64_t due_iter;
     fg_update_layer_t* specs;     /* out: this iteration's selection (may be the array `due`) */
     int32_t selected;             /* out: 1 = its row copy is left to the next call (`due`) or to fg_cache_update_commit */
-    int32_t next_pruned;          /* out: 1 = the top-down pass of `next` is queued (`promised`); admitted rows may be on their way on P->side in front of
-                                     ev_next_pruned: who reads the cache's rows before the next call waits for that event */
+    int32_t next_pruned;          /* out: 1 = the top-down pass of `next` is queued (`promised`) */
     int32_t begun;                /* out: 1 = the wait for what was promised and the row copy of `due` are queued; 0 = the call was refused
                                      before them and they are still to be asked for */
 } fg_path_call_t;

@@ -475,6 +475,7 @@ extern "C" fg_status_t fg_cache_clear(fg_cache_t* cache, void* stream) {
         l.last_iter = INT64_MIN;
         l.copy_pending = false;
     }
+    cache->rows_iter = INT64_MIN;
     // an emptied ring has "written" nothing, so rows placed earlier would count as intact although embeddings
     // may have been written over them: the feature side is dropped with the embeddings
     if (cache->feat_rank && cache->n_feat > 0) {
@@ -814,6 +815,7 @@ void update_queued(int phase, fg_cache_t* cache, int64_t iter, int32_t n_layers,
         }
         l->copy_pending = phase == 1;
     }
+    if (n_layers > 0) cache->rows_iter = INT64_MIN;
 }
 
 // phase 0: the whole update; 1: selection and index only; 2: the row copy of a selection made by phase 1 with the same
@@ -825,8 +827,12 @@ fg_status_t update_all(const char* who, int phase, fg_cache_t* cache, int64_t it
     if (rc != FG_OK) return rc;
     fg_clear_error();
     if (n_layers == 0) return FG_OK;
-    rc = launch_update(B, (hipStream_t)stream, phase != 2, phase != 1);
-    if (rc != FG_OK) return rc;
+    if (phase == 2 && cache->rows_iter == iter) {
+        FG_HIP(hipStreamWaitEvent((hipStream_t)stream, (hipEvent_t)cache->rows_event, 0));
+    } else {
+        rc = launch_update(B, (hipStream_t)stream, phase != 2, phase != 1);
+        if (rc != FG_OK) return rc;
+    }
     update_queued(phase, cache, iter, n_layers, layers);
     return FG_OK;
 }
@@ -844,6 +850,11 @@ fg_status_t fg_update_describe(const char* who, const fg_update_call& c, UpdBatc
 void fg_update_queued(const fg_update_call& c) { update_queued(0, c.cache, c.iter, c.n_layers, c.layers); }
 void fg_update_selected(const fg_update_call& c) { update_queued(1, c.cache, c.iter, c.n_layers, c.layers); }
 void fg_update_committed(const fg_update_call& c) { update_queued(2, c.cache, c.iter, c.n_layers, c.layers); }
+void fg_update_rows_queued(const fg_update_call& c, void* event) {
+    c.cache->rows_iter = c.iter;
+    c.cache->rows_event = event;
+}
+bool fg_update_rows_are_queued(const fg_cache_t* cache, int64_t iter) { return cache && cache->rows_iter == iter; }
 
 extern "C" fg_status_t fg_cache_update_all(fg_cache_t* cache, int64_t iter, float p_grad, int32_t n_layers,
                                            const fg_update_layer_t* layers, void* ws_dev, size_t ws_bytes, void* stream) {

@@ -35,6 +35,9 @@ struct fg_cache {
     int32_t* feat_rank = nullptr;  // [num_nodes] rank of a node's row on the feature side or -1; allocated by the first fill
     int64_t n_feat = 0;            // feature rows placed (0: no feature side)
     int64_t feat_row_bytes = 0;
+    // host: the row copies of this iteration's pending update are queued already, in front of an event of the caller (fg_path_run)
+    int64_t rows_iter = INT64_MIN;
+    void* rows_event = nullptr;
 };
 
 constexpr int FG_MAX_RINGS = 8;       // cached layers a feature side can share its buffer with

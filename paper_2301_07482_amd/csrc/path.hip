@@ -180,7 +180,7 @@ struct Iter {
 
     // The selection has gone with the loader: the index is final for this iteration, and with a second stream the next mini-batch is looked up and pruned
     // there beside the layers above. (What that pass overwrites was last read two iterations ago, in front of the event recorded here. The layers above
-    // and the row copies of this iteration are not: an iteration that puts its selection on the second stream next records them, see fg_path_run.)
+    // and the row copies of this iteration are not: the next iteration records them if it puts its selection on the second stream, see fg_path_run.)
     // *due_from: first of the update's layers whose admitted rows are still to be copied. With a second stream layer 1, most of them, is copied there
     // as well, beside the layers above (in the seed layer's launch, whose workgroups take half a compute unit each, 16 k rows took 15 us more: large
     // step 181.3 us, 175.8 so; medium 180.1, 173.7; with the paper's thresholds 164.8, 159.9).
@@ -355,9 +355,14 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
         FG_HIP(hipEventRecord((hipEvent_t)P.ev_done[iter % 2], main));
         return FG_OK;
     };
+    bool rows_queued = false;
     if (call->due) {      // the rows the previous iteration admitted
+        rows_queued = call->promised && fg_update_rows_are_queued(call->cache, call->due_iter);
         if (!call->promised) FG_HIP(hipStreamWaitEvent(main, (hipEvent_t)P.ev_selected, 0));
-        FG_TRY(commit(call->due_iter, L - 1, call->due));
+        if (rows_queued)      // in front of the event just waited for
+            fg_update_committed({call->cache, call->due_iter, 0.f, L - 1, call->due, nullptr, 0});
+        else
+            FG_TRY(commit(call->due_iter, L - 1, call->due));
     }
     call->begun = 1;
     if (!call->pruned_ahead) FG_TRY(I.top_down(*batch, main));
@@ -379,13 +384,13 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
         if (!call->pruned_ahead) {
             FG_HIP(hipEventRecord((hipEvent_t)P.ev_pruned, main));
             FG_HIP(hipStreamWaitEvent(side, (hipEvent_t)P.ev_pruned, 0));
-        } else if (!call->due) {
-            // Iteration it - 1 announced this one and left no rows: its selection went with its loader. Its layers and row copies have recorded
-            // nothing; they are on this stream in front of here.
+        } else if (rows_queued || !call->due) {
+            // Iteration it - 1's selection went with its loader: its layers and row copies have recorded nothing. They are on this stream in front of
+            // here (as is a copy that the caller has queued).
             FG_HIP(hipEventRecord((hipEvent_t)P.ev_done[(call->iter + 1) % 2], main));
         }
         // What it overwrites (half it % 2 of the workspace, set (it + 1) % 3 of the lists) was last read by iteration it - 2 and its row copy. If that
-        // iteration's rows were left to it - 1, or it - 1 found that its selection had gone with its loader, it - 1 recorded this event behind them;
+        // iteration's rows were left to it - 1, it - 1 recorded this event behind their copy, or behind itself where they had been copied already;
         // else they are in front of a wait of this stream: ev_pruned, of it - 1 or of this iteration.
         FG_HIP(hipStreamWaitEvent(side, (hipEvent_t)P.ev_done[call->iter % 2], 0));
         I.update_specs(*batch, false, call->specs);
@@ -425,8 +430,12 @@ extern "C" fg_status_t fg_path_run(const fg_path_t* path, const fg_path_batch_t*
             Iter::due_copies(selection, due_from, &copies);
             FG_TRY(fg_launch_row_copies(copies, main));
         }
-        fg_update_committed(ride);
-        call->selected = 0;
+        if (call->next_pruned) {      // some of the copies are on the second stream
+            fg_update_rows_queued(ride, P.ev_next_pruned);
+        } else {
+            fg_update_committed(ride);
+            call->selected = 0;
+        }
         return FG_OK;
     }
     // A training iteration ends with its weight gradients and the cache update beside each other: in the same two launches where a group of

@@ -486,7 +486,10 @@ fg_status_t fg_update_describe(const char* who, const fg_update_call& call, UpdB
 void fg_update_row_copies(const UpdBatch& B, fg_row_copy_batch* copies);
 void fg_update_queued(const fg_update_call& call);      // both are queued: the cache's state moves on ...
 void fg_update_selected(const fg_update_call& call);    // ... or in two steps: the group is queued (until the other step the next update is refused)
-void fg_update_committed(const fg_update_call& call);   // ... and the row copies
+void fg_update_committed(const fg_update_call& call);   // ... and the row copies,
+// or they are queued, some of them on another stream: fg_cache_update_commit then waits for this event in their place
+void fg_update_rows_queued(const fg_update_call& call, void* event);
+bool fg_update_rows_are_queued(const fg_cache_t* cache, int64_t iter);
 // fg_backward_weights_all with an update that rides along (NULL: none)
 fg_status_t fg_backward_weights_with(fg_dtype_t compute_dtype, int32_t n_layers, const fg_weight_grad_layer_t* layers, void* ws_dev, size_t ws_bytes,
                                      const UpdBatch* update, void* stream);

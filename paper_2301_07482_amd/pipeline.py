@@ -524,10 +524,8 @@ class HotPath:
 
     def flush(self, selection_done=False, main=None):
         """Copy the rows admitted by the last iteration into the cache, if that is still due (`run` leaves it to the next
-        call when that call's top-down pass is already on the second stream), and wait for those that are on their way on that stream
-        (of a selection that went with the loader, in front of the event of that pass). Called by everything that reads the cache."""
-        if self._td_for is not None and not selection_done:
-            (torch.cuda.current_stream() if main is None else main).wait_event(self.ev_next_pruned)
+        call when that call's top-down pass is already on the second stream), or wait for them if they are being copied there
+        (those of a selection that went with the loader). Called by everything that reads the cache."""
         if self._row_copy_due is None:
             return
         it, specs = self._row_copy_due
@@ -692,7 +690,6 @@ class HotPath:
         self._td_for = None
         if promised:      # (also when the promise was not kept: that pass writes the lists this call is about to use)
             main.wait_event(self.ev_next_pruned)   # behind the previous selection on that stream
-        rode = pruned_ahead and self._row_copy_due is None      # iteration it - 1's selection went with its loader (`_run_native`)
         self.flush(selection_done=promised, main=main)
         if not pruned_ahead:
             self._top_down(bt, it, st, tick)
@@ -714,12 +711,10 @@ class HotPath:
             if not pruned_ahead or hold_second_stream:
                 self.ev_pruned.record(main)
                 side.wait_event(self.ev_pruned)
-            if rode:      # its layers and row copies, in front of here, have recorded nothing
-                self.ev_done[(it - 1) % 2].record(main)
             # What this selection and the top-down pass behind it overwrite (half it % 2 of the workspace, set (it + 1) % 3
-            # of the lists) was last read by iteration it - 2 and its row copy. If that iteration's rows were left to it - 1, or
-            # its selection had gone with its loader, it - 1 recorded this event behind them (the copy of iteration it - 1, just
-            # queued, recorded the other one); else they are in front of ev_pruned, recorded by it - 1 or here.
+            # of the lists) was last read by iteration it - 2 and its row copy. If that iteration's rows were left to it - 1, it - 1
+            # recorded this event behind their copy, or behind itself where they had been copied already (iteration it - 1's,
+            # just flushed, the other one); else they are in front of ev_pruned, recorded by it - 1 or here.
             side.wait_event(self.ev_done[it % 2])
             if self.admit_budget:
                 self._estimates(bt, side_st)

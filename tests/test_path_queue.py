@@ -56,19 +56,19 @@ def test_steps_of_both_kinds_in_any_order_follow_each_other(tmp_path_factory, ki
         rc, selected, next_pruned, begun, _ = calls[i]
         mine = [name for j, _, name, _ in launches if j == i]
         assert rc == 0 and begun == 1 and next_pruned == (i + 1 < len(kinds) and k != "n")
-        assert selected == (k != "r" and next_pruned)
+        assert selected == next_pruned
         assert any("load_linear" in name for name in mine) == (k == "r")
     first = [min(n for n, x in enumerate(launches) if x[0] == i) for i in range(len(calls))] + [len(launches)]
     for n, (i, stream, name, before) in enumerate(launches):
         # the lists, the index and the rows that the call before this one put on the second stream (a caller's own copy in front of the call needs
         # the index only)
-        if i and stream == MAIN and not (kinds[i] == "c" and n == first[i]):
+        if i and stream == MAIN and not (kinds[i] == "c" and n == first[i] and "copy_rows" in name):
             needed = {m for m in range(first[i - 1], first[i]) if launches[m][1] == SIDE}
             assert needed <= before, f"call {i}: {name} does not wait for {[launches[m][2] for m in sorted(needed - before)]} on the second stream"
         if i < 2:
             continue
-        due = calls[i - 2][1] and "copy_rows" in launches[first[i - 1]][2]      # the first launch of the call before this one
-        assert due == calls[i - 2][1]
+        due = calls[i - 2][1] and kinds[i - 2] != "r"      # (a riding step's rows are copied by its own launches)
+        assert due == ("copy_rows" in launches[first[i - 1]][2])      # the first launch of the call before this one
         needed = set(range(first[i - 1] + (1 if due else 0)))
         assert needed <= before, f"call {i}: {name} on stream {stream} does not wait for {[launches[m][2] for m in sorted(needed - before)]}"
 
@@ -99,7 +99,7 @@ def test_a_step_that_fails_behind_its_selection_leaves_its_rows_due(tmp_path_fac
     now, later = (dict(good, no_weights=3), good) if at == "no_weights" else (good, dict(good, no_ids=2))
     calls = record(tmp_path_factory.getbasetemp(), [MODEL, ["run", dict(it=0, batch=good, next=now, overlap=overlap)], ["run", dict(it=1, batch=now, next=later, overlap=overlap)],
                                                     ["run", dict(it=2, batch=good, overlap=overlap, forget=True)]])[1:]
-    assert [c[0] for c in calls[:1]] == [0] and calls[0][1] == 0
+    assert calls[0][:2] == [0, overlap]
     rc, selected, next_pruned, begun, lines = calls[1]
     assert str(rc)[:2] in ("1:", "2:") and selected == 1 and begun == 1
     launches = behind(calls)
@@ -169,3 +169,20 @@ def test_which_launch_takes_a_steps_selection(tmp_path_factory, kernel, n1, n2, 
     if kernel != "load_linear":      # (its launch may also come without a selection)
         took = [k for k in took if "load_linear" not in k]
     assert rc == 0 and took and all(kernel in k for k in took)
+
+
+@pytest.mark.parametrize("how", ["next call", "commit", "neither"])
+def test_rows_that_are_copied_on_the_second_stream_are_due_until_they_are_waited_for(tmp_path_factory, how):
+    """A step whose selection goes with the loader and that prunes the next mini-batch ahead copies layer 1's rows on the second stream. It says, as every
+    step that does so, that its rows are left to the next call or to fg_cache_update_commit: these wait for them."""
+    first, after = record(tmp_path_factory.getbasetemp(), [MODEL, ["run", dict(it=0, batch=RIDES, next=RIDES)],
+                                                           ["run", dict(it=1, batch=RIDES, commit=how == "commit", forget=how == "neither")]])[1:]
+    assert first[:3] == [0, 1, 1]
+    copied = max(i for i, x in enumerate(first[4]) if x[0] == "launch" and x[1] == str(SIDE))
+    assert "copy_rows" in first[4][copied][2] and first[4][copied + 1][:2] == ["record", str(SIDE)]
+    if how == "neither":
+        assert str(after[0]).startswith("4:")
+        return
+    assert after[0] == 0 and not any("copy_rows_batch" in x[2] for x in after[4][:4] if x[0] == "launch")
+    queued = [i for i, x in enumerate(after[4]) if x == ["wait", str(MAIN), first[4][copied + 1][2]]]
+    assert queued and queued[0] < min(i for i, x in enumerate(after[4]) if x[0] == "launch") and len(queued) == (2 if how == "commit" else 1)
