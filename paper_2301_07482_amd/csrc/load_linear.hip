@@ -92,6 +92,8 @@ struct LoadLinear {
 // fewer of (large step with 16 fewer 194.4 us, 193.7 with all); hence twice the positions of the update's own workgroups
 // (with 4096 of them large 182.4 us, medium 188.9). On a second stream the selection found no compute unit before this launch ended, and the next
 // step waited for it and the top-down pass behind it: large step 194.5 -> 179.3 us, with the paper's thresholds 178.4 -> 166.5, medium 182.7 -> 179.0.
+// W's split columns are 192 registers of a lane at KS 16. What is left does not hold the gather too: 6 vector registers are spilled (28 bytes of
+// scratch a lane), and since the selection is part of the kernel 29 scalar ones; KS 8 takes 208 registers and spills no vector register.
 // KS: steps of 16 of the contraction; SLOTS: rows of the table a block's row is given (its own and SLOTS - 1 neighbours; what is beyond is read in a
 // loop of its own); LP: lanes a table row takes.
 template <int KS, int SLOTS, int LP>

@@ -220,8 +220,9 @@ struct Iter {
         return bytes;
     }
 
-    // ride: an update whose selection may go with the loader; *rode: it has. Up to 4 MB of its rows go with a seed layer of one launch (27 MB
-    // of them on one stream: 195 us, 186 to 190 with a launch of their own).
+    // ride: an update whose selection may go with the loader; *rode: it has. Up to 4 MB of its rows go with a seed layer of one launch: on one stream
+    // 0.95 to 1.00 of the time with a launch of their own up to 0.5 MB, 0.99 to 1.00 up to 4, from 6 MB on level (quartiles of 1200 steps; 27 MB
+    // took 195 us in one of them, 186 to 190 with their own).
     fg_status_t forward(const fg_path_batch_t& b, bool once, const fg_fetch_layer_t* fetch, int n_fetch, const fg_update_call* ride, const UpdBatch* selection,
                         bool* rode, int* due_from) const {
         const int L = P.n_layers;

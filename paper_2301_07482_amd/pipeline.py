@@ -698,7 +698,8 @@ class HotPath:
         # With gradient norms given from outside nothing of the update but its row copy depends on the layers computed below:
         # threshold, check-outs, admissions and slots are decided now, on a second stream, beside the loader and the layers.
         # (Not with raw features in the cache's buffer: the loader reads the rings' written extents, which the selection
-        # advances. Copying the admitted rows over there too, beside the seed layer, measured slower than on this stream.)
+        # advances. The admitted rows are copied on this stream: over there, beside the seed layer, measured slower. Where
+        # `_run_native` has the selection in the loader's launch it copies layer 1's over there, sooner, which is faster.)
         early_select = None
 
         def second_stream():
@@ -901,8 +902,9 @@ class HotPath:
     def runs_in_one_call(self):
         """Whether an iteration without a timer is queued by one call (fg_path_run): every configuration but those kept for
         comparison (a call per layer), the access-aware admission and raw features in the cache's buffer. The results of the two ways are
-        the same; their schedules differ where the one call runs the selection of a step without a second stream inside the loader's launch and
-        copies its rows in the seed layer's, and at the end of a training iteration: the one call runs the update inside the weight gradients' two launches
+        the same; their schedules differ where the one call runs the selection of a step inside the loader's launch (without a second stream, or where
+        layer 1 is one launch), with the next top-down pass and layer 1's row copies behind it on the second stream and the others in the seed
+        layer's launch, and at the end of a training iteration: the one call runs the update inside the weight gradients' two launches
         (of more than 64 chunks of 4096 positions: beside them on the second stream, the longer of the two on the current one), the single
         calls on the current stream with the weight gradients on the second, and with a timer one behind the other, since a
         step that is bracketed by events of one stream cannot run beside another."""
