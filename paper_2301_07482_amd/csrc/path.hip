@@ -144,9 +144,11 @@ struct Iter {
 
     // Whether the loader and the dense update of layer 1 are one call: where nobody reads the means and the nodes' own rows later. (A training
     // iteration does; with both written from the one launch it took what the two take, 122 us against 121.)
-    // - Every row's neighbours have to have a slot (15 of them, 7 of rows of more than 64 values where there are no more than 7 on average): one by one behind
-    //   the slots they cost more than the launch saves. The layer by itself, 54 k rows x (128 + 128) x 256, two launches / one, us: 15 each 127 / 114,
-    //   8 or 20 122 / 140, 4 or 25 126 / 167, 7 each 90 / 76, 3 or 10 87 / 105; one row of 500 in 500 167 / 357.
+    // - A row's neighbours have to have a slot (15 of them, 7 of rows of more than 64 values where there are no more than 7 on average), but for two: those
+    //   behind the slots are read one by one. The layer by itself, 54 k rows x (128 + 128) x 256, two launches / one, us: 15 each 127 / 114,
+    //   8 or 20 122 / 140, 4 or 25 126 / 167, 7 each 90 / 76, 3 or 10 87 / 105; one row of 500 in 500 167 / 357. Steps of blocks with 14 neighbours on average or
+    //   fewer, by the most that a row has: 16 6 us faster in one launch, 18 3, 20 5 slower, 25 15 slower; with 7 or fewer on average 8 and 9 4 us
+    //   faster, 10 3 slower, 12 9 slower (means of 71 to 273 steps each).
     // - Rows of more than 32 values: half of the operand is padding below that. Step of 71 k positions x 32 x 64, 6 neighbours, 82 / 99; 80 k x 64 96 / 95.
     // - Beside a second stream from 24 Ki positions on: its workgroups fill the chip, so that work there waits for it, and the layers above have to be long
     //   enough to hide that. Steps of positions x columns, us: 20.5 k x 72 77 / 84.5, 24.6 k x 96 83 / 81, x 256 103 / 102, 31 k x 256 119 / 109, 45 k x 96 125 / 117.
@@ -156,8 +158,8 @@ struct Iter {
     //   most of its wavefronts without a product, nor for rows of at most 64 values with most positions admitted (their copies are a launch behind it). Of 2374
     //   steps it is faster by 3.8 us on average, with the two exceptions by 5.2, and by more than 5 % the slower one in 16.
     bool loads_and_multiplies(const fg_path_batch_t& b, int l) const {
-        const int64_t n = b.layer[1].n, nnz = b.layer[1].nnz, most = b.own_rows_from_table, slots = P.dims[0] > 64 && nnz <= 7 * n ? 7 : 15;
-        if (l != 1 || !P.fused_input || b.reads_rows_once || !b.col_ids1_dev || most < 2 || most > slots) return false;
+        const int64_t n = b.layer[1].n, nnz = b.layer[1].nnz, most = b.own_rows_from_table, places = P.dims[0] > 64 && nnz <= 7 * n ? 7 : 15;
+        if (l != 1 || !P.fused_input || b.reads_rows_once || !b.col_ids1_dev || most < 2 || most > places + 2) return false;
         if (h_code(0) != FG_F32 || h_code(1) != FG_F32 || P.compute_dtype != FG_F32 || P.dims[0] <= 32) return false;
         if (C.overlap ? n < 24576 : P.dims[1] <= 64 || (P.dims[0] <= 64 && C.p_grad > 0.5f)) return false;
         return fg_tuning(FG_TUNE_LINEAR_TILE) == 0 && fg_one_launch_load(nnz, n, P.dims[0], P.dims[1]) != 0;

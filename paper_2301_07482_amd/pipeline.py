@@ -933,7 +933,7 @@ class HotPath:
     def loads_and_multiplies(self, bt):
         """Whether the loader and the dense update of layer 1 of this mini-batch are one call and one launch of it (path.hip has the reasons)."""
         n, nnz, d_in, d_out = bt.n[1], bt.nnz[1], self.dims[0], self.dims[1]
-        if not self.own_rows_from_table(bt) or self.h_code[1] != B.FG_F32 or d_in <= 32 or self.most_neighbours > (7 if d_in > 64 and nnz <= 7 * n else 15):
+        if not self.own_rows_from_table(bt) or self.h_code[1] != B.FG_F32 or d_in <= 32 or self.most_neighbours > (9 if d_in > 64 and nnz <= 7 * n else 17):
             return False
         if n < 24576 if self.overlap_update else d_out <= 64 or (d_in <= 64 and self.p_grad > 0.5):
             return False

@@ -121,8 +121,8 @@ def test_rows_of_a_step_that_fails_can_be_committed(tmp_path_factory, n1, overla
 
 
 @pytest.mark.parametrize("one,d_in,d_out,most,nnz,n,overlap,p_grad", [
-    (1, 128, 256, 15, 13, 25_000, 1, 0.3), (0, 128, 256, 16, 13, 25_000, 1, 0.3), (0, 128, 256, 1, 1, 25_000, 1, 0.3),      # what the rows have at most
-    (1, 128, 256, 8, 8, 25_000, 1, 0.3), (0, 128, 256, 8, 7, 25_000, 1, 0.3), (1, 128, 256, 7, 7, 25_000, 1, 0.3),          # places of a row
+    (1, 128, 256, 17, 13, 25_000, 1, 0.3), (0, 128, 256, 18, 13, 25_000, 1, 0.3), (0, 128, 256, 1, 1, 25_000, 1, 0.3),      # what the rows have at most
+    (1, 128, 256, 10, 8, 25_000, 1, 0.3), (0, 128, 256, 10, 7, 25_000, 1, 0.3), (1, 128, 256, 9, 7, 25_000, 1, 0.3),        # places of a row
     (1, 64, 128, 15, 7, 25_000, 1, 0.3), (0, 68, 128, 15, 7, 25_000, 1, 0.3),
     (1, 36, 64, 15, 13, 25_000, 1, 0.7), (0, 32, 64, 15, 13, 25_000, 1, 0.3),                                               # narrow rows
     (1, 128, 256, 15, 13, 24_576, 1, 0.3), (0, 128, 256, 15, 13, 24_575, 1, 0.3),                                           # two streams
