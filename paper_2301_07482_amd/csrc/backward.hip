@@ -1067,8 +1067,9 @@ __device__ __forceinline__ void weight_grad_tile(const WgIn& A, const int unit) 
 // of a small training iteration, and on a second stream it cost two waits for events (5 us each), its row copy (28 us beside the products, 9
 // by itself) taking memory time from the products. Its workgroups come first: they are the longer chain where there are few rows, and wait
 // for each other. A compute unit holds one workgroup of either kind, so a chunk of positions is 512 threads with twice the positions of
-// the update's own launch. Training iteration, own launches / here, us: 1.5 k positions 70.5 / 62.0, 28 k 168.5 / 150.0, 74 k 380 / 355, GCN 317 / 293,
-// mixed 288 / 278; the loop with a sampler beside it 410 / 411.
+// the update's own launch. Training iteration, own launches / here, us: 1.5 k positions 70.5 / 62.0, 28 k 168.5 / 150.0, 74 k 369 / 356 (runs of one side
+// 1 to 5 % apart), GCN 320 / 293, mixed 288.5 / 279; the loop with a sampler beside it 410 / 411. 1433 iterations of random sizes, fp32, GCN and mixed: 0.87 of
+// the time on average, none slower.
 template <int TERMS, int SRC>
 __global__ __launch_bounds__(WG_THREADS, 2) void weight_grad_kernel(WgBatch B, UpdBatch U) {
     const int beside = U.n_layers ? U.sel_first[U.n_layers] : 0, block = (int)blockIdx.x - beside;
@@ -1317,7 +1318,7 @@ fg_status_t wg_launch(WgIn* in, const WgPlan* p, int n, bool mixed, char* ws, hi
     if (update) fg_update_row_copies(U, &copies);
     if (B.red_first[n] == 0) return fg_launch_row_copies(copies, st);
     // Two workgroups per compute unit and layer copy rows, so that those that add run beside them: with as many as a launch of copies
-    // has (2048) they come one after the other (large training iteration 365 us, 361 so; GCN 295, 291.5; 28 k positions 150.5, 148.5), and with
+    // has (2048) they come one after the other (28 k positions 150.5 us, 148.5 so; GCN 295, 291.5, large 365, 361, within what their runs differ by), and with
     // one the launch takes longer (23.4 us, 19.3 so)
     const int row_blocks = update ? fg_row_copy_blocks(copies) : 0, copy_blocks = row_blocks < 512 ? row_blocks : 512;
     if (copy_blocks == 0) copies.n = 0;

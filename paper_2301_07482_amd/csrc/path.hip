@@ -156,7 +156,7 @@ struct Iter {
     //   than 5 % the slower one in 140.
     // - On one stream the selection rides with either loader, and what is left is what the layer saves: not where 64 columns or fewer leave
     //   most of its wavefronts without a product, nor for rows of at most 64 values with most positions admitted (their copies are a launch behind it). Of 2374
-    //   steps it is faster by 3.8 us on average, with the two exceptions by 5.2, and by more than 5 % the slower one in 16.
+    //   steps it is faster by 3.5 us on average, with the two exceptions by 5.2, and by more than 5 % the slower one in 16.
     bool loads_and_multiplies(const fg_path_batch_t& b, int l) const {
         const int64_t n = b.layer[1].n, nnz = b.layer[1].nnz, most = b.own_rows_from_table, places = P.dims[0] > 64 && nnz <= 7 * n ? 7 : 15;
         if (l != 1 || !P.fused_input || b.reads_rows_once || !b.col_ids1_dev || most < 2 || most > places + 2) return false;
