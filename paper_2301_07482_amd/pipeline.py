@@ -628,15 +628,28 @@ class HotPath:
             self.flush(main=main)
         due = self._row_copy_due
         call.due_iter, call.due = due if due is not None else (0, None)
+        failed = True
         try:
             B.fg_path_run(P, now, later if ahead else None, call)
+            failed = False
         finally:
             if call.begun:      # (a call that was refused before has queued nothing: both are still due)
                 self._row_copy_due = self._td_for = None
             if call.next_pruned:
                 self._td_for = (it + 1, next_bt)
+            if failed and call.selected:
+                self._forget_failed(call, main)
         if call.selected:
             self._row_copy_due = (it, specs)
+
+    def _forget_failed(self, call, main):
+        """A call has failed behind its selection: the index names rows that may never have been computed. The cache starts anew, so that the iteration can
+        be run again (a step that selects behind its layers would have left it as it was)."""
+        main.wait_event(self.ev_selected)
+        if call.next_pruned:      # that pass found rows of this cache
+            main.wait_event(self.ev_next_pruned)
+            self._td_for = (None, None)
+        B.fg_cache_clear(self.cache, main.cuda_stream)
 
     def _bind(self, it):
         """Point the per-iteration state (lists of the top-down pass, counters, statistics) at iteration `it`'s copies."""

@@ -2548,6 +2548,46 @@ def test_iteration_as_one_call_is_the_iteration_of_single_calls(env, workload, k
             hp.close()
 
 
+@pytest.mark.parametrize("rides,kwargs", [(True, dict(overlap_update=False)), (True, dict()), (False, dict())])
+def test_a_failed_step_can_be_run_again(env, rides, kwargs):
+    """A step whose seed layer is refused when its selection is queued already, with the loader or on the second stream: with the weights put right, it and
+    the steps behind it are those of a model whose cache is empty."""
+    torch, B = env
+    import dataclasses
+    from paper_2301_07482_amd.pipeline import DeviceBatch
+    w = dataclasses.replace(wl.WORKLOADS["tiny"], num_nodes=90_000, num_edges=1_800_000, feat_dim=52, hidden=96, fanouts=(3, 2, 8), batch=4501 if rides else 900,
+                            cache_capacity=20_000)
+    g = wl.make_graph(w)
+    L = w.num_layers
+    paths = [G.make_hotpath(w, fused_input=True, fuse_small_layers=True, **kwargs)[0] for _ in range(2)]
+    hp, ref = paths
+    try:
+        mbs = [wl.minibatch(w, g, it) for it in range(6)]
+        make = lambda it: DeviceBatch(mbs[it], {l: wl.grad_norms(w, it, l, mbs[it].ids[l]) for l in range(1, L)}, col_ids=True)
+        torch.cuda.synchronize()
+        ahead = make(1)
+        hp.run(make(0), 0, next_bt=ahead)
+        good, hp.W[L] = hp.W[L], None
+        with pytest.raises(B.FgError):
+            hp.run(ahead, 1, next_bt=make(2))
+        hp.W[L] = good
+        outs = []
+        for p in paths:
+            out = []
+            for it in range(1, 6):
+                p.run(make(it), it)
+                out += [p.H[l][:len(mbs[it].ids[l])].clone() for l in range(1, L + 1)] + [p.counts.clone(), p.stats.clone()]
+            for l in range(1, L):
+                e = p.export_cache(l, 6)
+                out += [torch.as_tensor(np.asarray(e[k])) for k in ("nodes", "slots", "stamps")] + [torch.from_numpy(p.cache_rows(l, e["slots"]))]
+            outs.append(out)
+        for i, (a, b) in enumerate(zip(*outs)):
+            assert torch.equal(a, b), f"record {i} of {len(outs[0])}"
+    finally:
+        for p in paths:
+            p.close()
+
+
 @pytest.mark.parametrize("kwargs", [dict(fused_input=True), dict(fused_input=True, backward=True, weight_grads=True),
                                     dict(backward=True, weight_grads=True, model="gcn")])
 def test_iteration_as_one_call_uses_the_tensors_that_are_there(env, kwargs):
